@@ -10,6 +10,7 @@
 #include <numeric>
 #include <unordered_map>
 
+#include "chain_plan.h"
 #include "internal.h"
 
 namespace tictac {
@@ -32,6 +33,72 @@ void set_error(const char *fmt, ...)
             return TICTAC_ERR_HIP;                                                           \
         }                                                                                    \
     } while (0)
+
+// Device memory of the handles.  A program that takes in one graph after another allocates and frees blocks of the
+// same sizes all the time, and hipMalloc and hipFree cost tens of microseconds each, large blocks much more.  Freed
+// blocks are therefore kept, up to kPoolMax bytes per process (the oldest go first), and given back to the runtime when
+// an allocation fails.  A block is freed only after the device has finished what was queued (as hipFree does), so the
+// next owner may use it on any stream.
+constexpr size_t kPoolMax = (size_t)1 << 30;
+struct PoolBlock { void *p; size_t bytes; int device; };
+static std::mutex g_pool_mutex;
+static std::vector<PoolBlock> g_pool;               // oldest first
+static size_t g_pool_bytes = 0;
+
+// sizes in steps of an eighth, so that blocks of nearly equal requests serve each other
+static size_t pool_size(size_t bytes)
+{
+    size_t step = 4096;
+    while (step * 16 < bytes) step *= 2;
+    return (bytes + step - 1) / step * step;
+}
+
+static hipError_t pool_alloc(void **p, size_t bytes)
+{
+    *p = nullptr;
+    const size_t want = pool_size(bytes);
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    {
+        std::lock_guard<std::mutex> lock(g_pool_mutex);
+        for (size_t i = g_pool.size(); i-- > 0;)
+            if (g_pool[i].bytes == want && g_pool[i].device == device) {
+                *p = g_pool[i].p;
+                g_pool_bytes -= want;
+                g_pool.erase(g_pool.begin() + i);
+                return hipSuccess;
+            }
+    }
+    e = hipMalloc(p, want);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    {
+        std::lock_guard<std::mutex> lock(g_pool_mutex);
+        for (const PoolBlock &b : g_pool) (void)hipFree(b.p);
+        g_pool.clear();
+        g_pool_bytes = 0;
+    }
+    return hipMalloc(p, want);
+}
+
+// (the device has finished with the block)
+static void pool_put(void *p, size_t bytes, int device)
+{
+    if (!p) return;
+    const size_t want = pool_size(bytes);
+    if (want > kPoolMax) { (void)hipFree(p); return; }
+    std::vector<void *> out;
+    {
+        std::lock_guard<std::mutex> lock(g_pool_mutex);
+        g_pool.push_back({p, want, device});
+        g_pool_bytes += want;
+        size_t n = 0;
+        while (g_pool_bytes > kPoolMax) { g_pool_bytes -= g_pool[n].bytes; out.push_back(g_pool[n++].p); }
+        g_pool.erase(g_pool.begin(), g_pool.begin() + n);
+    }
+    for (void *q : out) (void)hipFree(q);
+}
 
 // Pinned host memory for the transfers of tictac_build_deps: one block per calling thread,
 // grown on demand and kept until the thread's next larger request (pinning costs milliseconds,
@@ -69,7 +136,7 @@ struct Packer {
     std::vector<char> host;
     struct Fix { void **dst; size_t off; };
     std::vector<Fix> fixes;
-    size_t device_only = 0;
+    size_t device_only = 0, bytes = 0;              // bytes: of the block, after commit()
 
     static size_t align(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -97,8 +164,9 @@ struct Packer {
         *block = nullptr;
         const size_t total = align(host.size()) + device_only;
         if (!total) return hipSuccess;
-        hipError_t e = hipMalloc(block, total);
+        hipError_t e = pool_alloc(block, total);
         if (e != hipSuccess) return e;
+        bytes = total;
         for (const Fix &f : fixes) *f.dst = static_cast<char *>(*block) + f.off;
         if (host.empty()) return hipSuccess;
         const void *src = host.data();
@@ -165,13 +233,14 @@ hipError_t ensure_workspace(Dag *d, size_t bytes)
 {
     if (bytes <= d->work_bytes) return hipSuccess;
     if (d->d_work) {
-        hipError_t e = hipFree(d->d_work);   // synchronises: earlier users of the old block are done
+        hipError_t e = hipDeviceSynchronize();   // earlier users of the old block are done
+        if (e != hipSuccess) return e;
+        pool_put(d->d_work, d->work_bytes, d->device);
         d->d_work = nullptr;
         d->work_bytes = 0;
-        if (e != hipSuccess) return e;
     }
-    size_t want = bytes + bytes / 8;
-    hipError_t e = hipMalloc(&d->d_work, want);
+    const size_t want = bytes + bytes / 8;
+    const hipError_t e = pool_alloc(&d->d_work, want);
     if (e != hipSuccess) return e;
     d->work_bytes = want;
     return hipSuccess;
@@ -187,7 +256,7 @@ static hipError_t ensure_chan_table(Dag *d, const int32_t *chan, hipStream_t s)
         return hipSuccess;
     hipError_t e;
     if (!d->d_chan) {
-        e = hipMalloc((void **)&d->d_chan, bytes);
+        e = pool_alloc((void **)&d->d_chan, bytes);
         if (e != hipSuccess) return e;
     }
     e = hipStreamSynchronize(s);
@@ -202,9 +271,20 @@ static hipError_t ensure_chan_table(Dag *d, const int32_t *chan, hipStream_t s)
 static void free_dag(Dag *d)
 {
     if (!d) return;
-    void *ptrs[] = {d->d_graph_block, d->d_class_block, d->d_work, d->d_chan, d->d_send_block};
-    for (void *p : ptrs)
-        if (p) (void)hipFree(p);
+    int device = 0;
+    const bool other = hipGetDevice(&device) == hipSuccess && device != d->device;
+    if (other) (void)hipSetDevice(d->device);
+    // (whatever still runs on the blocks is waited for, on any stream; only then may another handle take them)
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
+    const struct { void *p; size_t bytes; } blocks[] = {
+        {d->d_graph_block, d->graph_bytes}, {d->d_class_block, d->class_bytes}, {d->d_work, d->work_bytes},
+        {d->d_chan, (size_t)d->R * sizeof(int32_t)}, {d->d_send_block, d->send_bytes}, {d->chain.block, d->chain.bytes}};
+    for (const auto &b : blocks) {
+        if (!b.p) continue;
+        if (idle) pool_put(b.p, b.bytes, d->device);
+        else (void)hipFree(b.p);
+    }
+    if (other) (void)hipSetDevice(device);
     delete d;
 }
 
@@ -730,6 +810,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     // (sized for the copy back of the rows as well, so that the block is not replaced while a copy is under way)
     (void)stage(std::max(graph.host.size(), dep_words * 8));
     HIP_TRY(graph.commit(&d->d_graph_block, s));
+    d->graph_bytes = graph.bytes;
     HIP_TRY(hipMemsetAsync(d->d_bad_order, 0, 256, s));
     if (dep_words) HIP_TRY(launch_propagate(*d, s));
 
@@ -858,6 +939,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     for (int32_t c = 0; c < d->C; ++c)
         for (int32_t m = cls_ptr[c]; m < cls_ptr[c + 1]; ++m) col_cls[cls_cols[m]] = c;
     cls.add(&d->d_col_cls, col_cls);
+    if (!on_device && d->C <= 512 + kChainMaxGates) { d->h_cls_dep = cls_dep; d->h_col_cls = col_cls; }
 
     // ---- tables of the bit-sliced TAC kernel (see internal.h), for graphs with many classes ----
     const int32_t CW = (d->C + 63) / 64;
@@ -948,6 +1030,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         cls.reserve(&d->d_cls_depT, (size_t)d->W * d->Cpad * 8);
     }
     HIP_TRY(cls.commit(&d->d_class_block, s));
+    d->class_bytes = cls.bytes;
     int32_t *mismatch = d->d_bad_order + 1;         // (a second word of the zeroed flag block)
     if (on_device) HIP_TRY(launch_class_rows(*d, d->d_op_of_col, d->d_cls_first_op, mismatch, s));
     if (want_sliced) HIP_TRY(launch_sliced_tables(*d, s));
@@ -962,10 +1045,79 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     };
     int rc = classes(dep_words * 8 >= ((size_t)8 << 20) && d->N > 0 && !getenv("TICTAC_GROUP_ON_HOST"));
     if (rc == 1) {
-        if (d->d_class_block) { HIP_TRY(hipStreamSynchronize(s)); (void)hipFree(d->d_class_block); d->d_class_block = nullptr; }
+        if (d->d_class_block) {
+            HIP_TRY(hipStreamSynchronize(s));
+            pool_put(d->d_class_block, d->class_bytes, d->device);
+            d->d_class_block = nullptr;
+        }
         rc = classes(false);
     }
     return rc;
+}
+
+hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
+{
+    ChainTables &c = d->chain;
+    if (c.tried) return hipSuccess;
+    c.tried = true;
+    const int32_t n = d->n, N = d->N, R = d->R, W = d->W;
+    if (d->h_cls_dep.empty() || R < 1) return hipSuccess;
+    // pieces of one set (classes with equal rows) are one set again: they follow each other
+    std::vector<const uint64_t *> rows;
+    std::vector<int32_t> row_of_set, set_of_cls(d->C), set_of_col(N);
+    for (int32_t k = 0; k < d->C; ++k) {
+        const uint64_t *row = &d->h_cls_dep[(size_t)k * W];
+        if (rows.empty() || memcmp(rows.back(), row, (size_t)W * 8) != 0) {
+            rows.push_back(row);
+            row_of_set.push_back(k);
+        }
+        set_of_cls[k] = (int32_t)rows.size() - 1;
+    }
+    for (int32_t j = 0; j < N; ++j) set_of_col[j] = set_of_cls[d->h_col_cls[j]];
+    std::vector<int32_t> recv_of_op(n, -1), col_of_op(n, -1), in_ptr(1, 0), in;
+    for (int32_t i = 0; i < R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
+    for (int32_t v = 0, j = 0; v < n; ++v)
+        if (recv_of_op[v] < 0) col_of_op[v] = j++;
+    in.reserve(d->E);
+    for (int32_t v = 0; v < n; ++v) {
+        if (recv_of_op[v] >= 0) continue;
+        for (int32_t e = d->h_row_ptr[v]; e < d->h_row_ptr[v + 1]; ++e) {
+            const int32_t u = d->h_col_idx[e];
+            in.push_back(recv_of_op[u] >= 0 ? ~recv_of_op[u] : col_of_op[u]);
+        }
+        in_ptr.push_back((int32_t)in.size());
+    }
+    ChainPlan p;
+    make_chain_plan(R, W, N, (int)rows.size(), rows.data(), row_of_set.data(), set_of_col.data(), in_ptr, in, set_of_col, p);
+    if (!p.ok) return hipSuccess;
+    static_assert(sizeof(ChainRec) == 16 && sizeof(ChainGate) == 16, "records are read as 16 bytes");
+    Packer t;
+    ChainRec *rec = nullptr;
+    ChainGate *gate = nullptr;
+    t.add(&rec, p.rec);
+    t.add(&gate, p.gate);
+    t.add(&c.d_list, p.list);
+    t.add(&c.d_place, p.place);
+    t.add(&c.d_extra, p.extra);
+    t.add(&c.d_several, p.several);
+    t.add(&c.d_head, p.head);
+    t.add(&c.d_cand_ptr, p.cand_ptr);
+    t.add(&c.d_cand, p.cand);
+    t.add(&c.d_flush, p.flush);
+    t.add(&c.d_flush_row, p.flush_row);
+    t.add(&c.d_block_first, p.block_first);
+    hipError_t e = t.commit(&c.block, s);
+    if (e != hipSuccess) return e;
+    c.bytes = t.bytes;
+    e = hipStreamSynchronize(s);                    // the copy came out of `t` or of the staging block
+    if (e != hipSuccess) return e;
+    c.d_rec = reinterpret_cast<int4 *>(rec);
+    c.d_gate = reinterpret_cast<int4 *>(gate);
+    c.n_chains = p.n_slots; c.n_totals = p.n_totals; c.n_gates = (int32_t)p.gate.size(); c.n_list = (int32_t)p.list.size();
+    c.start = p.start; c.n_start = p.n_start; c.n_several = (int32_t)p.several.size(); c.empty = p.empty;
+    c.n_extra = p.n_extra; c.n_pairs = p.n_pairs; c.n_head = (int32_t)p.head.size();
+    c.ok = true;
+    return hipSuccess;
 }
 
 }  // namespace tictac
@@ -1342,8 +1494,9 @@ static int ensure_send_tables(Dag *d, int32_t n_send, const int32_t *send_ids, h
     d->n_send_free = (int32_t)send_free.size();
     d->send_tables_built = false;
     HIP_TRY(hipStreamSynchronize(s));               // no kernel reads the old tables any more
-    if (d->d_send_block) { (void)hipFree(d->d_send_block); d->d_send_block = nullptr; }
+    if (d->d_send_block) { pool_put(d->d_send_block, d->send_bytes, d->device); d->d_send_block = nullptr; }
     HIP_TRY(tables.commit(&d->d_send_block, s));
+    d->send_bytes = tables.bytes;
     HIP_TRY(hipStreamSynchronize(s));               // the copy came out of `tables`, which ends here
     d->h_send_ids.assign(send_ids, send_ids + n_send);
     d->send_tables_built = true;

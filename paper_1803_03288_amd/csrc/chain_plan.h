@@ -1,0 +1,290 @@
+// Plan of the chain form of TAC (k3_tac_chain.hip): which graphs have it, and its tables.  Host code only.
+//
+// On model-shaped graphs every recv is introduced by one class of compute ops: with U(c) the union of the dep sets
+// of the classes that feed class c, dep(c) \ U(c) is one recv, which c *owns*, or nothing (c joins branches).  When
+// every recv has an owner c(r), a recv has P > 0 from the moment pre(r) = U(c(r)) has been transferred ("ready"):
+// Q is the set of ready recvs, never empty while recvs are outstanding, and selection is a walk through the partial
+// order r' < r iff r' is in pre(r).  (No class can point at a recv other than its own: the first one to do so would
+// have had its own recv taken before that recv was ready.)  P of a ready recv is the time of its own class, plus the
+// times of the joins of which it is the last recv outstanding.
+//
+//   direct predecessors of r ("sinks" of pre(r)): the recvs of pre(r) that are in pre of no other recv of pre(r);
+//   gate: a set of two or more sinks after which something starts.  It counts its sinks: at zero its successors are
+//     ready, at one its join (if it has one) points at the sink that is left;
+//   chain: the recvs are covered by chains of the partial order; ready recvs are pairwise incomparable, so there is
+//     at most one per chain, which is the slot it is kept in.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+#include <vector>
+
+namespace tictac {
+
+constexpr int kChainMaxChains = 8;      // slots of ready recvs in registers
+constexpr int kChainAhead = 4;          // how far ahead on its chain the kernel requests the values of a recv
+constexpr int kChainMaxGates = 40;      // one LDS word per lane each
+constexpr int kChainBlock = 256;        // columns of op_time per block of the class totals
+
+struct ChainRec {                       // per recv, 16 bytes
+    int16_t next;                       // the recv that is ready once this one is taken, in the same slot; -1 none
+    int16_t gate0, gate1;               // gates of which it is a sink; -1 none
+    int16_t more, n_more;               // further recvs that are ready once it is taken: list[more .. more + n_more)
+    int16_t slot;                       // its chain
+    int16_t total;                      // its class total
+    int16_t ahead;                      // the recv kChainAhead places further on its chain; -1 none
+};
+
+struct ChainGate {                      // 16 bytes
+    int32_t fan_in;                     // number of sinks << 16 | xor of the sinks
+    int16_t join;                       // class total of its join; -1 none
+    int16_t first, n;                   // successors: list[first .. first + n)
+    int16_t unused[3];
+};
+
+struct ChainPlan {
+    bool ok = false;
+    int n_slots = 0;                    // chains
+    int n_totals = 0;                   // rows of class totals; a set with several runs of columns has as many, consecutive
+    int32_t empty = -1;                 // total of the ops that depend on no recv
+    std::vector<ChainRec> rec;          // [R]
+    std::vector<ChainGate> gate;
+    std::vector<int16_t> list;          // recvs: the lists above, then those ready at the start at list[start ..)
+    int32_t start = 0, n_start = 0;
+    std::vector<int16_t> place;         // [R] place of a recv on its chain
+    std::vector<int32_t> head;          // the first kChainAhead recvs of every chain: recv | total << 16
+    std::vector<int16_t> extra;         // [R] 1-based number among the recvs with a second gate or a list, 0 for the others
+    int n_extra = 0;
+    // totals in more than one row, as first row | number of rows << 16: first those in two rows (n_pairs of them)
+    std::vector<int32_t> several;
+    int n_pairs = 0;
+    // classes that can attain M+ of a ready recv r: cand[cand_ptr[r] .. cand_ptr[r + 1]), as rows of cls_dep
+    std::vector<int32_t> cand_ptr, cand;
+    // op_time columns, block by block of kChainBlock: a bit per column after which a row of the totals is complete
+    // (sixteen columns per word), those rows in that order, and where a block starts among them
+    std::vector<uint32_t> flush;
+    std::vector<int32_t> flush_row, block_first;
+};
+
+// rows [D][W]: the distinct dep sets of the compute ops, in order of first member;  set_of_col [N];  row_of_set [D]: a
+// row of cls_dep that holds the set.
+// nodes: inputs of node k in node_in[node_in_ptr[k] .. node_in_ptr[k + 1]) (~i for recv i, else a node), node_set[k]: the
+// set its op belongs to.
+inline void make_chain_plan(int R, int W, int N, int D, const uint64_t *const *rows, const int32_t *row_of_set,
+                            const int32_t *set_of_col, const std::vector<int32_t> &node_in_ptr,
+                            const std::vector<int32_t> &node_in, const std::vector<int32_t> &node_set, ChainPlan &p)
+{
+    p.ok = false;
+    if (R < 1 || R > 512 || D < R || D > R + kChainMaxGates + 1) return;
+    const size_t w8 = (size_t)W;
+    std::vector<uint64_t> U((size_t)D * w8, 0);
+    std::vector<int32_t> edge_from, edge_into, last(D, -1);
+    for (size_t k = 0; k < node_set.size(); ++k) {
+        const int c = node_set[k];
+        for (int32_t e = node_in_ptr[k]; e < node_in_ptr[k + 1]; ++e) {
+            const int32_t x = node_in[e];
+            if (x < 0) continue;
+            const int u = node_set[x];
+            if (u == c || last[u] == c) continue;       // (nodes of one set tend to follow each other)
+            last[u] = c;
+            for (int w = 0; w < W; ++w) U[c * w8 + w] |= rows[u][w];
+            edge_from.push_back(u);
+            edge_into.push_back(c);
+        }
+    }
+    std::vector<int32_t> par_ptr(D + 1, 0), par(edge_from.size());
+    for (int32_t c : edge_into) ++par_ptr[c + 1];
+    for (int c = 0; c < D; ++c) par_ptr[c + 1] += par_ptr[c];
+    {
+        std::vector<int32_t> fill(par_ptr.begin(), par_ptr.end() - 1);
+        for (size_t e = 0; e < edge_from.size(); ++e) par[fill[edge_into[e]]++] = edge_from[e];
+    }
+    // owners and joins
+    std::vector<int32_t> own(D, -1), owner(R, -1), count(D, 0);
+    int empty_set = -1;
+    for (int c = 0; c < D; ++c) {
+        int fresh = 0, r = -1;
+        for (int w = 0; w < W; ++w) {
+            count[c] += __builtin_popcountll(rows[c][w]);
+            const uint64_t x = rows[c][w] & ~U[c * w8 + w];
+            fresh += __builtin_popcountll(x);
+            if (x) r = w * 64 + __builtin_ctzll(x);
+        }
+        if (count[c] == 0) { empty_set = c; continue; }
+        if (fresh > 1) return;
+        if (fresh == 1) {
+            if (owner[r] >= 0) return;
+            owner[r] = c;
+            own[c] = r;
+        }
+    }
+    for (int r = 0; r < R; ++r)
+        if (owner[r] < 0) return;
+    // sinks, smaller sets first
+    std::vector<int32_t> by_count(D);
+    for (int c = 0; c < D; ++c) by_count[c] = c;
+    std::sort(by_count.begin(), by_count.end(), [&](int a, int b) { return count[a] != count[b] ? count[a] < count[b] : a < b; });
+    std::vector<std::vector<int32_t>> sinks(D);
+    std::vector<uint64_t> cand(w8), covered(w8);
+    for (int c : by_count) {
+        if (count[c] == 0) continue;
+        std::fill(cand.begin(), cand.end(), 0);
+        std::fill(covered.begin(), covered.end(), 0);
+        auto take = [&](int r) {
+            cand[r >> 6] |= 1ull << (r & 63);
+            for (int w = 0; w < W; ++w) covered[w] |= U[owner[r] * w8 + w];
+        };
+        for (int32_t e = par_ptr[c]; e < par_ptr[c + 1]; ++e) {
+            const int u = par[e];
+            if (count[u] == 0) continue;
+            if (own[u] >= 0) take(own[u]);
+            else for (int r : sinks[u]) take(r);
+        }
+        for (int w = 0; w < W; ++w) {
+            if ((cand[w] | covered[w]) != U[c * w8 + w]) return;
+            for (uint64_t x = cand[w] & ~covered[w]; x; x &= x - 1) sinks[c].push_back(w * 64 + __builtin_ctzll(x));
+        }
+        if (own[c] < 0 && sinks[c].size() < 2) return;
+    }
+    // gates
+    p.gate.clear();
+    std::vector<int32_t> gate_set;                  // a set that has the sinks of the gate
+    std::vector<int32_t> gate_of(D, -1);
+    std::vector<std::vector<int32_t>> gate_next;
+    std::vector<int32_t> gate_join;
+    p.rec.assign(R, ChainRec{-1, -1, -1, 0, 0, 0, -1, -1});
+    for (int c : by_count) {
+        if (sinks[c].size() < 2) continue;
+        int g = 0;
+        while (g < (int)gate_set.size() && sinks[gate_set[g]] != sinks[c]) ++g;
+        if (g == (int)gate_set.size()) {
+            if (g == kChainMaxGates) return;
+            gate_set.push_back(c);
+            gate_next.emplace_back();
+            gate_join.push_back(-1);
+            int32_t v = (int32_t)sinks[c].size() << 16;
+            for (int r : sinks[c]) {
+                v ^= r;
+                ChainRec &q = p.rec[r];
+                if (q.gate0 < 0) q.gate0 = (int16_t)g;
+                else if (q.gate1 < 0) q.gate1 = (int16_t)g;
+                else return;
+            }
+            p.gate.push_back(ChainGate{v, -1, 0, 0, {0, 0, 0}});
+        }
+        gate_of[c] = g;
+        if (own[c] >= 0) gate_next[g].push_back(own[c]);
+        else gate_join[g] = c;
+    }
+    // chains
+    std::vector<int32_t> order_r(R);
+    for (int r = 0; r < R; ++r) order_r[r] = r;
+    std::sort(order_r.begin(), order_r.end(), [&](int a, int b) {
+        const int ca = count[owner[a]], cb = count[owner[b]];
+        return ca != cb ? ca < cb : a < b;
+    });
+    // (a recv goes on from a direct predecessor where it can, else from any recv of pre(r) that ends a chain so far)
+    std::vector<int32_t> tail;                      // last recv of every chain
+    std::vector<std::vector<int32_t>> more(R);
+    std::vector<int32_t> start;
+    for (int r : order_r) {
+        const std::vector<int32_t> &sk = sinks[owner[r]];
+        int k = -1;
+        for (int s : sk)
+            if (tail[p.rec[s].slot] == s) { k = p.rec[s].slot; break; }
+        for (int i = 0; i < (int)tail.size() && k < 0; ++i)
+            if ((U[owner[r] * w8 + (tail[i] >> 6)] >> (tail[i] & 63)) & 1ull) k = i;
+        if (sk.empty()) start.push_back(r);
+        else if (sk.size() == 1) {
+            if (k >= 0 && tail[k] == sk[0]) p.rec[sk[0]].next = (int16_t)r;
+            else more[sk[0]].push_back(r);
+        }
+        if (k < 0) {
+            if (tail.size() == (size_t)kChainMaxChains) return;
+            k = (int)tail.size();
+            tail.push_back(r);
+        }
+        tail[k] = r;
+        p.rec[r].slot = (int16_t)k;
+    }
+    p.n_slots = (int)tail.size();
+    p.place.assign(R, 0);
+    std::vector<std::vector<int32_t>> chain(p.n_slots);
+    for (int r : order_r) {
+        std::vector<int32_t> &c = chain[p.rec[r].slot];
+        p.place[r] = (int16_t)c.size();
+        if (c.size() >= (size_t)kChainAhead) p.rec[c[c.size() - kChainAhead]].ahead = (int16_t)r;
+        c.push_back(r);
+    }
+    p.list.clear();
+    for (int r = 0; r < R; ++r) {
+        p.rec[r].more = (int16_t)p.list.size();
+        p.rec[r].n_more = (int16_t)more[r].size();
+        p.list.insert(p.list.end(), more[r].begin(), more[r].end());
+    }
+    for (size_t g = 0; g < p.gate.size(); ++g) {
+        p.gate[g].first = (int16_t)p.list.size();
+        p.gate[g].n = (int16_t)gate_next[g].size();
+        p.list.insert(p.list.end(), gate_next[g].begin(), gate_next[g].end());
+    }
+    p.extra.assign(R, 0);
+    p.n_extra = 0;
+    for (int r = 0; r < R; ++r)
+        if (p.rec[r].gate1 >= 0 || p.rec[r].n_more > 0) p.extra[r] = (int16_t)++p.n_extra;
+    p.start = (int32_t)p.list.size();
+    p.n_start = (int32_t)start.size();
+    p.list.insert(p.list.end(), start.begin(), start.end());
+    // what can attain M+ of a ready recv: the classes owned by its direct successors and the joins it is a sink of (any
+    // other class that holds it and another outstanding recv contains one of these)
+    p.cand_ptr.assign(1, 0);
+    p.cand.clear();
+    for (int r = 0; r < R; ++r) {
+        auto add = [&](int set) { p.cand.push_back(row_of_set[set]); };
+        if (p.rec[r].next >= 0) add(owner[p.rec[r].next]);
+        for (int s : more[r]) add(owner[s]);
+        for (int g : {(int)p.rec[r].gate0, (int)p.rec[r].gate1})
+            if (g >= 0) {
+                for (int s : gate_next[g]) add(owner[s]);
+                if (gate_join[g] >= 0) add(gate_join[g]);
+            }
+        p.cand_ptr.push_back((int32_t)p.cand.size());
+    }
+    // class totals: one row per run of consecutive columns of a set inside a block; the rows of a set are consecutive
+    const int n_blocks = (N + kChainBlock - 1) / kChainBlock;
+    std::vector<int32_t> at(D + 1, 0);
+    for (int j = 0; j < N; ++j)
+        if (j + 1 == N || set_of_col[j + 1] != set_of_col[j] || (j + 1) % kChainBlock == 0) ++at[set_of_col[j] + 1];
+    p.several.clear();
+    p.n_pairs = 0;
+    for (int c = 0; c < D; ++c) {
+        const int n = at[c + 1];
+        at[c + 1] += at[c];
+        if (n > 1) p.several.push_back(at[c] | n << 16);
+        p.n_pairs += n == 2;
+        if (at[c + 1] > 32767) return;
+    }
+    std::stable_partition(p.several.begin(), p.several.end(), [](int32_t v) { return v >> 16 == 2; });
+    p.n_totals = at[D];
+    p.head.clear();
+    for (int r = 0; r < R; ++r) {
+        p.rec[r].total = (int16_t)at[owner[r]];
+        if (p.place[r] < kChainAhead) p.head.push_back(r | at[owner[r]] << 16);
+    }
+    for (size_t g = 0; g < p.gate.size(); ++g) p.gate[g].join = (int16_t)(gate_join[g] >= 0 ? at[gate_join[g]] : -1);
+    p.empty = empty_set >= 0 ? at[empty_set] : -1;
+    p.flush.assign((size_t)n_blocks * (kChainBlock / 16), 0);
+    p.flush_row.clear();
+    p.block_first.assign(1, 0);
+    std::vector<int32_t> fill(at.begin(), at.end() - 1);
+    for (int j = 0; j < N; ++j) {
+        if (j + 1 == N || set_of_col[j + 1] != set_of_col[j] || (j + 1) % kChainBlock == 0) {
+            p.flush[j / 16] |= 1u << (j % 16);
+            p.flush_row.push_back(fill[set_of_col[j]]++);
+        }
+        if (j + 1 == N || (j + 1) % kChainBlock == 0) p.block_first.push_back((int32_t)p.flush_row.size());
+    }
+    p.ok = true;
+}
+
+}  // namespace tictac

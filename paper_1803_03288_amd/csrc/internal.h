@@ -15,6 +15,18 @@ constexpr int kK1Rpt = 4;             // positions per thread group and chunk of
 
 void set_error(const char *fmt, ...);
 
+// Tables of the chain form of TAC (chain_plan.h, k3_tac_chain.hip), made at the first call that takes that form.
+struct ChainTables {
+    bool tried = false, ok = false;
+    int32_t n_chains = 0, n_totals = 0, n_gates = 0, n_list = 0, start = 0, n_start = 0, n_several = 0, empty = -1, n_extra = 0, n_pairs = 0, n_head = 0;
+    void *block = nullptr;
+    size_t bytes = 0;
+    int4 *d_rec = nullptr, *d_gate = nullptr;
+    int16_t *d_list = nullptr, *d_place = nullptr, *d_extra = nullptr;
+    int32_t *d_head = nullptr, *d_several = nullptr, *d_cand_ptr = nullptr, *d_cand = nullptr, *d_flush_row = nullptr, *d_block_first = nullptr;
+    uint32_t *d_flush = nullptr;
+};
+
 // Everything a handle owns.  Device arrays are sized exactly; empty ones are NULL.
 struct Dag {
     int32_t n = 0, R = 0, W = 0, N = 0, E = 0;
@@ -133,6 +145,7 @@ struct Dag {
     // scratch owned by the handle (grown on demand, stream-ordered use)
     // the two allocations that hold every array above (graph tables + dep; class tables)
     void *d_graph_block = nullptr, *d_class_block = nullptr;
+    size_t graph_bytes = 0, class_bytes = 0, send_bytes = 0;
     void *d_work = nullptr;
     int32_t *d_chan = nullptr;      // [R] channel table of the last several-channel simulation
     std::vector<int32_t> h_chan;    // its host copy
@@ -148,9 +161,15 @@ struct Dag {
     uint8_t *d_send_col_kind = nullptr;
     int32_t n_send_free = 0;
     size_t work_bytes = 0;
+    // chain form of TAC: its tables, and the class rows and columns (host) that they are made from
+    ChainTables chain;
+    std::vector<uint64_t> h_cls_dep;    // [C][W]   (small graphs only)
+    std::vector<int32_t> h_col_cls;     // [N]
 };
 
 hipError_t ensure_workspace(Dag *d, size_t bytes);
+// the tables of the chain form, made at the first call; d->chain.ok says whether the graph has that form
+hipError_t ensure_chain_tables(Dag *d, hipStream_t s);
 
 // Number of compute units of a device and the number of workgroups of a kernel that fit one,
 // asked of the runtime once and remembered (the queries cost microseconds on every launch
@@ -203,6 +222,8 @@ hipError_t launch_sliced_tables(const Dag &d, hipStream_t s);
 // register-resident variant for graphs with few classes; returns hipErrorNotSupported when
 // the graph does not fit it.  Samples it cannot order (a transfer time of zero) are marked
 // in flags[b] = 1 for the general kernel.
+// chain form, one lane per sample (needs d.chain; the same contract as launch_tac_sliced)
+hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, int32_t **flags_out, hipStream_t s);
 hipError_t launch_tac_reg(Dag &d, const TacArgs &a, int32_t *flags, hipStream_t s);
 
 struct SimArgs {

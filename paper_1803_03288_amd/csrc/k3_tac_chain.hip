@@ -1,0 +1,519 @@
+// TAC (Sec. 4.3, Algorithm 3) with the iteration under its order (Sec. 3.2) on graphs that have the chain form of
+// chain_plan.h (model-shaped graphs: one class of compute ops introduces each recv), one *lane* per timing sample.
+//
+// Two kernels:
+//   * class_totals_kernel streams op_time once.  A wave takes 64 samples and a range of columns, 256 bytes of a row at a time
+//     through LDS, so that lane l adds up the columns of sample l; the columns are the same
+//     for all lanes, so which class a column belongs to is a matter of scalar code and no atomics are needed.  Totals and
+//     transfer times are written transposed, [row][sample].
+//   * tac_chain_kernel walks through the partial order of the recvs.  The ready recvs of a sample (at most one per chain)
+//     sit in registers with P and Time; a round is one pass of the comparator over them, and the recv that follows the
+//     one taken on its chain is entered from values requested a round earlier.  The time released by a transfer is P of
+//     its recv when it is taken, so the makespan is a running maximum.
+// What bounds them: the first the bytes of the timing arrays, the second the R dependent rounds of a sample.
+// A sample with a transfer time or an owned class total of zero is flagged for the general kernel.
+#include <algorithm>
+
+#include "chain_plan.h"
+#include "device_utils.h"
+#include "internal.h"
+
+namespace tictac {
+
+struct TotalsParams {
+    int32_t B, N, R, n_blocks, blocks_per_part, n_parts;
+    size_t Bp;                          // samples per row of the outputs, a multiple of 64
+    const void *op_time, *recv_time;    // of the first sample
+    const uint32_t *flush;
+    const int32_t *flush_row, *block_first;
+    double *totals;                     // [n_totals][Bp]
+    double *t;                          // [R][Bp]
+    int32_t *flags;                     // [B] 1 = a transfer time is not positive
+};
+
+// Per tile 256 bytes of each of the 64 rows: a request of a wave covers four rows.  (128 and 512 bytes: 4 % and 5 % slower
+// on inception3's rows, 4 % and 12 % on resnet50's; 0.70 ms and 0.15 ms for 65 536 samples, 4.7 and 4.4 TB/s.)  The next
+// tile is requested once the present one is in LDS.
+template <typename T>
+__global__ void __launch_bounds__(64, 2)
+class_totals_kernel(const TotalsParams p)
+{
+    constexpr int VEC = 16 / (int)sizeof(T);            // elements per load
+    constexpr int LPR = 16;                             // lanes per row
+    constexpr int TC = LPR * VEC;                       // columns per tile
+    constexpr int RPI = 64 / LPR, NI = 64 / RPI;        // rows per load, loads per tile
+    typedef T Vec __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
+    __shared__ T tile[TC * 65];
+    const int lane = threadIdx.x, sub = (lane % LPR) * VEC, lr = lane / LPR;
+    const bool recvs = (int)blockIdx.y == p.n_parts;    // the last part transposes the transfer times
+    const int width = recvs ? p.R : p.N;
+    const int blk = recvs ? 0 : (int)blockIdx.y * p.blocks_per_part;
+    const int c_begin = blk * kChainBlock;
+    const int c_end = recvs ? width : min(width, c_begin + p.blocks_per_part * kChainBlock);
+    const int b0 = blockIdx.x * 64;
+    // rows beyond the batch are read as its last one; their outputs are padding
+    const T *src = static_cast<const T *>(recvs ? p.recv_time : p.op_time);
+    const T *base = src + (size_t)min(b0 + lr, p.B - 1) * width + sub;
+    const bool whole = b0 + 64 <= p.B;
+
+    Vec v[NI];
+    auto request = [&](int c0) {
+        if (whole && c0 + TC <= width) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) v[i] = *reinterpret_cast<const Vec *>(base + (size_t)i * RPI * width + c0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const T *q = src + (size_t)min(b0 + i * RPI + lr, p.B - 1) * width + sub;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[i][e] = c0 + sub + e < width ? q[c0 + e] : T(0);
+            }
+        }
+    };
+    auto to_lds = [&]() {
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) tile[(sub + e) * 65 + i * RPI + lr] = v[i][e];
+        wave_sync();
+    };
+    if (recvs) {
+        double *out = p.t + b0 + lane;
+        bool zero_seen = false;
+        request(0);
+        for (int c0 = 0; c0 < c_end; c0 += TC) {
+            to_lds();
+            if (c0 + TC < c_end) request(c0 + TC);
+            const int n = min(TC, c_end - c0);
+            for (int c = 0; c < n; ++c) {
+                const double y = (double)tile[c * 65 + lane];
+                zero_seen |= !(y > 0.0);
+                out[(size_t)(c0 + c) * p.Bp] = y;
+            }
+        }
+        if (b0 + lane < p.B) p.flags[b0 + lane] = zero_seen ? 1 : 0;
+        return;
+    }
+    if (c_begin >= c_end) return;
+    double *out = p.totals + b0 + lane;
+    double acc = 0.0;
+    int run = p.block_first[blk];
+    request(c_begin);
+    for (int c0 = c_begin; c0 < c_end; c0 += TC) {
+        to_lds();
+        if (c0 + TC < c_end) request(c0 + TC);
+#pragma unroll
+        for (int h = 0; h < TC / 16; ++h) {
+            const uint32_t mask = c0 + 16 * h < c_end ? p.flush[c0 / 16 + h] : 0u;
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+                acc += (double)tile[(16 * h + c) * 65 + lane];
+                if ((mask >> c) & 1u) {
+                    out[(size_t)p.flush_row[run++] * p.Bp] = acc;
+                    acc = 0.0;
+                }
+            }
+        }
+    }
+}
+
+struct ChainParams {
+    int32_t B, R, W, n_gates, n_list, start, n_start, n_several, empty;
+    size_t Bp;
+    const int4 *rec;                    // ChainRec [R]
+    const int4 *gate;                   // ChainGate [n_gates]
+    const int16_t *list, *place, *extra;
+    int32_t n_extra, n_pairs, n_head;
+    const int32_t *several, *head;
+    const int32_t *cand_ptr, *cand;
+    const uint64_t *cls_dep;            // [C][W]
+    double *totals;                     // [n_totals][Bp]
+    const double *t;                    // [R][Bp]
+    int32_t *order, *rank;
+    int32_t simulate;
+    double *makespan, *eff, *U, *L, *S;
+    int32_t *flags;
+};
+
+constexpr int kStage = 32;              // rounds whose selections are staged in LDS before they go to memory
+constexpr int kStagePad = 66;
+
+static size_t chain_lds_bytes(int NC, const ChainParams &p)
+{
+    return ((size_t)p.R + NC + p.n_extra + p.n_gates) * 16 + (size_t)NC * kChainAhead * 64 * 16 + ((size_t)p.n_gates + 1) * 64 * 12 +
+           ((size_t)2 * p.W + 1) * 64 * 4 + (size_t)kStage * kStagePad * 2 + (size_t)p.n_list * 2;
+}
+
+// A wave has a SIMD to itself at 65 536 samples, so a round costs its instructions (four cycles each) and every wait that
+// nothing covers; a row of totals or times that a wave asks for is used by that wave alone, so it comes from the Infinity
+// Cache or from HBM.  Therefore: when a recv is taken, the values of the recv four places further on its chain are
+// requested; they land three rounds later in a ring in LDS (per slot and lane), from which a recv that becomes ready is
+// entered.  A slot without a ready recv has P < 0 (the P of some recv with its sign set), which precedes nothing and is
+// preceded by every ready recv; a recv that is the sink of no gate counts down gate n_gates, which never opens; second
+// gates and lists of successors, which few recvs have, hide behind one field of the record.
+template <int NC>
+__global__ void __launch_bounds__(64)
+tac_chain_kernel(const ChainParams p)
+{
+    extern __shared__ int4 chain_smem[];
+    const int R = p.R, lane = threadIdx.x;
+    // record of recv r: x = next | number of its extra record << 10 | that of next << 20 | sign: no next (next = R + slot);
+    // y and z = byte offsets of the class total and the times of the recv kChainAhead places further; w = its ring entry |
+    // ring entry of next << 5 | its gate << 10 | gate of next << 16
+    int4 *rec_l = chain_smem;                                           // [R + NC]
+    int4 *more_l = rec_l + (R + NC);                                    // [n_extra] ChainRec of the recvs with a second gate or a list
+    int4 *gate_l = more_l + p.n_extra;                                  // [n_gates] ChainGate
+    double2 *ring = reinterpret_cast<double2 *>(gate_l + p.n_gates);    // [NC * kChainAhead][64] P, Time
+    double *join_l = reinterpret_cast<double *>(ring + NC * kChainAhead * 64);  // [n_gates + 1][64] time of the join
+    uint32_t *gcnt = reinterpret_cast<uint32_t *>(join_l + (p.n_gates + 1) * 64);     // [n_gates + 1][64] sinks outstanding << 16 | their xor
+    uint32_t *alive = gcnt + (p.n_gates + 1) * 64;                      // [2 W + 1][64] outstanding recvs
+    uint16_t *stage = reinterpret_cast<uint16_t *>(alive + (2 * p.W + 1) * 64); // [kStage][kStagePad]
+    int16_t *list_l = reinterpret_cast<int16_t *>(stage + kStage * kStagePad);  // [n_list]
+
+    const uint32_t row_bytes = (uint32_t)(p.Bp * 8);                    // (all rows together stay below 4 GB)
+    const int b0 = blockIdx.x * 64, b = b0 + lane;                      // (rows hold a multiple of 64 samples)
+    auto total_at = [&](uint32_t off) __attribute__((always_inline)) -> double & {
+        return *reinterpret_cast<double *>(reinterpret_cast<char *>(p.totals) + (off + (uint32_t)b * 8u));
+    };
+    auto time_at = [&](uint32_t off) __attribute__((always_inline)) {
+        return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(p.t) + (off + (uint32_t)b * 8u));
+    };
+    // totals in several rows are added up into the first, eight loads at a time
+    for (int i = 0; i < p.n_pairs; i += 4) {
+        double x[4], y[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t off = (uint32_t)(p.several[min(i + j, p.n_pairs - 1)] & 0xffff) * row_bytes;
+            x[j] = total_at(off);
+            y[j] = total_at(off + row_bytes);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i + j < p.n_pairs) total_at((uint32_t)(p.several[i + j] & 0xffff) * row_bytes) = x[j] + y[j];
+    }
+    for (int i = p.n_pairs; i < p.n_several; ++i) {
+        const uint32_t off = (uint32_t)(p.several[i] & 0xffff) * row_bytes;
+        const int n = p.several[i] >> 16;
+        double s = 0.0;
+        for (int j = 0; j < n; j += 8) {
+            double x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = total_at(off + (uint32_t)min(j + e, n - 1) * row_bytes);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += j + e < n ? x[e] : 0.0;
+        }
+        total_at(off) = s;
+    }
+    for (int r = lane; r < R; r += 64) {
+        const int4 q = p.rec[r];
+        const int next = (int)(int16_t)q.x, slot = q.z >> 16, at = p.place[r], extra = p.extra[r];
+        const int ahead = (q.w >> 16) >= 0 ? q.w >> 16 : r;             // (at the end of a chain: a value that is never used)
+        if (extra) more_l[extra - 1] = q;
+        const int e = slot * kChainAhead, own = e + (at & (kChainAhead - 1)), gate = q.x >> 16;
+        const int gate_next = next >= 0 ? p.rec[next].x >> 16 : -1;
+        rec_l[r] = make_int4((next >= 0 ? next : (R + slot) | (int)0x80000000u) | extra << 10 | (next >= 0 ? p.extra[next] << 20 : 0),
+                             (int)((int)(int16_t)p.rec[ahead].w * row_bytes), (int)(ahead * row_bytes),
+                             own | (next >= 0 ? e + ((at + 1) & (kChainAhead - 1)) : own) << 5 |
+                             (gate >= 0 ? gate : p.n_gates) << 10 | (gate_next >= 0 ? gate_next : p.n_gates) << 16);
+    }
+    for (int i = lane; i < p.n_gates; i += 64) gate_l[i] = p.gate[i];
+    for (int i = lane; i < p.n_list; i += 64) list_l[i] = p.list[i];
+    if (lane < NC) rec_l[R + lane] = make_int4((R + lane) | (int)0x80000000u, 0, 0, lane * kChainAhead * 0x21 | p.n_gates * 0x10400);
+    wave_sync();
+#pragma unroll 4
+    for (int g = 0; g < p.n_gates; ++g) {
+        const int4 c = gate_l[g];
+        gcnt[g * 64 + lane] = (uint32_t)c.x;
+        const int j = (int)(int16_t)c.y;
+        const double x = total_at((uint32_t)max(j, 0) * row_bytes);
+        join_l[g * 64 + lane] = j >= 0 ? x : 0.0;
+    }
+    gcnt[p.n_gates * 64 + lane] = 0x40000000u;
+    join_l[p.n_gates * 64 + lane] = 0.0;
+    // the first recvs of every chain
+#pragma unroll 4
+    for (int i = 0; i < p.n_head; ++i) {
+        const int r = p.head[i] & 0xffff;
+        ring[(rec_l[r].w & 0x1f) * 64 + lane] = make_double2(total_at((uint32_t)(p.head[i] >> 16) * row_bytes), time_at(r * row_bytes));
+    }
+    for (int h = 0; h <= 2 * p.W; ++h) {
+        const int nbits = min(32, max(0, R - 32 * h));
+        alive[h * 64 + lane] = nbits >= 32 ? 0xffffffffu : ((1u << nbits) - 1u);
+    }
+    wave_sync();
+    bool bad = b < p.B ? p.flags[b] != 0 : true;
+
+    // ---- the ready recvs: slot k holds recv id_k with its P and Time ----
+#define TC_EACH(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7)
+#define TC_DECL(k) int id_##k = R + k; double P_##k = -1.0 - k, T_##k = TT_INF;
+    TC_EACH(TC_DECL)
+
+    // time of the join of the second gate of a recv that is ready now, if it is the last outstanding sink of that gate
+    auto second_join = [&](int extra) __attribute__((always_inline)) {
+        const int g = (int)(int16_t)more_l[extra - 1].y;
+        return g >= 0 && (gcnt[g * 64 + lane] >> 16) == 1u ? join_l[g * 64 + lane] : 0.0;
+    };
+    // a recv that becomes ready other than as the next one of the one taken
+    auto enter = [&](int r) __attribute__((always_inline)) {
+        const int4 q = rec_l[r];
+        const double2 v = ring[(q.w & 0x1f) * 64 + lane];
+        const int s = (q.w & 0x1f) / kChainAhead, extra = (q.x >> 10) & 0x3ff, g = (q.w >> 10) & 0x3f;
+        double pr = v.x + ((gcnt[g * 64 + lane] >> 16) == 1u ? join_l[g * 64 + lane] : 0.0);
+        if (extra) pr += second_join(extra);
+#define TC_ENTER(k)                                                                       \
+        if constexpr (k < NC) {                                                           \
+            id_##k = s == k ? r : id_##k;                                                 \
+            P_##k = s == k ? pr : P_##k;                                                  \
+            T_##k = s == k ? v.y : T_##k;                                                 \
+        }
+        TC_EACH(TC_ENTER)
+    };
+    for (int i = 0; i < p.n_start; ++i) enter(list_l[p.start + i]);
+
+    // M+ of a ready recv, and the literal ascending scan: only where the comparator ties
+    auto m_plus = [&](int r) __attribute__((always_inline)) {
+        double best = TT_INF;
+        for (int e = p.cand_ptr[r]; e < p.cand_ptr[r + 1]; ++e) {
+            const uint64_t *row = p.cls_dep + (size_t)p.cand[e] * p.W;
+            int n = 0;
+            double s = 0.0;
+            for (int w = 0; w < p.W; ++w) {
+                uint64_t x = row[w] & ((uint64_t)alive[(2 * w + 1) * 64 + lane] << 32 | alive[2 * w * 64 + lane]);
+                n += __builtin_popcountll(x);
+                while (x) {
+                    s += time_at((w * 64 + __builtin_ctzll(x)) * row_bytes);
+                    x &= x - 1;
+                }
+            }
+            if (n >= 2) best = fmin(best, s);
+        }
+        return best;
+    };
+    auto literal_scan = [&]() __attribute__((always_inline)) {
+        int best = -1, at = -1, bslot = 0;
+        double bP = 0.0, bT = 0.0, mp = -1.0;
+        for (;;) {
+            int a = R, as = 0;
+            double aP = 0.0, aT = 0.0;
+#define TC_LOWEST(k)                                                                      \
+            if constexpr (k < NC) {                                                       \
+                if (id_##k > at && id_##k < a) { a = id_##k; as = k; aP = P_##k; aT = T_##k; } \
+            }
+            TC_EACH(TC_LOWEST)
+            if (a == R) break;
+            at = a;
+            if (best < 0) { best = a; bslot = as; bP = aP; bT = aT; continue; }
+            const double xa = fmin(bP, aT), ya = fmin(aP, bT);
+            double ma = -1.0;
+            bool prec = xa < ya;
+            if (xa == ya) {
+                ma = m_plus(a);
+                if (mp < 0.0) mp = m_plus(best);
+                prec = ma < mp;
+            }
+            if (prec) { best = a; bslot = as; bP = aP; bT = aT; mp = ma; }
+        }
+        return bslot;
+    };
+
+    const double e_time = p.empty >= 0 ? total_at(p.empty * row_bytes) : 0.0;
+    double F = 0.0, busy = e_time, sum_c = e_time;
+    int32_t *const order_w = p.order + (size_t)b0 * R;
+    int32_t *const rank_w = p.rank ? p.rank + (size_t)b0 * R : nullptr;
+    // values under way: requested three rounds, two rounds and one round ago, each with the ring entry it goes to
+    double2 in_a = ring[lane], in_b = in_a, in_c = in_a;
+    int at_a = 0, at_b = 0, at_c = 0;
+    // (the first rounds put back what entry 0 holds: nothing else goes there before the fourth round)
+
+    auto round = [&](int step, double2 &in, int &in_at) __attribute__((always_inline)) {
+        ring[in_at * 64 + lane] = in;
+
+        // ---- selection.  Without a tie the order in which the ready recvs are compared does not matter: strict
+        // precedence is transitive, so the one that is left precedes all others and the ascending scan ends with it too ----
+        int slot = 0, best = id_0;
+        double bP = P_0, bT = T_0;
+        bool tie = false;
+#define TC_COMPARE(k)                                                                     \
+        if constexpr (k >= 1 && k < NC) {                                                 \
+            const double xa = fmin(bP, T_##k), ya = fmin(P_##k, bT);                      \
+            tie |= xa == ya;                                                              \
+            const bool take = xa < ya;                                                    \
+            slot = take ? k : slot;                                                       \
+            best = take ? id_##k : best;                                                  \
+            bP = take ? P_##k : bP;                                                       \
+            bT = take ? T_##k : bT;                                                       \
+        }
+        TC_EACH(TC_COMPARE)
+        if (NC > 1 && tie) {
+            slot = literal_scan();
+#define TC_TAKEN(k) if constexpr (k < NC) { best = slot == k ? id_##k : best; bP = slot == k ? P_##k : bP; bT = slot == k ? T_##k : bT; }
+            TC_EACH(TC_TAKEN)
+        }
+        bad |= !(bP > 0.0);                             // (a time of zero, or nothing ready: left to the general kernel)
+
+        // ---- record it; the iteration ----
+        const int4 q = rec_l[best];
+        stage[(step & (kStage - 1)) * kStagePad + lane] = (uint16_t)best;
+        atomicAnd(&alive[(best >> 5) * 64 + lane], ~(1u << (best & 31)));
+        in.x = total_at((uint32_t)q.y);
+        in.y = time_at((uint32_t)q.z);
+        in_at = q.w & 0x1f;
+        const int g = (q.w >> 10) & 0x3f, gf = (q.w >> 16) & 0x3f;
+        const double2 v = ring[((q.w >> 5) & 0x1f) * 64 + lane];
+        const uint32_t c_f = gcnt[gf * 64 + lane], c = (gcnt[g * 64 + lane] - 0x10000u) ^ (uint32_t)best;
+        const double j_f = join_l[gf * 64 + lane];
+        gcnt[g * 64 + lane] = c;
+        F += bT;
+        busy = fmax(busy, F) + bP;
+        sum_c += bP;
+
+        // ---- what is ready now: the next recv on the chain, with the join that points at it already.  (It is no sink of
+        // the gate that was counted down: sinks of one gate do not depend on each other.) ----
+        const int f = q.x & 0x3ff, extra = (q.x >> 10) & 0x3ff, f_extra = (q.x >> 20) & 0x3ff;
+        double fP = __hiloint2double(__double2hiint(v.x) | (q.x & (int)0x80000000u), __double2loint(v.x));
+        fP += (c_f >> 16) == 1u ? j_f : 0.0;
+        if (f_extra) fP += second_join(f_extra);
+#define TC_NEXT(k)                                                                        \
+        if constexpr (k < NC) {                                                           \
+            id_##k = slot == k ? f : id_##k;                                              \
+            P_##k = slot == k ? fP : P_##k;                                               \
+            T_##k = slot == k ? v.y : T_##k;                                              \
+        }
+        TC_EACH(TC_NEXT)
+        // a gate with one sink outstanding: its join points at that sink, if it is ready (else it does once it is); with
+        // none: it opens
+        auto gate_counted = [&](int i, uint32_t left) __attribute__((always_inline)) {
+            const double x = (left >> 16) == 1u ? join_l[i * 64 + lane] : 0.0;
+            const int sink = (int)(left & 0xffffu);
+#define TC_JOIN(k) if constexpr (k < NC) { P_##k += id_##k == sink ? x : 0.0; }
+            TC_EACH(TC_JOIN)
+            if ((left >> 16) == 0u) {
+                const int4 gr = gate_l[i];
+                for (int n = 0; n < (int)(int16_t)gr.z; ++n) enter(list_l[(gr.y >> 16) + n]);
+            }
+        };
+        if (c < 0x20000u) gate_counted(g, c);
+        if (extra) {
+            const int4 m = more_l[extra - 1];
+            const int first = m.y >> 16, n_more = (int)(int16_t)m.z, g1 = (int)(int16_t)m.y;
+            for (int i = 0; i < n_more; ++i) enter(list_l[first + i]);
+            if (g1 >= 0) {
+                const uint32_t c1 = (gcnt[g1 * 64 + lane] - 0x10000u) ^ (uint32_t)best;
+                gcnt[g1 * 64 + lane] = c1;
+                if (c1 < 0x20000u) gate_counted(g1, c1);
+            }
+        }
+
+        // ---- selections to memory, kStage rounds at a time: two samples per store, whole lines of the order ----
+        if ((step & (kStage - 1)) == kStage - 1 || step == R - 1) {
+            wave_sync();
+            const int s = (step & ~(kStage - 1)) + (lane & 31), n_b = min(64, p.B - b0);
+            if (s <= step)
+                for (int j = lane >> 5; j < n_b; j += 2) {
+                    const int r = min((int)stage[(lane & 31) * kStagePad + j], R - 1);
+                    order_w[j * R + s] = r;
+                    if (rank_w) rank_w[j * R + r] = s;
+                }
+            wave_sync();
+        }
+    };
+    int step = 0;
+    for (; step + 3 <= R; step += 3) {
+        round(step, in_a, at_a);
+        round(step + 1, in_b, at_b);
+        round(step + 2, in_c, at_c);
+    }
+    if (step < R) round(step, in_a, at_a);
+    if (step + 1 < R) round(step + 1, in_b, at_b);
+
+    if (b < p.B) {
+        p.flags[b] = bad ? 1 : 0;
+        if (p.simulate && !bad) {
+            const double m = busy;                      // (not less than F: the last transfer is in it)
+            const double U = sum_c + F;
+            const double L = fmax(sum_c, F);
+            if (p.makespan) p.makespan[b] = m;
+            if (p.eff) p.eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
+            if (p.U) p.U[b] = U;
+            if (p.L) p.L[b] = L;
+            if (p.S) p.S[b] = (U == L || L == 0.0) ? 0.0 : (U - L) / L;
+        }
+    }
+}
+
+template <int NC>
+static hipError_t launch_chain_nc(const ChainParams &p, hipStream_t s)
+{
+    const size_t lds = chain_lds_bytes(NC, p);
+    if (lds > 48 * 1024) {
+        const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(tac_chain_kernel<NC>), lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((tac_chain_kernel<NC>), dim3((unsigned)((p.B + 63) / 64)), dim3(64), lds, s, p);
+    return hipGetLastError();
+}
+
+// Bytes of the workspace that a chunk of samples takes: totals and transposed transfer times.
+constexpr size_t kChainChunkBytes = (size_t)512 << 20;
+
+hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, int32_t **flags_out, hipStream_t s)
+{
+    const ChainTables &c = d.chain;
+    if (!c.ok || a.sel_P || a.sel_Mplus) return hipErrorNotSupported;
+    const size_t per_sample = ((size_t)c.n_totals + d.R) * 8;
+    size_t chunk = std::min((size_t)a.B, kChainChunkBytes / per_sample);
+    chunk = (chunk + 63) & ~(size_t)63;
+    hipError_t e = ensure_workspace(&d, flag_bytes + chunk * per_sample);
+    if (e != hipSuccess) return e;
+    int32_t *flags = static_cast<int32_t *>(d.d_work);
+    *flags_out = flags;
+    double *totals = reinterpret_cast<double *>(static_cast<char *>(d.d_work) + flag_bytes);
+    const size_t elem = a.f32 ? 4 : 8;
+    const int n_cu = device_cu_count(d.device);
+    for (size_t b0 = 0; b0 < (size_t)a.B; b0 += chunk) {
+        const int32_t nb = (int32_t)std::min(chunk, (size_t)a.B - b0);
+        const int groups = (nb + 63) / 64;
+        TotalsParams t{};
+        t.B = nb; t.N = d.N; t.R = d.R; t.Bp = chunk;
+        t.n_blocks = (d.N + kChainBlock - 1) / kChainBlock;
+        // columns are split until there are eight waves per compute unit, what LDS holds
+        const int parts = std::max(1, std::min(t.n_blocks, (8 * n_cu + groups - 1) / groups));
+        t.blocks_per_part = (t.n_blocks + parts - 1) / parts;
+        t.n_parts = (t.n_blocks + t.blocks_per_part - 1) / t.blocks_per_part;
+        t.op_time = static_cast<const char *>(a.op_time) + b0 * d.N * elem;
+        t.recv_time = static_cast<const char *>(a.recv_time) + b0 * d.R * elem;
+        t.flush = c.d_flush; t.flush_row = c.d_flush_row; t.block_first = c.d_block_first;
+        t.totals = totals; t.t = totals + (size_t)c.n_totals * chunk; t.flags = flags + b0;
+        const dim3 grid((unsigned)groups, (unsigned)t.n_parts + 1);
+        if (a.f32) hipLaunchKernelGGL(class_totals_kernel<float>, grid, dim3(64), 0, s, t);
+        else hipLaunchKernelGGL(class_totals_kernel<double>, grid, dim3(64), 0, s, t);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        ChainParams p{};
+        p.B = nb; p.R = d.R; p.W = d.W; p.Bp = chunk;
+        p.n_gates = c.n_gates; p.n_list = c.n_list; p.start = c.start; p.n_start = c.n_start;
+        p.n_several = c.n_several; p.empty = c.empty;
+        p.rec = c.d_rec; p.gate = c.d_gate; p.list = c.d_list; p.place = c.d_place; p.extra = c.d_extra; p.n_extra = c.n_extra;
+        p.n_pairs = c.n_pairs; p.n_head = c.n_head; p.head = c.d_head; p.several = c.d_several;
+        p.cand_ptr = c.d_cand_ptr; p.cand = c.d_cand; p.cls_dep = d.d_cls_dep;
+        p.totals = totals; p.t = t.t;
+        p.order = a.order + b0 * d.R;
+        p.rank = a.rank ? a.rank + b0 * d.R : nullptr;
+        p.simulate = a.simulate ? 1 : 0;
+        p.makespan = a.makespan ? a.makespan + b0 : nullptr;
+        p.eff = a.eff ? a.eff + b0 : nullptr;
+        p.U = a.U ? a.U + b0 : nullptr;
+        p.L = a.L ? a.L + b0 : nullptr;
+        p.S = a.S ? a.S + b0 : nullptr;
+        p.flags = flags + b0;
+        if (c.n_chains <= 1) e = launch_chain_nc<1>(p, s);
+        else if (c.n_chains <= 2) e = launch_chain_nc<2>(p, s);
+        else if (c.n_chains <= 4) e = launch_chain_nc<4>(p, s);
+        else e = launch_chain_nc<8>(p, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace tictac

@@ -1,0 +1,117 @@
+"""GPU parity of the chain form of TAC (one lane per sample, large batches of model-shaped graphs): against the
+wave-per-sample kernels, which take smaller batches, on every sample, and against the CPU oracle on some of them."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from paper_1803_03288_amd import workloads as wl
+
+from helpers import oracle_tac_rows
+
+
+@pytest.fixture(scope="module")
+def tt():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1803_03288_amd import binding
+    binding.lib()
+    return binding
+
+
+def modules_dag(modules, name="modules"):
+    """A chain of modules; a module is a list of branch lengths (layers that read one recv each), joined by an op that
+    reads no recv; a length may be zero (a branch of plain ops).  A module of one branch is a piece of a chain."""
+    b = wl._Builder()
+    x = b.op([], 1e-3, "input")
+    for lengths in modules:
+        ends = []
+        for n in lengths:
+            y = b.op([x], 1e-3, "branch")
+            for k in range(n):
+                y = b.op([y, b.recv(1e5 * (1 + k % 3))], 1e-3, "layer")
+                y = b.chain([y], [1e-3] * (k % 3 + 1), "op")
+            ends.append(y)
+        x = b.op(ends, 1e-3, "join")
+    return b.finish(name, seed=5, batch=8)
+
+
+GRAPHS = {
+    "chain": lambda: wl.chain_dag(97),
+    "one": lambda: wl.chain_dag(1),
+    "two_branches": lambda: modules_dag([[2], [3, 1], [0, 4], [1, 1], [5]]),
+    "ends_with_a_join": lambda: modules_dag([[1], [2, 3, 1]]),
+    "three_branches": lambda: modules_dag([[3], [1, 2, 9], [4, 4, 4], [1]]),
+    "starts_wide": lambda: modules_dag([[2, 1, 3, 2, 1], [1], [2, 2]]),
+    "eight_branches": lambda: modules_dag([[1, 2, 3, 1, 2, 3, 1, 2], [2], [1, 1, 1, 1, 1, 1, 1, 1]]),
+    "jobs": lambda: wl.independent_jobs_dag(8),
+    "resnet50": wl.resnet50_dag,
+}
+
+
+def times(d, B, kind, rng):
+    """Timing arrays: lognormal multiples of 2**-30 s; or a few values only, so that most comparisons tie; or with some
+    times of zero (which the samples are left to the general kernel for)."""
+    if kind == "lognormal":
+        op = wl.quantise(1e-3 * np.exp(0.4 * rng.standard_normal((B, d.n_compute))))
+        rv = wl.quantise(3e-3 * np.exp(0.6 * rng.standard_normal((B, d.n_recv))))
+        return op, rv
+    op = wl.QUANTUM * rng.integers(1, 4, size=(B, d.n_compute)).astype(np.float64)
+    rv = wl.QUANTUM * rng.integers(2, 7, size=(B, d.n_recv)).astype(np.float64)
+    if kind == "zeros":
+        rv[rng.random(B) < 0.1, 0] = 0.0
+        op[rng.random(B) < 0.1] = 0.0
+    return op, rv
+
+
+@pytest.mark.parametrize("kind", ["lognormal", "ties", "zeros"])
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_chain_form(tt, name, kind):
+    d = GRAPHS[name]()
+    rng = np.random.default_rng([len(name), len(kind)])
+    B = 8192 + 64 * 3 + 37
+    op, rv = times(d, B, kind, rng)
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    print(f"[chain] {name} {kind}: N={d.n_compute} R={d.n_recv} classes={h.n_classes}", flush=True)
+    gop, grv = torch.from_numpy(op).cuda(), torch.from_numpy(rv).cuda()
+    got = tt.tac_simulate(h, gop, grv, want_rank=True)
+    torch.cuda.synchronize()
+    for lo in range(0, B, 4096):
+        part = tt.tac_simulate(h, gop[lo:lo + 4096].contiguous(), grv[lo:lo + 4096].contiguous(), want_rank=True)
+        for k in (0, 1, 4, 5, 6, 7, 8):
+            assert torch.equal(got[k][lo:lo + 4096], part[k]), (name, kind, lo, k)
+    rows = sorted(set(np.linspace(0, B - 1, 12 if d.n_recv > 100 else 60).astype(int).tolist()))
+    dep = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    eo = oracle.tac(dep, d.recv_ids, op[rows], rv[rows])[0]
+    assert np.array_equal(got[0][rows].cpu().numpy(), eo)
+    em = oracle.simulate(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids, eo, op[rows], rv[rows])
+    for k in range(5):
+        np.testing.assert_allclose(got[4 + k][rows].cpu().numpy(), em[k], rtol=1e-12, atol=0)
+    # the orders alone, and the same samples stored as float32 (exact for the small multiples)
+    only = tt.tac_priority(h, gop, grv, want_rank=False)[0]
+    assert torch.equal(only, got[0])
+    if kind != "lognormal":
+        f32 = tt.tac_simulate(h, gop.float(), grv.float())
+        assert torch.equal(f32[0], got[0]) and torch.equal(f32[4], got[4])
+
+
+def test_chain_form_inception(tt):
+    """Seven class slots per lane: the chain form from 64 samples on, whose results are those of single samples."""
+    d = wl.inception3_dag()
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    for B in (64, 65, 200):
+        op, rv = wl.timing_samples(d, 0, B)
+        gop, grv = torch.from_numpy(op).cuda(), torch.from_numpy(rv).cuda()
+        got = tt.tac_simulate(h, gop, grv, want_rank=True)
+        for lo in range(0, B, 63):
+            part = tt.tac_simulate(h, gop[lo:lo + 63].contiguous(), grv[lo:lo + 63].contiguous(), want_rank=True)
+            for k in (0, 1, 4, 5, 6, 7, 8):
+                assert torch.equal(got[k][lo:lo + 63], part[k])
+    rows = [0, 63, 64, 199]
+    dep = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    eo, er = oracle_tac_rows(dep, d.recv_ids, op[rows], rv[rows])[:2]
+    assert np.array_equal(got[0][rows].cpu().numpy(), eo) and np.array_equal(got[1][rows].cpu().numpy(), er)
