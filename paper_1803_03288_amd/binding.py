@@ -193,7 +193,7 @@ def simulate(dag: Dag, order: torch.Tensor, op_time: torch.Tensor, recv_time: to
     else:
         assert tuple(order.shape) == (B, R)
         stride = R
-    out = [torch.empty(B, dtype=torch.float64, device="cuda") for _ in range(5)]
+    out = torch.empty((5, B), dtype=torch.float64, device="cuda").unbind(0)       # (rows of one block, as in tac_simulate)
     fn = lib().tictac_simulate_f32 if op_time.dtype == torch.float32 else lib().tictac_simulate
     _check(fn(dag._h, ctypes.c_int32(B), _dev(order), ctypes.c_int32(stride), _dev(op_time), _dev(recv_time),
               *(_dev(o) for o in out), _stream()))

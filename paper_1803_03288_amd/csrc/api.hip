@@ -1346,7 +1346,6 @@ static int simulate_any(const tictac_dag *dag, int32_t B, const int32_t *order, 
     if (!makespan || !eff) { set_error("makespan or eff is NULL"); return TICTAC_ERR_NULL; }
     SimArgs a{B, order, order_stride, op_time, recv_time, makespan, eff, U, L, S};
     a.f32 = f32;
-    HIP_TRY(launch_check_orders(*d, B, order, order_stride, (hipStream_t)stream));
     HIP_TRY(launch_simulate(*d, a, (hipStream_t)stream));
     return TICTAC_OK;
 }
@@ -1393,7 +1392,6 @@ int tictac_simulate_channels(const tictac_dag *dag, int32_t B, int32_t n_channel
     if (!makespan || !eff) { set_error("makespan or eff is NULL"); return TICTAC_ERR_NULL; }
     SimArgs a{B, order, order_stride, op_time, recv_time, makespan, eff, U, L, S};
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(launch_check_orders(*d, B, order, order_stride, s));
     if (d->R == 0) {                      // no transfers: the channels play no role
         HIP_TRY(launch_simulate(*d, a, s));
         return TICTAC_OK;
@@ -1402,6 +1400,7 @@ int tictac_simulate_channels(const tictac_dag *dag, int32_t B, int32_t n_channel
         set_error("%d recvs and %d classes: the several-channel simulation handles at most 512 of each", d->R, d->C);
         return TICTAC_ERR_UNSUPPORTED;
     }
+    HIP_TRY(launch_check_orders(*d, B, order, order_stride, s));
     // the channel table goes to the device through a staging block of the handle
     HIP_TRY(ensure_chan_table(d, channel_of_recv, s));
     const hipError_t e = launch_simulate_channels(*d, a, n_channels, d->d_chan, s);

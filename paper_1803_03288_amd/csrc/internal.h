@@ -245,7 +245,10 @@ hipError_t launch_row_digests(const Dag &d, const int32_t *op_of_col, int32_t *d
 hipError_t launch_class_rows(const Dag &d, const int32_t *op_of_col, const int32_t *first_op, int32_t *mismatch,
                              hipStream_t s);
 hipError_t launch_check_orders(Dag &d, int32_t B, const int32_t *order, int32_t order_stride, hipStream_t s);
+// (launch_simulate checks the orders, on the way or by launch_check_orders)
 hipError_t launch_simulate(Dag &d, const SimArgs &a, hipStream_t s);
+// one lane per sample, for graphs whose rows of 64 samples fit LDS; hipErrorNotSupported: the graph is none of these
+hipError_t launch_simulate_lanes(Dag &d, const SimArgs &a, hipStream_t s);
 // (needs the tables d_send_*; hipErrorNotSupported when the per-sample state does not fit LDS)
 hipError_t launch_simulate_sends(Dag &d, const SimArgs &a, hipStream_t s);
 hipError_t launch_simulate_channels(Dag &d, const SimArgs &a, int32_t n_channels, const int32_t *chan, hipStream_t s);

@@ -761,6 +761,14 @@ hipError_t launch_time_oracle_min(int32_t n_runs, int64_t n, const double *runs,
 hipError_t launch_simulate(Dag &d, const SimArgs &a, hipStream_t s)
 {
     if (a.B == 0) return hipSuccess;
+    {
+        const hipError_t e = launch_simulate_lanes(d, a, s);
+        if (e != hipErrorNotSupported) return e;
+    }
+    {
+        const hipError_t e = launch_check_orders(d, a.B, a.order, a.order_stride, s);
+        if (e != hipSuccess) return e;
+    }
     SimKernelParams p{};
     p.B = a.B; p.R = d.R; p.W = d.W; p.C = d.C; p.N = d.N;
     p.cls_dep = d.d_cls_dep; p.cls_ptr = d.d_cls_ptr; p.cls_cols = d.d_cls_cols;
