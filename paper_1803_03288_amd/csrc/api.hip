@@ -130,51 +130,57 @@ static void *stage(size_t bytes)
     return q;
 }
 
-// Collects host arrays (and device-only reservations) into one device block: one
-// allocation and one host-to-device copy instead of one of each per array.
+// Collects host arrays (and device-only reservations) into one device block: one allocation, one copy of each array
+// into the pinned staging block and one host-to-device copy.  The arrays must live until commit().
 struct Packer {
-    std::vector<char> host;
-    struct Fix { void **dst; size_t off; };
-    std::vector<Fix> fixes;
-    size_t device_only = 0, bytes = 0;              // bytes: of the block, after commit()
+    struct Part { void **dst; const void *src; size_t bytes, off; };
+    std::vector<Part> parts;
+    size_t host_bytes = 0, device_only = 0, bytes = 0;      // bytes: of the block, after commit()
 
     static size_t align(size_t x) { return (x + 255) & ~(size_t)255; }
 
     template <typename T>
-    void add(T **dst, const std::vector<T> &src)
+    void add(T **dst, const T *src, size_t n)
     {
         *dst = nullptr;
-        if (src.empty()) return;
-        const size_t off = align(host.size());
-        host.resize(off + src.size() * sizeof(T));
-        memcpy(host.data() + off, src.data(), src.size() * sizeof(T));
-        fixes.push_back({reinterpret_cast<void **>(dst), off});
+        if (!n) return;
+        host_bytes = align(host_bytes);
+        parts.push_back({reinterpret_cast<void **>(dst), src, n * sizeof(T), host_bytes});
+        host_bytes += n * sizeof(T);
     }
+    template <typename T>
+    void add(T **dst, const std::vector<T> &src) { add(dst, src.data(), src.size()); }
     // space after the copied part that only kernels write; call after the last add()
     template <typename T>
-    void reserve(T **dst, size_t bytes)
+    void reserve(T **dst, size_t n_bytes)
     {
         *dst = nullptr;
-        if (!bytes) return;
-        fixes.push_back({reinterpret_cast<void **>(dst), align(host.size()) + device_only});
-        device_only += align(bytes);
+        if (!n_bytes) return;
+        parts.push_back({reinterpret_cast<void **>(dst), nullptr, n_bytes, align(host_bytes) + device_only});
+        device_only += align(n_bytes);
     }
     hipError_t commit(void **block, hipStream_t s)
     {
         *block = nullptr;
-        const size_t total = align(host.size()) + device_only;
+        const size_t total = align(host_bytes) + device_only;
         if (!total) return hipSuccess;
         hipError_t e = pool_alloc(block, total);
         if (e != hipSuccess) return e;
         bytes = total;
-        for (const Fix &f : fixes) *f.dst = static_cast<char *>(*block) + f.off;
-        if (host.empty()) return hipSuccess;
-        const void *src = host.data();
-        if (void *st = stage(host.size())) {
-            memcpy(st, host.data(), host.size());
-            src = st;
+        std::vector<char> pageable;
+        char *st = static_cast<char *>(stage(host_bytes));
+        if (!st && host_bytes) {
+            pageable.resize(host_bytes);
+            st = pageable.data();
         }
-        return hipMemcpyAsync(*block, src, host.size(), hipMemcpyHostToDevice, s);
+        for (const Part &p : parts) {
+            *p.dst = static_cast<char *>(*block) + p.off;
+            if (p.src) memcpy(st + p.off, p.src, p.bytes);
+        }
+        if (!host_bytes) return hipSuccess;
+        e = hipMemcpyAsync(*block, st, host_bytes, hipMemcpyHostToDevice, s);
+        if (!pageable.empty() && e == hipSuccess) e = hipStreamSynchronize(s);
+        return e;
     }
 };
 
@@ -278,7 +284,8 @@ static void free_dag(Dag *d)
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     const struct { void *p; size_t bytes; } blocks[] = {
         {d->d_graph_block, d->graph_bytes}, {d->d_class_block, d->class_bytes}, {d->d_work, d->work_bytes},
-        {d->d_chan, (size_t)d->R * sizeof(int32_t)}, {d->d_send_block, d->send_bytes}, {d->chain.block, d->chain.bytes}};
+        {d->d_chan, (size_t)d->R * sizeof(int32_t)}, {d->d_send_block, d->send_bytes}, {d->chain.block, d->chain.bytes},
+        {d->d_sliced_block, d->sliced_bytes}};
     for (const auto &b : blocks) {
         if (!b.p) continue;
         if (idle) pool_put(b.p, b.bytes, d->device);
@@ -388,33 +395,30 @@ static void group_digests(const int32_t *digest, int32_t N, int32_t max_members,
         }
 }
 
-static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int32_t R, const int32_t *recv_ids,
-                 hipStream_t s, Dag *d)
+// Levels (longest path from a root, in ops before it) and a topological order of a validated graph.  Graphs whose
+// predecessors all have lower ids (topological: true), as traced graphs have as a rule, need no more than one pass over the
+// edges; `order` stays empty for them unless asked for.  False: the graph has a cycle.
+static bool find_levels(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, bool topological, bool want_order,
+                        std::vector<int32_t> &level, std::vector<int32_t> &order, int32_t &n_levels)
 {
-    // ---- validation (host) ----
-    if (n < 0 || R < 0 || R > n) { set_error("bad sizes: n_ops=%d n_recv=%d", n, R); return TICTAC_ERR_BAD_CSR; }
-    if (!row_ptr) { set_error("pred_row_ptr is NULL"); return TICTAC_ERR_NULL; }
-    if (R > 0 && !recv_ids) { set_error("recv_ids is NULL"); return TICTAC_ERR_NULL; }
-    if (row_ptr[0] != 0) { set_error("pred_row_ptr[0] != 0"); return TICTAC_ERR_BAD_CSR; }
-    for (int32_t v = 0; v < n; ++v)
-        if (row_ptr[v + 1] < row_ptr[v]) { set_error("pred_row_ptr decreases at op %d", v); return TICTAC_ERR_BAD_CSR; }
+    level.assign(n, 0);
+    order.clear();
+    n_levels = 0;
+    if (topological) {
+        for (int32_t v = 0; v < n; ++v) {
+            int32_t l = 0;
+            for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) l = std::max(l, level[col_idx[e]] + 1);
+            level[v] = l;
+            n_levels = std::max(n_levels, l + 1);
+        }
+        if (want_order) {
+            order.resize(n);
+            std::iota(order.begin(), order.end(), 0);
+        }
+        return true;
+    }
     const int32_t E = row_ptr[n];
-    if (E > 0 && !col_idx) { set_error("pred_col_idx is NULL"); return TICTAC_ERR_NULL; }
-    for (int32_t e = 0; e < E; ++e)
-        if (col_idx[e] < 0 || col_idx[e] >= n) { set_error("pred_col_idx[%d]=%d out of range", e, col_idx[e]); return TICTAC_ERR_BAD_CSR; }
-    std::vector<int32_t> recv_of_op(n, -1);
-    for (int32_t i = 0; i < R; ++i) {
-        int32_t v = recv_ids[i];
-        if (v < 0 || v >= n) { set_error("recv_ids[%d]=%d out of range", i, v); return TICTAC_ERR_BAD_CSR; }
-        if (recv_of_op[v] >= 0) { set_error("op %d listed twice in recv_ids", v); return TICTAC_ERR_DUP_RECV; }
-        recv_of_op[v] = i;
-    }
-    for (int32_t i = 0; i < R; ++i) {
-        int32_t v = recv_ids[i];
-        if (row_ptr[v + 1] != row_ptr[v]) { set_error("recv %d (op %d) has predecessors", i, v); return TICTAC_ERR_RECV_NOT_ROOT; }
-    }
-    // ---- levels = longest path from a root (Kahn) ----
-    std::vector<int32_t> sptr(n + 1, 0), sidx(E), waiting(n), level(n, 0), queue;
+    std::vector<int32_t> sptr(n + 1, 0), sidx(E), waiting(n);
     for (int32_t e = 0; e < E; ++e) sptr[col_idx[e] + 1]++;
     for (int32_t v = 0; v < n; ++v) sptr[v + 1] += sptr[v];
     {
@@ -422,29 +426,163 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         for (int32_t v = 0; v < n; ++v)
             for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) sidx[fill[col_idx[e]]++] = v;
     }
-    queue.reserve(n);
+    order.reserve(n);
     for (int32_t v = 0; v < n; ++v) {
         waiting[v] = row_ptr[v + 1] - row_ptr[v];
-        if (waiting[v] == 0) queue.push_back(v);
+        if (waiting[v] == 0) order.push_back(v);
     }
-    int32_t n_levels = 0;
-    for (size_t q = 0; q < queue.size(); ++q) {
-        int32_t u = queue[q];
+    for (size_t q = 0; q < order.size(); ++q) {
+        const int32_t u = order[q];
         n_levels = std::max(n_levels, level[u] + 1);
         for (int32_t e = sptr[u]; e < sptr[u + 1]; ++e) {
-            int32_t v = sidx[e];
+            const int32_t v = sidx[e];
             level[v] = std::max(level[v], level[u] + 1);
-            if (--waiting[v] == 0) queue.push_back(v);
+            if (--waiting[v] == 0) order.push_back(v);
         }
     }
-    if ((int32_t)queue.size() != n) { set_error("the graph has a cycle"); return TICTAC_ERR_CYCLE; }
-    std::vector<int32_t> comp_col(n, -1);
-    {
-        int32_t j = 0;
-        for (int32_t v = 0; v < n; ++v)
-            if (recv_of_op[v] < 0) comp_col[v] = j++;
-    }
+    return (int32_t)order.size() == n;
+}
 
+// Dependency rows of the compute ops as sets: of_op[v] the set of op v (-1 for a recv), sets numbered by their first
+// member in ascending op id, rows [sets][W].  Formed on the host, set by set: an op whose predecessors are compute ops of
+// one set, or whose predecessors' rows all lie within the largest of them, has that set; only the others form a union.
+struct HostSets {
+    std::vector<int32_t> of_op, count;
+    std::vector<uint64_t> rows;
+    int32_t n = 0;
+};
+static void host_sets(int32_t n, int32_t W, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
+                      const std::vector<int32_t> &order, HostSets &h)
+{
+    h.of_op.assign(n, -1);
+    size_t cap = 1024;
+    std::vector<int32_t> slot(cap, -1);
+    std::vector<uint64_t> hash_of;
+    std::vector<uint64_t> tmp(W);
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t v = order.empty() ? i : order[i];
+        if (recv_of_op[v] >= 0) continue;
+        const int32_t beg = row_ptr[v], end = row_ptr[v + 1];
+        int32_t best = -1;
+        bool mixed = false;
+        for (int32_t e = beg; e < end; ++e) {
+            const int32_t c = h.of_op[col_idx[e]];
+            if (c < 0) { mixed = true; continue; }              // a recv
+            if (best < 0) best = c;
+            else if (c != best) {
+                mixed = true;
+                if (h.count[c] > h.count[best]) best = c;
+            }
+        }
+        bool same = best >= 0;
+        if (same && mixed) {
+            const uint64_t *rb = &h.rows[(size_t)best * W];
+            for (int32_t e = beg; e < end && same; ++e) {
+                const int32_t u = col_idx[e], c = h.of_op[u];
+                if (c == best) continue;
+                if (c < 0) {
+                    const int32_t r = recv_of_op[u];
+                    same = (rb[r >> 6] >> (r & 63)) & 1ull;
+                } else {
+                    const uint64_t *rc = &h.rows[(size_t)c * W];
+                    uint64_t more = 0;
+                    for (int32_t w = 0; w < W; ++w) more |= rc[w] & ~rb[w];
+                    same = more == 0;
+                }
+            }
+        }
+        if (same) { h.of_op[v] = best; continue; }
+        std::fill(tmp.begin(), tmp.end(), 0);
+        for (int32_t e = beg; e < end; ++e) {
+            const int32_t u = col_idx[e], c = h.of_op[u];
+            if (c < 0) tmp[recv_of_op[u] >> 6] |= 1ull << (recv_of_op[u] & 63);
+            else for (int32_t w = 0; w < W; ++w) tmp[w] |= h.rows[(size_t)c * W + w];
+        }
+        uint64_t hash = 0x9E3779B97F4A7C15ull;
+        int32_t bits = 0;
+        for (int32_t w = 0; w < W; ++w) {
+            hash += (tmp[w] ^ (tmp[w] >> 31)) * (0xFF51AFD7ED558CCDull + 2 * (uint64_t)w);
+            hash ^= hash >> 29;
+            bits += __builtin_popcountll(tmp[w]);
+        }
+        hash ^= hash >> 32;
+        if ((size_t)h.n * 2 >= cap) {
+            cap *= 4;
+            slot.assign(cap, -1);
+            for (int32_t c = 0; c < h.n; ++c) {
+                size_t q = hash_of[c] & (cap - 1);
+                while (slot[q] >= 0) q = (q + 1) & (cap - 1);
+                slot[q] = c;
+            }
+        }
+        size_t q = hash & (cap - 1);
+        for (; slot[q] >= 0; q = (q + 1) & (cap - 1))
+            if (hash_of[slot[q]] == hash && (W == 0 || memcmp(&h.rows[(size_t)slot[q] * W], tmp.data(), (size_t)W * 8) == 0)) break;
+        if (slot[q] < 0) {
+            slot[q] = h.n++;
+            hash_of.push_back(hash);
+            h.count.push_back(bits);
+            h.rows.insert(h.rows.end(), tmp.begin(), tmp.end());
+        }
+        h.of_op[v] = slot[q];
+    }
+    if (order.empty()) return;
+    // numbered by first member
+    std::vector<int32_t> to(h.n, -1), count(h.n);
+    std::vector<uint64_t> rows(h.rows.size());
+    int32_t k = 0;
+    for (int32_t v = 0; v < n; ++v) {
+        int32_t &c = h.of_op[v];
+        if (c < 0) continue;
+        if (to[c] < 0) {
+            to[c] = k;
+            count[k] = h.count[c];
+            std::copy(h.rows.begin() + (size_t)c * W, h.rows.begin() + (size_t)(c + 1) * W, rows.begin() + (size_t)k * W);
+            ++k;
+        }
+        c = to[c];
+    }
+    h.count.swap(count);
+    h.rows.swap(rows);
+}
+
+// The same classes from sets of ops.  cls_of_set: the first class of every set.
+static void group_sets(const HostSets &h, const std::vector<int32_t> &recv_of_op, int32_t N, int32_t W, int32_t max_members,
+                       std::vector<uint64_t> &cls_dep, std::vector<int32_t> &cls_ptr, std::vector<int32_t> &cls_cols,
+                       int32_t &n_distinct, std::vector<int32_t> &cls_of_set)
+{
+    std::vector<int32_t> start(h.n + 1, 0);
+    for (int32_t c : h.of_op)
+        if (c >= 0) ++start[c + 1];
+    for (int32_t c = 0; c < h.n; ++c) start[c + 1] += start[c];
+    cls_cols.resize(N);
+    {
+        std::vector<int32_t> fill(start.begin(), start.end() - 1);
+        int32_t j = 0;
+        for (int32_t c : h.of_op)
+            if (c >= 0) cls_cols[fill[c]++] = j++;
+    }
+    n_distinct = h.n;
+    cls_of_set.resize(h.n);
+    cls_ptr.reserve(h.n + 8);
+    cls_dep.reserve(h.rows.size() + (size_t)8 * W);
+    cls_ptr.assign(1, 0);
+    for (int32_t c = 0; c < h.n; ++c) {
+        cls_of_set[c] = (int32_t)cls_ptr.size() - 1;
+        for (int32_t k = start[c]; k < start[c + 1]; k += max_members) {
+            cls_ptr.push_back(std::min(start[c + 1], k + max_members));
+            cls_dep.insert(cls_dep.end(), h.rows.begin() + (size_t)c * W, h.rows.begin() + (size_t)(c + 1) * W);
+        }
+    }
+}
+
+// ---- the tables of the propagation kernels (k1_propagate.hip) ----
+// order: the ops in topological order; level: longest path from a root.  own_dep: the handle's op.dep is made by these
+// kernels (large graphs), so its block holds op.dep as well.
+static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
+                                 const std::vector<int32_t> &level, const std::vector<int32_t> &order, bool own_dep, hipStream_t s)
+{
+    const int32_t n = d->n, E = d->E, n_levels = d->n_levels;
     // ---- condensed graph: chains of single-predecessor compute ops collapse onto their head ----
     // rep[v] = the node whose dep op v has (itself if v is a node); recvs are not nodes, they
     // enter a node as single bits.
@@ -454,7 +592,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     std::vector<int32_t> node_ops;                       // in topological order
     std::vector<int32_t> node_index(n, -1);              // op -> index into node_ops
     std::vector<int32_t> tmp;
-    for (int32_t v : queue) {
+    for (int32_t v : order) {
         if (recv_of_op[v] >= 0) continue;
         tmp.assign(col_idx + row_ptr[v], col_idx + row_ptr[v + 1]);
         std::sort(tmp.begin(), tmp.end());
@@ -515,22 +653,19 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     std::vector<int32_t> src(n);
     for (int32_t v = 0; v < n; ++v) src[v] = recv_of_op[v] >= 0 ? ~recv_of_op[v] : rep[v];
 
-    d->n = n; d->R = R; d->W = (R + 63) / 64; d->N = n - R; d->E = E;
-    d->h_row_ptr.assign(row_ptr, row_ptr + n + 1);
-    d->h_col_idx.assign(col_idx, col_idx + E);
-    d->h_recv_ids.assign(recv_ids, recv_ids + R);
-    d->n_levels = n_levels;
     d->M = M; d->n_node_levels = n_node_levels; d->max_node_level_width = max_width;
-    HIP_TRY(hipGetDevice(&d->device));
-
-    // ---- upload and propagate ----
+    // ---- tables ----
     // the ops whose rows are copies (of a recv's single bit, or of the row of the node the op collapses onto)
     std::vector<int32_t> copied;
     for (int32_t v = 0; v < n; ++v)
         if (src[v] != v) { copied.push_back(v); copied.push_back(src[v]); }
     d->n_copied = (int32_t)(copied.size() / 2);
     Packer graph;
-    graph.add(&d->d_recv_of_op, recv_of_op);
+    std::vector<Dag::FastRec> lrecs, frecs;
+    std::vector<Dag::QuadRec> qrecs;
+    std::vector<int32_t> chunk_end, qfovf, left, lfovf, fovf, op_of_col;
+    const std::vector<int32_t> zeros(64, 0);
+    if (own_dep) graph.add(&d->d_recv_of_op, recv_of_op);
     graph.add(&d->d_nodes, nodes);
     graph.add(&d->d_ovf_idx, ovf_idx);
     graph.add(&d->d_nlvl_ptr, nlvl_ptr);
@@ -563,7 +698,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         threads = threads < 64 ? 64 : (threads > 1024 ? 1024 : (threads + 63) / 64 * 64);
         d->k1_threads = threads;
         const int32_t per_pass = threads / d->k1_wc;
-        std::vector<int32_t> chunk_end(n_node_levels, 0);
+        chunk_end.assign(n_node_levels, 0);
         for (int32_t l0 = 0; l0 < n_node_levels;) {
             int32_t l1 = l0 + 1;
             while (l1 < n_node_levels && l1 - l0 < 64 && nlvl_ptr[l1 + 1] - nlvl_ptr[l0] <= 4 * per_pass) ++l1;
@@ -737,9 +872,6 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         };
         if (q_ring > 0) {
             std::vector<Dag::FastRec> unused;
-            std::vector<Dag::QuadRec> qrecs;
-            std::vector<int32_t> qfovf;
-            std::vector<int32_t> left;
             level_major(true, q_slots, q_ring, unused, qrecs, qfovf, left);
             graph.add(&d->d_qrecs, qrecs);
             graph.add(&d->d_qfovf, qfovf);
@@ -748,9 +880,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
             d->n_q_copied = (int32_t)(left.size() / 2);
         }
         if (lring > 0) {
-            std::vector<Dag::FastRec> lrecs;
             std::vector<Dag::QuadRec> unused;
-            std::vector<int32_t> lfovf;
             std::vector<int32_t> none_left;
             level_major(false, per_pass, lring, lrecs, unused, lfovf, none_left);
             graph.add(&d->d_lrecs, lrecs);
@@ -758,8 +888,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
             d->lfovf_len = (int32_t)lfovf.size();
         } else if (max_width <= per_pass) {
             const int32_t row_bytes = d->k1_wc * 8, zero_row = ring * row_bytes;
-            std::vector<Dag::FastRec> frecs(M);
-            std::vector<int32_t> fovf;
+            frecs.resize(M);
             for (int32_t l = 0; l < n_node_levels; ++l)
                 for (int32_t q = nlvl_ptr[l]; q < nlvl_ptr[l + 1]; ++q) {
                     const Dag::NodeRec &r = nodes[q];
@@ -797,32 +926,113 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         }
     }
     graph.add(&d->d_copied, copied);
-    std::vector<int32_t> op_of_col(d->N);
-    for (int32_t v = 0; v < n; ++v)
-        if (comp_col[v] >= 0) op_of_col[comp_col[v]] = v;
-    graph.add(&d->d_op_of_col, op_of_col);
     const size_t dep_words = (size_t)n * d->W;
-    graph.reserve(&d->d_dep, dep_words * 8);
+    if (own_dep) {
+        op_of_col.reserve(d->N);
+        for (int32_t v = 0; v < n; ++v)
+            if (recv_of_op[v] < 0) op_of_col.push_back(v);
+        graph.add(&d->d_op_of_col, op_of_col);
+        graph.add(&d->d_bad_order, zeros);
+        graph.reserve(&d->d_dep, dep_words * 8);
+    }
     if (d->k1_lring > 0)
         graph.reserve(&d->d_k1_sink, (size_t)((d->W + d->k1_wc - 1) / d->k1_wc) * d->k1_threads * 8);
     if (d->k1_q_ring > 0) graph.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
-    graph.reserve(&d->d_bad_order, 256);
     // (sized for the copy back of the rows as well, so that the block is not replaced while a copy is under way)
-    (void)stage(std::max(graph.host.size(), dep_words * 8));
+    if (own_dep) (void)stage(std::max(graph.host_bytes, dep_words * 8));
     HIP_TRY(graph.commit(&d->d_graph_block, s));
     d->graph_bytes = graph.bytes;
-    HIP_TRY(hipMemsetAsync(d->d_bad_order, 0, 256, s));
-    if (dep_words) HIP_TRY(launch_propagate(*d, s));
+    d->prop_tables = true;
+    // (the staging block is free again, and the arrays may go, once the copy is done)
+    HIP_TRY(hipStreamSynchronize(s));
+    return TICTAC_OK;
+}
+
+static std::mutex g_tables_mutex;       // of the tables that a handle's first call of a kind makes
+
+// the tables of the propagation kernels of a handle whose op.dep came from the host's rows, made at the first call that
+// runs those kernels
+static int ensure_propagate_tables(Dag *d, hipStream_t s)
+{
+    std::lock_guard<std::mutex> lock(g_tables_mutex);
+    if (d->prop_tables) return TICTAC_OK;
+    std::vector<int32_t> recv_of_op(d->n, -1), level, order;
+    for (int32_t i = 0; i < d->R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
+    int32_t n_levels = 0;
+    (void)find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), false, true, level, order, n_levels);
+    return make_propagate_tables(d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, false, s);
+}
+
+// The line between the rows formed on the host and by the kernels: on layered graphs of 11 000 ops and 16 words (0.6 million
+// words) the host part of a build takes 2.1 ms one way and 3.7 ms the other, at 21 000 ops (1.2 million) 3.7 and 6.8, at 22 000
+// ops of 32 words (2.6 million) 12.2 and 11.3, without the kernels' own time.
+constexpr int64_t kHostRowWords = (int64_t)1 << 21;
+
+static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int32_t R, const int32_t *recv_ids,
+                 hipStream_t s, Dag *d)
+{
+    // ---- validation (host) ----
+    if (n < 0 || R < 0 || R > n) { set_error("bad sizes: n_ops=%d n_recv=%d", n, R); return TICTAC_ERR_BAD_CSR; }
+    if (!row_ptr) { set_error("pred_row_ptr is NULL"); return TICTAC_ERR_NULL; }
+    if (R > 0 && !recv_ids) { set_error("recv_ids is NULL"); return TICTAC_ERR_NULL; }
+    if (row_ptr[0] != 0) { set_error("pred_row_ptr[0] != 0"); return TICTAC_ERR_BAD_CSR; }
+    for (int32_t v = 0; v < n; ++v)
+        if (row_ptr[v + 1] < row_ptr[v]) { set_error("pred_row_ptr decreases at op %d", v); return TICTAC_ERR_BAD_CSR; }
+    const int32_t E = row_ptr[n];
+    if (E > 0 && !col_idx) { set_error("pred_col_idx is NULL"); return TICTAC_ERR_NULL; }
+    bool topological = true;
+    for (int32_t v = 0; v < n; ++v)
+        for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) {
+            if (col_idx[e] < 0 || col_idx[e] >= n) { set_error("pred_col_idx[%d]=%d out of range", e, col_idx[e]); return TICTAC_ERR_BAD_CSR; }
+            topological &= col_idx[e] < v;
+        }
+    std::vector<int32_t> recv_of_op(n, -1);
+    for (int32_t i = 0; i < R; ++i) {
+        int32_t v = recv_ids[i];
+        if (v < 0 || v >= n) { set_error("recv_ids[%d]=%d out of range", i, v); return TICTAC_ERR_BAD_CSR; }
+        if (recv_of_op[v] >= 0) { set_error("op %d listed twice in recv_ids", v); return TICTAC_ERR_DUP_RECV; }
+        recv_of_op[v] = i;
+    }
+    for (int32_t i = 0; i < R; ++i) {
+        int32_t v = recv_ids[i];
+        if (row_ptr[v + 1] != row_ptr[v]) { set_error("recv %d (op %d) has predecessors", i, v); return TICTAC_ERR_RECV_NOT_ROOT; }
+    }
+    d->n = n; d->R = R; d->W = (R + 63) / 64; d->N = n - R; d->E = E;
+    // Small graphs (few words in the rows of all ops and predecessors) need no trip to the device and back before their ops
+    // can be grouped: the rows are formed here, and the device gets op.dep from those of the sets.  Larger graphs are
+    // propagated by the kernels of k1_propagate.hip.
+    const bool on_host = ((int64_t)n + E) * std::max(d->W, 1) <= kHostRowWords && !getenv("TICTAC_GROUP_ON_HOST");
+    std::vector<int32_t> level, order;
+    if (!find_levels(n, row_ptr, col_idx, topological, !on_host, level, order, d->n_levels)) {
+        set_error("the graph has a cycle");
+        return TICTAC_ERR_CYCLE;
+    }
+    d->h_row_ptr.assign(row_ptr, row_ptr + n + 1);
+    d->h_col_idx.assign(col_idx, col_idx + E);
+    d->h_recv_ids.assign(recv_ids, recv_ids + R);
+    HIP_TRY(hipGetDevice(&d->device));
+
+    HostSets sets;
+    if (on_host) {
+        host_sets(n, d->W, row_ptr, col_idx, recv_of_op, order, sets);
+    } else {
+        const int rc = make_propagate_tables(d, row_ptr, col_idx, recv_of_op, level, order, true, s);
+        if (rc != TICTAC_OK) return rc;
+        if ((size_t)n * d->W) HIP_TRY(launch_propagate(*d, s));
+    }
+    const size_t dep_words = (size_t)n * d->W;
 
     // ---- classes of identical rows among the compute ops (a lambda: done again on the host when the device's
     // grouping cannot be used; returns a status, or 1 for "again, from the rows") ----
     auto classes = [&](const bool on_device) -> int {
+    const bool from_sets = on_host;
     // Large graphs (8 MB of rows or more) are grouped without bringing the rows to the host: the device hashes
     // every row (128 bits, with the number of set bits and the lowest one), the host groups the hashes, and the
     // device forms the class rows and checks every op's row against its class (on a mismatch, which two
     // different rows with one hash would cause, everything below is done again from the rows themselves).
     std::vector<uint64_t> rows, cls_dep, depT;
-    std::vector<int32_t> cls_ptr, cls_cols, cnt0, first_op, lowest;
+    std::vector<int32_t> cls_ptr, cls_cols, cnt0, first_op, lowest, cls_of_set, op_src, op_of_col;
+    const std::vector<int32_t> zeros(64, 0);
     // only classes far larger than a lane's fair share of the ops are split
     const int32_t max_members = std::min(256, std::max(16, (d->N + 63) / 64));
     if (on_device) {
@@ -843,12 +1053,15 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         d->Cpad = (d->C + 63) / 64 * 64;
         if (d->R <= 1024 && d->C <= 512) return 1;      // the small-graph kernels want tables made from the rows
         cnt0.resize(d->C); first_op.resize(d->C); lowest.resize(d->C);
+        op_of_col.reserve(d->N);
+        for (int32_t v = 0; v < n; ++v)
+            if (recv_of_op[v] < 0) op_of_col.push_back(v);
         for (int32_t c = 0; c < d->C; ++c) {
             cnt0[c] = dg[(size_t)first_col[c] * 8 + 4];
             lowest[c] = dg[(size_t)first_col[c] * 8 + 5];
             first_op[c] = op_of_col[first_col[c]];
         }
-    } else {
+    } else if (!from_sets) {
         rows.resize((size_t)d->N * d->W);
         if (!rows.empty()) {
             std::vector<uint64_t> pageable;
@@ -859,11 +1072,14 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
             }
             HIP_TRY(hipMemcpyAsync(all, d->d_dep, dep_words * 8, hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
-            for (int32_t v = 0; v < n; ++v)
-                if (comp_col[v] >= 0)
-                    memcpy(&rows[(size_t)comp_col[v] * d->W], &all[(size_t)v * d->W], (size_t)d->W * 8);
+            for (int32_t v = 0, j = 0; v < n; ++v)
+                if (recv_of_op[v] < 0) memcpy(&rows[(size_t)j++ * d->W], &all[(size_t)v * d->W], (size_t)d->W * 8);
         }
         group_classes(rows, d->N, d->W, max_members, cls_dep, cls_ptr, cls_cols, d->C_distinct);
+    } else {
+        group_sets(sets, recv_of_op, d->N, d->W, max_members, cls_dep, cls_ptr, cls_cols, d->C_distinct, cls_of_set);
+    }
+    if (!on_device) {
         d->C = (int32_t)cls_ptr.size() - 1;
         d->Cpad = (d->C + 63) / 64 * 64;
         cnt0.assign(d->C, 0);
@@ -917,9 +1133,6 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         isum[c] = (int32_t)sum;
     }
     Packer cls;
-    cls.host.reserve((cls_dep.size() + depT.size()) * 8 +
-                     (isum.size() + run_ptr.size() + 2 * run_lo.size() + cnt0.size() + cls_ptr.size() + cls_cols.size() +
-                      (size_t)d->N) * 4 + 16 * 256);
     cls.add(&d->d_cls_isum, isum);      // index sums stay below 2^20 (nothing when the runs are not built)
     d->max_members = 0;
     for (int32_t c = 0; c < d->C; ++c) d->max_members = std::max(d->max_members, cls_ptr[c + 1] - cls_ptr[c]);
@@ -939,91 +1152,24 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     for (int32_t c = 0; c < d->C; ++c)
         for (int32_t m = cls_ptr[c]; m < cls_ptr[c + 1]; ++m) col_cls[cls_cols[m]] = c;
     cls.add(&d->d_col_cls, col_cls);
-    if (!on_device && d->C <= 512 + kChainMaxGates) { d->h_cls_dep = cls_dep; d->h_col_cls = col_cls; }
+    if (!on_device && d->C <= 512 + kChainMaxGates) d->h_cls_dep = cls_dep;
 
-    // ---- tables of the bit-sliced TAC kernel (see internal.h), for graphs with many classes ----
-    const int32_t CW = (d->C + 63) / 64;
-    const bool want_sliced = d->R >= 1 && d->W <= 64 && CW <= 15 * 64 * 4 && !(d->C <= 8 * 64 && d->W <= 6) &&
-                             !tac_small_graph(d->R, d->W, d->C);
-    if (want_sliced) {
-        d->CW = CW;
-        d->CWpad = (CW + 15) / 16 * 16;
-        // parents: among the classes of the compute predecessors of an op, those with a strictly smaller dep
-        // that holds two recvs or more; the two largest are kept
-        std::vector<int32_t> par((size_t)d->C * 2, -1);
-        for (int32_t v = 0; v < n; ++v) {
-            if (comp_col[v] < 0) continue;
-            const int32_t cv = col_cls[comp_col[v]];
-            for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) {
-                const int32_t u = col_idx[e];
-                if (comp_col[u] < 0) continue;
-                const int32_t cu = col_cls[comp_col[u]];
-                if (cnt0[cu] < 2 || cnt0[cu] >= cnt0[cv]) continue;
-                int32_t *pv = &par[(size_t)cv * 2];
-                if (pv[0] == cu || pv[1] == cu) continue;
-                if (pv[0] < 0 || cnt0[cu] > cnt0[pv[0]]) { pv[1] = pv[0]; pv[0] = cu; }
-                else if (pv[1] < 0 || cnt0[cu] > cnt0[pv[1]]) pv[1] = cu;
-            }
-        }
-        std::vector<uint64_t> ndom0((size_t)d->CWpad * 2, 0);
-        std::vector<int32_t> nchild(d->C, 0);
+    // what the tables of the bit-sliced TAC kernel are made from, when it is first run
+    d->h_cls_lowest = std::move(lowest);
+    if (!on_device) {
+        d->h_cls_lowest.assign(d->C, -1);
         for (int32_t c = 0; c < d->C; ++c)
-            for (int j = 0; j < 2; ++j) {
-                const int32_t u = par[(size_t)c * 2 + j];
-                if (u < 0) continue;
-                ndom0[(size_t)c >> 5] += 1ull << ((c & 31) * 2);
-                ++nchild[u];
-            }
-        std::vector<int32_t> cptr(d->C + 1, 0);
-        for (int32_t c = 0; c < d->C; ++c) cptr[c + 1] = cptr[c] + nchild[c];
-        std::vector<int32_t> cidx(cptr[d->C]), cfill(cptr.begin(), cptr.end() - 1);
-        for (int32_t c = 0; c < d->C; ++c)
-            for (int j = 0; j < 2; ++j) {
-                const int32_t u = par[(size_t)c * 2 + j];
-                if (u >= 0) cidx[cfill[u]++] = c;
-            }
-        std::vector<int4> crec(d->C);
-        std::vector<int32_t> child_ovf;
-        for (int32_t c = 0; c < d->C; ++c) {
-            const int32_t nc = nchild[c], *ch = cidx.data() + cptr[c];
-            int4 r = make_int4(nc, -1, -1, -1);
-            if (nc >= 1) r.y = ch[0];
-            if (nc >= 2) r.z = ch[1];
-            if (nc == 3) r.w = ch[2];
-            if (nc > 3) {
-                r.w = (int32_t)child_ovf.size();
-                child_ovf.insert(child_ovf.end(), ch + 2, ch + nc);
-            }
-            crec[c] = r;
-        }
-        // classes that depend on one recv (by recv, ascending class) and on none
-        std::vector<int32_t> single_ptr(d->R + 1, 0), single_cls, empty_cls, first_recv(d->C, -1);
-        for (int32_t c = 0; c < d->C; ++c) {
-            if (cnt0[c] == 0) empty_cls.push_back(c);
-            if (cnt0[c] != 1) continue;
-            if (on_device) first_recv[c] = lowest[c];
-            for (int32_t w = 0; !on_device && w < d->W; ++w)
-                if (const uint64_t x = cls_dep[(size_t)c * d->W + w]) { first_recv[c] = w * 64 + __builtin_ctzll(x); break; }
-            single_ptr[first_recv[c] + 1]++;
-        }
-        for (int32_t r = 0; r < d->R; ++r) single_ptr[r + 1] += single_ptr[r];
-        single_cls.resize(single_ptr[d->R]);
-        {
-            std::vector<int32_t> fill(single_ptr.begin(), single_ptr.end() - 1);
-            for (int32_t c = 0; c < d->C; ++c)
-                if (cnt0[c] == 1) single_cls[fill[first_recv[c]]++] = c;
-        }
-        d->n_empty_cls = (int32_t)empty_cls.size();
-        cls.add(&d->d_ndom0, ndom0);
-        cls.add(&d->d_cls_par, par);
-        cls.add(&d->d_crec, crec);
-        cls.add(&d->d_child_ovf, child_ovf);
-        cls.add(&d->d_single_ptr, single_ptr);
-        cls.add(&d->d_single_cls, single_cls);
-        cls.add(&d->d_empty_cls, empty_cls);
-        cls.reserve(&d->d_colbits, (size_t)d->R * d->CWpad * 8);
-        cls.reserve(&d->d_planes0, (size_t)13 * d->CWpad * 8);
-        cls.reserve(&d->d_live0, (size_t)d->CWpad * 8);
+            for (int32_t w = 0; w < d->W; ++w)
+                if (const uint64_t x = cls_dep[(size_t)c * d->W + w]) { d->h_cls_lowest[c] = w * 64 + __builtin_ctzll(x); break; }
+    }
+    if (from_sets) {
+        // where op.dep of every op comes from: a class, or (~i) the bit of recv i
+        op_src.resize(n);
+        for (int32_t v = 0; v < n; ++v) op_src[v] = recv_of_op[v] >= 0 ? ~recv_of_op[v] : cls_of_set[sets.of_op[v]];
+        cls.add(&d->d_op_src, op_src);
+        if (R > 1024 || d->C > 8192) cls.add(&d->d_recv_of_op, recv_of_op);        // (TIC from the rows of the ops)
+        cls.add(&d->d_bad_order, zeros);
+        cls.reserve(&d->d_dep, dep_words * 8);
     }
     if (on_device) {
         cls.reserve(&d->d_cls_dep, (size_t)d->C * d->W * 8);
@@ -1031,19 +1177,21 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     }
     HIP_TRY(cls.commit(&d->d_class_block, s));
     d->class_bytes = cls.bytes;
+    if (from_sets && dep_words) HIP_TRY(launch_expand_sets(*d, s));
     int32_t *mismatch = d->d_bad_order + 1;         // (a second word of the zeroed flag block)
     if (on_device) HIP_TRY(launch_class_rows(*d, d->d_op_of_col, d->d_cls_first_op, mismatch, s));
-    if (want_sliced) HIP_TRY(launch_sliced_tables(*d, s));
     int32_t differs = 0;
     if (on_device) HIP_TRY(hipMemcpyAsync(&differs, mismatch, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));   // host vectors go out of scope; the handle is complete
+    d->h_col_cls = std::move(col_cls);
+    d->h_cls_cnt0 = std::move(cnt0);
     if (differs) {
         HIP_TRY(hipMemsetAsync(mismatch, 0, sizeof(int32_t), s));
         return 1;
     }
     return TICTAC_OK;
     };
-    int rc = classes(dep_words * 8 >= ((size_t)8 << 20) && d->N > 0 && !getenv("TICTAC_GROUP_ON_HOST"));
+    int rc = classes(dep_words * 8 >= ((size_t)8 << 20) && d->N > 0 && !on_host && !getenv("TICTAC_GROUP_ON_HOST"));
     if (rc == 1) {
         if (d->d_class_block) {
             HIP_TRY(hipStreamSynchronize(s));
@@ -1055,8 +1203,111 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     return rc;
 }
 
+static std::vector<int32_t> classes_of_ops(const Dag *d)
+{
+    std::vector<int32_t> cls_of_op(d->n, 0);
+    for (int32_t r : d->h_recv_ids) cls_of_op[r] = -1;
+    for (int32_t v = 0, j = 0; v < d->n; ++v)
+        if (cls_of_op[v] >= 0) cls_of_op[v] = d->h_col_cls[j++];
+    return cls_of_op;
+}
+
+hipError_t ensure_sliced_tables(Dag *d, hipStream_t s)
+{
+    std::lock_guard<std::mutex> lock(g_tables_mutex);
+    if (d->sliced_tried) return hipSuccess;
+    d->sliced_tried = true;
+    const int32_t CW = (d->C + 63) / 64;
+    if (d->R < 1 || d->W > 64 || CW > 15 * 64 * 4) return hipSuccess;
+    const std::vector<int32_t> cls_of_op = classes_of_ops(d), &cnt0 = d->h_cls_cnt0;
+    Packer cls;
+    d->CW = CW;
+    d->CWpad = (CW + 15) / 16 * 16;
+    // parents: among the classes of the compute predecessors of an op, those with a strictly smaller dep
+    // that holds two recvs or more; the two largest are kept
+    std::vector<int32_t> par((size_t)d->C * 2, -1);
+    for (int32_t v = 0; v < d->n; ++v) {
+        if (cls_of_op[v] < 0) continue;
+        const int32_t cv = cls_of_op[v];
+        for (int32_t e = d->h_row_ptr[v]; e < d->h_row_ptr[v + 1]; ++e) {
+            const int32_t u = d->h_col_idx[e];
+            if (cls_of_op[u] < 0) continue;
+            const int32_t cu = cls_of_op[u];
+            if (cnt0[cu] < 2 || cnt0[cu] >= cnt0[cv]) continue;
+            int32_t *pv = &par[(size_t)cv * 2];
+            if (pv[0] == cu || pv[1] == cu) continue;
+            if (pv[0] < 0 || cnt0[cu] > cnt0[pv[0]]) { pv[1] = pv[0]; pv[0] = cu; }
+            else if (pv[1] < 0 || cnt0[cu] > cnt0[pv[1]]) pv[1] = cu;
+        }
+    }
+    std::vector<uint64_t> ndom0((size_t)d->CWpad * 2, 0);
+    std::vector<int32_t> nchild(d->C, 0);
+    for (int32_t c = 0; c < d->C; ++c)
+        for (int j = 0; j < 2; ++j) {
+            const int32_t u = par[(size_t)c * 2 + j];
+            if (u < 0) continue;
+            ndom0[(size_t)c >> 5] += 1ull << ((c & 31) * 2);
+            ++nchild[u];
+        }
+    std::vector<int32_t> cptr(d->C + 1, 0);
+    for (int32_t c = 0; c < d->C; ++c) cptr[c + 1] = cptr[c] + nchild[c];
+    std::vector<int32_t> cidx(cptr[d->C]), cfill(cptr.begin(), cptr.end() - 1);
+    for (int32_t c = 0; c < d->C; ++c)
+        for (int j = 0; j < 2; ++j) {
+            const int32_t u = par[(size_t)c * 2 + j];
+            if (u >= 0) cidx[cfill[u]++] = c;
+        }
+    std::vector<int4> crec(d->C);
+    std::vector<int32_t> child_ovf;
+    for (int32_t c = 0; c < d->C; ++c) {
+        const int32_t nc = nchild[c], *ch = cidx.data() + cptr[c];
+        int4 r = make_int4(nc, -1, -1, -1);
+        if (nc >= 1) r.y = ch[0];
+        if (nc >= 2) r.z = ch[1];
+        if (nc == 3) r.w = ch[2];
+        if (nc > 3) {
+            r.w = (int32_t)child_ovf.size();
+            child_ovf.insert(child_ovf.end(), ch + 2, ch + nc);
+        }
+        crec[c] = r;
+    }
+    // classes that depend on one recv (by recv, ascending class) and on none
+    std::vector<int32_t> single_ptr(d->R + 1, 0), single_cls, empty_cls, first_recv(d->C, -1);
+    for (int32_t c = 0; c < d->C; ++c) {
+        if (cnt0[c] == 0) empty_cls.push_back(c);
+        if (cnt0[c] != 1) continue;
+        first_recv[c] = d->h_cls_lowest[c];
+        single_ptr[first_recv[c] + 1]++;
+    }
+    for (int32_t r = 0; r < d->R; ++r) single_ptr[r + 1] += single_ptr[r];
+    single_cls.resize(single_ptr[d->R]);
+    {
+        std::vector<int32_t> fill(single_ptr.begin(), single_ptr.end() - 1);
+        for (int32_t c = 0; c < d->C; ++c)
+            if (cnt0[c] == 1) single_cls[fill[first_recv[c]]++] = c;
+    }
+    d->n_empty_cls = (int32_t)empty_cls.size();
+    cls.add(&d->d_ndom0, ndom0);
+    cls.add(&d->d_cls_par, par);
+    cls.add(&d->d_crec, crec);
+    cls.add(&d->d_child_ovf, child_ovf);
+    cls.add(&d->d_single_ptr, single_ptr);
+    cls.add(&d->d_single_cls, single_cls);
+    cls.add(&d->d_empty_cls, empty_cls);
+    cls.reserve(&d->d_colbits, (size_t)d->R * d->CWpad * 8);
+    cls.reserve(&d->d_planes0, (size_t)13 * d->CWpad * 8);
+    cls.reserve(&d->d_live0, (size_t)d->CWpad * 8);
+    hipError_t e = cls.commit(&d->d_sliced_block, s);
+    if (e != hipSuccess) return e;
+    d->sliced_bytes = cls.bytes;
+    e = launch_sliced_tables(*d, s);
+    if (e != hipSuccess) return e;
+    return hipStreamSynchronize(s);                 // the copy came out of `cls` or of the staging block
+}
+
 hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
 {
+    std::lock_guard<std::mutex> lock(g_tables_mutex);
     ChainTables &c = d->chain;
     if (c.tried) return hipSuccess;
     c.tried = true;
@@ -1179,6 +1430,8 @@ int tictac_dag_recompute_deps(tictac_dag *dag, tictac_stream stream)
 {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = reinterpret_cast<Dag *>(dag);
+    const int rc = ensure_propagate_tables(d, (hipStream_t)stream);
+    if (rc != TICTAC_OK) return rc;
     HIP_TRY(launch_propagate(*d, (hipStream_t)stream));
     return TICTAC_OK;
 }
@@ -1192,6 +1445,10 @@ int tictac_dag_recompute_deps_batch(tictac_dag *const *dags, int32_t n_dags, tic
         if (!dags[g]) { set_error("dags[%d] is NULL", g); return TICTAC_ERR_NULL; }
     Dag *const *ds = reinterpret_cast<Dag *const *>(dags);
     hipStream_t s = (hipStream_t)stream;
+    for (int32_t g = 0; g < n_dags; ++g) {
+        const int rc = ensure_propagate_tables(ds[g], s);
+        if (rc != TICTAC_OK) return rc;
+    }
     HIP_TRY(ensure_workspace(ds[0], propagate_batch_staging_bytes(n_dags)));
     const hipError_t e = launch_propagate_batch(ds, n_dags, ds[0]->d_work, s);
     if (e == hipErrorNotSupported) {

@@ -103,6 +103,8 @@ struct Dag {
     // the ops whose rows are copies, as pairs (op, ~i for recv i or the op id of the node whose row it has)
     int32_t *d_copied = nullptr;    // [n_copied][2]
     int32_t n_copied = 0;
+    bool prop_tables = false;       // the tables above exist
+    int32_t *d_op_src = nullptr;    // [n] (rows formed on the host) the class whose row op v has, or ~i: the bit of recv i
     // op.dep
     uint64_t *d_dep = nullptr;      // [n][W]
 
@@ -165,11 +167,17 @@ struct Dag {
     ChainTables chain;
     std::vector<uint64_t> h_cls_dep;    // [C][W]   (small graphs only)
     std::vector<int32_t> h_col_cls;     // [N]
+    // bit-sliced TAC: its tables are made at the first call that takes it, from |dep| and the lowest recv of every class
+    bool sliced_tried = false;
+    void *d_sliced_block = nullptr;
+    size_t sliced_bytes = 0;
+    std::vector<int32_t> h_cls_cnt0, h_cls_lowest;
 };
 
 hipError_t ensure_workspace(Dag *d, size_t bytes);
 // the tables of the chain form, made at the first call; d->chain.ok says whether the graph has that form
 hipError_t ensure_chain_tables(Dag *d, hipStream_t s);
+hipError_t ensure_sliced_tables(Dag *d, hipStream_t s);
 
 // Number of compute units of a device and the number of workgroups of a kernel that fit one,
 // asked of the runtime once and remembered (the queries cost microseconds on every launch
@@ -184,6 +192,8 @@ hipError_t cached_blocks_per_cu(int *per_cu, const void *kernel, int threads, si
 
 // op.dep for every op (Sec. 4.1)
 hipError_t launch_propagate(const Dag &d, hipStream_t s);
+// op.dep from cls_dep and d_op_src
+hipError_t launch_expand_sets(const Dag &d, hipStream_t s);
 // the same for G graphs of one launch shape in one launch; staging: device memory of propagate_batch_staging_bytes(G)
 size_t propagate_batch_staging_bytes(int G);
 hipError_t launch_propagate_batch(Dag *const *ds, int G, void *staging, hipStream_t s);

@@ -955,4 +955,22 @@ hipError_t launch_propagate(const Dag &d, hipStream_t s)
     return hipGetLastError();
 }
 
+// op.dep of graphs whose rows were formed on the host: a thread per word
+__global__ void __launch_bounds__(256)
+expand_sets_kernel(int32_t n, int32_t W, const int32_t *__restrict__ src, const uint64_t *__restrict__ cls_dep, uint64_t *__restrict__ dep)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= (uint32_t)n * (uint32_t)W) return;
+    const int v = (int)(i / (uint32_t)W), w = (int)(i % (uint32_t)W), c = src[v];
+    dep[i] = c >= 0 ? cls_dep[(size_t)c * W + w] : ((~c >> 6) == w ? 1ull << (~c & 63) : 0ull);
+}
+
+hipError_t launch_expand_sets(const Dag &d, hipStream_t s)
+{
+    const size_t total = (size_t)d.n * d.W;             // (at most 2^32: the host forms the rows of small graphs only)
+    if (!total) return hipSuccess;
+    hipLaunchKernelGGL(expand_sets_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, d.n, d.W, d.d_op_src, d.d_cls_dep, d.d_dep);
+    return hipGetLastError();
+}
+
 }  // namespace tictac

@@ -405,8 +405,8 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
     p.only_flagged = nullptr;
 
-    // graphs with few classes: register-resident kernel; graphs with many: bit-sliced kernel; then the
-    // general kernel for the samples either of them flagged (those with a transfer time of zero).
+    // model-shaped graphs: chain form; graphs with few classes: register-resident kernel; with many: bit-sliced
+    // kernel; then the general kernel for the samples that one of them flagged.
     // The handle's workspace: one flag per sample first, the state of the running kernel after them.
     const size_t flag_bytes = ((size_t)a.B * sizeof(int32_t) + 255) & ~(size_t)255;
     const size_t lds_small = tac_lds_bytes(d, false);
@@ -450,13 +450,15 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
         if (e == hipSuccess) p.only_flagged = flags;
         else if (e != hipErrorNotSupported) return e;
     }
-    if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && !small && tac_sliced_fits(d)) {
+    if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && !small) {
         // (sized first for the general kernel's pass over the flagged samples, so that the block is not replaced
         // between the two launches)
         hipError_t e = ensure_workspace(&d, flag_bytes + gstate_bytes);
         if (e != hipSuccess) return e;
+        e = ensure_sliced_tables(&d, s);
+        if (e != hipSuccess) return e;
         int32_t *flags = nullptr;
-        e = launch_tac_sliced(d, a, flag_bytes, &flags, s);
+        e = tac_sliced_fits(d) ? launch_tac_sliced(d, a, flag_bytes, &flags, s) : hipErrorNotSupported;
         if (e == hipSuccess) p.only_flagged = flags;
         else if (e != hipErrorNotSupported) return e;
     }
