@@ -1739,7 +1739,120 @@ static int ensure_send_tables(Dag *d, int32_t n_send, const int32_t *send_ids, h
             succ[at_u] = make_int4(last ? (int32_t)((uint32_t)v | 0x80000000u) : v, rec[v].z, rec[v].x, rec[v].w);
         }
 
+    // The form with one lane per sample: columns of 13 bits, lists short on average (a lane goes through its successors one
+    // by one), and counters of half a byte, or of a byte, for the ops of several predecessors.
+    std::vector<uint2> lane_rec, lane_recv_rec;
+    std::vector<uint32_t> lane_succ;
+    std::vector<uint8_t> lane_cnt0;
+    std::vector<uint64_t> lane_ready0;
+    const uint16_t most = n > 0 ? *std::max_element(indeg.begin(), indeg.end()) : (uint16_t)0;
+    if (d->N <= 8128 && most <= 255 && (int64_t)E <= 4 * (int64_t)n) {
+        d->lane_half = most <= 15;
+        std::vector<uint32_t> entry(n, 0);
+        lane_ready0.assign(((size_t)d->N + 63) / 64, 0);
+        uint32_t counters = 0;
+        for (int32_t v = 0; v < n; ++v) {
+            const int32_t j = col_of_op[v];
+            if (j < 0) continue;
+            uint32_t c = 0;
+            if (indeg[v] > 1) {
+                c = ++counters;
+                if (!d->lane_half || (c & 1)) lane_cnt0.push_back((uint8_t)indeg[v]);
+                else lane_cnt0.back() |= (uint8_t)(indeg[v] << 4);
+            }
+            entry[v] = (uint32_t)j | (is_send[v] ? 1u << 13 : 0u) | c << 14;
+            if (indeg[v] == 0 && !is_send[v]) lane_ready0[j >> 6] |= 1ull << (j & 63);
+        }
+        lane_rec.resize(d->N);
+        lane_recv_rec.resize(d->R);
+        for (int32_t v = 0; v < n; ++v) {
+            uint2 &r = recv_of_op[v] >= 0 ? lane_recv_rec[recv_of_op[v]] : lane_rec[col_of_op[v]];
+            r = make_uint2(1u << 30, 0u);
+            if (n_succ[v] == 0) continue;
+            // (the sends last: the first successor is the op that is expected to run next)
+            const int4 *list = &succ[rec[v].x];
+            const size_t first = lane_succ.size();
+            for (int pass = 0; pass < 2; ++pass)
+                for (int32_t e = 0; e < n_succ[v]; ++e)
+                    if (list[e].w == pass) lane_succ.push_back(entry[list[e].x & 0x7fffffff]);
+            r.x = lane_succ[first];
+            lane_succ.erase(lane_succ.begin() + first);
+            if (n_succ[v] == 1) continue;
+            lane_succ.back() |= 0x80000000u;
+            r.y = (uint32_t)first + 1u;
+        }
+    }
+    lane_cnt0.resize((lane_cnt0.size() + 3) / 8 * 8 + 4, 0);       // (an odd number of words of 4 bytes: see SendLaneParams::words)
+    d->n_lane_succ = (int32_t)lane_succ.size();
+
+    // The straight form: ids in topological order, sends behind compute ops only, at most a tile's worth of recvs per op.
+    // A graph that starts with several ops waiting side by side would give up nearly every sample at once (the transfers
+    // have no lead yet): none of the first ops may wait for a recv unless it is alone.
+    std::vector<uint32_t> st_code;
+    std::vector<int32_t> st_chk, st_req(send_free);
+    std::vector<int4> st_tiles;
+    {
+        bool ok = d->N > 1;
+        std::vector<int32_t> last_pred(d->N, -1), n_chk(d->N, 0), n_req(d->N, 0), others(d->N + 1, 0);
+        std::vector<std::vector<int32_t>> sends_after(d->N);
+        for (int32_t v = 0; v < n && ok; ++v) {
+            const int32_t j = col_of_op[v];
+            for (int32_t e = d->h_row_ptr[v]; e < d->h_row_ptr[v + 1]; ++e) {
+                const int32_t u = d->h_col_idx[e];
+                ok = ok && u < v && !(is_send[v] && recv_of_op[u] >= 0);
+                if (recv_of_op[u] >= 0) ++n_chk[j];
+                else last_pred[j] = std::max(last_pred[j], col_of_op[u]);
+            }
+            ok = ok && (j < 0 || n_chk[j] <= 32);
+            if (j < 0 || !ok) continue;
+            if (is_send[v]) {
+                if (last_pred[j] >= 0) sends_after[last_pred[j]].push_back(j);
+            } else if (last_pred[j] + 1 < j) {
+                // between its last predecessor and itself the op could run in place of one that waits
+                ++others[last_pred[j] + 1];
+                --others[j];
+            }
+        }
+        for (int32_t v = 0, open = 0; v < n && ok; ++v) {
+            const int32_t j = col_of_op[v];
+            if (j < 0) continue;
+            open += others[j];
+            if (st_tiles.empty() || st_tiles[st_tiles.size() - 2].y == 64 || st_tiles[st_tiles.size() - 2].w + n_chk[j] > 32) {
+                st_tiles.push_back(make_int4(j, 0, (int32_t)st_chk.size(), 0));
+                st_tiles.push_back(make_int4(0, 0, 0, 0));
+                st_code.resize(st_tiles.size() * 32, 0u);
+            }
+            int4 &tile = st_tiles[st_tiles.size() - 2], &mask = st_tiles.back();
+            const int32_t at = tile.y++;
+            uint32_t &code = st_code[st_tiles.size() * 32 - 64 + at];
+            if (is_send[v]) continue;
+            ok = sends_after[j].size() <= 0xffffu;
+            code = 1u | (uint32_t)n_chk[j] << 1 | (open == 0 ? 0x100u : 0u) | (uint32_t)sends_after[j].size() << 16;
+            st_req.insert(st_req.end(), sends_after[j].begin(), sends_after[j].end());
+            if (j < 16 && n_chk[j] > 0 && open != 0) ok = false;
+            (at < 32 ? mask.x : mask.y) |= (int32_t)(1u << (at & 31));
+            if (n_chk[j] > 0 || !sends_after[j].empty()) (at < 32 ? mask.z : mask.w) |= (int32_t)(1u << (at & 31));
+            tile.w += n_chk[j];
+            for (int32_t e = d->h_row_ptr[v]; e < d->h_row_ptr[v + 1]; ++e)
+                if (recv_of_op[d->h_col_idx[e]] >= 0) st_chk.push_back(recv_of_op[d->h_col_idx[e]]);
+        }
+        if (!ok) { st_tiles.clear(); st_code.clear(); st_chk.clear(); }
+    }
+    st_chk.resize(st_chk.size() + 32, 0);
+    d->n_straight_tiles = (int32_t)st_tiles.size() / 2;
+    if (d->n_straight_tiles > 0) st_tiles.resize(st_tiles.size() + 2, make_int4(0, 0, 0, 0));      // (read, not used)
+    d->lane_cnt_bytes = (int32_t)lane_cnt0.size();
+
     Packer tables;
+    tables.add(&d->d_straight_code, st_code);
+    tables.add(&d->d_straight_chk, st_chk);
+    tables.add(&d->d_straight_req, st_req);
+    tables.add(&d->d_straight_tiles, st_tiles);
+    tables.add(&d->d_lane_rec, lane_rec);
+    tables.add(&d->d_lane_recv_rec, lane_recv_rec);
+    tables.add(&d->d_lane_succ, lane_succ);
+    tables.add(&d->d_lane_cnt0, lane_cnt0);
+    tables.add(&d->d_lane_ready0, lane_ready0);
     tables.add(&d->d_send_rec, rec);
     tables.add(&d->d_send_succ, succ);
     tables.add(&d->d_send_indeg, indeg);

@@ -161,6 +161,21 @@ struct Dag {
     uint16_t *d_send_indeg = nullptr;
     uint32_t *d_send_ready0 = nullptr;
     uint8_t *d_send_col_kind = nullptr;
+    // the tables of the form with one lane per sample (k6_sends.hip); d_lane_rec is NULL where the graph does not suit it
+    uint2 *d_lane_rec = nullptr, *d_lane_recv_rec = nullptr;
+    uint32_t *d_lane_succ = nullptr;
+    uint8_t *d_lane_cnt0 = nullptr;
+    uint64_t *d_lane_ready0 = nullptr;
+    int32_t n_lane_succ = 0, lane_cnt_bytes = 0, lane_half = 0;
+    // The tables of the straight form (k6_sends_straight.hip; d_straight_tiles is NULL where the graph does not suit it).
+    // code, 64 words per tile, a column each: bit 0 a compute op (not a send); bits 1..7 the number of its recvs (the next
+    // entries of chk); bit 8 no other op can run while it waits; bits 16.. the number of sends requested when it ends.
+    // tiles, two of four words each: first column, columns, first entry of chk, entries; the columns with bit 0 (64 bits),
+    // those with recvs or sends (64 bits).
+    uint32_t *d_straight_code = nullptr;
+    int32_t *d_straight_chk = nullptr, *d_straight_req = nullptr;
+    int4 *d_straight_tiles = nullptr;
+    int32_t n_straight_tiles = 0;
     int32_t n_send_free = 0;
     size_t work_bytes = 0;
     // chain form of TAC: its tables, and the class rows and columns (host) that they are made from
@@ -259,6 +274,8 @@ hipError_t launch_check_orders(Dag &d, int32_t B, const int32_t *order, int32_t 
 hipError_t launch_simulate(Dag &d, const SimArgs &a, hipStream_t s);
 // one lane per sample, for graphs whose rows of 64 samples fit LDS; hipErrorNotSupported: the graph is none of these
 hipError_t launch_simulate_lanes(Dag &d, const SimArgs &a, hipStream_t s);
+hipError_t launch_sends_straight(Dag &d, const SimArgs &a, size_t rest, int32_t **list, int32_t **count, hipStream_t s);
+void *sends_straight_rest(int32_t *count, int32_t B);
 // (needs the tables d_send_*; hipErrorNotSupported when the per-sample state does not fit LDS)
 hipError_t launch_simulate_sends(Dag &d, const SimArgs &a, hipStream_t s);
 hipError_t launch_simulate_channels(Dag &d, const SimArgs &a, int32_t n_channels, const int32_t *chan, hipStream_t s);

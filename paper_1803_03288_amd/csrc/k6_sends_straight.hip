@@ -1,0 +1,292 @@
+// The iteration with send ops (k6_sends.hip) for graphs whose op ids are a topological order, of samples in which the
+// compute device runs its ops by ascending id.
+//
+// The device takes the ready op of lowest id.  With topological ids the lowest op not yet run is always held up by
+// recvs alone; as long as those have arrived when the device gets to it, nothing can come before it, and the device goes
+// through the columns of op_time one after the other.  An op that has to wait for a recv keeps its place too when no other
+// op could run meanwhile, which the graph tells (`alone`: no later op has all its compute predecessors among the ops
+// before this one).  A sample in which an op would have to wait and is not alone is given up here and handed to the
+// event-driven kernels through a list.  With a deployed order a model's graph has hardly any such sample: the transfers
+// run ahead of the ops that need them.
+//
+// What is left per op is one addition, in an order known beforehand, so the kernel is a stream over op_time.  A workgroup
+// takes 64 samples; four of its waves read tiles of 64 columns (512 consecutive bytes of a row) into registers, two tiles
+// ahead, sum them along the rows and lay the sums out in LDS by column; the fifth follows the samples, a lane each, and
+// looks only at the columns with recvs or sends.  Arrivals (prefix sums over the transfers, laid out by recv) come with the
+// tile whose ops need them.  The instant at which a send is requested is the sum after its last predecessor; the sends are
+// known in the order of their requests, so the uplink is a second, shorter stream, taken by the four waves in four parts
+// (busy -> max(busy + A, B)).
+//
+// 16 384 samples of the ResNet-50 inference graph with 161 sends (187 MB of times, 38 us at the copy rate): 4.0 ms in the
+// event-driven form with a wave per sample, 97 us here.  Bound by the latencies of a tile, since there is one workgroup
+// of 64 samples per compute unit: 15 us for the arrivals, 60 us for the 20 tiles, 20 us for the uplink.  With the columns
+// followed one by one the fifth wave took 4 us per tile (137 us in all), at the columns that matter 2 us.
+#include <algorithm>
+
+#include "device_utils.h"
+#include "internal.h"
+
+namespace tictac {
+
+constexpr int kTileCols = 64, kTileChecks = 32, kTilePitch = 65;
+typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
+
+struct StraightParams {
+    int32_t B, N, R, n_req, n_req0, n_tiles;
+    const uint32_t *code;           // [n_tiles * 64] see internal.h
+    const int32_t *chk;             // recvs, in the order in which the columns need them; 32 zeros after the last
+    const int32_t *req_col;         // [n_req] columns of the sends in the order of their requests, the first n_req0 at 0
+    const int4 *tiles;              // [n_tiles][2] first column, columns, first entry of chk, entries; see internal.h
+    const int32_t *order;
+    int32_t order_stride;
+    const double *op_time, *recv_time;
+    double *makespan, *eff, *U, *L, *S;
+    double *arrive;                 // [blocks][R][64]
+    double *req_at;                 // [blocks][n_req][64]
+    int32_t *list, *count;          // the samples given up
+};
+
+__global__ void __launch_bounds__(320)
+sends_straight_kernel(const StraightParams p)
+{
+    extern __shared__ double smem[];
+    double *xs = smem;                                          // [2][kTileCols * kTilePitch] column by column
+    double *as = xs + 2 * kTileCols * kTilePitch;               // [2][kTileChecks * 64]
+    double *red = as + 2 * kTileChecks * 64;                    // [2][4][64]
+    uint32_t *codes = reinterpret_cast<uint32_t *>(red + 2 * 4 * 64);   // [2][kTileCols]
+    int32_t *stop = reinterpret_cast<int32_t *>(codes + 2 * kTileCols); // [2] by turns: a wave may be late to read the last one
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool loader = wave < 4;                               // (the fifth wave follows the samples)
+    const int N = p.N, R = p.R;
+    double *arrive = p.arrive + (size_t)blockIdx.x * (R + 1) * 64;
+    double *req_at = p.req_at + (size_t)blockIdx.x * p.n_req * 64;
+    const int groups = (p.B + 63) / 64;
+
+    for (int g = blockIdx.x; g < groups; g += gridDim.x) {
+        const int b0 = g * 64, here = min(64, p.B - b0);
+        const int64_t b = min(b0 + lane, p.B - 1);
+
+        // ---- arrivals: each loader takes a quarter of the transfers, twice (sums, then ends) ----
+        const int quarter = (R + 3) / 4, k0 = min(R, wave * quarter), k1 = loader ? min(R, k0 + quarter) : k0;
+        double sum = 0.0;
+        for (int pass = 0; pass < 2; ++pass) {
+            if (pass == 1) {
+                if (loader) red[wave * 64 + lane] = sum;
+                __syncthreads();
+                sum = 0.0;
+                for (int w = 0; w < wave; ++w) sum += red[w * 64 + lane];
+            }
+            for (int k = k0; k < k1; k += 16) {
+                int r[16];
+                double x[16];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) r[q] = k + q < k1 ? p.order[b * p.order_stride + k + q] : -1;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    x[q] = 0.0;
+                    if ((unsigned)r[q] < (unsigned)R) x[q] = p.recv_time[b * R + r[q]];     // (invalid: skipped)
+                }
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    sum += x[q];
+                    if (pass == 1 && (unsigned)r[q] < (unsigned)R) arrive[(size_t)r[q] * 64 + lane] = sum;
+                }
+            }
+        }
+        const double sum_r = wave == 4 ? sum : 0.0;             // (the fifth wave has added up all four quarters)
+        if (tid < 2) stop[tid] = 0;
+        __syncthreads();
+
+        // ---- the compute device ----
+        double base = 0.0, sum_c = 0.0;
+        bool off = false, given_up = false;
+        if (loader) {
+            // Two tiles are on their way while a third is worked on, their registers by turns.  Every load is executed
+            // (places outside the tile read something else, which the masks drop), so that the waits can be counted.
+            const int at_row = tid >> 5, at_col = (tid & 31) * 2;
+            auto load = [&](int t, Pair (&x)[8], Pair (&a)[4], uint32_t &code) {
+                const int4 tile = p.tiles[2 * t];
+                const int c = tile.x + at_col, from = min(c, N - 2);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    x[i] = *reinterpret_cast<const Pair *>(p.op_time + (int64_t)min(b0 + i * 8 + at_row, p.B - 1) * N + from);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int32_t *q = p.chk + tile.z + i * 8 + wave * 2;
+                    const int r0 = q[0], r1 = q[1];
+                    a[i] = *reinterpret_cast<const Pair *>(arrive + (size_t)((at_row & 1) ? r1 : r0) * 64 + at_col);
+                }
+                code = p.code[t * kTileCols + lane];
+            };
+            // into LDS: the sums of the row's times up to every column (sends count as zeros)
+            auto keep = [&](int t, const Pair (&x)[8], const Pair (&a)[4], uint32_t code) {
+                const int4 tile = p.tiles[2 * t], mask = p.tiles[2 * t + 1];
+                const uint64_t run = (uint64_t)(uint32_t)mask.y << 32 | (uint32_t)mask.x;
+                const bool run0 = run >> at_col & 1ull, run1 = run >> at_col & 2ull, shifted = tile.x + at_col > N - 2;
+                double *xt = xs + (t & 1) * kTileCols * kTilePitch, *at = as + (t & 1) * kTileChecks * 64;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int row = i * 8 + at_row;
+                    const double u0 = run0 ? (shifted ? x[i].y : x[i].x) : 0.0, u1 = run1 ? x[i].y : 0.0;
+                    double v = u0 + u1;                         // (32 lanes hold a row: the scan stops at half a wave)
+                    const double own = v;
+                    v += dpp_f64<0x111, 0xf>(0.0, v);
+                    v += dpp_f64<0x112, 0xf>(0.0, v);
+                    v += dpp_f64<0x114, 0xf>(0.0, v);
+                    v += dpp_f64<0x118, 0xf>(0.0, v);
+                    v += dpp_f64<0x142, 0xa>(0.0, v);
+                    xt[at_col * kTilePitch + row] = (v - own) + u0;
+                    xt[(at_col + 1) * kTilePitch + row] = v;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    at[(i * 8 + at_row) * 64 + at_col] = a[i].x;
+                    at[(i * 8 + at_row) * 64 + at_col + 1] = a[i].y;
+                }
+                if (wave == 0) codes[(t & 1) * kTileCols + lane] = code;
+            };
+            Pair x0[8], a0[4], x1[8], a1[4];
+            uint32_t c0, c1;
+            const int last = p.n_tiles - 1;
+            load(0, x0, a0, c0);
+            load(min(1, last), x1, a1, c1);
+            keep(0, x0, a0, c0);
+            __syncthreads();
+            for (int t = 0;;) {
+                load(min(t + 2, last), x0, a0, c0);
+                keep(t + 1, x1, a1, c1);                        // (past the last tile: into the buffer that nobody reads)
+                __syncthreads();
+                if (stop[t & 1]) { given_up = true; break; }
+                if (++t > last) break;
+                load(min(t + 2, last), x1, a1, c1);
+                keep(t + 1, x0, a0, c0);
+                __syncthreads();
+                if (stop[t & 1]) { given_up = true; break; }
+                if (++t > last) break;
+            }
+        } else {
+            double *req = req_at + (size_t)p.n_req0 * 64 + lane;
+            __syncthreads();
+            for (int t = 0; t < p.n_tiles; ++t) {
+                const int4 mask = p.tiles[2 * t + 1];
+                const uint64_t special = (uint64_t)(uint32_t)mask.w << 32 | (uint32_t)mask.z;   // recvs to look at, sends to request
+                const uint32_t code = codes[(t & 1) * kTileCols + lane];
+                const double *xt = xs + (t & 1) * kTileCols * kTilePitch + lane;
+                const double *at = as + (t & 1) * kTileChecks * 64 + lane;
+                const double all = xt[(kTileCols - 1) * kTilePitch];
+                // only the columns with recvs or sends are looked at; the device is at base + the sum up to there
+                uint64_t rest = special;
+                while (rest != 0ull) {
+                    const int c = __builtin_ctzll(rest);
+                    rest &= rest - 1ull;
+                    const uint32_t todo = (uint32_t)__builtin_amdgcn_readlane((int)code, c);
+                    const double done = xt[c * kTilePitch];
+                    if (const int n_chk = (int)(todo >> 1 & 0x7fu)) {
+                        double before = xt[max(c - 1, 0) * kTilePitch], last = *at;
+                        if (c == 0) before = 0.0;
+                        at += 64;
+                        for (int j = 1; j < n_chk; ++j, at += 64) last = fmax(last, *at);
+                        const bool late = last > base + before;
+                        off |= !(todo & 0x100u) && late;
+                        base = late ? last - before : base;     // (`off`: whatever, the sample is given up)
+                    }
+                    for (uint32_t j = todo >> 16; j > 0u; --j) { *req = base + done; req += 64; }
+                }
+                base += all;
+                sum_c += all;
+                if (__ballot(!off && lane < here) == 0ull) stop[t & 1] = 1;
+                __syncthreads();
+                if (stop[t & 1]) { given_up = true; break; }
+            }
+        }
+
+        // ---- the uplink ----
+        double add = 0.0, least = -TT_INF;
+        if (loader && !given_up) {
+            const int part = (p.n_req + 3) / 4, q0 = min(p.n_req, wave * part), q1 = min(p.n_req, q0 + part);
+            for (int q = q0; q < q1; q += 16) {
+                double at[16], y[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    at[i] = y[i] = 0.0;
+                    if (q + i < q1) {
+                        y[i] = p.op_time[b * N + p.req_col[q + i]];
+                        if (q + i >= p.n_req0) at[i] = req_at[(size_t)(q + i) * 64 + lane];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    if (q + i < q1) { add += y[i]; least = fmax(least, at[i]) + y[i]; }
+                }
+            }
+        }
+        if (loader) {
+            red[wave * 64 + lane] = add;
+            red[(4 + wave) * 64 + lane] = least;
+        }
+        __syncthreads();
+        if (!loader) {
+            const bool mine = lane < here;
+            const uint64_t out = __ballot(mine && (off || given_up));
+            if (out) {
+                int at = 0;
+                if (lane == 0) at = atomicAdd(p.count, (int)__builtin_popcountll(out));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (mine && (off || given_up)) p.list[at + __builtin_popcountll(out & ((1ull << lane) - 1ull))] = b0 + lane;
+            }
+            if (mine && !off && !given_up) {
+                double busy = 0.0, sum_s = 0.0;
+                for (int w = 0; w < 4; ++w) {
+                    busy = fmax(busy + red[w * 64 + lane], red[(4 + w) * 64 + lane]);
+                    sum_s += red[w * 64 + lane];
+                }
+                const double m = fmax(fmax(base, busy), sum_r);
+                const double U = sum_c + sum_r + sum_s;
+                const double Lb = fmax(fmax(sum_c, sum_r), sum_s);
+                p.makespan[b] = m;
+                p.eff[b] = (U == Lb) ? 1.0 : (U - m) / (U - Lb);
+                if (p.U) p.U[b] = U;
+                if (p.L) p.L[b] = Lb;
+                if (p.S) p.S[b] = (U == Lb || Lb == 0.0) ? 0.0 : (U - Lb) / Lb;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The workspace: the count, the list of up to B samples, and from here on what a kernel needs while it runs (arrivals and
+// requests, afterwards the state of the event-driven form).
+static size_t rest_offset(int32_t B) { return ((size_t)B * 4 + 4 + 255) & ~(size_t)255; }
+void *sends_straight_rest(int32_t *count, int32_t B) { return reinterpret_cast<char *>(count) + rest_offset(B); }
+
+__global__ void clear_count_kernel(int32_t *count) { *count = 0; }
+
+// Runs the kernel above; *list and *count: the samples it gave up.  At least `rest` bytes follow the list.
+hipError_t launch_sends_straight(Dag &d, const SimArgs &a, size_t rest, int32_t **list, int32_t **count, hipStream_t s)
+{
+    const int groups = (int)(((int64_t)a.B + 63) / 64);
+    const int grid = std::min(groups, device_cu_count(d.device));
+    StraightParams p{};
+    p.B = a.B; p.N = d.N; p.R = d.R; p.n_req = (int32_t)d.h_send_ids.size(); p.n_req0 = d.n_send_free; p.n_tiles = d.n_straight_tiles;
+    p.code = d.d_straight_code; p.chk = d.d_straight_chk; p.req_col = d.d_straight_req; p.tiles = d.d_straight_tiles;
+    p.order = a.order; p.order_stride = a.order_stride;
+    p.op_time = static_cast<const double *>(a.op_time); p.recv_time = static_cast<const double *>(a.recv_time);
+    p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
+    const size_t arrive = (size_t)grid * (d.R + 1) * 64 * 8, req = (size_t)grid * p.n_req * 64 * 8;
+    hipError_t e = ensure_workspace(&d, rest_offset(a.B) + std::max(arrive + req, rest));
+    if (e != hipSuccess) return e;
+    p.count = static_cast<int32_t *>(d.d_work);
+    p.list = p.count + 1;
+    p.arrive = static_cast<double *>(sends_straight_rest(p.count, a.B));
+    p.req_at = p.arrive + (size_t)grid * (d.R + 1) * 64;
+    *list = p.list;
+    *count = p.count;
+    const size_t lds = (size_t)(2 * kTileCols * kTilePitch + 2 * kTileChecks * 64 + 2 * 4 * 64) * 8 + 2 * kTileCols * 4 + 16;
+    e = ensure_dynamic_lds(reinterpret_cast<const void *>(sends_straight_kernel), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(1), 0, s, p.count);
+    hipLaunchKernelGGL(sends_straight_kernel, dim3(grid), dim3(320), lds, s, p);
+    return hipGetLastError();
+}
+
+}  // namespace tictac
