@@ -1051,7 +1051,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         group_digests(dg, d->N, max_members, cls_ptr, cls_cols, first_col, d->C_distinct);
         d->C = (int32_t)cls_ptr.size() - 1;
         d->Cpad = (d->C + 63) / 64 * 64;
-        if (d->R <= 1024 && d->C <= 512) return 1;      // the small-graph kernels want tables made from the rows
+        if (d->R <= 1024 && d->C <= 1024) return 1;      // the small-graph kernels want tables made from the rows
         cnt0.resize(d->C); first_op.resize(d->C); lowest.resize(d->C);
         op_of_col.reserve(d->N);
         for (int32_t v = 0; v < n; ++v)
@@ -1101,12 +1101,19 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     d->cls_nnz = 0;
     for (int32_t c = 0; c < d->C; ++c) d->cls_nnz += cnt0[c];
     // runs [lo, hi) of consecutive recv indices of every class row, and the sum of its indices
-    // (only the kernels for graphs with at most 1 024 recvs and 512 classes use them)
+    // (only the kernels for graphs with at most 1 024 recvs and 512 classes use the runs, with up to 1 024 classes the sums)
     const bool want_runs = !on_device && d->R <= 1024 && d->C <= 512;
+    const bool want_isum = !on_device && d->R <= 1024 && d->C <= 1024;
     std::vector<int32_t> run_ptr, run_lo, run_hi, isum;
     if (want_runs) {
         run_ptr.assign(1, 0);
         isum.assign(d->C, 0);
+    }
+    if (want_isum && !want_runs) {
+        isum.assign(d->C, 0);
+        for (int32_t c = 0; c < d->C; ++c)
+            for (int32_t w = 0; w < d->W; ++w)
+                for (uint64_t x = cls_dep[(size_t)c * d->W + w]; x; x &= x - 1) isum[c] += w * 64 + __builtin_ctzll(x);
     }
     for (int32_t c = 0; want_runs && c < d->C; ++c) {
         const uint64_t *row = &cls_dep[(size_t)c * d->W];
@@ -1133,7 +1140,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         isum[c] = (int32_t)sum;
     }
     Packer cls;
-    cls.add(&d->d_cls_isum, isum);      // index sums stay below 2^20 (nothing when the runs are not built)
+    cls.add(&d->d_cls_isum, isum);      // index sums stay below 2^20
     d->max_members = 0;
     for (int32_t c = 0; c < d->C; ++c) d->max_members = std::max(d->max_members, cls_ptr[c + 1] - cls_ptr[c]);
     cls.add(&d->d_run_ptr, run_ptr);

@@ -1,5 +1,5 @@
 // TAC (Sec. 4.3, Algorithm 3) with the iteration under its order (Sec. 3.2), one wavefront
-// per timing sample, for graphs with few classes (at most 8 per lane).  A workgroup is a few
+// per timing sample, for graphs with few classes (at most 16 per lane).  A workgroup is a few
 // independent waves that share one read-only LDS copy of the class rows; lane l of a wave
 // owns the classes l, l + 64, ... and keeps their outstanding counts and class times in
 // VGPRs for the whole selection loop.  Per round nothing is read from global memory.
@@ -15,13 +15,12 @@
 //     anything else has to happen), and once the count is 1 the index sum *is* the last
 //     outstanding recv of the class, to whose P the class time is then added: the class
 //     "points" at that recv;
-//   * Q, the set of recvs pointed at by a class with a positive time, is tracked by the number
-//     of pointers and the targets of the latest two of them (one pointer: its target is the
-//     member of Q, the common case on layered models; two pointers at two recvs: one
-//     comparison).  With many classes per lane the latest four targets are kept: with three or
-//     four pointers at distinct recvs the scan over Q is a sorting network on scalars and two or
-//     three comparisons in straight-line code, and the members that stay are known afterwards.
-//     Only the general path enumerates Q, from the class registers;
+//   * Q, the set of recvs pointed at by a class with a positive time, is tracked by its pointers.  With few classes per
+//     lane by their number and the targets of the latest two of them (one pointer: its target is the member of Q, the
+//     common case on layered models; two pointers at two recvs: one comparison), and only the general path enumerates
+//     Q, from the class registers.  With more classes all targets are kept, one per lane, and the first member of Q comes
+//     out of one reduction over them (Johnson's rule, checked against every other member).  61 x 23 layered ops, 203
+//     recvs, 775 classes, 5 003 samples: 2.37 ms enumerating, 1.15 ms with the list (4.85 ms in the general kernel);
 //   * M of a class is needed only when Q is empty or the comparator ties.  It is formed at the
 //     first such round as the sum of the transfer times over the runs of consecutive recv
 //     indices of its row and brought up to date from the order built so far; rounds that do
@@ -37,6 +36,7 @@
 //     general kernel, which takes the literal path for it.
 // LDS atomics of one wave are served in issue order and lane order, so the sums they form
 // are reproducible from run to run.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_utils.h"
@@ -61,14 +61,15 @@ struct TacRegParams {
     double *makespan, *eff, *U, *L, *S;
     int32_t *flags;             // [B] 1 = left to the general kernel
     int32_t wave_doubles;       // LDS doubles per wave
-    int32_t n_waves;            // total waves of the grid
+    int32_t active, n_waves;    // waves of a workgroup that take samples, of the grid
 };
 
 // Waves per workgroup.  The class rows in LDS are shared by the workgroup, so with many classes
 // per lane (large rows, many registers) one large workgroup per compute unit leaves the most
 // LDS to the per-wave arrays; sixteen waves cap the registers at 128 per lane, four waves per SIMD.
+// More than eight classes per lane need up to 256 registers, two waves per SIMD.
 constexpr int kRegWavesMax = 16;
-constexpr int reg_waves(int KT) { return KT <= 4 ? 4 : kRegWavesMax; }
+constexpr int reg_waves(int KT) { return KT <= 4 ? 4 : (KT <= 8 ? kRegWavesMax : 8); }
 // Words per lane in the LDS table of class rows: the KT words of a lane sit next to each other,
 // with one word of padding when KT is even, so that the lanes of a wave reading their k-th word
 // fall into different banks (an even stride puts every 32 / gcd(stride, 32)-th lane on one bank).
@@ -89,10 +90,11 @@ __device__ __forceinline__ int first_alive(const uint32_t *rows, const uint32_t 
 
 // The per-class state is kept in individually named scalars (not arrays), so that every
 // class stays in its own registers across the branches of the loop.  K(F) applies F to the
-// class slots 0..7; a slot beyond KT compiles to nothing.
-#define TT_EACH_K(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7)
+// class slots 0..15; a slot beyond KT compiles to nothing.
+#define TT_EACH_K(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7) F(8) F(9) F(10) F(11) F(12) F(13) F(14) F(15)
 
-template <int KT>
+// LIST: for graphs whose Q often has several members (see launch_tac_reg)
+template <int KT, bool LIST>
 __global__ void __launch_bounds__(64 * reg_waves(KT), (KT <= 3 ? 6 : (KT <= 4 ? 5 : 1)))
 tac_reg_kernel(const TacRegParams p)
 {
@@ -118,6 +120,7 @@ tac_reg_kernel(const TacRegParams p)
         rows[idx] = (h & 1) ? (uint32_t)(x >> 32) : (uint32_t)x;
     }
     __syncthreads();                        // the only workgroup barrier
+    if (wave >= p.active) return;
 
     // ---- wave-uniform bounds of the member loops of the class slots ----
 #define TT_DECL_CONST(k) int mmax_##k = 0;
@@ -134,7 +137,7 @@ tac_reg_kernel(const TacRegParams p)
     const uint32_t *rows_lane = rows + lane * KS;      // this lane's KT words of half-row 0
     double *csum = P;                                  // [64 KT] class totals while they are summed (spans P, ordl, aliveh)
 
-    const int gwave = blockIdx.x * (blockDim.x >> 6) + wave;
+    const int gwave = blockIdx.x * p.active + wave;
     for (int b = gwave; b < p.B; b += p.n_waves) {
         const TimeRow rt = time_row(p.recv_time, (size_t)b * R, p.f32 != 0);
         const TimeRow ot = time_row(p.op_time, (size_t)b * N, p.f32 != 0);
@@ -193,13 +196,10 @@ tac_reg_kernel(const TacRegParams p)
         // wave-uniformly: the number of pointers and the targets of the latest ones, q0 the newest.
         // While there are no more pointers than tracked targets, Q is known without looking at
         // the classes.
-        int qm = 0, q0 = 0, q1 = 0, q2 = 0, q3 = 0;
-        // (four targets only where classes are many: graphs with few classes rarely have more than two
-        // members in Q, and the forced rounds are measurably slower with the two extra values)
-        constexpr bool kFour = KT >= 4;
+        int qm = 0, q0 = 0, q1 = 0;
+        // With LIST all of them are kept, the i-th in lane i of ql (while there are no more than 64).
+        int ql = 0;
         int m_sync = -1;                    // M_k is current up to this step; -1: not formed yet
-        // lane 4 i + j: bit offsets of member i and of member j in the packed scalars of the scan over three or four
-        const int pair_shift = 10 * min((lane >> 2) & 3, 2) | (10 * max((lane & 3) - 1, 0)) << 8;
         int32_t *ord_next = ordl;           // where the next selected recv is recorded
 
         // outstanding recvs as 32-bit halves in LDS, rebuilt from the order so far on the rare
@@ -234,6 +234,25 @@ tac_reg_kernel(const TacRegParams p)
             }                                                                             \
             M_##k = Mk;                                                                   \
         }
+        // With many classes per lane (layered graphs, whose rows are no few runs) every recv is added where its bit is
+        // set, in the same order.
+#define TT_M_ADD(k)                                                                       \
+        if constexpr (k < KT) {                                                           \
+            const int m_ = __builtin_amdgcn_sbfe(rbm[k], shm, 1);                         \
+            M_##k += __hiloint2double(thi & m_, tlo & m_);                                \
+        }
+#define TT_M_FORM_BITS()                                                                  \
+        for (int s0 = 0; s0 < R; s0 += 64) {                                              \
+            const int n_ = min(64, R - s0);                                               \
+            const double t_l = lane < n_ ? t[s0 + lane] : 0.0;                            \
+            for (int i = 0; i < n_; ++i) {                                                \
+                const int tlo = __builtin_amdgcn_readlane(__double2loint(t_l), i);        \
+                const int thi = __builtin_amdgcn_readlane(__double2hiint(t_l), i);        \
+                const uint32_t *rbm = rows_lane + ((s0 + i) >> 5) * (64 * KS);            \
+                const int shm = (s0 + i) & 31;                                            \
+                TT_EACH_K(TT_M_ADD)                                                       \
+            }                                                                             \
+        }
 #define TT_M_SUB(k)                                                                       \
         if constexpr (k < KT) {                                                           \
             const int m_ = __builtin_amdgcn_sbfe(rbm[k], shm, 1);                         \
@@ -242,7 +261,7 @@ tac_reg_kernel(const TacRegParams p)
 #define TT_ENSURE_M(upto)                                                                 \
         {                                                                                 \
             if (m_sync < 0) {                                                             \
-                TT_EACH_K(TT_M_FORM)                                                      \
+                if constexpr (KT > 8) { TT_M_FORM_BITS() } else { TT_EACH_K(TT_M_FORM) }  \
                 m_sync = 0;                                                               \
             }                                                                             \
             for (int s0 = m_sync; s0 < (upto); s0 += 64) {                                \
@@ -264,8 +283,10 @@ tac_reg_kernel(const TacRegParams p)
         // A class that fell to one outstanding recv: its time goes to P of that recv, and with a
         // positive time it becomes a pointer.
 #define TT_PUSH_Q(target)                                                                 \
+                if constexpr (LIST) {                                                     \
+                    if (lane == qm) ql = (target);                                        \
+                }                                                                         \
                 qm += 1;                                                                  \
-                if constexpr (kFour) { q3 = q2; q2 = q1; }                                \
                 q1 = q0;                                                                  \
                 q0 = (target);
 #define TT_POINTER(k)                                                                     \
@@ -307,8 +328,10 @@ tac_reg_kernel(const TacRegParams p)
                 mk_##k = __builtin_amdgcn_sbfe(row_##k, best, 1); /* 0 or -1; the bit offset is best mod 32 */ \
                 __builtin_assume(mk_##k >= -1 && mk_##k <= 0);                            \
                 pk_##k += mk_##k * delta;           /* both fit 24 bits: one multiply-add */ \
-                hmax = max(hmax, (uint32_t)(pk_##k & mk_##k));   /* count fell to 1: top 12 bits all set */ \
+                TT_HMAX(k) = max(TT_HMAX(k), (uint32_t)(pk_##k & mk_##k));   /* count fell to 1: top 12 bits all set */ \
             }
+        // (one maximum for up to eight slots; with more of them one for every four, so that few slots are looked at)
+#define TT_HMAX(k) (KT <= 8 || k < 4 ? hmax : k < 8 ? hmax1 : k < 12 ? hmax2 : hmax3)
 #define TT_EVENT(k)                                                                       \
             if constexpr (k < KT) {                                                       \
                 const bool hit1 = (uint32_t)(pk_##k & mk_##k) >= (uint32_t)-CNT1;         \
@@ -324,11 +347,18 @@ tac_reg_kernel(const TacRegParams p)
                 *ord_next++ = best;                     /* every lane writes the same value */ \
                 const uint32_t *rb = rows_lane + (best >> 5) * (64 * KS);                 \
                 const int delta = CNT1 + (best & IDX_MASK);    /* the mask tells the compiler it fits 24 bits */ \
-                uint32_t hmax = 0;                                                        \
+                uint32_t hmax = 0, hmax1 = 0, hmax2 = 0, hmax3 = 0;                       \
                 TT_EACH_K(TT_ROW_LOAD)                                                    \
                 TT_EACH_K(TT_ROW_KEEP)                                                    \
                 TT_EACH_K(TT_UPDATE)                                                      \
-                if (__ballot(hmax >= (uint32_t)-CNT1) != 0ull) { TT_EACH_K(TT_EVENT) }    \
+                if constexpr (KT <= 8) {                                                  \
+                    if (__ballot(hmax >= (uint32_t)-CNT1) != 0ull) { TT_EACH_K(TT_EVENT) } \
+                } else {                                                                  \
+                    if (__ballot(hmax >= (uint32_t)-CNT1) != 0ull) { TT_EVENT(0) TT_EVENT(1) TT_EVENT(2) TT_EVENT(3) } \
+                    if (__ballot(hmax1 >= (uint32_t)-CNT1) != 0ull) { TT_EVENT(4) TT_EVENT(5) TT_EVENT(6) TT_EVENT(7) } \
+                    if (__ballot(hmax2 >= (uint32_t)-CNT1) != 0ull) { TT_EVENT(8) TT_EVENT(9) TT_EVENT(10) TT_EVENT(11) } \
+                    if (__ballot(hmax3 >= (uint32_t)-CNT1) != 0ull) { TT_EVENT(12) TT_EVENT(13) TT_EVENT(14) TT_EVENT(15) } \
+                }                                                                         \
                 ++step;                                                                   \
             }
 #define TT_UNIFORM_Q()                                                                    \
@@ -336,10 +366,6 @@ tac_reg_kernel(const TacRegParams p)
                 qm = __builtin_amdgcn_readfirstlane(qm);                                  \
                 q0 = __builtin_amdgcn_readfirstlane(q0);                                  \
                 q1 = __builtin_amdgcn_readfirstlane(q1);                                  \
-                if constexpr (kFour) {                                                    \
-                    q2 = __builtin_amdgcn_readfirstlane(q2);                              \
-                    q3 = __builtin_amdgcn_readfirstlane(q3);                              \
-                }                                                                         \
             }
         // pointers counted afresh from the class registers (after a round that removed an
         // unknown number of them)
@@ -353,6 +379,15 @@ tac_reg_kernel(const TacRegParams p)
                     TT_PUSH_Q(sole)                                                       \
                 }                                                                         \
             }
+        // the entries of ql in `gone` are dropped, from the last one on: the last entry takes the place
+#define TT_LIST_DROP(gone)                                                                \
+            for (uint64_t g_ = (gone); g_ != 0ull;) {                                     \
+                const int at_ = 63 - __builtin_clzll(g_);                                 \
+                g_ ^= 1ull << at_;                                                        \
+                qm -= 1;                                                                  \
+                const int last_ = __builtin_amdgcn_readlane(ql, qm);                      \
+                if (lane == at_) ql = last_;                                              \
+            }
         int step = 0;
         TT_UNIFORM_Q()
         while (step < R) {
@@ -360,13 +395,53 @@ tac_reg_kernel(const TacRegParams p)
             // pointers (all of them) are gone with it.  These rounds form the inner loop; M of the
             // classes is not touched in it.
             while (qm == 1) {
-                const int best = q0;
+                const int best = LIST ? __builtin_amdgcn_readlane(ql, 0) : q0;
                 qm = 0;
                 TT_APPLY()
                 TT_UNIFORM_Q()
             }
             if (step >= R) break;
-            if (qm == 2) {
+            if (LIST && qm == 2) {
+                // one comparison (equal members or a tie: below)
+                const int e0 = __builtin_amdgcn_readlane(ql, 0), e1 = __builtin_amdgcn_readlane(ql, 1);
+                const double x0 = fmin(P[e0], t[e1]), x1 = fmin(P[e1], t[e0]);
+                if (e0 != e1 && __ballot(x0 != x1) != 0ull) {
+                    const bool second = __ballot(x0 < x1) != 0ull;       // e1 precedes e0
+                    const int best = second ? e1 : e0;
+                    qm = 1;
+                    ql = lane == 0 ? (second ? e0 : e1) : ql;
+                    TT_APPLY()
+                    TT_UNIFORM_Q()
+                    continue;
+                }
+            }
+            if constexpr (LIST) {
+                // Johnson's rule finds the member that comes first without a scan: the one of shortest transfer among
+                // those with Time < P, or the one of largest P when there is none.  It is the scan's result, whatever the
+                // scan's order, when it strictly precedes every other member; a tie is left to the scan below.
+                if (qm >= 2 && qm <= 64) {
+                    const bool in = lane < qm;
+                    const int who = in ? ql : 0;
+                    const double Pq = P[who], tq = t[who];
+                    const bool shorter = in && tq < Pq;
+                    const bool any = __ballot(shorter) != 0ull;
+                    const double key = any ? (shorter ? tq : TT_INF) : (in ? -Pq : TT_INF);
+                    const double first = wave_min_f64_dpp(key);
+                    const uint64_t at = __ballot(in && key == first);
+                    const int l = at ? __builtin_ctzll(at) : 0;
+                    const int best = __builtin_amdgcn_readlane(ql, l);
+                    const double Pb = readlane_f64(Pq, l), tb = readlane_f64(tq, l);
+                    const uint64_t gone = __ballot(in && ql == best);
+                    const bool after = fmin(Pq, tb) < fmin(Pb, tq);
+                    if (at != 0ull && (__ballot(in && !after) & ~gone) == 0ull) {
+                        TT_LIST_DROP(gone)
+                        TT_APPLY()
+                        TT_UNIFORM_Q()
+                        continue;
+                    }
+                }
+            }
+            if (!LIST && qm == 2) {
                 if (q0 == q1) { qm = 1; continue; }      // two pointers at one recv: |Q| = 1 as well
                 // two pointers at two recvs a < b: Q = {a, b}, and the scan is one comparison:
                 // b precedes a when min{P_a, Time(b)} < min{P_b, Time(a)}.  A tie is left to
@@ -382,55 +457,11 @@ tac_reg_kernel(const TacRegParams p)
                     continue;
                 }
             }
-            if (kFour && (qm == 3 || qm == 4)) {
-                // Three or four pointers, all of them tracked.  When their targets are distinct, Q is these
-                // recvs and the ascending scan is two or three comparisons in straight-line code; those that
-                // stay are known, nothing is counted again.  Anything else (two pointers at one recv, a tie in
-                // a comparison) is left to the paths below.
-                const bool four = qm == 4;
-                int m0 = q0, m1 = q1, m2 = q2, m3 = four ? q3 : INT32_MAX;
-                { const int lo = min(m0, m1), hi = max(m0, m1); m0 = lo; m1 = hi; }
-                { const int lo = min(m2, m3), hi = max(m2, m3); m2 = lo; m3 = hi; }
-                { const int lo = min(m0, m2), hi = max(m0, m2); m0 = lo; m2 = hi; }
-                { const int lo = min(m1, m3), hi = max(m1, m3); m1 = lo; m3 = hi; }
-                { const int lo = min(m1, m2), hi = max(m1, m2); m1 = lo; m2 = hi; }
-                if (m0 != m1 && m1 != m2 && m2 != m3) {
-                    // Lane 4 i + j (i < j) evaluates the comparator for the members i and j: j precedes i when
-                    // min{P_i, Time(j)} < min{P_j, Time(i)}.  Its members come out of two scalars that hold three
-                    // members of ten bits each (0, 1, 2 for i; 1, 2, 3 for j; with three members the fourth is a copy
-                    // of the third).  The scan then walks over the outcomes in scalar code.
-                    const int m3r = four ? m3 : m2;
-                    const int pack_i = m0 | m1 << 10 | m2 << 20, pack_j = m1 | m2 << 10 | m3r << 20;
-                    const int mi = __builtin_amdgcn_ubfe(pack_i, pair_shift & 31, 10);
-                    const int mj = __builtin_amdgcn_ubfe(pack_j, pair_shift >> 8, 10);
-                    const double xi = fmin(P[mi], t[mj]), yi = fmin(P[mj], t[mi]);
-                    const uint64_t lt = __ballot(xi < yi), eq = __ballot(xi == yi);
-                    int bi = (int)(lt >> 1) & 1;                                 // members 0 and 1: lane 1
-                    uint64_t looked = 1ull << 1;
-                    looked |= 1ull << (4 * bi + 2);
-                    if ((lt >> (4 * bi + 2)) & 1) bi = 2;
-                    if (four) {
-                        looked |= 1ull << (4 * bi + 3);
-                        if ((lt >> (4 * bi + 3)) & 1) bi = 3;
-                    }
-                    if ((eq & looked) == 0ull) {                                // no tie in a comparison that was made
-                        const int best = bi == 0 ? m0 : (bi == 1 ? m1 : (bi == 2 ? m2 : m3));
-                        // the members that stay, in ascending order
-                        qm -= 1;
-                        q0 = best == m0 ? m1 : m0;
-                        q1 = (best == m0 || best == m1) ? m2 : m1;
-                        q2 = best == m3 ? m2 : m3;
-                        TT_APPLY()
-                        TT_UNIFORM_Q()
-                        continue;
-                    }
-                }
-            }
-            if (qm >= 2 && q0 == q1 && (!kFour || (q1 == q2 && (qm == 3 || q2 == q3)))) {
+            if (!LIST && qm >= 2 && q0 == q1) {
                 // the latest pointers aim at one recv; with more pointers than tracked targets, look at
                 // all of them to be sure
                 uint64_t other_target = 0;
-                if (qm > (kFour ? 4 : 2)) {
+                if (qm > 2) {
 #define TT_SAME(k)                                                                        \
                     if constexpr (k < KT)                                                 \
                         other_target |= __ballot((uint32_t)pk_##k >= (uint32_t)-CNT1 && sole_##k != q0) & ctpos_##k;
@@ -484,7 +515,14 @@ tac_reg_kernel(const TacRegParams p)
                         qbits_l |= (uint32_t)(lane == (sole & 63)) << (sole >> 6);        \
                     }                                                                     \
                 }
-                TT_EACH_K(TT_QBITS)
+                if (LIST && qm <= 64) {
+                    for (int i = 0; i < qm; ++i) {
+                        const int sole = __builtin_amdgcn_readlane(ql, i);
+                        qbits_l |= (uint32_t)(lane == (sole & 63)) << (sole >> 6);
+                    }
+                } else {
+                    TT_EACH_K(TT_QBITS)
+                }
                 for (int j = 0; j < W; ++j) {
                     uint64_t x = __ballot((qbits_l >> j) & 1u);
                     while (x) {
@@ -517,6 +555,13 @@ tac_reg_kernel(const TacRegParams p)
                 }
             }
             best = __builtin_amdgcn_readfirstlane(best);
+            if (LIST && qm <= 64) {
+                const uint64_t gone = __ballot(lane < qm && ql == best);
+                TT_LIST_DROP(gone)
+                TT_APPLY()
+                TT_UNIFORM_Q()
+                continue;
+            }
             TT_APPLY()
             qm = 0;
             TT_EACH_K(TT_RECOUNT)
@@ -585,42 +630,46 @@ tac_reg_kernel(const TacRegParams p)
     }
 }
 
-template <int KT>
+template <int KT, bool LIST>
 static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
 {
     // LDS: shared rows + per wave t [R+1], P [R+1], ordl [R] i32, outstanding set [2W] u32
     const size_t rows_doubles = ((size_t)2 * d.W * 64 * row_stride(KT) + 1) / 2;
-    const size_t per_wave = 2 * ((size_t)d.R + 1) + ((size_t)d.R + 2 * d.W + 1) / 2 + 1;
+    size_t per_wave = 2 * ((size_t)d.R + 1) + ((size_t)d.R + 2 * d.W + 1) / 2 + 1;
+    if (KT > 8) per_wave = std::max(per_wave, (size_t)d.R + 1 + 64 * KT + 1);       // (room for the class totals)
     // as many waves as LDS allows, at most reg_waves(KT)
     int waves = reg_waves(KT);
     while (waves > 4 && (rows_doubles + per_wave * waves) * 8 > 150 * 1024) --waves;
     const size_t lds = (rows_doubles + per_wave * waves) * 8;
-    if (lds > (waves > 4 ? 150 : 80) * 1024) return hipErrorNotSupported;
+    if (lds > (size_t)(waves > 4 ? 150 : 80) * 1024) return hipErrorNotSupported;
+    // (a small batch is spread over the compute units, the waves of a SIMD slow each other down; those without a sample
+    // help to bring in the rows)
+    p.active = std::min(waves, std::max(1, (p.B + device_cu_count(d.device) - 1) / device_cu_count(d.device)));
     p.wave_doubles = (int32_t)per_wave;
     // the class totals are summed in the space of P, ordl and the outstanding set when that holds
     // one double per class slot
-    p.col_cls = (size_t)64 * KT <= (size_t)d.R + 1 + ((size_t)d.R + 2 * d.W) / 2 ? d.d_col_cls : nullptr;
+    p.col_cls = KT > 8 || (size_t)64 * KT <= (size_t)d.R + 1 + ((size_t)d.R + 2 * d.W) / 2 ? d.d_col_cls : nullptr;
     int per_cu = 0;
     hipError_t e;
     if (lds > 48 * 1024) {
-        e = ensure_dynamic_lds(reinterpret_cast<const void *>(tac_reg_kernel<KT>), lds);
+        e = ensure_dynamic_lds(reinterpret_cast<const void *>(tac_reg_kernel<KT, LIST>), lds);
         if (e != hipSuccess) return e;
     }
-    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(tac_reg_kernel<KT>), 64 * waves, lds);
+    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(tac_reg_kernel<KT, LIST>), 64 * waves, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
     const int n_cu = device_cu_count(d.device);
     int grid = per_cu * n_cu;                       // one resident set of workgroups, no tail
-    const int need = (p.B + waves - 1) / waves;
+    const int need = (p.B + p.active - 1) / p.active;
     if (grid > need) grid = need;
-    p.n_waves = grid * waves;
-    hipLaunchKernelGGL((tac_reg_kernel<KT>), dim3(grid), dim3(64 * waves), lds, s, p);
+    p.n_waves = grid * p.active;
+    hipLaunchKernelGGL((tac_reg_kernel<KT, LIST>), dim3(grid), dim3(64 * waves), lds, s, p);
     return hipGetLastError();
 }
 
 hipError_t launch_tac_reg(Dag &d, const TacArgs &a, int32_t *flags, hipStream_t s)
 {
-    if (d.R == 0 || d.R > 1024 || d.C > 8 * 64 || a.sel_P || a.sel_Mplus || !d.d_cls_isum || !d.d_run_ptr)
+    if (d.R == 0 || d.R > 1024 || d.C > 16 * 64 || a.sel_P || a.sel_Mplus || !d.d_cls_isum || (d.C <= 8 * 64 && !d.d_run_ptr))
         return hipErrorNotSupported;
     TacRegParams p{};
     p.B = a.B; p.R = d.R; p.W = d.W; p.C = d.C; p.N = d.N;
@@ -633,14 +682,23 @@ hipError_t launch_tac_reg(Dag &d, const TacArgs &a, int32_t *flags, hipStream_t 
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
     p.flags = flags;
     const int K = (d.C + 63) / 64;
-    if (K <= 1) return launch_reg_k<1>(p, d, s);
-    if (K <= 2) return launch_reg_k<2>(p, d, s);
-    if (K <= 3) return launch_reg_k<3>(p, d, s);
-    if (K <= 4) return launch_reg_k<4>(p, d, s);
-    if (K <= 5) return launch_reg_k<5>(p, d, s);
-    if (K <= 6) return launch_reg_k<6>(p, d, s);
-    if (K <= 7) return launch_reg_k<7>(p, d, s);
-    return launch_reg_k<8>(p, d, s);
+    // Model graphs have about one recv per class and seldom more than two members in Q: up to three slots the latest two
+    // pointers in scalar registers are a little faster (resnet50, 512 samples: 52.8 us, with the list 55.1).  Graphs with more
+    // classes than that have several members as a rule (layered, 15 x 12 ops and 30 recvs, 84 classes: 62 us, with the list
+    // 46), and from four slots on the list costs the model graphs nothing (inception3, one sample: 207 us either way).
+    const bool list = (int64_t)d.R * 10 < (int64_t)d.C * 9;
+    if (K <= 1) return launch_reg_k<1, false>(p, d, s);
+#define TT_LAUNCH(k) if (K <= k) return list ? launch_reg_k<k, true>(p, d, s) : launch_reg_k<k, false>(p, d, s);
+    TT_LAUNCH(2) TT_LAUNCH(3)
+    if (K <= 4) return launch_reg_k<4, true>(p, d, s);
+    if (K <= 5) return launch_reg_k<5, true>(p, d, s);
+    if (K <= 6) return launch_reg_k<6, true>(p, d, s);
+    if (K <= 7) return launch_reg_k<7, true>(p, d, s);
+    if (K <= 8) return launch_reg_k<8, true>(p, d, s);
+    if (K <= 10) return launch_reg_k<10, true>(p, d, s);
+    if (K <= 12) return launch_reg_k<12, true>(p, d, s);
+    if (K <= 14) return launch_reg_k<14, true>(p, d, s);
+    return launch_reg_k<16, true>(p, d, s);
 }
 
 }  // namespace tictac
