@@ -22,8 +22,7 @@
 //     out of one reduction over them (Johnson's rule, checked against every other member).  61 x 23 layered ops, 203
 //     recvs, 775 classes, 5 003 samples: 2.37 ms enumerating, 1.15 ms with the list (4.85 ms in the general kernel);
 //   * M of a class is needed only when Q is empty or the comparator ties.  It is formed at the
-//     first such round as the sum of the transfer times over the runs of consecutive recv
-//     indices of its row and brought up to date from the order built so far; rounds that do
+//     first such round as the sum of the transfer times of its row's recvs and brought up to date from the order built so far; rounds that do
 //     not need it do not touch it;
 //   * the class totals of a sample are formed by one coalesced pass over its op_time row,
 //     each column adding itself to its class's total in LDS;
@@ -52,8 +51,6 @@ struct TacRegParams {
     const int32_t *cls_ptr;     // [C+1]
     const int32_t *cls_cols;    // [N]
     const int32_t *col_cls;     // [N]   class of every op_time column; NULL: gather by member lists
-    const int32_t *run_ptr;     // [C+1]
-    const int32_t *run_lo, *run_hi;
     const void *op_time, *recv_time;    // float64, or float32 when f32 is set
     int32_t f32;
     int32_t *order, *rank;
@@ -218,41 +215,31 @@ tac_reg_kernel(const TacRegParams p)
         };
 
         // M of the classes is only needed when Q is empty or the comparator ties, so its
-        // updates are deferred: formed as the sum of the transfer times over the runs [lo, hi)
-        // of consecutive recv indices of the class row, and then brought up to `upto` by the
+        // updates are deferred: formed as the sum of the transfer times of the class row's recvs
+        // (recv by recv, each added where its bit is set), and then brought up to `upto` by the
         // subtractions of the rounds since m_sync, in their order.  ordl holds those rounds.
-#define TT_M_FORM(k)                                                                      \
-        if constexpr (k < KT) {                                                           \
-            const int c = k * 64 + lane;                                                  \
-            double Mk = 0.0;                                                              \
-            if (c < C) {                                                                  \
-                const int rend = p.run_ptr[c + 1];                                        \
-                for (int q = p.run_ptr[c]; q < rend; ++q) {                               \
-                    const int hi_ = p.run_hi[q];                                          \
-                    for (int r_ = p.run_lo[q]; r_ < hi_; ++r_) Mk += t[r_];               \
-                }                                                                         \
-            }                                                                             \
-            M_##k = Mk;                                                                   \
-        }
-        // With many classes per lane (layered graphs, whose rows are no few runs) every recv is added where its bit is
-        // set, in the same order.
+#define TT_M_WORD(k) uint32_t w_##k = 0; if constexpr (k < KT) { w_##k = wr[k]; }
 #define TT_M_ADD(k)                                                                       \
         if constexpr (k < KT) {                                                           \
-            const int m_ = __builtin_amdgcn_sbfe(rbm[k], shm, 1);                         \
+            const int m_ = __builtin_amdgcn_sbfe(w_##k, i, 1);                            \
             M_##k += __hiloint2double(thi & m_, tlo & m_);                                \
         }
-#define TT_M_FORM_BITS()                                                                  \
-        for (int s0 = 0; s0 < R; s0 += 64) {                                              \
-            const int n_ = min(64, R - s0);                                               \
-            const double t_l = lane < n_ ? t[s0 + lane] : 0.0;                            \
-            for (int i = 0; i < n_; ++i) {                                                \
-                const int tlo = __builtin_amdgcn_readlane(__double2loint(t_l), i);        \
-                const int thi = __builtin_amdgcn_readlane(__double2hiint(t_l), i);        \
-                const uint32_t *rbm = rows_lane + ((s0 + i) >> 5) * (64 * KS);            \
-                const int shm = (s0 + i) & 31;                                            \
-                TT_EACH_K(TT_M_ADD)                                                       \
+#define TT_M_FORM()                                                                       \
+        {                                                                                 \
+            TT_EACH_K(TT_M_ZERO)                                                          \
+            for (int h = 0; 32 * h < R; ++h) {                                            \
+                const int n_ = min(32, R - 32 * h);                                       \
+                const double t_l = lane < n_ ? t[32 * h + lane] : 0.0;                    \
+                const uint32_t *wr = rows_lane + h * (64 * KS);                           \
+                TT_EACH_K(TT_M_WORD)                                                      \
+                for (int i = 0; i < n_; ++i) {                                            \
+                    const int tlo = __builtin_amdgcn_readlane(__double2loint(t_l), i);    \
+                    const int thi = __builtin_amdgcn_readlane(__double2hiint(t_l), i);    \
+                    TT_EACH_K(TT_M_ADD)                                                   \
+                }                                                                         \
             }                                                                             \
         }
+#define TT_M_ZERO(k) if constexpr (k < KT) M_##k = 0.0;
 #define TT_M_SUB(k)                                                                       \
         if constexpr (k < KT) {                                                           \
             const int m_ = __builtin_amdgcn_sbfe(rbm[k], shm, 1);                         \
@@ -261,7 +248,7 @@ tac_reg_kernel(const TacRegParams p)
 #define TT_ENSURE_M(upto)                                                                 \
         {                                                                                 \
             if (m_sync < 0) {                                                             \
-                if constexpr (KT > 8) { TT_M_FORM_BITS() } else { TT_EACH_K(TT_M_FORM) }  \
+                TT_M_FORM()                                                               \
                 m_sync = 0;                                                               \
             }                                                                             \
             for (int s0 = m_sync; s0 < (upto); s0 += 64) {                                \
@@ -669,13 +656,12 @@ static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
 
 hipError_t launch_tac_reg(Dag &d, const TacArgs &a, int32_t *flags, hipStream_t s)
 {
-    if (d.R == 0 || d.R > 1024 || d.C > 16 * 64 || a.sel_P || a.sel_Mplus || !d.d_cls_isum || (d.C <= 8 * 64 && !d.d_run_ptr))
+    if (d.R == 0 || d.R > 1024 || d.C > 16 * 64 || a.sel_P || a.sel_Mplus || !d.d_cls_isum)
         return hipErrorNotSupported;
     TacRegParams p{};
     p.B = a.B; p.R = d.R; p.W = d.W; p.C = d.C; p.N = d.N;
     p.cls_dep = d.d_cls_dep; p.cls_cnt0 = d.d_cls_cnt0; p.cls_isum = d.d_cls_isum;
     p.cls_ptr = d.d_cls_ptr; p.cls_cols = d.d_cls_cols;
-    p.run_ptr = d.d_run_ptr; p.run_lo = d.d_run_lo; p.run_hi = d.d_run_hi;
     p.op_time = a.op_time; p.recv_time = a.recv_time; p.f32 = a.f32 ? 1 : 0;
     p.order = a.order; p.rank = a.rank;
     p.simulate = a.simulate ? 1 : 0;
