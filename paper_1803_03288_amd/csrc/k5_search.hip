@@ -16,9 +16,9 @@
 // positions l, l + 64, ... of the order (the transfer time at that position).  A move changes
 // kappa of few classes: when the recv at the earlier position (x) and the one at the later
 // position (y) change places, a class with x in its row gets max(kappa, later position); a class
-// with y and without x whose kappa was y's position needs its maximum taken again, which the whole
-// wave does over the row (one recv per lane and word); every other class keeps its kappa.  A and
-// the two scans are then formed afresh from the registers, so every makespan is the one a full
+// with y and without x whose kappa was y's position needs its maximum taken again, for which the wave
+// looks at 64 positions below at once; every other class keeps its kappa.  Which classes hold a recv is
+// one word per 64 classes, in LDS, read by all lanes and used as a scalar.  A and the two scans are then formed afresh from the registers, so every makespan is the one a full
 // evaluation of that order gives.
 //
 // Most moves are turned down without that evaluation.  Let k* be a position where the current
@@ -37,7 +37,8 @@ namespace tictac {
 struct SearchParams {
     int32_t B, R, C, N, W, n_waves, wave_bytes, levels, n_moves, fa_len, rows_bytes;
     const int32_t *col_cls;     // [N] class of every op_time column
-    const uint64_t *cls_dep;    // [C][W] class rows
+    const uint64_t *cls_depT;   // [W][Cpad] class rows, word by word
+    int32_t Cpad;
     const int32_t *run_ptr;     // [C+1] runs [run_lo, run_hi) of consecutive recv indices of the class rows
     const int32_t *run_lo, *run_hi;
     const int32_t *order;       // start orders
@@ -52,6 +53,11 @@ struct SearchParams {
 
 constexpr int kSearchWaves = 4;
 
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t x)      // the same in every lane
+{
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
 #define OS_EACH(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7)
 
 // T slots per lane, for classes (64 T >= C) and for positions (64 T >= R)
@@ -62,7 +68,7 @@ order_search_kernel(const SearchParams p)
     extern __shared__ double smem[];
     const int R = p.R, C = p.C, N = p.N, W = p.W;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint64_t *rows = reinterpret_cast<const uint64_t *>(smem);          // [C][W], shared by the waves
+    uint64_t *holders = reinterpret_cast<uint64_t *>(smem);     // [R][T] the classes with recv r: bit l of word k for (k, l); shared
     char *mine = reinterpret_cast<char *>(smem) + p.rows_bytes + (size_t)wave * p.wave_bytes;
     double *t = reinterpret_cast<double *>(mine);           // [R]   Time(recv)
     double *A = t + R;                                      // [R+1] class time by kappa
@@ -70,9 +76,13 @@ order_search_kernel(const SearchParams p)
     uint16_t *ordl = reinterpret_cast<uint16_t *>(t + p.fa_len);     // [R] the order being tried
     uint16_t *pos = ordl + R + (R & 1);                     // [levels][R] level 0: 1-based position of every recv;
                                                             // level j: maxima over [i, min(i + 2^j, R)) (start order only)
-    {
-        uint64_t *rw = reinterpret_cast<uint64_t *>(smem);
-        for (int i = threadIdx.x; i < C * W; i += blockDim.x) rw[i] = p.cls_dep[i];
+    for (int i = wave; i < W * T; i += kSearchWaves) {
+        const int w = i / T, k = i % T, c = k * 64 + lane;
+        const uint64_t x = c < C ? p.cls_depT[(size_t)w * p.Cpad + c] : 0ull;
+        for (int j = 0; j < 64 && w * 64 + j < R; ++j) {
+            const uint64_t has = __ballot((x >> j) & 1ull);
+            if (lane == 0) holders[(w * 64 + j) * T + k] = has;
+        }
     }
     __syncthreads();
 
@@ -173,49 +183,49 @@ order_search_kernel(const SearchParams p)
                 x = __builtin_amdgcn_readfirstlane((int)ordl[lo]);      // moves from lo to hi
                 y = __builtin_amdgcn_readfirstlane((int)ordl[hi]);      // moves from hi to lo
                 const double tx = t[x], ty = t[y];
-                // which classes hold x, which hold y
-                const int wx = x >> 6, wy = y >> 6;
-                const uint64_t bx = (uint64_t)1 << (x & 63), by = (uint64_t)1 << (y & 63);
+                // which classes hold x, which hold y: the same words in every lane, so they go to scalar registers, as do
+                // the sets of classes that are gained or may be lost
                 double dsum = 0.0;          // change of S at k*: classes gained, classes that may be lost
-                bool moved = false;
+                uint64_t moved = 0ull;
+#define OS_HOLD(k)                                                                        \
+                uint64_t hx_##k = 0ull, hy_##k = 0ull;                                    \
+                if constexpr (k < T) { hx_##k = holders[x * T + k]; hy_##k = holders[y * T + k]; }
+                OS_EACH(OS_HOLD)
 #define OS_MEMBER(k)                                                                      \
-                bool redo_##k = false;                                                    \
+                uint64_t redo_##k = 0ull;                                                 \
                 if constexpr (k < T) {                                                    \
-                    kn_##k = kap_##k;                                                     \
-                    const int c = k * 64 + lane;                                          \
-                    if (c < C) {                                                          \
-                        const bool has_x = (rows[(size_t)c * W + wx] & bx) != 0;          \
-                        const bool has_y = (rows[(size_t)c * W + wy] & by) != 0;          \
-                        if (has_x) kn_##k = max(kap_##k, hi + 1);                         \
-                        redo_##k = has_y && !has_x && kap_##k == hi + 1;                  \
-                        if (has_x && kap_##k < kstar) { dsum += ct_##k; moved = true; }   \
-                        if (redo_##k) { dsum -= ct_##k; moved = true; }                   \
-                    }                                                                     \
+                    hx_##k = uniform_u64(hx_##k);                                         \
+                    redo_##k = uniform_u64(hy_##k) & ~hx_##k & __ballot(kap_##k == hi + 1); \
+                    const uint64_t gain = hx_##k & __ballot(kap_##k < kstar);             \
+                    kn_##k = __builtin_amdgcn_inverse_ballot_w64(hx_##k) ? max(kap_##k, hi + 1) : kap_##k; \
+                    dsum += __builtin_amdgcn_inverse_ballot_w64(gain) ? ct_##k : 0.0;     \
+                    dsum -= __builtin_amdgcn_inverse_ballot_w64(redo_##k) ? ct_##k : 0.0; \
+                    moved |= gain | redo_##k;                                             \
                 }
                 OS_EACH(OS_MEMBER)
                 double d = kstar <= hi ? ty - tx : 0.0;
-                if (__ballot(moved)) d += wave_sum_f64_dpp(dsum);
+                if (moved != 0ull) d += wave_sum_f64_dpp(dsum);
                 // (the comparison is the same in every lane; taking it from the first one tells the compiler so)
                 if (__builtin_amdgcn_readfirstlane((int)(d >= 0.0))) continue;     // F'_k* + S'_k* >= m_cur: the move cannot help
                 wave_sync();
-                if (lane == 0) {
-                    ordl[lo] = (uint16_t)y; ordl[hi] = (uint16_t)x;
-                    pos[x] = (uint16_t)(hi + 1); pos[y] = (uint16_t)(lo + 1);
-                }
+                if (lane == 0) { ordl[lo] = (uint16_t)y; ordl[hi] = (uint16_t)x; }
                 wave_sync();
-                // classes that lose their last recv: the maximum over the row again, by the whole wave
+                // Classes that lose their last recv: the highest position below hi with one of theirs, which is lo (where y
+                // is now) at the latest.  64 positions at a time, one per lane, for all such classes of a slot.
 #define OS_REDO(k)                                                                        \
                 if constexpr (k < T) {                                                    \
-                    unsigned long long todo = __ballot(redo_##k);                         \
-                    while (todo) {                                                        \
-                        const int l = __builtin_ctzll(todo);                              \
-                        todo &= todo - 1;                                                 \
-                        const uint64_t *row = rows + (size_t)(k * 64 + l) * W;            \
-                        int v = 0;                                                        \
-                        for (int w = 0; w < W; ++w)                                       \
-                            if ((row[w] >> lane) & 1) v = max(v, (int)pos[w * 64 + lane]);\
-                        v = wave_max_i32_dpp(v);                                          \
-                        if (lane == l) kn_##k = v;                                        \
+                    for (int top = hi - 1; redo_##k != 0ull; top -= 64) {                 \
+                        const int at = top - lane;                                        \
+                        const uint64_t who = at >= lo ? holders[(int)ordl[at] * T + k] : 0ull; \
+                        for (uint64_t left = redo_##k; left != 0ull; left &= left - 1ull) { \
+                            const int l = __builtin_ctzll(left);                          \
+                            const uint64_t found = __ballot((who >> l) & 1ull);           \
+                            if (found != 0ull) {                                          \
+                                kn_##k = lane == l ? top - (int)__builtin_ctzll(found) + 1 : kn_##k; \
+                                redo_##k &= ~(1ull << l);                                 \
+                            }                                                             \
+                        }                                                                 \
+                        if (top - 63 <= lo) break;      /* (an order with a recv missing) */ \
                     }                                                                     \
                 }
                 OS_EACH(OS_REDO)
@@ -285,10 +295,7 @@ order_search_kernel(const SearchParams p)
 #define OS_SWAP_BACK(k) OS_SWAP_X(k, tx, ty)
                 OS_EACH(OS_SWAP_BACK)
                 wave_sync();
-                if (lane == 0) {
-                    ordl[lo] = (uint16_t)x; ordl[hi] = (uint16_t)y;
-                    pos[x] = (uint16_t)(lo + 1); pos[y] = (uint16_t)(hi + 1);
-                }
+                if (lane == 0) { ordl[lo] = (uint16_t)x; ordl[hi] = (uint16_t)y; }
                 wave_sync();
             }
         }
@@ -311,7 +318,7 @@ static hipError_t launch_search_t(SearchParams &p, const Dag &d, hipStream_t s)
     p.fa_len = (int32_t)fa;
     size_t wave_bytes = fa * 8 + ((size_t)d.R + (d.R & 1)) * 2 + (size_t)levels * d.R * 2;
     wave_bytes = (wave_bytes + 15) & ~(size_t)15;
-    const size_t rows_bytes = (((size_t)d.C * d.W * 8) + 15) & ~(size_t)15;
+    const size_t rows_bytes = (((size_t)d.R * T * 8) + 15) & ~(size_t)15;
     const size_t lds = rows_bytes + wave_bytes * kSearchWaves;
     if (lds > 150 * 1024) return hipErrorNotSupported;     // 160 KB of LDS per compute unit
     p.wave_bytes = (int32_t)wave_bytes;
@@ -338,10 +345,10 @@ hipError_t launch_order_search(Dag &d, const SearchArgs &a, hipStream_t s)
 {
     const int KC = (d.C + 63) / 64, KR = (d.R + 63) / 64;
     const int K = KC > KR ? KC : KR;
-    if (d.R == 0 || d.R > 512 || d.C == 0 || K > 8 || !d.d_col_cls || !d.d_cls_dep || !d.d_run_ptr) return hipErrorNotSupported;
+    if (d.R == 0 || d.R > 512 || d.C == 0 || K > 8 || !d.d_col_cls || !d.d_cls_depT || !d.d_run_ptr) return hipErrorNotSupported;
     SearchParams p{};
     p.B = a.B; p.R = d.R; p.C = d.C; p.N = d.N; p.W = d.W; p.n_moves = a.n_moves;
-    p.col_cls = d.d_col_cls; p.cls_dep = d.d_cls_dep;
+    p.col_cls = d.d_col_cls; p.cls_depT = d.d_cls_depT; p.Cpad = d.Cpad;
     p.run_ptr = d.d_run_ptr; p.run_lo = d.d_run_lo; p.run_hi = d.d_run_hi;
     p.order = a.order; p.order_stride = a.order_stride; p.moves = a.moves;
     p.op_time = a.op_time; p.recv_time = a.recv_time;
