@@ -31,6 +31,8 @@
 //     (k4_simulate.hip) needs nothing but the order and the values of P at selection.
 //   * A sample with a transfer time of zero is flagged for the general kernel (k3_tac.hip), which
 //     takes the literal path for it.
+#include <algorithm>
+
 #include "device_utils.h"
 #include "internal.h"
 
@@ -250,50 +252,54 @@ tac_sliced_kernel(const SlicedParams p)
 
                 // ---- the events of the previous round: class times into P, new members of Q ----
                 // Every worker wave has left its events in a region of its own, in an order that depends on
-                // nothing but the state of the round.  They are taken wave by wave, 64 at a time: the events of a
-                // chunk that name one recv add their class times to its P one after the other, in list order, so
-                // the sums do not depend on which wave was first.
-                const int cnt_w = lane < n_workers ? evcnt[lane] : 0;
-                int incl_w = cnt_w;
-                incl_w += dpp_i32<0x111, 0xf>(0, incl_w);
-                incl_w += dpp_i32<0x112, 0xf>(0, incl_w);
-                incl_w += dpp_i32<0x114, 0xf>(0, incl_w);
-                incl_w += dpp_i32<0x118, 0xf>(0, incl_w);          // (at most fifteen workers: the first row of lanes)
-                const int n = __builtin_amdgcn_readlane(incl_w, 15);
-                if (wave_max_i32_dpp(cnt_w) > kEvPerWave) TS_REQUEST(REQ_FLUSH)   // entries in memory: wait until they have arrived
-                for (int base = 0; base < n; base += 64) {      // (no event: nothing to do)
-                    const int pos = base + lane;
-                    const int m = min(64, n - base);
-                    // the wave whose region holds position pos, and the offset in it
-                    int wv = 0, off = 0;
-                    for (int v = 0; v < n_workers; ++v) {
-                        const int end_v = __builtin_amdgcn_readlane(incl_w, v), cnt_v = __builtin_amdgcn_readlane(cnt_w, v);
-                        if (pos < end_v && pos >= end_v - cnt_v) { wv = v; off = pos - (end_v - cnt_v); }
+                // nothing but the state of the round.  They are taken wave by wave, each adding its class time to P
+                // of its recv by an LDS atomic: those of one wave are served in lane order, so the sums do not depend
+                // on which worker was first.  A lane looks at one place of one region; a round with more events of
+                // one worker than that (four or eight) goes through the list in chunks of 64.
+                const int per = n_workers <= 8 ? 8 : 4;
+                const int my_w = lane / per, my_off = lane % per;
+                const int my_cnt = my_w < n_workers ? evcnt[my_w] : 0;
+                if (__ballot(my_cnt > per) == 0ull) {
+                    if (my_off < my_cnt) {
+                        const EvEntry e = ev[my_w * kEvPerWave + my_off];
+                        atomicAdd(&P[e.sole], e.ct);
+                        if (e.ct > 0.0) atomicOr((unsigned long long *)&Qb[e.sole >> 6], 1ull << (e.sole & 63));
                     }
-                    int sole = -1;
-                    double x = 0.0;
-                    if (lane < m) {
-                        if (off < kEvPerWave) {
-                            sole = ev[wv * kEvPerWave + off].sole;
-                            x = ev[wv * kEvPerWave + off].ct;
-                        } else {
-                            const int2 q = spill[(size_t)wv * kSpillPerWave + off - kEvPerWave];
-                            sole = q.y;
-                            x = ct[q.x];
+                    wave_sync();
+                } else {
+                    const int cnt_w = lane < n_workers ? evcnt[lane] : 0;
+                    int incl_w = cnt_w;
+                    incl_w += dpp_i32<0x111, 0xf>(0, incl_w);
+                    incl_w += dpp_i32<0x112, 0xf>(0, incl_w);
+                    incl_w += dpp_i32<0x114, 0xf>(0, incl_w);
+                    incl_w += dpp_i32<0x118, 0xf>(0, incl_w);          // (at most fifteen workers: the first row of lanes)
+                    const int n = __builtin_amdgcn_readlane(incl_w, 15);
+                    if (wave_max_i32_dpp(cnt_w) > kEvPerWave) TS_REQUEST(REQ_FLUSH)   // entries in memory: wait until they have arrived
+                    for (int base = 0; base < n; base += 64) {
+                        const int pos = base + lane;
+                        const int m = min(64, n - base);
+                        // the wave whose region holds position pos, and the offset in it
+                        int wv = 0, off = 0;
+                        for (int v = 0; v < n_workers; ++v) {
+                            const int end_v = __builtin_amdgcn_readlane(incl_w, v), cnt_v = __builtin_amdgcn_readlane(cnt_w, v);
+                            if (pos < end_v && pos >= end_v - cnt_v) { wv = v; off = pos - (end_v - cnt_v); }
                         }
-                    }
-                    int rank = 0;                   // earlier events of the chunk with the same recv
-                    for (int i = 0; i < m; ++i) {
-                        const int si = __builtin_amdgcn_readlane(sole, i);
-                        rank += (si == sole && i < lane) ? 1 : 0;
-                    }
-                    const int maxrank = wave_max_i32_dpp(lane < m ? rank : 0);
-                    for (int j = 0; j <= maxrank; ++j) {
-                        if (lane < m && rank == j) P[sole] += x;
+                        if (lane < m) {
+                            int sole;
+                            double x;
+                            if (off < kEvPerWave) {
+                                sole = ev[wv * kEvPerWave + off].sole;
+                                x = ev[wv * kEvPerWave + off].ct;
+                            } else {
+                                const int2 q = spill[(size_t)wv * kSpillPerWave + off - kEvPerWave];
+                                sole = q.y;
+                                x = ct[q.x];
+                            }
+                            atomicAdd(&P[sole], x);
+                            if (x > 0.0) atomicOr((unsigned long long *)&Qb[sole >> 6], 1ull << (sole & 63));
+                        }
                         wave_sync();
                     }
-                    if (lane < m && P[sole] > 0.0) atomicOr((unsigned long long *)&Qb[sole >> 6], 1ull << (sole & 63));
-                    wave_sync();
                 }
 
                 // ---- the selection ----
@@ -818,7 +824,16 @@ hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, int32_
     p.order = a.order; p.rank = a.rank;
     p.simulate = a.simulate ? 1 : 0;
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
-    const int per_lane = (d.CW + kWorkersMax * 64 - 1) / (kWorkersMax * 64);
+    // One word per lane where fifteen worker waves hold all classes, the fewest words otherwise; but three where two words
+    // fill less than a compute unit whose LDS has room for two workgroups: the waves that three need leave place for both
+    // (128 registers, sixteen waves).  A round takes 7.5 instead of 5.9 us then, and 4 096 samples of 4 096 recvs and 60 567
+    // classes 312 instead of 427 ms (264 ms with the events added by LDS atomics).
+    int per_lane = (d.CW + kWorkersMax * 64 - 1) / (kWorkersMax * 64);
+    auto pair = [&](int kw) {
+        const int waves = (d.CW + kw * 64 - 1) / (kw * 64) + 1;
+        return 2 * waves <= 16 && 2 * sliced_lds_bytes(d) <= 158 * 1024;
+    };
+    if (per_lane <= 2 && a.B > device_cu_count(d.device) && !pair(std::max(per_lane, 2)) && pair(3)) per_lane = 3;
     if (per_lane <= 1) return launch_sliced_k<1>(p, d, a, flag_bytes, flags_out, s);
     if (per_lane <= 2) return launch_sliced_k<2>(p, d, a, flag_bytes, flags_out, s);
     if (per_lane <= 3) return launch_sliced_k<3>(p, d, a, flag_bytes, flags_out, s);
