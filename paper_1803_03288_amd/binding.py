@@ -67,8 +67,15 @@ def _check(rc: int) -> None:
         raise TicTacError(rc, lib().tictac_last_error().decode())
 
 
+# the current stream of the current device without a torch.cuda.Stream object around it (2.5 us) where torch has the call
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(_raw_device()))
 
 
 def _dev(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
@@ -80,7 +87,7 @@ def _host_i32(a) -> np.ndarray:
 
 
 def _np_ptr(a: np.ndarray) -> ctypes.c_void_p:
-    return a.ctypes.data_as(ctypes.c_void_p)
+    return ctypes.c_void_p(a.ctypes.data)       # (the caller keeps the array)
 
 
 class Dag:
@@ -88,9 +95,9 @@ class Dag:
 
     def __init__(self, handle: ctypes.c_void_p):
         self._h = handle
-        vals = [ctypes.c_int32() for _ in range(5)]
-        _check(lib().tictac_dag_info(self._h, *(ctypes.byref(v) for v in vals)))
-        self.n_ops, self.n_recv, self.words, self.n_levels, self.n_classes = (v.value for v in vals)
+        vals = (ctypes.c_int32 * 5)()
+        _check(lib().tictac_dag_info(self._h, *(ctypes.byref(vals, 4 * i) for i in range(5))))
+        self.n_ops, self.n_recv, self.words, self.n_levels, self.n_classes = vals
         self.n_compute = self.n_ops - self.n_recv
 
     def deps(self) -> torch.Tensor:
@@ -151,7 +158,7 @@ def build_deps(n_ops: int, row_ptr, col_idx, recv_ids) -> Dag:
 def tic_priority(dag: Dag) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """``tictac_tic_priority``: ``(prio, order, rank)``, int32 CUDA tensors ``[R]``."""
     R = dag.n_recv
-    prio, order, rank = (torch.empty(R, dtype=torch.int32, device="cuda") for _ in range(3))
+    prio, order, rank = torch.empty((3, R), dtype=torch.int32, device="cuda").unbind(0)
     _check(lib().tictac_tic_priority(dag._h, _dev(prio), _dev(order), _dev(rank), _stream()))
     return prio, order, rank
 
@@ -215,9 +222,9 @@ def simulate_channels(dag: Dag, n_channels: int, channel_of_recv, order: torch.T
     else:
         assert tuple(order.shape) == (B, R)
         stride = R
-    out = [torch.empty(B, dtype=torch.float64, device="cuda") for _ in range(5)]
+    out = torch.empty((5, B), dtype=torch.float64, device="cuda").unbind(0)
     _check(lib().tictac_simulate_channels(dag._h, ctypes.c_int32(B), ctypes.c_int32(n_channels),
-                                          chan.ctypes.data_as(ctypes.c_void_p), _dev(order), ctypes.c_int32(stride),
+                                          _np_ptr(chan), _dev(order), ctypes.c_int32(stride),
                                           _dev(op_time), _dev(recv_time), *(_dev(o) for o in out), _stream()))
     return tuple(out)
 
@@ -245,9 +252,9 @@ def simulate_sends(dag: Dag, send_ids, order: torch.Tensor, op_time: torch.Tenso
     else:
         assert tuple(order.shape) == (B, R)
         stride = R
-    out = [torch.empty(B, dtype=torch.float64, device=recv_time.device) for _ in range(5)]
+    out = torch.empty((5, B), dtype=torch.float64, device=recv_time.device).unbind(0)
     _check(lib().tictac_simulate_sends(dag._h, ctypes.c_int32(B), ctypes.c_int32(sends.size),
-                                       sends.ctypes.data_as(ctypes.c_void_p), _dev(order), ctypes.c_int32(stride),
+                                       _np_ptr(sends), _dev(order), ctypes.c_int32(stride),
                                        _dev(op_time), _dev(recv_time), *(_dev(o) for o in out), _stream()))
     return tuple(out)
 

@@ -130,6 +130,8 @@ static void *stage(size_t bytes)
     return q;
 }
 
+constexpr size_t kCopyInMax = (size_t)512 << 10;
+
 // Collects host arrays (and device-only reservations) into one device block: one allocation, one copy of each array
 // into the pinned staging block and one host-to-device copy.  The arrays must live until commit().
 struct Packer {
@@ -178,6 +180,8 @@ struct Packer {
             if (p.src) memcpy(st + p.off, p.src, p.bytes);
         }
         if (!host_bytes) return hipSuccess;
+        // (small blocks: a kernel reads the pinned memory itself)
+        if (pageable.empty() && host_bytes <= kCopyInMax) return launch_copy_in(*block, st, host_bytes, s);
         e = hipMemcpyAsync(*block, st, host_bytes, hipMemcpyHostToDevice, s);
         if (!pageable.empty() && e == hipSuccess) e = hipStreamSynchronize(s);
         return e;

@@ -207,6 +207,8 @@ hipError_t cached_blocks_per_cu(int *per_cu, const void *kernel, int threads, si
 
 // op.dep for every op (Sec. 4.1)
 hipError_t launch_propagate(const Dag &d, hipStream_t s);
+// copies from pinned host memory (16-byte aligned, rounded up to 16 bytes) by a kernel
+hipError_t launch_copy_in(void *dst, const void *pinned, size_t bytes, hipStream_t s);
 // op.dep from cls_dep and d_op_src
 hipError_t launch_expand_sets(const Dag &d, hipStream_t s);
 // the same for G graphs of one launch shape in one launch; staging: device memory of propagate_batch_staging_bytes(G)

@@ -955,6 +955,20 @@ hipError_t launch_propagate(const Dag &d, hipStream_t s)
     return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(256)
+copy_in_kernel(uint32_t n, const int4 *__restrict__ src, int4 *__restrict__ dst)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
+hipError_t launch_copy_in(void *dst, const void *pinned, size_t bytes, hipStream_t s)
+{
+    const uint32_t n = (uint32_t)((bytes + 15) / 16);
+    if (n) hipLaunchKernelGGL(copy_in_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, static_cast<const int4 *>(pinned), static_cast<int4 *>(dst));
+    return hipGetLastError();
+}
+
 // op.dep of graphs whose rows were formed on the host: a thread per word
 __global__ void __launch_bounds__(256)
 expand_sets_kernel(int32_t n, int32_t W, const int32_t *__restrict__ src, const uint64_t *__restrict__ cls_dep, uint64_t *__restrict__ dep)

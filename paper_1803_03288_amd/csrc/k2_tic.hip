@@ -3,6 +3,8 @@
 //   priority(recv i) = M+ = min{ |dep[v]| : v a compute op, i in dep[v], |dep[v]| > 1 }.
 // Integer arithmetic throughout, so the result does not depend on the order of the
 // min-updates.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace tictac {
@@ -77,55 +79,65 @@ tic_rank_kernel(int32_t R, const int32_t *__restrict__ prio, int32_t *order, int
     }
 }
 
-// Small graphs in one launch of one workgroup: thread i owns recv i, takes the minimum of
-// |dep| over the classes (compute ops with identical rows) whose row holds i, and ranks
-// itself by counting.  depT is the transposed class table [W][Cpad].  When the table and the
-// class sizes fit (lds_words > 0: W * Cpad words, then C counts), the workgroup first copies them
-// to LDS with all its threads, so that the loop over the classes does not wait on memory.
+// Small graphs in one launch of one workgroup: the minimum of |dep| over the classes (compute ops with identical rows)
+// whose row holds the recv, then its rank by counting.  depT is the transposed class table [W][Cpad].  When the table and
+// the class sizes fit (lds_words > 0: W * Cpad words, then C counts), the workgroup first copies them to LDS with all its
+// threads, so that the loop over the classes does not wait on memory.  Each recv has `parts` threads, a wave apart
+// (thread q * Rpad + i, Rpad the recvs rounded up to whole waves), each with a share of the classes and then of the other
+// recvs: one thread per recv took 14 us for 161 recvs and 166 classes, nearly all of it the two loops.
 __global__ void __launch_bounds__(1024)
-tic_small_kernel(int32_t R, int32_t C, int32_t Cpad, int32_t lds_words, const uint64_t *__restrict__ depT,
-                 const int32_t *__restrict__ cnt0, int32_t *prio, int32_t *order, int32_t *rank)
+tic_small_kernel(int32_t R, int32_t C, int32_t Cpad, int32_t lds_words, int32_t Rpad, int32_t parts,
+                 const uint64_t *__restrict__ depT, const int32_t *__restrict__ cnt0, int32_t *prio, int32_t *order, int32_t *rank)
 {
     extern __shared__ uint64_t tic_table[];         // [lds_words] depT, then [C] counts
-    __shared__ int32_t tile[1024];
-    const int32_t i = threadIdx.x;
+    __shared__ int32_t tile[1024], below[1024];
+    const int32_t t = threadIdx.x;
+    const int32_t q = t / Rpad, i = t - q * Rpad;
+    int32_t *cnt_l = reinterpret_cast<int32_t *>(tic_table + lds_words);
     if (lds_words > 0) {
-        int32_t *cnt_l = reinterpret_cast<int32_t *>(tic_table + lds_words);
-        for (int32_t x = i; x < lds_words; x += blockDim.x) tic_table[x] = depT[x];
-        for (int32_t c = i; c < C; c += blockDim.x) cnt_l[c] = cnt0[c];
-        __syncthreads();
+        for (int32_t x = t; x < lds_words; x += blockDim.x) tic_table[x] = depT[x];
+        for (int32_t c = t; c < C; c += blockDim.x) cnt_l[c] = cnt0[c];
     }
-    int32_t m = TICTAC_PRIO_INF;
-    if (i < R) {
+    if (t < Rpad) { tile[t] = TICTAC_PRIO_INF; below[t] = 0; }
+    __syncthreads();
+    if (q < parts && i < R) {
+        const int32_t share = (C + parts - 1) / parts, c0 = q * share, c1 = min(C, c0 + share);
         const int sh = i & 63;
+        int32_t m = TICTAC_PRIO_INF;
         if (lds_words > 0) {
             const uint64_t *col = tic_table + (size_t)(i >> 6) * Cpad;
-            const int32_t *cnt_l = reinterpret_cast<const int32_t *>(tic_table + lds_words);
-#pragma unroll 4
-            for (int32_t c = 0; c < C; ++c) {
+#pragma unroll 8
+            for (int32_t c = c0; c < c1; ++c) {
                 const int32_t k = cnt_l[c];
                 if (((col[c] >> sh) & 1ull) && k > 1) m = min(m, k);
             }
         } else {
             const uint64_t *col = depT + (size_t)(i >> 6) * Cpad;   // the same word for the 64 lanes of a wave
 #pragma unroll 8
-            for (int32_t c = 0; c < C; ++c) {
+            for (int32_t c = c0; c < c1; ++c) {
                 const int32_t k = cnt0[c];
                 if (((col[c] >> sh) & 1ull) && k > 1) m = min(m, k);
             }
         }
-        prio[i] = m;
+        atomicMin(&tile[i], m);
     }
-    tile[i] = m;
     __syncthreads();
-    if (i < R && (order || rank)) {
+    if (q < parts && i < R && (order || rank)) {
+        const int32_t share = (R + parts - 1) / parts, j0 = q * share, j1 = min(R, j0 + share);
+        const int32_t m = tile[i];
         int32_t r = 0;
-        for (int32_t j = 0; j < R; ++j) {
+#pragma unroll 8
+        for (int32_t j = j0; j < j1; ++j) {
             const int32_t pj = tile[j];
             r += (pj < m) || (pj == m && j < i);
         }
-        if (rank) rank[i] = r;
-        if (order) order[r] = i;
+        atomicAdd(&below[i], r);
+    }
+    __syncthreads();
+    if (t < R) {
+        prio[t] = tile[t];
+        if (rank) rank[t] = below[t];
+        if (order) order[below[t]] = t;
     }
 }
 
@@ -134,13 +146,16 @@ hipError_t launch_tic(const Dag &d, int32_t *prio, int32_t *order, int32_t *rank
     const int32_t R = d.R;
     if (R == 0) return hipSuccess;
     if (R <= 1024 && d.C <= 8192 && d.d_cls_depT && d.d_cls_cnt0) {
-        int threads = (R + 63) / 64 * 64;
+        const int Rpad = (R + 63) / 64 * 64;
+        // (parts that save less than a few steps of the loops are not worth their atomics)
+        const int parts = std::max(1, std::min(1024 / Rpad, (std::max(R, d.C) + 15) / 16));
         const size_t words = (size_t)d.W * d.Cpad;
         const size_t lds = words * 8 + (size_t)d.C * 4;
         const bool in_lds = lds <= 40 * 1024;
+        int threads = Rpad * parts;
         if (in_lds && threads < 256) threads = 256;     // more threads for the copy
         hipLaunchKernelGGL(tic_small_kernel, dim3(1), dim3(threads), in_lds ? lds : 0, s, R, d.C, d.Cpad,
-                           in_lds ? (int32_t)words : 0, d.d_cls_depT, d.d_cls_cnt0, prio, order, rank);
+                           in_lds ? (int32_t)words : 0, Rpad, parts, d.d_cls_depT, d.d_cls_cnt0, prio, order, rank);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(fill_i32, dim3((R + 255) / 256), dim3(256), 0, s, prio, R, (int32_t)TICTAC_PRIO_INF);
