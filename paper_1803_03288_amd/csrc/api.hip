@@ -287,7 +287,7 @@ static void free_dag(Dag *d)
     // (whatever still runs on the blocks is waited for, on any stream; only then may another handle take them)
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     const struct { void *p; size_t bytes; } blocks[] = {
-        {d->d_graph_block, d->graph_bytes}, {d->d_class_block, d->class_bytes}, {d->d_work, d->work_bytes},
+        {d->d_graph_block, d->graph_bytes}, {d->d_quad_block, d->quad_bytes}, {d->d_class_block, d->class_bytes}, {d->d_work, d->work_bytes},
         {d->d_chan, (size_t)d->R * sizeof(int32_t)}, {d->d_send_block, d->send_bytes}, {d->chain.block, d->chain.bytes},
         {d->d_sliced_block, d->sliced_bytes}};
     for (const auto &b : blocks) {
@@ -581,357 +581,247 @@ static void group_sets(const HostSets &h, const std::vector<int32_t> &recv_of_op
 }
 
 // ---- the tables of the propagation kernels (k1_propagate.hip) ----
+// The condensed graph: a compute op whose predecessors come down to one node has that node's row; every other compute op is
+// a node of its own.  Nodes k in topological order, their inputs in[ptr[k] .. ptr[k + 1]): ~i for recv i, else a node.
+struct Condensed {
+    std::vector<int32_t> val;               // of every op: ~i for recv i, else the node whose row it has
+    std::vector<int32_t> op, ptr, in;
+    std::vector<int32_t> lvl_ptr, lvl, pos; // positions by level: of each level, and level and position of every node
+    int32_t M = 0, n_levels = 0, max_width = 0;
+
+    const int32_t *begin(int32_t k) const { return &in[0] + ptr[k]; }
+    const int32_t *end(int32_t k) const { return &in[0] + ptr[k + 1]; }
+};
+
+static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
+                     const std::vector<int32_t> &level, const std::vector<int32_t> &order, Condensed &g)
+{
+    const int32_t n = d.n;
+    g.val.resize(n);
+    g.op.reserve(n); g.ptr.reserve(n + 1);
+    g.in.resize((size_t)d.E + 1);           // (one more: begin() of an empty list)
+    g.ptr.push_back(0);
+    int32_t *in = g.in.data(), at = 0;
+    std::vector<int32_t> used(d.n_levels + 1, 0);
+    for (int32_t v : order) {
+        if (recv_of_op[v] >= 0) { g.val[v] = ~recv_of_op[v]; continue; }
+        const int32_t first = at, deg = row_ptr[v + 1] - row_ptr[v];
+        for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) {
+            const int32_t x = g.val[col_idx[e]];
+            bool seen = false;
+            if (deg <= 16)
+                for (int32_t i = first; i < at; ++i) seen |= in[i] == x;
+            if (!seen) in[at++] = x;
+        }
+        if (deg > 16) {
+            std::sort(in + first, in + at);
+            at = (int32_t)(std::unique(in + first, in + at) - in);
+        }
+        if (at == first + 1 && in[first] >= 0) {
+            g.val[v] = in[first];
+            at = first;
+            continue;
+        }
+        g.val[v] = (int32_t)g.op.size();
+        g.op.push_back(v);
+        g.ptr.push_back(at);
+        used[level[v]] = 1;
+    }
+    g.M = (int32_t)g.op.size();
+    // Nodes are grouped by the level of their op in the full graph (an input of a node lies on a
+    // strictly lower level, and close to it, which keeps inputs inside the kernel's LDS ring);
+    // levels without nodes are dropped.
+    for (int32_t l = 0; l < d.n_levels; ++l) { const int32_t u = used[l]; used[l] = g.n_levels; g.n_levels += u; }
+    g.lvl.resize(g.M);
+    g.pos.resize(g.M);
+    g.lvl_ptr.assign(g.n_levels + 1, 0);
+    for (int32_t k = 0; k < g.M; ++k) ++g.lvl_ptr[(g.lvl[k] = used[level[g.op[k]]]) + 1];
+    for (int32_t l = 0; l < g.n_levels; ++l) {
+        g.max_width = std::max(g.max_width, g.lvl_ptr[l + 1]);
+        g.lvl_ptr[l + 1] += g.lvl_ptr[l];
+    }
+    std::vector<int32_t> fill(g.lvl_ptr.begin(), g.lvl_ptr.end() - 1);
+    for (int32_t k = 0; k < g.M; ++k) g.pos[k] = fill[g.lvl[k]]++;
+}
+
+// The ops whose rows are copies (of a recv's single bit, or of the row of the node the op collapses onto).
+static std::vector<int32_t> copied_rows(const Condensed &g)
+{
+    std::vector<int32_t> copied;
+    copied.reserve(2 * (g.val.size() - g.op.size()));
+    for (int32_t v = 0; v < (int32_t)g.val.size(); ++v) {
+        const int32_t x = g.val[v], from = x < 0 ? x : g.op[x];
+        if (from != v) { copied.push_back(v); copied.push_back(from); }
+    }
+    return copied;
+}
+
 // order: the ops in topological order; level: longest path from a root.  own_dep: the handle's op.dep is made by these
 // kernels (large graphs), so its block holds op.dep as well.
 static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
                                  const std::vector<int32_t> &level, const std::vector<int32_t> &order, bool own_dep, hipStream_t s)
 {
-    const int32_t n = d->n, E = d->E, n_levels = d->n_levels;
-    // ---- condensed graph: chains of single-predecessor compute ops collapse onto their head ----
-    // rep[v] = the node whose dep op v has (itself if v is a node); recvs are not nodes, they
-    // enter a node as single bits.
-    std::vector<int32_t> rep(n, -1), node_level(n, 0);
-    std::vector<int32_t> node_in, node_in_ptr(1, 0);     // inputs of node k: node_in[node_in_ptr[k] .. node_in_ptr[k + 1])
-    node_in.reserve(E);
-    std::vector<int32_t> node_ops;                       // in topological order
-    std::vector<int32_t> node_index(n, -1);              // op -> index into node_ops
-    std::vector<int32_t> tmp;
-    for (int32_t v : order) {
-        if (recv_of_op[v] >= 0) continue;
-        tmp.assign(col_idx + row_ptr[v], col_idx + row_ptr[v + 1]);
-        std::sort(tmp.begin(), tmp.end());
-        tmp.erase(std::unique(tmp.begin(), tmp.end()), tmp.end());
-        if (tmp.size() == 1 && recv_of_op[tmp[0]] < 0) { rep[v] = rep[tmp[0]]; continue; }
-        rep[v] = v;
-        node_index[v] = (int32_t)node_ops.size();
-        node_ops.push_back(v);
-        const size_t first = node_in.size();             // ~i for recv i, else index of the input node
-        for (int32_t u : tmp) {
-            if (recv_of_op[u] >= 0) node_in.push_back(~recv_of_op[u]);
-            else node_in.push_back(node_index[rep[u]]);
-        }
-        std::sort(node_in.begin() + first, node_in.end());
-        node_in.erase(std::unique(node_in.begin() + first, node_in.end()), node_in.end());
-        node_in_ptr.push_back((int32_t)node_in.size());
-    }
-    const int32_t M = (int32_t)node_ops.size();
-    // Nodes are grouped by the level of their op in the full graph (an input of a node lies on a
-    // strictly lower level, and close to it, which keeps inputs inside the kernel's LDS ring);
-    // levels without nodes are dropped.
-    int32_t n_node_levels = 0;
-    {
-        std::vector<int32_t> used(n_levels + 1, 0);
-        for (int32_t v : node_ops) used[level[v]] = 1;
-        for (int32_t l = 0; l < n_levels; ++l) { const int32_t u = used[l]; used[l] = n_node_levels; n_node_levels += u; }
-        for (int32_t v : node_ops) node_level[v] = used[level[v]];
-    }
-    std::vector<int32_t> nlvl_ptr(n_node_levels + 1, 0), pos_of_index(M);
-    for (int32_t v : node_ops) nlvl_ptr[node_level[v] + 1]++;
-    int32_t max_width = 0;
-    for (int32_t l = 0; l < n_node_levels; ++l) { max_width = std::max(max_width, nlvl_ptr[l + 1]); nlvl_ptr[l + 1] += nlvl_ptr[l]; }
-    {
-        std::vector<int32_t> fill(nlvl_ptr.begin(), nlvl_ptr.end() - 1);
-        for (int32_t k = 0; k < M; ++k) pos_of_index[k] = fill[node_level[node_ops[k]]]++;
-    }
-    std::vector<Dag::NodeRec> nodes(M);
-    std::vector<int32_t> ovf_idx;
-    for (int32_t k = 0; k < M; ++k) {
-        Dag::NodeRec &r = nodes[pos_of_index[k]];
-        r.op = node_ops[k];
-        r.ovf_beg = -1;
-        for (int j = 0; j < 6; ++j) r.in[j] = INT32_MIN;
-        int j = 0;
-        for (int32_t e = node_in_ptr[k]; e < node_in_ptr[k + 1]; ++e) {
-            const int32_t x = node_in[e];
-            const int32_t y = x < 0 ? x : pos_of_index[x];
-            if (j < 6) {
-                r.in[j] = y;
-            } else {
-                if (r.ovf_beg < 0) { r.ovf_beg = (int32_t)ovf_idx.size(); ovf_idx.push_back(0); }
-                ovf_idx.push_back(y);
-                ovf_idx[r.ovf_beg]++;
-            }
-            ++j;
-        }
-    }
-    std::vector<int32_t> src(n);
-    for (int32_t v = 0; v < n; ++v) src[v] = recv_of_op[v] >= 0 ? ~recv_of_op[v] : rep[v];
-
+    const int32_t n = d->n;
+    Condensed g;
+    condense(*d, row_ptr, col_idx, recv_of_op, level, order, g);
+    const int32_t M = g.M, n_node_levels = g.n_levels, max_width = g.max_width;
+    const std::vector<int32_t> &nlvl_ptr = g.lvl_ptr;
     d->M = M; d->n_node_levels = n_node_levels; d->max_node_level_width = max_width;
-    // ---- tables ----
-    // the ops whose rows are copies (of a recv's single bit, or of the row of the node the op collapses onto)
-    std::vector<int32_t> copied;
-    for (int32_t v = 0; v < n; ++v)
-        if (src[v] != v) { copied.push_back(v); copied.push_back(src[v]); }
+    const std::vector<int32_t> copied = copied_rows(g);
     d->n_copied = (int32_t)(copied.size() / 2);
     Packer graph;
+    std::vector<Dag::NodeRec> nodes;
     std::vector<Dag::FastRec> lrecs, frecs;
-    std::vector<Dag::QuadRec> qrecs;
-    std::vector<int32_t> chunk_end, qfovf, left, lfovf, fovf, op_of_col;
+    std::vector<int32_t> ovf_idx, chunk_end, lfovf, fovf, op_of_col;
     const std::vector<int32_t> zeros(64, 0);
-    if (own_dep) graph.add(&d->d_recv_of_op, recv_of_op);
-    graph.add(&d->d_nodes, nodes);
-    graph.add(&d->d_ovf_idx, ovf_idx);
-    graph.add(&d->d_nlvl_ptr, nlvl_ptr);
-    {
-        // words per workgroup slice, threads, and the chunks of levels of the node kernel
-        // a workgroup's LDS traffic per level grows with its slice, so wide bitsets get many narrow slices
-        d->k1_wc = d->W <= 1 ? 1 : (d->W <= 2 ? 2 : (d->W >= 16 ? 1 : 4));
-        // Graphs with narrow levels take a level per LDS round trip when one wave holds every row of its slice,
-        // every record and the input lists of the nodes that fit no record in LDS (propagate_nodes_wave); the
-        // slice is narrowed until that fits.
-        size_t list_entries = 0;
-        for (int32_t q = 0; q < M; ++q) {
-            const Dag::NodeRec &r = nodes[q];
-            int nn = 0, nr = 0;
-            for (int j = 0; j < 6; ++j) if (r.in[j] != INT32_MIN) (r.in[j] < 0 ? nr : nn) += 1;
-            if (r.ovf_beg >= 0)
-                for (int32_t e = 1; e <= ovf_idx[r.ovf_beg]; ++e) (ovf_idx[r.ovf_beg + e] < 0 ? nr : nn) += 1;
-            if (nn > 4 || nr > 2) list_entries += 1 + (size_t)nn + nr;
+    // words per workgroup slice, threads, and the chunks of levels of the node kernel
+    // a workgroup's LDS traffic per level grows with its slice, so wide bitsets get many narrow slices
+    d->k1_wc = d->W <= 1 ? 1 : (d->W <= 2 ? 2 : (d->W >= 16 ? 1 : 4));
+    // Graphs with narrow levels take a level per LDS round trip when one wave holds every row of its slice,
+    // every record and the input lists of the nodes that fit no record in LDS (propagate_nodes_wave); the
+    // slice is narrowed until that fits.
+    size_t list_entries = 0;
+    for (int32_t k = 0; k < M && max_width <= 64; ++k) {
+        int nn = 0, nr = 0;
+        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) (*x < 0 ? nr : nn) += 1;
+        if (nn > 4 || nr > 2) list_entries += 1 + (size_t)nn + nr;
+    }
+    d->k1_wave = false;
+    for (int wc = d->k1_wc; wc >= 1 && max_width <= 64 && list_entries <= 4096 && M > 0; wc >>= 1) {
+        if (max_width * wc <= 64 &&
+            ((size_t)(M + 2) * wc + 1) * 8 + (size_t)M * 32 + (size_t)(n_node_levels + 1) * 4 + list_entries * 4 <= 150 * 1024) {
+            d->k1_wc = wc;
+            d->k1_wave = true;
+            break;
         }
-        d->k1_wave = false;
-        for (int wc = d->k1_wc; wc >= 1 && max_width <= 64 && list_entries <= 4096 && M > 0; wc >>= 1) {
-            if (max_width * wc <= 64 &&
-                ((size_t)(M + 2) * wc + 1) * 8 + (size_t)M * 32 + (size_t)(n_node_levels + 1) * 4 + list_entries * 4 <= 150 * 1024) {
-                d->k1_wc = wc;
-                d->k1_wave = true;
-                break;
-            }
-        }
-        int threads = max_width * d->k1_wc;
-        threads = threads < 64 ? 64 : (threads > 1024 ? 1024 : (threads + 63) / 64 * 64);
-        d->k1_threads = threads;
-        const int32_t per_pass = threads / d->k1_wc;
-        chunk_end.assign(n_node_levels, 0);
-        for (int32_t l0 = 0; l0 < n_node_levels;) {
-            int32_t l1 = l0 + 1;
-            while (l1 < n_node_levels && l1 - l0 < 64 && nlvl_ptr[l1 + 1] - nlvl_ptr[l0] <= 4 * per_pass) ++l1;
-            chunk_end[l0] = l1;
-            l0 = l1;
-        }
-        graph.add(&d->d_chunk_end, chunk_end);
-        // the LDS ring: a power of two of positions, at least two chunks (or all nodes), at most 64 KB beyond that
-        int32_t ring = 64;
-        while (ring < M && (ring < 2 * kK1Rpt * per_pass || (size_t)ring * 2 * d->k1_wc * 8 <= 64 * 1024)) ring *= 2;
-        if (d->k1_wave) ring = M;                   // every row stays: no ring, positions are used as they are
-        d->k1_ring = ring;
-        // level-major records (see internal.h): when a workgroup has more than one wave, the padding at
-        // most quadruples the records, and sixteen levels of slots fit the ring: at most 64 KB, and 32 KB for
-        // one-word slices (many narrow workgroups: four of them then share a compute unit when several
-        // graphs are propagated by one launch)
-        int32_t lring = 0;
-        if (max_width <= per_pass && threads > 64 && (int64_t)n_node_levels * per_pass <= (int64_t)4 * M + 8192) {
-            const size_t ring_cap = d->k1_wc == 1 ? 32 * 1024 : 64 * 1024;
-            lring = 64;
-            while ((size_t)lring * 2 * d->k1_wc * 8 <= ring_cap && lring < n_node_levels * per_pass) lring *= 2;
-            if (lring < 16 * per_pass && lring < n_node_levels * per_pass) lring = 0;
-        }
-        d->k1_lring = lring;
-        // Rows of a multiple of eight words, levels of at most 256 nodes: also the records of the kernel with
-        // 64-byte slices (four lanes per slot, or two with 32-byte slices; P slots per level, a multiple of 32 so that the
-        // slots of a wave are whole; 2048 slots in the ring), which the propagation of several graphs by one launch takes.
-        int32_t q_slots = (max_width + 31) / 32 * 32, q_ring = 0;
-        if (q_slots < 32) q_slots = 32;
-        if (d->k1_wc == 1 && d->W % 8 == 0 && d->W <= 1016 && max_width <= 256 && M > 0 &&
-            (int64_t)n_node_levels * q_slots <= (int64_t)4 * M + 8192) {
-            q_ring = 2048;
-            while (q_ring > 64 && q_ring / 2 >= n_node_levels * q_slots) q_ring /= 2;
-            if (q_ring < 4 * q_slots && q_ring < n_node_levels * q_slots) q_ring = 0;
-        }
-        d->k1_q_ring = q_ring;
-        d->k1_q_threads = q_ring > 0 ? 4 * q_slots : 0;
-        // Level-major records, of either kind.  While level l is computed the ring holds the slots from
-        // (l + 1) * P - ring on.  With 64-byte slices that is few levels, and a row that a later level needs is
-        // handed on by copy nodes (op = -2: one input, the row goes to the ring only) in free slots of the levels
-        // between, each within reach of the one before; the copies of a row form one chain, which the consumers,
-        // taken level by level, extend.
-        auto level_major = [&](bool quad, int32_t P, int32_t lring, std::vector<Dag::FastRec> &lrecs,
-                               std::vector<Dag::QuadRec> &qrecs, std::vector<int32_t> &lfovf, std::vector<int32_t> &left) {
-            const int32_t row_bytes = d->k1_wc * 8, zero_row = lring * row_bytes;
-            std::vector<int32_t> slot_of(M);            // position -> slot
-            for (int32_t l = 0; l < n_node_levels; ++l)
-                for (int32_t q = nlvl_ptr[l]; q < nlvl_ptr[l + 1]; ++q) slot_of[q] = l * P + (q - nlvl_ptr[l]);
-            if (quad) {
-                const uint32_t zero2 = (uint32_t)lring | (uint32_t)lring << 16;
-                qrecs.assign((size_t)n_node_levels * P, Dag::QuadRec{zero2, zero2, 0xffffffffu, -1});
+    }
+    int threads = max_width * d->k1_wc;
+    threads = threads < 64 ? 64 : (threads > 1024 ? 1024 : (threads + 63) / 64 * 64);
+    d->k1_threads = threads;
+    const int32_t per_pass = threads / d->k1_wc;
+    chunk_end.assign(n_node_levels, 0);
+    for (int32_t l0 = 0; l0 < n_node_levels;) {
+        int32_t l1 = l0 + 1;
+        while (l1 < n_node_levels && l1 - l0 < 64 && nlvl_ptr[l1 + 1] - nlvl_ptr[l0] <= 4 * per_pass) ++l1;
+        chunk_end[l0] = l1;
+        l0 = l1;
+    }
+    // the LDS ring: a power of two of positions, at least two chunks (or all nodes), at most 64 KB beyond that
+    int32_t ring = 64;
+    while (ring < M && (ring < 2 * kK1Rpt * per_pass || (size_t)ring * 2 * d->k1_wc * 8 <= 64 * 1024)) ring *= 2;
+    if (d->k1_wave) ring = M;                   // every row stays: no ring, positions are used as they are
+    d->k1_ring = ring;
+    // level-major records (see internal.h): when a workgroup has more than one wave, the padding at
+    // most quadruples the records, and sixteen levels of slots fit the ring: at most 64 KB, and 32 KB for
+    // one-word slices (many narrow workgroups: four of them then share a compute unit when several
+    // graphs are propagated by one launch)
+    int32_t lring = 0;
+    if (max_width <= per_pass && threads > 64 && (int64_t)n_node_levels * per_pass <= (int64_t)4 * M + 8192) {
+        const size_t ring_cap = d->k1_wc == 1 ? 32 * 1024 : 64 * 1024;
+        lring = 64;
+        while ((size_t)lring * 2 * d->k1_wc * 8 <= ring_cap && lring < n_node_levels * per_pass) lring *= 2;
+        if (lring < 16 * per_pass && lring < n_node_levels * per_pass) lring = 0;
+    }
+    d->k1_lring = lring;
+    // Rows of a multiple of eight words, levels of at most 256 nodes: the kernel with 64-byte slices (four lanes per
+    // slot, or two with 32-byte slices; P slots per level, a multiple of 32 so that the slots of a wave are whole; 2048
+    // slots in the ring), which the propagation of several graphs by one launch takes; its records are made then.
+    int32_t q_slots = (max_width + 31) / 32 * 32, q_ring = 0;
+    if (q_slots < 32) q_slots = 32;
+    if (d->k1_wc == 1 && d->W % 8 == 0 && d->W <= 1016 && max_width <= 256 && M > 0 &&
+        (int64_t)n_node_levels * q_slots <= (int64_t)4 * M + 8192) {
+        q_ring = 2048;
+        while (q_ring > 64 && q_ring / 2 >= n_node_levels * q_slots) q_ring /= 2;
+        if (q_ring < 4 * q_slots && q_ring < n_node_levels * q_slots) q_ring = 0;
+    }
+    d->k1_q_ring = q_ring;
+    d->k1_q_threads = q_ring > 0 ? 4 * q_slots : 0;
+
+    // FastRec of node k at level l: place(x) the byte offset of input node x in the ring, or -1 when it has left it
+    auto fast = [&](Dag::FastRec &f, int32_t k, int32_t zero_row, std::vector<int32_t> &lists, auto &&place, auto &&name) {
+        for (int j = 0; j < 4; ++j) f.in[j] = zero_row;
+        f.rcv[0] = f.rcv[1] = -1;
+        f.op = g.op[k];
+        f.ovf = -1;
+        int a = 0, b = 0;
+        bool fits = true;
+        for (const int32_t *x = g.begin(k); x != g.end(k) && fits; ++x) {
+            if (*x < 0) {
+                if ((fits = b < 2)) f.rcv[b++] = ~*x;
             } else {
-                Dag::FastRec none;
-                for (int j = 0; j < 4; ++j) none.in[j] = zero_row;
-                none.rcv[0] = none.rcv[1] = -1;
-                none.op = -1;
-                none.ovf = -1;
-                lrecs.assign((size_t)n_node_levels * P, none);
+                const int32_t q = a < 4 ? place(*x) : -1;
+                if ((fits = q >= 0)) f.in[a++] = q;
             }
-            const int32_t reach = lring / P - 1;        // a row of level x is in the ring up to level x + reach
-            std::vector<int32_t> used(n_node_levels);
-            for (int32_t l = 0; l < n_node_levels; ++l) used[l] = nlvl_ptr[l + 1] - nlvl_ptr[l];
-            std::unordered_map<int32_t, std::vector<int32_t>> chain;       // slot of a row -> slots of its copies
-            auto within_reach = [&](int32_t slot, int32_t l) -> int32_t {   // the slot to read at level l, or -1
-                if ((int64_t)slot >= (int64_t)(l + 1) * P - lring) return slot;
-                if (!quad || reach < 1 || l - slot / P > 8 * reach) return -1;
-                std::vector<int32_t> &ch = chain[slot];
-                int32_t cur = ch.empty() ? slot : ch.back();
-                while (l - cur / P > reach) {
-                    int32_t t = cur / P + reach;
-                    while (t > cur / P && used[t] >= P) --t;
-                    if (t == cur / P) return -1;
-                    const int32_t c = t * P + used[t]++;
-                    qrecs[c].in01 = (uint32_t)(cur & (lring - 1)) | (uint32_t)lring << 16;
-                    qrecs[c].op = -2;
-                    ch.push_back(c);
-                    cur = c;
+        }
+        if (fits) return;
+        for (int j = 0; j < 4; ++j) f.in[j] = zero_row;
+        f.rcv[0] = f.rcv[1] = -1;
+        f.ovf = (int32_t)lists.size();
+        lists.push_back((int32_t)(g.end(k) - g.begin(k)));
+        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) lists.push_back(*x < 0 ? *x : name(*x));
+    };
+    if (lring > 0) {
+        // While level l is computed the ring holds the slots from (l + 1) * P - ring on.
+        const int32_t P = per_pass, row_bytes = d->k1_wc * 8, zero_row = lring * row_bytes;
+        Dag::FastRec none;
+        for (int j = 0; j < 4; ++j) none.in[j] = zero_row;
+        none.rcv[0] = none.rcv[1] = -1;
+        none.op = -1;
+        none.ovf = -1;
+        lrecs.assign((size_t)n_node_levels * P, none);
+        std::vector<int32_t> slot(M);
+        for (int32_t k = 0; k < M; ++k) {
+            const int32_t l = g.lvl[k];
+            slot[k] = l * P + (g.pos[k] - nlvl_ptr[l]);
+            const int32_t oldest = (l + 1) * P - lring;
+            fast(lrecs[slot[k]], k, zero_row, lfovf,
+                 [&](int32_t x) { return slot[x] >= oldest ? (slot[x] & (lring - 1)) * row_bytes : -1; },
+                 [&](int32_t x) { return slot[x]; });
+        }
+        graph.add(&d->d_lrecs, lrecs);
+        graph.add(&d->d_lfovf, lfovf);
+        d->lfovf_len = (int32_t)lfovf.size();
+    } else if (max_width <= per_pass) {
+        const int32_t row_bytes = d->k1_wc * 8, zero_row = ring * row_bytes;
+        frecs.resize(M);
+        for (int32_t k = 0; k < M; ++k) {
+            const int32_t oldest = nlvl_ptr[g.lvl[k] + 1] - ring;
+            fast(frecs[g.pos[k]], k, zero_row, fovf,
+                 [&](int32_t x) { const int32_t q = g.pos[x]; return q >= oldest ? (d->k1_wave ? q : (q & (ring - 1))) * row_bytes : -1; },
+                 [&](int32_t x) { return g.pos[x]; });
+        }
+        graph.add(&d->d_frecs, frecs);
+        graph.add(&d->d_fovf, fovf);
+        d->fovf_len = (int32_t)fovf.size();
+    }
+    if (lring == 0) {
+        // the kernels that go by positions; the one for wide levels reads NodeRecs
+        if (max_width > per_pass) {
+            nodes.resize(M);
+            for (int32_t k = 0; k < M; ++k) {
+                Dag::NodeRec &r = nodes[g.pos[k]];
+                r.op = g.op[k];
+                r.ovf_beg = -1;
+                for (int j = 0; j < 6; ++j) r.in[j] = INT32_MIN;
+                int j = 0;
+                for (const int32_t *x = g.begin(k); x != g.end(k); ++x, ++j) {
+                    const int32_t y = *x < 0 ? *x : g.pos[*x];
+                    if (j < 6) { r.in[j] = y; continue; }
+                    if (r.ovf_beg < 0) { r.ovf_beg = (int32_t)ovf_idx.size(); ovf_idx.push_back(0); }
+                    ovf_idx.push_back(y);
+                    ovf_idx[r.ovf_beg]++;
                 }
-                return cur;
-            };
-            std::vector<int32_t> src_slot;
-            for (int32_t l = 0; l < n_node_levels; ++l)
-                for (int32_t q = nlvl_ptr[l]; q < nlvl_ptr[l + 1]; ++q) {
-                    const Dag::NodeRec &r = nodes[q];
-                    tmp.clear();
-                    for (int j = 0; j < 6; ++j) if (r.in[j] != INT32_MIN) tmp.push_back(r.in[j]);
-                    if (r.ovf_beg >= 0)
-                        for (int32_t e = 1; e <= ovf_idx[r.ovf_beg]; ++e) tmp.push_back(ovf_idx[r.ovf_beg + e]);
-                    int nn = 0, nr = 0;
-                    for (int32_t &x : tmp) {
-                        if (x < 0) { ++nr; continue; }
-                        ++nn;
-                        x = slot_of[x];
-                    }
-                    // (copies are made only for a node that then fits a record)
-                    bool resident = nn <= 4 && nr <= 2;
-                    src_slot.clear();
-                    if (resident)
-                        for (int32_t x : tmp) {
-                            if (x < 0) continue;
-                            const int32_t c = within_reach(x, l);
-                            if (c < 0) { resident = false; break; }
-                            src_slot.push_back(c);
-                        }
-                    if (quad) {
-                        Dag::QuadRec &f = qrecs[slot_of[q]];
-                        f.op = r.op;
-                        if (resident) {
-                            uint32_t in[4] = {(uint32_t)lring, (uint32_t)lring, (uint32_t)lring, (uint32_t)lring};
-                            uint32_t rc[2] = {0xffffu, 0xffffu};
-                            int a = 0, b = 0;
-                            for (int32_t x : tmp) if (x < 0) rc[b++] = (uint32_t)~x;
-                            for (int32_t c : src_slot) in[a++] = (uint32_t)(c & (lring - 1));
-                            f.in01 = in[0] | in[1] << 16;
-                            f.in23 = in[2] | in[3] << 16;
-                            f.rcv01 = rc[0] | rc[1] << 16;
-                        } else {
-                            f.in01 = 0xffffffffu;
-                            f.in23 = (uint32_t)lfovf.size();
-                        }
-                    } else {
-                        Dag::FastRec &f = lrecs[slot_of[q]];
-                        f.op = r.op;
-                        if (resident) {
-                            int a = 0, b = 0;
-                            for (int32_t x : tmp) if (x < 0) f.rcv[b++] = ~x;
-                            for (int32_t c : src_slot) f.in[a++] = (c & (lring - 1)) * row_bytes;
-                        } else {
-                            f.ovf = (int32_t)lfovf.size();
-                        }
-                    }
-                    if (!resident) {
-                        lfovf.push_back((int32_t)tmp.size());
-                        lfovf.insert(lfovf.end(), tmp.begin(), tmp.end());
-                    }
-                }
-            if (!quad) return;
-            // The copied rows ride along in slots that are still free: a recv's row anywhere (no input, one recv
-            // bit), the copy of a node's row at a level within reach of the node or of one of its copy nodes, as
-            // a node with that one input and the op's own id.  What finds no slot stays on the list `left`.
-            std::vector<int32_t> slot_of_op(n, -1);
-            for (int32_t q = 0; q < M; ++q) slot_of_op[nodes[q].op] = slot_of[q];
-            const uint32_t zero2 = (uint32_t)lring | (uint32_t)lring << 16;
-            int32_t cursor = 0;
-            for (size_t e = 0; e + 1 < copied.size(); e += 2) {
-                const int32_t v = copied[e], sv = copied[e + 1];
-                int32_t c = -1;
-                if (sv < 0) {
-                    while (cursor < n_node_levels && used[cursor] >= P) ++cursor;
-                    if (cursor < n_node_levels) {
-                        c = cursor * P + used[cursor]++;
-                        qrecs[c] = Dag::QuadRec{zero2, zero2, (uint32_t)~sv | 0xffff0000u, v};
-                    }
-                } else if (slot_of_op[sv] >= 0 && reach >= 1) {
-                    const int32_t base = slot_of_op[sv];
-                    auto it = chain.find(base);
-                    const size_t n_cand = 1 + (it == chain.end() ? 0 : it->second.size());
-                    for (size_t k = 0; k < n_cand && c < 0; ++k) {
-                        const int32_t from = k == 0 ? base : it->second[k - 1];
-                        for (int32_t t = from / P + 1; t <= from / P + reach && t < n_node_levels; ++t)
-                            if (used[t] < P) {
-                                c = t * P + used[t]++;
-                                qrecs[c] = Dag::QuadRec{(uint32_t)(from & (lring - 1)) | (uint32_t)lring << 16, zero2,
-                                                        0xffffffffu, v};
-                                break;
-                            }
-                    }
-                }
-                if (c < 0) { left.push_back(v); left.push_back(sv); }
             }
-        };
-        if (q_ring > 0) {
-            std::vector<Dag::FastRec> unused;
-            level_major(true, q_slots, q_ring, unused, qrecs, qfovf, left);
-            graph.add(&d->d_qrecs, qrecs);
-            graph.add(&d->d_qfovf, qfovf);
-            graph.add(&d->d_q_copied, left);
-            d->qfovf_len = (int32_t)qfovf.size();
-            d->n_q_copied = (int32_t)(left.size() / 2);
+            graph.add(&d->d_nodes, nodes);
+            graph.add(&d->d_ovf_idx, ovf_idx);
         }
-        if (lring > 0) {
-            std::vector<Dag::QuadRec> unused;
-            std::vector<int32_t> none_left;
-            level_major(false, per_pass, lring, lrecs, unused, lfovf, none_left);
-            graph.add(&d->d_lrecs, lrecs);
-            graph.add(&d->d_lfovf, lfovf);
-            d->lfovf_len = (int32_t)lfovf.size();
-        } else if (max_width <= per_pass) {
-            const int32_t row_bytes = d->k1_wc * 8, zero_row = ring * row_bytes;
-            frecs.resize(M);
-            for (int32_t l = 0; l < n_node_levels; ++l)
-                for (int32_t q = nlvl_ptr[l]; q < nlvl_ptr[l + 1]; ++q) {
-                    const Dag::NodeRec &r = nodes[q];
-                    Dag::FastRec &f = frecs[q];
-                    tmp.clear();
-                    for (int j = 0; j < 6; ++j) if (r.in[j] != INT32_MIN) tmp.push_back(r.in[j]);
-                    if (r.ovf_beg >= 0)
-                        for (int32_t e = 1; e <= ovf_idx[r.ovf_beg]; ++e) tmp.push_back(ovf_idx[r.ovf_beg + e]);
-                    int nn = 0, nr = 0;
-                    bool resident = true;       // every node input is in the ring while level l is computed
-                    for (int32_t x : tmp) {
-                        if (x < 0) { ++nr; continue; }
-                        ++nn;
-                        resident = resident && x >= nlvl_ptr[l + 1] - ring;
-                    }
-                    f.op = r.op;
-                    f.ovf = -1;
-                    for (int j = 0; j < 4; ++j) f.in[j] = zero_row;
-                    f.rcv[0] = f.rcv[1] = -1;
-                    if (nn <= 4 && nr <= 2 && resident) {
-                        int a = 0, b = 0;
-                        for (int32_t x : tmp) {
-                            if (x < 0) f.rcv[b++] = ~x;
-                            else f.in[a++] = (d->k1_wave ? x : (x & (ring - 1))) * row_bytes;
-                        }
-                    } else {
-                        f.ovf = (int32_t)fovf.size();
-                        fovf.push_back((int32_t)tmp.size());
-                        fovf.insert(fovf.end(), tmp.begin(), tmp.end());
-                    }
-                }
-            graph.add(&d->d_frecs, frecs);
-            graph.add(&d->d_fovf, fovf);
-            d->fovf_len = (int32_t)fovf.size();
-        }
+        graph.add(&d->d_nlvl_ptr, nlvl_ptr);
+        graph.add(&d->d_chunk_end, chunk_end);
     }
     graph.add(&d->d_copied, copied);
     const size_t dep_words = (size_t)n * d->W;
     if (own_dep) {
+        graph.add(&d->d_recv_of_op, recv_of_op);
         op_of_col.reserve(d->N);
         for (int32_t v = 0; v < n; ++v)
             if (recv_of_op[v] < 0) op_of_col.push_back(v);
@@ -941,9 +831,6 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
     }
     if (d->k1_lring > 0)
         graph.reserve(&d->d_k1_sink, (size_t)((d->W + d->k1_wc - 1) / d->k1_wc) * d->k1_threads * 8);
-    if (d->k1_q_ring > 0) graph.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
-    // (sized for the copy back of the rows as well, so that the block is not replaced while a copy is under way)
-    if (own_dep) (void)stage(std::max(graph.host_bytes, dep_words * 8));
     HIP_TRY(graph.commit(&d->d_graph_block, s));
     d->graph_bytes = graph.bytes;
     d->prop_tables = true;
@@ -952,19 +839,136 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
     return TICTAC_OK;
 }
 
+// The level-major records of the kernel with 64-byte slices (see internal.h).  With such slices the ring holds few levels,
+// and a row that a later level needs is handed on by copy nodes (op = -2: one input, the row goes to the ring only) in free
+// slots of the levels between, each within reach of the one before; the copies of a row form one chain, which the
+// consumers, taken level by level, extend.
+static int make_quad_tables(Dag *d, const Condensed &g, hipStream_t s)
+{
+    const int32_t M = g.M, n_node_levels = g.n_levels, P = d->k1_q_threads / 4, ring = d->k1_q_ring;
+    const std::vector<int32_t> copied = copied_rows(g);
+    std::vector<int32_t> lists, left;
+    std::vector<int32_t> slot_of(M), node_at(M);     // of a node; the nodes by position
+    for (int32_t k = 0; k < M; ++k) {
+        slot_of[k] = g.lvl[k] * P + (g.pos[k] - g.lvl_ptr[g.lvl[k]]);
+        node_at[g.pos[k]] = k;
+    }
+    const uint32_t zero2 = (uint32_t)ring | (uint32_t)ring << 16;
+    std::vector<Dag::QuadRec> qrecs((size_t)n_node_levels * P, Dag::QuadRec{zero2, zero2, 0xffffffffu, -1});
+    const int32_t reach = ring / P - 1;        // a row of level x is in the ring up to level x + reach
+    std::vector<int32_t> used(n_node_levels);
+    for (int32_t l = 0; l < n_node_levels; ++l) used[l] = g.lvl_ptr[l + 1] - g.lvl_ptr[l];
+    std::unordered_map<int32_t, std::vector<int32_t>> chain;       // slot of a row -> slots of its copies
+    auto within_reach = [&](int32_t slot, int32_t l) -> int32_t {   // the slot to read at level l, or -1
+        if ((int64_t)slot >= (int64_t)(l + 1) * P - ring) return slot;
+        if (reach < 1 || l - slot / P > 8 * reach) return -1;
+        std::vector<int32_t> &ch = chain[slot];
+        int32_t cur = ch.empty() ? slot : ch.back();
+        while (l - cur / P > reach) {
+            int32_t t = cur / P + reach;
+            while (t > cur / P && used[t] >= P) --t;
+            if (t == cur / P) return -1;
+            const int32_t c = t * P + used[t]++;
+            qrecs[c].in01 = (uint32_t)(cur & (ring - 1)) | (uint32_t)ring << 16;
+            qrecs[c].op = -2;
+            ch.push_back(c);
+            cur = c;
+        }
+        return cur;
+    };
+    for (int32_t q = 0; q < M; ++q) {
+        const int32_t k = node_at[q], l = g.lvl[k];
+        Dag::QuadRec &f = qrecs[slot_of[k]];
+        f.op = g.op[k];
+        int nn = 0, nr = 0;
+        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) (*x < 0 ? nr : nn) += 1;
+        // (copies are made only for a node that then fits a record)
+        bool resident = nn <= 4 && nr <= 2;
+        uint32_t in[4] = {(uint32_t)ring, (uint32_t)ring, (uint32_t)ring, (uint32_t)ring}, rc[2] = {0xffffu, 0xffffu};
+        int a = 0, b = 0;
+        if (resident)
+            for (const int32_t *x = g.begin(k); x != g.end(k); ++x) {
+                if (*x < 0) { rc[b++] = (uint32_t)~*x; continue; }
+                const int32_t c = within_reach(slot_of[*x], l);
+                if (c < 0) { resident = false; break; }
+                in[a++] = (uint32_t)(c & (ring - 1));
+            }
+        if (resident) {
+            f.in01 = in[0] | in[1] << 16;
+            f.in23 = in[2] | in[3] << 16;
+            f.rcv01 = rc[0] | rc[1] << 16;
+            continue;
+        }
+        f.in01 = 0xffffffffu;
+        f.in23 = (uint32_t)lists.size();
+        lists.push_back(nn + nr);
+        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) lists.push_back(*x < 0 ? *x : slot_of[*x]);
+    }
+    // The copied rows ride along in slots that are still free: a recv's row anywhere (no input, one recv
+    // bit), the copy of a node's row at a level within reach of the node or of one of its copy nodes, as
+    // a node with that one input and the op's own id.  What finds no slot stays on the list `left`.
+    int32_t cursor = 0;
+    for (size_t e = 0; e + 1 < copied.size(); e += 2) {
+        const int32_t v = copied[e], sv = copied[e + 1];
+        int32_t c = -1;
+        if (sv < 0) {
+            while (cursor < n_node_levels && used[cursor] >= P) ++cursor;
+            if (cursor < n_node_levels) {
+                c = cursor * P + used[cursor]++;
+                qrecs[c] = Dag::QuadRec{zero2, zero2, (uint32_t)~sv | 0xffff0000u, v};
+            }
+        } else if (reach >= 1) {
+            const int32_t base = slot_of[g.val[sv]];
+            auto it = chain.find(base);
+            const size_t n_cand = 1 + (it == chain.end() ? 0 : it->second.size());
+            for (size_t k = 0; k < n_cand && c < 0; ++k) {
+                const int32_t from = k == 0 ? base : it->second[k - 1];
+                for (int32_t t = from / P + 1; t <= from / P + reach && t < n_node_levels; ++t)
+                    if (used[t] < P) {
+                        c = t * P + used[t]++;
+                        qrecs[c] = Dag::QuadRec{(uint32_t)(from & (ring - 1)) | (uint32_t)ring << 16, zero2, 0xffffffffu, v};
+                        break;
+                    }
+            }
+        }
+        if (c < 0) { left.push_back(v); left.push_back(sv); }
+    }
+    Packer tables;
+    tables.add(&d->d_qrecs, qrecs);
+    tables.add(&d->d_qfovf, lists);
+    tables.add(&d->d_q_copied, left);
+    d->qfovf_len = (int32_t)lists.size();
+    d->n_q_copied = (int32_t)(left.size() / 2);
+    tables.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
+    HIP_TRY(tables.commit(&d->d_quad_block, s));
+    d->quad_bytes = tables.bytes;
+    HIP_TRY(hipStreamSynchronize(s));
+    return TICTAC_OK;
+}
+
 static std::mutex g_tables_mutex;       // of the tables that a handle's first call of a kind makes
 
-// the tables of the propagation kernels of a handle whose op.dep came from the host's rows, made at the first call that
-// runs those kernels
-static int ensure_propagate_tables(Dag *d, hipStream_t s)
+// The tables of the propagation kernels of a handle whose op.dep came from the host's rows, and those of the kernel for
+// several graphs of any handle (`several`), made at the first call that runs those kernels.
+static int ensure_propagate_tables(Dag *d, bool several, hipStream_t s)
 {
     std::lock_guard<std::mutex> lock(g_tables_mutex);
-    if (d->prop_tables) return TICTAC_OK;
+    if (d->prop_tables && (!several || d->k1_q_ring == 0 || d->d_quad_block)) return TICTAC_OK;
     std::vector<int32_t> recv_of_op(d->n, -1), level, order;
     for (int32_t i = 0; i < d->R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
+    bool topological = true;
+    for (int32_t v = 0; v < d->n; ++v)
+        for (int32_t e = d->h_row_ptr[v]; e < d->h_row_ptr[v + 1]; ++e) topological &= d->h_col_idx[e] < v;
     int32_t n_levels = 0;
-    (void)find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), false, true, level, order, n_levels);
-    return make_propagate_tables(d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, false, s);
+    (void)find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), topological, true, level, order, n_levels);
+    if (!d->prop_tables) {
+        const int rc = make_propagate_tables(d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, false, s);
+        if (rc != TICTAC_OK) return rc;
+    }
+    if (!several || d->k1_q_ring == 0) return TICTAC_OK;
+    Condensed g;
+    condense(*d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, g);
+    return make_quad_tables(d, g, s);
 }
 
 // The line between the rows formed on the host and by the kernels: on layered graphs of 11 000 ops and 16 words (0.6 million
@@ -1441,7 +1445,7 @@ int tictac_dag_recompute_deps(tictac_dag *dag, tictac_stream stream)
 {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = reinterpret_cast<Dag *>(dag);
-    const int rc = ensure_propagate_tables(d, (hipStream_t)stream);
+    const int rc = ensure_propagate_tables(d, false, (hipStream_t)stream);
     if (rc != TICTAC_OK) return rc;
     HIP_TRY(launch_propagate(*d, (hipStream_t)stream));
     return TICTAC_OK;
@@ -1457,7 +1461,7 @@ int tictac_dag_recompute_deps_batch(tictac_dag *const *dags, int32_t n_dags, tic
     Dag *const *ds = reinterpret_cast<Dag *const *>(dags);
     hipStream_t s = (hipStream_t)stream;
     for (int32_t g = 0; g < n_dags; ++g) {
-        const int rc = ensure_propagate_tables(ds[g], s);
+        const int rc = ensure_propagate_tables(ds[g], n_dags > 1, s);
         if (rc != TICTAC_OK) return rc;
     }
     HIP_TRY(ensure_workspace(ds[0], propagate_batch_staging_bytes(n_dags)));

@@ -146,8 +146,8 @@ struct Dag {
 
     // scratch owned by the handle (grown on demand, stream-ordered use)
     // the two allocations that hold every array above (graph tables + dep; class tables)
-    void *d_graph_block = nullptr, *d_class_block = nullptr;
-    size_t graph_bytes = 0, class_bytes = 0, send_bytes = 0;
+    void *d_graph_block = nullptr, *d_quad_block = nullptr, *d_class_block = nullptr;
+    size_t graph_bytes = 0, quad_bytes = 0, class_bytes = 0, send_bytes = 0;
     void *d_work = nullptr;
     int32_t *d_chan = nullptr;      // [R] channel table of the last several-channel simulation
     std::vector<int32_t> h_chan;    // its host copy
