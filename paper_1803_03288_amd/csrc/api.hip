@@ -355,72 +355,47 @@ static void group_classes(const std::vector<uint64_t> &rows, int32_t N, int32_t 
         }
 }
 
-// The same grouping from per-op digests (int32[8] per op: a 128-bit hash of the row in the first four words, the
-// number of set bits in the fifth): ops with equal digests form a class.  first_col: the first member of every
+// The same grouping from the device's: rep[j] the lowest op with the row of op j.  first_col: the first member of every
 // class (piece), whose row is the row of the class.
-static void group_digests(const int32_t *digest, int32_t N, int32_t max_members, std::vector<int32_t> &cls_ptr,
-                          std::vector<int32_t> &cls_cols, std::vector<int32_t> &first_col, int32_t &n_distinct)
+static void group_reps(const int32_t *rep, int32_t N, int32_t max_members, std::vector<int32_t> &cls_ptr,
+                       std::vector<int32_t> &cls_cols, std::vector<int32_t> &first_col, int32_t &n_distinct)
 {
-    size_t cap = 16;
-    while (cap < (size_t)N * 2) cap <<= 1;
-    std::vector<int32_t> slot(cap, -1), first, cls_of(N), count;
+    std::vector<int32_t> set_of(N), start(1, 0);
     for (int32_t j = 0; j < N; ++j) {
-        const int32_t *g = digest + (size_t)j * 8;
-        size_t q = ((uint32_t)g[0] ^ ((size_t)(uint32_t)g[1] << 17) ^ ((size_t)(uint32_t)g[3] << 33)) & (cap - 1);
-        for (;;) {
-            const int32_t c = slot[q];
-            if (c < 0) {
-                slot[q] = (int32_t)first.size();
-                cls_of[j] = (int32_t)first.size();
-                first.push_back(j);
-                count.push_back(1);
-                break;
-            }
-            if (memcmp(digest + (size_t)first[c] * 8, g, 5 * sizeof(int32_t)) == 0) {
-                cls_of[j] = c;
-                ++count[c];
-                break;
-            }
-            q = (q + 1) & (cap - 1);
+        if (rep[j] == j) {
+            set_of[j] = (int32_t)start.size() - 1;
+            start.push_back(0);
+        } else {
+            set_of[j] = set_of[rep[j]];
         }
+        ++start[set_of[j] + 1];
     }
-    n_distinct = (int32_t)first.size();
-    std::vector<int32_t> start(n_distinct + 1, 0);
-    for (int32_t c = 0; c < n_distinct; ++c) start[c + 1] = start[c] + count[c];
-    std::vector<int32_t> members(N), fill(start.begin(), start.end() - 1);
-    for (int32_t j = 0; j < N; ++j) members[fill[cls_of[j]]++] = j;
-    cls_ptr.assign(1, 0); cls_cols.clear(); first_col.clear();
+    n_distinct = (int32_t)start.size() - 1;
+    for (int32_t c = 0; c < n_distinct; ++c) start[c + 1] += start[c];
+    cls_cols.resize(N);
+    {
+        std::vector<int32_t> fill(start.begin(), start.end() - 1);
+        for (int32_t j = 0; j < N; ++j) cls_cols[fill[set_of[j]]++] = j;
+    }
+    cls_ptr.reserve(n_distinct + 64);
+    first_col.reserve(n_distinct + 64);
+    cls_ptr.assign(1, 0);
+    first_col.clear();
     for (int32_t c = 0; c < n_distinct; ++c)
         for (int32_t k = start[c]; k < start[c + 1]; k += max_members) {
-            const int32_t e = std::min(start[c + 1], k + max_members);
-            for (int32_t m = k; m < e; ++m) cls_cols.push_back(members[m]);
-            cls_ptr.push_back((int32_t)cls_cols.size());
-            first_col.push_back(first[c]);
+            cls_ptr.push_back(std::min(start[c + 1], k + max_members));
+            first_col.push_back(cls_cols[start[c]]);
         }
 }
 
-// Levels (longest path from a root, in ops before it) and a topological order of a validated graph.  Graphs whose
-// predecessors all have lower ids (topological: true), as traced graphs have as a rule, need no more than one pass over the
-// edges; `order` stays empty for them unless asked for.  False: the graph has a cycle.
-static bool find_levels(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, bool topological, bool want_order,
-                        std::vector<int32_t> &level, std::vector<int32_t> &order, int32_t &n_levels)
+// Levels (longest path from a root, in ops before it) and a topological order of a validated graph.  False: the graph has a
+// cycle.  (A graph whose predecessors all have lower ids, as traced graphs have as a rule, has its ids for an order.)
+static bool find_levels(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, std::vector<int32_t> &level,
+                        std::vector<int32_t> &order, int32_t &n_levels)
 {
     level.assign(n, 0);
     order.clear();
     n_levels = 0;
-    if (topological) {
-        for (int32_t v = 0; v < n; ++v) {
-            int32_t l = 0;
-            for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) l = std::max(l, level[col_idx[e]] + 1);
-            level[v] = l;
-            n_levels = std::max(n_levels, l + 1);
-        }
-        if (want_order) {
-            order.resize(n);
-            std::iota(order.begin(), order.end(), 0);
-        }
-        return true;
-    }
     const int32_t E = row_ptr[n];
     std::vector<int32_t> sptr(n + 1, 0), sidx(E), waiting(n);
     for (int32_t e = 0; e < E; ++e) sptr[col_idx[e] + 1]++;
@@ -956,11 +931,8 @@ static int ensure_propagate_tables(Dag *d, bool several, hipStream_t s)
     if (d->prop_tables && (!several || d->k1_q_ring == 0 || d->d_quad_block)) return TICTAC_OK;
     std::vector<int32_t> recv_of_op(d->n, -1), level, order;
     for (int32_t i = 0; i < d->R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
-    bool topological = true;
-    for (int32_t v = 0; v < d->n; ++v)
-        for (int32_t e = d->h_row_ptr[v]; e < d->h_row_ptr[v + 1]; ++e) topological &= d->h_col_idx[e] < v;
     int32_t n_levels = 0;
-    (void)find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), topological, true, level, order, n_levels);
+    (void)find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), level, order, n_levels);
     if (!d->prop_tables) {
         const int rc = make_propagate_tables(d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, false, s);
         if (rc != TICTAC_OK) return rc;
@@ -988,12 +960,21 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         if (row_ptr[v + 1] < row_ptr[v]) { set_error("pred_row_ptr decreases at op %d", v); return TICTAC_ERR_BAD_CSR; }
     const int32_t E = row_ptr[n];
     if (E > 0 && !col_idx) { set_error("pred_col_idx is NULL"); return TICTAC_ERR_NULL; }
+    // (levels along the way, as long as every predecessor has a lower id)
     bool topological = true;
-    for (int32_t v = 0; v < n; ++v)
+    std::vector<int32_t> level(n, 0);
+    int32_t n_levels = 0;
+    for (int32_t v = 0; v < n; ++v) {
+        int32_t l = 0;
         for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) {
-            if (col_idx[e] < 0 || col_idx[e] >= n) { set_error("pred_col_idx[%d]=%d out of range", e, col_idx[e]); return TICTAC_ERR_BAD_CSR; }
-            topological &= col_idx[e] < v;
+            const int32_t u = col_idx[e];
+            if (u < 0 || u >= n) { set_error("pred_col_idx[%d]=%d out of range", e, u); return TICTAC_ERR_BAD_CSR; }
+            topological &= u < v;
+            l = std::max(l, level[u] + 1);
         }
+        level[v] = l;
+        n_levels = std::max(n_levels, l + 1);
+    }
     std::vector<int32_t> recv_of_op(n, -1);
     for (int32_t i = 0; i < R; ++i) {
         int32_t v = recv_ids[i];
@@ -1010,8 +991,14 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     // can be grouped: the rows are formed here, and the device gets op.dep from those of the sets.  Larger graphs are
     // propagated by the kernels of k1_propagate.hip.
     const bool on_host = ((int64_t)n + E) * std::max(d->W, 1) <= kHostRowWords && !getenv("TICTAC_GROUP_ON_HOST");
-    std::vector<int32_t> level, order;
-    if (!find_levels(n, row_ptr, col_idx, topological, !on_host, level, order, d->n_levels)) {
+    std::vector<int32_t> order;
+    if (topological) {
+        d->n_levels = n_levels;
+        if (!on_host) {
+            order.resize(n);
+            std::iota(order.begin(), order.end(), 0);
+        }
+    } else if (!find_levels(n, row_ptr, col_idx, level, order, d->n_levels)) {
         set_error("the graph has a cycle");
         return TICTAC_ERR_CYCLE;
     }
@@ -1035,8 +1022,8 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     auto classes = [&](const bool on_device) -> int {
     const bool from_sets = on_host;
     // Large graphs (8 MB of rows or more) are grouped without bringing the rows to the host: the device hashes
-    // every row (128 bits, with the number of set bits and the lowest one), the host groups the hashes, and the
-    // device forms the class rows and checks every op's row against its class (on a mismatch, which two
+    // every row (128 bits, with the number of set bits and the lowest one) and finds the ops of equal hashes through a
+    // table, the host numbers the sets, and the device forms the class rows and checks every op's row against its class (on a mismatch, which two
     // different rows with one hash would cause, everything below is done again from the rows themselves).
     std::vector<uint64_t> rows, cls_dep, depT;
     std::vector<int32_t> cls_ptr, cls_cols, cnt0, first_op, lowest, cls_of_set, op_src, op_of_col;
@@ -1044,19 +1031,18 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     // only classes far larger than a lane's fair share of the ops are split
     const int32_t max_members = std::min(256, std::max(16, (d->N + 63) / 64));
     if (on_device) {
-        HIP_TRY(ensure_workspace(d, (size_t)d->N * 32));
-        int32_t *d_digest = static_cast<int32_t *>(d->d_work);
-        HIP_TRY(launch_row_digests(*d, d->d_op_of_col, d_digest, s));
+        HIP_TRY(ensure_workspace(d, group_workspace_bytes(d->N)));
+        HIP_TRY(launch_group_rows(*d, d->d_op_of_col, d->d_work, s));
         std::vector<int32_t> pageable;
-        int32_t *dg = static_cast<int32_t *>(stage((size_t)d->N * 32));
-        if (!dg) {
-            pageable.resize((size_t)d->N * 8);
-            dg = pageable.data();
+        int32_t *rep = static_cast<int32_t *>(stage((size_t)d->N * 12));
+        if (!rep) {
+            pageable.resize((size_t)d->N * 3);
+            rep = pageable.data();
         }
-        HIP_TRY(hipMemcpyAsync(dg, d_digest, (size_t)d->N * 32, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(rep, d->d_work, (size_t)d->N * 12, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         std::vector<int32_t> first_col;
-        group_digests(dg, d->N, max_members, cls_ptr, cls_cols, first_col, d->C_distinct);
+        group_reps(rep, d->N, max_members, cls_ptr, cls_cols, first_col, d->C_distinct);
         d->C = (int32_t)cls_ptr.size() - 1;
         d->Cpad = (d->C + 63) / 64 * 64;
         if (d->R <= 1024 && d->C <= 1024) return 1;      // the small-graph kernels want tables made from the rows
@@ -1065,8 +1051,8 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         for (int32_t v = 0; v < n; ++v)
             if (recv_of_op[v] < 0) op_of_col.push_back(v);
         for (int32_t c = 0; c < d->C; ++c) {
-            cnt0[c] = dg[(size_t)first_col[c] * 8 + 4];
-            lowest[c] = dg[(size_t)first_col[c] * 8 + 5];
+            cnt0[c] = rep[(size_t)d->N + first_col[c]];
+            lowest[c] = rep[(size_t)2 * d->N + first_col[c]];
             first_op[c] = op_of_col[first_col[c]];
         }
     } else if (!from_sets) {

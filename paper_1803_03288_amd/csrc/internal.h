@@ -263,12 +263,13 @@ struct SimArgs {
 };
 // raises *d.d_bad_order when a row of `order` (B rows, or one when order_stride = 0) is no permutation of 0 .. R-1
 // Class grouping on the device, for graphs whose rows are too many to bring back to the host:
-//   launch_row_digests: per compute op (op_of_col[j]) a 128-bit hash of its row, its number of set bits and its
-//   lowest set bit (-1 none), as int32[8] per op: h0 lo, h0 hi, h1 lo, h1 hi, count, lowest, 0, 0;
+//   launch_group_rows: per compute op (op_of_col[j]) the lowest one whose row has the same 128-bit hash and number of
+//   set bits, that number, and the lowest set bit (-1 none), as int32[3][N] at the start of `work`;
 //   launch_class_rows: cls_dep[c] = dep[first_op[c]] for every class, its transpose cls_depT (columns C..Cpad-1
 //   zero), and *mismatch is raised when the row of a compute op differs from the row of its class (two different
 //   rows with one hash: the caller then groups on the host)
-hipError_t launch_row_digests(const Dag &d, const int32_t *op_of_col, int32_t *digest, hipStream_t s);
+size_t group_workspace_bytes(int32_t N);
+hipError_t launch_group_rows(const Dag &d, const int32_t *op_of_col, void *work, hipStream_t s);
 hipError_t launch_class_rows(const Dag &d, const int32_t *op_of_col, const int32_t *first_op, int32_t *mismatch,
                              hipStream_t s);
 hipError_t launch_check_orders(Dag &d, int32_t B, const int32_t *order, int32_t order_stride, hipStream_t s);

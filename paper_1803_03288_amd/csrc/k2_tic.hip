@@ -225,10 +225,64 @@ row_digest_kernel(int32_t N, int32_t W, const int32_t *__restrict__ op_of_col, c
     }
 }
 
-hipError_t launch_row_digests(const Dag &d, const int32_t *op_of_col, int32_t *digest, hipStream_t s)
+// Ops of equal digests find each other through a table of at least twice as many slots, probed one after the other: the
+// first to take a slot lends it its digest, the lowest op of the slot becomes the representative of all of them.
+__global__ void __launch_bounds__(256)
+group_insert_kernel(int32_t N, uint32_t mask, const int4 *__restrict__ digest, int32_t *slot, uint32_t *lowest, uint32_t *where)
 {
-    if (d.N == 0) return hipSuccess;
-    hipLaunchKernelGGL(row_digest_kernel, dim3((d.N + 3) / 4), dim3(256), 0, s, d.N, d.W, op_of_col, d.d_dep, digest);
+    const int32_t j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= N) return;
+    const int4 g = digest[2 * (size_t)j];
+    const int cnt = digest[2 * (size_t)j + 1].x;
+    uint32_t q = ((uint32_t)g.x ^ (uint32_t)g.y * 0x9E3779B1u ^ (uint32_t)g.w) & mask;
+    for (uint32_t tries = 0; tries <= mask; ++tries) {
+        const int32_t held = atomicCAS(&slot[q], -1, j);
+        const int32_t leader = held < 0 ? j : held;
+        const int4 l = digest[2 * (size_t)leader];
+        if (l.x == g.x && l.y == g.y && l.z == g.z && l.w == g.w && digest[2 * (size_t)leader + 1].x == cnt) break;
+        q = (q + 1) & mask;
+    }
+    atomicMin(&lowest[q], (uint32_t)j);
+    where[j] = q;
+}
+
+// out: [N] the representative of every op, [N] the set bits of its row, [N] the lowest one
+__global__ void __launch_bounds__(256)
+group_out_kernel(int32_t N, const int4 *__restrict__ digest, const uint32_t *__restrict__ lowest, const uint32_t *__restrict__ where,
+                 int32_t *out)
+{
+    const int32_t j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= N) return;
+    const int4 d = digest[2 * (size_t)j + 1];
+    out[j] = (int32_t)lowest[where[j]];
+    out[N + (size_t)j] = d.x;
+    out[2 * (size_t)N + j] = d.y;
+}
+
+// workspace: the result [3][N] first (see group_out_kernel), then digests [N][8], slots, lowest members and the op's slot
+static uint32_t group_slots(int32_t N)
+{
+    uint32_t cap = 64;
+    while (cap < 2 * (uint32_t)N) cap *= 2;
+    return cap;
+}
+static size_t group_digest_offset(int32_t N) { return ((size_t)N * 12 + 255) & ~(size_t)255; }
+size_t group_workspace_bytes(int32_t N) { return group_digest_offset(N) + (size_t)N * 36 + (size_t)group_slots(N) * 8; }
+
+hipError_t launch_group_rows(const Dag &d, const int32_t *op_of_col, void *work, hipStream_t s)
+{
+    const int32_t N = d.N;
+    if (N == 0) return hipSuccess;
+    const uint32_t cap = group_slots(N);
+    int32_t *digest = reinterpret_cast<int32_t *>(static_cast<char *>(work) + group_digest_offset(N));
+    int32_t *slot = digest + (size_t)N * 8;
+    uint32_t *lowest = reinterpret_cast<uint32_t *>(slot + cap), *where = lowest + cap;
+    const int4 *dg = reinterpret_cast<const int4 *>(digest);
+    const dim3 per_op((N + 255) / 256);
+    hipLaunchKernelGGL(row_digest_kernel, dim3((N + 3) / 4), dim3(256), 0, s, N, d.W, op_of_col, d.d_dep, digest);
+    hipLaunchKernelGGL(fill_i32, dim3((2 * cap + 255) / 256), dim3(256), 0, s, slot, (int32_t)(2 * cap), -1);
+    hipLaunchKernelGGL(group_insert_kernel, per_op, dim3(256), 0, s, N, cap - 1, dg, slot, lowest, where);
+    hipLaunchKernelGGL(group_out_kernel, per_op, dim3(256), 0, s, N, dg, lowest, where, static_cast<int32_t *>(work));
     return hipGetLastError();
 }
 
