@@ -6,9 +6,10 @@
 #include <string.h>
 
 #include <algorithm>
+#include <future>
+#include <memory>
 #include <mutex>
 #include <numeric>
-#include <unordered_map>
 
 #include "chain_plan.h"
 #include "internal.h"
@@ -631,18 +632,145 @@ static std::vector<int32_t> copied_rows(const Condensed &g)
     return copied;
 }
 
+// The level-major records of the kernel with 64-byte slices (see internal.h).  With such slices the ring holds few levels,
+// and a row that a later level needs is handed on by copy nodes (op = -2: one input, the row goes to the ring only) in free
+// slots of the levels between, each within reach of the one before; the copies of a row form one chain, which the
+// consumers, taken level by level, extend.
+struct QuadTables {
+    std::vector<Dag::QuadRec> qrecs;
+    std::vector<int32_t> lists, left;       // inputs of the nodes that fit no record; copied rows that found no slot
+};
+static QuadTables make_quad_tables(const Condensed &g, const std::vector<int32_t> &copied, int32_t P, int32_t ring)
+{
+    const int32_t M = g.M, n_node_levels = g.n_levels;
+    QuadTables out;
+    std::vector<int32_t> &lists = out.lists, &left = out.left;
+    std::vector<int32_t> slot_of(M), node_at(M);     // of a node; the nodes by position
+    for (int32_t k = 0; k < M; ++k) {
+        slot_of[k] = g.lvl[k] * P + (g.pos[k] - g.lvl_ptr[g.lvl[k]]);
+        node_at[g.pos[k]] = k;
+    }
+    const uint32_t none = (uint32_t)ring, zero2 = none | none << 16;
+    std::vector<Dag::QuadRec> &qrecs = out.qrecs;
+    qrecs.assign((size_t)n_node_levels * P, Dag::QuadRec{zero2, zero2, 0xffffffffu, -1});
+    const int32_t reach = ring / P - 1;        // a row of level x is in the ring up to level x + reach
+    std::vector<int32_t> used(n_node_levels);
+    for (int32_t l = 0; l < n_node_levels; ++l) used[l] = g.lvl_ptr[l + 1] - g.lvl_ptr[l];
+    // the copies of node k's row, from the first to the last: copy q at level copy_lvl[q], followed by copy_next[q]
+    std::vector<int32_t> first_copy(M, -1), last_copy(M, -1), copy_slot, copy_lvl, copy_next;
+    auto within_reach = [&](int32_t k, int32_t l) -> int32_t {      // the slot to read the row of node k from at level l, or -1
+        if (g.lvl[k] + reach >= l || slot_of[k] >= (l + 1) * P - ring) return slot_of[k];
+        if (reach < 1 || l - g.lvl[k] > 8 * reach) return -1;
+        int32_t q = last_copy[k], cur = q < 0 ? slot_of[k] : copy_slot[q], at = q < 0 ? g.lvl[k] : copy_lvl[q];
+        while (l - at > reach) {
+            int32_t t = at + reach;
+            while (t > at && used[t] >= P) --t;
+            if (t == at) return -1;
+            const int32_t c = t * P + used[t]++;
+            qrecs[c].in01 = (uint32_t)(cur & (ring - 1)) | none << 16;
+            qrecs[c].op = -2;
+            const int32_t made = (int32_t)copy_slot.size();
+            copy_slot.push_back(c); copy_lvl.push_back(t); copy_next.push_back(-1);
+            (q < 0 ? first_copy[k] : copy_next[q]) = made;
+            q = last_copy[k] = made;
+            cur = c;
+            at = t;
+        }
+        return cur;
+    };
+    for (int32_t p = 0; p < M; ++p) {
+        const int32_t k = node_at[p], l = g.lvl[k];
+        Dag::QuadRec &f = qrecs[slot_of[k]];
+        f.op = g.op[k];
+        int nn = 0, nr = 0;
+        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) (*x < 0 ? nr : nn) += 1;
+        // (copies are made only for a node that then fits a record)
+        bool resident = nn <= 4 && nr <= 2;
+        uint32_t in[4] = {none, none, none, none}, rc[2] = {0xffffu, 0xffffu};
+        int a = 0, b = 0;
+        if (resident)
+            for (const int32_t *x = g.begin(k); x != g.end(k); ++x) {
+                if (*x < 0) { rc[b++] = (uint32_t)~*x; continue; }
+                const int32_t c = within_reach(*x, l);
+                if (c < 0) { resident = false; break; }
+                in[a++] = (uint32_t)(c & (ring - 1));
+            }
+        if (resident) {
+            f.in01 = in[0] | in[1] << 16;
+            f.in23 = in[2] | in[3] << 16;
+            f.rcv01 = rc[0] | rc[1] << 16;
+            continue;
+        }
+        f.in01 = 0xffffffffu;
+        f.in23 = (uint32_t)lists.size();
+        lists.push_back(nn + nr);
+        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) lists.push_back(*x < 0 ? *x : slot_of[*x]);
+    }
+    // The copied rows ride along in slots that are still free: a recv's row anywhere (no input, one recv
+    // bit), the copy of a node's row at a level within reach of the node or of one of its copy nodes, as
+    // a node with that one input and the op's own id.  What finds no slot stays on the list `left`.
+    int32_t cursor = 0;
+    for (size_t e = 0; e + 1 < copied.size(); e += 2) {
+        const int32_t v = copied[e], sv = copied[e + 1];
+        int32_t c = -1;
+        if (sv < 0) {
+            while (cursor < n_node_levels && used[cursor] >= P) ++cursor;
+            if (cursor < n_node_levels) {
+                c = cursor * P + used[cursor]++;
+                qrecs[c] = Dag::QuadRec{zero2, zero2, (uint32_t)~sv | 0xffff0000u, v};
+            }
+        } else if (reach >= 1) {
+            const int32_t k = g.val[sv];
+            int32_t from = slot_of[k], at = g.lvl[k], q = first_copy[k];
+            for (;;) {
+                const int32_t end = std::min(at + reach + 1, n_node_levels);
+                int32_t t = at + 1;
+                while (t < end && used[t] >= P) ++t;
+                if (t < end) {
+                    c = t * P + used[t]++;
+                    qrecs[c] = Dag::QuadRec{(uint32_t)(from & (ring - 1)) | none << 16, zero2, 0xffffffffu, v};
+                }
+                if (c >= 0 || q < 0) break;
+                from = copy_slot[q]; at = copy_lvl[q]; q = copy_next[q];
+            }
+        }
+        if (c < 0) { left.push_back(v); left.push_back(sv); }
+    }
+    return out;
+}
+
+static int upload_quad_tables(Dag *d, const QuadTables &q, hipStream_t s)
+{
+    Packer tables;
+    tables.add(&d->d_qrecs, q.qrecs);
+    tables.add(&d->d_qfovf, q.lists);
+    tables.add(&d->d_q_copied, q.left);
+    d->qfovf_len = (int32_t)q.lists.size();
+    d->n_q_copied = (int32_t)(q.left.size() / 2);
+    tables.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
+    HIP_TRY(tables.commit(&d->d_quad_block, s));
+    d->quad_bytes = tables.bytes;
+    // (the staging block is free again, and the arrays may go, once the copy is done)
+    HIP_TRY(hipStreamSynchronize(s));
+    return TICTAC_OK;
+}
+
 // order: the ops in topological order; level: longest path from a root.  own_dep: the handle's op.dep is made by these
-// kernels (large graphs), so its block holds op.dep as well.
+// kernels (large graphs), so its block holds op.dep as well.  The tables for several graphs are made by a thread of their own
+// meanwhile; `later`: where the caller takes them from (upload_quad_tables), or NULL to have them uploaded here.
 static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
-                                 const std::vector<int32_t> &level, const std::vector<int32_t> &order, bool own_dep, hipStream_t s)
+                                 const std::vector<int32_t> &level, const std::vector<int32_t> &order, bool own_dep,
+                                 std::future<QuadTables> *later, hipStream_t s)
 {
     const int32_t n = d->n;
-    Condensed g;
+    const auto kept = std::make_shared<Condensed>();
+    Condensed &g = *kept;
     condense(*d, row_ptr, col_idx, recv_of_op, level, order, g);
     const int32_t M = g.M, n_node_levels = g.n_levels, max_width = g.max_width;
     const std::vector<int32_t> &nlvl_ptr = g.lvl_ptr;
     d->M = M; d->n_node_levels = n_node_levels; d->max_node_level_width = max_width;
-    const std::vector<int32_t> copied = copied_rows(g);
+    const auto copied_kept = std::make_shared<std::vector<int32_t>>(copied_rows(g));
+    const std::vector<int32_t> &copied = *copied_kept;
     d->n_copied = (int32_t)(copied.size() / 2);
     Packer graph;
     std::vector<Dag::NodeRec> nodes;
@@ -700,7 +828,7 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
     d->k1_lring = lring;
     // Rows of a multiple of eight words, levels of at most 256 nodes: the kernel with 64-byte slices (four lanes per
     // slot, or two with 32-byte slices; P slots per level, a multiple of 32 so that the slots of a wave are whole; 2048
-    // slots in the ring), which the propagation of several graphs by one launch takes; its records are made then.
+    // slots in the ring), which the propagation of several graphs by one launch takes (make_quad_tables).
     int32_t q_slots = (max_width + 31) / 32 * 32, q_ring = 0;
     if (q_slots < 32) q_slots = 32;
     if (d->k1_wc == 1 && d->W % 8 == 0 && d->W <= 1016 && max_width <= 256 && M > 0 &&
@@ -711,6 +839,8 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
     }
     d->k1_q_ring = q_ring;
     d->k1_q_threads = q_ring > 0 ? 4 * q_slots : 0;
+    std::future<QuadTables> quads;
+    if (q_ring > 0) quads = std::async([=] { return make_quad_tables(*kept, *copied_kept, q_slots, q_ring); });
 
     // FastRec of node k at level l: place(x) the byte offset of input node x in the ring, or -1 when it has left it
     auto fast = [&](Dag::FastRec &f, int32_t k, int32_t zero_row, std::vector<int32_t> &lists, auto &&place, auto &&name) {
@@ -811,136 +941,26 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
     d->prop_tables = true;
     // (the staging block is free again, and the arrays may go, once the copy is done)
     HIP_TRY(hipStreamSynchronize(s));
-    return TICTAC_OK;
-}
-
-// The level-major records of the kernel with 64-byte slices (see internal.h).  With such slices the ring holds few levels,
-// and a row that a later level needs is handed on by copy nodes (op = -2: one input, the row goes to the ring only) in free
-// slots of the levels between, each within reach of the one before; the copies of a row form one chain, which the
-// consumers, taken level by level, extend.
-static int make_quad_tables(Dag *d, const Condensed &g, hipStream_t s)
-{
-    const int32_t M = g.M, n_node_levels = g.n_levels, P = d->k1_q_threads / 4, ring = d->k1_q_ring;
-    const std::vector<int32_t> copied = copied_rows(g);
-    std::vector<int32_t> lists, left;
-    std::vector<int32_t> slot_of(M), node_at(M);     // of a node; the nodes by position
-    for (int32_t k = 0; k < M; ++k) {
-        slot_of[k] = g.lvl[k] * P + (g.pos[k] - g.lvl_ptr[g.lvl[k]]);
-        node_at[g.pos[k]] = k;
+    if (later) {
+        *later = std::move(quads);
+        return TICTAC_OK;
     }
-    const uint32_t zero2 = (uint32_t)ring | (uint32_t)ring << 16;
-    std::vector<Dag::QuadRec> qrecs((size_t)n_node_levels * P, Dag::QuadRec{zero2, zero2, 0xffffffffu, -1});
-    const int32_t reach = ring / P - 1;        // a row of level x is in the ring up to level x + reach
-    std::vector<int32_t> used(n_node_levels);
-    for (int32_t l = 0; l < n_node_levels; ++l) used[l] = g.lvl_ptr[l + 1] - g.lvl_ptr[l];
-    std::unordered_map<int32_t, std::vector<int32_t>> chain;       // slot of a row -> slots of its copies
-    auto within_reach = [&](int32_t slot, int32_t l) -> int32_t {   // the slot to read at level l, or -1
-        if ((int64_t)slot >= (int64_t)(l + 1) * P - ring) return slot;
-        if (reach < 1 || l - slot / P > 8 * reach) return -1;
-        std::vector<int32_t> &ch = chain[slot];
-        int32_t cur = ch.empty() ? slot : ch.back();
-        while (l - cur / P > reach) {
-            int32_t t = cur / P + reach;
-            while (t > cur / P && used[t] >= P) --t;
-            if (t == cur / P) return -1;
-            const int32_t c = t * P + used[t]++;
-            qrecs[c].in01 = (uint32_t)(cur & (ring - 1)) | (uint32_t)ring << 16;
-            qrecs[c].op = -2;
-            ch.push_back(c);
-            cur = c;
-        }
-        return cur;
-    };
-    for (int32_t q = 0; q < M; ++q) {
-        const int32_t k = node_at[q], l = g.lvl[k];
-        Dag::QuadRec &f = qrecs[slot_of[k]];
-        f.op = g.op[k];
-        int nn = 0, nr = 0;
-        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) (*x < 0 ? nr : nn) += 1;
-        // (copies are made only for a node that then fits a record)
-        bool resident = nn <= 4 && nr <= 2;
-        uint32_t in[4] = {(uint32_t)ring, (uint32_t)ring, (uint32_t)ring, (uint32_t)ring}, rc[2] = {0xffffu, 0xffffu};
-        int a = 0, b = 0;
-        if (resident)
-            for (const int32_t *x = g.begin(k); x != g.end(k); ++x) {
-                if (*x < 0) { rc[b++] = (uint32_t)~*x; continue; }
-                const int32_t c = within_reach(slot_of[*x], l);
-                if (c < 0) { resident = false; break; }
-                in[a++] = (uint32_t)(c & (ring - 1));
-            }
-        if (resident) {
-            f.in01 = in[0] | in[1] << 16;
-            f.in23 = in[2] | in[3] << 16;
-            f.rcv01 = rc[0] | rc[1] << 16;
-            continue;
-        }
-        f.in01 = 0xffffffffu;
-        f.in23 = (uint32_t)lists.size();
-        lists.push_back(nn + nr);
-        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) lists.push_back(*x < 0 ? *x : slot_of[*x]);
-    }
-    // The copied rows ride along in slots that are still free: a recv's row anywhere (no input, one recv
-    // bit), the copy of a node's row at a level within reach of the node or of one of its copy nodes, as
-    // a node with that one input and the op's own id.  What finds no slot stays on the list `left`.
-    int32_t cursor = 0;
-    for (size_t e = 0; e + 1 < copied.size(); e += 2) {
-        const int32_t v = copied[e], sv = copied[e + 1];
-        int32_t c = -1;
-        if (sv < 0) {
-            while (cursor < n_node_levels && used[cursor] >= P) ++cursor;
-            if (cursor < n_node_levels) {
-                c = cursor * P + used[cursor]++;
-                qrecs[c] = Dag::QuadRec{zero2, zero2, (uint32_t)~sv | 0xffff0000u, v};
-            }
-        } else if (reach >= 1) {
-            const int32_t base = slot_of[g.val[sv]];
-            auto it = chain.find(base);
-            const size_t n_cand = 1 + (it == chain.end() ? 0 : it->second.size());
-            for (size_t k = 0; k < n_cand && c < 0; ++k) {
-                const int32_t from = k == 0 ? base : it->second[k - 1];
-                for (int32_t t = from / P + 1; t <= from / P + reach && t < n_node_levels; ++t)
-                    if (used[t] < P) {
-                        c = t * P + used[t]++;
-                        qrecs[c] = Dag::QuadRec{(uint32_t)(from & (ring - 1)) | (uint32_t)ring << 16, zero2, 0xffffffffu, v};
-                        break;
-                    }
-            }
-        }
-        if (c < 0) { left.push_back(v); left.push_back(sv); }
-    }
-    Packer tables;
-    tables.add(&d->d_qrecs, qrecs);
-    tables.add(&d->d_qfovf, lists);
-    tables.add(&d->d_q_copied, left);
-    d->qfovf_len = (int32_t)lists.size();
-    d->n_q_copied = (int32_t)(left.size() / 2);
-    tables.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
-    HIP_TRY(tables.commit(&d->d_quad_block, s));
-    d->quad_bytes = tables.bytes;
-    HIP_TRY(hipStreamSynchronize(s));
-    return TICTAC_OK;
+    return q_ring > 0 ? upload_quad_tables(d, quads.get(), s) : TICTAC_OK;
 }
 
 static std::mutex g_tables_mutex;       // of the tables that a handle's first call of a kind makes
 
-// The tables of the propagation kernels of a handle whose op.dep came from the host's rows, and those of the kernel for
-// several graphs of any handle (`several`), made at the first call that runs those kernels.
-static int ensure_propagate_tables(Dag *d, bool several, hipStream_t s)
+// the tables of the propagation kernels of a handle whose op.dep came from the host's rows, made at the first call that
+// runs those kernels
+static int ensure_propagate_tables(Dag *d, hipStream_t s)
 {
     std::lock_guard<std::mutex> lock(g_tables_mutex);
-    if (d->prop_tables && (!several || d->k1_q_ring == 0 || d->d_quad_block)) return TICTAC_OK;
+    if (d->prop_tables) return TICTAC_OK;
     std::vector<int32_t> recv_of_op(d->n, -1), level, order;
     for (int32_t i = 0; i < d->R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
     int32_t n_levels = 0;
     (void)find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), level, order, n_levels);
-    if (!d->prop_tables) {
-        const int rc = make_propagate_tables(d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, false, s);
-        if (rc != TICTAC_OK) return rc;
-    }
-    if (!several || d->k1_q_ring == 0) return TICTAC_OK;
-    Condensed g;
-    condense(*d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, g);
-    return make_quad_tables(d, g, s);
+    return make_propagate_tables(d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, false, nullptr, s);
 }
 
 // The line between the rows formed on the host and by the kernels: on layered graphs of 11 000 ops and 16 words (0.6 million
@@ -1008,10 +1028,11 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     HIP_TRY(hipGetDevice(&d->device));
 
     HostSets sets;
+    std::future<QuadTables> quads;
     if (on_host) {
         host_sets(n, d->W, row_ptr, col_idx, recv_of_op, order, sets);
     } else {
-        const int rc = make_propagate_tables(d, row_ptr, col_idx, recv_of_op, level, order, true, s);
+        const int rc = make_propagate_tables(d, row_ptr, col_idx, recv_of_op, level, order, true, &quads, s);
         if (rc != TICTAC_OK) return rc;
         if ((size_t)n * d->W) HIP_TRY(launch_propagate(*d, s));
     }
@@ -1201,6 +1222,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         }
         rc = classes(false);
     }
+    if (rc == TICTAC_OK && quads.valid()) rc = upload_quad_tables(d, quads.get(), s);
     return rc;
 }
 
@@ -1431,7 +1453,7 @@ int tictac_dag_recompute_deps(tictac_dag *dag, tictac_stream stream)
 {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = reinterpret_cast<Dag *>(dag);
-    const int rc = ensure_propagate_tables(d, false, (hipStream_t)stream);
+    const int rc = ensure_propagate_tables(d, (hipStream_t)stream);
     if (rc != TICTAC_OK) return rc;
     HIP_TRY(launch_propagate(*d, (hipStream_t)stream));
     return TICTAC_OK;
@@ -1447,7 +1469,7 @@ int tictac_dag_recompute_deps_batch(tictac_dag *const *dags, int32_t n_dags, tic
     Dag *const *ds = reinterpret_cast<Dag *const *>(dags);
     hipStream_t s = (hipStream_t)stream;
     for (int32_t g = 0; g < n_dags; ++g) {
-        const int rc = ensure_propagate_tables(ds[g], n_dags > 1, s);
+        const int rc = ensure_propagate_tables(ds[g], s);
         if (rc != TICTAC_OK) return rc;
     }
     HIP_TRY(ensure_workspace(ds[0], propagate_batch_staging_bytes(n_dags)));
