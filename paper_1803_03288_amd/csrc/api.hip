@@ -1213,7 +1213,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     }
     return TICTAC_OK;
     };
-    int rc = classes(dep_words * 8 >= ((size_t)8 << 20) && d->N > 0 && !on_host && !getenv("TICTAC_GROUP_ON_HOST"));
+    int rc = classes(dep_words * 8 >= ((size_t)8 << 20) && d->N > 0 && group_on_device(d->N, d->W) && !on_host && !getenv("TICTAC_GROUP_ON_HOST"));
     if (rc == 1) {
         if (d->d_class_block) {
             HIP_TRY(hipStreamSynchronize(s));

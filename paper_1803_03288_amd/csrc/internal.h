@@ -268,6 +268,8 @@ struct SimArgs {
 //   launch_class_rows: cls_dep[c] = dep[first_op[c]] for every class, its transpose cls_depT (columns C..Cpad-1
 //   zero), and *mismatch is raised when the row of a compute op differs from the row of its class (two different
 //   rows with one hash: the caller then groups on the host)
+//   (graphs for which group_on_device says no are grouped on the host)
+bool group_on_device(int32_t N, int32_t W);
 size_t group_workspace_bytes(int32_t N);
 hipError_t launch_group_rows(const Dag &d, const int32_t *op_of_col, void *work, hipStream_t s);
 hipError_t launch_class_rows(const Dag &d, const int32_t *op_of_col, const int32_t *first_op, int32_t *mismatch,

@@ -9,9 +9,9 @@
 
 namespace tictac {
 
-__global__ void fill_i32(int32_t *p, int32_t n, int32_t value)
+__global__ void fill_i32(int32_t *p, size_t n, int32_t value)
 {
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = value;
 }
 
@@ -158,7 +158,7 @@ hipError_t launch_tic(const Dag &d, int32_t *prio, int32_t *order, int32_t *rank
                            in_lds ? (int32_t)words : 0, Rpad, parts, d.d_cls_depT, d.d_cls_cnt0, prio, order, rank);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(fill_i32, dim3((R + 255) / 256), dim3(256), 0, s, prio, R, (int32_t)TICTAC_PRIO_INF);
+    hipLaunchKernelGGL(fill_i32, dim3((R + 255) / 256), dim3(256), 0, s, prio, (size_t)R, (int32_t)TICTAC_PRIO_INF);
     if (d.n > 0) {
         const int32_t rows_per_block = d.n <= 4096 ? 32 : 128;
         const int blocks = (d.n + rows_per_block - 1) / rows_per_block;
@@ -260,6 +260,7 @@ group_out_kernel(int32_t N, const int4 *__restrict__ digest, const uint32_t *__r
 }
 
 // workspace: the result [3][N] first (see group_out_kernel), then digests [N][8], slots, lowest members and the op's slot
+// (N is bounded by group_on_device, so the places of the table are counted in 32 bits)
 static uint32_t group_slots(int32_t N)
 {
     uint32_t cap = 64;
@@ -269,10 +270,14 @@ static uint32_t group_slots(int32_t N)
 static size_t group_digest_offset(int32_t N) { return ((size_t)N * 12 + 255) & ~(size_t)255; }
 size_t group_workspace_bytes(int32_t N) { return group_digest_offset(N) + (size_t)N * 36 + (size_t)group_slots(N) * 8; }
 
+// The digests take a wave per op and the check of the rows a thread per word; a grid counts its threads in 32 bits.
+bool group_on_device(int32_t N, int32_t W) { return N <= 1 << 25 && (int64_t)N * W <= (int64_t)1 << 31; }
+
 hipError_t launch_group_rows(const Dag &d, const int32_t *op_of_col, void *work, hipStream_t s)
 {
     const int32_t N = d.N;
     if (N == 0) return hipSuccess;
+    if (!group_on_device(N, d.W)) return hipErrorInvalidValue;
     const uint32_t cap = group_slots(N);
     int32_t *digest = reinterpret_cast<int32_t *>(static_cast<char *>(work) + group_digest_offset(N));
     int32_t *slot = digest + (size_t)N * 8;
@@ -280,7 +285,7 @@ hipError_t launch_group_rows(const Dag &d, const int32_t *op_of_col, void *work,
     const int4 *dg = reinterpret_cast<const int4 *>(digest);
     const dim3 per_op((N + 255) / 256);
     hipLaunchKernelGGL(row_digest_kernel, dim3((N + 3) / 4), dim3(256), 0, s, N, d.W, op_of_col, d.d_dep, digest);
-    hipLaunchKernelGGL(fill_i32, dim3((2 * cap + 255) / 256), dim3(256), 0, s, slot, (int32_t)(2 * cap), -1);
+    hipLaunchKernelGGL(fill_i32, dim3((2 * cap + 255) / 256), dim3(256), 0, s, slot, (size_t)2 * cap, -1);
     hipLaunchKernelGGL(group_insert_kernel, per_op, dim3(256), 0, s, N, cap - 1, dg, slot, lowest, where);
     hipLaunchKernelGGL(group_out_kernel, per_op, dim3(256), 0, s, N, dg, lowest, where, static_cast<int32_t *>(work));
     return hipGetLastError();
