@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <exception>
 #include <future>
 #include <memory>
 #include <mutex>
@@ -25,6 +26,22 @@ void set_error(const char *fmt, ...)
     vsnprintf(g_err, sizeof(g_err), fmt, ap);
     va_end(ap);
 }
+
+// No exception leaves an entry point: each is a function try block that ends in TT_CATCH.
+static int caught()
+{
+    try {
+        throw;
+    } catch (const std::bad_alloc &) {
+        set_error("out of host memory");
+    } catch (const std::exception &e) {             // (a length or a thread that the host cannot provide)
+        set_error("out of host resources: %s", e.what());
+    } catch (...) {
+        set_error("out of host resources");
+    }
+    return TICTAC_ERR_NO_MEM;
+}
+#define TT_CATCH catch (...) { return caught(); }
 
 #define HIP_TRY(expr)                                                                        \
     do {                                                                                     \
@@ -84,21 +101,22 @@ static hipError_t pool_alloc(void **p, size_t bytes)
 }
 
 // (the device has finished with the block)
-static void pool_put(void *p, size_t bytes, int device)
+static void pool_put(void *p, size_t bytes, int device) noexcept
 {
     if (!p) return;
     const size_t want = pool_size(bytes);
     if (want > kPoolMax) { (void)hipFree(p); return; }
-    std::vector<void *> out;
-    {
-        std::lock_guard<std::mutex> lock(g_pool_mutex);
+    std::lock_guard<std::mutex> lock(g_pool_mutex);
+    try {
         g_pool.push_back({p, want, device});
-        g_pool_bytes += want;
-        size_t n = 0;
-        while (g_pool_bytes > kPoolMax) { g_pool_bytes -= g_pool[n].bytes; out.push_back(g_pool[n++].p); }
-        g_pool.erase(g_pool.begin(), g_pool.begin() + n);
+    } catch (const std::bad_alloc &) {
+        (void)hipFree(p);
+        return;
     }
-    for (void *q : out) (void)hipFree(q);
+    g_pool_bytes += want;
+    size_t n = 0;
+    while (g_pool_bytes > kPoolMax) { g_pool_bytes -= g_pool[n].bytes; (void)hipFree(g_pool[n++].p); }
+    g_pool.erase(g_pool.begin(), g_pool.begin() + n);
 }
 
 // Pinned host memory for the transfers of tictac_build_deps: one block per calling thread,
@@ -1402,25 +1420,24 @@ extern "C" {
 
 int tictac_build_deps(int32_t n_ops, const int32_t *pred_row_ptr, const int32_t *pred_col_idx, int32_t n_recv,
                       const int32_t *recv_ids, tictac_stream stream, tictac_dag **out)
-{
+try {
     if (!out) { set_error("out is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = new (std::nothrow) Dag();
     if (!d) { set_error("out of host memory"); return TICTAC_ERR_NO_MEM; }
     int rc;
     try {
         rc = build(n_ops, pred_row_ptr, pred_col_idx, n_recv, recv_ids, (hipStream_t)stream, d);
-    } catch (const std::bad_alloc &) {
-        set_error("out of host memory");
-        rc = TICTAC_ERR_NO_MEM;
+    } catch (...) {
+        rc = caught();
     }
     if (rc != TICTAC_OK) { free_dag(d); return rc; }
     *out = reinterpret_cast<tictac_dag *>(d);
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_dag_info(const tictac_dag *dag, int32_t *n_ops, int32_t *n_recv, int32_t *words, int32_t *n_levels,
                     int32_t *n_classes)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     const Dag *d = reinterpret_cast<const Dag *>(dag);
     if (n_ops) *n_ops = d->n;
@@ -1429,17 +1446,17 @@ int tictac_dag_info(const tictac_dag *dag, int32_t *n_ops, int32_t *n_recv, int3
     if (n_levels) *n_levels = d->n_levels;
     if (n_classes) *n_classes = d->C_distinct;
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_dag_deps(const tictac_dag *dag, const uint64_t **dep_device)
-{
+try {
     if (!dag || !dep_device) { set_error("NULL argument"); return TICTAC_ERR_NULL; }
     *dep_device = reinterpret_cast<const Dag *>(dag)->d_dep;
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_dag_copy_deps(const tictac_dag *dag, uint64_t *dst_device, tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     const Dag *d = reinterpret_cast<const Dag *>(dag);
     const size_t bytes = (size_t)d->n * d->W * 8;
@@ -1447,20 +1464,20 @@ int tictac_dag_copy_deps(const tictac_dag *dag, uint64_t *dst_device, tictac_str
     if (!dst_device) { set_error("dst_device is NULL"); return TICTAC_ERR_NULL; }
     HIP_TRY(hipMemcpyAsync(dst_device, d->d_dep, bytes, hipMemcpyDeviceToDevice, (hipStream_t)stream));
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_dag_recompute_deps(tictac_dag *dag, tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = reinterpret_cast<Dag *>(dag);
     const int rc = ensure_propagate_tables(d, (hipStream_t)stream);
     if (rc != TICTAC_OK) return rc;
     HIP_TRY(launch_propagate(*d, (hipStream_t)stream));
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_dag_recompute_deps_batch(tictac_dag *const *dags, int32_t n_dags, tictac_stream stream)
-{
+try {
     if (n_dags < 0) { set_error("n_dags = %d is negative", n_dags); return TICTAC_ERR_UNSUPPORTED; }
     if (n_dags == 0) return TICTAC_OK;
     if (!dags) { set_error("dags is NULL"); return TICTAC_ERR_NULL; }
@@ -1481,24 +1498,24 @@ int tictac_dag_recompute_deps_batch(tictac_dag *const *dags, int32_t n_dags, tic
     }
     HIP_TRY(e);
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_dag_free(tictac_dag *dag)
-{
+try {
     if (!dag) return TICTAC_OK;
     free_dag(reinterpret_cast<Dag *>(dag));
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_tic_priority(const tictac_dag *dag, int32_t *prio, int32_t *order, int32_t *rank, tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     const Dag *d = reinterpret_cast<const Dag *>(dag);
     if (d->R == 0) return TICTAC_OK;
     if (!prio) { set_error("prio is NULL"); return TICTAC_ERR_NULL; }
     HIP_TRY(launch_tic(*d, prio, order, rank, nullptr, (hipStream_t)stream));
     return TICTAC_OK;
-}
+} TT_CATCH
 
 static int check_batch(const Dag *d, int32_t B, const void *op_time, const void *recv_time)
 {
@@ -1510,7 +1527,7 @@ static int check_batch(const Dag *d, int32_t B, const void *op_time, const void 
 
 int tictac_tac_priority(const tictac_dag *dag, int32_t B, const double *op_time, const double *recv_time,
                         int32_t *order, int32_t *rank, double *sel_P, double *sel_Mplus, tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = const_cast<Dag *>(reinterpret_cast<const Dag *>(dag));
     int rc = check_batch(d, B, op_time, recv_time);
@@ -1520,7 +1537,7 @@ int tictac_tac_priority(const tictac_dag *dag, int32_t B, const double *op_time,
     TacArgs a{B, op_time, recv_time, order, rank, sel_P, sel_Mplus, false, nullptr, nullptr, nullptr, nullptr, nullptr};
     HIP_TRY(launch_tac(*d, a, (hipStream_t)stream));
     return TICTAC_OK;
-}
+} TT_CATCH
 
 static int tac_simulate_any(const tictac_dag *dag, int32_t B, const void *op_time, const void *recv_time, bool f32,
                             int32_t *order, int32_t *rank, double *sel_P, double *sel_Mplus, double *makespan,
@@ -1568,7 +1585,7 @@ static hipError_t scratch_address(int32_t **out)
 int tictac_tac_simulate_noalloc(const tictac_dag *dag, int32_t B, const double *op_time, const double *recv_time,
                                 int32_t *order, int32_t *rank, double *makespan, double *eff, double *U, double *L,
                                 double *S, tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = const_cast<Dag *>(reinterpret_cast<const Dag *>(dag));
     int rc = check_batch(d, B, op_time, recv_time);
@@ -1591,23 +1608,23 @@ int tictac_tac_simulate_noalloc(const tictac_dag *dag, int32_t B, const double *
     }
     HIP_TRY(e);
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_tac_simulate(const tictac_dag *dag, int32_t B, const double *op_time, const double *recv_time,
                         int32_t *order, int32_t *rank, double *sel_P, double *sel_Mplus, double *makespan,
                         double *eff, double *U, double *L, double *S, tictac_stream stream)
-{
+try {
     return tac_simulate_any(dag, B, op_time, recv_time, false, order, rank, sel_P, sel_Mplus, makespan, eff, U, L, S,
                             stream);
-}
+} TT_CATCH
 
 int tictac_tac_simulate_f32(const tictac_dag *dag, int32_t B, const float *op_time, const float *recv_time,
                             int32_t *order, int32_t *rank, double *sel_P, double *sel_Mplus, double *makespan,
                             double *eff, double *U, double *L, double *S, tictac_stream stream)
-{
+try {
     return tac_simulate_any(dag, B, op_time, recv_time, true, order, rank, sel_P, sel_Mplus, makespan, eff, U, L, S,
                             stream);
-}
+} TT_CATCH
 
 static int simulate_any(const tictac_dag *dag, int32_t B, const int32_t *order, int32_t order_stride,
                         const void *op_time, const void *recv_time, bool f32, double *makespan, double *eff, double *U,
@@ -1633,22 +1650,22 @@ static int simulate_any(const tictac_dag *dag, int32_t B, const int32_t *order, 
 int tictac_simulate(const tictac_dag *dag, int32_t B, const int32_t *order, int32_t order_stride,
                     const double *op_time, const double *recv_time, double *makespan, double *eff, double *U,
                     double *L, double *S, tictac_stream stream)
-{
+try {
     return simulate_any(dag, B, order, order_stride, op_time, recv_time, false, makespan, eff, U, L, S, stream);
-}
+} TT_CATCH
 
 int tictac_simulate_f32(const tictac_dag *dag, int32_t B, const int32_t *order, int32_t order_stride,
                         const float *op_time, const float *recv_time, double *makespan, double *eff, double *U,
                         double *L, double *S, tictac_stream stream)
-{
+try {
     return simulate_any(dag, B, order, order_stride, op_time, recv_time, true, makespan, eff, U, L, S, stream);
-}
+} TT_CATCH
 
 int tictac_simulate_channels(const tictac_dag *dag, int32_t B, int32_t n_channels, const int32_t *channel_of_recv,
                              const int32_t *order, int32_t order_stride, const double *op_time,
                              const double *recv_time, double *makespan, double *eff, double *U, double *L,
                              double *S, tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = const_cast<Dag *>(reinterpret_cast<const Dag *>(dag));
     int rc = check_batch(d, B, op_time, recv_time);
@@ -1690,10 +1707,10 @@ int tictac_simulate_channels(const tictac_dag *dag, int32_t B, int32_t n_channel
     }
     HIP_TRY(e);
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_dag_check_orders(tictac_dag *dag, tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = reinterpret_cast<Dag *>(dag);
     if (!d->d_bad_order) return TICTAC_OK;
@@ -1705,7 +1722,7 @@ int tictac_dag_check_orders(tictac_dag *dag, tictac_stream stream)
     HIP_TRY(hipMemsetAsync(d->d_bad_order, 0, sizeof(int32_t), s));
     set_error("an order given since the last check was no permutation of 0 .. n_recv-1");
     return TICTAC_ERR_BAD_ORDER;
-}
+} TT_CATCH
 
 // Tables of the iteration with send ops for the given send set (kept until another set is given).
 // TICTAC_OK, or the status to return (the error text is set).
@@ -1899,7 +1916,7 @@ int tictac_simulate_sends(const tictac_dag *dag, int32_t B, int32_t n_send, cons
                           const int32_t *order, int32_t order_stride, const double *op_time,
                           const double *recv_time, double *makespan, double *eff, double *U, double *L, double *S,
                           tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = const_cast<Dag *>(reinterpret_cast<const Dag *>(dag));
     int rc = check_batch(d, B, op_time, recv_time);
@@ -1930,33 +1947,33 @@ int tictac_simulate_sends(const tictac_dag *dag, int32_t B, int32_t n_send, cons
     }
     HIP_TRY(e);
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_straggler_effect(int32_t B, int32_t w, const double *makespan, double *straggler, tictac_stream stream)
-{
+try {
     if (B < 0) { set_error("B = %d is negative", B); return TICTAC_ERR_UNSUPPORTED; }
     if (w < 1) { set_error("w = %d, expected at least 1", w); return TICTAC_ERR_UNSUPPORTED; }
     if (B / w == 0) return TICTAC_OK;
     if (!makespan || !straggler) { set_error("makespan or straggler is NULL"); return TICTAC_ERR_NULL; }
     HIP_TRY(launch_straggler(B, w, makespan, straggler, (hipStream_t)stream));
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_time_oracle_min(int32_t n_runs, int64_t n, const double *runs, double *time, tictac_stream stream)
-{
+try {
     if (n_runs < 1) { set_error("n_runs = %d, expected at least 1", n_runs); return TICTAC_ERR_UNSUPPORTED; }
     if (n < 0) { set_error("n is negative"); return TICTAC_ERR_UNSUPPORTED; }
     if (n == 0) return TICTAC_OK;
     if (!runs || !time) { set_error("runs or time is NULL"); return TICTAC_ERR_NULL; }
     HIP_TRY(launch_time_oracle_min(n_runs, n, runs, time, (hipStream_t)stream));
     return TICTAC_OK;
-}
+} TT_CATCH
 
 int tictac_order_search(const tictac_dag *dag, int32_t B, const int32_t *order, int32_t order_stride,
                         int32_t n_moves, const int32_t *moves, const double *op_time, const double *recv_time,
                         int32_t *best_order, double *best_makespan, double *start_makespan, int32_t *n_accepted,
                         tictac_stream stream)
-{
+try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
     Dag *d = const_cast<Dag *>(reinterpret_cast<const Dag *>(dag));
     int rc = check_batch(d, B, op_time, recv_time);
@@ -1985,7 +2002,7 @@ int tictac_order_search(const tictac_dag *dag, int32_t B, const int32_t *order, 
     }
     HIP_TRY(e);
     return TICTAC_OK;
-}
+} TT_CATCH
 
 const char *tictac_last_error(void) { return g_err; }
 

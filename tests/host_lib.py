@@ -48,7 +48,8 @@ class HostLib:
     def __init__(self, path: str):
         self.L = ctypes.CDLL(path)
         self.L.tictac_last_error.restype = ctypes.c_char_p
-        self.L.host_count.restype = self.L.host_group_bytes.restype = I64
+        for f in ("host_count", "host_group_bytes", "host_fail_new_left", "host_fail_device_left"):
+            getattr(self.L, f).restype = I64
         for f in ("host_fail_device", "host_device_limit", "host_fail_new"):
             getattr(self.L, f).argtypes = [I64]
         self.L.host_delays.argtypes = [I64, I64]

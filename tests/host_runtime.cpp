@@ -30,7 +30,7 @@ struct Launch { std::string name; int64_t grid, block, lds, filled; };      // (
 std::vector<Launch> g_launches;
 std::atomic<int64_t> g_fail_device{-1}, g_fail_new{-1}, g_device_limit{INT64_MAX};
 std::atomic<int64_t> g_waits{0}, g_allocs{0}, g_frees{0}, g_device_bytes{0}, g_pinned_bytes{0}, g_new_calls{0}, g_event_delay_us{0}, g_wait_us{0};
-std::atomic<int> g_capturing{0};
+std::atomic<int> g_capturing{0}, g_paused{0};
 thread_local hipError_t g_last = hipSuccess;
 thread_local bool g_inside = false;             // (allocations of the stand-in itself do not fail)
 struct Inside { bool was; Inside() : was(g_inside) { g_inside = true; } ~Inside() { g_inside = was; } };
@@ -47,7 +47,7 @@ void wait_a_little() { if (const int64_t us = g_wait_us.load()) std::this_thread
 
 void *operator new(size_t n)
 {
-    if (!g_inside) {
+    if (!g_inside && !g_paused) {
         ++g_new_calls;
         if (strikes(g_fail_new)) throw std::bad_alloc();
     }
@@ -109,7 +109,7 @@ hipError_t hipMalloc(void **p, size_t n)
     if (g_capturing) return result(hipErrorStreamCaptureUnsupported);
     *p = nullptr;
     ++g_allocs;
-    if (strikes(g_fail_device) || (int64_t)n + g_device_bytes.load() > g_device_limit.load()) return result(hipErrorOutOfMemory);
+    if ((!g_paused && strikes(g_fail_device)) || (int64_t)n + g_device_bytes.load() > g_device_limit.load()) return result(hipErrorOutOfMemory);
     *p = calloc(1, n);
     std::lock_guard<std::mutex> lock(g_mutex);
     g_blocks[*p] = n;
@@ -203,6 +203,9 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
 void host_fail_device(int64_t after) { g_fail_device = after; }          // the allocation after so many more; -1: none
 void host_device_limit(int64_t bytes) { g_device_limit = bytes < 0 ? INT64_MAX : bytes; }
 void host_fail_new(int64_t after) { g_fail_new = after; }
+int64_t host_fail_new_left() { return g_fail_new; }
+int64_t host_fail_device_left() { return g_fail_device; }
+void host_pause_failures(int on) { g_paused = on; }
 void host_capturing(int on) { g_capturing = on; }
 void host_delays(int64_t event_us, int64_t wait_us) { g_event_delay_us = event_us; g_wait_us = wait_us; }
 int64_t host_count(const char *what)

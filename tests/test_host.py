@@ -1,9 +1,13 @@
 """The library's host code against a stand-in for the HIP runtime (host_lib.py): no GPU, no kernel runs."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
-from host_lib import HostLib, build_host_lib
+from paper_1803_03288_amd import workloads as wl
+
+from host_lib import HostLib, I32, build_host_lib, ptr
 
 
 @pytest.fixture(scope="module")
@@ -32,3 +36,81 @@ def test_the_table_of_the_class_grouping_is_cleared_whole(lib, N, W):
     for name, blocks, threads, _, filled in launches:
         assert blocks * threads < 1 << 32
         assert blocks * threads >= (filled if "fill_i32" in name else N)
+
+
+# ---- memory that runs out ----
+
+def layered(levels, width, recvs):
+    return wl.layered_dag(41, levels=levels, width=width, fan_in=(1, 3), back=3, n_recv=recvs, attach=(1, 3))
+
+
+def with_sends():
+    """The chain of twelve jobs, and a send behind each of its compute ops."""
+    d = wl.chain_dag(12)
+    behind = d.compute_ids()
+    k = behind.size
+    row = np.concatenate([d.row_ptr, d.row_ptr[-1] + 1 + np.arange(k)]).astype(np.int32)
+    col = np.concatenate([d.col_idx, behind]).astype(np.int32)
+    return wl.Dag("chain_sends", d.n_ops + k, row, col, d.recv_ids, np.ones(d.n_compute + k), np.ones(d.n_recv))
+
+
+GRAPHS = {
+    "chain": lambda: wl.chain_dag(40),                  # rows formed on the host, TAC by chains
+    "layered": lambda: layered(30, 12, 70),             # rows formed on the host, TAC in registers
+    "wide": lambda: layered(16, 220, 512),              # level-major records of both kinds, bit-sliced TAC
+    "device": lambda: layered(60, 220, 1280),           # rows formed on the device
+}
+
+
+def calls(lib, d):
+    """The calls on a handle that may take memory, as ``(name, call)``."""
+    B, R = 8192, d.n_recv
+    room, five = {}, [np.zeros(64) for _ in range(5)]
+    op, rv = np.ones((64, d.n_compute)), np.ones((64, R))
+    order, chan = np.arange(R, dtype=np.int32), np.zeros(R, dtype=np.int32)
+    out = [ptr(x) for x in five]
+    big = d.n_ops > 2000
+    yield "recompute", lambda h: lib.tictac_dag_recompute_deps(h, None)
+    yield "batch", lambda h: lib.tictac_dag_recompute_deps_batch((ctypes.c_void_p * 2)(h, h), I32(2), None)
+    yield "tac", lambda h: lib.tac(h, d, 300 if big else B, room)
+    yield "simulate", lambda h: lib.tictac_simulate(h, I32(64), ptr(order), I32(0), ptr(op), ptr(rv), *out, None)
+    if not big:
+        yield "channels", lambda h: lib.tictac_simulate_channels(h, I32(64), I32(2), ptr(chan), ptr(order), I32(0), ptr(op), ptr(rv), *out, None)
+    if d.name == "chain_sends":
+        sends = np.arange(24, 36, dtype=np.int32)
+        yield "sends", lambda h: lib.tictac_simulate_sends(h, I32(64), I32(12), ptr(sends), ptr(order), I32(0), ptr(op), ptr(rv), *out, None)
+
+
+@pytest.mark.parametrize("name", list(GRAPHS) + ["sends"])
+def test_no_exception_leaves_an_entry_point(lib, name):
+    """Every allocation of host memory that a call makes fails once, one after the other: the call says so."""
+    d = with_sends() if name == "sends" else GRAPHS[name]()
+
+    def fails_at_each(call, done):
+        for k in range(4000):
+            lib.host_fail_new(k)
+            rc, h = call()
+            struck = lib.host_fail_new_left() < 0
+            lib.host_fail_new(-1)
+            if not struck:
+                assert rc == 0, lib.error()
+                return h
+            assert rc in (0, -8), (k, rc, lib.error())          # (0: made do without)
+            done(h)
+        raise AssertionError("no end")
+
+    h = fails_at_each(lambda: lib.build(d), lambda h: lib.free(h) if h.value else None)
+    lib.free(h)
+    for what, call in calls(lib, d):
+        handles = []
+
+        def fresh():
+            lib.host_pause_failures(1)
+            rc, h = lib.build(d)
+            lib.host_pause_failures(0)
+            assert rc == 0
+            handles.append(h)
+            return call(h), h
+        fails_at_each(fresh, lambda h: None)
+        for h in handles:
+            lib.free(h)
