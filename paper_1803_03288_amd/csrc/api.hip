@@ -97,7 +97,9 @@ static hipError_t pool_alloc(void **p, size_t bytes)
         g_pool.clear();
         g_pool_bytes = 0;
     }
-    return hipMalloc(p, want);
+    e = hipMalloc(p, want);
+    if (e != hipSuccess) (void)hipGetLastError();       // (else the next launch would report it)
+    return e;
 }
 
 // (the device has finished with the block)
@@ -117,6 +119,17 @@ static void pool_put(void *p, size_t bytes, int device) noexcept
     size_t n = 0;
     while (g_pool_bytes > kPoolMax) { g_pool_bytes -= g_pool[n].bytes; (void)hipFree(g_pool[n++].p); }
     g_pool.erase(g_pool.begin(), g_pool.begin() + n);
+}
+
+// Gives a block of a handle back once the device has finished with it.
+static hipError_t release(Block &b, int device)
+{
+    if (!b.p) return hipSuccess;
+    const hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) return e;
+    pool_put(b.p, b.bytes, device);
+    b = Block();
+    return hipSuccess;
 }
 
 // Pinned host memory for the transfers of tictac_build_deps: one block per calling thread,
@@ -156,7 +169,7 @@ constexpr size_t kCopyInMax = (size_t)512 << 10;
 struct Packer {
     struct Part { void **dst; const void *src; size_t bytes, off; };
     std::vector<Part> parts;
-    size_t host_bytes = 0, device_only = 0, bytes = 0;      // bytes: of the block, after commit()
+    size_t host_bytes = 0, device_only = 0;
 
     static size_t align(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -180,29 +193,36 @@ struct Packer {
         parts.push_back({reinterpret_cast<void **>(dst), nullptr, n_bytes, align(host_bytes) + device_only});
         device_only += align(n_bytes);
     }
-    hipError_t commit(void **block, hipStream_t s)
+    // What the block held is released first.  On an error no array of the packer is there, and what has been allocated
+    // belongs to the block.
+    hipError_t commit(Block &block, int device, hipStream_t s)
     {
-        *block = nullptr;
+        for (const Part &p : parts) *p.dst = nullptr;
+        hipError_t e = release(block, device);
         const size_t total = align(host_bytes) + device_only;
-        if (!total) return hipSuccess;
-        hipError_t e = pool_alloc(block, total);
-        if (e != hipSuccess) return e;
-        bytes = total;
+        if (e != hipSuccess || !total) return e;
         std::vector<char> pageable;
         char *st = static_cast<char *>(stage(host_bytes));
         if (!st && host_bytes) {
             pageable.resize(host_bytes);
             st = pageable.data();
         }
-        for (const Part &p : parts) {
-            *p.dst = static_cast<char *>(*block) + p.off;
+        e = pool_alloc(&block.p, total);
+        if (e != hipSuccess) return e;
+        block.bytes = total;
+        for (const Part &p : parts)
             if (p.src) memcpy(st + p.off, p.src, p.bytes);
+        if (host_bytes) {
+            // (small blocks: a kernel reads the pinned memory itself)
+            if (pageable.empty() && host_bytes <= kCopyInMax) {
+                e = launch_copy_in(block.p, st, host_bytes, s);
+            } else {
+                e = hipMemcpyAsync(block.p, st, host_bytes, hipMemcpyHostToDevice, s);
+                if (!pageable.empty() && e == hipSuccess) e = hipStreamSynchronize(s);
+            }
         }
-        if (!host_bytes) return hipSuccess;
-        // (small blocks: a kernel reads the pinned memory itself)
-        if (pageable.empty() && host_bytes <= kCopyInMax) return launch_copy_in(*block, st, host_bytes, s);
-        e = hipMemcpyAsync(*block, st, host_bytes, hipMemcpyHostToDevice, s);
-        if (!pageable.empty() && e == hipSuccess) e = hipStreamSynchronize(s);
+        for (const Part &p : parts)
+            if (e == hipSuccess) *p.dst = static_cast<char *>(block.p) + p.off;
         return e;
     }
 };
@@ -305,10 +325,9 @@ static void free_dag(Dag *d)
     if (other) (void)hipSetDevice(d->device);
     // (whatever still runs on the blocks is waited for, on any stream; only then may another handle take them)
     const bool idle = hipDeviceSynchronize() == hipSuccess;
-    const struct { void *p; size_t bytes; } blocks[] = {
-        {d->d_graph_block, d->graph_bytes}, {d->d_quad_block, d->quad_bytes}, {d->d_class_block, d->class_bytes}, {d->d_work, d->work_bytes},
-        {d->d_chan, (size_t)d->R * sizeof(int32_t)}, {d->d_send_block, d->send_bytes}, {d->chain.block, d->chain.bytes},
-        {d->d_sliced_block, d->sliced_bytes}};
+    const Block blocks[] = {
+        d->graph_block, d->quad_block, d->class_block, {d->d_work, d->work_bytes}, {d->d_chan, (size_t)d->R * sizeof(int32_t)},
+        d->send_block, d->chain.block, d->sliced_block};
     for (const auto &b : blocks) {
         if (!b.p) continue;
         if (idle) pool_put(b.p, b.bytes, d->device);
@@ -766,8 +785,7 @@ static int upload_quad_tables(Dag *d, const QuadTables &q, hipStream_t s)
     d->qfovf_len = (int32_t)q.lists.size();
     d->n_q_copied = (int32_t)(q.left.size() / 2);
     tables.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
-    HIP_TRY(tables.commit(&d->d_quad_block, s));
-    d->quad_bytes = tables.bytes;
+    HIP_TRY(tables.commit(d->quad_block, d->device, s));
     // (the staging block is free again, and the arrays may go, once the copy is done)
     HIP_TRY(hipStreamSynchronize(s));
     return TICTAC_OK;
@@ -954,16 +972,17 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
     }
     if (d->k1_lring > 0)
         graph.reserve(&d->d_k1_sink, (size_t)((d->W + d->k1_wc - 1) / d->k1_wc) * d->k1_threads * 8);
-    HIP_TRY(graph.commit(&d->d_graph_block, s));
-    d->graph_bytes = graph.bytes;
-    d->prop_tables = true;
+    HIP_TRY(graph.commit(d->graph_block, d->device, s));
     // (the staging block is free again, and the arrays may go, once the copy is done)
     HIP_TRY(hipStreamSynchronize(s));
     if (later) {
         *later = std::move(quads);
-        return TICTAC_OK;
+    } else if (q_ring > 0) {
+        const int rc = upload_quad_tables(d, quads.get(), s);
+        if (rc != TICTAC_OK) return rc;
     }
-    return q_ring > 0 ? upload_quad_tables(d, quads.get(), s) : TICTAC_OK;
+    d->prop_tables = true;
+    return TICTAC_OK;
 }
 
 static std::mutex g_tables_mutex;       // of the tables that a handle's first call of a kind makes
@@ -1215,8 +1234,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         cls.reserve(&d->d_cls_dep, (size_t)d->C * d->W * 8);
         cls.reserve(&d->d_cls_depT, (size_t)d->W * d->Cpad * 8);
     }
-    HIP_TRY(cls.commit(&d->d_class_block, s));
-    d->class_bytes = cls.bytes;
+    HIP_TRY(cls.commit(d->class_block, d->device, s));
     if (from_sets && dep_words) HIP_TRY(launch_expand_sets(*d, s));
     int32_t *mismatch = d->d_bad_order + 1;         // (a second word of the zeroed flag block)
     if (on_device) HIP_TRY(launch_class_rows(*d, d->d_op_of_col, d->d_cls_first_op, mismatch, s));
@@ -1232,14 +1250,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     return TICTAC_OK;
     };
     int rc = classes(dep_words * 8 >= ((size_t)8 << 20) && d->N > 0 && group_on_device(d->N, d->W) && !on_host && !getenv("TICTAC_GROUP_ON_HOST"));
-    if (rc == 1) {
-        if (d->d_class_block) {
-            HIP_TRY(hipStreamSynchronize(s));
-            pool_put(d->d_class_block, d->class_bytes, d->device);
-            d->d_class_block = nullptr;
-        }
-        rc = classes(false);
-    }
+    if (rc == 1) rc = classes(false);
     if (rc == TICTAC_OK && quads.valid()) rc = upload_quad_tables(d, quads.get(), s);
     return rc;
 }
@@ -1256,10 +1267,12 @@ static std::vector<int32_t> classes_of_ops(const Dag *d)
 hipError_t ensure_sliced_tables(Dag *d, hipStream_t s)
 {
     std::lock_guard<std::mutex> lock(g_tables_mutex);
-    if (d->sliced_tried) return hipSuccess;
-    d->sliced_tried = true;
+    if (d->sliced_made) return hipSuccess;
     const int32_t CW = (d->C + 63) / 64;
-    if (d->R < 1 || d->W > 64 || CW > 15 * 64 * 4) return hipSuccess;
+    if (d->R < 1 || d->W > 64 || CW > 15 * 64 * 4) {
+        d->sliced_made = true;
+        return hipSuccess;
+    }
     const std::vector<int32_t> cls_of_op = classes_of_ops(d), &cnt0 = d->h_cls_cnt0;
     Packer cls;
     d->CW = CW;
@@ -1338,22 +1351,24 @@ hipError_t ensure_sliced_tables(Dag *d, hipStream_t s)
     cls.reserve(&d->d_colbits, (size_t)d->R * d->CWpad * 8);
     cls.reserve(&d->d_planes0, (size_t)13 * d->CWpad * 8);
     cls.reserve(&d->d_live0, (size_t)d->CWpad * 8);
-    hipError_t e = cls.commit(&d->d_sliced_block, s);
+    hipError_t e = cls.commit(d->sliced_block, d->device, s);
     if (e != hipSuccess) return e;
-    d->sliced_bytes = cls.bytes;
     e = launch_sliced_tables(*d, s);
-    if (e != hipSuccess) return e;
-    return hipStreamSynchronize(s);                 // the copy came out of `cls` or of the staging block
+    if (e == hipSuccess) e = hipStreamSynchronize(s);       // the copy came out of `cls` or of the staging block
+    d->sliced_made = e == hipSuccess;
+    return e;
 }
 
 hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
 {
     std::lock_guard<std::mutex> lock(g_tables_mutex);
     ChainTables &c = d->chain;
-    if (c.tried) return hipSuccess;
-    c.tried = true;
+    if (c.made) return hipSuccess;
     const int32_t n = d->n, N = d->N, R = d->R, W = d->W;
-    if (d->h_cls_dep.empty() || R < 1) return hipSuccess;
+    if (d->h_cls_dep.empty() || R < 1) {
+        c.made = true;
+        return hipSuccess;
+    }
     // pieces of one set (classes with equal rows) are one set again: they follow each other
     std::vector<const uint64_t *> rows;
     std::vector<int32_t> row_of_set, set_of_cls(d->C), set_of_col(N);
@@ -1381,7 +1396,10 @@ hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
     }
     ChainPlan p;
     make_chain_plan(R, W, N, (int)rows.size(), rows.data(), row_of_set.data(), set_of_col.data(), in_ptr, in, set_of_col, p);
-    if (!p.ok) return hipSuccess;
+    if (!p.ok) {
+        c.made = true;
+        return hipSuccess;
+    }
     static_assert(sizeof(ChainRec) == 16 && sizeof(ChainGate) == 16, "records are read as 16 bytes");
     Packer t;
     ChainRec *rec = nullptr;
@@ -1398,9 +1416,8 @@ hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
     t.add(&c.d_flush, p.flush);
     t.add(&c.d_flush_row, p.flush_row);
     t.add(&c.d_block_first, p.block_first);
-    hipError_t e = t.commit(&c.block, s);
+    hipError_t e = t.commit(c.block, d->device, s);
     if (e != hipSuccess) return e;
-    c.bytes = t.bytes;
     e = hipStreamSynchronize(s);                    // the copy came out of `t` or of the staging block
     if (e != hipSuccess) return e;
     c.d_rec = reinterpret_cast<int4 *>(rec);
@@ -1408,7 +1425,7 @@ hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
     c.n_chains = p.n_slots; c.n_totals = p.n_totals; c.n_gates = (int32_t)p.gate.size(); c.n_list = (int32_t)p.list.size();
     c.start = p.start; c.n_start = p.n_start; c.n_several = (int32_t)p.several.size(); c.empty = p.empty;
     c.n_extra = p.n_extra; c.n_pairs = p.n_pairs; c.n_head = (int32_t)p.head.size();
-    c.ok = true;
+    c.ok = c.made = true;
     return hipSuccess;
 }
 
@@ -1902,10 +1919,7 @@ static int ensure_send_tables(Dag *d, int32_t n_send, const int32_t *send_ids, h
     tables.add(&d->d_send_recv_ids, d->h_recv_ids);
     d->n_send_free = (int32_t)send_free.size();
     d->send_tables_built = false;
-    HIP_TRY(hipStreamSynchronize(s));               // no kernel reads the old tables any more
-    if (d->d_send_block) { pool_put(d->d_send_block, d->send_bytes, d->device); d->d_send_block = nullptr; }
-    HIP_TRY(tables.commit(&d->d_send_block, s));
-    d->send_bytes = tables.bytes;
+    HIP_TRY(tables.commit(d->send_block, d->device, s));
     HIP_TRY(hipStreamSynchronize(s));               // the copy came out of `tables`, which ends here
     d->h_send_ids.assign(send_ids, send_ids + n_send);
     d->send_tables_built = true;

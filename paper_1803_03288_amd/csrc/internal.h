@@ -15,12 +15,17 @@ constexpr int kK1Rpt = 4;             // positions per thread group and chunk of
 
 void set_error(const char *fmt, ...);
 
+// A device allocation of a handle (see Packer::commit and release() in api.hip).
+struct Block {
+    void *p = nullptr;
+    size_t bytes = 0;
+};
+
 // Tables of the chain form of TAC (chain_plan.h, k3_tac_chain.hip), made at the first call that takes that form.
 struct ChainTables {
-    bool tried = false, ok = false;
+    bool made = false, ok = false;  // made: whether the graph has the form is known, and if so (ok) the tables are there
     int32_t n_chains = 0, n_totals = 0, n_gates = 0, n_list = 0, start = 0, n_start = 0, n_several = 0, empty = -1, n_extra = 0, n_pairs = 0, n_head = 0;
-    void *block = nullptr;
-    size_t bytes = 0;
+    Block block;
     int4 *d_rec = nullptr, *d_gate = nullptr;
     int16_t *d_list = nullptr, *d_place = nullptr, *d_extra = nullptr;
     int32_t *d_head = nullptr, *d_several = nullptr, *d_cand_ptr = nullptr, *d_cand = nullptr, *d_flush_row = nullptr, *d_block_first = nullptr;
@@ -146,8 +151,7 @@ struct Dag {
 
     // scratch owned by the handle (grown on demand, stream-ordered use)
     // the two allocations that hold every array above (graph tables + dep; class tables)
-    void *d_graph_block = nullptr, *d_quad_block = nullptr, *d_class_block = nullptr;
-    size_t graph_bytes = 0, quad_bytes = 0, class_bytes = 0, send_bytes = 0;
+    Block graph_block, quad_block, class_block;
     void *d_work = nullptr;
     int32_t *d_chan = nullptr;      // [R] channel table of the last several-channel simulation
     std::vector<int32_t> h_chan;    // its host copy
@@ -155,7 +159,7 @@ struct Dag {
     // built for the send set of the last such call (one device block; see k6_sends.hip for the arrays).
     std::vector<int32_t> h_row_ptr, h_col_idx, h_recv_ids, h_send_ids;
     bool send_tables_built = false;
-    void *d_send_block = nullptr;
+    Block send_block;
     int4 *d_send_rec = nullptr, *d_send_succ = nullptr;
     int32_t *d_send_free = nullptr, *d_send_recv_ids = nullptr;
     uint16_t *d_send_indeg = nullptr;
@@ -183,9 +187,8 @@ struct Dag {
     std::vector<uint64_t> h_cls_dep;    // [C][W]   (small graphs only)
     std::vector<int32_t> h_col_cls;     // [N]
     // bit-sliced TAC: its tables are made at the first call that takes it, from |dep| and the lowest recv of every class
-    bool sliced_tried = false;
-    void *d_sliced_block = nullptr;
-    size_t sliced_bytes = 0;
+    bool sliced_made = false;
+    Block sliced_block;
     std::vector<int32_t> h_cls_cnt0, h_cls_lowest;
 };
 

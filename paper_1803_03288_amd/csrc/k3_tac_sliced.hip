@@ -762,7 +762,7 @@ hipError_t launch_sliced_tables(const Dag &d, hipStream_t s)
 
 bool tac_sliced_fits(const Dag &d)
 {
-    return d.d_colbits != nullptr;
+    return d.sliced_made && d.d_colbits != nullptr;
 }
 
 static size_t sliced_lds_bytes(const Dag &d)

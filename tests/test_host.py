@@ -114,3 +114,46 @@ def test_no_exception_leaves_an_entry_point(lib, name):
         fails_at_each(fresh, lambda h: None)
         for h in handles:
             lib.free(h)
+
+
+@pytest.mark.parametrize("name", list(GRAPHS) + ["sends"])
+def test_a_failed_allocation_leaves_nothing_behind(lib, name):
+    """Every allocation of device memory that a call makes fails once, one after the other, and so does every one of host
+    memory: the next call on the handle launches what it launches on a fresh one, and a freed handle's blocks serve the
+    next handle."""
+    d = with_sends() if name == "sends" else GRAPHS[name]()
+    fail = {"device": (lib.host_fail_device, lib.host_fail_device_left), "new": (lib.host_fail_new, lib.host_fail_new_left)}
+
+    def kernels(call, h):
+        lib.host_forget_launches()
+        assert call(h) == 0, lib.error()
+        tables = ("copy_in", "sliced_colbits", "sliced_planes")         # (made once per handle)
+        return [k for k in lib.launches() if not any(t in k[0] for t in tables)]
+
+    for what, call in calls(lib, d):
+        rc, h = lib.build(d)
+        want = kernels(call, h)
+        lib.free(h)
+        for kind, (order, left) in fail.items():
+            for k in range(4000):
+                rc, h = lib.build(d)
+                assert rc == 0
+                lib.host_drain_pool()                           # (so that the call allocates)
+                order(k)
+                rc = call(h)
+                struck = left() < 0
+                order(-1)
+                assert rc in (0, -7, -8), (what, kind, k, lib.error())
+                assert lib.hipGetLastError() == 0, (what, kind, k)
+                assert kernels(call, h) == want, (what, kind, k)
+                lib.free(h)
+                if not struck:
+                    break
+    rc, h = lib.build(d)
+    lib.free(h)
+    allocs = lib.count("allocs")
+    rc, h = lib.build(d)
+    lib.free(h)
+    assert lib.count("allocs") == allocs
+    lib.host_drain_pool()
+    assert lib.count("device_bytes") == 0
