@@ -1360,7 +1360,7 @@ hipError_t ensure_sliced_tables(Dag *d, hipStream_t s)
 }
 
 hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
-{
+try {
     std::lock_guard<std::mutex> lock(g_tables_mutex);
     ChainTables &c = d->chain;
     if (c.made) return hipSuccess;
@@ -1427,6 +1427,8 @@ hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
     c.n_extra = p.n_extra; c.n_pairs = p.n_pairs; c.n_head = (int32_t)p.head.size();
     c.ok = c.made = true;
     return hipSuccess;
+} catch (const std::bad_alloc &) {
+    return hipErrorOutOfMemory;
 }
 
 }  // namespace tictac

@@ -252,8 +252,9 @@ hipError_t launch_sliced_tables(const Dag &d, hipStream_t s);
 // register-resident variant for graphs with few classes; returns hipErrorNotSupported when
 // the graph does not fit it.  Samples it cannot order (a transfer time of zero) are marked
 // in flags[b] = 1 for the general kernel.
-// chain form, one lane per sample (needs d.chain; the same contract as launch_tac_sliced)
-hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, int32_t **flags_out, hipStream_t s);
+// chain form, one lane per sample (needs d.chain; the same contract as launch_tac_sliced; at_least: bytes of the workspace
+// that the pass over the flagged samples needs).  hipErrorOutOfMemory: nothing has been launched
+hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s);
 hipError_t launch_tac_reg(Dag &d, const TacArgs &a, int32_t *flags, hipStream_t s);
 
 struct SimArgs {

@@ -431,16 +431,12 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
     // against 319 us for 64.
     const int32_t chain_min_B = d.C <= 4 * 64 ? 8192 : 64;
     if (!a.sel_P && !a.sel_Mplus && !a.ext_flags && a.B >= chain_min_B) {
+        // (where there is no memory for its tables or for enough samples at once, the kernels below take the call)
+        int32_t *flags = nullptr;
         hipError_t e = ensure_chain_tables(&d, s);
-        if (e != hipSuccess) return e;
-        if (d.chain.ok) {
-            e = ensure_workspace(&d, flag_bytes + gstate_bytes);
-            if (e != hipSuccess) return e;
-            int32_t *flags = nullptr;
-            e = launch_tac_chain(d, a, flag_bytes, &flags, s);
-            if (e == hipSuccess) p.only_flagged = flags;
-            else if (e != hipErrorNotSupported) return e;
-        }
+        if (e == hipSuccess) e = d.chain.ok ? launch_tac_chain(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s) : hipErrorNotSupported;
+        if (e == hipSuccess) p.only_flagged = flags;
+        else if (e != hipErrorNotSupported && e != hipErrorOutOfMemory) return e;
     }
     if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && d.C <= 16 * 64 && d.W <= 6) {
         hipError_t e = ensure_workspace(&d, flag_bytes + gstate_bytes);

@@ -454,17 +454,24 @@ static hipError_t launch_chain_nc(const ChainParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-// Bytes of the workspace that a chunk of samples takes: totals and transposed transfer times.
+// Bytes of the workspace that a chunk of samples takes: totals and transposed transfer times.  Where the device has less,
+// the chunks are halved, down to 8 192 samples: a chunk takes R rounds whatever its size, and below that the
+// register-resident kernel, which needs four bytes per sample, is as fast (launch_tac).
 constexpr size_t kChainChunkBytes = (size_t)512 << 20;
+constexpr size_t kChainChunkLeast = 8192;
 
-hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, int32_t **flags_out, hipStream_t s)
+hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s)
 {
     const ChainTables &c = d.chain;
     if (!c.ok || a.sel_P || a.sel_Mplus) return hipErrorNotSupported;
     const size_t per_sample = ((size_t)c.n_totals + d.R) * 8;
     size_t chunk = std::min((size_t)a.B, kChainChunkBytes / per_sample);
     chunk = (chunk + 63) & ~(size_t)63;
-    hipError_t e = ensure_workspace(&d, flag_bytes + chunk * per_sample);
+    hipError_t e = ensure_workspace(&d, std::max(at_least, flag_bytes + chunk * per_sample));
+    while (e == hipErrorOutOfMemory && chunk > kChainChunkLeast) {
+        chunk = std::max(kChainChunkLeast, (chunk / 2 + 63) & ~(size_t)63);
+        e = ensure_workspace(&d, std::max(at_least, flag_bytes + chunk * per_sample));
+    }
     if (e != hipSuccess) return e;
     int32_t *flags = static_cast<int32_t *>(d.d_work);
     *flags_out = flags;

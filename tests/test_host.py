@@ -157,3 +157,33 @@ def test_a_failed_allocation_leaves_nothing_behind(lib, name):
     assert lib.count("allocs") == allocs
     lib.host_drain_pool()
     assert lib.count("device_bytes") == 0
+
+
+def test_tac_makes_do_with_the_memory_there_is(lib):
+    """The chain form takes a call in smaller chunks when the device has no room for a large one, and leaves it to the
+    register-resident kernel when it has none for 8 192 samples or for the tables."""
+    d = wl.chain_dag(40)
+    B = 1 << 16
+    room = {}
+
+    def run(limit, h=None):
+        rc, fresh = (0, h) if h is not None else lib.build(d)
+        lib.host_drain_pool()
+        lib.host_forget_launches()
+        lib.host_device_limit(limit if limit < 0 else lib.count("device_bytes") + limit)
+        rc = lib.tac(fresh, d, B, room)
+        lib.host_device_limit(-1)
+        assert rc == 0, lib.error()
+        assert lib.hipGetLastError() == 0
+        return fresh, lib.kernels()
+
+    h, all_of_it = run(-1)
+    assert sum("class_totals" in k for k in all_of_it) == 1
+    lib.free(h)
+    flags = 4 * B
+    for limit, chunks in ((40 << 20, 2), (14 << 20, 4), (flags + (7 << 20), 8), (flags + (5 << 20), 0), (flags * 2, 0)):
+        h, kernels = run(limit)
+        assert sum("class_totals" in k for k in kernels) == chunks, (limit, kernels)
+        assert sum("tac_reg_kernel" in k for k in kernels) == (chunks == 0), (limit, kernels)
+        assert run(-1, h)[1][-3:] == all_of_it[-3:]           # with memory there again: as on a fresh handle
+        lib.free(h)
