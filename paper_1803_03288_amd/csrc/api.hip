@@ -167,9 +167,9 @@ constexpr size_t kCopyInMax = (size_t)512 << 10;
 // Collects host arrays (and device-only reservations) into one device block: one allocation, one copy of each array
 // into the pinned staging block and one host-to-device copy.  The arrays must live until commit().
 struct Packer {
-    struct Part { void **dst; const void *src; size_t bytes, off; };
+    struct Part { void **dst; const void *src; size_t bytes, off; };    // (src NULL: only kernels write it)
     std::vector<Part> parts;
-    size_t host_bytes = 0, device_only = 0;
+    size_t host_bytes = 0, device_only = 0;     // the copied arrays come first
 
     static size_t align(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -184,13 +184,12 @@ struct Packer {
     }
     template <typename T>
     void add(T **dst, const std::vector<T> &src) { add(dst, src.data(), src.size()); }
-    // space after the copied part that only kernels write; call after the last add()
     template <typename T>
     void reserve(T **dst, size_t n_bytes)
     {
         *dst = nullptr;
         if (!n_bytes) return;
-        parts.push_back({reinterpret_cast<void **>(dst), nullptr, n_bytes, align(host_bytes) + device_only});
+        parts.push_back({reinterpret_cast<void **>(dst), nullptr, n_bytes, device_only});
         device_only += align(n_bytes);
     }
     // What the block held is released first.  On an error no array of the packer is there, and what has been allocated
@@ -222,7 +221,7 @@ struct Packer {
             }
         }
         for (const Part &p : parts)
-            if (e == hipSuccess) *p.dst = static_cast<char *>(block.p) + p.off;
+            if (e == hipSuccess) *p.dst = static_cast<char *>(block.p) + (p.src ? 0 : align(host_bytes)) + p.off;
         return e;
     }
 };
@@ -601,6 +600,7 @@ struct Condensed {
     std::vector<int32_t> op, ptr, in;
     std::vector<int32_t> lvl_ptr, lvl, pos; // positions by level: of each level, and level and position of every node
     int32_t M = 0, n_levels = 0, max_width = 0;
+    size_t list_entries = 0;                // of the nodes with more than four nodes or two recvs among their inputs
 
     const int32_t *begin(int32_t k) const { return &in[0] + ptr[k]; }
     const int32_t *end(int32_t k) const { return &in[0] + ptr[k + 1]; }
@@ -614,28 +614,37 @@ static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_id
     g.op.reserve(n); g.ptr.reserve(n + 1);
     g.in.resize((size_t)d.E + 1);           // (one more: begin() of an empty list)
     g.ptr.push_back(0);
-    int32_t *in = g.in.data(), at = 0;
+    int32_t *in = g.in.data(), *val = g.val.data(), at = 0;
     std::vector<int32_t> used(d.n_levels + 1, 0);
-    for (int32_t v : order) {
-        if (recv_of_op[v] >= 0) { g.val[v] = ~recv_of_op[v]; continue; }
-        const int32_t first = at, deg = row_ptr[v + 1] - row_ptr[v];
-        for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) {
-            const int32_t x = g.val[col_idx[e]];
-            bool seen = false;
-            if (deg <= 16)
-                for (int32_t i = first; i < at; ++i) seen |= in[i] == x;
-            if (!seen) in[at++] = x;
-        }
-        if (deg > 16) {
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t v = order.empty() ? i : order[i];
+        if (recv_of_op[v] >= 0) { val[v] = ~recv_of_op[v]; continue; }
+        const int32_t first = at, e0 = row_ptr[v], deg = row_ptr[v + 1] - e0;
+        if (deg == 1) {
+            in[at++] = val[col_idx[e0]];
+        } else if (deg <= 16) {
+            for (int32_t e = e0; e < e0 + deg; ++e) {
+                const int32_t x = val[col_idx[e]];
+                bool seen = false;
+                for (int32_t k = first; k < at; ++k) seen |= in[k] == x;
+                if (!seen) in[at++] = x;
+            }
+        } else {
+            for (int32_t e = e0; e < e0 + deg; ++e) in[at++] = val[col_idx[e]];
             std::sort(in + first, in + at);
             at = (int32_t)(std::unique(in + first, in + at) - in);
         }
         if (at == first + 1 && in[first] >= 0) {
-            g.val[v] = in[first];
+            val[v] = in[first];
             at = first;
             continue;
         }
-        g.val[v] = (int32_t)g.op.size();
+        if (at - first > 2) {
+            int32_t nr = 0;
+            for (int32_t k = first; k < at; ++k) nr += in[k] < 0;
+            if (nr > 2 || at - first - nr > 4) g.list_entries += 1 + (size_t)(at - first);
+        }
+        val[v] = (int32_t)g.op.size();
         g.op.push_back(v);
         g.ptr.push_back(at);
         used[level[v]] = 1;
@@ -660,11 +669,12 @@ static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_id
 // The ops whose rows are copies (of a recv's single bit, or of the row of the node the op collapses onto).
 static std::vector<int32_t> copied_rows(const Condensed &g)
 {
-    std::vector<int32_t> copied;
-    copied.reserve(2 * (g.val.size() - g.op.size()));
-    for (int32_t v = 0; v < (int32_t)g.val.size(); ++v) {
+    const int32_t n = (int32_t)g.val.size();
+    std::vector<int32_t> copied(2 * (size_t)(n - g.M));
+    size_t at = 0;
+    for (int32_t v = 0; v < n && at < copied.size(); ++v) {
         const int32_t x = g.val[v], from = x < 0 ? x : g.op[x];
-        if (from != v) { copied.push_back(v); copied.push_back(from); }
+        if (from != v) { copied[at++] = v; copied[at++] = from; }
     }
     return copied;
 }
@@ -776,55 +786,67 @@ static QuadTables make_quad_tables(const Condensed &g, const std::vector<int32_t
     return out;
 }
 
-static int upload_quad_tables(Dag *d, const QuadTables &q, hipStream_t s)
-{
-    Packer tables;
-    tables.add(&d->d_qrecs, q.qrecs);
-    tables.add(&d->d_qfovf, q.lists);
-    tables.add(&d->d_q_copied, q.left);
-    d->qfovf_len = (int32_t)q.lists.size();
-    d->n_q_copied = (int32_t)(q.left.size() / 2);
-    tables.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
-    HIP_TRY(tables.commit(d->quad_block, d->device, s));
-    // (the staging block is free again, and the arrays may go, once the copy is done)
-    HIP_TRY(hipStreamSynchronize(s));
-    return TICTAC_OK;
-}
+// The tables of the propagation kernels on the host, and where they go on the device.
+struct PropTables {
+    Condensed g;
+    std::vector<int32_t> copied;
+    std::vector<Dag::NodeRec> nodes;
+    std::vector<Dag::FastRec> lrecs, frecs;
+    std::vector<int32_t> ovf_idx, chunk_end, lfovf, fovf;
+    QuadTables quads;
+    std::future<void> quads_made;           // (waited for before the rest goes: a thread of their own makes them)
 
-// order: the ops in topological order; level: longest path from a root.  own_dep: the handle's op.dep is made by these
-// kernels (large graphs), so its block holds op.dep as well.  The tables for several graphs are made by a thread of their own
-// meanwhile; `later`: where the caller takes them from (upload_quad_tables), or NULL to have them uploaded here.
-static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
-                                 const std::vector<int32_t> &level, const std::vector<int32_t> &order, bool own_dep,
-                                 std::future<QuadTables> *later, hipStream_t s)
+    void add_to(Packer &p, Dag *d)
+    {
+        p.add(&d->d_lrecs, lrecs);
+        p.add(&d->d_lfovf, lfovf);
+        p.add(&d->d_frecs, frecs);
+        p.add(&d->d_fovf, fovf);
+        d->lfovf_len = (int32_t)lfovf.size();
+        d->fovf_len = (int32_t)fovf.size();
+        if (d->k1_lring == 0) {
+            // the kernels that go by positions; the one for wide levels reads NodeRecs
+            p.add(&d->d_nodes, nodes);
+            p.add(&d->d_ovf_idx, ovf_idx);
+            p.add(&d->d_nlvl_ptr, g.lvl_ptr);
+            p.add(&d->d_chunk_end, chunk_end);
+        } else {
+            p.reserve(&d->d_k1_sink, (size_t)((d->W + d->k1_wc - 1) / d->k1_wc) * d->k1_threads * 8);
+        }
+        p.add(&d->d_copied, copied);
+    }
+    void add_quads_to(Packer &p, Dag *d)
+    {
+        if (!quads_made.valid()) return;
+        quads_made.get();
+        p.add(&d->d_qrecs, quads.qrecs);
+        p.add(&d->d_qfovf, quads.lists);
+        p.add(&d->d_q_copied, quads.left);
+        d->qfovf_len = (int32_t)quads.lists.size();
+        d->n_q_copied = (int32_t)(quads.left.size() / 2);
+        p.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
+    }
+};
+
+// Makes them.  order: the ops in topological order (empty: by id); level: longest path from a root.  The tables for several
+// graphs are made by a thread of their own meanwhile.
+static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
+                                  const std::vector<int32_t> &level, const std::vector<int32_t> &order, PropTables &t)
 {
-    const int32_t n = d->n;
-    const auto kept = std::make_shared<Condensed>();
-    Condensed &g = *kept;
+    Condensed &g = t.g;
     condense(*d, row_ptr, col_idx, recv_of_op, level, order, g);
     const int32_t M = g.M, n_node_levels = g.n_levels, max_width = g.max_width;
     const std::vector<int32_t> &nlvl_ptr = g.lvl_ptr;
     d->M = M; d->n_node_levels = n_node_levels; d->max_node_level_width = max_width;
-    const auto copied_kept = std::make_shared<std::vector<int32_t>>(copied_rows(g));
-    const std::vector<int32_t> &copied = *copied_kept;
-    d->n_copied = (int32_t)(copied.size() / 2);
-    Packer graph;
-    std::vector<Dag::NodeRec> nodes;
-    std::vector<Dag::FastRec> lrecs, frecs;
-    std::vector<int32_t> ovf_idx, chunk_end, lfovf, fovf, op_of_col;
-    const std::vector<int32_t> zeros(64, 0);
+    t.copied = copied_rows(g);
+    d->n_copied = (int32_t)(t.copied.size() / 2);
     // words per workgroup slice, threads, and the chunks of levels of the node kernel
     // a workgroup's LDS traffic per level grows with its slice, so wide bitsets get many narrow slices
     d->k1_wc = d->W <= 1 ? 1 : (d->W <= 2 ? 2 : (d->W >= 16 ? 1 : 4));
     // Graphs with narrow levels take a level per LDS round trip when one wave holds every row of its slice,
     // every record and the input lists of the nodes that fit no record in LDS (propagate_nodes_wave); the
     // slice is narrowed until that fits.
-    size_t list_entries = 0;
-    for (int32_t k = 0; k < M && max_width <= 64; ++k) {
-        int nn = 0, nr = 0;
-        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) (*x < 0 ? nr : nn) += 1;
-        if (nn > 4 || nr > 2) list_entries += 1 + (size_t)nn + nr;
-    }
+    const size_t list_entries = g.list_entries;
     d->k1_wave = false;
     for (int wc = d->k1_wc; wc >= 1 && max_width <= 64 && list_entries <= 4096 && M > 0; wc >>= 1) {
         if (max_width * wc <= 64 &&
@@ -838,11 +860,11 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
     threads = threads < 64 ? 64 : (threads > 1024 ? 1024 : (threads + 63) / 64 * 64);
     d->k1_threads = threads;
     const int32_t per_pass = threads / d->k1_wc;
-    chunk_end.assign(n_node_levels, 0);
+    t.chunk_end.assign(n_node_levels, 0);
     for (int32_t l0 = 0; l0 < n_node_levels;) {
         int32_t l1 = l0 + 1;
         while (l1 < n_node_levels && l1 - l0 < 64 && nlvl_ptr[l1 + 1] - nlvl_ptr[l0] <= 4 * per_pass) ++l1;
-        chunk_end[l0] = l1;
+        t.chunk_end[l0] = l1;
         l0 = l1;
     }
     // the LDS ring: a power of two of positions, at least two chunks (or all nodes), at most 64 KB beyond that
@@ -875,8 +897,7 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
     }
     d->k1_q_ring = q_ring;
     d->k1_q_threads = q_ring > 0 ? 4 * q_slots : 0;
-    std::future<QuadTables> quads;
-    if (q_ring > 0) quads = std::async([=] { return make_quad_tables(*kept, *copied_kept, q_slots, q_ring); });
+    if (q_ring > 0) t.quads_made = std::async([&t, q_slots, q_ring] { t.quads = make_quad_tables(t.g, t.copied, q_slots, q_ring); });
 
     // FastRec of node k at level l: place(x) the byte offset of input node x in the ring, or -1 when it has left it
     auto fast = [&](Dag::FastRec &f, int32_t k, int32_t zero_row, std::vector<int32_t> &lists, auto &&place, auto &&name) {
@@ -909,101 +930,54 @@ static int make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *
         none.rcv[0] = none.rcv[1] = -1;
         none.op = -1;
         none.ovf = -1;
-        lrecs.assign((size_t)n_node_levels * P, none);
+        t.lrecs.assign((size_t)n_node_levels * P, none);
         std::vector<int32_t> slot(M);
         for (int32_t k = 0; k < M; ++k) {
             const int32_t l = g.lvl[k];
             slot[k] = l * P + (g.pos[k] - nlvl_ptr[l]);
             const int32_t oldest = (l + 1) * P - lring;
-            fast(lrecs[slot[k]], k, zero_row, lfovf,
+            fast(t.lrecs[slot[k]], k, zero_row, t.lfovf,
                  [&](int32_t x) { return slot[x] >= oldest ? (slot[x] & (lring - 1)) * row_bytes : -1; },
                  [&](int32_t x) { return slot[x]; });
         }
-        graph.add(&d->d_lrecs, lrecs);
-        graph.add(&d->d_lfovf, lfovf);
-        d->lfovf_len = (int32_t)lfovf.size();
     } else if (max_width <= per_pass) {
         const int32_t row_bytes = d->k1_wc * 8, zero_row = ring * row_bytes;
-        frecs.resize(M);
+        t.frecs.resize(M);
         for (int32_t k = 0; k < M; ++k) {
             const int32_t oldest = nlvl_ptr[g.lvl[k] + 1] - ring;
-            fast(frecs[g.pos[k]], k, zero_row, fovf,
+            fast(t.frecs[g.pos[k]], k, zero_row, t.fovf,
                  [&](int32_t x) { const int32_t q = g.pos[x]; return q >= oldest ? (d->k1_wave ? q : (q & (ring - 1))) * row_bytes : -1; },
                  [&](int32_t x) { return g.pos[x]; });
         }
-        graph.add(&d->d_frecs, frecs);
-        graph.add(&d->d_fovf, fovf);
-        d->fovf_len = (int32_t)fovf.size();
-    }
-    if (lring == 0) {
-        // the kernels that go by positions; the one for wide levels reads NodeRecs
-        if (max_width > per_pass) {
-            nodes.resize(M);
-            for (int32_t k = 0; k < M; ++k) {
-                Dag::NodeRec &r = nodes[g.pos[k]];
-                r.op = g.op[k];
-                r.ovf_beg = -1;
-                for (int j = 0; j < 6; ++j) r.in[j] = INT32_MIN;
-                int j = 0;
-                for (const int32_t *x = g.begin(k); x != g.end(k); ++x, ++j) {
-                    const int32_t y = *x < 0 ? *x : g.pos[*x];
-                    if (j < 6) { r.in[j] = y; continue; }
-                    if (r.ovf_beg < 0) { r.ovf_beg = (int32_t)ovf_idx.size(); ovf_idx.push_back(0); }
-                    ovf_idx.push_back(y);
-                    ovf_idx[r.ovf_beg]++;
-                }
+    } else {
+        t.nodes.resize(M);
+        for (int32_t k = 0; k < M; ++k) {
+            Dag::NodeRec &r = t.nodes[g.pos[k]];
+            r.op = g.op[k];
+            r.ovf_beg = -1;
+            for (int j = 0; j < 6; ++j) r.in[j] = INT32_MIN;
+            int j = 0;
+            for (const int32_t *x = g.begin(k); x != g.end(k); ++x, ++j) {
+                const int32_t y = *x < 0 ? *x : g.pos[*x];
+                if (j < 6) { r.in[j] = y; continue; }
+                if (r.ovf_beg < 0) { r.ovf_beg = (int32_t)t.ovf_idx.size(); t.ovf_idx.push_back(0); }
+                t.ovf_idx.push_back(y);
+                t.ovf_idx[r.ovf_beg]++;
             }
-            graph.add(&d->d_nodes, nodes);
-            graph.add(&d->d_ovf_idx, ovf_idx);
         }
-        graph.add(&d->d_nlvl_ptr, nlvl_ptr);
-        graph.add(&d->d_chunk_end, chunk_end);
     }
-    graph.add(&d->d_copied, copied);
-    const size_t dep_words = (size_t)n * d->W;
-    if (own_dep) {
-        graph.add(&d->d_recv_of_op, recv_of_op);
-        op_of_col.reserve(d->N);
-        for (int32_t v = 0; v < n; ++v)
-            if (recv_of_op[v] < 0) op_of_col.push_back(v);
-        graph.add(&d->d_op_of_col, op_of_col);
-        graph.add(&d->d_bad_order, zeros);
-        graph.reserve(&d->d_dep, dep_words * 8);
-    }
-    if (d->k1_lring > 0)
-        graph.reserve(&d->d_k1_sink, (size_t)((d->W + d->k1_wc - 1) / d->k1_wc) * d->k1_threads * 8);
-    HIP_TRY(graph.commit(d->graph_block, d->device, s));
-    // (the staging block is free again, and the arrays may go, once the copy is done)
-    HIP_TRY(hipStreamSynchronize(s));
-    if (later) {
-        *later = std::move(quads);
-    } else if (q_ring > 0) {
-        const int rc = upload_quad_tables(d, quads.get(), s);
-        if (rc != TICTAC_OK) return rc;
-    }
-    d->prop_tables = true;
-    return TICTAC_OK;
-}
-
-static std::mutex g_tables_mutex;       // of the tables that a handle's first call of a kind makes
-
-// the tables of the propagation kernels of a handle whose op.dep came from the host's rows, made at the first call that
-// runs those kernels
-static int ensure_propagate_tables(Dag *d, hipStream_t s)
-{
-    std::lock_guard<std::mutex> lock(g_tables_mutex);
-    if (d->prop_tables) return TICTAC_OK;
-    std::vector<int32_t> recv_of_op(d->n, -1), level, order;
-    for (int32_t i = 0; i < d->R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
-    int32_t n_levels = 0;
-    (void)find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), level, order, n_levels);
-    return make_propagate_tables(d, d->h_row_ptr.data(), d->h_col_idx.data(), recv_of_op, level, order, false, nullptr, s);
 }
 
 // The line between the rows formed on the host and by the kernels: on layered graphs of 11 000 ops and 16 words (0.6 million
 // words) the host part of a build takes 2.1 ms one way and 3.7 ms the other, at 21 000 ops (1.2 million) 3.7 and 6.8, at 22 000
 // ops of 32 words (2.6 million) 12.2 and 11.3, without the kernels' own time.
 constexpr int64_t kHostRowWords = (int64_t)1 << 21;
+// From so many ops and predecessors on, the tables of the propagation kernels are made by a thread of their own while the
+// rows and classes are formed: a build of 20 512 ops takes 1.25 ms with it and 1.30 without, of 10 512 ops 0.64 and 0.66, of
+// 6 292 ops (inception3) 0.14 either way.  The tables are a fifth of a small graph's build (resnet50 41 us, 37 without them)
+// and are made nevertheless: a first tictac_dag_recompute_deps would otherwise make them, wait for the stream twice and take
+// 1.1 ms instead of 0.1 at 20 512 ops, a first batch of 32 such handles 31 ms instead of 2.8.
+constexpr int64_t kPropThread = 16384;
 
 static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int32_t R, const int32_t *recv_ids,
                  hipStream_t s, Dag *d)
@@ -1051,10 +1025,6 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     std::vector<int32_t> order;
     if (topological) {
         d->n_levels = n_levels;
-        if (!on_host) {
-            order.resize(n);
-            std::iota(order.begin(), order.end(), 0);
-        }
     } else if (!find_levels(n, row_ptr, col_idx, level, order, d->n_levels)) {
         set_error("the graph has a cycle");
         return TICTAC_ERR_CYCLE;
@@ -1065,12 +1035,30 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     HIP_TRY(hipGetDevice(&d->device));
 
     HostSets sets;
-    std::future<QuadTables> quads;
+    PropTables prop;
+    std::future<void> prop_made;            // (after what its thread works on: it ends first)
+    if ((size_t)n * d->W) {
+        auto make = [&] { make_propagate_tables(d, row_ptr, col_idx, recv_of_op, level, order, prop); };
+        if (on_host && (int64_t)n + E > kPropThread) prop_made = std::async(make);
+        else make();
+    }
     if (on_host) {
         host_sets(n, d->W, row_ptr, col_idx, recv_of_op, order, sets);
     } else {
-        const int rc = make_propagate_tables(d, row_ptr, col_idx, recv_of_op, level, order, true, &quads, s);
-        if (rc != TICTAC_OK) return rc;
+        std::vector<int32_t> op_of_col;
+        const std::vector<int32_t> zeros(64, 0);
+        Packer graph;
+        prop.add_to(graph, d);
+        graph.add(&d->d_recv_of_op, recv_of_op);
+        op_of_col.reserve(d->N);
+        for (int32_t v = 0; v < n; ++v)
+            if (recv_of_op[v] < 0) op_of_col.push_back(v);
+        graph.add(&d->d_op_of_col, op_of_col);
+        graph.add(&d->d_bad_order, zeros);
+        graph.reserve(&d->d_dep, (size_t)n * d->W * 8);
+        HIP_TRY(graph.commit(d->graph_block, d->device, s));
+        // (the staging block is free again, and the arrays may go, once the copy is done)
+        HIP_TRY(hipStreamSynchronize(s));
         if ((size_t)n * d->W) HIP_TRY(launch_propagate(*d, s));
     }
     const size_t dep_words = (size_t)n * d->W;
@@ -1229,6 +1217,12 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         if (R > 1024 || d->C > 8192) cls.add(&d->d_recv_of_op, recv_of_op);        // (TIC from the rows of the ops)
         cls.add(&d->d_bad_order, zeros);
         cls.reserve(&d->d_dep, dep_words * 8);
+        // the tables of the propagation kernels, which recompute_deps runs
+        if (prop_made.valid()) prop_made.get();
+        if (dep_words) {
+            prop.add_to(cls, d);
+            prop.add_quads_to(cls, d);
+        }
     }
     if (on_device) {
         cls.reserve(&d->d_cls_dep, (size_t)d->C * d->W * 8);
@@ -1251,9 +1245,15 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     };
     int rc = classes(dep_words * 8 >= ((size_t)8 << 20) && d->N > 0 && group_on_device(d->N, d->W) && !on_host && !getenv("TICTAC_GROUP_ON_HOST"));
     if (rc == 1) rc = classes(false);
-    if (rc == TICTAC_OK && quads.valid()) rc = upload_quad_tables(d, quads.get(), s);
-    return rc;
+    if (rc != TICTAC_OK || on_host) return rc;
+    Packer quads;
+    prop.add_quads_to(quads, d);
+    HIP_TRY(quads.commit(d->quad_block, d->device, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    return TICTAC_OK;
 }
+
+static std::mutex g_tables_mutex;       // of the tables that a handle's first TAC call makes
 
 static std::vector<int32_t> classes_of_ops(const Dag *d)
 {
@@ -1488,10 +1488,7 @@ try {
 int tictac_dag_recompute_deps(tictac_dag *dag, tictac_stream stream)
 try {
     if (!dag) { set_error("dag is NULL"); return TICTAC_ERR_NULL; }
-    Dag *d = reinterpret_cast<Dag *>(dag);
-    const int rc = ensure_propagate_tables(d, (hipStream_t)stream);
-    if (rc != TICTAC_OK) return rc;
-    HIP_TRY(launch_propagate(*d, (hipStream_t)stream));
+    HIP_TRY(launch_propagate(*reinterpret_cast<Dag *>(dag), (hipStream_t)stream));
     return TICTAC_OK;
 } TT_CATCH
 
@@ -1504,10 +1501,6 @@ try {
         if (!dags[g]) { set_error("dags[%d] is NULL", g); return TICTAC_ERR_NULL; }
     Dag *const *ds = reinterpret_cast<Dag *const *>(dags);
     hipStream_t s = (hipStream_t)stream;
-    for (int32_t g = 0; g < n_dags; ++g) {
-        const int rc = ensure_propagate_tables(ds[g], s);
-        if (rc != TICTAC_OK) return rc;
-    }
     HIP_TRY(ensure_workspace(ds[0], propagate_batch_staging_bytes(n_dags)));
     const hipError_t e = launch_propagate_batch(ds, n_dags, ds[0]->d_work, s);
     if (e == hipErrorNotSupported) {

@@ -36,7 +36,6 @@ struct ChainTables {
 struct Dag {
     int32_t n = 0, R = 0, W = 0, N = 0, E = 0;
     int32_t n_levels = 0;
-    int32_t max_level_width = 0;
     int device = 0;
 
     int32_t *d_recv_of_op = nullptr;// [n]  recv index or -1
@@ -108,7 +107,6 @@ struct Dag {
     // the ops whose rows are copies, as pairs (op, ~i for recv i or the op id of the node whose row it has)
     int32_t *d_copied = nullptr;    // [n_copied][2]
     int32_t n_copied = 0;
-    bool prop_tables = false;       // the tables above exist
     int32_t *d_op_src = nullptr;    // [n] (rows formed on the host) the class whose row op v has, or ~i: the bit of recv i
     // op.dep
     uint64_t *d_dep = nullptr;      // [n][W]

@@ -32,3 +32,24 @@ def test_recompute_from_cleared(tt, name):  # noqa: F811
     for x in (h, other):
         assert np.array_equal(x.deps().cpu().numpy().view(np.uint64), want)
         x.close()
+
+
+@pytest.mark.parametrize("name", ["tiny", "inception3", "layered70"])
+def test_first_recompute_in_a_captured_graph(tt, name):  # noqa: F811
+    """A handle's first recompute_deps, captured, replayed with eager work and cleared rows in between."""
+    d = SMALL[name]() if name in SMALL else wl.preset(name)
+    want = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    rows = h.deps_view()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        h.recompute_deps()
+    for k in range(4):
+        rows.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(rows.cpu().numpy().view(np.uint64), want), k
+        if k == 1:
+            h.recompute_deps()
+    h.close()

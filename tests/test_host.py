@@ -187,3 +187,22 @@ def test_tac_makes_do_with_the_memory_there_is(lib):
         assert sum("tac_reg_kernel" in k for k in kernels) == (chunks == 0), (limit, kernels)
         assert run(-1, h)[1][-3:] == all_of_it[-3:]           # with memory there again: as on a fresh handle
         lib.free(h)
+
+
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_the_first_propagation_finds_its_tables_made(lib, name):
+    """recompute_deps on a handle that has just been built allocates nothing, waits for nothing and can be captured; the
+    same for several handles waits for nothing."""
+    d = GRAPHS[name]()
+    rc, h = lib.build(d)
+    rc, other = lib.build(d)
+    before = {what: lib.count(what) for what in ("waits", "allocs", "new")}
+    lib.host_capturing(1)
+    rc = lib.tictac_dag_recompute_deps(h, None)
+    lib.host_capturing(0)
+    assert rc == 0, lib.error()
+    assert before == {what: lib.count(what) for what in before}
+    assert lib.tictac_dag_recompute_deps_batch((ctypes.c_void_p * 2)(h, other), I32(2), None) == 0
+    assert before["waits"] == lib.count("waits")
+    lib.free(h)
+    lib.free(other)
