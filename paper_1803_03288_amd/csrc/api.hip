@@ -1253,7 +1253,28 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     return TICTAC_OK;
 }
 
-static std::mutex g_tables_mutex;       // of the tables that a handle's first TAC call makes
+// The tables of a handle's first TAC call go to the device on a stream of the library's own, one per device: the call waits
+// for that copy and not for what is queued on the caller's stream, which may also be one that is being captured.
+constexpr int kMaxDevices = 64;
+static hipError_t table_stream(int device, hipStream_t *out)
+{
+    static std::mutex mutex;
+    static hipStream_t streams[kMaxDevices];
+    if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
+    std::lock_guard<std::mutex> lock(mutex);
+    if (!streams[device]) {
+        const hipError_t e = hipStreamCreateWithFlags(&streams[device], hipStreamNonBlocking);
+        if (e != hipSuccess) return e;
+    }
+    *out = streams[device];
+    return hipSuccess;
+}
+
+bool being_captured(hipStream_t s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &c) == hipSuccess && c != hipStreamCaptureStatusNone;
+}
 
 static std::vector<int32_t> classes_of_ops(const Dag *d)
 {
@@ -1264,9 +1285,9 @@ static std::vector<int32_t> classes_of_ops(const Dag *d)
     return cls_of_op;
 }
 
-hipError_t ensure_sliced_tables(Dag *d, hipStream_t s)
+hipError_t ensure_sliced_tables(Dag *d)
 {
-    std::lock_guard<std::mutex> lock(g_tables_mutex);
+    std::lock_guard<std::mutex> lock(d->tables_mutex);
     if (d->sliced_made) return hipSuccess;
     const int32_t CW = (d->C + 63) / 64;
     if (d->R < 1 || d->W > 64 || CW > 15 * 64 * 4) {
@@ -1351,17 +1372,18 @@ hipError_t ensure_sliced_tables(Dag *d, hipStream_t s)
     cls.reserve(&d->d_colbits, (size_t)d->R * d->CWpad * 8);
     cls.reserve(&d->d_planes0, (size_t)13 * d->CWpad * 8);
     cls.reserve(&d->d_live0, (size_t)d->CWpad * 8);
-    hipError_t e = cls.commit(d->sliced_block, d->device, s);
-    if (e != hipSuccess) return e;
-    e = launch_sliced_tables(*d, s);
+    hipStream_t s;
+    hipError_t e = table_stream(d->device, &s);
+    if (e == hipSuccess) e = cls.commit(d->sliced_block, d->device, s);
+    if (e == hipSuccess) e = launch_sliced_tables(*d, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);       // the copy came out of `cls` or of the staging block
     d->sliced_made = e == hipSuccess;
     return e;
 }
 
-hipError_t ensure_chain_tables(Dag *d, hipStream_t s)
+hipError_t ensure_chain_tables(Dag *d)
 try {
-    std::lock_guard<std::mutex> lock(g_tables_mutex);
+    std::lock_guard<std::mutex> lock(d->tables_mutex);
     ChainTables &c = d->chain;
     if (c.made) return hipSuccess;
     const int32_t n = d->n, N = d->N, R = d->R, W = d->W;
@@ -1416,9 +1438,10 @@ try {
     t.add(&c.d_flush, p.flush);
     t.add(&c.d_flush_row, p.flush_row);
     t.add(&c.d_block_first, p.block_first);
-    hipError_t e = t.commit(c.block, d->device, s);
-    if (e != hipSuccess) return e;
-    e = hipStreamSynchronize(s);                    // the copy came out of `t` or of the staging block
+    hipStream_t s;
+    hipError_t e = table_stream(d->device, &s);
+    if (e == hipSuccess) e = t.commit(c.block, d->device, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);       // the copy came out of `t` or of the staging block
     if (e != hipSuccess) return e;
     c.d_rec = reinterpret_cast<int4 *>(rec);
     c.d_gate = reinterpret_cast<int4 *>(gate);
@@ -1572,7 +1595,6 @@ static int tac_simulate_any(const tictac_dag *dag, int32_t B, const void *op_tim
 // array exists once per GPU for as long as the library is loaded; every call on a GPU uses it.
 constexpr int32_t kNoallocMaxB = 1 << 20;
 static __device__ __align__(256) int32_t scratch[kNoallocMaxB];
-constexpr int kMaxDevices = 64;
 static void *g_scratch_ptr[kMaxDevices];         // device address of `scratch` on every device, 0 = not asked yet
 static std::mutex g_scratch_mutex;
 

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -180,6 +181,8 @@ struct Dag {
     int32_t n_straight_tiles = 0;
     int32_t n_send_free = 0;
     size_t work_bytes = 0;
+    // of the tables below, which a handle's first TAC call makes
+    std::mutex tables_mutex;
     // chain form of TAC: its tables, and the class rows and columns (host) that they are made from
     ChainTables chain;
     std::vector<uint64_t> h_cls_dep;    // [C][W]   (small graphs only)
@@ -192,8 +195,9 @@ struct Dag {
 
 hipError_t ensure_workspace(Dag *d, size_t bytes);
 // the tables of the chain form, made at the first call; d->chain.ok says whether the graph has that form
-hipError_t ensure_chain_tables(Dag *d, hipStream_t s);
-hipError_t ensure_sliced_tables(Dag *d, hipStream_t s);
+hipError_t ensure_chain_tables(Dag *d);
+hipError_t ensure_sliced_tables(Dag *d);
+bool being_captured(hipStream_t s);
 
 // Number of compute units of a device and the number of workgroups of a kernel that fit one,
 // asked of the runtime once and remembered (the queries cost microseconds on every launch
@@ -243,15 +247,16 @@ inline size_t tac_lds_state_bytes(int32_t R, int32_t W, int32_t C)
 inline bool tac_small_graph(int32_t R, int32_t W, int32_t C) { return tac_lds_state_bytes(R, W, C) <= 40 * 1024 && C <= 1024; }
 // bit-sliced variant for graphs with many classes (tables above); the same contract as launch_tac_reg
 bool tac_sliced_fits(const Dag &d);
-// (flags: the first flag_bytes of the handle's workspace, which the launcher grows as needed)
-hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, int32_t **flags_out, hipStream_t s);
+// (flags: the first flag_bytes of the handle's workspace, which the launcher grows as needed; at_least: bytes of the
+// workspace that the pass over the flagged samples needs)
+hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s);
 // device-side construction of colbits, planes0 and live0 from cls_dep and cls_cnt0
 hipError_t launch_sliced_tables(const Dag &d, hipStream_t s);
 // register-resident variant for graphs with few classes; returns hipErrorNotSupported when
 // the graph does not fit it.  Samples it cannot order (a transfer time of zero) are marked
 // in flags[b] = 1 for the general kernel.
-// chain form, one lane per sample (needs d.chain; the same contract as launch_tac_sliced; at_least: bytes of the workspace
-// that the pass over the flagged samples needs).  hipErrorOutOfMemory: nothing has been launched
+// chain form, one lane per sample (needs d.chain; the same contract as launch_tac_sliced).  hipErrorOutOfMemory: nothing has
+// been launched
 hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s);
 hipError_t launch_tac_reg(Dag &d, const TacArgs &a, int32_t *flags, hipStream_t s);
 

@@ -431,9 +431,10 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
     // against 319 us for 64.
     const int32_t chain_min_B = d.C <= 4 * 64 ? 8192 : 64;
     if (!a.sel_P && !a.sel_Mplus && !a.ext_flags && a.B >= chain_min_B) {
-        // (where there is no memory for its tables or for enough samples at once, the kernels below take the call)
+        // (where there is no memory for its tables or for enough samples at once, the kernels below take the call; also on a
+        // stream that is being captured, where tables cannot be made)
         int32_t *flags = nullptr;
-        hipError_t e = ensure_chain_tables(&d, s);
+        hipError_t e = !d.chain.made && being_captured(s) ? hipErrorNotSupported : ensure_chain_tables(&d);
         if (e == hipSuccess) e = d.chain.ok ? launch_tac_chain(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s) : hipErrorNotSupported;
         if (e == hipSuccess) p.only_flagged = flags;
         else if (e != hipErrorNotSupported && e != hipErrorOutOfMemory) return e;
@@ -447,14 +448,12 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
         else if (e != hipErrorNotSupported) return e;
     }
     if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && !small) {
-        // (sized first for the general kernel's pass over the flagged samples, so that the block is not replaced
-        // between the two launches)
-        hipError_t e = ensure_workspace(&d, flag_bytes + gstate_bytes);
-        if (e != hipSuccess) return e;
-        e = ensure_sliced_tables(&d, s);
+        // (the workspace is sized for the general kernel's pass over the flagged samples as well, so that the block is not
+        // replaced between the two launches)
+        hipError_t e = ensure_sliced_tables(&d);
         if (e != hipSuccess) return e;
         int32_t *flags = nullptr;
-        e = tac_sliced_fits(d) ? launch_tac_sliced(d, a, flag_bytes, &flags, s) : hipErrorNotSupported;
+        e = tac_sliced_fits(d) ? launch_tac_sliced(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s) : hipErrorNotSupported;
         if (e == hipSuccess) p.only_flagged = flags;
         else if (e != hipErrorNotSupported) return e;
     }

@@ -467,6 +467,7 @@ hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t 
     const size_t per_sample = ((size_t)c.n_totals + d.R) * 8;
     size_t chunk = std::min((size_t)a.B, kChainChunkBytes / per_sample);
     chunk = (chunk + 63) & ~(size_t)63;
+    if (std::max(at_least, flag_bytes + chunk * per_sample) > d.work_bytes && being_captured(s)) return hipErrorNotSupported;
     hipError_t e = ensure_workspace(&d, std::max(at_least, flag_bytes + chunk * per_sample));
     while (e == hipErrorOutOfMemory && chunk > kChainChunkLeast) {
         chunk = std::max(kChainChunkLeast, (chunk / 2 + 63) & ~(size_t)63);

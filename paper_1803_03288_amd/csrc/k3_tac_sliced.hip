@@ -779,8 +779,8 @@ static size_t tac_sliced_scratch_stride(const Dag &d, int KW)
 }
 
 template <int KW>
-static hipError_t launch_sliced_k(SlicedParams &p, Dag &d, const TacArgs &a, size_t flag_bytes, int32_t **flags_out,
-                                  hipStream_t s)
+static hipError_t launch_sliced_k(SlicedParams &p, Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least,
+                                  int32_t **flags_out, hipStream_t s)
 {
     int workers = (d.CW + KW * 64 - 1) / (KW * 64);
     if (workers < 1) workers = 1;
@@ -800,7 +800,7 @@ static hipError_t launch_sliced_k(SlicedParams &p, Dag &d, const TacArgs &a, siz
     int grid = per_cu * device_cu_count(d.device);
     if (grid > a.B) grid = a.B;
     p.scratch_stride = tac_sliced_scratch_stride(d, KW);
-    e = ensure_workspace(&d, flag_bytes + p.scratch_stride * (size_t)grid);
+    e = ensure_workspace(&d, std::max(at_least, flag_bytes + p.scratch_stride * (size_t)grid));
     if (e != hipSuccess) return e;
     p.flags = static_cast<int32_t *>(d.d_work);
     p.scratch = static_cast<char *>(d.d_work) + flag_bytes;
@@ -809,7 +809,7 @@ static hipError_t launch_sliced_k(SlicedParams &p, Dag &d, const TacArgs &a, siz
     return hipGetLastError();
 }
 
-hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, int32_t **flags_out, hipStream_t s)
+hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s)
 {
     if (!tac_sliced_fits(d) || a.sel_P || a.sel_Mplus) return hipErrorNotSupported;
     SlicedParams p{};
@@ -834,10 +834,10 @@ hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, int32_
         return 2 * waves <= 16 && 2 * sliced_lds_bytes(d) <= 158 * 1024;
     };
     if (per_lane <= 2 && a.B > device_cu_count(d.device) && !pair(std::max(per_lane, 2)) && pair(3)) per_lane = 3;
-    if (per_lane <= 1) return launch_sliced_k<1>(p, d, a, flag_bytes, flags_out, s);
-    if (per_lane <= 2) return launch_sliced_k<2>(p, d, a, flag_bytes, flags_out, s);
-    if (per_lane <= 3) return launch_sliced_k<3>(p, d, a, flag_bytes, flags_out, s);
-    if (per_lane <= 4) return launch_sliced_k<4>(p, d, a, flag_bytes, flags_out, s);
+    if (per_lane <= 1) return launch_sliced_k<1>(p, d, a, flag_bytes, at_least, flags_out, s);
+    if (per_lane <= 2) return launch_sliced_k<2>(p, d, a, flag_bytes, at_least, flags_out, s);
+    if (per_lane <= 3) return launch_sliced_k<3>(p, d, a, flag_bytes, at_least, flags_out, s);
+    if (per_lane <= 4) return launch_sliced_k<4>(p, d, a, flag_bytes, at_least, flags_out, s);
     return hipErrorNotSupported;
 }
 

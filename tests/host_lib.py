@@ -50,9 +50,8 @@ class HostLib:
         self.L.tictac_last_error.restype = ctypes.c_char_p
         for f in ("host_count", "host_group_bytes", "host_fail_new_left", "host_fail_device_left"):
             getattr(self.L, f).restype = I64
-        for f in ("host_fail_device", "host_device_limit", "host_fail_new"):
+        for f in ("host_fail_device", "host_device_limit", "host_fail_new", "host_slow_copies"):
             getattr(self.L, f).argtypes = [I64]
-        self.L.host_delays.argtypes = [I64, I64]
 
     def __getattr__(self, name):
         return getattr(self.L, name)

@@ -29,7 +29,7 @@ std::map<void *, size_t> g_blocks;              // live device blocks
 struct Launch { std::string name; int64_t grid, block, lds, filled; };      // (filled: words, of a fill)
 std::vector<Launch> g_launches;
 std::atomic<int64_t> g_fail_device{-1}, g_fail_new{-1}, g_device_limit{INT64_MAX};
-std::atomic<int64_t> g_waits{0}, g_allocs{0}, g_frees{0}, g_device_bytes{0}, g_pinned_bytes{0}, g_new_calls{0}, g_event_delay_us{0}, g_wait_us{0};
+std::atomic<int64_t> g_waits{0}, g_allocs{0}, g_frees{0}, g_device_bytes{0}, g_pinned_bytes{0}, g_new_calls{0}, g_wait_us{0};
 std::atomic<int> g_capturing{0}, g_paused{0};
 thread_local hipError_t g_last = hipSuccess;
 thread_local bool g_inside = false;             // (allocations of the stand-in itself do not fail)
@@ -157,10 +157,12 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind)
 }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t)
+// (the caller's stream is the null stream; a stream that the library made is never captured, and waited for on its own)
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = reinterpret_cast<hipStream_t>(&g_waits); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s)
 {
-    if (g_capturing) return result(hipErrorStreamCaptureUnsupported);
-    ++g_waits;
+    if (g_capturing && !s) return result(hipErrorStreamCaptureUnsupported);
+    if (!s) ++g_waits;
     wait_a_little();
     return hipSuccess;
 }
@@ -170,23 +172,11 @@ hipError_t hipDeviceSynchronize()
     ++g_waits;
     return hipSuccess;
 }
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *c)
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *c)
 {
-    *c = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    *c = g_capturing && !s ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-// an event: the time from which on it has happened
-hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { Inside in; *e = reinterpret_cast<hipEvent_t>(calloc(1, 8)); return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
-static int64_t now_us() { return std::chrono::duration_cast<std::chrono::microseconds>(std::chrono::steady_clock::now().time_since_epoch()).count(); }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { *reinterpret_cast<int64_t *>(e) = now_us() + g_event_delay_us; return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t e) { return now_us() >= *reinterpret_cast<int64_t *>(e) ? hipSuccess : hipErrorNotReady; }
-hipError_t hipEventSynchronize(hipEvent_t e)
-{
-    while (hipEventQuery(e) != hipSuccess) std::this_thread::yield();
-    return hipSuccess;
-}
-
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t)
 {
     Inside in;
@@ -207,7 +197,7 @@ int64_t host_fail_new_left() { return g_fail_new; }
 int64_t host_fail_device_left() { return g_fail_device; }
 void host_pause_failures(int on) { g_paused = on; }
 void host_capturing(int on) { g_capturing = on; }
-void host_delays(int64_t event_us, int64_t wait_us) { g_event_delay_us = event_us; g_wait_us = wait_us; }
+void host_slow_copies(int64_t us) { g_wait_us = us; }        // a wait for a stream takes so long
 int64_t host_count(const char *what)
 {
     const std::string w(what);

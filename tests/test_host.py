@@ -1,6 +1,8 @@
 """The library's host code against a stand-in for the HIP runtime (host_lib.py): no GPU, no kernel runs."""
 
 import ctypes
+import time
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 import pytest
@@ -206,3 +208,57 @@ def test_the_first_propagation_finds_its_tables_made(lib, name):
     assert before["waits"] == lib.count("waits")
     lib.free(h)
     lib.free(other)
+
+
+@pytest.mark.parametrize("name", ["chain", "wide", "device"])
+def test_a_first_tac_call_waits_for_nothing_of_the_callers(lib, name):
+    """The tables that a first TAC call makes go to the device without a wait for the caller's stream or the device."""
+    d = GRAPHS[name]()
+    rc, h = lib.build(d)
+    waits = lib.count("waits")
+    assert lib.tac(h, d, 8192 if name == "chain" else 300) == 0
+    assert lib.count("waits") == waits
+    lib.free(h)
+
+
+def test_a_first_tac_call_under_capture(lib):
+    """Chain tables cannot be made on a stream that is being captured: the register-resident kernel takes the call, as far
+    as the workspace reaches, and the next call outside makes them."""
+    d = GRAPHS["chain"]()
+    rc, h = lib.build(d)
+    assert lib.tac(h, d, 8190) == 0                 # (one sample short of the chain form, two of its workspace)
+    lib.host_forget_launches()
+    lib.host_capturing(1)
+    rc = lib.tac(h, d, 8192)
+    lib.host_capturing(0)
+    assert rc == 0, lib.error()
+    assert any("tac_reg" in k for k in lib.kernels()) and not any("chain" in k for k in lib.kernels())
+    lib.host_forget_launches()
+    assert lib.tac(h, d, 8192) == 0 and any("tac_chain" in k for k in lib.kernels())
+    lib.host_forget_launches()
+    lib.host_capturing(1)
+    assert lib.tac(h, d, 8192) == 0 and any("tac_chain" in k for k in lib.kernels())
+    lib.host_forget_launches()
+    assert lib.tac(h, d, 8256) == 0 and any("tac_reg" in k or "tac_chain" in k for k in lib.kernels())
+    lib.host_capturing(0)
+    lib.free(h)
+
+
+def test_handles_do_not_wait_for_each_others_tables(lib):
+    """Four threads make the tables of a handle each while every copy takes 50 ms: side by side, not one after the other."""
+    d = GRAPHS["chain"]()
+    handles = [lib.build(d)[1] for _ in range(4)]
+    rooms = [{} for _ in range(4)]
+
+    with ThreadPoolExecutor(4) as ex:
+        assert list(ex.map(lambda k: lib.tac(handles[k], d, 8190, rooms[k]), range(4))) == [0] * 4
+        lib.host_forget_launches()
+        lib.host_slow_copies(50000)
+        start = time.perf_counter()
+        assert list(ex.map(lambda k: lib.tac(handles[k], d, 8192, rooms[k]), range(4))) == [0] * 4
+        took = time.perf_counter() - start
+    lib.host_slow_copies(0)
+    assert sum("copy_in" in k for k in lib.kernels()) == 4
+    assert took < 0.15
+    for h in handles:
+        lib.free(h)
