@@ -24,7 +24,9 @@
  *   - "host" pointers are ordinary memory, "device" pointers are HIP device
  *     memory of the current device.  The library never takes ownership of a
  *     caller's buffer; it only uses it for the duration of the stream-ordered
- *     call.  Everything a tictac_dag owns is released by tictac_dag_free.
+ *     call.  Everything a tictac_dag owns is released by tictac_dag_free: its device
+ *     memory serves the next handles, up to 1 GiB of it per process (and 192 MiB of
+ *     pinned host memory); tictac_trim_memory gives that back.
  *   - Ops are numbered 0..n_ops-1 in any order.  recv i is the op recv_ids[i];
  *     bit i of a dependency bitset (bit i & 63 of 64-bit word i >> 6) stands
  *     for it.  W = ceil(n_recv / 64) words per bitset.
@@ -116,6 +118,10 @@ int tictac_dag_recompute_deps_batch(tictac_dag *const *dags, int32_t n_dags, tic
 int tictac_dag_check_orders(tictac_dag *dag, tictac_stream stream);
 
 int tictac_dag_free(tictac_dag *dag);
+
+/* Gives back to the runtime the device and pinned host memory that the library keeps from freed handles
+ * (on every device).  Handles in use are not touched. */
+int tictac_trim_memory(void);
 
 /*
  * Sec. 4.2, Algorithm 2 (TIC): the property update of Algorithm 1 with every recv

@@ -29,7 +29,7 @@ STATUS = {
 EXPORTS = (
     "tictac_build_deps", "tictac_dag_info", "tictac_dag_deps", "tictac_dag_copy_deps", "tictac_dag_recompute_deps",
     "tictac_dag_recompute_deps_batch", "tictac_dag_check_orders",
-    "tictac_dag_free",
+    "tictac_dag_free", "tictac_trim_memory",
     "tictac_tic_priority", "tictac_tac_priority", "tictac_simulate", "tictac_tac_simulate",
     "tictac_tac_simulate_noalloc",
     "tictac_simulate_f32", "tictac_tac_simulate_f32",
@@ -144,6 +144,11 @@ def recompute_deps_batch(dags) -> None:
     """``tictac_dag_recompute_deps_batch``: the propagation kernel for several handles in one launch."""
     arr = (ctypes.c_void_p * len(dags))(*[d._h for d in dags])
     _check(lib().tictac_dag_recompute_deps_batch(arr, ctypes.c_int32(len(dags)), _stream()))
+
+
+def trim_memory() -> None:
+    """``tictac_trim_memory``: gives back the device and pinned host memory kept from freed handles."""
+    _check(lib().tictac_trim_memory())
 
 
 def build_deps(n_ops: int, row_ptr, col_idx, recv_ids) -> Dag:

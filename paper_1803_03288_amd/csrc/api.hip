@@ -55,7 +55,7 @@ static int caught()
 // Device memory of the handles.  A program that takes in one graph after another allocates and frees blocks of the
 // same sizes all the time, and hipMalloc and hipFree cost tens of microseconds each, large blocks much more.  Freed
 // blocks are therefore kept, up to kPoolMax bytes per process (the oldest go first), and given back to the runtime when
-// an allocation fails.  A block is freed only after the device has finished what was queued (as hipFree does), so the
+// an allocation fails and by tictac_trim_memory.  A block is freed only after the device has finished what was queued (as hipFree does), so the
 // next owner may use it on any stream.
 constexpr size_t kPoolMax = (size_t)1 << 30;
 struct PoolBlock { void *p; size_t bytes; int device; };
@@ -132,44 +132,114 @@ static hipError_t release(Block &b, int device)
     return hipSuccess;
 }
 
-// Pinned host memory for the transfers of tictac_build_deps: one block per calling thread,
-// grown on demand and kept until the thread's next larger request (pinning costs milliseconds,
-// and copies from or to pageable memory are staged by the runtime and take three to four
-// times as long).  NULL when the request is empty, beyond the cap, or cannot be pinned: the
-// caller then copies from or to its own pageable memory.  The block is free again once the
-// stream has been synchronised, which tictac_build_deps does before it returns.
-static thread_local void *g_stage = nullptr;
-static thread_local size_t g_stage_bytes = 0;
-constexpr size_t kStageMax = (size_t)96 << 20;
+// Pinned host memory for transfers (pinning costs milliseconds, and copies from or to pageable memory are staged by the
+// runtime and take three to four times as long).  Blocks that nobody uses are kept for the next taker, any thread, up to
+// kPinnedKept bytes per process.
+constexpr size_t kStageMax = (size_t)96 << 20, kPinnedKept = (size_t)192 << 20;
+static std::mutex g_pinned_mutex;
+static std::vector<Block> g_pinned;                 // oldest first
+static size_t g_pinned_bytes = 0;
 
-static void *stage(size_t bytes)
+// Holds a block while its owner lives.  NULL when the request is empty, beyond the cap, or cannot be pinned: the caller then
+// copies from or to its own pageable memory.
+class Stage {
+    Block b;
+public:
+    Stage() = default;
+    Stage(const Stage &) = delete;
+    Stage &operator=(const Stage &) = delete;
+    ~Stage() { give_back(); }
+
+    void *take(size_t bytes)
+    {
+        give_back();
+        if (bytes == 0 || bytes > kStageMax) return nullptr;
+        {
+            std::lock_guard<std::mutex> lock(g_pinned_mutex);
+            for (size_t i = g_pinned.size(); i-- > 0;)
+                if (g_pinned[i].bytes >= bytes) {
+                    b = g_pinned[i];
+                    g_pinned.erase(g_pinned.begin() + i);
+                    g_pinned_bytes -= b.bytes;
+                    return b.p;
+                }
+        }
+        const size_t want = (bytes + ((size_t)1 << 20) - 1) & ~(((size_t)1 << 20) - 1);
+        if (hipHostMalloc(&b.p, want, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            b.p = nullptr;
+            return nullptr;
+        }
+        b.bytes = want;
+        return b.p;
+    }
+    // (no copy from or to it is under way)
+    void give_back() noexcept
+    {
+        if (!b.p) return;
+        std::lock_guard<std::mutex> lock(g_pinned_mutex);
+        try {
+            g_pinned.push_back(b);
+            g_pinned_bytes += b.bytes;
+        } catch (const std::bad_alloc &) {
+            (void)hipHostFree(b.p);
+        }
+        b = Block();
+        while (g_pinned_bytes > kPinnedKept) {
+            g_pinned_bytes -= g_pinned[0].bytes;
+            (void)hipHostFree(g_pinned[0].p);
+            g_pinned.erase(g_pinned.begin());
+        }
+    }
+};
+
+// Gives back what the pool and the staging blocks keep; what the runtime does not take stays.
+static hipError_t trim_memory()
 {
-    if (bytes == 0 || bytes > kStageMax) return nullptr;
-    if (bytes <= g_stage_bytes) return g_stage;
-    if (g_stage) {
-        (void)hipHostFree(g_stage);
-        g_stage = nullptr;
-        g_stage_bytes = 0;
+    hipError_t err = hipSuccess;
+    auto drop = [&](void *p, bool pinned) {
+        const hipError_t e = pinned ? hipHostFree(p) : hipFree(p);
+        if (e != hipSuccess) { (void)hipGetLastError(); err = e; }
+        return e == hipSuccess;
+    };
+    {
+        std::lock_guard<std::mutex> lock(g_pool_mutex);
+        for (size_t i = g_pool.size(); i-- > 0;)
+            if (drop(g_pool[i].p, false)) {
+                g_pool_bytes -= g_pool[i].bytes;
+                g_pool.erase(g_pool.begin() + i);
+            }
     }
-    const size_t want = (bytes + ((size_t)1 << 20) - 1) & ~(((size_t)1 << 20) - 1);
-    void *q = nullptr;
-    if (hipHostMalloc(&q, want, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    g_stage = q;
-    g_stage_bytes = want;
-    return q;
+    std::lock_guard<std::mutex> lock(g_pinned_mutex);
+    for (size_t i = g_pinned.size(); i-- > 0;)
+        if (drop(g_pinned[i].p, true)) {
+            g_pinned_bytes -= g_pinned[i].bytes;
+            g_pinned.erase(g_pinned.begin() + i);
+        }
+    return err;
 }
 
 constexpr size_t kCopyInMax = (size_t)512 << 10;
 
 // Collects host arrays (and device-only reservations) into one device block: one allocation, one copy of each array
-// into the pinned staging block and one host-to-device copy.  The arrays must live until commit().
+// into a pinned staging block and one host-to-device copy.  The arrays must live until commit(), and finish() waits for the
+// copy (so does the destructor, where an error has come between).
 struct Packer {
     struct Part { void **dst; const void *src; size_t bytes, off; };    // (src NULL: only kernels write it)
     std::vector<Part> parts;
     size_t host_bytes = 0, device_only = 0;     // the copied arrays come first
+    Stage staging;
+    hipStream_t stream = nullptr;
+    bool under_way = false;
+
+    Packer() = default;
+    ~Packer() { if (under_way) (void)hipStreamSynchronize(stream); }
+    hipError_t finish()
+    {
+        const hipError_t e = hipStreamSynchronize(stream);
+        if (e == hipSuccess) under_way = false;
+        return e;
+    }
 
     static size_t align(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -201,7 +271,7 @@ struct Packer {
         const size_t total = align(host_bytes) + device_only;
         if (e != hipSuccess || !total) return e;
         std::vector<char> pageable;
-        char *st = static_cast<char *>(stage(host_bytes));
+        char *st = static_cast<char *>(staging.take(host_bytes));
         if (!st && host_bytes) {
             pageable.resize(host_bytes);
             st = pageable.data();
@@ -211,7 +281,9 @@ struct Packer {
         block.bytes = total;
         for (const Part &p : parts)
             if (p.src) memcpy(st + p.off, p.src, p.bytes);
+        stream = s;
         if (host_bytes) {
+            under_way = true;
             // (small blocks: a kernel reads the pinned memory itself)
             if (pageable.empty() && host_bytes <= kCopyInMax) {
                 e = launch_copy_in(block.p, st, host_bytes, s);
@@ -1057,8 +1129,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         graph.add(&d->d_bad_order, zeros);
         graph.reserve(&d->d_dep, (size_t)n * d->W * 8);
         HIP_TRY(graph.commit(d->graph_block, d->device, s));
-        // (the staging block is free again, and the arrays may go, once the copy is done)
-        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(graph.finish());
         if ((size_t)n * d->W) HIP_TRY(launch_propagate(*d, s));
     }
     const size_t dep_words = (size_t)n * d->W;
@@ -1080,7 +1151,8 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         HIP_TRY(ensure_workspace(d, group_workspace_bytes(d->N)));
         HIP_TRY(launch_group_rows(*d, d->d_op_of_col, d->d_work, s));
         std::vector<int32_t> pageable;
-        int32_t *rep = static_cast<int32_t *>(stage((size_t)d->N * 12));
+        Stage staging;
+        int32_t *rep = static_cast<int32_t *>(staging.take((size_t)d->N * 12));
         if (!rep) {
             pageable.resize((size_t)d->N * 3);
             rep = pageable.data();
@@ -1105,7 +1177,8 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         rows.resize((size_t)d->N * d->W);
         if (!rows.empty()) {
             std::vector<uint64_t> pageable;
-            uint64_t *all = static_cast<uint64_t *>(stage(dep_words * 8));   // stream order: after the copy of the graph block out of it
+            Stage staging;
+            uint64_t *all = static_cast<uint64_t *>(staging.take(dep_words * 8));
             if (!all) {
                 pageable.resize(dep_words);
                 all = pageable.data();
@@ -1234,7 +1307,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     if (on_device) HIP_TRY(launch_class_rows(*d, d->d_op_of_col, d->d_cls_first_op, mismatch, s));
     int32_t differs = 0;
     if (on_device) HIP_TRY(hipMemcpyAsync(&differs, mismatch, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));   // host vectors go out of scope; the handle is complete
+    HIP_TRY(cls.finish());              // (waits for `differs` as well; the handle is complete)
     d->h_col_cls = std::move(col_cls);
     d->h_cls_cnt0 = std::move(cnt0);
     if (differs) {
@@ -1249,7 +1322,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     Packer quads;
     prop.add_quads_to(quads, d);
     HIP_TRY(quads.commit(d->quad_block, d->device, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(quads.finish());
     return TICTAC_OK;
 }
 
@@ -1376,7 +1449,7 @@ hipError_t ensure_sliced_tables(Dag *d)
     hipError_t e = table_stream(d->device, &s);
     if (e == hipSuccess) e = cls.commit(d->sliced_block, d->device, s);
     if (e == hipSuccess) e = launch_sliced_tables(*d, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);       // the copy came out of `cls` or of the staging block
+    if (e == hipSuccess) e = cls.finish();
     d->sliced_made = e == hipSuccess;
     return e;
 }
@@ -1441,7 +1514,7 @@ try {
     hipStream_t s;
     hipError_t e = table_stream(d->device, &s);
     if (e == hipSuccess) e = t.commit(c.block, d->device, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);       // the copy came out of `t` or of the staging block
+    if (e == hipSuccess) e = t.finish();
     if (e != hipSuccess) return e;
     c.d_rec = reinterpret_cast<int4 *>(rec);
     c.d_gate = reinterpret_cast<int4 *>(gate);
@@ -1539,6 +1612,12 @@ int tictac_dag_free(tictac_dag *dag)
 try {
     if (!dag) return TICTAC_OK;
     free_dag(reinterpret_cast<Dag *>(dag));
+    return TICTAC_OK;
+} TT_CATCH
+
+int tictac_trim_memory(void)
+try {
+    HIP_TRY(trim_memory());
     return TICTAC_OK;
 } TT_CATCH
 
@@ -1937,7 +2016,7 @@ static int ensure_send_tables(Dag *d, int32_t n_send, const int32_t *send_ids, h
     d->n_send_free = (int32_t)send_free.size();
     d->send_tables_built = false;
     HIP_TRY(tables.commit(d->send_block, d->device, s));
-    HIP_TRY(hipStreamSynchronize(s));               // the copy came out of `tables`, which ends here
+    HIP_TRY(tables.finish());
     d->h_send_ids.assign(send_ids, send_ids + n_send);
     d->send_tables_built = true;
     return TICTAC_OK;

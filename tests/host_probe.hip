@@ -12,13 +12,3 @@ extern "C" int host_group_rows(int32_t N, int32_t W)
     return (int)launch_group_rows(d, nullptr, nullptr, nullptr);
 }
 extern "C" int64_t host_group_bytes(int32_t N) { return (int64_t)group_workspace_bytes(N); }
-
-// gives the pool's blocks back, as an allocation does that the device cannot serve
-extern "C" void host_device_limit(int64_t bytes);
-extern "C" void host_drain_pool()
-{
-    Dag d;
-    host_device_limit(0);
-    (void)ensure_workspace(&d, (size_t)1 << 40);
-    host_device_limit(-1);
-}

@@ -140,7 +140,7 @@ def test_a_failed_allocation_leaves_nothing_behind(lib, name):
             for k in range(4000):
                 rc, h = lib.build(d)
                 assert rc == 0
-                lib.host_drain_pool()                           # (so that the call allocates)
+                assert lib.tictac_trim_memory() == 0            # (so that the call allocates)
                 order(k)
                 rc = call(h)
                 struck = left() < 0
@@ -157,7 +157,7 @@ def test_a_failed_allocation_leaves_nothing_behind(lib, name):
     rc, h = lib.build(d)
     lib.free(h)
     assert lib.count("allocs") == allocs
-    lib.host_drain_pool()
+    lib.tictac_trim_memory()
     assert lib.count("device_bytes") == 0
 
 
@@ -170,7 +170,7 @@ def test_tac_makes_do_with_the_memory_there_is(lib):
 
     def run(limit, h=None):
         rc, fresh = (0, h) if h is not None else lib.build(d)
-        lib.host_drain_pool()
+        lib.tictac_trim_memory()
         lib.host_forget_launches()
         lib.host_device_limit(limit if limit < 0 else lib.count("device_bytes") + limit)
         rc = lib.tac(fresh, d, B, room)
@@ -262,3 +262,33 @@ def test_handles_do_not_wait_for_each_others_tables(lib):
     assert took < 0.15
     for h in handles:
         lib.free(h)
+
+
+def test_kept_memory_is_bounded_and_given_back(lib):
+    """Threads that come and go leave no pinned memory of their own behind, and everything kept from freed handles can be
+    given back while another handle lives on."""
+    lib.tictac_trim_memory()
+    assert lib.count("device_bytes") == lib.count("pinned_bytes") == 0
+    d = GRAPHS["wide"]()
+    for _ in range(6):
+        with ThreadPoolExecutor(1) as ex:
+            lib.free(ex.submit(lib.build, d).result()[1])
+    assert 0 < lib.count("pinned_bytes") <= 4 << 20
+    rc, h = lib.build(d)
+    lib.free(lib.build(d)[1])
+    held = lib.count("device_bytes")
+    assert lib.tictac_trim_memory() == 0
+    assert 0 < lib.count("device_bytes") < held and lib.count("pinned_bytes") == 0
+    assert lib.tac(h, d, 300) == 0
+    lib.free(h)
+    assert lib.tictac_trim_memory() == 0 and lib.count("device_bytes") == 0
+    # no more than the bound is kept
+    handles = []
+    for _ in range(16):
+        handles.append(lib.build(d)[1])
+        assert lib.tac(handles[-1], d, 512) == 0
+    assert lib.count("device_bytes") > 2 << 30
+    for h in handles:
+        lib.free(h)
+    assert 1 << 29 < lib.count("device_bytes") <= 1 << 30
+    lib.tictac_trim_memory()
