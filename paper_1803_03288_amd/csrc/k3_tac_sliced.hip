@@ -824,16 +824,24 @@ hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, size_t
     p.order = a.order; p.rank = a.rank;
     p.simulate = a.simulate ? 1 : 0;
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
-    // One word per lane where fifteen worker waves hold all classes, the fewest words otherwise; but three where two words
-    // fill less than a compute unit whose LDS has room for two workgroups: the waves that three need leave place for both
-    // (128 registers, sixteen waves).  A round takes 7.5 instead of 5.9 us then, and 4 096 samples of 4 096 recvs and 60 567
-    // classes 312 instead of 427 ms (264 ms with the events added by LDS atomics).
+    // Where one workgroup per compute unit is all there is to do, the fewest words per lane that fifteen worker waves need:
+    // a round is shortest then.  With more samples than compute units, the fewest with which two workgroups share a compute
+    // unit (sixteen waves of 128 registers, twice the LDS), up to three words: a round takes longer (7.5 instead of 5.9 us
+    // with 60 567 classes), but two are under way.  4 096 samples, layered graphs, ms with one / two / three words:
+    //   classes (recvs)   6 465 (600)  13 781 (1 024)  26 508 (2 048)  30 119 (4 096)  44 588 (2 048)  53 188 (4 096)  58 086 (4 096)  62 837 (4 096)
+    //                    18 / 22 / 24    59 / 59 / 65   86 / 118 / 118  257 / 181 / 246 171 / 121 / 189 284 / 203 / 279 270 / 304 / 254   - / 314 / 256
+    // (two of one word fit up to 28 672 classes, of two up to 57 344, of three up to 86 016).  512 samples, 53 188 classes:
+    // 48 / 44 / 56; 300 samples, 30 119 classes: 31 / 31 / 41.  Four words need more registers than two workgroups have
+    // (535 ms with 53 188 classes).
     int per_lane = (d.CW + kWorkersMax * 64 - 1) / (kWorkersMax * 64);
-    auto pair = [&](int kw) {
-        const int waves = (d.CW + kw * 64 - 1) / (kw * 64) + 1;
-        return 2 * waves <= 16 && 2 * sliced_lds_bytes(d) <= 158 * 1024;
-    };
-    if (per_lane <= 2 && a.B > device_cu_count(d.device) && !pair(std::max(per_lane, 2)) && pair(3)) per_lane = 3;
+    if (a.B > device_cu_count(d.device))
+        for (int kw = per_lane; kw <= 3; ++kw) {
+            const int waves = (d.CW + kw * 64 - 1) / (kw * 64) + 1;
+            if (2 * waves <= 16 && 2 * sliced_lds_bytes(d) <= 158 * 1024) {
+                per_lane = kw;
+                break;
+            }
+        }
     if (per_lane <= 1) return launch_sliced_k<1>(p, d, a, flag_bytes, at_least, flags_out, s);
     if (per_lane <= 2) return launch_sliced_k<2>(p, d, a, flag_bytes, at_least, flags_out, s);
     if (per_lane <= 3) return launch_sliced_k<3>(p, d, a, flag_bytes, at_least, flags_out, s);

@@ -70,3 +70,20 @@ def test_tac_with_many_classes(tt, name):
         assert np.array_equal(order[rows], eo), what
         assert np.array_equal(rank[rows], er), what
     h.close()
+
+
+def test_one_and_two_words_per_lane(tt):
+    """The bit-sliced kernel on a graph whose classes take two words per lane for a batch of more samples than compute
+    units (two workgroups share one) and one word for a smaller batch: the same results for every sample."""
+    d = wl.stress_dag(levels=220, width=200, n_recv=3000, seed=9, batch=8)
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    assert 28672 < h.n_classes <= 57344, h.n_classes
+    B = 300
+    op, rv = (torch.from_numpy(x).cuda() for x in wl.timing_samples(d, 0, B))
+    print(f"[tac] words per lane: classes={h.n_classes} R={d.n_recv}", flush=True)
+    got = tt.tac_simulate(h, op, rv, want_rank=True)
+    for lo in range(0, B, 150):
+        part = tt.tac_simulate(h, op[lo:lo + 150].contiguous(), rv[lo:lo + 150].contiguous(), want_rank=True)
+        for k in (0, 1, 4, 5, 6, 7, 8):
+            assert torch.equal(got[k][lo:lo + 150], part[k]), (lo, k)
+    h.close()

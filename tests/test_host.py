@@ -292,3 +292,20 @@ def test_kept_memory_is_bounded_and_given_back(lib):
         lib.free(h)
     assert 1 << 29 < lib.count("device_bytes") <= 1 << 30
     lib.tictac_trim_memory()
+
+
+@pytest.mark.parametrize("C,R,B,words", [
+    (1025, 600, 4096, 1), (28672, 2048, 4096, 1), (28673, 2048, 4096, 2), (30119, 4096, 4096, 2), (44588, 2048, 4096, 2),
+    (57344, 4096, 4096, 2), (57345, 4096, 4096, 3), (62837, 4096, 4096, 3), (86016, 4096, 4096, 3),
+    (86017, 4096, 4096, 2),                                     # too many for two workgroups of three words: the fewest
+    (122881, 4096, 4096, 3), (30119, 4096, 256, 1), (53188, 4096, 256, 1), (62837, 4096, 256, 2), (62837, 4096, 257, 3)])
+def test_two_workgroups_of_the_sliced_kernel_share_a_compute_unit_where_they_fit(lib, C, R, B, words):
+    """Words per lane: the fewest with which two workgroups fit a compute unit, on small graphs as on the largest; the
+    fewest at all where there are no two samples per compute unit or no such number up to three."""
+    lib.tictac_trim_memory()
+    lib.host_forget_launches()
+    assert lib.host_tac_sliced(C, R, B) == 0
+    (name, blocks, threads, lds, _), = lib.launches()
+    assert f"tac_sliced_kernelILi{words}E" in name, name
+    assert (threads // 64 - 1) * 64 * 64 * words >= C
+    assert blocks == min(B, 256 * min(160 * 1024 // lds, 16 // (threads // 64)))
