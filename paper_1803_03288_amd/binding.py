@@ -82,6 +82,18 @@ def _dev(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
     return ctypes.c_void_p(0 if t is None or t.numel() == 0 else t.data_ptr())
 
 
+# Output vectors of one call.  Small ones (up to 8 KB each) are rows of one allocation, 512 bytes or a multiple apart, which
+# saves a short call 2 us; large ones are allocations of their own, so that keeping one does not keep the others.
+_ROW_BYTES = 512
+
+
+def _vectors(count: int, size: int, dtype: torch.dtype, device="cuda") -> Tuple[torch.Tensor, ...]:
+    if size * dtype.itemsize > 16 * _ROW_BYTES:
+        return tuple(torch.empty(size, dtype=dtype, device=device) for _ in range(count))
+    per_row = _ROW_BYTES // dtype.itemsize
+    return torch.empty_strided((count, size), ((size + per_row - 1) // per_row * per_row, 1), dtype=dtype, device=device).unbind(0)
+
+
 def _host_i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
@@ -163,7 +175,7 @@ def build_deps(n_ops: int, row_ptr, col_idx, recv_ids) -> Dag:
 def tic_priority(dag: Dag) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """``tictac_tic_priority``: ``(prio, order, rank)``, int32 CUDA tensors ``[R]``."""
     R = dag.n_recv
-    prio, order, rank = torch.empty((3, R), dtype=torch.int32, device="cuda").unbind(0)
+    prio, order, rank = _vectors(3, R, torch.int32)
     _check(lib().tictac_tic_priority(dag._h, _dev(prio), _dev(order), _dev(rank), _stream()))
     return prio, order, rank
 
@@ -205,7 +217,7 @@ def simulate(dag: Dag, order: torch.Tensor, op_time: torch.Tensor, recv_time: to
     else:
         assert tuple(order.shape) == (B, R)
         stride = R
-    out = torch.empty((5, B), dtype=torch.float64, device="cuda").unbind(0)       # (rows of one block, as in tac_simulate)
+    out = _vectors(5, B, torch.float64)
     fn = lib().tictac_simulate_f32 if op_time.dtype == torch.float32 else lib().tictac_simulate
     _check(fn(dag._h, ctypes.c_int32(B), _dev(order), ctypes.c_int32(stride), _dev(op_time), _dev(recv_time),
               *(_dev(o) for o in out), _stream()))
@@ -227,7 +239,7 @@ def simulate_channels(dag: Dag, n_channels: int, channel_of_recv, order: torch.T
     else:
         assert tuple(order.shape) == (B, R)
         stride = R
-    out = torch.empty((5, B), dtype=torch.float64, device="cuda").unbind(0)
+    out = _vectors(5, B, torch.float64)
     _check(lib().tictac_simulate_channels(dag._h, ctypes.c_int32(B), ctypes.c_int32(n_channels),
                                           _np_ptr(chan), _dev(order), ctypes.c_int32(stride),
                                           _dev(op_time), _dev(recv_time), *(_dev(o) for o in out), _stream()))
@@ -257,7 +269,7 @@ def simulate_sends(dag: Dag, send_ids, order: torch.Tensor, op_time: torch.Tenso
     else:
         assert tuple(order.shape) == (B, R)
         stride = R
-    out = torch.empty((5, B), dtype=torch.float64, device=recv_time.device).unbind(0)
+    out = _vectors(5, B, torch.float64, recv_time.device)
     _check(lib().tictac_simulate_sends(dag._h, ctypes.c_int32(B), ctypes.c_int32(sends.size),
                                        _np_ptr(sends), _dev(order), ctypes.c_int32(stride),
                                        _dev(op_time), _dev(recv_time), *(_dev(o) for o in out), _stream()))
@@ -303,12 +315,11 @@ def tac_simulate(dag: Dag, op_time: torch.Tensor, recv_time: torch.Tensor, want_
     under its order in one pass.  Returns ``(order, rank, sel_P, sel_Mplus, makespan, eff, U, L, S)``."""
     B = _check_times(dag, op_time, recv_time, allow_f32=True)
     R = dag.n_recv
-    # (one allocation per dtype: the outputs are rows of two blocks)
-    ints = torch.empty((2 if want_rank else 1, B, R), dtype=torch.int32, device="cuda")
-    order, rank = ints[0], (ints[1] if want_rank else None)
+    order = torch.empty((B, R), dtype=torch.int32, device="cuda")
+    rank = torch.empty((B, R), dtype=torch.int32, device="cuda") if want_rank else None
     sel_P = torch.empty((B, R), dtype=torch.float64, device="cuda") if want_sel else None
     sel_M = torch.empty((B, R), dtype=torch.float64, device="cuda") if want_sel else None
-    out = torch.empty((5, B), dtype=torch.float64, device="cuda").unbind(0)
+    out = _vectors(5, B, torch.float64)
     fn = lib().tictac_tac_simulate_f32 if op_time.dtype == torch.float32 else lib().tictac_tac_simulate
     _check(fn(dag._h, ctypes.c_int32(B), _dev(op_time), _dev(recv_time), _dev(order), _dev(rank), _dev(sel_P),
               _dev(sel_M), *(_dev(o) for o in out), _stream()))
