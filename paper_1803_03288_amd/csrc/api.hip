@@ -683,26 +683,43 @@ static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_id
 {
     const int32_t n = d.n;
     g.val.resize(n);
-    g.op.reserve(n); g.ptr.reserve(n + 1);
+    g.op.resize(n); g.ptr.resize(n + 1);
     g.in.resize((size_t)d.E + 1);           // (one more: begin() of an empty list)
-    g.ptr.push_back(0);
-    int32_t *in = g.in.data(), *val = g.val.data(), at = 0;
+    int32_t *in = g.in.data(), *val = g.val.data(), at = 0, M = 0;
     std::vector<int32_t> used(d.n_levels + 1, 0);
     for (int32_t i = 0; i < n; ++i) {
         const int32_t v = order.empty() ? i : order[i];
         if (recv_of_op[v] >= 0) { val[v] = ~recv_of_op[v]; continue; }
         const int32_t first = at, e0 = row_ptr[v], deg = row_ptr[v + 1] - e0;
-        if (deg == 1) {
-            in[at++] = val[col_idx[e0]];
+        // (few predecessors, as most ops have: each value is written and kept if it differs from those before, without a
+        // branch that could go either way)
+        const int32_t *pred = col_idx + e0;
+        if (deg <= 4) {
+            if (deg > 0) in[at++] = val[pred[0]];
+            if (deg > 1) {
+                const int32_t x = val[pred[1]];
+                in[at] = x;
+                at += x != in[first];
+            }
+            if (deg > 2) {
+                const int32_t x = val[pred[2]];
+                in[at] = x;
+                at += (x != in[first]) & (x != in[at - 1]);
+            }
+            if (deg > 3) {
+                const int32_t x = val[pred[3]], mid = std::min(first + 1, at - 1);
+                in[at] = x;
+                at += (x != in[first]) & (x != in[mid]) & (x != in[at - 1]);
+            }
         } else if (deg <= 16) {
-            for (int32_t e = e0; e < e0 + deg; ++e) {
-                const int32_t x = val[col_idx[e]];
+            for (int32_t e = 0; e < deg; ++e) {
+                const int32_t x = val[pred[e]];
                 bool seen = false;
                 for (int32_t k = first; k < at; ++k) seen |= in[k] == x;
                 if (!seen) in[at++] = x;
             }
         } else {
-            for (int32_t e = e0; e < e0 + deg; ++e) in[at++] = val[col_idx[e]];
+            for (int32_t e = 0; e < deg; ++e) in[at++] = val[pred[e]];
             std::sort(in + first, in + at);
             at = (int32_t)(std::unique(in + first, in + at) - in);
         }
@@ -716,12 +733,12 @@ static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_id
             for (int32_t k = first; k < at; ++k) nr += in[k] < 0;
             if (nr > 2 || at - first - nr > 4) g.list_entries += 1 + (size_t)(at - first);
         }
-        val[v] = (int32_t)g.op.size();
-        g.op.push_back(v);
-        g.ptr.push_back(at);
+        val[v] = M;
+        g.op[M++] = v;
+        g.ptr[M] = at;
         used[level[v]] = 1;
     }
-    g.M = (int32_t)g.op.size();
+    g.M = M;
     // Nodes are grouped by the level of their op in the full graph (an input of a node lies on a
     // strictly lower level, and close to it, which keeps inputs inside the kernel's LDS ring);
     // levels without nodes are dropped.
@@ -1045,10 +1062,12 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
 // ops of 32 words (2.6 million) 12.2 and 11.3, without the kernels' own time.
 constexpr int64_t kHostRowWords = (int64_t)1 << 21;
 // From so many ops and predecessors on, the tables of the propagation kernels are made by a thread of their own while the
-// rows and classes are formed: a build of 20 512 ops takes 1.25 ms with it and 1.30 without, of 10 512 ops 0.64 and 0.66, of
-// 6 292 ops (inception3) 0.14 either way.  The tables are a fifth of a small graph's build (resnet50 41 us, 37 without them)
-// and are made nevertheless: a first tictac_dag_recompute_deps would otherwise make them, wait for the stream twice and take
-// 1.1 ms instead of 0.1 at 20 512 ops, a first batch of 32 such handles 31 ms instead of 2.8.
+// rows and classes are formed.  Starting it costs what it saves on small graphs (a build of inception3, 15 984, takes 136 us
+// without it and 175 with it; 7 061 ops with 17 300 predecessors 281 and 130, 10 512 with 26 900 661 and 643).  The tables are
+// a tenth of a small graph's build (resnet50 41 us, 37 without them) and up to two fifths where sets and classes are quick
+// to form (3 236 ops, 8 122 predecessors, two words: 163 us, 93 without), and are made nevertheless: a first
+// tictac_dag_recompute_deps would otherwise make them, wait for the stream twice and take 1.1 ms instead of 0.1 at 20 512
+// ops, a first batch of 32 such handles 31 ms instead of 2.8.
 constexpr int64_t kPropThread = 16384;
 
 static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int32_t R, const int32_t *recv_ids,
