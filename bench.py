@@ -39,7 +39,6 @@ HEADLINE = "inception3"
 
 # peaks of MI355X used for the roofline records
 HBM_PEAK_GBS = 8000.0
-FP64_VECTOR_PEAK_TFLOPS = 78.6      # 256 compute units x 4 SIMD x 16 lanes x 2 (fused multiply-add) x 2.4 GHz
 
 
 def parse() -> argparse.Namespace:
@@ -69,6 +68,16 @@ def tac_algorithmic_ops(nnz_ops: int, R: int, N: int) -> float:
     subtract when that recv is removed, and four float64 operations (two min, two compares) per
     comparator step of the R(R+1)/2 steps of the selection scans."""
     return float(N + 2 * nnz_ops + 4 * (R * (R + 1) // 2))
+
+
+def tac_kernels(d, n_classes: int, B: int) -> str:
+    """The kernels that a TAC call on a preset runs (the rules of launch_tac): by chains where one class of ops introduces
+    each recv, from 64 samples on, or 8 192 where the classes are few; else in registers; bit-sliced for many classes."""
+    if n_classes > 1024:
+        return "tac_sliced_kernel"
+    if d.name.startswith(("resnet50", "vgg16", "inception3")) and B >= (8192 if n_classes <= 256 else 64):
+        return "class_totals_kernel + tac_chain_kernel"
+    return "tac_reg_kernel"
 
 
 def traffic_from_profiles(workload: str, B: int):
@@ -183,8 +192,9 @@ def main() -> int:
             "tac_simulate_ms": tac_ms, "tac_simulate_schedules_per_s": B / (tac_ms * 1e-3),
             "build_deps_ms": build_ms, "tic_priority_ms": tic_ms, "dep_propagation_us": k1_ms * 1e3,
             "classes": h.n_classes, "levels": h.n_levels, "dep_incidences": nnz,
-            "alu": {"algorithmic_Tops_per_s": ops / (tac_ms * 1e-3) / 1e12,
-                    "frac_of_fp64_vector_peak": ops / (tac_ms * 1e-3) / 1e12 / FP64_VECTOR_PEAK_TFLOPS},
+            # (a rate of the method's op-by-op form: the kernels work on classes of ops and carry out far fewer)
+            "alu": {"algorithmic_Tops_per_s": ops / (tac_ms * 1e-3) / 1e12},
+            "tac_kernels": tac_kernels(d, h.n_classes, B),
             "hbm": {"compulsory_GBs": hbm_bytes / (tac_ms * 1e-3) / 1e9,
                     "frac_of_hbm_peak": hbm_bytes / (tac_ms * 1e-3) / 1e9 / HBM_PEAK_GBS},
             "mean_scheduling_efficiency": float(res[5].mean()), "mean_makespan_s": float(res[4].mean()),
@@ -216,14 +226,12 @@ def main() -> int:
     tac_s = head["tac_simulate_ms"] * 1e-3
 
     # ---- roofline record of the dominant kernel (the fused TAC + simulation launch), from the HIP events ----
-    # On model-shaped graphs a full batch goes through class_totals_kernel (a stream over the times) and tac_chain_kernel
-    # (R dependent rounds): most of the bytes are in the first, so the record is against HBM.  The operation count of the
-    # method per op stays in per_config; the kernels, which work on classes, carry out far fewer.
-    if args.workload == "stress":
-        kernel_name, note = "tac_sliced_kernel", "bound by the barriers of R dependent rounds per sample"
-    else:
-        kernel_name, note = "class_totals_kernel + tac_chain_kernel", ("compulsory bytes of the call over the time of both "
-                                                                       "launches; the second is a chain of R rounds per sample")
+    # Compulsory bytes over the time of the launches, against HBM.  The operation count of the method per op stays in
+    # per_config; the kernels, which work on classes, carry out far fewer.
+    kernel_name = head["tac_kernels"]
+    note = {"tac_sliced_kernel": "bound by the barriers of R dependent rounds per sample",
+            "tac_reg_kernel": "bound by the instructions of R dependent rounds per sample"}.get(
+                kernel_name, "the first streams the times, the second is a chain of R rounds per sample")
     roofline = {"kernel": f"{kernel_name} (TAC + simulation fused)", "bound": "hbm", "achieved": head["hbm"]["compulsory_GBs"],
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": head["hbm"]["frac_of_hbm_peak"],
                 "traffic": traffic_from_profiles(args.workload, B), "ms_per_launch": tac_s * 1e3,

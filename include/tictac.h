@@ -38,7 +38,9 @@
  *     message.  No exception or abort crosses this boundary.
  *   - Calls taking a stream are asynchronous on it unless stated otherwise.
  *     Calls on the same tictac_dag must not overlap in time on different
- *     streams (the handle owns one scratch workspace).
+ *     streams (the handle owns one scratch workspace, which a call that needs
+ *     a larger one replaces; TAC on large batches takes up to about 0.6 GB, on
+ *     graphs of thousands of classes up to 1.3 GB).
  */
 #ifndef TICTAC_H
 #define TICTAC_H
@@ -69,9 +71,11 @@ typedef struct tictac_dag tictac_dag; /* opaque; owns device copies of the graph
 typedef void *tictac_stream;          /* a hipStream_t; NULL = the default stream */
 
 /*
- * Sec. 4.1, Communication Dependency.  Validates the graph, uploads it, and
- * computes dep[v] = ({i} if v is recv i) U (union of dep[u] over predecessors u)
- * for every op on the device.
+ * Sec. 4.1, Communication Dependency.  Validates the graph and computes
+ * dep[v] = ({i} if v is recv i) U (union of dep[u] over predecessors u) for every op,
+ * into device memory: by the propagation kernels, or for small graphs (up to 2^21 words
+ * in the rows of all ops and predecessors) on the host, set by set, expanded on the
+ * device.  Makes the classes of ops with one dep and the tables of the kernels.
  *   pred_row_ptr [n_ops+1], pred_col_idx [E]  host: predecessors of op v are
  *       pred_col_idx[pred_row_ptr[v] .. pred_row_ptr[v+1])
  *   recv_ids [n_recv]                         host
@@ -148,6 +152,10 @@ int tictac_tic_priority(const tictac_dag *dag, int32_t *prio, int32_t *order, in
  *   sel_P, sel_Mplus [B][n_recv] device: P and M+ of each recv in the round that
  *         selected it (+infinity when no M+ exists)          (each may be NULL)
  * B = 0 is valid.
+ * The first call on a handle may make tables on the host; they go to the device on a
+ * stream of the library's own, and the call waits for that copy, not for `stream`.
+ * Under stream capture a call allocates nothing when an earlier one with the same
+ * outputs had at least as many samples.
  */
 int tictac_tac_priority(const tictac_dag *dag, int32_t B, const double *op_time, const double *recv_time,
                         int32_t *order, int32_t *rank, double *sel_P, double *sel_Mplus,

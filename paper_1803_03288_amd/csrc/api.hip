@@ -1,6 +1,7 @@
-// C ABI of libtictac: argument checks, graph validation and levelling, grouping of
-// compute ops into classes of identical dependency sets, and the calls into the
-// kernel launchers.  All arithmetic of the method runs in the kernels.
+// C ABI of libtictac: argument checks, graph validation and levelling, the dependency
+// sets of small graphs (large ones are propagated by the kernels), grouping of compute
+// ops into classes of identical dependency sets, the tables that the kernels read, and
+// the calls into the kernel launchers.  Everything per timing sample runs in the kernels.
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>

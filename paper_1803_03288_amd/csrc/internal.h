@@ -43,7 +43,7 @@ struct Dag {
 
     // Condensed graph used by the propagation.  A compute op whose only predecessor is a
     // compute op has that op's dep; every other compute op is a *node*.  Nodes are sorted
-    // by level (longest path counted in nodes) into positions 0..M-1.
+    // by level (of their op in the full graph; levels without a node dropped) into positions 0..M-1.
     int32_t M = 0;                  // number of nodes
     int32_t n_node_levels = 0;
     int32_t max_node_level_width = 0;
@@ -149,7 +149,8 @@ struct Dag {
     int32_t n_empty_cls = 0;
 
     // scratch owned by the handle (grown on demand, stream-ordered use)
-    // the two allocations that hold every array above (graph tables + dep; class tables)
+    // The allocations that hold the arrays above.  Rows formed on the host: class_block holds them all.  Rows formed on the
+    // device: the graph's tables and op.dep; the records of the kernel with 64-byte slices; the class tables.
     Block graph_block, quad_block, class_block;
     void *d_work = nullptr;
     int32_t *d_chan = nullptr;      // [R] channel table of the last several-channel simulation
