@@ -1366,7 +1366,9 @@ static hipError_t table_stream(int device, hipStream_t *out)
 bool being_captured(hipStream_t s)
 {
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &c) == hipSuccess && c != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();            // (the null stream while another stream is captured; the next launch would report it)
+    return false;
 }
 
 static std::vector<int32_t> classes_of_ops(const Dag *d)
