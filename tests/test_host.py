@@ -245,7 +245,7 @@ def test_a_first_tac_call_under_capture(lib):
 
 
 def test_handles_do_not_wait_for_each_others_tables(lib):
-    """Four threads make the tables of a handle each while every copy takes 50 ms: side by side, not one after the other."""
+    """Four threads make the tables of a handle each while every copy takes 0.2 s: side by side, not one after the other."""
     d = GRAPHS["chain"]()
     handles = [lib.build(d)[1] for _ in range(4)]
     rooms = [{} for _ in range(4)]
@@ -253,13 +253,13 @@ def test_handles_do_not_wait_for_each_others_tables(lib):
     with ThreadPoolExecutor(4) as ex:
         assert list(ex.map(lambda k: lib.tac(handles[k], d, 8190, rooms[k]), range(4))) == [0] * 4
         lib.host_forget_launches()
-        lib.host_slow_copies(50000)
+        lib.host_slow_copies(200000)
         start = time.perf_counter()
         assert list(ex.map(lambda k: lib.tac(handles[k], d, 8192, rooms[k]), range(4))) == [0] * 4
         took = time.perf_counter() - start
     lib.host_slow_copies(0)
     assert sum("copy_in" in k for k in lib.kernels()) == 4
-    assert took < 0.15
+    assert took < 0.6
     for h in handles:
         lib.free(h)
 
