@@ -3,7 +3,7 @@ of per-op timing samples.
 
 This module only *draws inputs*.  It contains none of the scheduling method's
 arithmetic (no dependency sets, priorities or makespans), so that the CPU
-checker and the GPU library can both be fed from it without sharing any code of
+oracle and the GPU library can both be fed from it without sharing any code of
 the method itself.
 
 The paper (Sec. 3.1) takes as input a partitioned graph, whose communication
