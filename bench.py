@@ -72,9 +72,10 @@ def tac_algorithmic_ops(nnz_ops: int, R: int, N: int) -> float:
 
 def tac_kernels(d, n_classes: int, B: int) -> str:
     """The kernels that a TAC call on a preset runs (the rules of launch_tac): by chains where one class of ops introduces
-    each recv, from 64 samples on, or 8 192 where the classes are few; else in registers; bit-sliced for many classes."""
+    each recv, from 64 samples on, or 8 192 where the classes are few; else in registers; for many classes by the frontier, small
+    batches bit-sliced."""
     if n_classes > 1024:
-        return "tac_sliced_kernel"
+        return "tac_frontier_kernel" if B > 512 else "tac_sliced_kernel"
     if d.name.startswith(("resnet50", "vgg16", "inception3")) and B >= (8192 if n_classes <= 256 else 64):
         return "class_totals_kernel + tac_chain_kernel"
     return "tac_reg_kernel"
@@ -103,7 +104,7 @@ def traffic_from_profiles(workload: str, B: int):
 
 def kernel_sources_hash() -> str:
     h = hashlib.sha256()
-    for f in ("k3_tac_chain.hip", "k3_tac_reg.hip", "k3_tac_sliced.hip", "k3_tac.hip", "device_utils.h"):
+    for f in ("k3_tac_chain.hip", "k3_tac_reg.hip", "k3_tac_frontier.hip", "frontier_plan.h", "k3_tac_sliced.hip", "k3_tac.hip", "device_utils.h"):
         h.update(open(os.path.join(ROOT, "paper_1803_03288_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -229,7 +230,8 @@ def main() -> int:
     # Compulsory bytes over the time of the launches, against HBM.  The operation count of the method per op stays in
     # per_config; the kernels, which work on classes, carry out far fewer.
     kernel_name = head["tac_kernels"]
-    note = {"tac_sliced_kernel": "bound by the barriers of R dependent rounds per sample",
+    note = {"tac_frontier_kernel": "bound by the latency of dependent trips to memory in R rounds per sample",
+            "tac_sliced_kernel": "bound by the barriers of R dependent rounds per sample",
             "tac_reg_kernel": "bound by the instructions of R dependent rounds per sample"}.get(
                 kernel_name, "the first streams the times, the second is a chain of R rounds per sample")
     roofline = {"kernel": f"{kernel_name} (TAC + simulation fused)", "bound": "hbm", "achieved": head["hbm"]["compulsory_GBs"],

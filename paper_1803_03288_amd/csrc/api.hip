@@ -14,6 +14,7 @@
 #include <numeric>
 
 #include "chain_plan.h"
+#include "frontier_plan.h"
 #include "internal.h"
 
 namespace tictac {
@@ -399,7 +400,7 @@ static void free_dag(Dag *d)
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     const Block blocks[] = {
         d->graph_block, d->quad_block, d->class_block, {d->d_work, d->work_bytes}, {d->d_chan, (size_t)d->R * sizeof(int32_t)},
-        d->send_block, d->chain.block, d->sliced_block};
+        d->send_block, d->chain.block, d->sliced_block, d->frontier.block};
     for (const auto &b : blocks) {
         if (!b.p) continue;
         if (idle) pool_put(b.p, b.bytes, d->device);
@@ -1474,6 +1475,50 @@ hipError_t ensure_sliced_tables(Dag *d)
     if (e == hipSuccess) e = cls.finish();
     d->sliced_made = e == hipSuccess;
     return e;
+}
+
+hipError_t ensure_frontier_tables(Dag *d)
+try {
+    std::lock_guard<std::mutex> lock(d->tables_mutex);
+    FrontierTables &f = d->frontier;
+    if (f.made) return hipSuccess;
+    const std::vector<int32_t> cls_of_op = classes_of_ops(d);
+    std::vector<int32_t> recv_of_op(d->n, -1), level, order;
+    for (int32_t i = 0; i < d->R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
+    int32_t n_levels = 0;
+    FrontierPlan p;
+    if (find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), level, order, n_levels))
+        make_frontier_plan(d->n, d->R, d->C, d->h_row_ptr.data(), d->h_col_idx.data(), level.data(), cls_of_op.data(), recv_of_op.data(),
+                           d->h_cls_cnt0, d->h_col_cls, p);
+    if (!p.ok) {
+        f.made = true;
+        return hipSuccess;
+    }
+    static_assert(sizeof(FrontierRow) == 64, "as it is read");
+    Packer t;
+    FrontierRow *row = nullptr;
+    t.add(&row, p.row);
+    t.add(&f.d_inputs, p.inputs);
+    t.add(&f.d_outputs, p.outputs);
+    t.add(&f.d_counters, p.counters);
+    t.add(&f.d_wide, p.wide);
+    t.add(&f.d_roots, p.roots);
+    t.add(&f.d_free_cols, p.free_cols);
+    t.add(&f.d_own_ptr, p.own_ptr);
+    t.add(&f.d_own, p.own);
+    hipStream_t s;
+    hipError_t e = table_stream(d->device, &s);
+    if (e == hipSuccess) e = t.commit(f.block, d->device, s);
+    if (e == hipSuccess) e = t.finish();
+    if (e != hipSuccess) return e;
+    f.d_row = reinterpret_cast<int4 *>(row);
+    f.n_counters = (int32_t)p.counters.size();
+    f.n_roots = (int32_t)p.roots.size();
+    f.n_free = (int32_t)p.free_cols.size();
+    f.ok = f.made = true;
+    return hipSuccess;
+} catch (const std::bad_alloc &) {
+    return hipErrorOutOfMemory;
 }
 
 hipError_t ensure_chain_tables(Dag *d)

@@ -1,0 +1,168 @@
+// Plan of the frontier form of TAC (k3_tac_frontier.hip): the graph of the classes of compute ops.
+//
+// dep of a class is the union of dep of its inputs: of the classes of the compute ops and of the recvs that precede one
+// member none of whose predecessors has the same dep (for a piece of a split set, a member whose predecessors with the same
+// dep are of other pieces).  The member of lowest level is such a one, and levels rise along the inputs.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+#include <vector>
+
+namespace tictac {
+
+constexpr int32_t kFrontierMaxClasses = (1 << 18) - 1;  // a class shares a word of the kernel's lists with a recv
+constexpr int32_t kFrontierMaxRecvs = (1 << 14) - 2;
+constexpr int32_t kFrontierMaxQ = 128;                  // members of Q, of the frontier: what the kernel has room for
+constexpr int32_t kFrontierMaxFrontier = 448;
+constexpr int32_t kFrontierMaxInputs = 64;              // of a class: they are looked at again and again
+
+// An output of a class, a class that has it among its inputs: bits 0..17 the class.  Each class keeps the number of its inputs
+// (classes) that do not point yet in four bits, those with more than fifteen in a word (bits 0..17 are its number).
+constexpr uint32_t kFrontierFill = 1u << 18;            // no class: fills the last four of a list up
+constexpr uint32_t kFrontierWide = 1u << 19;            // its counter is a word
+constexpr uint32_t kFrontierOnly = 1u << 30;            // no other class is among its inputs
+constexpr uint32_t kFrontierLast = 1u << 31;            // of the last four of a list
+
+struct FrontierRow {        // 64 bytes: a class
+    int32_t in[4];          // the first inputs: a class, or ~i for recv i, or ~R: none
+    uint32_t out[4];        // the first outputs
+    int32_t more;           // further inputs: where they start in `inputs` (a multiple of four), times four, and their number of fours
+    int32_t rest;           // further outputs: where they start in `outputs`
+    int32_t pad[2];
+    int32_t n, list;        // number of op_time columns, where they are in cls_cols
+    int32_t c0, c1;         // the first two
+};
+
+struct FrontierPlan {
+    bool ok = false;
+    std::vector<FrontierRow> row;
+    std::vector<int32_t> inputs;            // (filled up to fours with ~R)
+    std::vector<uint32_t> outputs;
+    std::vector<uint32_t> counters;         // before the first round: eight classes per word, then the words of the wide ones
+    std::vector<int32_t> wide;              // the wide ones
+    std::vector<int32_t> roots;             // classes with recvs but no class among their inputs
+    std::vector<int32_t> free_cols;         // columns of the ops that depend on no recv
+    std::vector<int32_t> own_ptr, own;      // [R + 1]: the classes with recv i among their inputs
+};
+
+// By op: level, class (-1: a recv), recv (-1: a compute op).  cnt0: |dep| by class.  col_cls: class by column.
+inline void make_frontier_plan(int32_t n, int32_t R, int32_t C, const int32_t *row_ptr, const int32_t *col_idx, const int32_t *level,
+                               const int32_t *cls_of_op, const int32_t *recv_of_op, const std::vector<int32_t> &cnt0,
+                               const std::vector<int32_t> &col_cls, FrontierPlan &p)
+{
+    if (R < 1 || R > kFrontierMaxRecvs || C < 1 || C > kFrontierMaxClasses) return;
+    std::vector<int32_t> rep(C, -1);
+    for (int32_t v = 0; v < n; ++v) {
+        const int32_t c = cls_of_op[v];
+        if (c >= 0 && (rep[c] < 0 || level[v] < level[rep[c]])) rep[c] = v;
+    }
+    std::vector<int32_t> col_ptr(C + 1, 0), cols(col_cls.size());
+    for (int32_t c : col_cls) ++col_ptr[c + 1];
+    for (int32_t c = 0; c < C; ++c) col_ptr[c + 1] += col_ptr[c];
+    {
+        std::vector<int32_t> fill(col_ptr.begin(), col_ptr.end() - 1);
+        for (int32_t j = 0; j < (int32_t)col_cls.size(); ++j) cols[fill[col_cls[j]]++] = j;
+    }
+    // inputs of every class, in_ptr[c] .. in_ptr[c + 1], ascending: recvs (~i) first
+    std::vector<int32_t> all_ptr(1, 0), all, in_ptr(1, 0), in, n_open(C, 0), n_out(C, 0), mark(C + R, -1);
+    all_ptr.reserve(C + 1);
+    all.reserve((size_t)C * 4);
+    for (int32_t c = 0; c < C; ++c) {
+        const size_t first = all.size();
+        if (cnt0[c] > 0)
+            for (int32_t e = row_ptr[rep[c]]; e < row_ptr[rep[c] + 1]; ++e) {
+                const int32_t u = col_idx[e], v = cls_of_op[u] < 0 ? ~recv_of_op[u] : cls_of_op[u];
+                if (v >= 0 && cnt0[v] == 0) continue;
+                size_t k = all.size();
+                while (k > first && all[k - 1] > v) --k;
+                if (k == first || all[k - 1] != v) all.insert(all.begin() + k, v);
+            }
+        all_ptr.push_back((int32_t)all.size());
+    }
+    // without those that are an input of another input: dep of that holds theirs
+    p.own_ptr.assign(R + 1, 0);
+    in_ptr.reserve(C + 1);
+    in.reserve(all.size());
+    for (int32_t c = 0; c < C; ++c) {
+        for (int32_t k = all_ptr[c]; k < all_ptr[c + 1]; ++k)
+            if (const int32_t w = all[k]; w >= 0)
+                for (int32_t i = all_ptr[w]; i < all_ptr[w + 1]; ++i) mark[all[i] >= 0 ? all[i] : C + ~all[i]] = c;
+        for (int32_t k = all_ptr[c]; k < all_ptr[c + 1]; ++k) {
+            const int32_t v = all[k];
+            if (mark[v >= 0 ? v : C + ~v] == c) continue;
+            in.push_back(v);
+            if (v >= 0) { ++n_out[v]; ++n_open[c]; }
+            else ++p.own_ptr[~v + 1];
+        }
+        in_ptr.push_back((int32_t)in.size());
+        if (in_ptr[c + 1] - in_ptr[c] > kFrontierMaxInputs) return;
+    }
+    p.counters.assign(((size_t)C + 7) / 8, 0);
+    std::vector<int32_t> place(C, 0);               // (of the wide ones)
+    for (int32_t c = 0; c < C; ++c) {
+        if (n_open[c] < 16) {
+            p.counters[c >> 3] |= (uint32_t)n_open[c] << (c & 7) * 4;
+            place[c] = c;
+        } else {
+            place[c] = (int32_t)p.wide.size();
+            p.wide.push_back(c);
+        }
+    }
+    for (int32_t c : p.wide) p.counters.push_back((uint32_t)n_open[c]);
+    p.counters.resize((p.counters.size() + 3) / 4 * 4, 0);
+    p.row.resize(C);
+    std::vector<int32_t> at(C, 0);                  // the output of class c that is next
+    int32_t rest = 0;
+    for (int32_t c = 0; c < C; ++c) {
+        FrontierRow &r = p.row[c];
+        const int32_t k = in_ptr[c + 1] - in_ptr[c], *q = in.data() + in_ptr[c];
+        for (int32_t j = 0; j < 4; ++j) r.in[j] = j < k ? q[j] : ~R;
+        r.more = (int32_t)p.inputs.size() << 2 | std::max(0, (k - 1) / 4);      // (a multiple of four: bits 0..3 are free)
+        for (int32_t j = 4; j < (k + 3) / 4 * 4; ++j) p.inputs.push_back(j < k ? q[j] : ~R);
+        for (uint32_t &o : r.out) o = kFrontierFill | (n_out[c] <= 4 ? kFrontierLast : 0u);
+        r.rest = rest;
+        rest += std::max(0, (n_out[c] - 1) / 4 * 4);
+        r.pad[0] = r.pad[1] = 0;
+        if (!n_open[c] && cnt0[c] > 0) p.roots.push_back(c);
+        r.n = col_ptr[c + 1] - col_ptr[c];
+        r.list = col_ptr[c];
+        const int32_t *col = cols.data() + col_ptr[c];
+        r.c0 = r.n > 0 ? col[0] : 0;
+        r.c1 = r.n > 1 ? col[1] : 0;
+        if (cnt0[c] == 0) p.free_cols.insert(p.free_cols.end(), col, col + r.n);
+    }
+    p.outputs.assign(rest, kFrontierFill);
+    for (int32_t c = 0; c < C; ++c)
+        if (n_out[c] > 4)
+            for (int32_t j = 0; j < 4; ++j) p.outputs[p.row[c].rest + (n_out[c] - 1) / 4 * 4 - 4 + j] |= kFrontierLast;
+    // what is in the kernel's lists before the first round
+    {
+        std::vector<char> pointed(R, 0);
+        int32_t n_q = 0, n_frontier = 0;
+        for (int32_t c : p.roots) {
+            const int32_t k = in_ptr[c + 1] - in_ptr[c], r = ~in[in_ptr[c]];
+            if (k > 1) ++n_frontier;
+            else if (!pointed[r]) { pointed[r] = 1; ++n_q; }
+        }
+        if (n_q > kFrontierMaxQ || n_frontier > kFrontierMaxFrontier) return;
+    }
+    for (int32_t i = 0; i < R; ++i) p.own_ptr[i + 1] += p.own_ptr[i];
+    p.own.resize(p.own_ptr[R]);
+    std::vector<int32_t> own_fill(p.own_ptr.begin(), p.own_ptr.end() - 1);
+    for (int32_t c = 0; c < C; ++c)
+        for (int32_t k = in_ptr[c]; k < in_ptr[c + 1]; ++k) {
+            const int32_t v = in[k];
+            if (v < 0) {
+                p.own[own_fill[~v]++] = c;
+                continue;
+            }
+            const int32_t j = at[v]++;
+            uint32_t &o = j < 4 ? p.row[v].out[j] : p.outputs[p.row[v].rest + j - 4];
+            o = (o & kFrontierLast) | (uint32_t)place[c] | (n_open[c] == 1 ? kFrontierOnly : n_open[c] > 15 ? kFrontierWide : 0u);
+        }
+    p.ok = true;
+}
+
+}  // namespace tictac

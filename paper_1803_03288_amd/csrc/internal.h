@@ -33,6 +33,16 @@ struct ChainTables {
     uint32_t *d_flush = nullptr;
 };
 
+// Tables of the frontier form of TAC (frontier_plan.h, k3_tac_frontier.hip), made at the first call that takes that form.
+struct FrontierTables {
+    bool made = false, ok = false;
+    int32_t n_roots = 0, n_free = 0, n_counters = 0;
+    Block block;
+    int4 *d_row = nullptr;
+    int32_t *d_inputs = nullptr, *d_roots = nullptr, *d_free_cols = nullptr, *d_own_ptr = nullptr, *d_own = nullptr, *d_wide = nullptr;
+    uint32_t *d_outputs = nullptr, *d_counters = nullptr;
+};
+
 // Everything a handle owns.  Device arrays are sized exactly; empty ones are NULL.
 struct Dag {
     int32_t n = 0, R = 0, W = 0, N = 0, E = 0;
@@ -186,6 +196,7 @@ struct Dag {
     std::mutex tables_mutex;
     // chain form of TAC: its tables, and the class rows and columns (host) that they are made from
     ChainTables chain;
+    FrontierTables frontier;
     std::vector<uint64_t> h_cls_dep;    // [C][W]   (small graphs only)
     std::vector<int32_t> h_col_cls;     // [N]
     // bit-sliced TAC: its tables are made at the first call that takes it, from |dep| and the lowest recv of every class
@@ -198,6 +209,8 @@ hipError_t ensure_workspace(Dag *d, size_t bytes);
 // the tables of the chain form, made at the first call; d->chain.ok says whether the graph has that form
 hipError_t ensure_chain_tables(Dag *d);
 hipError_t ensure_sliced_tables(Dag *d);
+// likewise for the frontier form
+hipError_t ensure_frontier_tables(Dag *d);
 bool being_captured(hipStream_t s);
 
 // Number of compute units of a device and the number of workgroups of a kernel that fit one,
@@ -246,11 +259,13 @@ inline size_t tac_lds_state_bytes(int32_t R, int32_t W, int32_t C)
     return ((size_t)R * 2 + (R + 1) + 16 + (size_t)W * 2) * 8 + (size_t)C * 16 + (size_t)R * 8 + (size_t)C * 4;
 }
 inline bool tac_small_graph(int32_t R, int32_t W, int32_t C) { return tac_lds_state_bytes(R, W, C) <= 40 * 1024 && C <= 1024; }
-// bit-sliced variant for graphs with many classes (tables above); the same contract as launch_tac_reg
+// bit-sliced variant for graphs with many classes (tables above); the same contract as launch_tac_reg.  only_left: only the samples
+// that launch_tac_frontier has left.  flags_out NULL: nothing is launched, the workspace is made large enough.
 bool tac_sliced_fits(const Dag &d);
 // (flags: the first flag_bytes of the handle's workspace, which the launcher grows as needed; at_least: bytes of the
 // workspace that the pass over the flagged samples needs)
-hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s);
+hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s,
+                             bool only_left = false);
 // device-side construction of colbits, planes0 and live0 from cls_dep and cls_cnt0
 hipError_t launch_sliced_tables(const Dag &d, hipStream_t s);
 // register-resident variant for graphs with few classes; returns hipErrorNotSupported when
@@ -259,6 +274,9 @@ hipError_t launch_sliced_tables(const Dag &d, hipStream_t s);
 // chain form, one lane per sample (needs d.chain; the same contract as launch_tac_sliced).  hipErrorOutOfMemory: nothing has
 // been launched
 hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s);
+// frontier form, one wave per sample (needs d.frontier; the same contract as launch_tac_sliced; the samples that outgrow its lists
+// are flagged 2, for launch_tac_sliced or, like those flagged 1, for the general kernel)
+hipError_t launch_tac_frontier(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s);
 hipError_t launch_tac_reg(Dag &d, const TacArgs &a, int32_t *flags, hipStream_t s);
 
 struct SimArgs {

@@ -405,7 +405,7 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
     p.only_flagged = nullptr;
 
-    // model-shaped graphs: chain form; graphs with few classes: register-resident kernel; with many: bit-sliced
+    // model-shaped graphs: chain form; graphs with few classes: register-resident kernel; with many: frontier form or bit-sliced
     // kernel; then the general kernel for the samples that one of them flagged.
     // The handle's workspace: one flag per sample first, the state of the running kernel after them.
     const size_t flag_bytes = ((size_t)a.B * sizeof(int32_t) + 255) & ~(size_t)255;
@@ -452,9 +452,25 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
         // replaced between the two launches)
         hipError_t e = ensure_sliced_tables(&d);
         if (e != hipSuccess) return e;
+        // A sample by itself takes 1.4 times as long by the frontier form on large graphs as by the bit-sliced kernel, in which
+        // sixteen waves work on it, but many more samples are under way at a time.  Bit-sliced / frontier, ms, for 64, 300,
+        // 1 200 and 4 096 samples: 62 837 classes, 4 096 recvs 19 / 25, 44 / 32, 97 / 34, 265 / 48; 17 249 classes, 2 000 recvs
+        // 7.2 / 9.2, 7.8 / 9.8, 22 / 12, 66 / 16; 10 182 classes, 4 096 recvs 21 / 17, 30 / 22, 69 / 23, 250 / 40; 4 411 classes,
+        // 1 000 recvs 3.6 / 3.8, 3.8 / 4.0, 5.8 / 4.7, 16 / 5.9; 1 556 classes with up to 21 outstanding recvs each, 4 096
+        // recvs 30 / 49, 32 / 51, 93 / 59, 255 / 134.
         int32_t *flags = nullptr;
-        e = tac_sliced_fits(d) ? launch_tac_sliced(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s) : hipErrorNotSupported;
-        if (e == hipSuccess) p.only_flagged = flags;
+        bool frontier = false;
+        if (a.B > 2 * device_cu_count(d.device)) {
+            e = !d.frontier.made && being_captured(s) ? hipErrorNotSupported : ensure_frontier_tables(&d);
+            // (room for the form that takes what this one leaves, before the flags are written)
+            if (e == hipSuccess && d.frontier.ok && tac_sliced_fits(d)) e = launch_tac_sliced(d, a, flag_bytes, flag_bytes + gstate_bytes, nullptr, s, true);
+            if (e == hipSuccess) e = launch_tac_frontier(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s);
+            if (e == hipSuccess) frontier = true;
+            else if (e != hipErrorNotSupported && e != hipErrorOutOfMemory) return e;
+        }
+        // (after the frontier form: the samples that outgrew its lists)
+        e = tac_sliced_fits(d) ? launch_tac_sliced(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s, frontier) : hipErrorNotSupported;
+        if (e == hipSuccess || (frontier && e == hipErrorNotSupported)) p.only_flagged = flags;
         else if (e != hipErrorNotSupported) return e;
     }
 

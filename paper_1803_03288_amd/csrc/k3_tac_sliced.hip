@@ -1,6 +1,7 @@
 // TAC (Sec. 4.3, Algorithm 3) with the iteration under its order (Sec. 3.2) for graphs with many
-// classes of compute ops (thousands of distinct dependency sets, up to 4096 recvs).  One workgroup
-// per timing sample: a control wave that selects, and up to fifteen worker waves that keep the
+// classes of compute ops (thousands of distinct dependency sets, up to 4096 recvs), in small batches,
+// for graphs that the frontier form (k3_tac_frontier.hip) does not take and for the samples that it
+// leaves.  One workgroup per timing sample: a control wave that selects, and up to fifteen worker waves that keep the
 // properties of Algorithm 1 up to date.
 //
 // The selection loop of Algorithm 3 takes the properties of Algorithm 1 afresh in every round; as in
@@ -65,6 +66,7 @@ struct SlicedParams {
     int32_t simulate;
     double *makespan, *eff, *U, *L, *S;
     int32_t *flags;                 // [B] 1 = left to the general kernel
+    int32_t only_left;              // only the samples with flags[b] = 2, which the frontier form has left
     char *scratch;                  // per workgroup: class times [C] f64, parent counts [CWpad][2] u64, spilled events [C] int2,
                                     // the classes with two or more outstanding recvs [CWpad] u64 (written when a tie needs them)
     size_t scratch_stride;
@@ -185,6 +187,7 @@ tac_sliced_kernel(const SlicedParams p)
     for (int k = 0; k < KW; ++k) cwk[k] = lane * n_workers + (wave - 1) + k * NWT;
 
     for (int b = blockIdx.x; b < p.B; b += gridDim.x) {
+        if (p.only_left && __builtin_amdgcn_readfirstlane(p.flags[b]) != 2) continue;       // uniform over the workgroup
         const TimeRow rt = time_row(p.recv_time, (size_t)b * R, p.f32 != 0);
         const TimeRow ot = time_row(p.op_time, (size_t)b * N, p.f32 != 0);
         __syncthreads();                    // the previous sample is finished with LDS and with its memory
@@ -801,7 +804,7 @@ static hipError_t launch_sliced_k(SlicedParams &p, Dag &d, const TacArgs &a, siz
     if (grid > a.B) grid = a.B;
     p.scratch_stride = tac_sliced_scratch_stride(d, KW);
     e = ensure_workspace(&d, std::max(at_least, flag_bytes + p.scratch_stride * (size_t)grid));
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || !flags_out) return e;
     p.flags = static_cast<int32_t *>(d.d_work);
     p.scratch = static_cast<char *>(d.d_work) + flag_bytes;
     *flags_out = p.flags;
@@ -809,10 +812,12 @@ static hipError_t launch_sliced_k(SlicedParams &p, Dag &d, const TacArgs &a, siz
     return hipGetLastError();
 }
 
-hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s)
+hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s,
+                             bool only_left)
 {
     if (!tac_sliced_fits(d) || a.sel_P || a.sel_Mplus) return hipErrorNotSupported;
     SlicedParams p{};
+    p.only_left = only_left ? 1 : 0;
     p.B = a.B; p.R = d.R; p.W = d.W; p.C = d.C; p.CW = d.CW; p.CWpad = d.CWpad; p.N = d.N;
     p.cls_dep = d.d_cls_dep; p.cls_ptr = d.d_cls_ptr; p.cls_cols = d.d_cls_cols;
     p.colbits = d.d_colbits; p.planes0 = d.d_planes0; p.live0 = d.d_live0; p.ndom0 = d.d_ndom0;
@@ -830,7 +835,7 @@ hipError_t launch_tac_sliced(Dag &d, const TacArgs &a, size_t flag_bytes, size_t
     // with 60 567 classes), but two are under way.  4 096 samples, layered graphs, ms with one / two / three words:
     //   classes (recvs)   6 465 (600)  13 781 (1 024)  26 508 (2 048)  30 119 (4 096)  44 588 (2 048)  53 188 (4 096)  58 086 (4 096)  62 837 (4 096)
     //                    18 / 22 / 24    59 / 59 / 65   86 / 118 / 118  257 / 181 / 246 171 / 121 / 189 284 / 203 / 279 270 / 304 / 254   - / 314 / 256
-    // (two of one word fit up to 28 672 classes, of two up to 57 344, of three up to 86 016).  512 samples, 53 188 classes:
+    // (the frontier form takes batches of more than two samples per compute unit now, except what outgrows its lists; two of one word fit up to 28 672 classes, of two up to 57 344, of three up to 86 016).  512 samples, 53 188 classes:
     // 48 / 44 / 56; 300 samples, 30 119 classes: 31 / 31 / 41.  Four words need more registers than two workgroups have
     // (535 ms with 53 188 classes).
     int per_lane = (d.CW + kWorkersMax * 64 - 1) / (kWorkersMax * 64);

@@ -1,0 +1,72 @@
+"""Host side of the frontier form of TAC, against the stand-in for the HIP runtime: which calls take it, memory that runs out
+while its tables are made, and streams under capture."""
+
+import pytest
+
+from test_host import GRAPHS, layered, lib          # noqa: F401  (lib: the fixture)
+
+LARGE = 600                                         # samples: more than two per compute unit
+
+
+def names(lib):
+    return [n for n in ("tac_frontier_kernel", "tac_sliced_kernel", "tac_kernel") if any(n in k for k in lib.kernels())]
+
+
+def tac(lib, h, d, B, rc=0):
+    lib.host_forget_launches()
+    assert lib.tac(h, d, B) == rc, lib.error()
+    return names(lib)
+
+
+@pytest.mark.parametrize("B,frontier", [(1, False), (512, False), (513, True), (LARGE, True)])
+def test_batches_that_take_the_frontier_form(lib, B, frontier):
+    d = GRAPHS["wide"]()
+    h = lib.build(d)[1]
+    assert tac(lib, h, d, B) == ["tac_frontier_kernel"] * frontier + ["tac_sliced_kernel", "tac_kernel"]
+    lib.free(h)
+
+
+def test_under_capture(lib):
+    """A first call allocates, which the runtime refuses under capture; a later one is launches only."""
+    d = GRAPHS["wide"]()
+    h = lib.build(d)[1]
+    lib.tictac_trim_memory()
+    lib.host_capturing(1)
+    rc = lib.tac(h, d, LARGE)
+    lib.host_capturing(0)
+    lib.hipGetLastError()
+    assert rc == -7
+    want = tac(lib, h, d, LARGE)
+    assert "tac_frontier_kernel" in want
+    waits = lib.count("waits")
+    lib.host_capturing(1)
+    again = tac(lib, h, d, LARGE)
+    lib.host_capturing(0)
+    assert again == want and lib.count("waits") == waits
+    lib.free(h)
+
+
+def test_memory_that_runs_out(lib):
+    """Every allocation of device and of host memory that a first call makes fails once, one after the other: the call makes do
+    without or says so, and the next one is as on a fresh handle."""
+    d = layered(12, 160, 300)
+    h = lib.build(d)[1]
+    want = tac(lib, h, d, LARGE)
+    assert "tac_frontier_kernel" in want
+    lib.free(h)
+    for order, left in ((lib.host_fail_device, lib.host_fail_device_left), (lib.host_fail_new, lib.host_fail_new_left)):
+        for k in range(4000):
+            h = lib.build(d)[1]
+            assert lib.tictac_trim_memory() == 0
+            order(k)
+            rc = lib.tac(h, d, LARGE)
+            struck = left() < 0
+            order(-1)
+            assert rc in (0, -7, -8), (k, lib.error())
+            assert lib.hipGetLastError() == 0, k
+            assert tac(lib, h, d, LARGE) == want, k
+            lib.free(h)
+            if not struck:
+                break
+        else:
+            raise AssertionError("no end")
