@@ -286,7 +286,7 @@ tac_chain_kernel(const ChainParams p)
                     x &= x - 1;
                 }
             }
-            if (n >= 2) best = fmin(best, s);
+            if (n >= 2) best = min_f64(best, s);
         }
         return best;
     };
@@ -304,7 +304,7 @@ tac_chain_kernel(const ChainParams p)
             if (a == R) break;
             at = a;
             if (best < 0) { best = a; bslot = as; bP = aP; bT = aT; continue; }
-            const double xa = fmin(bP, aT), ya = fmin(aP, bT);
+            const double xa = min_f64(bP, aT), ya = min_f64(aP, bT);
             double ma = -1.0;
             bool prec = xa < ya;
             if (xa == ya) {
@@ -336,7 +336,7 @@ tac_chain_kernel(const ChainParams p)
         bool tie = false;
 #define TC_COMPARE(k)                                                                     \
         if constexpr (k >= 1 && k < NC) {                                                 \
-            const double xa = fmin(bP, T_##k), ya = fmin(P_##k, bT);                      \
+            const double xa = min_f64(bP, T_##k), ya = min_f64(P_##k, bT);                      \
             tie |= xa == ya;                                                              \
             const bool take = xa < ya;                                                    \
             slot = take ? k : slot;                                                       \
@@ -365,7 +365,7 @@ tac_chain_kernel(const ChainParams p)
         const double j_f = join_l[gf * 64 + lane];
         gcnt[g * 64 + lane] = c;
         F += bT;
-        busy = fmax(busy, F) + bP;
+        busy = max_f64(busy, F) + bP;
         sum_c += bP;
 
         // ---- what is ready now: the next recv on the chain, with the join that points at it already.  (It is no sink of
@@ -432,7 +432,7 @@ tac_chain_kernel(const ChainParams p)
         if (p.simulate && !bad) {
             const double m = busy;                      // (not less than F: the last transfer is in it)
             const double U = sum_c + F;
-            const double L = fmax(sum_c, F);
+            const double L = max_f64(sum_c, F);
             if (p.makespan) p.makespan[b] = m;
             if (p.eff) p.eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
             if (p.U) p.U[b] = U;

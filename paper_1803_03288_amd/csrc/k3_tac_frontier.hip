@@ -238,7 +238,7 @@ __device__ __forceinline__ FrontierLeast frontier_least(const Sample<T> s, int r
             }
         }
         if (M < gm || (M == gm && low < gl)) { gm = M; gl = low; }
-        if (holds) gr = fmin(gr, M);
+        if (holds) gr = min_f64(gr, M);
     }
     FrontierLeast f;
     f.M = wave_min_f64_dpp(gm);
@@ -308,7 +308,7 @@ __device__ __forceinline__ double frontier_M_plus(const Sample<T> s, const uint3
                         const int l = __builtin_ctzll(c);
                         c &= c - 1;
                         int low;
-                        best = fmin(best, row_M(s, __builtin_amdgcn_readlane(y, l), low));
+                        best = min_f64(best, row_M(s, __builtin_amdgcn_readlane(y, l), low));
                     }
                     if (!__ballot(!(z & kFrontierLast))) break;
                     z = z & kFrontierLast ? kFrontierFill | kFrontierLast : outputs[o + (lane & 3)];
@@ -441,12 +441,12 @@ tac_frontier_kernel(const FrontierParams p)
                         uint64_t ca, cb = 0ull;
                         if (__ballot(ea || eb)) {
                             const double va = ea ? ta : TT_INF;
-                            const double m = wave_min_f64_dpp(two && eb ? fmin(va, tb) : va);
+                            const double m = wave_min_f64_dpp(two && eb ? min_f64(va, tb) : va);
                             ca = __ballot(ea && ta == m);
                             if (two) cb = __ballot(eb && tb == m);
                         } else {
                             const double va = ra >= 0 ? Pa : -TT_INF;
-                            const double m = wave_max_f64_dpp(two && rb >= 0 ? fmax(va, Pb) : va);
+                            const double m = wave_max_f64_dpp(two && rb >= 0 ? max_f64(va, Pb) : va);
                             ca = __ballot(ra >= 0 && Pa == m);
                             if (two) cb = __ballot(rb >= 0 && Pb == m);
                         }
@@ -462,9 +462,9 @@ tac_frontier_kernel(const FrontierParams p)
                             ts = readlane_f64(tb, pos - 64);
                         }
                         // (it does not precede itself)
-                        const bool na = ra >= 0 && lane != pos && !(fmin(Pa, ts) < fmin(Ps, ta));
+                        const bool na = ra >= 0 && lane != pos && !(min_f64(Pa, ts) < min_f64(Ps, ta));
                         sure = __ballot(na) == 0ull;
-                        if (two) sure = sure && __ballot(rb >= 0 && lane + 64 != pos && !(fmin(Pb, ts) < fmin(Ps, tb))) == 0ull;
+                        if (two) sure = sure && __ballot(rb >= 0 && lane + 64 != pos && !(min_f64(Pb, ts) < min_f64(Ps, tb))) == 0ull;
                     }
                     if (!sure) {
                         // the scan itself, from one recv to the first later one that precedes it or ties with it
@@ -475,15 +475,15 @@ tac_frontier_kernel(const FrontierParams p)
                         Ps = ts = 0.0;
                         for (int last = -1;;) {
                             const bool first = cur < 0;
-                            const bool ha = ra > last && (first || fmin(Ps, ta) <= fmin(Pa, ts));
-                            const bool hc = rb > last && (first || fmin(Ps, tb) <= fmin(Pb, ts));
+                            const bool ha = ra > last && (first || min_f64(Ps, ta) <= min_f64(Pa, ts));
+                            const bool hc = rb > last && (first || min_f64(Ps, tb) <= min_f64(Pb, ts));
                             const int low = wave_min_i32_dpp(min(ha ? ra : INT32_MAX, hc ? rb : INT32_MAX));
                             if (low == INT32_MAX) break;
                             const uint64_t ma = __ballot(ra == low);
                             at = ma ? (int)__builtin_ctzll(ma) : 64 + (int)__builtin_ctzll(__ballot(rb == low));
                             const double P_ = at < 64 ? readlane_f64(Pa, at) : readlane_f64(Pb, at - 64);
                             const double t_ = at < 64 ? readlane_f64(ta, at) : readlane_f64(tb, at - 64);
-                            const double xa = fmin(Ps, t_), ya = fmin(P_, ts);
+                            const double xa = min_f64(Ps, t_), ya = min_f64(P_, ts);
                             bool take = first || xa < ya;
                             double la = -1.0, ua = 0.0;
                             if (!first && xa == ya) {
@@ -493,7 +493,7 @@ tac_frontier_kernel(const FrontierParams p)
                                 for (int k = lb < 0.0 ? 0 : 1; k < 2; ++k) {
                                     const int r = k ? low : cur;
                                     const FrontierLeast f = frontier_least(sample, r);
-                                    la = fmin(f.M_of_r, f.M + (double)rt[r]);
+                                    la = min_f64(f.M_of_r, f.M + (double)rt[r]);
                                     ua = f.M_of_r;
                                     if (!k) { lb = la; hb = ua; }
                                 }
@@ -518,7 +518,7 @@ tac_frontier_kernel(const FrontierParams p)
                 }
                 if (lane == 0) alive[best >> 5] &= ~(1u << (best & 31));
                 F += ts;
-                busy = fmax(busy, F) + Ps;
+                busy = max_f64(busy, F) + Ps;
                 sum_c += Ps;
                 if ((step & 63) == lane) mine = best;
                 if ((step & 63) == 63 || step == R - 1) {
@@ -723,7 +723,7 @@ tac_frontier_kernel(const FrontierParams p)
             Arg *q = rare();
             q->flags[b] = over ? 2 : 0;
             if (q->simulate && !over) {
-                const double m = fmax(busy, F), U = sum_c + F, L = fmax(sum_c, F);
+                const double m = max_f64(busy, F), U = sum_c + F, L = max_f64(sum_c, F);
                 if (q->makespan) q->makespan[b] = m;
                 if (q->eff) q->eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
                 if (q->U) q->U[b] = U;

@@ -391,7 +391,7 @@ tac_reg_kernel(const TacRegParams p)
             if (LIST && qm == 2) {
                 // one comparison (equal members or a tie: below)
                 const int e0 = __builtin_amdgcn_readlane(ql, 0), e1 = __builtin_amdgcn_readlane(ql, 1);
-                const double x0 = fmin(P[e0], t[e1]), x1 = fmin(P[e1], t[e0]);
+                const double x0 = min_f64(P[e0], t[e1]), x1 = min_f64(P[e1], t[e0]);
                 if (e0 != e1 && __ballot(x0 != x1) != 0ull) {
                     const bool second = __ballot(x0 < x1) != 0ull;       // e1 precedes e0
                     const int best = second ? e1 : e0;
@@ -419,7 +419,7 @@ tac_reg_kernel(const TacRegParams p)
                     const int best = __builtin_amdgcn_readlane(ql, l);
                     const double Pb = readlane_f64(Pq, l), tb = readlane_f64(tq, l);
                     const uint64_t gone = __ballot(in && ql == best);
-                    const bool after = fmin(Pq, tb) < fmin(Pb, tq);
+                    const bool after = min_f64(Pq, tb) < min_f64(Pb, tq);
                     if (at != 0ull && (__ballot(in && !after) & ~gone) == 0ull) {
                         TT_LIST_DROP(gone)
                         TT_APPLY()
@@ -434,8 +434,8 @@ tac_reg_kernel(const TacRegParams p)
                 // b precedes a when min{P_a, Time(b)} < min{P_b, Time(a)}.  A tie is left to
                 // the general path below.
                 const int a_ = min(q0, q1), b_ = max(q0, q1);
-                const double xa = fmin(P[a_], t[b_]);
-                const double ya = fmin(P[b_], t[a_]);
+                const double xa = min_f64(P[a_], t[b_]);
+                const double ya = min_f64(P[b_], t[a_]);
                 if (__ballot(xa != ya) != 0ull) {               // (the same in every lane)
                     const int best = __ballot(xa < ya) != 0ull ? b_ : a_;
                     qm = 1; q0 = a_ + b_ - best;
@@ -471,7 +471,7 @@ tac_reg_kernel(const TacRegParams p)
                 TT_ENSURE_M(step)
                 publish_alive(step);
                 double lmin = TT_INF;
-#define TT_LMIN(k) if constexpr (k < KT) { if (pk_##k >= 0) lmin = fmin(lmin, M_##k); }
+#define TT_LMIN(k) if constexpr (k < KT) { if (pk_##k >= 0) lmin = min_f64(lmin, M_##k); }
                 TT_EACH_K(TT_LMIN)
                 const double g = wave_min_f64_dpp(lmin);
                 int cand = INT32_MAX;
@@ -516,8 +516,8 @@ tac_reg_kernel(const TacRegParams p)
                         const int a = j * 64 + __builtin_ctzll(x);
                         x &= x - 1;
                         if (best < 0) { best = a; continue; }
-                        const double xa = fmin(P[best], t[a]);
-                        const double ya = fmin(P[a], t[best]);
+                        const double xa = min_f64(P[best], t[a]);
+                        const double ya = min_f64(P[a], t[best]);
                         bool prec;
                         double mp_a = -1.0;
                         if (xa != ya) {
@@ -529,8 +529,8 @@ tac_reg_kernel(const TacRegParams p)
                             if constexpr (k < KT) {                                   \
                                 const uint32_t ra = rows[((a >> 5) * 64 + lane) * KS + k] >> (a & 31);       \
                                 const uint32_t rb2 = rows[((best >> 5) * 64 + lane) * KS + k] >> (best & 31); \
-                                if (pk_##k >= 0 && (ra & 1u)) v = fmin(v, M_##k);     \
-                                if (pk_##k >= 0 && (rb2 & 1u)) u = fmin(u, M_##k);    \
+                                if (pk_##k >= 0 && (ra & 1u)) v = min_f64(v, M_##k);     \
+                                if (pk_##k >= 0 && (rb2 & 1u)) u = min_f64(u, M_##k);    \
                             }
                             TT_EACH_K(TT_MPLUS)
                             mp_a = wave_min_f64_dpp(v);
@@ -600,13 +600,13 @@ tac_reg_kernel(const TacRegParams p)
                 const double x = k <= R ? A[k] : 0.0;
                 const double inc = wave_incl_scan_f64_dpp(x);
                 const double tot = lane63_f64(inc);
-                if (k <= R) mloc = fmax(mloc, P[k - 1] + (sfx + (tot - inc + x)));
+                if (k <= R) mloc = max_f64(mloc, P[k - 1] + (sfx + (tot - inc + x)));
                 sfx += tot;
             }
             const double m = wave_max_f64_dpp(mloc);
             if (lane == 0) {
                 const double U = sum_c + F;
-                const double L = fmax(sum_c, F);
+                const double L = max_f64(sum_c, F);
                 if (p.makespan) p.makespan[b] = m;
                 if (p.eff) p.eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
                 if (p.U) p.U[b] = U;

@@ -65,7 +65,7 @@ __device__ __forceinline__ void write_metrics(const SimLanesParams &p, int b, do
 {
     if (b >= p.B) return;
     const double U = sum_c + F;
-    const double L = fmax(sum_c, F);
+    const double L = max_f64(sum_c, F);
     p.makespan[b] = m;
     p.eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
     if (p.U) p.U[b] = U;
@@ -157,7 +157,7 @@ simulate_lanes_shared_kernel(const SimLanesParams p)
                 for (int i = 0; i < 8; ++i) {
                     if (e[i] & 0x8000) {
                         F += x[i];
-                        busy = fmax(busy, F);
+                        busy = max_f64(busy, F);
                     } else {
                         busy += x[i];
                         sum_c += x[i];
@@ -290,7 +290,7 @@ simulate_lanes_kernel(const SimLanesParams p)
                 const bool ok = (unsigned)r[i] < (unsigned)R;
                 bad |= !ok || at[i] != T(k0 + i + 1);
                 F += ok ? (double)x[i] : 0.0;
-                busy = fmax(busy, F) + a[i];
+                busy = max_f64(busy, F) + a[i];
             }
         }
         write_metrics(p, b0 + lane, busy, sum_c, F);

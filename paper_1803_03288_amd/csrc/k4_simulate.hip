@@ -119,11 +119,11 @@ simulate_kernel(const SimKernelParams p)
             double F = 0.0, busy = A[0];
             for (int k = 1; k <= R; ++k) {
                 F += Fs[k];
-                busy = fmax(busy, F) + A[k];
+                busy = max_f64(busy, F) + A[k];
             }
-            const double m = fmax(busy, F);
+            const double m = max_f64(busy, F);
             const double U = sum_c + F;
-            const double L = fmax(sum_c, F);
+            const double L = max_f64(sum_c, F);
             p.makespan[b] = m;
             p.eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
             if (p.U) p.U[b] = U;
@@ -289,13 +289,13 @@ simulate_wave_kernel(const SimWaveParams p)
             const double x = k <= R ? A[k] : 0.0;
             const double inc = wave_incl_scan_f64_dpp(x);
             const double tot = lane63_f64(inc);
-            if (k <= R) mloc = fmax(mloc, F[k - 1] + (sfx + (tot - inc + x)));
+            if (k <= R) mloc = max_f64(mloc, F[k - 1] + (sfx + (tot - inc + x)));
             sfx += tot;
         }
         const double m = wave_max_f64_dpp(mloc);
         if (lane == 0) {
             const double U = sum_c + Ftot;
-            const double L = fmax(sum_c, Ftot);
+            const double L = max_f64(sum_c, Ftot);
             p.makespan[b] = m;
             p.eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
             if (p.U) p.U[b] = U;
@@ -512,14 +512,14 @@ simulate_channels_kernel(const SimChanParams p)
         // looked up in a table of maxima over 2^j blocks (two reads), the recvs at the ends are read one by one.
         for (int i = lane; i < nb; i += 64) {
             const double2 x = *reinterpret_cast<const double2 *>(arr + 4 * i), y = *reinterpret_cast<const double2 *>(arr + 4 * i + 2);
-            tab[i] = fmax(fmax(x.x, x.y), fmax(y.x, y.y));
+            tab[i] = max_f64(max_f64(x.x, x.y), max_f64(y.x, y.y));
         }
         wave_sync();
         for (int j = 1; j < p.levels; ++j) {
             const double *prev = tab + (size_t)(j - 1) * nb;
             double *cur = tab + (size_t)j * nb;
             const int h = 1 << (j - 1);
-            for (int i = lane; i < nb; i += 64) cur[i] = fmax(prev[i], prev[min(i + h, nb - 1)]);
+            for (int i = lane; i < nb; i += 64) cur[i] = max_f64(prev[i], prev[min(i + h, nb - 1)]);
             wave_sync();
         }
 #define SC_RANGE_MAX(lo, hi)                                                              \
@@ -529,13 +529,13 @@ simulate_channels_kernel(const SimChanParams p)
                     const int e1 = min(4 * b_lo, hi_), s2 = max(4 * b_hi, e1);            \
                     _Pragma("unroll")                                                     \
                     for (int u = 0; u < 3; ++u) {                                         \
-                        if (lo_ + u < e1) m = fmax(m, arr[lo_ + u]);                      \
-                        if (s2 + u < hi_) m = fmax(m, arr[s2 + u]);                       \
+                        if (lo_ + u < e1) m = max_f64(m, arr[lo_ + u]);                      \
+                        if (s2 + u < hi_) m = max_f64(m, arr[s2 + u]);                       \
                     }                                                                     \
                     if (b_lo < b_hi) {                                                    \
                         const int j_ = 31 - __builtin_clz(b_hi - b_lo);                   \
                         const double *lv_ = tab + (size_t)j_ * nb;                        \
-                        m = fmax(m, fmax(lv_[b_lo], lv_[b_hi - (1 << j_)]));              \
+                        m = max_f64(m, max_f64(lv_[b_lo], lv_[b_hi - (1 << j_)]));              \
                     }                                                                     \
                 }
 #define SC_RHO(k)                                                                         \
@@ -598,14 +598,14 @@ simulate_channels_kernel(const SimChanParams p)
                 sfx += tot;
             }
             wave_sync();
-#define SC_RANK_MAX(k) if constexpr (k < KT) { if (k * 64 + lane < C) mloc = fmax(mloc, rho_##k + A[rank_##k]); }
+#define SC_RANK_MAX(k) if constexpr (k < KT) { if (k * 64 + lane < C) mloc = max_f64(mloc, rho_##k + A[rank_##k]); }
             SW_EACH_K(SC_RANK_MAX)
         }
         const double m = wave_max_f64_dpp(mloc);
         const double sum_c = wave_sum_f64_dpp(ct_sum);
         if (lane == 0) {
             const double U = sum_c + sum_r;
-            const double L = fmax(sum_c, last_arrival);
+            const double L = max_f64(sum_c, last_arrival);
             p.makespan[b] = m;
             p.eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
             if (p.U) p.U[b] = U;
@@ -689,8 +689,8 @@ straggler_kernel(int32_t n_groups, int32_t w, const double *__restrict__ makespa
         double mx = makespan[(size_t)g * w], mn = mx;
         for (int i = 1; i < w; ++i) {
             const double m = makespan[(size_t)g * w + i];
-            mx = fmax(mx, m);
-            mn = fmin(mn, m);
+            mx = max_f64(mx, m);
+            mn = min_f64(mn, m);
         }
         out[g] = mx > 0.0 ? (mx - mn) / mx : 0.0;
         return;
@@ -701,8 +701,8 @@ straggler_kernel(int32_t n_groups, int32_t w, const double *__restrict__ makespa
     double mx = -TT_INF, mn = TT_INF;
     for (int i = lane; i < w; i += 64) {
         const double m = makespan[(size_t)g * w + i];
-        mx = fmax(mx, m);
-        mn = fmin(mn, m);
+        mx = max_f64(mx, m);
+        mn = min_f64(mn, m);
     }
     mx = wave_max_f64_dpp(mx);
     mn = wave_min_f64_dpp(mn);
@@ -732,15 +732,15 @@ time_oracle_min_kernel(int32_t n_runs, int64_t n, bool pairs_ok, const double *_
             double2 m = reinterpret_cast<const double2 *>(runs)[i];
             for (int k = 1; k < n_runs; ++k) {
                 const double2 x = reinterpret_cast<const double2 *>(runs + (size_t)k * n)[i];
-                m.x = fmin(m.x, x.x);
-                m.y = fmin(m.y, x.y);
+                m.x = min_f64(m.x, x.x);
+                m.y = min_f64(m.y, x.y);
             }
             reinterpret_cast<double2 *>(time)[i] = m;
         }
     } else {
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
             double m = runs[i];
-            for (int k = 1; k < n_runs; ++k) m = fmin(m, runs[(size_t)k * n + i]);
+            for (int k = 1; k < n_runs; ++k) m = min_f64(m, runs[(size_t)k * n + i]);
             time[i] = m;
         }
     }

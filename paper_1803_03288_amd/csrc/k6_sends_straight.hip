@@ -130,13 +130,13 @@ sends_straight_kernel(const StraightParams p)
                     const int row = i * 8 + at_row;
                     const double u0 = run0 ? (shifted ? x[i].y : x[i].x) : 0.0, u1 = run1 ? x[i].y : 0.0;
                     double v = u0 + u1;                         // (32 lanes hold a row: the scan stops at half a wave)
-                    v += dpp_f64<0x111, 0xf>(0.0, v);
-                    v += dpp_f64<0x112, 0xf>(0.0, v);
-                    v += dpp_f64<0x114, 0xf>(0.0, v);
-                    v += dpp_f64<0x118, 0xf>(0.0, v);
+                    v += dpp0_f64<0x111>(v);
+                    v += dpp0_f64<0x112>(v);
+                    v += dpp0_f64<0x114>(v);
+                    v += dpp0_f64<0x118>(v);
                     v += dpp_f64<0x142, 0xa>(0.0, v);
                     // (what the lane before has: v less the own two would lose the low bits of a short sum before a long op)
-                    const double before = dpp_f64<0x138, 0xf>(0.0, v);
+                    const double before = dpp0_f64<0x138>(v);
                     xt[at_col * kTilePitch + row] = (at_col ? before : 0.0) + u0;
                     xt[(at_col + 1) * kTilePitch + row] = v;
                 }
@@ -187,7 +187,7 @@ sends_straight_kernel(const StraightParams p)
                         double before = xt[max(c - 1, 0) * kTilePitch], last = *at;
                         if (c == 0) before = 0.0;
                         at += 64;
-                        for (int j = 1; j < n_chk; ++j, at += 64) last = fmax(last, *at);
+                        for (int j = 1; j < n_chk; ++j, at += 64) last = max_f64(last, *at);
                         const bool late = last > base + before;
                         off |= !(todo & 0x100u) && late;
                         base = late ? last - before : base;     // (`off`: whatever, the sample is given up)
@@ -218,7 +218,7 @@ sends_straight_kernel(const StraightParams p)
                 }
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    if (q + i < q1) { add += y[i]; least = fmax(least, at[i]) + y[i]; }
+                    if (q + i < q1) { add += y[i]; least = max_f64(least, at[i]) + y[i]; }
                 }
             }
         }
@@ -239,12 +239,12 @@ sends_straight_kernel(const StraightParams p)
             if (mine && !off && !given_up) {
                 double busy = 0.0, sum_s = 0.0;
                 for (int w = 0; w < 4; ++w) {
-                    busy = fmax(busy + red[w * 64 + lane], red[(4 + w) * 64 + lane]);
+                    busy = max_f64(busy + red[w * 64 + lane], red[(4 + w) * 64 + lane]);
                     sum_s += red[w * 64 + lane];
                 }
-                const double m = fmax(fmax(base, busy), sum_r);
+                const double m = max_f64(max_f64(base, busy), sum_r);
                 const double U = sum_c + sum_r + sum_s;
-                const double Lb = fmax(fmax(sum_c, sum_r), sum_s);
+                const double Lb = max_f64(max_f64(sum_c, sum_r), sum_s);
                 p.makespan[b] = m;
                 p.eff[b] = (U == Lb) ? 1.0 : (U - m) / (U - Lb);
                 if (p.U) p.U[b] = U;
