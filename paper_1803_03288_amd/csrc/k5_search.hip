@@ -12,23 +12,34 @@
 // row, A_k = class time released by transfer k, makespan = max_k (F_k + sum_{k' >= k} A_k').
 //
 // One wave per sample.  The op_time row is read once (class totals); after that a move touches
-// registers and LDS only.  Lane l owns classes l, l + 64, ... (their totals and kappa) and the
-// positions l, l + 64, ... of the order (the transfer time at that position).  A move changes
+// registers and LDS only.  A lane owns consecutive classes (their totals and kappa) and consecutive
+// positions of the order (the transfer time at that position), so that a sum over positions is a few
+// adds per lane and one scan over the lanes, and classes that are released together (neighbours, mostly)
+// are added up in the lane before they go to A.  A move changes
 // kappa of few classes: when the recv at the earlier position (x) and the one at the later
 // position (y) change places, a class with x in its row gets max(kappa, later position); a class
 // with y and without x whose kappa was y's position needs its maximum taken again, for which the wave
 // looks at 64 positions below at once; every other class keeps its kappa.  Which classes hold a recv is
-// one word per 64 classes, in LDS, read by all lanes and used as a scalar.  A and the two scans are then formed afresh from the registers, so every makespan is the one a full
-// evaluation of that order gives.
+// one word per slot of classes, in LDS, read by all lanes and used as a scalar.  A and the two scans
+// are then formed afresh from the registers, so every makespan is the one a full evaluation of that
+// order gives.
 //
 // Most moves are turned down without that evaluation.  Let k* be a position where the current
 // makespan is attained, m_cur = F_k* + S_k* (S_k = class time with kappa >= k).  The makespan after
 // the move is at least F'_k* + S'_k*.  Exchanging positions lo < hi leaves F_k and S_k as they are
-// for k <= lo and for k > hi + 1, so a move with k* outside lo + 1 .. hi + 1 cannot help (decided
-// for 64 moves at a time, one per lane).  Otherwise F_k* changes by Time(y) - Time(x) when k* <= hi, S_k* gains the
+// for k <= lo and for k > hi + 1, so a move with k* outside lo + 1 .. hi + 1 cannot help, nor does
+// one that makes F_k* longer by as much as the classes released at hi + 1, which is the most that S_k*
+// can lose (both decided for 64 moves at a time, one per lane; of 1 024 moves on resnet50 162 pass the
+// first and 79 both).  Otherwise F_k* changes by Time(y) - Time(x) when k* <= hi, S_k* gains the
 // classes with x whose kappa was below k* and loses at most the classes that need their maximum
 // taken again; when that sum is not negative the move cannot help either (one wave sum, no LDS
-// write).  Only the remaining moves are evaluated.
+// write).  Only the remaining moves, 63 there, are evaluated; 52 are kept.
+//
+// Bound by the issue of vector and scalar instructions, five or six waves per SIMD.  resnet50, 16 384 samples, 1 024 moves:
+// 1 675 us with positions and classes l, l + 64, ... of a lane and without the second test (41 000 vector instructions per sample,
+// 3.4 bank-conflict cycles per LDS instruction), 962 us now (24 000; 1.2).  inception3: 5.59 -> 3.04 ms.
+#include <algorithm>
+
 #include "device_utils.h"
 #include "internal.h"
 
@@ -60,24 +71,26 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t x)      // the same in 
 
 #define OS_EACH(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7)
 
-// T slots per lane, for classes (64 T >= C) and for positions (64 T >= R)
+// T slots per lane for classes (64 T >= C), and D of consecutive positions (64 D >= R)
 template <int T>
 __global__ void __launch_bounds__(64 * kSearchWaves)
 order_search_kernel(const SearchParams p)
 {
     extern __shared__ double smem[];
+    constexpr int D = T | 1;                                    // (odd: what lanes read of their positions is in different banks)
     const int R = p.R, C = p.C, N = p.N, W = p.W;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint64_t *holders = reinterpret_cast<uint64_t *>(smem);     // [R][T] the classes with recv r: bit l of word k for (k, l); shared
     char *mine = reinterpret_cast<char *>(smem) + p.rows_bytes + (size_t)wave * p.wave_bytes;
     double *t = reinterpret_cast<double *>(mine);           // [R]   Time(recv)
     double *A = t + R;                                      // [R+1] class time by kappa
-    double *csum = t;                                       // [64 T] class totals while they are summed (fa_len doubles from t on)
-    uint16_t *ordl = reinterpret_cast<uint16_t *>(t + p.fa_len);     // [R] the order being tried
-    uint16_t *pos = ordl + R + (R & 1);                     // [levels][R] level 0: 1-based position of every recv;
+    double *Acur = A + (R + 1);                             // [R+1] the same for the order kept
+    double *csum = A;                                       // [64 T] class totals while they are summed
+    uint16_t *pos = reinterpret_cast<uint16_t *>(A);        // [levels][R] level 0: 1-based position of every recv;
                                                             // level j: maxima over [i, min(i + 2^j, R)) (start order only)
+    uint16_t *ordl = reinterpret_cast<uint16_t *>(t + R + p.fa_len);     // [R] the order being tried
     for (int i = wave; i < W * T; i += kSearchWaves) {
-        const int w = i / T, k = i % T, c = k * 64 + lane;
+        const int w = i / T, k = i % T, c = lane * T + k;
         const uint64_t x = c < C ? p.cls_depT[(size_t)w * p.Cpad + c] : 0ull;
         for (int j = 0; j < 64 && w * 64 + j < R; ++j) {
             const uint64_t has = __ballot((x >> j) & 1ull);
@@ -98,9 +111,10 @@ order_search_kernel(const SearchParams p)
         wave_sync();
         class_totals(csum, ot, p.col_cls, N, lane);
         wave_sync();
-#define OS_DECL(k) double ct_##k = 0.0, xs_##k = 0.0; int kap_##k = 0, kn_##k = 0;
+#define OS_DECL(k) double ct_##k = 0.0; int kap_##k = 0, kn_##k = 0;
         OS_EACH(OS_DECL)
-#define OS_TOTAL(k) if constexpr (k < T) { ct_##k = csum[k * 64 + lane]; }
+        double xs[D];                           // transfer times at the lane's positions
+#define OS_TOTAL(k) if constexpr (k < T) { ct_##k = csum[lane * T + k]; }
         OS_EACH(OS_TOTAL)
         double ct_sum = 0.0;
 #define OS_SUM(k) if constexpr (k < T) { ct_sum += ct_##k; }
@@ -116,16 +130,9 @@ order_search_kernel(const SearchParams p)
             ordl[r] = (uint16_t)((unsigned)o < (unsigned)R ? o : 0);     // an invalid entry is never used as an index
         }
         wave_sync();
-#define OS_PLACE(k)                                                                       \
-        if constexpr (k < T) {                                                            \
-            const int s = k * 64 + lane;                                                  \
-            if (s < R) {                                                                  \
-                const int r = ordl[s];                                                    \
-                pos[r] = (uint16_t)(s + 1);                                               \
-                xs_##k = t[r];                                                            \
-            }                                                                             \
-        }
-        OS_EACH(OS_PLACE)
+        for (int i = lane; i < R; i += 64) pos[ordl[i]] = (uint16_t)(i + 1);
+#pragma unroll
+        for (int k = 0; k < D; ++k) xs[k] = lane * D + k < R ? t[ordl[lane * D + k]] : 0.0;
         wave_sync();
 
         // ---- kappa of the start order: range maxima over the runs of every class row ----
@@ -138,7 +145,7 @@ order_search_kernel(const SearchParams p)
         }
 #define OS_KAPPA0(k)                                                                      \
         if constexpr (k < T) {                                                            \
-            const int c = k * 64 + lane;                                                  \
+            const int c = lane * T + k;                                                   \
             if (c < C) {                                                                  \
                 const int rend = p.run_ptr[c + 1];                                        \
                 int m = 0;                                                                \
@@ -152,6 +159,7 @@ order_search_kernel(const SearchParams p)
             }                                                                             \
         }
         OS_EACH(OS_KAPPA0)
+        wave_sync();                        // (A takes the place of the positions)
 
         double m_cur = 0.0;
         int n_acc = 0;
@@ -160,6 +168,13 @@ order_search_kernel(const SearchParams p)
         int base = -64;                     // first move of the chunk in mv_lo / mv_hi
         int mv_lo = 0, mv_hi = -1;          // lane i: the positions of move base + i; mv_hi < 0: not an exchange
         unsigned long long todo = 0;        // moves of the chunk that are still to be looked at
+        // Which of the moves may help, as far as a lane sees it by itself: k* between their positions, and what F and S lose there
+        // is more than what F gains (S loses no more than the classes released at the later position).
+        const auto worth = [&]() {
+            bool ok = mv_hi >= 0 && kstar > mv_lo && kstar <= mv_hi + 1;
+            if (ok) ok = (kstar <= mv_hi ? t[ordl[mv_hi]] - t[ordl[mv_lo]] : 0.0) - Acur[mv_hi + 1] < 0.0;
+            return __ballot(ok);
+        };
         bool first = true;                  // the start order is evaluated before any move
         for (;;) {
             int lo = 0, hi = 0, x = 0, y = 0, cur = 0;
@@ -173,7 +188,7 @@ order_search_kernel(const SearchParams p)
                     const bool ok = (unsigned)pa < (unsigned)R && (unsigned)pb < (unsigned)R && pa != pb;
                     mv_lo = min(pa, pb);
                     mv_hi = ok ? max(pa, pb) : -1;
-                    todo = __ballot(mv_hi >= 0 && kstar > mv_lo && kstar <= mv_hi + 1);
+                    todo = worth();
                 }
                 if (todo == 0) break;       // no move left
                 cur = __builtin_ctzll(todo);
@@ -230,49 +245,50 @@ order_search_kernel(const SearchParams p)
                 }
                 OS_EACH(OS_REDO)
                 // the transfer times at the two positions change places
-#define OS_SWAP_X(k, to_lo, to_hi)                                                        \
-                if constexpr (k < T) {                                                    \
-                    if (k * 64 + lane == lo) xs_##k = to_lo;                              \
-                    if (k * 64 + lane == hi) xs_##k = to_hi;                              \
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    xs[k] = lane * D + k == lo ? ty : xs[k];
+                    xs[k] = lane * D + k == hi ? tx : xs[k];
                 }
-#define OS_SWAP_FWD(k) OS_SWAP_X(k, ty, tx)
-                OS_EACH(OS_SWAP_FWD)
             }
 
             // ---- A by kappa; F; suffix sums of A; makespan ----
             for (int j = lane; j <= R; j += 64) A[j] = 0.0;
             wave_sync();
-#define OS_RELEASE(k) if constexpr (k < T) { if (k * 64 + lane < C) atomicAdd(&A[kn_##k], ct_##k); }
+            // (classes next to each other tend to be released together: those of a lane are added up first, since adds of several
+            // lanes to one place are served one after the other)
+            double together = ct_0;
+#define OS_RELEASE(k)                                                                     \
+            if constexpr (k > 0 && k < T) {                                               \
+                if (kn_##k != OS_KN(k - 1)) {                                             \
+                    atomicAdd(&A[OS_KN(k - 1)], together);                                \
+                    together = 0.0;                                                       \
+                }                                                                         \
+                together += ct_##k;                                                       \
+            }
+#define OS_KN(k) ((k) == 0 ? kn_0 : (k) == 1 ? kn_1 : (k) == 2 ? kn_2 : (k) == 3 ? kn_3 : (k) == 4 ? kn_4 : (k) == 5 ? kn_5 : (k) == 6 ? kn_6 : kn_7)
             OS_EACH(OS_RELEASE)
-            double fc = 0.0;
-#define OS_F(k)                                                                           \
-            double F_##k = 0.0;                                                           \
-            if constexpr (k < T) {                                                        \
-                if (k * 64 < R) {                                                         \
-                    const double inc = wave_incl_scan_f64_dpp(xs_##k);                    \
-                    F_##k = fc + inc;                                                     \
-                    fc += lane63_f64(inc);                                                \
-                }                                                                         \
-            }
-            OS_EACH(OS_F)
+            if (lane * T < C) atomicAdd(&A[OS_KN(T - 1)], together);    // (what the last lane has beyond C is nothing, at kappa 0)
+            // prefix sums of the transfer times, suffix sums of the class times: over the lane's positions, then over the lanes
+            double F[D], S[D];
+            F[0] = xs[0];
+#pragma unroll
+            for (int k = 1; k < D; ++k) F[k] = F[k - 1] + xs[k];
+            const double F_before = dpp0_f64<0x138>(wave_incl_scan_f64_dpp(F[D - 1]));
             wave_sync();
-            double sfx = 0.0, mloc = sum_c;                   // k = 0: F_0 + S_0 = all class time
-            int kb = 0;                                       // where this lane's maximum is attained
-#define OS_SUFFIX(kk)                                                                     \
-            if constexpr (7 - kk < T) {                                                   \
-                constexpr int j = 7 - kk;                                                 \
-                if (j * 64 < R) {                                                         \
-                    const int k = j * 64 + lane + 1;          /* 1 <= k <= R handled here */ \
-                    const double a = k <= R ? A[k] : 0.0;                                 \
-                    const double inc = wave_incl_scan_f64_dpp(a);                         \
-                    const double tot = lane63_f64(inc);                                   \
-                    const double cand = OS_F_OF(j) + (sfx + (tot - inc + a));             \
-                    if (k <= R && cand > mloc) { mloc = cand; kb = k; }                   \
-                    sfx += tot;                                                           \
-                }                                                                         \
+#pragma unroll
+            for (int k = D - 1; k >= 0; --k) {
+                S[k] = lane * D + k < R ? A[lane * D + k + 1] : 0.0;
+                if (k < D - 1) S[k] += S[k + 1];
             }
-#define OS_F_OF(j) (j == 0 ? F_0 : j == 1 ? F_1 : j == 2 ? F_2 : j == 3 ? F_3 : j == 4 ? F_4 : j == 5 ? F_5 : j == 6 ? F_6 : F_7)
-            OS_EACH(OS_SUFFIX)
+            const double S_incl = wave_incl_scan_f64_dpp(S[0]), S_after = lane63_f64(S_incl) - S_incl;
+            double mloc = sum_c;                              // k = 0: F_0 + S_0 = all class time
+            int kb = 0;                                       // where this lane's maximum is attained
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                const double cand = (F_before + F[k]) + (S_after + S[k]);
+                if (lane * D + k < R && cand > mloc) { mloc = cand; kb = lane * D + k + 1; }
+            }
             const double m = wave_max_f64_dpp(mloc);
 
 #define OS_KEEP(k) if constexpr (k < T) { kap_##k = kn_##k; }
@@ -281,6 +297,7 @@ order_search_kernel(const SearchParams p)
                 const unsigned long long at = __ballot(mloc == m);
                 kstar = at ? __builtin_amdgcn_readlane(kb, __builtin_ctzll(at)) : 0;
                 OS_EACH(OS_KEEP)
+                for (int j = lane; j <= R; j += 64) Acur[j] = A[j];
                 if (first) {
                     if (lane == 0 && p.start_makespan) p.start_makespan[b] = m;
                     first = false;
@@ -288,12 +305,16 @@ order_search_kernel(const SearchParams p)
                     ++n_acc;
                     // the moves after this one, under the new k*
                     const unsigned long long later = cur == 63 ? 0ull : ~0ull << (cur + 1);
-                    todo = __ballot(mv_hi >= 0 && kstar > mv_lo && kstar <= mv_hi + 1) & later;
+                    wave_sync();
+                    todo = worth() & later;
                 }
             } else {
                 const double tx = t[x], ty = t[y];
-#define OS_SWAP_BACK(k) OS_SWAP_X(k, tx, ty)
-                OS_EACH(OS_SWAP_BACK)
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    xs[k] = lane * D + k == lo ? tx : xs[k];
+                    xs[k] = lane * D + k == hi ? ty : xs[k];
+                }
                 wave_sync();
                 if (lane == 0) { ordl[lo] = (uint16_t)x; ordl[hi] = (uint16_t)y; }
                 wave_sync();
@@ -314,9 +335,10 @@ static hipError_t launch_search_t(SearchParams &p, const Dag &d, hipStream_t s)
     int levels = 1;
     while ((1 << levels) <= d.R) ++levels;            // floor(log2 R) + 1 levels of the table
     p.levels = levels;
-    const size_t fa = (size_t)2 * d.R + 1 > (size_t)64 * T ? (size_t)2 * d.R + 1 : (size_t)64 * T;
+    // (one after the other in the same place: class totals; positions and their maxima; A and what it was)
+    const size_t fa = std::max(std::max((size_t)64 * T, ((size_t)levels * d.R * 2 + 7) / 8), (size_t)2 * d.R + 2);
     p.fa_len = (int32_t)fa;
-    size_t wave_bytes = fa * 8 + ((size_t)d.R + (d.R & 1)) * 2 + (size_t)levels * d.R * 2;
+    size_t wave_bytes = ((size_t)d.R + fa) * 8 + ((size_t)d.R + (d.R & 1)) * 2;
     wave_bytes = (wave_bytes + 15) & ~(size_t)15;
     const size_t rows_bytes = (((size_t)d.R * T * 8) + 15) & ~(size_t)15;
     const size_t lds = rows_bytes + wave_bytes * kSearchWaves;
