@@ -1277,6 +1277,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     cls.add(&d->d_cls_isum, isum);      // index sums stay below 2^20
     d->max_members = 0;
     for (int32_t c = 0; c < d->C; ++c) d->max_members = std::max(d->max_members, cls_ptr[c + 1] - cls_ptr[c]);
+    d->n_runs = (int32_t)run_lo.size();
     cls.add(&d->d_run_ptr, run_ptr);
     cls.add(&d->d_run_lo, run_lo);
     cls.add(&d->d_run_hi, run_hi);
@@ -1877,7 +1878,6 @@ try {
         set_error("%d recvs and %d classes: the several-channel simulation handles at most 512 of each", d->R, d->C);
         return TICTAC_ERR_UNSUPPORTED;
     }
-    HIP_TRY(launch_check_orders(*d, B, order, order_stride, s));
     // the channel table goes to the device through a staging block of the handle
     HIP_TRY(ensure_chan_table(d, channel_of_recv, s));
     const hipError_t e = launch_simulate_channels(*d, a, n_channels, d->d_chan, s);

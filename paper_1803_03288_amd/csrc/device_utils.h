@@ -116,6 +116,16 @@ __device__ __forceinline__ double wave_incl_scan_f64_dpp(double v)
     v += dpp_f64<0x143, 0xc>(0.0, v);
     return v;
 }
+__device__ __forceinline__ int wave_incl_scan_i32_dpp(int v)
+{
+    v += dpp0_i32<0x111>(v);
+    v += dpp0_i32<0x112>(v);
+    v += dpp0_i32<0x114>(v);
+    v += dpp0_i32<0x118>(v);
+    v += dpp_i32<0x142, 0xa>(0, v);
+    v += dpp_i32<0x143, 0xc>(0, v);
+    return v;
+}
 // Reductions are read from lane 63, which sees its own row, the total of row 2 by the first broadcast and that of rows 0 and 1,
 // in lane 31 by then, by the second.  (What the broadcasts leave in rows 0 and 2 is not looked at, so no row is masked out.)  Sums
 // are added up in the order of the scan above; minima and maxima go round the rows, where every lane has a source.

@@ -138,6 +138,7 @@ struct Dag {
     int32_t *d_run_ptr = nullptr;   // [C+1]
     int32_t *d_run_lo = nullptr;    // [n_runs]
     int32_t *d_run_hi = nullptr;    // [n_runs]
+    int32_t n_runs = 0;
     int32_t max_members = 0;        // largest class (ops)
 
     // Tables of the bit-sliced TAC kernel (graphs with many classes; NULL / 0 otherwise).  Classes are

@@ -378,13 +378,14 @@ static hipError_t launch_sim_t(const SimKernelParams &p, int grid, size_t lds, h
 // device that never idles while an op is ready finishes at
 //     max( latest arrival,  max over classes c of  rho_c + sum of the times of the classes with rho >= rho_c ).
 // One wave per sample: arrivals by one wave scan per channel, rho by range maxima over the
-// arrival array (runs of the class rows; lane l owns classes l, l + 64, ...), the last step by ranking the
+// arrival array (runs of the class rows), the last step by ranking the
 // release dates among the arrivals: on one channel the arrivals increase along the order, so the number of
 // arrivals up to rho is one binary search per channel; the class times are added up by that rank and one
 // suffix sum over the ranks gives the second term for every class.
 struct SimChanParams {
     int32_t B, R, C, N, n_waves, wave_bytes, levels, n_channels, chan_bytes;
-    int32_t nb, x_doubles;      // blocks of four recvs; doubles shared by the transfer times and the table of block maxima
+    int32_t nb, arr_doubles;    // blocks of four recvs; doubles for the arrivals
+    int32_t cls_lane, cls_slot; // class of lane l's k-th slot: l * cls_lane + k * cls_slot
     const int32_t *col_cls, *run_ptr, *run_lo, *run_hi;
     const int32_t *chan;        // [R] channel of every recv, 0 <= chan < n_channels <= 64
     const int32_t *order;
@@ -392,14 +393,24 @@ struct SimChanParams {
     const void *op_time, *recv_time;    // float64, or float32 when f32 is set
     int32_t f32;
     double *makespan, *eff, *U, *L, *S;
+    int32_t *bad_order;         // raised when an order is no permutation
 };
 
-// (three waves per SIMD: 168 registers per lane; with a cap of 128 the kernel spills and is slower)
+// D consecutive positions of the order per lane, so that a sum over positions is a few adds per lane and one scan over the lanes.
+// The classes of a lane are consecutive too where rows are short: classes that are released together (neighbours, mostly) are
+// then added up in the lane.  Where rows have many runs they are l, l + 64, ...: lanes wait for the longest row of a slot, and
+// neighbours have rows of similar length.  (More than two runs per row on average; resnet50, less than one, four channels: 257 us
+// with consecutive classes, 343 without; 24 x 20 layered ops, 300 recvs: 6.9 and 6.2 ms.)
+// The order is checked on the way.  65 536 samples, four channels, with the check: inception3 1 188 -> 1 000 us (a scan per channel
+// and 64 positions before, 26 % more vector instructions), resnet50 357 -> 257 us.  Waves wait for the op_time row two thirds of
+// their time; the registers (an occupancy bound per KT: where spills of a few words cost less than a wave) and LDS, which holds
+// everything but the arrivals in one place, say how many there are.
 template <int KT>
-__global__ void __launch_bounds__(256, 3)
+__global__ void __launch_bounds__(256, KT <= 3 ? 5 : KT <= 4 ? 4 : 3)
 simulate_channels_kernel(const SimChanParams p)
 {
     extern __shared__ double smem[];
+    constexpr int D = KT | 1;               // (odd: what lanes read of their positions is in different banks)
     const int R = p.R, C = p.C, N = p.N;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t *chan_l = reinterpret_cast<int32_t *>(smem);    // [R] channel of every recv, shared by the waves
@@ -408,10 +419,13 @@ simulate_channels_kernel(const SimChanParams p)
     double *mine = reinterpret_cast<double *>(reinterpret_cast<char *>(smem) + p.chan_bytes + (size_t)wave * p.wave_bytes);
     const int Rp = (R + 3) & ~3, nb = p.nb;
     double *arr = mine;                     // [Rp] arrival of recv r, zero beyond R
-    double *t = arr + Rp;                   // [R]  Time(recv), until the arrivals are known; then
+    // in one place, one after the other:
+    double *csum = arr + p.arr_doubles;     // [64 KT] the class totals while they are summed
+    double *t = csum;                       // [R]  Time(recv), until the arrivals are known
+    int32_t *place = reinterpret_cast<int32_t *>(t);        // [R] the position of every recv
     double *tab = t;                        // [levels][nb] level j: maxima of the arrivals over the blocks [i, i + 2^j) of four recvs
-    double *csum = t + p.x_doubles;         // [64 KT] the class totals while they are summed; then
-    double *lists = csum;                   // [R] the arrivals channel by channel, in the order's sequence
+    double *lists = t;                      // [R] the arrivals channel by channel, in the order's sequence
+    const int cls_lane = p.cls_lane, cls_slot = p.cls_slot;
     for (int r = threadIdx.x; r < R; r += blockDim.x) chan_l[r] = p.chan[r];
     __syncthreads();
     if (wave == 0) {
@@ -426,22 +440,21 @@ simulate_channels_kernel(const SimChanParams p)
         clen[lane] = n_mine;
     }
     __syncthreads();
-    const uint64_t lanes_below = (1ull << lane) - 1ull;
-    // the first two runs of every class row (lo | hi << 16), fixed for the launch; longer rows read the rest
-#define SC_RUNS(k)                                                                        \
-    int rb_##k = 0, re_##k = 0;                                                           \
-    unsigned ra_##k = 0, rc_##k = 0;                                                      \
-    if constexpr (k < KT) {                                                               \
-        const int c = k * 64 + lane;                                                      \
-        if (c < C) {                                                                      \
-            rb_##k = p.run_ptr[c];                                                        \
-            re_##k = p.run_ptr[c + 1];                                                    \
-            if (re_##k > rb_##k) ra_##k = (unsigned)p.run_lo[rb_##k] | ((unsigned)p.run_hi[rb_##k] << 16);              \
-            if (re_##k > rb_##k + 1) rc_##k = (unsigned)p.run_lo[rb_##k + 1] | ((unsigned)p.run_hi[rb_##k + 1] << 16);  \
-        }                                                                                 \
+    // the first two runs of every class row (lo | hi << 10) and, above the first, their number; fixed for the launch, as are the
+    // further ones, which stay in memory
+    uint32_t ra[KT], rc[KT];
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+        const int c = lane * cls_lane + k * cls_slot;
+        ra[k] = rc[k] = 0;
+        if (c < C) {
+            const int q = p.run_ptr[c], n = p.run_ptr[c + 1] - q;
+            if (n > 0) ra[k] = (uint32_t)p.run_lo[q] | (uint32_t)p.run_hi[q] << 10 | (uint32_t)n << 20;
+            if (n > 1) rc[k] = (uint32_t)p.run_lo[q + 1] | (uint32_t)p.run_hi[q + 1] << 10;
+        }
     }
-    SW_EACH_K(SC_RUNS)
 
+    bool bad = false;
     const int gwave = blockIdx.x * (blockDim.x >> 6) + wave;
     for (int b = gwave; b < p.B; b += p.n_waves) {
         const TimeRow rt = time_row(p.recv_time, (size_t)b * R, p.f32 != 0);
@@ -449,60 +462,77 @@ simulate_channels_kernel(const SimChanParams p)
         const int32_t *ord = p.order + (size_t)b * p.order_stride;
         wave_sync();
 
-        // ---- transfer times and the order are requested first, into registers (position slot q:
-        // q * 64 + lane), then the op_time row ----
-#define SC_REQUEST(q)                                                                     \
-        double rt_##q = 0.0;                                                              \
-        int or_##q = -1;                                                                  \
-        if constexpr (q < KT) {                                                           \
-            if (q * 64 + lane < R) { rt_##q = rt[q * 64 + lane]; or_##q = ord[q * 64 + lane]; } \
-        }
-        SW_EACH_K(SC_REQUEST)
+        // ---- transfer times and the order are requested first, into registers, then the op_time row ----
+        double rt_q[KT];
+        int at[D];                          // the recvs at the lane's positions
+#pragma unroll
+        for (int q = 0; q < KT; ++q) rt_q[q] = q * 64 + lane < R ? rt[q * 64 + lane] : 0.0;
+#pragma unroll
+        for (int k = 0; k < D; ++k) at[k] = lane * D + k < R ? ord[lane * D + k] : -1;
         for (int c = lane; c < 64 * KT; c += 64) csum[c] = 0.0;
         wave_sync();
         class_totals(csum, ot, p.col_cls, N, lane);
         wave_sync();
-#define SC_DECL(k) double ct_##k = 0.0, rho_##k = 0.0;
-        SW_EACH_K(SC_DECL)
-#define SC_TOTAL(k) if constexpr (k < KT) { ct_##k = csum[k * 64 + lane]; }
-        SW_EACH_K(SC_TOTAL)
-#define SC_TIMES(q) if constexpr (q < KT) { if (q * 64 + lane < R) { t[q * 64 + lane] = rt_##q; arr[q * 64 + lane] = 0.0; } }
-        SW_EACH_K(SC_TIMES)
+        double ct[KT];
+#pragma unroll
+        for (int k = 0; k < KT; ++k) ct[k] = csum[lane * cls_lane + k * cls_slot];
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < KT; ++q)
+            if (q * 64 + lane < R) { t[q * 64 + lane] = rt_q[q]; arr[q * 64 + lane] = 0.0; }
         if (R + lane < Rp) arr[R + lane] = 0.0;
         wave_sync();
 
         // ---- arrivals: per channel, prefix sums over the positions of the order ----
-        double carry = 0.0;                 // lane c: time queued on channel c so far
-        int queued = 0;                     // lane c: recvs queued on channel c so far
+        double x[D], a[D];
+        int of[D];                          // recv | channel << 10 | number among those of the channel << 16, -1: none
         double sum_r = 0.0;
-#define SC_ARRIVE(q)                                                                      \
-        if constexpr (q < KT) {                                                           \
-            if (q * 64 < R) {                                                             \
-                const int r = or_##q;                                                     \
-                const bool ok = (unsigned)r < (unsigned)R;  /* an invalid entry is skipped, never dereferenced */ \
-                const int cl = ok ? chan_l[r] : -1;                                       \
-                const double x = ok ? t[r] : 0.0;                                         \
-                double a = 0.0;                                                           \
-                int nth = 0;                        /* this recv is the nth of its channel */ \
-                for (int c = 0; c < p.n_channels; ++c) {                                  \
-                    const double inc = wave_incl_scan_f64_dpp(cl == c ? x : 0.0);         \
-                    const double before = readlane_f64(carry, c);                         \
-                    if (cl == c) a = before + inc;                                        \
-                    if (lane == c) carry += lane63_f64(inc);                              \
-                    const uint64_t on_c = __ballot(cl == c);                              \
-                    const int n_before = __builtin_amdgcn_readlane(queued, c);            \
-                    if (cl == c) nth = n_before + __popcll(on_c & lanes_below);           \
-                    if (lane == c) queued += __popcll(on_c);                              \
-                }                                                                         \
-                if (ok) {                                                                 \
-                    arr[r] = a;                                                           \
-                    /* (an order that is no permutation cannot write past the channel's share) */ \
-                    if (nth < clen[cl]) lists[coff[cl] + nth] = a;                        \
-                }                                                                         \
-                sum_r += x;                                                               \
-            }                                                                             \
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            const bool ok = (unsigned)at[k] < (unsigned)R;      // an invalid entry is skipped, never dereferenced
+            of[k] = ok ? at[k] | chan_l[at[k]] << 10 : -1;
+            x[k] = ok ? t[at[k]] : 0.0;
+            a[k] = 0.0;
+            sum_r += x[k];
         }
-        SW_EACH_K(SC_ARRIVE)
+        wave_sync();
+        // (the check of the order: every recv is at the place that it has been given last)
+#pragma unroll
+        for (int k = 0; k < D; ++k)
+            if ((unsigned)at[k] < (unsigned)R) place[at[k]] = lane * D + k;
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < D; ++k)
+            if (lane * D + k < R) bad |= (unsigned)at[k] >= (unsigned)R || place[at[k]] != lane * D + k;
+        double carry = 0.0;                 // lane c: time queued on channel c
+        int queued = 0;                     // lane c: recvs queued on channel c
+        for (int c = 0; c < p.n_channels; ++c) {
+            double run = 0.0;
+            int n = 0;
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                run += ((of[k] >> 10) & 63) == c && of[k] >= 0 ? x[k] : 0.0;
+                n += ((of[k] >> 10) & 63) == c && of[k] >= 0 ? 1 : 0;
+            }
+            const double incl = wave_incl_scan_f64_dpp(run);
+            const int n_incl = wave_incl_scan_i32_dpp(n);
+            if (lane == c) {
+                carry = lane63_f64(incl);
+                queued = __builtin_amdgcn_readlane(n_incl, 63);
+            }
+            run = dpp0_f64<0x138>(incl);                        // (what the lanes before have)
+            n = dpp0_i32<0x138>(n_incl);
+#pragma unroll
+            for (int k = 0; k < D; ++k)
+                if (((of[k] >> 10) & 63) == c && of[k] >= 0) {
+                    run += x[k];
+                    a[k] = run;
+                    of[k] |= n++ << 16;
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < D; ++k)
+            if (of[k] >= 0) arr[of[k] & 1023] = a[k];
         sum_r = wave_sum_f64_dpp(sum_r);
         const double last_arrival = wave_max_f64_dpp(lane < p.n_channels ? carry : 0.0);   // = largest channel sum
         wave_sync();
@@ -511,8 +541,8 @@ simulate_channels_kernel(const SimChanParams p)
         // A run [lo, hi) is at most three recvs, whole blocks of four, and at most three recvs: the blocks are
         // looked up in a table of maxima over 2^j blocks (two reads), the recvs at the ends are read one by one.
         for (int i = lane; i < nb; i += 64) {
-            const double2 x = *reinterpret_cast<const double2 *>(arr + 4 * i), y = *reinterpret_cast<const double2 *>(arr + 4 * i + 2);
-            tab[i] = max_f64(max_f64(x.x, x.y), max_f64(y.x, y.y));
+            const double2 u = *reinterpret_cast<const double2 *>(arr + 4 * i), v = *reinterpret_cast<const double2 *>(arr + 4 * i + 2);
+            tab[i] = max_f64(max_f64(u.x, u.y), max_f64(v.x, v.y));
         }
         wave_sync();
         for (int j = 1; j < p.levels; ++j) {
@@ -522,87 +552,108 @@ simulate_channels_kernel(const SimChanParams p)
             for (int i = lane; i < nb; i += 64) cur[i] = max_f64(prev[i], prev[min(i + h, nb - 1)]);
             wave_sync();
         }
-#define SC_RANGE_MAX(lo, hi)                                                              \
-                {                                                                         \
-                    const int lo_ = (lo), hi_ = (hi);                                     \
-                    const int b_lo = (lo_ + 3) >> 2, b_hi = hi_ >> 2;                     \
-                    const int e1 = min(4 * b_lo, hi_), s2 = max(4 * b_hi, e1);            \
-                    _Pragma("unroll")                                                     \
-                    for (int u = 0; u < 3; ++u) {                                         \
-                        if (lo_ + u < e1) m = max_f64(m, arr[lo_ + u]);                      \
-                        if (s2 + u < hi_) m = max_f64(m, arr[s2 + u]);                       \
-                    }                                                                     \
-                    if (b_lo < b_hi) {                                                    \
-                        const int j_ = 31 - __builtin_clz(b_hi - b_lo);                   \
-                        const double *lv_ = tab + (size_t)j_ * nb;                        \
-                        m = max_f64(m, max_f64(lv_[b_lo], lv_[b_hi - (1 << j_)]));              \
-                    }                                                                     \
+        const auto range_max = [&](double m, int lo, int hi) {
+            const int b_lo = (lo + 3) >> 2, b_hi = hi >> 2;
+            const int e1 = min(4 * b_lo, hi), s2 = max(4 * b_hi, e1);
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                if (lo + u < e1) m = max_f64(m, arr[lo + u]);
+                if (s2 + u < hi) m = max_f64(m, arr[s2 + u]);
+            }
+            if (b_lo < b_hi) {
+                const int j = 31 - __builtin_clz(b_hi - b_lo);
+                const double *lv = tab + (size_t)j * nb;
+                m = max_f64(m, max_f64(lv[b_lo], lv[b_hi - (1 << j)]));
+            }
+            return m;
+        };
+        double rho[KT];
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {
+            double m = 0.0;
+            const int n = (int)(ra[k] >> 20);
+            if (n > 0) m = range_max(m, (int)(ra[k] & 1023u), (int)((ra[k] >> 10) & 1023u));
+            if (n > 1) m = range_max(m, (int)(rc[k] & 1023u), (int)(rc[k] >> 10));
+            if (n > 2) {
+                const int q = p.run_ptr[lane * cls_lane + k * cls_slot];
+                int lo = p.run_lo[q + 2], hi = p.run_hi[q + 2];
+                for (int i = 3;; ++i) {             // (the next run on its way)
+                    const int next = q + min(i, n - 1), lo1 = p.run_lo[next], hi1 = p.run_hi[next];
+                    m = range_max(m, lo, hi);
+                    if (i >= n) break;
+                    lo = lo1;
+                    hi = hi1;
                 }
-#define SC_RHO(k)                                                                         \
-        if constexpr (k < KT) {                                                           \
-            const int c = k * 64 + lane;                                                  \
-            if (c < C) {                                                                  \
-                double m = 0.0;                                                           \
-                if (re_##k > rb_##k) SC_RANGE_MAX((int)(ra_##k & 0xffffu), (int)(ra_##k >> 16))         \
-                if (re_##k > rb_##k + 1) SC_RANGE_MAX((int)(rc_##k & 0xffffu), (int)(rc_##k >> 16))     \
-                for (int q = rb_##k + 2; q < re_##k; ++q) {                               \
-                    const int lo = p.run_lo[q], hi = p.run_hi[q];                         \
-                    SC_RANGE_MAX(lo, hi)                                                  \
-                }                                                                         \
-                rho_##k = m;                                                              \
-            }                                                                             \
+            }
+            rho[k] = m;
+            if constexpr (KT > 4) __builtin_amdgcn_sched_barrier(0);        // (slots one after the other: fewer registers)
         }
-        SW_EACH_K(SC_RHO)
         wave_sync();
 
         // ---- the compute device: makespan = max over classes of (release date + time of the classes released
         // then or later) ----
-        double mloc = last_arrival, ct_sum = 0.0;
-        {
-            // the rank of a release date is the number of arrivals up to it, one branch-free binary
-            // search per channel (release dates are arrivals, so a later release date has a higher rank and equal
-            // ones the same); the class times are added up by rank, a suffix sum over the ranks follows
-            double *A = arr;                // [R + 1] by rank (the arrivals and the table are not read any more)
-            for (int j = lane; j <= R; j += 64) A[j] = 0.0;
-#define SC_RANK_DECL(k) int rank_##k = 0, pos_##k = 0;
-            SW_EACH_K(SC_RANK_DECL)
-            for (int c = 0; c < p.n_channels; ++c) {
-                const int len = min(__builtin_amdgcn_readlane(queued, c), clen[c]);
-                if (len == 0) continue;
-                const double *lc = lists + coff[c];
-#define SC_RANK_ZERO(k) pos_##k = 0;
-                SW_EACH_K(SC_RANK_ZERO)
-                for (int step = 1 << (31 - __builtin_clz(len)); step > 0; step >>= 1) {
-#define SC_RANK_STEP(k)                                                                   \
-                    if constexpr (k < KT) {                                               \
-                        const int np = pos_##k + step;                                    \
-                        const double v = lc[min(np, len) - 1];                            \
-                        if (np <= len && v <= rho_##k) pos_##k = np;                      \
-                    }
-                    SW_EACH_K(SC_RANK_STEP)
-                }
-#define SC_RANK_ADD(k) rank_##k += pos_##k;
-                SW_EACH_K(SC_RANK_ADD)
+        // the rank of a release date is the number of arrivals up to it, one branch-free binary
+        // search per channel (release dates are arrivals, so a later release date has a higher rank and equal
+        // ones the same); the class times are added up by rank, a suffix sum over the ranks follows
+        double *A = arr;                    // [R + 1] by rank (the arrivals and the table are not read any more)
+        for (int j = lane; j <= R; j += 64) A[j] = 0.0;
+#pragma unroll
+        for (int k = 0; k < D; ++k)         // (an order that is no permutation cannot write past the channel's share)
+            if (of[k] >= 0 && of[k] >> 16 < clen[(of[k] >> 10) & 63]) lists[coff[(of[k] >> 10) & 63] + (of[k] >> 16)] = a[k];
+        wave_sync();
+        int rank[KT];
+#pragma unroll
+        for (int k = 0; k < KT; ++k) rank[k] = 0;
+        for (int c = 0; c < p.n_channels; ++c) {
+            const int len = min(__builtin_amdgcn_readlane(queued, c), __builtin_amdgcn_readfirstlane(clen[c]));
+            if (len == 0) continue;
+            const double *lc = lists + __builtin_amdgcn_readfirstlane(coff[c]);
+            // `left` arrivals from pos on may still be up to rho, all before are
+            int pos[KT];
+#pragma unroll
+            for (int k = 0; k < KT; ++k) pos[k] = 0;
+            for (int left = len; left > 1;) {
+                const int half = left >> 1;
+#pragma unroll
+                for (int k = 0; k < KT; ++k) pos[k] += lc[pos[k] + half - 1] <= rho[k] ? half : 0;
+                left -= half;
             }
-            wave_sync();
-#define SC_RANK_SUM(k) if constexpr (k < KT) { if (k * 64 + lane < C) atomicAdd(&A[rank_##k], ct_##k); ct_sum += ct_##k; }
-            SW_EACH_K(SC_RANK_SUM)
-            wave_sync();
-            double sfx = 0.0;
-            for (int base = (R / 64) * 64; base >= 0; base -= 64) {
-                const int j = base + lane;
-                const double x = j <= R ? A[j] : 0.0;
-                const double inc = wave_incl_scan_f64_dpp(x);
-                const double tot = lane63_f64(inc);
-                if (j <= R) A[j] = sfx + (tot - inc + x);           // this rank and every later one
-                sfx += tot;
-            }
-            wave_sync();
-#define SC_RANK_MAX(k) if constexpr (k < KT) { if (k * 64 + lane < C) mloc = max_f64(mloc, rho_##k + A[rank_##k]); }
-            SW_EACH_K(SC_RANK_MAX)
+#pragma unroll
+            for (int k = 0; k < KT; ++k) rank[k] += pos[k] + (lc[pos[k]] <= rho[k] ? 1 : 0);
         }
-        const double m = wave_max_f64_dpp(mloc);
+        wave_sync();
+        double ct_sum = 0.0, together = 0.0;
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {
+            ct_sum += ct[k];
+            together += ct[k];
+            // (a lane without a class in this slot has none in the later ones either; its time is zero)
+            if (lane * cls_lane + k * cls_slot < C &&
+                (k == KT - 1 || rank[min(k + 1, KT - 1)] != rank[k] || lane * cls_lane + (k + 1) * cls_slot >= C)) {
+                atomicAdd(&A[rank[k]], together);
+                together = 0.0;
+            }
+        }
+        wave_sync();
         const double sum_c = wave_sum_f64_dpp(ct_sum);
+        // ranks 1 .. R; of rank 0 are classes that are there from the start, with all the class time ahead
+        double S[D];
+#pragma unroll
+        for (int k = D - 1; k >= 0; --k) {
+            S[k] = lane * D + k < R ? A[lane * D + k + 1] : 0.0;
+            if (k < D - 1) S[k] += S[k + 1];
+        }
+        const double S_incl = wave_incl_scan_f64_dpp(S[0]), S_after = lane63_f64(S_incl) - S_incl;
+        if (lane == 0) A[0] = sum_c;
+#pragma unroll
+        for (int k = 0; k < D; ++k)
+            if (lane * D + k < R) A[lane * D + k + 1] = S_after + S[k];         // this rank and every later one
+        wave_sync();
+        double mloc = last_arrival;
+#pragma unroll
+        for (int k = 0; k < KT; ++k)
+            if (lane * cls_lane + k * cls_slot < C) mloc = max_f64(mloc, rho[k] + A[rank[k]]);
+        const double m = wave_max_f64_dpp(mloc);
         if (lane == 0) {
             const double U = sum_c + sum_r;
             const double L = max_f64(sum_c, last_arrival);
@@ -613,6 +664,7 @@ simulate_channels_kernel(const SimChanParams p)
             if (p.S) p.S[b] = (U == L || L == 0.0) ? 0.0 : (U - L) / L;
         }
     }
+    if (bad) atomicOr(p.bad_order, 1);
 }
 
 template <int KT>
@@ -623,12 +675,13 @@ static hipError_t launch_sim_chan(SimChanParams &p, const Dag &d, hipStream_t s)
     while ((1 << levels) <= nb) ++levels;             // floor(log2 nb) + 1 levels of the table of block maxima
     p.levels = levels;
     p.nb = nb;
-    // the transfer times, later the table; at least one double beyond the padded arrivals for the sums by rank
-    const size_t x_doubles = (std::max((size_t)d.R, (size_t)levels * nb) + 2) & ~(size_t)1;
-    p.x_doubles = (int32_t)x_doubles;
-    // after those: the class totals, then the arrivals by channel
-    const size_t extra = std::max((size_t)64 * KT, ((size_t)d.R + 1) & ~(size_t)1);
-    const size_t wave_bytes = ((size_t)4 * nb + x_doubles + extra) * 8;       // a multiple of 16
+    // the class totals, the transfer times, the table, the arrivals by channel
+    const size_t x_doubles = (std::max(std::max((size_t)64 * KT, (size_t)d.R), (size_t)levels * nb) + 1) & ~(size_t)1;
+    const size_t arr_doubles = ((size_t)4 * nb + 2) & ~(size_t)1;             // (sums by rank: one more than there are recvs)
+    p.arr_doubles = (int32_t)arr_doubles;
+    const size_t wave_bytes = (arr_doubles + x_doubles) * 8;                    // a multiple of 16
+    p.cls_lane = d.n_runs <= 2 * d.C ? KT : 1;
+    p.cls_slot = d.n_runs <= 2 * d.C ? 1 : 64;
     int waves = 4;
     while (waves > 1 && wave_bytes * waves > 40 * 1024) waves >>= 1;
     const size_t chan_bytes = (((size_t)d.R + 128) * 4 + 15) & ~(size_t)15;
@@ -660,7 +713,9 @@ hipError_t launch_simulate_channels(Dag &d, const SimArgs &a, int32_t n_channels
     const int K = std::max((d.C + 63) / 64, (d.R + 63) / 64);   // slots per lane: classes, and positions of the order
     const int KT = K < 1 ? 1 : K;
     if (d.R == 0 || d.R > 512 || K > 8 || n_channels > 64 || (d.C > 0 && (!d.d_col_cls || !d.d_run_ptr))) return hipErrorNotSupported;
+    if (!d.d_bad_order || !a.order) return hipErrorInvalidValue;
     SimChanParams p{};
+    p.bad_order = d.d_bad_order;
     p.B = a.B; p.R = d.R; p.C = d.C; p.N = d.N; p.n_channels = n_channels;
     p.col_cls = d.d_col_cls; p.run_ptr = d.d_run_ptr; p.run_lo = d.d_run_lo; p.run_hi = d.d_run_hi;
     p.chan = chan; p.order = a.order; p.order_stride = a.order_stride;
