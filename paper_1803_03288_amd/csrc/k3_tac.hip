@@ -439,7 +439,7 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
         if (e == hipSuccess) p.only_flagged = flags;
         else if (e != hipErrorNotSupported && e != hipErrorOutOfMemory) return e;
     }
-    if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && d.C <= 16 * 64 && d.W <= 6) {
+    if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && d.C <= 16 * 64) {
         hipError_t e = ensure_workspace(&d, flag_bytes + gstate_bytes);
         if (e != hipSuccess) return e;
         int32_t *flags = static_cast<int32_t *>(d.d_work);

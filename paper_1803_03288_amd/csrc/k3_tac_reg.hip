@@ -20,10 +20,11 @@
 //     common case on layered models; two pointers at two recvs: one comparison), and only the general path enumerates
 //     Q, from the class registers.  With more classes all targets are kept, one per lane, and the first member of Q comes
 //     out of one reduction over them (Johnson's rule, checked against every other member).  61 x 23 layered ops, 203
-//     recvs, 775 classes, 5 003 samples: 2.37 ms enumerating, 1.15 ms with the list (4.85 ms in the general kernel);
+//     recvs, 775 classes, 5 003 samples, with eight waves per workgroup: 2.37 ms enumerating, 1.15 ms with the list (4.85 ms in
+//     the general kernel);
 //   * M of a class is needed only when Q is empty or the comparator ties.  It is formed at the
-//     first such round as the sum of the transfer times of its row's recvs and brought up to date from the order built so far; rounds that do
-//     not need it do not touch it;
+//     first such round as the sum of the transfer times of its row's recvs and brought up to date from the order built so
+//     far; rounds that do not need it do not touch it;
 //   * the class totals of a sample are formed by one coalesced pass over its op_time row,
 //     each column adding itself to its class's total in LDS;
 //   * a class is released when the recv it pointed at (its last one) is selected, so its release
@@ -61,12 +62,21 @@ struct TacRegParams {
     int32_t active, n_waves;    // waves of a workgroup that take samples, of the grid
 };
 
-// Waves per workgroup.  The class rows in LDS are shared by the workgroup, so with many classes
-// per lane (large rows, many registers) one large workgroup per compute unit leaves the most
-// LDS to the per-wave arrays; sixteen waves cap the registers at 128 per lane, four waves per SIMD.
-// More than eight classes per lane need up to 256 registers, two waves per SIMD.
+// Waves per workgroup.  The class rows in LDS are shared by the workgroup, so where they are large (many classes per lane, many
+// recvs) one large workgroup per compute unit leaves the most LDS to the per-wave arrays; sixteen waves cap the registers at
+// 128 per lane, four waves per SIMD.  From nine classes per lane on some are spilled at that, outside the common rounds: 61 x 23
+// layered ops, 203 recvs, 775 classes, one set of eight waves with 196 registers against sixteen, 65 536 samples 11.4 and 7.1 ms
+// (vector instructions issue in 22 % of a wave's time, so that four waves per SIMD keep it busy), 5 003 samples, in two sets, 1.13
+// and 0.94 ms, a single sample 316 and 307 us.  More than 384 recvs, any number that LDS holds, against the general kernel, 5 003
+// samples, ms: 20 x 10 ops and 500 recvs 5.8 and 2.1; 30 x 20 and 400, 9.2 and 1.5; 61 x 23 and 400, 17.6 and 2.7; 25 x 15 and
+// 1 000, 28.8 and 11.4.
 constexpr int kRegWavesMax = 16;
-constexpr int reg_waves(int KT) { return KT <= 4 ? 4 : (KT <= 8 ? kRegWavesMax : 8); }
+constexpr int reg_waves(int KT, int W) { return KT <= 4 && W <= 6 ? 4 : kRegWavesMax; }
+// More than this many classes per lane: the class totals are summed in the whole region of the wave, M comes out of tables of
+// subset sums (with both, 61 x 23 ops: 54 900 -> 44 700 vector instructions per sample).  Below, where M is rarely looked at and
+// LDS is what bounds the waves, neither.
+constexpr int kTableSlots = 8;
+constexpr int state_doubles(int R, int W) { return 2 * (R + 1) + (R + 2 * W + 1) / 2 + 1; }     // t, P, ordl, aliveh
 // Words per lane in the LDS table of class rows: the KT words of a lane sit next to each other,
 // with one word of padding when KT is even, so that the lanes of a wave reading their k-th word
 // fall into different banks (an even stride puts every 32 / gcd(stride, 32)-th lane on one bank).
@@ -92,7 +102,7 @@ __device__ __forceinline__ int first_alive(const uint32_t *rows, const uint32_t 
 
 // LIST: for graphs whose Q often has several members (see launch_tac_reg)
 template <int KT, bool LIST>
-__global__ void __launch_bounds__(64 * reg_waves(KT), (KT <= 3 ? 6 : (KT <= 4 ? 5 : 1)))
+__global__ void __launch_bounds__(64 * kRegWavesMax, (KT <= 3 ? 6 : (KT <= 4 ? 5 : 1)))
 tac_reg_kernel(const TacRegParams p)
 {
     extern __shared__ double smem[];
@@ -123,7 +133,7 @@ tac_reg_kernel(const TacRegParams p)
 #define TT_DECL_CONST(k) int mmax_##k = 0;
     TT_EACH_K(TT_DECL_CONST)
 #define TT_INIT_CONST(k)                                                                  \
-    if constexpr (k < KT) {                                                               \
+    if constexpr (k < KT && KT <= kTableSlots) {                                          \
         const int c = k * 64 + lane;                                                      \
         int mx = c < C ? p.cls_ptr[c + 1] - p.cls_ptr[c] : 0;                             \
         for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off));         \
@@ -132,7 +142,8 @@ tac_reg_kernel(const TacRegParams p)
     TT_EACH_K(TT_INIT_CONST)
 
     const uint32_t *rows_lane = rows + lane * KS;      // this lane's KT words of half-row 0
-    double *csum = P;                                  // [64 KT] class totals while they are summed (spans P, ordl, aliveh)
+    double *csum = KT > kTableSlots ? mine : P;        // [64 KT] class totals while they are summed (spans P, ordl, aliveh)
+    double *tab = KT > kTableSlots ? mine + state_doubles(R, W) : nullptr;   // [256] KT > kTableSlots: subset sums of eight transfer times
 
     const int gwave = blockIdx.x * p.active + wave;
     for (int b = gwave; b < p.B; b += p.n_waves) {
@@ -140,21 +151,25 @@ tac_reg_kernel(const TacRegParams p)
         const TimeRow ot = time_row(p.op_time, (size_t)b * N, p.f32 != 0);
         wave_sync();                        // LDS of the previous sample is no longer read
 
-        // ---- a. transfer times ----
-        bool zero_seen = false;
-        for (int r = lane; r < R; r += 64) {
-            const double x = rt[r];
-            t[r] = x;
-            zero_seen |= !(x > 0.0);
+        // ---- a. transfer times (after the class totals where those need their place) ----
+#define TT_READ_TIMES()                                                                   \
+        {                                                                                 \
+            bool zero_seen = false;                                                       \
+            for (int r = lane; r < R; r += 64) {                                          \
+                const double x = rt[r];                                                   \
+                t[r] = x;                                                                 \
+                zero_seen |= !(x > 0.0);                                                  \
+            }                                                                             \
+            const bool skip = __ballot(zero_seen) != 0ull;                                \
+            if (lane == 0) p.flags[b] = skip ? 1 : 0;                                     \
+            if (skip) continue;                                                           \
         }
-        const bool skip = __ballot(zero_seen) != 0ull;
-        if (lane == 0) p.flags[b] = skip ? 1 : 0;
-        if (skip) continue;
+        if constexpr (KT <= kTableSlots) TT_READ_TIMES()
 
         // ---- b. class totals ----
-#define TT_DECL_STATE(k) int pk_##k = -2 * CNT1, sole_##k = -1, mk_##k = 0; double M_##k = 0.0, ct_##k = 0.0;
+#define TT_DECL_STATE(k) int pk_##k = -2 * CNT1, mk_##k = 0; [[maybe_unused]] int sole_##k = -1; [[maybe_unused]] uint32_t last_##k = ~0u; double M_##k = 0.0, ct_##k = 0.0;
         TT_EACH_K(TT_DECL_STATE)
-        if (p.col_cls) {
+        if (KT > kTableSlots || p.col_cls) {
             // the row is read once; every column (run of columns) adds itself to the total of its class
             for (int c = lane; c < 64 * KT; c += 64) csum[c] = 0.0;
             wave_sync();
@@ -165,7 +180,7 @@ tac_reg_kernel(const TacRegParams p)
             wave_sync();
         } else {
 #define TT_GATHER_TOTAL(k)                                                                \
-            if constexpr (k < KT) {                                                       \
+            if constexpr (k < KT && KT <= kTableSlots) {                                  \
                 const int c = k * 64 + lane;                                              \
                 double s = 0.0;                                                           \
                 if (c < C) {                                                              \
@@ -178,6 +193,7 @@ tac_reg_kernel(const TacRegParams p)
             }
             TT_EACH_K(TT_GATHER_TOTAL)
         }
+        if constexpr (KT > kTableSlots) TT_READ_TIMES()
 #define TT_INIT_STATE(k)                                                                  \
         if constexpr (k < KT) {                                                           \
             const int c = k * 64 + lane;                                                  \
@@ -218,11 +234,45 @@ tac_reg_kernel(const TacRegParams p)
         // updates are deferred: formed as the sum of the transfer times of the class row's recvs
         // (recv by recv, each added where its bit is set), and then brought up to `upto` by the
         // subtractions of the rounds since m_sync, in their order.  ordl holds those rounds.
+        // With many class slots it is formed from the outstanding recvs of the row, eight at a time: one lookup in a table of the
+        // 256 sums of their subsets (lane l has those of bits 0..5 of its number), and formed again when more rounds have
+        // passed than that costs (about 42 + 3 KT instructions per eight recvs, 5 KT + 6 per round).  It is looked at in 21 of
+        // the 203 rounds of 61 x 23 layered ops and in 163 of 500 with 50 x 20.
 #define TT_M_WORD(k) uint32_t w_##k = 0; if constexpr (k < KT) { w_##k = wr[k]; }
 #define TT_M_ADD(k)                                                                       \
         if constexpr (k < KT) {                                                           \
             const int m_ = __builtin_amdgcn_sbfe(w_##k, i, 1);                            \
             M_##k += __hiloint2double(thi & m_, tlo & m_);                                \
+        }
+#define TT_M_ALIVE(k) if constexpr (k < KT) w_##k &= alive_;
+#define TT_M_LOOKUP(k) if constexpr (k < KT) M_##k += tab[(w_##k >> (8 * j)) & 255u];
+#define TT_M_TABLES()                                                                     \
+        {                                                                                 \
+            TT_EACH_K(TT_M_ZERO)                                                          \
+            for (int h = 0; 32 * h < R; ++h) {                                            \
+                const uint32_t alive_ = aliveh[h];                                        \
+                const double t_l = lane < min(32, R - 32 * h) ? t[32 * h + lane] : 0.0;   \
+                const uint32_t *wr = rows_lane + h * (64 * KS);                           \
+                TT_EACH_K(TT_M_WORD)                                                      \
+                TT_EACH_K(TT_M_ALIVE)                                                     \
+                _Pragma("unroll 1")                                                       \
+                for (int j = 0; j < 4; ++j) {                                             \
+                    double s_ = 0.0;                                                      \
+                    _Pragma("unroll")                                                     \
+                    for (int i = 0; i < 6; ++i) {                                         \
+                        const double x_ = readlane_f64(t_l, 8 * j + i);                   \
+                        s_ += (lane >> i) & 1 ? x_ : 0.0;                                 \
+                    }                                                                     \
+                    const double x6 = readlane_f64(t_l, 8 * j + 6), x7 = readlane_f64(t_l, 8 * j + 7); \
+                    wave_sync();            /* (the table before is not read any more) */ \
+                    tab[lane] = s_;                                                       \
+                    tab[64 + lane] = s_ + x6;                                             \
+                    tab[128 + lane] = s_ + x7;                                            \
+                    tab[192 + lane] = s_ + (x6 + x7);                                     \
+                    wave_sync();                                                          \
+                    TT_EACH_K(TT_M_LOOKUP)                                                \
+                }                                                                         \
+            }                                                                             \
         }
 #define TT_M_FORM()                                                                       \
         {                                                                                 \
@@ -247,7 +297,13 @@ tac_reg_kernel(const TacRegParams p)
         }
 #define TT_ENSURE_M(upto)                                                                 \
         {                                                                                 \
-            if (m_sync < 0) {                                                             \
+            if constexpr (KT > kTableSlots) {                                             \
+                if (m_sync < 0 || ((upto) - m_sync) * (5 * KT + 6) > (R >> 3) * (3 * KT + 42)) { \
+                    publish_alive(upto);                                                  \
+                    TT_M_TABLES()                                                         \
+                    m_sync = (upto);                                                      \
+                }                                                                         \
+            } else if (m_sync < 0) {                                                      \
                 TT_M_FORM()                                                               \
                 m_sync = 0;                                                               \
             }                                                                             \
@@ -267,6 +323,26 @@ tac_reg_kernel(const TacRegParams p)
             m_sync = (upto);                                                              \
         }
 
+        // The last recv of a class: sole_k, or, with many class slots, two classes to a register, 0xffff: none (while the class
+        // points at it, it is in `packed` as well).
+#define TT_AIM(k, l) (KT > kTableSlots ? __builtin_amdgcn_readlane(pk_##k, l) & IDX_MASK : __builtin_amdgcn_readlane(sole_##k, l))
+#define TT_LAST_0 last_0
+#define TT_LAST_1 last_0
+#define TT_LAST_2 last_2
+#define TT_LAST_3 last_2
+#define TT_LAST_4 last_4
+#define TT_LAST_5 last_4
+#define TT_LAST_6 last_6
+#define TT_LAST_7 last_6
+#define TT_LAST_8 last_8
+#define TT_LAST_9 last_8
+#define TT_LAST_10 last_10
+#define TT_LAST_11 last_10
+#define TT_LAST_12 last_12
+#define TT_LAST_13 last_12
+#define TT_LAST_14 last_14
+#define TT_LAST_15 last_14
+#define TT_LAST(k) TT_LAST_##k
         // A class that fell to one outstanding recv: its time goes to P of that recv, and with a
         // positive time it becomes a pointer.
 #define TT_PUSH_Q(target)                                                                 \
@@ -280,14 +356,17 @@ tac_reg_kernel(const TacRegParams p)
             {                                                                             \
                 const int l = __builtin_ctzll(nm);                                        \
                 nm ^= 1ull << l;                                                          \
-                const int sole = __builtin_amdgcn_readlane(sole_##k, l);                  \
+                const int sole = TT_AIM(k, l);         \
                 TT_PUSH_Q(sole)                                                           \
             }
 #define TT_TO_P(k, hit1, hm)     /* hm: the ballot of hit1 */                            \
         {                                                                                 \
             if (hit1) {                                                                   \
-                sole_##k = pk_##k & IDX_MASK;       /* the class is released when this recv is */ \
-                atomicAdd(&P[sole_##k], ct_##k);                                          \
+                const int sole = pk_##k & IDX_MASK; /* the class is released when this recv is */ \
+                sole_##k = sole;                                                          \
+                if constexpr (KT > kTableSlots)                                           \
+                TT_LAST(k) = (k) & 1 ? (TT_LAST(k) & 0xffffu) | (uint32_t)sole << 16 : (TT_LAST(k) & 0xffff0000u) | (uint32_t)sole; \
+                atomicAdd(&P[sole], ct_##k);                                              \
             }                                                                             \
             uint64_t nm = (hm) & ctpos_##k;               /* positive class time: a pointer */ \
             if (nm) {                                     /* one, as a rule */            \
@@ -362,7 +441,7 @@ tac_reg_kernel(const TacRegParams p)
                 while (nm) {                                                              \
                     const int l = __builtin_ctzll(nm);                                    \
                     nm ^= 1ull << l;                                                      \
-                    const int sole = __builtin_amdgcn_readlane(sole_##k, l);              \
+                    const int sole = TT_AIM(k, l);              \
                     TT_PUSH_Q(sole)                                                       \
                 }                                                                         \
             }
@@ -498,7 +577,7 @@ tac_reg_kernel(const TacRegParams p)
                     while (nm) {                                                          \
                         const int l = __builtin_ctzll(nm);                                \
                         nm ^= 1ull << l;                                                  \
-                        const int sole = __builtin_amdgcn_readlane(sole_##k, l);          \
+                        const int sole = TT_AIM(k, l);          \
                         qbits_l |= (uint32_t)(lane == (sole & 63)) << (sole >> 6);        \
                     }                                                                     \
                 }
@@ -568,7 +647,14 @@ tac_reg_kernel(const TacRegParams p)
             int32_t *posl = reinterpret_cast<int32_t *>(P);        // [R] recv -> step (P is free now)
             for (int s = lane; s < R; s += 64) posl[ordl[s]] = s;
             wave_sync();
-#define TT_KAPPA(k) const int kap_##k = (k < KT && sole_##k >= 0) ? posl[sole_##k] + 1 : 0;
+#define TT_KAPPA(k)                                                                       \
+            int kap_##k = 0;                                                              \
+            if constexpr (k < KT && KT <= kTableSlots) {                                  \
+                if (sole_##k >= 0) kap_##k = posl[sole_##k] + 1;                          \
+            } else if constexpr (k < KT) {                                                \
+                const uint32_t last = (k) & 1 ? TT_LAST(k) >> 16 : TT_LAST(k) & 0xffffu;  \
+                if (last != 0xffffu) kap_##k = posl[last] + 1;                            \
+            }
             TT_EACH_K(TT_KAPPA)
             wave_sync();
             // F_k into P[k - 1]: prefix sums of the transfer times in TAC order
@@ -622,20 +708,20 @@ static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
 {
     // LDS: shared rows + per wave t [R+1], P [R+1], ordl [R] i32, outstanding set [2W] u32
     const size_t rows_doubles = ((size_t)2 * d.W * 64 * row_stride(KT) + 1) / 2;
-    size_t per_wave = 2 * ((size_t)d.R + 1) + ((size_t)d.R + 2 * d.W + 1) / 2 + 1;
-    if (KT > 8) per_wave = std::max(per_wave, (size_t)d.R + 1 + 64 * KT + 1);       // (room for the class totals)
-    // as many waves as LDS allows, at most reg_waves(KT)
-    int waves = reg_waves(KT);
+    size_t per_wave = state_doubles(d.R, d.W);
+    if (KT > kTableSlots) per_wave = std::max(per_wave + 256, (size_t)64 * KT);     // (the table; room for the class totals)
+    // as many waves as LDS allows
+    int waves = reg_waves(KT, d.W);
     while (waves > 4 && (rows_doubles + per_wave * waves) * 8 > 150 * 1024) --waves;
     const size_t lds = (rows_doubles + per_wave * waves) * 8;
-    if (lds > (size_t)(waves > 4 ? 150 : 80) * 1024) return hipErrorNotSupported;
+    if (lds > 150 * 1024) return hipErrorNotSupported;
     // (a small batch is spread over the compute units, the waves of a SIMD slow each other down; those without a sample
     // help to bring in the rows)
     p.active = std::min(waves, std::max(1, (p.B + device_cu_count(d.device) - 1) / device_cu_count(d.device)));
     p.wave_doubles = (int32_t)per_wave;
     // the class totals are summed in the space of P, ordl and the outstanding set when that holds
     // one double per class slot
-    p.col_cls = KT > 8 || (size_t)64 * KT <= (size_t)d.R + 1 + ((size_t)d.R + 2 * d.W) / 2 ? d.d_col_cls : nullptr;
+    p.col_cls = KT > kTableSlots || (size_t)64 * KT <= (size_t)d.R + 1 + ((size_t)d.R + 2 * d.W) / 2 ? d.d_col_cls : nullptr;
     int per_cu = 0;
     hipError_t e;
     if (lds > 48 * 1024) {

@@ -1,0 +1,127 @@
+"""GPU parity where the work of a wave changes its layout: consecutive positions and classes per lane (several channels, the
+order search) and the class slots, tables and waves of TAC in registers, against the CPU oracle."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from paper_1803_03288_amd import workloads as wl
+
+from helpers import oracle_tac_rows
+
+
+@pytest.fixture(scope="module")
+def tt():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1803_03288_amd import binding
+    binding.lib()
+    return binding
+
+
+def cuda(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def layered(levels, width, recvs, attach=(1, 8)):
+    return wl.layered_dag(17, levels=levels, width=width, fan_in=(1, 4), back=3, n_recv=recvs, attach=attach)
+
+
+def chain(recvs, free=0):
+    """A class per recv, rows of one run."""
+    b = wl._Builder()
+    rs = [b.recv(1e5 * (1 + k % 7)) for k in range(recvs)]
+    x = []
+    for r in rs:
+        x = [b.op(x + [r], 1e-3, "op")]
+    for _ in range(free):
+        b.op([], 1e-3, "op")                # (depends on no recv)
+    return b.finish("chain", seed=3, batch=4)
+
+
+# recvs on both sides of every 64 of a wave's positions per lane; rows of one run and of many
+POSITIONS = {f"chain{r}": (lambda r=r: chain(r, r % 3 if r < 511 else 0)) for r in (1, 2, 63, 64, 65, 192, 193, 319, 320, 321, 448, 511, 512)}
+POSITIONS.update({f"layered{r}": (lambda r=r: layered(9, 9, r, (1, 5))) for r in (3, 64, 128, 257, 449, 512)})
+
+
+@pytest.mark.parametrize("name", list(POSITIONS))
+def test_consecutive_positions(tt, name):
+    d = POSITIONS[name]()
+    R, B = d.n_recv, 23
+    args = (d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    h = tt.build_deps(*args)
+    rng = np.random.default_rng(5)
+    orders = np.stack([rng.permutation(R) for _ in range(B)]).astype(np.int32)
+    op = rng.integers(0, 50, size=(B, d.n_compute)).astype(np.float64) * wl.QUANTUM      # (equal and zero times as well)
+    rv = rng.integers(0, 50, size=(B, R)).astype(np.float64) * wl.QUANTUM
+    for n_ch in (1, 3, 64):
+        chan = rng.integers(0, n_ch, size=R).astype(np.int32)
+        exp = oracle.simulate_channels(*args, n_ch, chan, orders, op, rv)
+        got = tt.simulate_channels(h, n_ch, chan, cuda(orders), cuda(op), cuda(rv))
+        for g, e in zip(got, exp):
+            assert np.array_equal(g.cpu().numpy(), e), n_ch
+        exp1 = oracle.simulate_channels(*args, n_ch, chan, orders[0], op, rv)
+        got1 = tt.simulate_channels(h, n_ch, chan, cuda(orders[0]), cuda(op), cuda(rv))
+        assert np.array_equal(got1[0].cpu().numpy(), exp1[0])
+    h.check_orders()
+    if h.n_classes <= 512:
+        moves = rng.integers(0, R, size=(64, 2)).astype(np.int32)
+        exp = oracle.order_search(*args, orders, moves, op, rv)
+        for g, e in zip(tt.order_search(h, cuda(orders), cuda(moves), cuda(op), cuda(rv)), exp):
+            assert np.array_equal(g.cpu().numpy(), e)
+        h.check_orders()
+    # an order that is none, in one sample: the others come out as before, the call is reported
+    if R > 1:
+        chan = (np.arange(R) % 3).astype(np.int32)
+        clean = tt.simulate_channels(h, 3, chan, cuda(orders), cuda(op), cuda(rv))[0].cpu().numpy()
+        for twice in (True, False):
+            bad = orders.copy()
+            bad[7, R - 1] = bad[7, 0] if twice else R
+            got = tt.simulate_channels(h, 3, chan, cuda(bad), cuda(op), cuda(rv))[0].cpu().numpy()
+            assert np.array_equal(np.delete(got, 7), np.delete(clean, 7))
+            with pytest.raises(tt.TicTacError):
+                h.check_orders()
+
+
+# class slots per lane (one register kernel for each, two slots apart above eight), words of the rows, waves that fit
+SLOTS = {
+    "chain385": lambda: chain(385), "chain1000": lambda: chain(1000, 1),
+    "few_classes": lambda: layered(3, 12, 700, (2, 5)),
+    "k4": lambda: layered(20, 10, 500), "k6": lambda: layered(25, 15, 640), "k6_1024": lambda: layered(25, 15, 1024),
+    "k8": lambda: layered(40, 20, 203), "k10": lambda: layered(50, 20, 203), "k10_short": lambda: layered(40, 20, 61), "k9_wide": lambda: layered(30, 20, 400),
+    "k13": lambda: layered(61, 23, 203), "k13_wide": lambda: layered(50, 20, 500), "k15": lambda: layered(58, 23, 380),
+    "k16": lambda: layered(65, 24, 330),
+}
+
+
+@pytest.mark.parametrize("name", list(SLOTS))
+def test_tac_in_registers(tt, name):
+    d = SLOTS[name]()
+    R, B = d.n_recv, 37
+    args = (d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    h = tt.build_deps(*args)
+    assert h.n_classes <= 1024, h.n_classes
+    dep = oracle.find_dependencies(*args)
+    rng = np.random.default_rng(9)
+    rows = [0, 17, 36]
+
+    def ints(lo, hi, n):
+        return rng.integers(lo, hi, size=(B, n)).astype(np.float64) * wl.QUANTUM
+
+    zero = ints(1, 1 << 20, R)
+    zero[::5, 0] = 0.0                      # (these go to the general kernel, between the others)
+    for what, op, rv in (("distinct", ints(1, 1 << 20, d.n_compute), ints(1, 1 << 20, R)),
+                         ("ties", ints(0, 3, d.n_compute), ints(1, 4, R)),
+                         ("zeros", ints(0, 1 << 20, d.n_compute), zero)):
+        print(f"[registers] {name} {what}: classes={h.n_classes} R={R}", flush=True)
+        got = tt.tac_simulate(h, cuda(op), cuda(rv), want_rank=True)
+        eo, er = oracle_tac_rows(dep, d.recv_ids, op[rows], rv[rows])[:2]
+        assert np.array_equal(got[0].cpu().numpy()[rows], eo), what
+        assert np.array_equal(got[1].cpu().numpy()[rows], er), what
+        exp = oracle.simulate(*args, eo, op[rows], rv[rows])
+        for g, e in zip(got[4:9], exp):     # (integers times a power of two: every sum is exact)
+            assert np.array_equal(g.cpu().numpy()[rows], e), what
