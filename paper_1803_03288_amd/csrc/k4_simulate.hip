@@ -30,22 +30,24 @@ struct SimKernelParams {
     double *makespan, *eff, *U, *L, *S;
 };
 
-// 1-based position of every recv in an order shared by all samples (one workgroup; 0 for a recv that an
-// invalid order leaves out, so that every position read later is in 0 .. R)
+// kappa of every class under an order shared by all samples.  Every workgroup makes the 1-based positions for itself (0 for a
+// recv that an invalid order leaves out, so that every position read is in 0 .. R); the first one checks the order.  In
+// launches of their own the positions and the check took a third of a call on 1 000 samples of resnet50 (33 us).
 __global__ void __launch_bounds__(256)
-position_kernel(int32_t R, const int32_t *__restrict__ order, int32_t *pos /*[R]*/)
+kappa_kernel(int32_t R, int32_t W, int32_t C, const uint64_t *__restrict__ cls_dep, const int32_t *__restrict__ order,
+             int32_t *kappa /*[C]*/, int32_t *bad_order)
 {
+    extern __shared__ int32_t pos[];        // [R]
     for (int k = threadIdx.x; k < R; k += 256) pos[k] = 0;
     __syncthreads();
     for (int k = threadIdx.x; k < R; k += 256)
         if ((unsigned)order[k] < (unsigned)R) pos[order[k]] = k + 1;
-}
-
-// kappa of every class under that order
-__global__ void __launch_bounds__(256)
-kappa_kernel(int32_t W, int32_t C, const uint64_t *__restrict__ cls_dep, const int32_t *__restrict__ pos,
-             int32_t *kappa /*[C]*/)
-{
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        bool bad = false;
+        for (int k = threadIdx.x; k < R; k += 256) bad |= (unsigned)order[k] >= (unsigned)R || pos[order[k]] != k + 1;
+        if (bad) atomicOr(bad_order, 1);
+    }
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= C) return;
     int kap = 0;
@@ -138,29 +140,39 @@ simulate_kernel(const SimKernelParams p)
 // l + 64, ... of the order; a workgroup is four independent waves.  Per sample: the transfer
 // times and the order are requested first, into registers, then the op_time row is read once,
 // coalesced, every run of columns of one class adding itself to the total of its class in LDS
-// (so one trip to memory per sample is waited for, not three); kappa of a class is the maximum of the positions of its recvs, taken run by run of
-// consecutive recv indices from a sparse table of range maxima over the position array (or read
-// from a table when all samples share one order); then A by kappa, and
+// (so one trip to memory per sample is waited for, not three); kappa of a class is the maximum of the positions of its recvs,
+// taken run by run of consecutive recv indices from a sparse table of range maxima over the position array (or read
+// from a table when all samples share one order).  A row of many runs mostly holds one of the recvs that come last, so those are
+// tried first, from the last one on: 24 x 20 layered ops, 300 recvs, 65 536 samples of an order each 3.59 -> 1.10 ms.  An order
+// of the sample's own is checked on the way (resnet50, 65 536 samples: 202 -> 187 us).  Then A by kappa, and
 //     makespan = max over k of F_k + (A_k + ... + A_R),   F_0 = 0,
-// which is the recurrence above unrolled.
+// which is the recurrence above unrolled.  The class totals are summed where A comes to be, and beyond: 21 x 18 layered ops, 378
+// classes, 28 recvs, whose totals do not fit there, took 652 us for 65 536 samples in the kernel above and take 66 here.
 struct SimWaveParams {
     int32_t B, R, C, N, n_waves, wave_bytes, levels;
     const int32_t *col_cls;     // [N] class of every op_time column
     const int32_t *run_ptr;     // [C+1] runs [run_lo, run_hi) of consecutive recv indices of the class rows
     const int32_t *run_lo, *run_hi;
+    const uint32_t *depT;       // cls_depT in halves: half h of class c at (h / 2 * Cpad + c) * 2 + h % 2
+    int32_t Cpad;
     const int32_t *order;
     int32_t order_stride;
     const int32_t *kappa;       // [C] for a shared order, else NULL
     const void *op_time, *recv_time;    // float64, or float32 when f32 is set
     int32_t f32;
     double *makespan, *eff, *U, *L, *S;
+    int32_t *bad_order;         // raised when an order is no permutation; not looked at with kappa
 };
 
 constexpr int kSimWaves = 4;
+constexpr int kWalkRuns = 6, kWalkSteps = 16;
 
 #define SW_EACH_K(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7)
 
-template <int KT>
+// Where kappa comes from: a table, two runs of most rows, or rows of many runs.
+enum { kKappaTable, kKappaRuns, kKappaWalk };
+
+template <int KT, int KAPPA>
 __global__ void __launch_bounds__(64 * kSimWaves, KT <= 3 ? 5 : (KT <= 4 ? 4 : 2))
 simulate_wave_kernel(const SimWaveParams p)
 {
@@ -171,8 +183,8 @@ simulate_wave_kernel(const SimWaveParams p)
     double *t = reinterpret_cast<double *>(mine);           // [R]   Time(recv)
     double *F = t + R;                                      // [R]   F[k-1] = end of the k-th transfer
     double *A = F + R;                                      // [R+1] class time by kappa
-    double *csum = F;                                       // [64 KT] class totals while they are summed (spans F and A)
-    uint16_t *pos = reinterpret_cast<uint16_t *>(A + (R + 1));   // [levels][R] range maxima of the 1-based positions
+    double *csum = F;                                       // [64 KT] class totals while they are summed (the space of F and A)
+    uint16_t *pos = reinterpret_cast<uint16_t *>(F + max(2 * R + 1, 64 * KT));      // [levels][R] range maxima of the 1-based positions
 
     // Per class slot, fixed for the launch: kappa from the table when all samples share one order,
     // else the first two runs of the class row (lo | hi << 16; longer rows read the rest from memory).
@@ -182,7 +194,7 @@ simulate_wave_kernel(const SimWaveParams p)
     if constexpr (k < KT) {                                                               \
         const int c = k * 64 + lane;                                                      \
         if (c < C) {                                                                      \
-            if (p.kappa) {                                                                \
+            if constexpr (KAPPA == kKappaTable) {                                         \
                 ra_##k = (unsigned)p.kappa[c];                                            \
             } else {                                                                      \
                 rb_##k = p.run_ptr[c];                                                    \
@@ -194,6 +206,7 @@ simulate_wave_kernel(const SimWaveParams p)
     }
     SW_EACH_K(SW_RUNS)
 
+    bool bad = false;
     const int gwave = blockIdx.x * kSimWaves + wave;
     for (int b = gwave; b < p.B; b += p.n_waves) {
         const TimeRow rt = time_row(p.recv_time, (size_t)b * R, p.f32 != 0);
@@ -243,10 +256,17 @@ simulate_wave_kernel(const SimWaveParams p)
         wave_sync();
 
         // ---- kappa ----
-        if (p.kappa) {
+        if constexpr (KAPPA == kKappaTable) {
 #define SW_KAPPA_TABLE(k) if constexpr (k < KT) { kap_##k = (int)ra_##k; }
             SW_EACH_K(SW_KAPPA_TABLE)
         } else {
+            // (the check of the order: every recv is at the position that it has been given last)
+#define SW_CHECK(q)                                                                       \
+            if constexpr (q < KT) {                                                       \
+                if (q * 64 + lane < R) bad |= (unsigned)or_##q >= (unsigned)R || pos[or_##q] != q * 64 + lane + 1; \
+            }
+            SW_EACH_K(SW_CHECK)
+            [[maybe_unused]] const int late = KAPPA == kKappaWalk && lane < kWalkSteps && lane < R ? min((unsigned)ord[R - 1 - lane], (unsigned)R - 1) : 0;      // the recvs that come last, last one first
             // level j of the table: maximum over [i, min(i + 2^j, R))
             for (int j = 1; j < p.levels; ++j) {
                 const uint16_t *prev = pos + (size_t)(j - 1) * R;
@@ -265,11 +285,25 @@ simulate_wave_kernel(const SimWaveParams p)
             if constexpr (k < KT) {                                                       \
                 if (k * 64 + lane < C) {                                                  \
                     int m = 0;                                                            \
+                    if (KAPPA == kKappaWalk && re_##k > rb_##k + kWalkRuns)               \
+                        for (int i = 0; i < min(R, kWalkSteps) && m == 0; i += 4) {       \
+                            uint32_t w[4];                                                \
+                            _Pragma("unroll")                                             \
+                            for (int j = 0; j < 4; ++j) {                                 \
+                                const int r = __builtin_amdgcn_readlane(late, i + j);     \
+                                w[j] = p.depT[((size_t)(r >> 6) * p.Cpad + k * 64 + lane) * 2 + (r >> 5 & 1)] >> (r & 31) & 1u; \
+                            }                                                             \
+                            _Pragma("unroll")                                             \
+                            for (int j = 3; j >= 0; --j)                                  \
+                                if (w[j] && i + j < R) m = R - (i + j);                   \
+                        }                                                                 \
+                    if (m == 0) {                                                         \
                     if (re_##k > rb_##k) SW_RANGE_MAX((int)(ra_##k & 0xffffu), (int)(ra_##k >> 16))          \
                     if (re_##k > rb_##k + 1) SW_RANGE_MAX((int)(rc_##k & 0xffffu), (int)(rc_##k >> 16))      \
                     for (int q = rb_##k + 2; q < re_##k; ++q) {                           \
                         const int lo = p.run_lo[q], hi = p.run_hi[q];                     \
                         SW_RANGE_MAX(lo, hi)                                              \
+                    }                                                                     \
                     }                                                                     \
                     kap_##k = m;                                                          \
                 }                                                                         \
@@ -303,26 +337,27 @@ simulate_wave_kernel(const SimWaveParams p)
             if (p.S) p.S[b] = (U == L || L == 0.0) ? 0.0 : (U - L) / L;
         }
     }
+    if (bad) atomicOr(p.bad_order, 1);
 }
 
-template <int KT>
+template <int KT, int KAPPA>
 static hipError_t launch_sim_wave(SimWaveParams &p, const Dag &d, hipStream_t s)
 {
     int levels = 1;
     while ((1 << levels) <= d.R) ++levels;            // floor(log2 R) + 1 levels of the table
     p.levels = levels;
-    size_t wave_bytes = ((size_t)3 * d.R + 1) * 8 + (size_t)levels * d.R * 2;
+    size_t wave_bytes = ((size_t)d.R + std::max((size_t)2 * d.R + 1, (size_t)64 * KT)) * 8 + (size_t)levels * d.R * 2;
     wave_bytes = (wave_bytes + 15) & ~(size_t)15;
     const size_t lds = wave_bytes * kSimWaves;
     if (lds > 150 * 1024) return hipErrorNotSupported;     // 160 KB of LDS per compute unit
     p.wave_bytes = (int32_t)wave_bytes;
     hipError_t e;
     if (lds > 48 * 1024) {
-        e = ensure_dynamic_lds(reinterpret_cast<const void *>(simulate_wave_kernel<KT>), lds);
+        e = ensure_dynamic_lds(reinterpret_cast<const void *>(simulate_wave_kernel<KT, KAPPA>), lds);
         if (e != hipSuccess) return e;
     }
     int per_cu = 0;
-    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(simulate_wave_kernel<KT>), 64 * kSimWaves, lds);
+    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(simulate_wave_kernel<KT, KAPPA>), 64 * kSimWaves, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
     const int n_cu = device_cu_count(d.device);
@@ -330,7 +365,7 @@ static hipError_t launch_sim_wave(SimWaveParams &p, const Dag &d, hipStream_t s)
     const int need = (p.B + kSimWaves - 1) / kSimWaves;
     if (grid > need) grid = need;
     p.n_waves = grid * kSimWaves;
-    hipLaunchKernelGGL((simulate_wave_kernel<KT>), dim3(grid), dim3(64 * kSimWaves), lds, s, p);
+    hipLaunchKernelGGL((simulate_wave_kernel<KT, KAPPA>), dim3(grid), dim3(64 * kSimWaves), lds, s, p);
     return hipGetLastError();
 }
 
@@ -338,24 +373,22 @@ static hipError_t launch_sim_wave(SimWaveParams &p, const Dag &d, hipStream_t s)
 static hipError_t try_simulate_wave(const Dag &d, const SimArgs &a, const int32_t *kappa, hipStream_t s)
 {
     const int K = std::max((d.C + 63) / 64, (d.R + 63) / 64);   // slots per lane: classes, and positions of the order
-    const int KT = K;                                 // the instantiation that is launched below
-    // (the class totals are summed in the space of F and A: one double per class slot must fit)
-    if (d.R == 0 || d.R > 512 || d.C == 0 || K > 8 || !d.d_col_cls || !d.d_run_ptr || (size_t)64 * KT > 2 * (size_t)d.R + 1)
+    if (d.R == 0 || d.R > 512 || d.C == 0 || K > 8 || !d.d_col_cls || !d.d_run_ptr || !d.d_cls_depT || !d.d_bad_order)
         return hipErrorNotSupported;
     SimWaveParams p{};
     p.B = a.B; p.R = d.R; p.C = d.C; p.N = d.N;
     p.col_cls = d.d_col_cls; p.run_ptr = d.d_run_ptr; p.run_lo = d.d_run_lo; p.run_hi = d.d_run_hi;
+    p.depT = reinterpret_cast<const uint32_t *>(d.d_cls_depT); p.Cpad = d.Cpad; p.bad_order = d.d_bad_order;
     p.order = a.order; p.order_stride = a.order_stride; p.kappa = kappa;
     p.op_time = a.op_time; p.recv_time = a.recv_time; p.f32 = a.f32 ? 1 : 0;
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
-    if (K <= 1) return launch_sim_wave<1>(p, d, s);
-    if (K <= 2) return launch_sim_wave<2>(p, d, s);
-    if (K <= 3) return launch_sim_wave<3>(p, d, s);
-    if (K <= 4) return launch_sim_wave<4>(p, d, s);
-    if (K <= 5) return launch_sim_wave<5>(p, d, s);
-    if (K <= 6) return launch_sim_wave<6>(p, d, s);
-    if (K <= 7) return launch_sim_wave<7>(p, d, s);
-    return launch_sim_wave<8>(p, d, s);
+    // (more than two runs per row on average, as with the channels' classes)
+#define SW_LAUNCH(k)                                                                      \
+    if (K <= k) return kappa ? launch_sim_wave<k, kKappaTable>(p, d, s)                   \
+                     : d.n_runs <= 2 * d.C ? launch_sim_wave<k, kKappaRuns>(p, d, s) : launch_sim_wave<k, kKappaWalk>(p, d, s);
+    SW_LAUNCH(1) SW_LAUNCH(2) SW_LAUNCH(3) SW_LAUNCH(4) SW_LAUNCH(5) SW_LAUNCH(6) SW_LAUNCH(7)
+    SW_LAUNCH(8)
+    return hipErrorNotSupported;
 }
 
 template <int BS>
@@ -820,28 +853,30 @@ hipError_t launch_simulate(Dag &d, const SimArgs &a, hipStream_t s)
         const hipError_t e = launch_simulate_lanes(d, a, s);
         if (e != hipErrorNotSupported) return e;
     }
-    {
-        const hipError_t e = launch_check_orders(d, a.B, a.order, a.order_stride, s);
-        if (e != hipSuccess) return e;
-    }
     SimKernelParams p{};
     p.B = a.B; p.R = d.R; p.W = d.W; p.C = d.C; p.N = d.N;
     p.cls_dep = d.d_cls_dep; p.cls_ptr = d.d_cls_ptr; p.cls_cols = d.d_cls_cols;
     p.order = a.order; p.order_stride = a.order_stride; p.kappa = nullptr;
     p.op_time = a.op_time; p.recv_time = a.recv_time; p.f32 = a.f32 ? 1 : 0;
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
-    if (a.order_stride == 0 && d.R > 0 && d.C > 0) {
-        hipError_t e = ensure_workspace(&d, ((size_t)d.R + d.C) * sizeof(int32_t));
+    const bool shared = a.order_stride == 0 && d.R > 0 && d.C > 0;
+    if (shared) {
+        const size_t lds = (size_t)d.R * 4;
+        if (!d.d_bad_order || lds > 48 * 1024) return hipErrorInvalidValue;
+        hipError_t e = ensure_workspace(&d, (size_t)d.C * sizeof(int32_t));
         if (e != hipSuccess) return e;
-        int32_t *pos = static_cast<int32_t *>(d.d_work);
-        int32_t *kappa = pos + d.R;
-        hipLaunchKernelGGL(position_kernel, dim3(1), dim3(256), 0, s, d.R, a.order, pos);
-        hipLaunchKernelGGL(kappa_kernel, dim3((d.C + 255) / 256), dim3(256), 0, s, d.W, d.C, d.d_cls_dep, pos, kappa);
+        int32_t *kappa = static_cast<int32_t *>(d.d_work);
+        hipLaunchKernelGGL(kappa_kernel, dim3((d.C + 255) / 256), dim3(256), lds, s, d.R, d.W, d.C, d.d_cls_dep, a.order, kappa,
+                           d.d_bad_order);
         p.kappa = kappa;
     }
     {
         const hipError_t e = try_simulate_wave(d, a, p.kappa, s);
         if (e != hipErrorNotSupported) return e;
+    }
+    if (!shared) {
+        const hipError_t e = launch_check_orders(d, a.B, a.order, a.order_stride, s);
+        if (e != hipSuccess) return e;
     }
     const size_t lds = ((size_t)(d.R + 1) * 2 + 16) * 8 + (size_t)d.R * 4;
     if (lds > 160 * 1024) return hipErrorInvalidValue;

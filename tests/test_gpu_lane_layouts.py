@@ -1,5 +1,5 @@
 """GPU parity where the work of a wave changes its layout: consecutive positions and classes per lane (several channels, the
-order search) and the class slots, tables and waves of TAC in registers, against the CPU oracle."""
+order search), where the release positions of classes come from (one order for a sample each) and the class slots, tables and waves of TAC in registers, against the CPU oracle."""
 
 import numpy as np
 import pytest
@@ -46,6 +46,7 @@ def chain(recvs, free=0):
 # recvs on both sides of every 64 of a wave's positions per lane; rows of one run and of many
 POSITIONS = {f"chain{r}": (lambda r=r: chain(r, r % 3 if r < 511 else 0)) for r in (1, 2, 63, 64, 65, 192, 193, 319, 320, 321, 448, 511, 512)}
 POSITIONS.update({f"layered{r}": (lambda r=r: layered(9, 9, r, (1, 5))) for r in (3, 64, 128, 257, 449, 512)})
+POSITIONS.update({f"many_classes{r}": (lambda r=r: layered(24, 18, r, (2, 6))) for r in (6, 15, 16, 17, 28, 130, 300)})
 
 
 @pytest.mark.parametrize("name", list(POSITIONS))
@@ -68,6 +69,13 @@ def test_consecutive_positions(tt, name):
         got1 = tt.simulate_channels(h, n_ch, chan, cuda(orders[0]), cuda(op), cuda(rv))
         assert np.array_equal(got1[0].cpu().numpy(), exp1[0])
     h.check_orders()
+    exp = oracle.simulate(*args, orders, op, rv)
+    for g, e in zip(tt.simulate(h, cuda(orders), cuda(op), cuda(rv)), exp):
+        assert np.array_equal(g.cpu().numpy(), e)
+    exp = oracle.simulate(*args, orders[0], op, rv)
+    for g, e in zip(tt.simulate(h, cuda(orders[0]), cuda(op), cuda(rv)), exp):
+        assert np.array_equal(g.cpu().numpy(), e)
+    h.check_orders()
     if h.n_classes <= 512:
         moves = rng.integers(0, R, size=(64, 2)).astype(np.int32)
         exp = oracle.order_search(*args, orders, moves, op, rv)
@@ -78,11 +86,19 @@ def test_consecutive_positions(tt, name):
     if R > 1:
         chan = (np.arange(R) % 3).astype(np.int32)
         clean = tt.simulate_channels(h, 3, chan, cuda(orders), cuda(op), cuda(rv))[0].cpu().numpy()
+        alone = tt.simulate(h, cuda(orders), cuda(op), cuda(rv))[0].cpu().numpy()
         for twice in (True, False):
             bad = orders.copy()
             bad[7, R - 1] = bad[7, 0] if twice else R
             got = tt.simulate_channels(h, 3, chan, cuda(bad), cuda(op), cuda(rv))[0].cpu().numpy()
             assert np.array_equal(np.delete(got, 7), np.delete(clean, 7))
+            with pytest.raises(tt.TicTacError):
+                h.check_orders()
+            got = tt.simulate(h, cuda(bad), cuda(op), cuda(rv))[0].cpu().numpy()
+            assert np.array_equal(np.delete(got, 7), np.delete(alone, 7))
+            with pytest.raises(tt.TicTacError):
+                h.check_orders()
+            tt.simulate(h, cuda(bad[7]), cuda(op), cuda(rv))
             with pytest.raises(tt.TicTacError):
                 h.check_orders()
 
