@@ -30,14 +30,18 @@ struct SimKernelParams {
     double *makespan, *eff, *U, *L, *S;
 };
 
-// kappa of every class under an order shared by all samples.  Every workgroup makes the 1-based positions for itself (0 for a
-// recv that an invalid order leaves out, so that every position read is in 0 .. R); the first one checks the order.  In
-// launches of their own the positions and the check took a third of a call on 1 000 samples of resnet50 (33 us).
+// kappa of every class and of every op_time column under an order shared by all samples.  Every workgroup makes the 1-based
+// positions for itself (0 for a recv that an invalid order leaves out, so that every position read is in 0 .. R); the first
+// one checks the order.  In launches of their own the positions and the check took a third of a call on 1 000 samples of
+// resnet50 (33 us).
+constexpr int kKappaBlock = 64;             // classes per workgroup, whose columns its 256 threads share
 __global__ void __launch_bounds__(256)
 kappa_kernel(int32_t R, int32_t W, int32_t C, const uint64_t *__restrict__ cls_dep, const int32_t *__restrict__ order,
-             int32_t *kappa /*[C]*/, int32_t *bad_order)
+             const int32_t *__restrict__ cls_ptr, const int32_t *__restrict__ cls_cols, const int32_t *__restrict__ col_cls,
+             int32_t *kappa /*[C]*/, int32_t *kappa_col /*[N]*/, int32_t *bad_order)
 {
-    extern __shared__ int32_t pos[];        // [R]
+    extern __shared__ int32_t pos[];        // [R], then [kKappaBlock] kappa
+    int32_t *mine = pos + R;
     for (int k = threadIdx.x; k < R; k += 256) pos[k] = 0;
     __syncthreads();
     for (int k = threadIdx.x; k < R; k += 256)
@@ -48,18 +52,30 @@ kappa_kernel(int32_t R, int32_t W, int32_t C, const uint64_t *__restrict__ cls_d
         for (int k = threadIdx.x; k < R; k += 256) bad |= (unsigned)order[k] >= (unsigned)R || pos[order[k]] != k + 1;
         if (bad) atomicOr(bad_order, 1);
     }
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
+    const int c0 = blockIdx.x * kKappaBlock, c = c0 + (threadIdx.x >> 2), part = threadIdx.x & 3;     // four threads per class
     int kap = 0;
-    const uint64_t *row = cls_dep + (size_t)c * W;
-    for (int w = 0; w < W; ++w) {
-        uint64_t x = row[w];
-        while (x) {
-            kap = max(kap, pos[w * 64 + __builtin_ctzll(x)]);
-            x &= x - 1;
+    if (c < C) {
+        const uint64_t *row = cls_dep + (size_t)c * W;
+        for (int w = part; w < W; w += 4) {
+            uint64_t x = row[w];
+            while (x) {
+                kap = max(kap, pos[w * 64 + __builtin_ctzll(x)]);
+                x &= x - 1;
+            }
         }
     }
-    kappa[c] = kap;
+    kap = max(kap, __shfl_xor(kap, 1));
+    kap = max(kap, __shfl_xor(kap, 2));
+    if (c < C && part == 0) {
+        kappa[c] = kap;
+        mine[c - c0] = kap;
+    }
+    __syncthreads();
+    const int end = cls_ptr[min(c0 + kKappaBlock, C)];
+    for (int m = cls_ptr[c0] + threadIdx.x; m < end; m += 256) {
+        const int j = cls_cols[m];
+        kappa_col[j] = mine[col_cls[j] - c0];
+    }
 }
 
 template <int BS>
@@ -135,42 +151,57 @@ simulate_kernel(const SimKernelParams p)
     }
 }
 
-// The same computation with one wavefront per sample, for graphs with at most 8 classes per
-// lane and at most 512 recvs.  Lane l owns the classes l, l + 64, ... and the positions l,
-// l + 64, ... of the order; a workgroup is four independent waves.  Per sample: the transfer
+// The same computation with one wavefront per sample, for graphs with at most 512 recvs.  Lane l owns the classes l, l + 64, ...
+// and the positions l, l + 64, ... of the order; a workgroup is four independent waves.  Per sample: the transfer
 // times and the order are requested first, into registers, then the op_time row is read once,
 // coalesced, every run of columns of one class adding itself to the total of its class in LDS
 // (so one trip to memory per sample is waited for, not three); kappa of a class is the maximum of the positions of its recvs,
-// taken run by run of consecutive recv indices from a sparse table of range maxima over the position array (or read
-// from a table when all samples share one order).  A row of many runs mostly holds one of the recvs that come last, so those are
-// tried first, from the last one on: 24 x 20 layered ops, 300 recvs, 65 536 samples of an order each 3.59 -> 1.10 ms.  An order
-// of the sample's own is checked on the way (resnet50, 65 536 samples: 202 -> 187 us).  Then A by kappa, and
+// taken run by run of consecutive recv indices from a sparse table of range maxima over the position array.  An order of the
+// sample's own is checked on the way (resnet50, 65 536 samples: 202 us with a launch for it, 187 without).
+//   * When all samples share one order, kappa is a table by column, and the columns are added up by it at once, whatever the
+//     number of classes (inception3, 65 536 samples: 650 -> 606 us; 61 x 23 layered ops, 203 recvs, 775 classes, 20 000
+//     samples, which went to the kernel above: 917 -> 72 us).
+//   * A row of many runs mostly holds one of the recvs that come last: there, and where there are too many classes for the
+//     registers, those are tried first, from the last one on (61 x 23 ops, an order each: 1 470 -> 222 us).
+// Then A by kappa, and
 //     makespan = max over k of F_k + (A_k + ... + A_R),   F_0 = 0,
-// which is the recurrence above unrolled.  The class totals are summed where A comes to be, and beyond: 21 x 18 layered ops, 378
-// classes, 28 recvs, whose totals do not fit there, took 652 us for 65 536 samples in the kernel above and take 66 here.
+// which is the recurrence above unrolled.
 struct SimWaveParams {
     int32_t B, R, C, N, n_waves, wave_bytes, levels;
     const int32_t *col_cls;     // [N] class of every op_time column
     const int32_t *run_ptr;     // [C+1] runs [run_lo, run_hi) of consecutive recv indices of the class rows
     const int32_t *run_lo, *run_hi;
+    const int32_t *cls_cnt0;    // [C] recvs of the row
     const uint32_t *depT;       // cls_depT in halves: half h of class c at (h / 2 * Cpad + c) * 2 + h % 2
     int32_t Cpad;
     const int32_t *order;
     int32_t order_stride;
-    const int32_t *kappa;       // [C] for a shared order, else NULL
+    const int32_t *kappa_col;   // [N] for a shared order, else NULL
     const void *op_time, *recv_time;    // float64, or float32 when f32 is set
     int32_t f32;
     double *makespan, *eff, *U, *L, *S;
-    int32_t *bad_order;         // raised when an order is no permutation; not looked at with kappa
+    int32_t *bad_order;         // raised when an order is no permutation; not looked at with kappa_col
 };
 
 constexpr int kSimWaves = 4;
-constexpr int kWalkRuns = 6, kWalkSteps = 16;
+constexpr int kWalkRecvs = 6, kWalkSteps = 32;
 
 #define SW_EACH_K(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7)
 
-// Where kappa comes from: a table, two runs of most rows, or rows of many runs.
-enum { kKappaTable, kKappaRuns, kKappaWalk };
+// Where kappa comes from: a table by column; two runs of most rows, of classes in registers (and memory for the other runs); or
+// rows that are read again for every sample, recv by recv, the recvs that come last first.
+enum { kKappaTable, kKappaRuns, kKappaLoop };
+
+// Bytes of a wave.  Times and sums; then the class totals (in the space of F and A while classes are in registers) and the
+// range maxima of the positions.
+static size_t sim_wave_bytes(int KAPPA, int KT, int R, int C, int levels)
+{
+    size_t n = ((size_t)3 * R + 1) * 8;
+    if (KAPPA == kKappaTable) return n;
+    if (KAPPA == kKappaLoop) return n + (size_t)C * 8 + (size_t)R * 2;
+    n = ((size_t)R + std::max((size_t)2 * R + 1, (size_t)64 * KT)) * 8;
+    return n + (size_t)levels * R * 2;
+}
 
 template <int KT, int KAPPA>
 __global__ void __launch_bounds__(64 * kSimWaves, KT <= 3 ? 5 : (KT <= 4 ? 4 : 2))
@@ -183,31 +214,29 @@ simulate_wave_kernel(const SimWaveParams p)
     double *t = reinterpret_cast<double *>(mine);           // [R]   Time(recv)
     double *F = t + R;                                      // [R]   F[k-1] = end of the k-th transfer
     double *A = F + R;                                      // [R+1] class time by kappa
-    double *csum = F;                                       // [64 KT] class totals while they are summed (the space of F and A)
-    uint16_t *pos = reinterpret_cast<uint16_t *>(F + max(2 * R + 1, 64 * KT));      // [levels][R] range maxima of the 1-based positions
+    // the class totals while they are summed: by kappa at once; [64 KT] in the space of F and A; [C]
+    double *csum = KAPPA == kKappaTable ? A : KAPPA == kKappaLoop ? A + (R + 1) : F;
+    uint16_t *pos = reinterpret_cast<uint16_t *>(KAPPA == kKappaLoop ? csum + C : F + max(2 * R + 1, 64 * KT)); // [levels][R] range maxima of the 1-based positions
+    constexpr bool kInRegs = KAPPA == kKappaRuns;
 
-    // Per class slot, fixed for the launch: kappa from the table when all samples share one order,
-    // else the first two runs of the class row (lo | hi << 16; longer rows read the rest from memory).
+    // Per class slot, fixed for the launch: the first two runs of the class row (lo | hi << 16; longer rows read the rest from
+    // memory).
 #define SW_RUNS(k)                                                                        \
-    int rb_##k = 0, re_##k = 0;                                                           \
-    unsigned ra_##k = 0, rc_##k = 0;                                                      \
-    if constexpr (k < KT) {                                                               \
+    [[maybe_unused]] int rb_##k = 0, re_##k = 0;                                          \
+    [[maybe_unused]] unsigned ra_##k = 0, rc_##k = 0;                                     \
+    if constexpr (k < KT && kInRegs) {                                                    \
         const int c = k * 64 + lane;                                                      \
         if (c < C) {                                                                      \
-            if constexpr (KAPPA == kKappaTable) {                                         \
-                ra_##k = (unsigned)p.kappa[c];                                            \
-            } else {                                                                      \
-                rb_##k = p.run_ptr[c];                                                    \
-                re_##k = p.run_ptr[c + 1];                                                \
-                if (re_##k > rb_##k) ra_##k = (unsigned)p.run_lo[rb_##k] | ((unsigned)p.run_hi[rb_##k] << 16);              \
-                if (re_##k > rb_##k + 1) rc_##k = (unsigned)p.run_lo[rb_##k + 1] | ((unsigned)p.run_hi[rb_##k + 1] << 16);  \
-            }                                                                             \
+            rb_##k = p.run_ptr[c];                                                        \
+            re_##k = p.run_ptr[c + 1];                                                    \
+            if (re_##k > rb_##k) ra_##k = (unsigned)p.run_lo[rb_##k] | ((unsigned)p.run_hi[rb_##k] << 16);              \
+            if (re_##k > rb_##k + 1) rc_##k = (unsigned)p.run_lo[rb_##k + 1] | ((unsigned)p.run_hi[rb_##k + 1] << 16);  \
         }                                                                                 \
     }
     SW_EACH_K(SW_RUNS)
 
     bool bad = false;
-    const int gwave = blockIdx.x * kSimWaves + wave;
+    const int gwave = blockIdx.x * (blockDim.x >> 6) + wave;
     for (int b = gwave; b < p.B; b += p.n_waves) {
         const TimeRow rt = time_row(p.recv_time, (size_t)b * R, p.f32 != 0);
         const TimeRow ot = time_row(p.op_time, (size_t)b * N, p.f32 != 0);
@@ -223,15 +252,22 @@ simulate_wave_kernel(const SimWaveParams p)
             if (q * 64 + lane < R) { rt_##q = rt[q * 64 + lane]; or_##q = ord[q * 64 + lane]; } \
         }
         SW_EACH_K(SW_REQUEST)
-        for (int c = lane; c < 64 * KT; c += 64) csum[c] = 0.0;
+        const int n_totals = KAPPA == kKappaTable ? R + 1 : KAPPA == kKappaLoop ? C : 64 * KT;
+        for (int c = lane; c < n_totals; c += 64) csum[c] = 0.0;
         wave_sync();
-        class_totals(csum, ot, p.col_cls, N, lane);
+        class_totals(csum, ot, KAPPA == kKappaTable ? p.kappa_col : p.col_cls, N, lane);
         wave_sync();
-#define SW_DECL(k) double ct_##k = 0.0; int kap_##k = 0;
+#define SW_DECL(k) [[maybe_unused]] double ct_##k = 0.0; [[maybe_unused]] int kap_##k = 0;
         SW_EACH_K(SW_DECL)
-#define SW_TOTAL(k) if constexpr (k < KT) { ct_##k = csum[k * 64 + lane]; }
+#define SW_TOTAL(k) if constexpr (k < KT && kInRegs) { ct_##k = csum[k * 64 + lane]; }
         SW_EACH_K(SW_TOTAL)
-#define SW_TIMES(q) if constexpr (q < KT) { if (q * 64 + lane < R) { t[q * 64 + lane] = rt_##q; pos[q * 64 + lane] = 0; } }
+#define SW_TIMES(q)                                                                       \
+        if constexpr (q < KT) {                                                           \
+            if (q * 64 + lane < R) {                                                      \
+                t[q * 64 + lane] = rt_##q;                                                \
+                if constexpr (KAPPA != kKappaTable) pos[q * 64 + lane] = 0;               \
+            }                                                                             \
+        }
         SW_EACH_K(SW_TIMES)
         wave_sync();
 
@@ -243,7 +279,7 @@ simulate_wave_kernel(const SimWaveParams p)
                 const int s = q * 64 + lane;                                              \
                 const int r = or_##q;                                                     \
                 const bool ok = (unsigned)r < (unsigned)R;  /* an invalid entry is skipped, never dereferenced */ \
-                if (ok) pos[r] = (uint16_t)(s + 1);                                       \
+                if (KAPPA != kKappaTable && ok) pos[r] = (uint16_t)(s + 1);                                       \
                 const double x = ok ? t[r] : 0.0;                                         \
                 const double inc = wave_incl_scan_f64_dpp(x);                             \
                 if (s < R) F[s] = fc + inc;                                               \
@@ -252,23 +288,22 @@ simulate_wave_kernel(const SimWaveParams p)
         }
         SW_EACH_K(SW_PLACE)
         const double Ftot = fc;
-        for (int j = lane; j <= R; j += 64) A[j] = 0.0;
+        if constexpr (KAPPA != kKappaTable)
+            for (int j = lane; j <= R; j += 64) A[j] = 0.0;
         wave_sync();
 
         // ---- kappa ----
-        if constexpr (KAPPA == kKappaTable) {
-#define SW_KAPPA_TABLE(k) if constexpr (k < KT) { kap_##k = (int)ra_##k; }
-            SW_EACH_K(SW_KAPPA_TABLE)
-        } else {
+        double ct_sum = 0.0;
+        if constexpr (KAPPA != kKappaTable) {
             // (the check of the order: every recv is at the position that it has been given last)
 #define SW_CHECK(q)                                                                       \
             if constexpr (q < KT) {                                                       \
                 if (q * 64 + lane < R) bad |= (unsigned)or_##q >= (unsigned)R || pos[or_##q] != q * 64 + lane + 1; \
             }
             SW_EACH_K(SW_CHECK)
-            [[maybe_unused]] const int late = KAPPA == kKappaWalk && lane < kWalkSteps && lane < R ? min((unsigned)ord[R - 1 - lane], (unsigned)R - 1) : 0;      // the recvs that come last, last one first
+            [[maybe_unused]] const int late = KAPPA == kKappaLoop && lane < kWalkSteps && lane < R ? min((unsigned)ord[R - 1 - lane], (unsigned)R - 1) : 0;      // the recvs that come last, last one first
             // level j of the table: maximum over [i, min(i + 2^j, R))
-            for (int j = 1; j < p.levels; ++j) {
+            for (int j = 1; KAPPA != kKappaLoop && j < p.levels; ++j) {
                 const uint16_t *prev = pos + (size_t)(j - 1) * R;
                 uint16_t *cur = pos + (size_t)j * R;
                 const int h = 1 << (j - 1);
@@ -282,40 +317,52 @@ simulate_wave_kernel(const SimWaveParams p)
                         m = max(m, max((int)lv_[lo], (int)lv_[(hi) - (1 << j_)]));        \
                     }
 #define SW_KAPPA_RUNS(k)                                                                  \
-            if constexpr (k < KT) {                                                       \
+            if constexpr (k < KT && kInRegs) {                                            \
                 if (k * 64 + lane < C) {                                                  \
                     int m = 0;                                                            \
-                    if (KAPPA == kKappaWalk && re_##k > rb_##k + kWalkRuns)               \
-                        for (int i = 0; i < min(R, kWalkSteps) && m == 0; i += 4) {       \
-                            uint32_t w[4];                                                \
-                            _Pragma("unroll")                                             \
-                            for (int j = 0; j < 4; ++j) {                                 \
-                                const int r = __builtin_amdgcn_readlane(late, i + j);     \
-                                w[j] = p.depT[((size_t)(r >> 6) * p.Cpad + k * 64 + lane) * 2 + (r >> 5 & 1)] >> (r & 31) & 1u; \
-                            }                                                             \
-                            _Pragma("unroll")                                             \
-                            for (int j = 3; j >= 0; --j)                                  \
-                                if (w[j] && i + j < R) m = R - (i + j);                   \
-                        }                                                                 \
-                    if (m == 0) {                                                         \
                     if (re_##k > rb_##k) SW_RANGE_MAX((int)(ra_##k & 0xffffu), (int)(ra_##k >> 16))          \
                     if (re_##k > rb_##k + 1) SW_RANGE_MAX((int)(rc_##k & 0xffffu), (int)(rc_##k >> 16))      \
                     for (int q = rb_##k + 2; q < re_##k; ++q) {                           \
                         const int lo = p.run_lo[q], hi = p.run_hi[q];                     \
                         SW_RANGE_MAX(lo, hi)                                              \
                     }                                                                     \
-                    }                                                                     \
                     kap_##k = m;                                                          \
                 }                                                                         \
             }
             SW_EACH_K(SW_KAPPA_RUNS)
+            if constexpr (KAPPA == kKappaLoop) {
+                for (int c = lane; c < C; c += 64) {
+                    const double ct = csum[c];
+                    int m = 0, n = 0;
+                    if (p.cls_cnt0[c] > kWalkRecvs)
+                        for (int i = 0; i < min(R, kWalkSteps) && m == 0; i += 4) {
+                            uint32_t w[4];
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                const int r = __builtin_amdgcn_readlane(late, i + j);
+                                w[j] = p.depT[((size_t)(r >> 6) * p.Cpad + c) * 2 + (r >> 5 & 1)] >> (r & 31) & 1u;
+                            }
+#pragma unroll
+                            for (int j = 3; j >= 0; --j)
+                                if (w[j] && i + j < R) m = R - (i + j);
+                        }
+                    for (int h = 0; m == 0 && 32 * h < R; h += 2) {
+                        const uint2 row = *reinterpret_cast<const uint2 *>(p.depT + ((size_t)(h >> 1) * p.Cpad + c) * 2);
+                        for (uint64_t x = (uint64_t)row.y << 32 | row.x; x != 0ull; x &= x - 1) n = max(n, (int)pos[h * 32 + __builtin_ctzll(x)]);
+                    }
+                    m = max(m, n);
+                    ct_sum += ct;
+                    atomicAdd(&A[m], ct);
+                }
+            }
         }
 
         // ---- A by kappa, suffix sums, makespan ----
-        double ct_sum = 0.0;
-#define SW_RELEASE(k) if constexpr (k < KT) { if (k * 64 + lane < C) atomicAdd(&A[kap_##k], ct_##k); ct_sum += ct_##k; }
+#define SW_RELEASE(k) if constexpr (k < KT && kInRegs) { if (k * 64 + lane < C) atomicAdd(&A[kap_##k], ct_##k); ct_sum += ct_##k; }
         SW_EACH_K(SW_RELEASE)
         wave_sync();
+        if constexpr (KAPPA == kKappaTable)
+            for (int j = lane; j <= R; j += 64) ct_sum += A[j];
         const double sum_c = wave_sum_f64_dpp(ct_sum);
         double sfx = 0.0, mloc = sum_c;                   // k = 0: F_0 + S_0 = all class time
         for (int base = ((R - 1) / 64) * 64; base >= 0; base -= 64) {
@@ -346,9 +393,10 @@ static hipError_t launch_sim_wave(SimWaveParams &p, const Dag &d, hipStream_t s)
     int levels = 1;
     while ((1 << levels) <= d.R) ++levels;            // floor(log2 R) + 1 levels of the table
     p.levels = levels;
-    size_t wave_bytes = ((size_t)d.R + std::max((size_t)2 * d.R + 1, (size_t)64 * KT)) * 8 + (size_t)levels * d.R * 2;
-    wave_bytes = (wave_bytes + 15) & ~(size_t)15;
-    const size_t lds = wave_bytes * kSimWaves;
+    const size_t wave_bytes = (sim_wave_bytes(KAPPA, KT, d.R, d.C, levels) + 15) & ~(size_t)15;
+    int waves = kSimWaves;
+    while (waves > 1 && wave_bytes * waves > 150 * 1024) waves >>= 1;
+    const size_t lds = wave_bytes * waves;
     if (lds > 150 * 1024) return hipErrorNotSupported;     // 160 KB of LDS per compute unit
     p.wave_bytes = (int32_t)wave_bytes;
     hipError_t e;
@@ -357,37 +405,45 @@ static hipError_t launch_sim_wave(SimWaveParams &p, const Dag &d, hipStream_t s)
         if (e != hipSuccess) return e;
     }
     int per_cu = 0;
-    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(simulate_wave_kernel<KT, KAPPA>), 64 * kSimWaves, lds);
+    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(simulate_wave_kernel<KT, KAPPA>), 64 * waves, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
     const int n_cu = device_cu_count(d.device);
     int grid = per_cu * n_cu;
-    const int need = (p.B + kSimWaves - 1) / kSimWaves;
+    const int need = (p.B + waves - 1) / waves;
     if (grid > need) grid = need;
-    p.n_waves = grid * kSimWaves;
-    hipLaunchKernelGGL((simulate_wave_kernel<KT, KAPPA>), dim3(grid), dim3(64 * kSimWaves), lds, s, p);
+    p.n_waves = grid * waves;
+    hipLaunchKernelGGL((simulate_wave_kernel<KT, KAPPA>), dim3(grid), dim3(64 * waves), lds, s, p);
     return hipGetLastError();
 }
 
 // hipErrorNotSupported: the graph is outside what the wave kernel handles
-static hipError_t try_simulate_wave(const Dag &d, const SimArgs &a, const int32_t *kappa, hipStream_t s)
+static hipError_t try_simulate_wave(const Dag &d, const SimArgs &a, const int32_t *kappa_col, hipStream_t s)
 {
-    const int K = std::max((d.C + 63) / 64, (d.R + 63) / 64);   // slots per lane: classes, and positions of the order
-    if (d.R == 0 || d.R > 512 || d.C == 0 || K > 8 || !d.d_col_cls || !d.d_run_ptr || !d.d_cls_depT || !d.d_bad_order)
+    if (d.R == 0 || d.R > 512 || d.C == 0 || !d.d_col_cls || !d.d_cls_depT || !d.d_bad_order)
         return hipErrorNotSupported;
     SimWaveParams p{};
     p.B = a.B; p.R = d.R; p.C = d.C; p.N = d.N;
     p.col_cls = d.d_col_cls; p.run_ptr = d.d_run_ptr; p.run_lo = d.d_run_lo; p.run_hi = d.d_run_hi;
-    p.depT = reinterpret_cast<const uint32_t *>(d.d_cls_depT); p.Cpad = d.Cpad; p.bad_order = d.d_bad_order;
-    p.order = a.order; p.order_stride = a.order_stride; p.kappa = kappa;
+    p.cls_cnt0 = d.d_cls_cnt0; p.depT = reinterpret_cast<const uint32_t *>(d.d_cls_depT); p.Cpad = d.Cpad; p.bad_order = d.d_bad_order;
+    p.order = a.order; p.order_stride = a.order_stride; p.kappa_col = kappa_col;
     p.op_time = a.op_time; p.recv_time = a.recv_time; p.f32 = a.f32 ? 1 : 0;
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
-    // (more than two runs per row on average, as with the channels' classes)
-#define SW_LAUNCH(k)                                                                      \
-    if (K <= k) return kappa ? launch_sim_wave<k, kKappaTable>(p, d, s)                   \
-                     : d.n_runs <= 2 * d.C ? launch_sim_wave<k, kKappaRuns>(p, d, s) : launch_sim_wave<k, kKappaWalk>(p, d, s);
-    SW_LAUNCH(1) SW_LAUNCH(2) SW_LAUNCH(3) SW_LAUNCH(4) SW_LAUNCH(5) SW_LAUNCH(6) SW_LAUNCH(7)
-    SW_LAUNCH(8)
+    // Rows of more than two runs on average, or more classes than the registers of a lane hold: by recv.  65 536 samples, an order
+    // each, by run and by recv: 24 x 20 layered ops, 300 recvs 3.59 and 0.58 ms; 21 x 18 and 28, 227 and 107 us; resnet50, less
+    // than one run, 187 and 222 us; inception3 844 and 839.
+    const int kr = (d.R + 63) / 64, K = std::max((d.C + 63) / 64, kr);      // slots per lane: positions; classes as well
+#define SW_LAUNCH_EACH(k, kappa)                                                          \
+    SW_LAUNCH(k, 1, kappa) SW_LAUNCH(k, 2, kappa) SW_LAUNCH(k, 3, kappa) SW_LAUNCH(k, 4, kappa)     \
+    SW_LAUNCH(k, 5, kappa) SW_LAUNCH(k, 6, kappa) SW_LAUNCH(k, 7, kappa) SW_LAUNCH(k, 8, kappa)
+#define SW_LAUNCH(k, n, kappa) if (k <= n) return launch_sim_wave<n, kappa>(p, d, s);
+    if (kappa_col) {
+        SW_LAUNCH_EACH(kr, kKappaTable)
+    } else if (K > 8 || !d.d_run_ptr || d.n_runs > 2 * d.C) {
+        SW_LAUNCH_EACH(kr, kKappaLoop)
+    } else {
+        SW_LAUNCH_EACH(K, kKappaRuns)
+    }
     return hipErrorNotSupported;
 }
 
@@ -860,18 +916,20 @@ hipError_t launch_simulate(Dag &d, const SimArgs &a, hipStream_t s)
     p.op_time = a.op_time; p.recv_time = a.recv_time; p.f32 = a.f32 ? 1 : 0;
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
     const bool shared = a.order_stride == 0 && d.R > 0 && d.C > 0;
+    int32_t *kappa_col = nullptr;
     if (shared) {
-        const size_t lds = (size_t)d.R * 4;
+        const size_t lds = ((size_t)d.R + kKappaBlock) * 4;
         if (!d.d_bad_order || lds > 48 * 1024) return hipErrorInvalidValue;
-        hipError_t e = ensure_workspace(&d, (size_t)d.C * sizeof(int32_t));
+        hipError_t e = ensure_workspace(&d, ((size_t)d.C + 3 + d.N) * sizeof(int32_t));
         if (e != hipSuccess) return e;
         int32_t *kappa = static_cast<int32_t *>(d.d_work);
-        hipLaunchKernelGGL(kappa_kernel, dim3((d.C + 255) / 256), dim3(256), lds, s, d.R, d.W, d.C, d.d_cls_dep, a.order, kappa,
-                           d.d_bad_order);
+        kappa_col = kappa + ((d.C + 3) & ~3);           // (read four at a time)
+        hipLaunchKernelGGL(kappa_kernel, dim3((d.C + kKappaBlock - 1) / kKappaBlock), dim3(256), lds, s, d.R, d.W, d.C, d.d_cls_dep,
+                           a.order, d.d_cls_ptr, d.d_cls_cols, d.d_col_cls, kappa, kappa_col, d.d_bad_order);
         p.kappa = kappa;
     }
     {
-        const hipError_t e = try_simulate_wave(d, a, p.kappa, s);
+        const hipError_t e = try_simulate_wave(d, a, kappa_col, s);
         if (e != hipErrorNotSupported) return e;
     }
     if (!shared) {

@@ -103,6 +103,43 @@ def test_consecutive_positions(tt, name):
                 h.check_orders()
 
 
+# more classes than the registers of a lane hold, about as many recvs as are tried first, rows with few and with all recvs
+RELEASES = {f"layered{r}": (lambda r=r: layered(45, 30, r, (2, 9))) for r in (4, 31, 32, 33, 63, 65, 192, 300, 511, 512)}
+RELEASES["wide"] = lambda: layered(4, 300, 260, (3, 12))
+RELEASES["chain512"] = lambda: chain(512, 40)
+
+
+@pytest.mark.parametrize("name", list(RELEASES))
+def test_release_positions(tt, name):
+    d = RELEASES[name]()
+    R, B = d.n_recv, 29
+    args = (d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    h = tt.build_deps(*args)
+    rng = np.random.default_rng(8)
+    orders = np.stack([rng.permutation(R) for _ in range(B)]).astype(np.int32)
+    op = rng.integers(0, 50, size=(B, d.n_compute)).astype(np.float64) * wl.QUANTUM
+    rv = rng.integers(0, 50, size=(B, R)).astype(np.float64) * wl.QUANTUM
+    print(f"[releases] {name}: classes={h.n_classes} R={R}", flush=True)
+    for o in (orders, orders[0]):
+        exp = oracle.simulate(*args, o, op, rv)
+        for g, e in zip(tt.simulate(h, cuda(o), cuda(op), cuda(rv)), exp):
+            assert np.array_equal(g.cpu().numpy(), e)
+        for g, e in zip(tt.simulate(h, cuda(o), cuda(op).float(), cuda(rv).float()), exp):     # (float32 holds the values)
+            assert np.array_equal(g.cpu().numpy(), e)
+    h.check_orders()
+    clean = tt.simulate(h, cuda(orders), cuda(op), cuda(rv))[0].cpu().numpy()
+    for wrong in (orders[7, 0], R, -1):
+        bad = orders.copy()
+        bad[7, R - 1] = wrong
+        got = tt.simulate(h, cuda(bad), cuda(op), cuda(rv))[0].cpu().numpy()
+        assert np.array_equal(np.delete(got, 7), np.delete(clean, 7))
+        with pytest.raises(tt.TicTacError):
+            h.check_orders()
+        tt.simulate(h, cuda(bad[7]), cuda(op), cuda(rv))
+        with pytest.raises(tt.TicTacError):
+            h.check_orders()
+
+
 # class slots per lane (one register kernel for each, two slots apart above eight), words of the rows, waves that fit
 SLOTS = {
     "chain385": lambda: chain(385), "chain1000": lambda: chain(1000, 1),
