@@ -513,8 +513,8 @@ tac_reg_kernel(const TacRegParams p)
                 // b precedes a when min{P_a, Time(b)} < min{P_b, Time(a)}.  A tie is left to
                 // the general path below.
                 const int a_ = min(q0, q1), b_ = max(q0, q1);
-                const double xa = min_f64(P[a_], t[b_]);
-                const double ya = min_f64(P[b_], t[a_]);
+                const double xa = fmin(P[a_], t[b_]);
+                const double ya = fmin(P[b_], t[a_]);
                 if (__ballot(xa != ya) != 0ull) {               // (the same in every lane)
                     const int best = __ballot(xa < ya) != 0ull ? b_ : a_;
                     qm = 1; q0 = a_ + b_ - best;

@@ -137,8 +137,8 @@ simulate_sends_kernel(const SendSimParams p)
                 if (ends) break;
             }
             if (__ballot(any_send) != 0ull) {
-                up_busy = max_f64(up_busy, at) + wave_sum_f64_dpp(sent);
-                m = max_f64(m, up_busy);
+                up_busy = fmax(up_busy, at) + wave_sum_f64_dpp(sent);
+                m = fmax(m, up_busy);
             }
         };
 
@@ -162,7 +162,7 @@ simulate_sends_kernel(const SendSimParams p)
                 if (k >= R) break;                                  // nothing ready and no transfer left
                 // the device idles until the next transfer ends
                 const double at = uniform(F[k]);
-                t_dev = max_f64(t_dev, at);
+                t_dev = fmax(t_dev, at);
                 do {
                     release(__builtin_amdgcn_readfirstlane(rop[k]), uniform(F[k]));
                     ++k;
@@ -190,13 +190,13 @@ simulate_sends_kernel(const SendSimParams p)
             }
             release(v_beg, finish);
             t_dev = finish;
-            m = max_f64(m, finish);
+            m = fmax(m, finish);
         }
-        if (R > 0) m = max_f64(m, uniform(F[R - 1]));
+        if (R > 0) m = fmax(m, uniform(F[R - 1]));
 
         if (lane == 0) {
             const double U = sum_c + sum_r + sum_s;
-            const double L = max_f64(max_f64(sum_c, sum_r), sum_s);
+            const double L = fmax(fmax(sum_c, sum_r), sum_s);
             p.makespan[b] = m;
             p.eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);
             if (p.U) p.U[b] = U;
@@ -434,13 +434,13 @@ simulate_sends_lanes_kernel(const SendLaneParams p)
                 if (idle && k >= R) break;                  // nothing ready and no transfer left
                 uint2 rv = make_uint2(kNoEntry, 0u);
                 if (idle) {
-                    t_dev = max_f64(t_dev, cur.end);           // the device idles until the next transfer ends
+                    t_dev = fmax(t_dev, cur.end);           // the device idles until the next transfer ends
                 } else {
                     if (v != ahead) { ahead_rec = rec[v]; ahead_x = ot[v]; }
                     rv = ahead_rec;
                     t_dev += ahead_x;
                     sum_c += ahead_x;
-                    m = max_f64(m, t_dev);
+                    m = fmax(m, t_dev);
                     // (a send is not run: its time is not touched here)
                     ahead = (rv.x & (0x2000u | kNoEntry)) ? v : (int)(rv.x & 0x1fffu);
                     ahead_rec = rec[ahead];
@@ -474,7 +474,7 @@ simulate_sends_lanes_kernel(const SendLaneParams p)
                 }
                 release(rv.x, rv.y, t_dev);
             }
-            m = max_f64(m, sum_r);
+            m = fmax(m, sum_r);
         }
         __threadfence_block();
         wave_sync();
@@ -508,21 +508,21 @@ simulate_sends_lanes_kernel(const SendLaneParams p)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const double inc = wave_incl_scan_f64_dpp(x[q]);
-                    if (op[q] >= 0) last[q] = max_f64(last[q], at[q] + (acc[q] + inc));
+                    if (op[q] >= 0) last[q] = fmax(last[q], at[q] + (acc[q] + inc));
                     acc[q] += lane63_f64(inc);
                 }
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const double end = wave_max_f64_dpp(last[q]);
-                m = lane == j0 + q ? max_f64(m, end) : m;
+                m = lane == j0 + q ? fmax(m, end) : m;
                 sum_s = lane == j0 + q ? acc[q] : sum_s;
             }
         }
 
         if (lane < here) {
             const double U = sum_c + sum_r + sum_s;
-            const double Lb = max_f64(max_f64(sum_c, sum_r), sum_s);
+            const double Lb = fmax(fmax(sum_c, sum_r), sum_s);
             p.makespan[b] = m;
             p.eff[b] = (U == Lb) ? 1.0 : (U - m) / (U - Lb);
             if (p.U) p.U[b] = U;
