@@ -475,6 +475,8 @@ struct SimChanParams {
     int32_t B, R, C, N, n_waves, wave_bytes, levels, n_channels, chan_bytes;
     int32_t nb, arr_doubles;    // blocks of four recvs; doubles for the arrivals
     int32_t cls_lane, cls_slot; // class of lane l's k-th slot: l * cls_lane + k * cls_slot
+    const uint32_t *depT;       // rows of many runs: cls_depT in halves, as above; else NULL
+    int32_t Cpad;
     const int32_t *col_cls, *run_ptr, *run_lo, *run_hi;
     const int32_t *chan;        // [R] channel of every recv, 0 <= chan < n_channels <= 64
     const int32_t *order;
@@ -489,7 +491,7 @@ struct SimChanParams {
 // The classes of a lane are consecutive too where rows are short: classes that are released together (neighbours, mostly) are
 // then added up in the lane.  Where rows have many runs they are l, l + 64, ...: lanes wait for the longest row of a slot, and
 // neighbours have rows of similar length.  (More than two runs per row on average; resnet50, less than one, four channels: 257 us
-// with consecutive classes, 343 without; 24 x 20 layered ops, 300 recvs: 6.9 and 6.2 ms.)
+// with consecutive classes, 343 without; 24 x 20 layered ops, 300 recvs, all run by run: 6.9 and 6.2 ms.)
 // The order is checked on the way.  65 536 samples, four channels, with the check: inception3 1 188 -> 1 000 us (a scan per channel
 // and 64 positions before, 26 % more vector instructions), resnet50 357 -> 257 us.  Waves wait for the op_time row two thirds of
 // their time; the registers (an occupancy bound per KT: where spills of a few words cost less than a wave) and LDS, which holds
@@ -658,9 +660,27 @@ simulate_channels_kernel(const SimChanParams p)
         };
         double rho[KT];
 #pragma unroll
+        for (int k = 0; k < KT; ++k) rho[k] = 0.0;
+        if (p.depT) {
+            // Rows of many runs: most hold one of the recvs that arrive late.  The maximum over those of them that the row holds
+            // is the maximum over the row, whatever the line between late and not.
+            const double line = last_arrival * max(0.0, 1.0 - 32.0 / R);
+#pragma unroll
+            for (int q = 0; q < D; ++q) {
+                for (uint64_t late = __ballot(of[q] >= 0 && a[q] >= line); late != 0ull; late &= late - 1ull) {
+                    const int l = __builtin_ctzll(late), r = __builtin_amdgcn_readlane(of[q], l) & 1023;
+                    const double at_r = readlane_f64(a[q], l);
+                    const uint32_t *word = p.depT + ((size_t)(r >> 6) * p.Cpad + lane) * 2 + (r >> 5 & 1);
+#pragma unroll
+                    for (int k = 0; k < KT; ++k)
+                        if (k * 64 < C && (word[(size_t)min(k * 64, p.Cpad - 64) * 2] >> (r & 31) & 1u) && at_r > rho[k]) rho[k] = at_r;
+                }
+            }
+        }
+#pragma unroll
         for (int k = 0; k < KT; ++k) {
-            double m = 0.0;
-            const int n = (int)(ra[k] >> 20);
+            double m = rho[k];
+            const int n = m > 0.0 ? 0 : (int)(ra[k] >> 20);
             if (n > 0) m = range_max(m, (int)(ra[k] & 1023u), (int)((ra[k] >> 10) & 1023u));
             if (n > 1) m = range_max(m, (int)(rc[k] & 1023u), (int)(rc[k] >> 10));
             if (n > 2) {
@@ -769,6 +789,10 @@ static hipError_t launch_sim_chan(SimChanParams &p, const Dag &d, hipStream_t s)
     const size_t arr_doubles = ((size_t)4 * nb + 2) & ~(size_t)1;             // (sums by rank: one more than there are recvs)
     p.arr_doubles = (int32_t)arr_doubles;
     const size_t wave_bytes = (arr_doubles + x_doubles) * 8;                    // a multiple of 16
+    // (trying the late recvs costs what several runs cost: 65 536 samples, four channels, three runs per row (tiny) 106 us without,
+    // 132 with; six (21 x 18 layered ops, 28 recvs) 303 either way; 42 (24 x 20 and 300) 5 498 and 1 878)
+    p.depT = d.n_runs <= 8 * d.C ? nullptr : reinterpret_cast<const uint32_t *>(d.d_cls_depT);
+    p.Cpad = d.Cpad;
     p.cls_lane = d.n_runs <= 2 * d.C ? KT : 1;
     p.cls_slot = d.n_runs <= 2 * d.C ? 1 : 64;
     int waves = 4;

@@ -63,16 +63,18 @@ struct SearchParams {
 };
 
 constexpr int kSearchWaves = 4;
+constexpr int kWalk = 32;                // recvs that are tried first where rows have many runs
 
 __device__ __forceinline__ uint64_t uniform_u64(uint64_t x)      // the same in every lane
 {
     return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 
+#define OS_EACH_T(F) F(1) F(2) F(3) F(4) F(5) F(6) F(7) F(8)
 #define OS_EACH(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7)
 
 // T slots per lane for classes (64 T >= C), and D of consecutive positions (64 D >= R)
-template <int T>
+template <int T, bool WALK>
 __global__ void __launch_bounds__(64 * kSearchWaves)
 order_search_kernel(const SearchParams p)
 {
@@ -143,10 +145,20 @@ order_search_kernel(const SearchParams p)
             for (int i = lane; i < R; i += 64) cur[i] = max(prev[i], prev[min(i + h, R - 1)]);
             wave_sync();
         }
+        // (rows of many runs: most hold one of the recvs that come last)
+        if constexpr (WALK) {
+            const int last = max(0, R - kWalk);
+#pragma unroll 4
+            for (int i = R - 1; i >= last; --i) {
+                const uint64_t *has = holders + (size_t)ordl[i] * T;
+#define OS_LATE(k) if constexpr (k < T) { if (kn_##k == 0 && (has[k] >> lane & 1ull)) kn_##k = i + 1; }
+                OS_EACH(OS_LATE)
+            }
+        }
 #define OS_KAPPA0(k)                                                                      \
         if constexpr (k < T) {                                                            \
             const int c = lane * T + k;                                                   \
-            if (c < C) {                                                                  \
+            if (c < C && (!WALK || kn_##k == 0)) {                                        \
                 const int rend = p.run_ptr[c + 1];                                        \
                 int m = 0;                                                                \
                 for (int q = p.run_ptr[c]; q < rend; ++q) {                               \
@@ -329,7 +341,7 @@ order_search_kernel(const SearchParams p)
     }
 }
 
-template <int T>
+template <int T, bool WALK>
 static hipError_t launch_search_t(SearchParams &p, const Dag &d, hipStream_t s)
 {
     int levels = 1;
@@ -347,11 +359,11 @@ static hipError_t launch_search_t(SearchParams &p, const Dag &d, hipStream_t s)
     p.rows_bytes = (int32_t)rows_bytes;
     hipError_t e;
     if (lds > 48 * 1024) {
-        e = ensure_dynamic_lds(reinterpret_cast<const void *>(order_search_kernel<T>), lds);
+        e = ensure_dynamic_lds(reinterpret_cast<const void *>(order_search_kernel<T, WALK>), lds);
         if (e != hipSuccess) return e;
     }
     int per_cu = 0;
-    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(order_search_kernel<T>), 64 * kSearchWaves, lds);
+    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(order_search_kernel<T, WALK>), 64 * kSearchWaves, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
     const int n_cu = device_cu_count(d.device);
@@ -359,7 +371,7 @@ static hipError_t launch_search_t(SearchParams &p, const Dag &d, hipStream_t s)
     const int need = (p.B + kSearchWaves - 1) / kSearchWaves;
     if (grid > need) grid = need;
     p.n_waves = grid * kSearchWaves;
-    hipLaunchKernelGGL((order_search_kernel<T>), dim3(grid), dim3(64 * kSearchWaves), lds, s, p);
+    hipLaunchKernelGGL((order_search_kernel<T, WALK>), dim3(grid), dim3(64 * kSearchWaves), lds, s, p);
     return hipGetLastError();
 }
 
@@ -372,18 +384,16 @@ hipError_t launch_order_search(Dag &d, const SearchArgs &a, hipStream_t s)
     p.B = a.B; p.R = d.R; p.C = d.C; p.N = d.N; p.W = d.W; p.n_moves = a.n_moves;
     p.col_cls = d.d_col_cls; p.cls_depT = d.d_cls_depT; p.Cpad = d.Cpad;
     p.run_ptr = d.d_run_ptr; p.run_lo = d.d_run_lo; p.run_hi = d.d_run_hi;
+    // Trying 32 recvs costs what eight runs or so cost: with seven runs per row (18 x 17 layered ops, 45 recvs) it is neither here nor
+    // there, with 17 (12 x 10 and 100) 4 290 samples, 107 moves take 51 us instead of 61, with 42 (24 x 20 and 300) 190 instead of 367.
+    const bool walk = d.n_runs > 8 * d.C;
     p.order = a.order; p.order_stride = a.order_stride; p.moves = a.moves;
     p.op_time = a.op_time; p.recv_time = a.recv_time;
     p.best_order = a.best_order; p.best_makespan = a.best_makespan;
     p.start_makespan = a.start_makespan; p.n_accepted = a.n_accepted;
-    if (K <= 1) return launch_search_t<1>(p, d, s);
-    if (K <= 2) return launch_search_t<2>(p, d, s);
-    if (K <= 3) return launch_search_t<3>(p, d, s);
-    if (K <= 4) return launch_search_t<4>(p, d, s);
-    if (K <= 5) return launch_search_t<5>(p, d, s);
-    if (K <= 6) return launch_search_t<6>(p, d, s);
-    if (K <= 7) return launch_search_t<7>(p, d, s);
-    return launch_search_t<8>(p, d, s);
+#define OS_LAUNCH(k) if (K <= k) return walk ? launch_search_t<k, true>(p, d, s) : launch_search_t<k, false>(p, d, s);
+    OS_EACH_T(OS_LAUNCH)
+    return hipErrorNotSupported;
 }
 
 }  // namespace tictac
