@@ -198,15 +198,44 @@ __device__ __forceinline__ void load4(const float *__restrict__ q, double (&x)[4
     x[0] = (double)a.x; x[1] = (double)a.y; x[2] = (double)a.z; x[3] = (double)a.w;
 }
 
+// a + b; what is rounded off is added to `lost`
+__device__ __forceinline__ double add_exact(double a, double b, double &lost)
+{
+    const double s = a + b, bb = s - a;
+    lost += (a - (s - bb)) + (b - bb);
+    return s;
+}
+
+// x to sums[at] (at < 0: nowhere), a wave with one place, or rows of 16 lanes with one, by one addition for all of them: many
+// lanes with the same place would be added one after the other, which takes its time and rounds more.
+__device__ __forceinline__ void add_by_rows(double *sums, int at, double x, int lane)
+{
+    if (__ballot(at == __builtin_amdgcn_readfirstlane(at)) == ~0ull) {
+        const double all = wave_sum_f64_dpp(x);
+        if (lane == 0 && at >= 0) atomicAdd(&sums[at], all);
+        return;
+    }
+    const uint64_t same = __ballot(at == dpp0_i32<0x111>(at)) | 0x0001000100010001ull;
+    const bool whole = ((same >> (lane & 48)) & 0xffffull) == 0xffffull;
+    double all = x;
+    all += dpp0_f64<0x128>(all);
+    all += dpp0_f64<0x124>(all);
+    all += dpp0_f64<0x122>(all);
+    all += dpp0_f64<0x121>(all);
+    if (at >= 0 && (!whole || (lane & 15) == 0)) atomicAdd(&sums[at], whole ? all : x);
+}
+
 // totals[cls_of[j]] += row[j] for j in [0, N), totals in LDS, by one wave.  A lane takes four
 // consecutive columns at a time and first adds up runs of equal class in registers: columns of
 // one class tend to sit next to each other, and every LDS add of several lanes to one address
 // is served one lane after the other.
-template <typename T>
+// ROWS: neighbours in the row mostly go to one place (add_by_rows)
+template <bool ROWS = false, typename T>
 __device__ __forceinline__ void class_totals(double *totals, const T *__restrict__ row,
                                              const int32_t *__restrict__ cls_of, int N, int lane)
 {
-    for (int j0 = lane * 4; j0 < N; j0 += 64 * 4 * 2) {          // two groups of four in flight per lane
+    for (int j0 = lane * 4; (ROWS ? j0 - lane * 4 : j0) < N; j0 += 64 * 4 * 2) {     // (ROWS: no lane leaves before the others)
+        // two groups of four in flight per lane
         double x[2][4];
         int c[2][4];
 #pragma unroll
@@ -224,6 +253,8 @@ __device__ __forceinline__ void class_totals(double *totals, const T *__restrict
                 }
             }
         }
+        [[maybe_unused]] double acc0 = 0.0;
+        [[maybe_unused]] int cur0 = -1;
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             double acc = x[g][0];
@@ -238,16 +269,29 @@ __device__ __forceinline__ void class_totals(double *totals, const T *__restrict
                     acc = x[g][i];
                 }
             }
-            if (cur >= 0) atomicAdd(&totals[cur], acc);
+            if constexpr (ROWS) {
+                if (g == 0) {
+                    acc0 = acc;
+                    cur0 = cur;
+                } else if (__ballot(cur == cur0) == ~0ull) {
+                    add_by_rows(totals, cur, acc0 + acc, lane);
+                } else {
+                    add_by_rows(totals, cur0, acc0, lane);
+                    add_by_rows(totals, cur, acc, lane);
+                }
+            } else if (cur >= 0) {
+                atomicAdd(&totals[cur], acc);
+            }
         }
     }
 }
 
+template <bool ROWS = false>
 __device__ __forceinline__ void class_totals(double *totals, const TimeRow &row, const int32_t *__restrict__ cls_of,
                                              int N, int lane)
 {
-    if (row.f32) class_totals(totals, row.as_f32(), cls_of, N, lane);
-    else class_totals(totals, row.as_f64(), cls_of, N, lane);
+    if (row.f32) class_totals<ROWS>(totals, row.as_f32(), cls_of, N, lane);
+    else class_totals<ROWS>(totals, row.as_f64(), cls_of, N, lane);
 }
 
 __device__ __forceinline__ int wave_min_i32(int v)

@@ -384,7 +384,8 @@ tac_frontier_kernel(const FrontierParams p)
         double ta = 0.0, tb = 0.0;
         int nf = 0, ns = 0, nl = 0;                         // entries of frontier, stack, log (uniform)
         bool over = false;                                  // a list was too short (uniform)
-        double F = 0.0, busy = free_time, sum_c = free_time;
+        // (sums with what was rounded off beside them: one after the other, their error is otherwise twice that of a tree)
+        double F = 0.0, busy = free_time, sum_c = free_time, F_lo = 0.0, busy_lo = 0.0, sum_lo = 0.0;
         int mine = 0;                                       // the order, by the lane of step mod 64
 
         const auto push = [&](bool in, uint32_t v) {
@@ -517,9 +518,10 @@ tac_frontier_kernel(const FrontierParams p)
                     if (lane + 64 == pos) rb = -1;
                 }
                 if (lane == 0) alive[best >> 5] &= ~(1u << (best & 31));
-                F += ts;
-                busy = max_f64(busy, F) + Ps;
-                sum_c += Ps;
+                F = add_exact(F, ts, F_lo);
+                if ((F - busy) + (F_lo - busy_lo) > 0.0) { busy = F; busy_lo = F_lo; }
+                busy = add_exact(busy, Ps, busy_lo);
+                sum_c = add_exact(sum_c, Ps, sum_lo);
                 if ((step & 63) == lane) mine = best;
                 if ((step & 63) == 63 || step == R - 1) {
                     const int s = (step & ~63) + lane;
@@ -723,6 +725,9 @@ tac_frontier_kernel(const FrontierParams p)
             Arg *q = rare();
             q->flags[b] = over ? 2 : 0;
             if (q->simulate && !over) {
+                busy += busy_lo;
+                F += F_lo;
+                sum_c += sum_lo;
                 const double m = max_f64(busy, F), U = sum_c + F, L = max_f64(sum_c, F);
                 if (q->makespan) q->makespan[b] = m;
                 if (q->eff) q->eff[b] = (U == L) ? 1.0 : (U - m) / (U - L);

@@ -255,7 +255,7 @@ simulate_wave_kernel(const SimWaveParams p)
         const int n_totals = KAPPA == kKappaTable ? R + 1 : KAPPA == kKappaLoop ? C : 64 * KT;
         for (int c = lane; c < n_totals; c += 64) csum[c] = 0.0;
         wave_sync();
-        class_totals(csum, ot, KAPPA == kKappaTable ? p.kappa_col : p.col_cls, N, lane);
+        class_totals<KAPPA == kKappaTable>(csum, ot, KAPPA == kKappaTable ? p.kappa_col : p.col_cls, N, lane);
         wave_sync();
 #define SW_DECL(k) [[maybe_unused]] double ct_##k = 0.0; [[maybe_unused]] int kap_##k = 0;
         SW_EACH_K(SW_DECL)
@@ -331,8 +331,10 @@ simulate_wave_kernel(const SimWaveParams p)
             }
             SW_EACH_K(SW_KAPPA_RUNS)
             if constexpr (KAPPA == kKappaLoop) {
-                for (int c = lane; c < C; c += 64) {
-                    const double ct = csum[c];
+                for (int c0 = 0; c0 < C; c0 += 64) {            // (all lanes take part in the last step)
+                    const int c = min(c0 + lane, C - 1);
+                    const bool in = c0 + lane < C;
+                    const double ct = in ? csum[c] : 0.0;
                     int m = 0, n = 0;
                     if (p.cls_cnt0[c] > kWalkRecvs)
                         for (int i = 0; i < min(R, kWalkSteps) && m == 0; i += 4) {
@@ -352,7 +354,7 @@ simulate_wave_kernel(const SimWaveParams p)
                     }
                     m = max(m, n);
                     ct_sum += ct;
-                    atomicAdd(&A[m], ct);
+                    add_by_rows(A, in ? m : -1, ct, lane);
                 }
             }
         }
