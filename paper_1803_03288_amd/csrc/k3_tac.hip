@@ -439,13 +439,17 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
         if (e == hipSuccess) p.only_flagged = flags;
         else if (e != hipErrorNotSupported && e != hipErrorOutOfMemory) return e;
     }
-    if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && d.C <= 16 * 64) {
+    // (more than 384 recvs: where there is no room for the flags, the kernels below take the call, one of which needs none; on a
+    // stream that is being captured none can be made)
+    const bool many_recvs = d.W > 6;
+    if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && d.C <= 16 * 64 &&
+        !(many_recvs && flag_bytes + gstate_bytes > d.work_bytes && being_captured(s))) {
         hipError_t e = ensure_workspace(&d, flag_bytes + gstate_bytes);
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess && !(many_recvs && e == hipErrorOutOfMemory)) return e;
         int32_t *flags = static_cast<int32_t *>(d.d_work);
-        e = launch_tac_reg(d, a, flags, s);
+        if (e == hipSuccess) e = launch_tac_reg(d, a, flags, s);
         if (e == hipSuccess) p.only_flagged = flags;
-        else if (e != hipErrorNotSupported) return e;
+        else if (e != hipErrorNotSupported && e != hipErrorOutOfMemory) return e;
     }
     if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && !small) {
         // (the workspace is sized for the general kernel's pass over the flagged samples as well, so that the block is not

@@ -38,7 +38,7 @@ constexpr int kKappaBlock = 64;             // classes per workgroup, whose colu
 __global__ void __launch_bounds__(256)
 kappa_kernel(int32_t R, int32_t W, int32_t C, const uint64_t *__restrict__ cls_dep, const int32_t *__restrict__ order,
              const int32_t *__restrict__ cls_ptr, const int32_t *__restrict__ cls_cols, const int32_t *__restrict__ col_cls,
-             int32_t *kappa /*[C]*/, int32_t *kappa_col /*[N]*/, int32_t *bad_order)
+             int32_t *kappa /*[C]*/, int32_t *kappa_col /*[N] or NULL*/, int32_t *bad_order)
 {
     extern __shared__ int32_t pos[];        // [R], then [kKappaBlock] kappa
     int32_t *mine = pos + R;
@@ -71,6 +71,7 @@ kappa_kernel(int32_t R, int32_t W, int32_t C, const uint64_t *__restrict__ cls_d
         mine[c - c0] = kap;
     }
     __syncthreads();
+    if (!kappa_col) return;
     const int end = cls_ptr[min(c0 + kKappaBlock, C)];
     for (int m = cls_ptr[c0] + threadIdx.x; m < end; m += 256) {
         const int j = cls_cols[m];
@@ -946,15 +947,22 @@ hipError_t launch_simulate(Dag &d, const SimArgs &a, hipStream_t s)
     if (shared) {
         const size_t lds = ((size_t)d.R + kKappaBlock) * 4;
         if (!d.d_bad_order || lds > 48 * 1024) return hipErrorInvalidValue;
-        hipError_t e = ensure_workspace(&d, ((size_t)d.C + 3 + d.N) * sizeof(int32_t));
+        // (where there is no room for a word per column, also on a stream that is being captured: by class, in the last kernel)
+        const size_t by_class = (size_t)d.C * sizeof(int32_t), by_col = by_class + (3 + (size_t)d.N) * sizeof(int32_t);
+        bool cols = d.R <= 512 && !(by_col > d.work_bytes && being_captured(s));
+        hipError_t e = ensure_workspace(&d, cols ? by_col : by_class);
+        if (e == hipErrorOutOfMemory && cols) {
+            cols = false;
+            e = ensure_workspace(&d, by_class);
+        }
         if (e != hipSuccess) return e;
         int32_t *kappa = static_cast<int32_t *>(d.d_work);
-        kappa_col = kappa + ((d.C + 3) & ~3);           // (read four at a time)
+        if (cols) kappa_col = kappa + ((d.C + 3) & ~3);         // (read four at a time)
         hipLaunchKernelGGL(kappa_kernel, dim3((d.C + kKappaBlock - 1) / kKappaBlock), dim3(256), lds, s, d.R, d.W, d.C, d.d_cls_dep,
                            a.order, d.d_cls_ptr, d.d_cls_cols, d.d_col_cls, kappa, kappa_col, d.d_bad_order);
         p.kappa = kappa;
     }
-    {
+    if (!shared || kappa_col) {
         const hipError_t e = try_simulate_wave(d, a, kappa_col, s);
         if (e != hipErrorNotSupported) return e;
     }

@@ -244,6 +244,32 @@ def test_a_first_tac_call_under_capture(lib):
     lib.free(h)
 
 
+def test_many_recvs_without_room_for_flags(lib):
+    """A graph with more than 384 recvs, whose general kernel needs no workspace, is taken without one: on a stream that is
+    being captured, and where the device has no memory left."""
+    d = wl.layered_dag(17, levels=8, width=8, fan_in=(1, 3), back=3, n_recv=400, attach=(1, 4))
+    rc, h = lib.build(d)
+
+    def which():
+        lib.host_forget_launches()
+        rc = lib.tac(h, d, 50)
+        assert rc == 0, lib.error()
+        return ["tac_reg" if "tac_reg" in k else "tac" for k in lib.kernels() if "tac" in k]
+
+    lib.host_capturing(1)
+    assert which() == ["tac"]
+    lib.host_capturing(0)
+    lib.tictac_trim_memory()
+    lib.host_device_limit(lib.count("device_bytes"))
+    assert which() == ["tac"]
+    lib.host_device_limit(-1)
+    assert which() == ["tac_reg", "tac"]
+    lib.host_capturing(1)
+    assert which() == ["tac_reg", "tac"]
+    lib.host_capturing(0)
+    lib.free(h)
+
+
 def test_handles_do_not_wait_for_each_others_tables(lib):
     """Four threads make the tables of a handle each while every copy takes 0.2 s: side by side, not one after the other."""
     d = GRAPHS["chain"]()
