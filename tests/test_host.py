@@ -270,6 +270,32 @@ def test_many_recvs_without_room_for_flags(lib):
     lib.free(h)
 
 
+def test_one_order_without_room_for_a_word_per_column(lib):
+    """One order for all samples on a stream that is being captured: a workspace that holds a word per class but not per
+    column serves the call, by class."""
+    d = wl.layered_dag(17, levels=40, width=30, fan_in=(1, 3), back=3, n_recv=100, attach=(1, 4))
+    rc, h = lib.build(d)
+    B = 256
+    op, rv, order = np.ones((B, d.n_compute)), np.ones((B, d.n_recv)), np.arange(d.n_recv, dtype=np.int32)
+    out = [np.zeros(B) for _ in range(5)]
+
+    def which():
+        lib.host_forget_launches()
+        rc = lib.tictac_simulate(h, I32(B), ptr(order), I32(0), ptr(op), ptr(rv), *(ptr(x) for x in out), None)
+        assert rc == 0, lib.error()
+        return [name for name in ("simulate_wave", "simulate_kernel") if any(name in k for k in lib.kernels())]
+
+    assert lib.tac(h, d, 1000) == 0             # (leaves a word per sample)
+    lib.host_capturing(1)
+    assert which() == ["simulate_kernel"]
+    lib.host_capturing(0)
+    assert which() == ["simulate_wave"]
+    lib.host_capturing(1)
+    assert which() == ["simulate_wave"]
+    lib.host_capturing(0)
+    lib.free(h)
+
+
 def test_handles_do_not_wait_for_each_others_tables(lib):
     """Four threads make the tables of a handle each while every copy takes 0.2 s: side by side, not one after the other."""
     d = GRAPHS["chain"]()
