@@ -302,7 +302,9 @@ simulate_wave_kernel(const SimWaveParams p)
                 if (q * 64 + lane < R) bad |= (unsigned)or_##q >= (unsigned)R || pos[or_##q] != q * 64 + lane + 1; \
             }
             SW_EACH_K(SW_CHECK)
-            [[maybe_unused]] const int late = KAPPA == kKappaLoop && lane < kWalkSteps && lane < R ? min((unsigned)ord[R - 1 - lane], (unsigned)R - 1) : 0;      // the recvs that come last, last one first
+            // the recvs that come last, last one first (an invalid entry is skipped)
+            [[maybe_unused]] const int late = KAPPA == kKappaLoop && lane < kWalkSteps && lane < R ? ord[R - 1 - lane] : -1;
+            [[maybe_unused]] const uint32_t is_late = (uint32_t)__ballot((unsigned)late < (unsigned)R);
             // level j of the table: maximum over [i, min(i + 2^j, R))
             for (int j = 1; KAPPA != kKappaLoop && j < p.levels; ++j) {
                 const uint16_t *prev = pos + (size_t)(j - 1) * R;
@@ -342,12 +344,12 @@ simulate_wave_kernel(const SimWaveParams p)
                             uint32_t w[4];
 #pragma unroll
                             for (int j = 0; j < 4; ++j) {
-                                const int r = __builtin_amdgcn_readlane(late, i + j);
+                                const int r = is_late >> (i + j) & 1u ? __builtin_amdgcn_readlane(late, i + j) : 0;
                                 w[j] = p.depT[((size_t)(r >> 6) * p.Cpad + c) * 2 + (r >> 5 & 1)] >> (r & 31) & 1u;
                             }
 #pragma unroll
                             for (int j = 3; j >= 0; --j)
-                                if (w[j] && i + j < R) m = R - (i + j);
+                                if (w[j] && is_late >> (i + j) & 1u) m = R - (i + j);
                         }
                     for (int h = 0; m == 0 && 32 * h < R; h += 2) {
                         const uint2 row = *reinterpret_cast<const uint2 *>(p.depT + ((size_t)(h >> 1) * p.Cpad + c) * 2);

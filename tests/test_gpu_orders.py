@@ -95,3 +95,32 @@ def test_orders_are_checked_on_the_device(tt, name):
     tt.simulate(h, o, gop, grv)
     h.check_orders()
     h.close()
+
+
+@pytest.mark.parametrize("R", [33, 70, 300])
+def test_entries_out_of_range_are_skipped(tt, R):
+    """A sample whose order holds entries out of range comes out as if these steps transferred nothing, and the recvs that
+    are left out were there from the start: also where the recvs that come last are tried first."""
+    d = wl.layered_dag(29, levels=12, width=50, fan_in=(1, 3), back=3, n_recv=R, attach=(1, 4))
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    dep = h.deps().cpu().numpy().view(np.uint8).reshape(d.n_ops, -1)
+    holds = np.unpackbits(dep, axis=1, bitorder="little")[d.compute_ids(), :R].astype(bool)
+    rng = np.random.default_rng(4)
+    B = 24
+    op, rv = wl.timing_samples(d, 0, B)
+    order = np.stack([rng.permutation(R) for _ in range(B)]).astype(np.int32)
+    for b in range(B):
+        late = R - 1 - rng.choice(min(R, 32), size=1 + b % 3, replace=False)
+        order[b, late] = rng.choice([-1, -2**31, R, R + 1, 2**31 - 1], size=late.size)
+    got = [x.cpu().numpy() for x in tt.simulate(h, cuda(order), cuda(op), cuda(rv))]
+    expect_bad(tt, h)
+    for b in range(B):
+        ok = (order[b] >= 0) & (order[b] < R)
+        F = np.cumsum(np.where(ok, rv[b, np.where(ok, order[b], 0)], 0.0))
+        pos = np.zeros(R, np.int64)
+        pos[order[b, ok]] = np.nonzero(ok)[0] + 1
+        kappa = np.where(holds, pos, 0).max(axis=1)
+        ahead = np.cumsum(np.bincount(kappa, weights=op[b], minlength=R + 1)[::-1])[::-1]       # time of the ops with kappa >= k
+        m = max(ahead[0], (F + ahead[1:]).max())
+        assert got[0][b] == m, (R, b)           # (the times are multiples of 2^-30 s: every sum is exact)
+    h.close()
