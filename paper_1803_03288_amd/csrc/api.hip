@@ -12,6 +12,7 @@
 #include <memory>
 #include <mutex>
 #include <numeric>
+#include <system_error>
 
 #include "chain_plan.h"
 #include "frontier_plan.h"
@@ -1382,10 +1383,8 @@ static std::vector<int32_t> classes_of_ops(const Dag *d)
     return cls_of_op;
 }
 
-hipError_t ensure_sliced_tables(Dag *d)
+static hipError_t make_sliced_tables(Dag *d)
 {
-    std::lock_guard<std::mutex> lock(d->tables_mutex);
-    if (d->sliced_made) return hipSuccess;
     const int32_t CW = (d->C + 63) / 64;
     if (d->R < 1 || d->W > 64 || CW > 15 * 64 * 4) {
         d->sliced_made = true;
@@ -1478,19 +1477,27 @@ hipError_t ensure_sliced_tables(Dag *d)
     return e;
 }
 
-hipError_t ensure_frontier_tables(Dag *d)
-try {
-    std::lock_guard<std::mutex> lock(d->tables_mutex);
-    FrontierTables &f = d->frontier;
-    if (f.made) return hipSuccess;
+// What the frontier form's tables hold, from the graph as given (host work only).
+static void plan_frontier(const Dag *d, FrontierPlan &p)
+{
     const std::vector<int32_t> cls_of_op = classes_of_ops(d);
-    std::vector<int32_t> recv_of_op(d->n, -1), level, order;
+    std::vector<int32_t> recv_of_op(d->n, -1), level(d->n, 0), order;
     for (int32_t i = 0; i < d->R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
+    const int32_t *row_ptr = d->h_row_ptr.data(), *col_idx = d->h_col_idx.data();
+    bool topological = true;
+    for (int32_t v = 0; v < d->n; ++v)
+        for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) {
+            topological &= col_idx[e] < v;
+            level[v] = std::max(level[v], level[col_idx[e]] + 1);
+        }
     int32_t n_levels = 0;
-    FrontierPlan p;
-    if (find_levels(d->n, d->h_row_ptr.data(), d->h_col_idx.data(), level, order, n_levels))
-        make_frontier_plan(d->n, d->R, d->C, d->h_row_ptr.data(), d->h_col_idx.data(), level.data(), cls_of_op.data(), recv_of_op.data(),
-                           d->h_cls_cnt0, d->h_col_cls, p);
+    if (topological || find_levels(d->n, row_ptr, col_idx, level, order, n_levels))
+        make_frontier_plan(d->n, d->R, d->C, row_ptr, col_idx, level.data(), cls_of_op.data(), recv_of_op.data(), d->h_cls_cnt0, d->h_col_cls, p);
+}
+
+static hipError_t commit_frontier(Dag *d, const FrontierPlan &p)
+{
+    FrontierTables &f = d->frontier;
     if (!p.ok) {
         f.made = true;
         return hipSuccess;
@@ -1518,8 +1525,34 @@ try {
     f.n_free = (int32_t)p.free_cols.size();
     f.ok = f.made = true;
     return hipSuccess;
-} catch (const std::bad_alloc &) {
-    return hipErrorOutOfMemory;
+}
+
+hipError_t ensure_large_tables(Dag *d, bool frontier)
+{
+    std::lock_guard<std::mutex> lock(d->tables_mutex);
+    frontier = frontier && !d->frontier.made;
+    if (!frontier) return d->sliced_made ? hipSuccess : make_sliced_tables(d);
+    FrontierPlan plan;
+    std::future<void> planned;              // (after what its thread works on: it ends first)
+    auto make = [&] { plan_frontier(d, plan); };
+    hipError_t e = hipSuccess, ef = hipSuccess;
+    if (!d->sliced_made) {
+        if ((int64_t)d->n + d->E > kPropThread) {
+            try {
+                planned = std::async(std::launch::async, make);
+            } catch (const std::system_error &) {           // (no thread to be had)
+            }
+        }
+        e = make_sliced_tables(d);
+    }
+    try {
+        if (planned.valid()) planned.get();
+        else make();
+        ef = commit_frontier(d, plan);
+    } catch (const std::bad_alloc &) {
+        ef = hipErrorOutOfMemory;
+    }
+    return e != hipSuccess || ef == hipErrorOutOfMemory ? e : ef;
 }
 
 hipError_t ensure_chain_tables(Dag *d)

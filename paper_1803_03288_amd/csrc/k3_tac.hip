@@ -454,8 +454,9 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
     if (!p.only_flagged && !a.sel_P && !a.sel_Mplus && !small) {
         // (the workspace is sized for the general kernel's pass over the flagged samples as well, so that the block is not
         // replaced between the two launches)
-        hipError_t e = ensure_sliced_tables(&d);
-        if (e != hipSuccess) return e;
+        const bool many = a.B > 2 * device_cu_count(d.device);
+        hipError_t e = ensure_large_tables(&d, many && (d.frontier.made || !being_captured(s)));
+        if (e != hipSuccess && !(e == hipErrorOutOfMemory && many && d.frontier.ok)) return e;
         // A sample by itself takes 1.4 times as long by the frontier form on large graphs as by the bit-sliced kernel, in which
         // sixteen waves work on it, but many more samples are under way at a time.  Bit-sliced / frontier, ms, for 64, 300,
         // 1 200 and 4 096 samples: 62 837 classes, 4 096 recvs 19 / 25, 44 / 32, 97 / 34, 265 / 48; 17 249 classes, 2 000 recvs
@@ -463,17 +464,20 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
         // 1 000 recvs 3.6 / 3.8, 3.8 / 4.0, 5.8 / 4.7, 16 / 5.9; 1 556 classes with up to 21 outstanding recvs each, 4 096
         // recvs 30 / 49, 32 / 51, 93 / 59, 255 / 134.
         int32_t *flags = nullptr;
-        bool frontier = false;
-        if (a.B > 2 * device_cu_count(d.device)) {
-            e = !d.frontier.made && being_captured(s) ? hipErrorNotSupported : ensure_frontier_tables(&d);
-            // (room for the form that takes what this one leaves, before the flags are written)
-            if (e == hipSuccess && d.frontier.ok && tac_sliced_fits(d)) e = launch_tac_sliced(d, a, flag_bytes, flag_bytes + gstate_bytes, nullptr, s, true);
-            if (e == hipSuccess) e = launch_tac_frontier(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s);
-            if (e == hipSuccess) frontier = true;
-            else if (e != hipErrorNotSupported && e != hipErrorOutOfMemory) return e;
+        bool frontier = false, sliced = e == hipSuccess && tac_sliced_fits(d);
+        if (many && d.frontier.ok) {
+            // (room for the form that takes what this one leaves, before the flags are written; where there is none the general
+            // kernel takes that as well)
+            hipError_t room = sliced ? launch_tac_sliced(d, a, flag_bytes, flag_bytes + gstate_bytes, nullptr, s, true) : hipErrorNotSupported;
+            if (room != hipSuccess && room != hipErrorNotSupported && room != hipErrorOutOfMemory) return room;
+            const hipError_t ef = launch_tac_frontier(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s);
+            if (ef != hipSuccess && ef != hipErrorNotSupported && ef != hipErrorOutOfMemory) return ef;
+            frontier = ef == hipSuccess;
+            if (frontier && room != hipSuccess) sliced = false;
+            if (!frontier && e != hipSuccess) return e;
         }
         // (after the frontier form: the samples that outgrew its lists)
-        e = tac_sliced_fits(d) ? launch_tac_sliced(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s, frontier) : hipErrorNotSupported;
+        e = sliced ? launch_tac_sliced(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s, frontier) : hipErrorNotSupported;
         if (e == hipSuccess || (frontier && e == hipErrorNotSupported)) p.only_flagged = flags;
         else if (e != hipErrorNotSupported) return e;
     }

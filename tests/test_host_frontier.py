@@ -46,10 +46,13 @@ def test_under_capture(lib):
     lib.free(h)
 
 
-def test_memory_that_runs_out(lib):
+# the second: large enough that the frontier form's tables are planned by a thread of their own
+@pytest.mark.parametrize("levels,width", [(12, 160), (20, 300)])
+def test_memory_that_runs_out(lib, levels, width):
     """Every allocation of device and of host memory that a first call makes fails once, one after the other: the call makes do
     without or says so, and the next one is as on a fresh handle."""
-    d = layered(12, 160, 300)
+    d = layered(levels, width, 300)
+    assert (d.n_ops + d.row_ptr[-1] > 16384) == (levels == 20)
     h = lib.build(d)[1]
     want = tac(lib, h, d, LARGE)
     assert "tac_frontier_kernel" in want
@@ -70,3 +73,27 @@ def test_memory_that_runs_out(lib):
                 break
         else:
             raise AssertionError("no end")
+
+
+def test_without_room_for_the_bit_sliced_form(lib):
+    """The frontier form takes a batch for which the scratch or the tables of the bit-sliced form find no room; what it leaves
+    is the general kernel's then.  With memory there again the next call is as on a fresh handle."""
+    d = GRAPHS["wide"]()
+    h = lib.build(d)[1]
+    lib.tictac_trim_memory()
+    before = lib.count("device_bytes")
+    want = tac(lib, h, d, LARGE)
+    assert want == ["tac_frontier_kernel", "tac_sliced_kernel", "tac_kernel"]
+    most = lib.count("device_bytes") - before
+    lib.free(h)
+    taken = []
+    for part in (1.0, 0.5, 0.1, 0.05, 0.02):
+        h = lib.build(d)[1]
+        lib.tictac_trim_memory()
+        lib.host_device_limit(int(lib.count("device_bytes") + part * most))
+        taken.append(tac(lib, h, d, LARGE))
+        lib.host_device_limit(-1)
+        assert lib.hipGetLastError() == 0
+        assert tac(lib, h, d, LARGE) == want
+        lib.free(h)
+    assert taken[0] == want and all(t == ["tac_frontier_kernel", "tac_kernel"] for t in taken[1:]), taken
