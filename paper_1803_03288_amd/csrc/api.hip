@@ -929,7 +929,7 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
     condense(*d, row_ptr, col_idx, recv_of_op, level, order, g);
     const int32_t M = g.M, n_node_levels = g.n_levels, max_width = g.max_width;
     const std::vector<int32_t> &nlvl_ptr = g.lvl_ptr;
-    d->M = M; d->n_node_levels = n_node_levels; d->max_node_level_width = max_width;
+    d->M = M; d->n_node_levels = n_node_levels;
     t.copied = copied_rows(g);
     d->n_copied = (int32_t)(t.copied.size() / 2);
     // words per workgroup slice, threads, and the chunks of levels of the node kernel
@@ -976,6 +976,9 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
         if (lring < 16 * per_pass && lring < n_node_levels * per_pass) lring = 0;
     }
     d->k1_lring = lring;
+    // (the records of the chunked kernel take 256 bytes per node of a pass: beside the ring there is no room for those of levels
+    // of more than 256 nodes with one-word slices, 288 with two-word slices)
+    d->k1_wide = max_width > per_pass || (lring == 0 && !d->k1_wave && k1_nodes_lds(ring, d->k1_wc, per_pass) > kK1LdsMax);
     // Rows of a multiple of eight words, levels of at most 256 nodes: the kernel with 64-byte slices (four lanes per
     // slot, or two with 32-byte slices; P slots per level, a multiple of 32 so that the slots of a wave are whole; 2048
     // slots in the ring), which the propagation of several graphs by one launch takes (make_quad_tables).
@@ -1032,7 +1035,7 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
                  [&](int32_t x) { return slot[x] >= oldest ? (slot[x] & (lring - 1)) * row_bytes : -1; },
                  [&](int32_t x) { return slot[x]; });
         }
-    } else if (max_width <= per_pass) {
+    } else if (!d->k1_wide) {
         const int32_t row_bytes = d->k1_wc * 8, zero_row = ring * row_bytes;
         t.frecs.resize(M);
         for (int32_t k = 0; k < M; ++k) {

@@ -13,6 +13,13 @@
 namespace tictac {
 
 constexpr int kK1Rpt = 4;             // positions per thread group and chunk of the node kernel
+constexpr int kK1Window = 512 + 330;    // levels whose bounds and chunks it keeps (k1_propagate.hip)
+constexpr size_t kK1LdsMax = 150 * 1024;
+// LDS bytes of the chunked node kernel, without the input lists
+inline size_t k1_nodes_lds(int32_t ring, int32_t wc, int32_t per_pass)
+{
+    return (size_t)(ring + 2) * wc * 8 + (size_t)4 * kK1Rpt * per_pass * 16 + (size_t)2 * kK1Window * 4;
+}
 
 void set_error(const char *fmt, ...);
 
@@ -56,7 +63,6 @@ struct Dag {
     // by level (of their op in the full graph; levels without a node dropped) into positions 0..M-1.
     int32_t M = 0;                  // number of nodes
     int32_t n_node_levels = 0;
-    int32_t max_node_level_width = 0;
     struct NodeRec {                // 32 bytes, one per position
         int32_t in[6];              // first inputs: q >= 0 node position, ~i < 0 recv i, INT32_MIN none
         int32_t op;                 // op id of the node
@@ -83,8 +89,9 @@ struct Dag {
         int32_t ovf;                // -1 for a fast node
     };
     int32_t k1_ring = 0;
+    bool k1_wide = false;       // a level is wider than one pass, or the records of the chunked kernel do not fit LDS: NodeRecs
     bool k1_wave = false;       // narrow levels, everything in LDS: one wave per slice, k1_ring = M rows, no ring
-    FastRec *d_frecs = nullptr;     // [M] (not built when a level is wider than one pass)
+    FastRec *d_frecs = nullptr;     // [M] (not built with k1_wide)
     int32_t *d_fovf = nullptr;
     int32_t fovf_len = 0;
     // Level-major form of the same records for graphs whose levels fill most of a pass: level l

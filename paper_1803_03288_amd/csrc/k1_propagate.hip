@@ -202,6 +202,7 @@ propagate_nodes_wide(const PropParams p)
 //     in memory.
 constexpr int WIN_LEVELS = 512;                 // levels per refill of the bounds window
 constexpr int WIN_MARGIN = 330;                 // one chunk past the window and four chunks ahead (64 levels each), and slack
+static_assert(WIN_LEVELS + WIN_MARGIN == kK1Window, "as the host counts it");
 constexpr int RPT = kK1Rpt;                     // positions per thread group and chunk
 
 template <int WC>
@@ -892,7 +893,7 @@ static hipError_t launch_nodes(const Dag &d, hipStream_t s)
     const int threads = d.k1_threads;
     const int per_pass = threads / WC;
     const int blocks = (d.W + WC - 1) / WC;
-    const bool wide = d.max_node_level_width > per_pass;
+    const bool wide = d.k1_wide;
     if (!wide && !d.d_frecs && !d.d_lrecs) return hipErrorInvalidValue;
     if (d.d_lrecs) {
         // level-major records: no staging, no chunks
@@ -921,11 +922,10 @@ static hipError_t launch_nodes(const Dag &d, hipStream_t s)
         hipLaunchKernelGGL(propagate_nodes_wave<WC>, dim3(blocks), dim3(64), lds_w, s, p);
         return hipGetLastError();
     }
-    size_t lds = (size_t)ring * WC * 8;
-    if (wide) lds += (size_t)4 * per_pass * 16 + (size_t)(LVL_CHUNK + WC + 3) * 4;
-    else lds += (size_t)2 * WC * 8 + (size_t)4 * RPT * per_pass * 16 + (size_t)2 * (WIN_LEVELS + WIN_MARGIN) * 4 +
-                (size_t)p.fovf_lds * 4;
-    if (lds > 150 * 1024) return hipErrorInvalidValue;
+    size_t lds = wide ? (size_t)ring * WC * 8 + (size_t)4 * per_pass * 16 + (size_t)(LVL_CHUNK + WC + 3) * 4 : k1_nodes_lds(ring, WC, per_pass);
+    if (!wide && lds + (size_t)p.fovf_lds * 4 > kK1LdsMax) p.fovf_lds = 0;          // (the lists are read from memory)
+    if (!wide) lds += (size_t)p.fovf_lds * 4;
+    if (lds > kK1LdsMax) return hipErrorInvalidValue;
     const void *kern = wide ? reinterpret_cast<const void *>(propagate_nodes_wide<WC>)
                             : reinterpret_cast<const void *>(propagate_nodes<WC>);
     if (lds > 48 * 1024) {

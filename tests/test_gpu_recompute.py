@@ -17,7 +17,10 @@ from test_gpu_parity import SMALL, tt  # noqa: F401
 
 @pytest.mark.parametrize("name", ["tiny", "vgg16", "inception3"] + list(SMALL))
 def test_recompute_from_cleared(tt, name):  # noqa: F811
-    d = SMALL[name]() if name in SMALL else wl.preset(name)
+    check(tt, name, SMALL[name]() if name in SMALL else wl.preset(name))
+
+
+def check(tt, name, d):  # noqa: F811
     want = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
     h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
     other = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
@@ -32,6 +35,27 @@ def test_recompute_from_cleared(tt, name):  # noqa: F811
     for x in (h, other):
         assert np.array_equal(x.deps().cpu().numpy().view(np.uint64), want)
         x.close()
+
+
+def wide(levels, width, recvs, fan_in=(2, 3), back=1):
+    return wl.layered_dag(31, levels=levels, width=width, fan_in=fan_in, back=back, n_recv=recvs, attach=(1, 3))
+
+
+# Levels that one pass of the workgroup takes and the level-major kernel does not or just does; about the width from which on the records of
+# the chunked one do not fit LDS, with slices of one, two and four words.  w32: rows formed by the kernels in the build.
+WIDE = {
+    "w1_256": lambda: wide(20, 256, 60), "w1_257": lambda: wide(20, 257, 60), "w1_1024": lambda: wide(18, 1024, 60),
+    "w2_288": lambda: wide(20, 288, 128), "w2_289": lambda: wide(20, 289, 128),
+    "w4_256": lambda: wide(20, 256, 200), "w4_lists": lambda: wide(20, 256, 200, (4, 9)),
+    "w16_257": lambda: wide(20, 257, 1024), "w32_330": lambda: wide(30, 330, 2048), "w32_800": lambda: wide(30, 800, 2000),
+    # inputs that have left the ring (8 192 positions with one-word slices)
+    "long_w1": lambda: wide(40, 700, 60, back=30), "long_w2": lambda: wide(40, 400, 128, back=30),
+}
+
+
+@pytest.mark.parametrize("name", list(WIDE))
+def test_wide_levels(tt, name):  # noqa: F811
+    check(tt, name, WIDE[name]())
 
 
 @pytest.mark.parametrize("name", ["tiny", "inception3", "layered70"])

@@ -210,6 +210,22 @@ def test_the_first_propagation_finds_its_tables_made(lib, name):
     lib.free(other)
 
 
+@pytest.mark.parametrize("recvs,at,kernel", [(60, 256, "propagate_levelsILi1E"), (60, 257, "wideILi1E"), (60, 1024, "wideILi1E"),
+                                             (128, 288, "propagate_nodesILi2E"), (128, 289, "wideILi2E"), (200, 256, "propagate_nodesILi4E"),
+                                             (1024, 256, "propagate_levelsILi1E"), (1024, 257, "wideILi1E"), (2000, 800, "wideILi1E"),
+                                             (2000, 1025, "wideILi1E")])
+def test_graphs_with_wide_levels_are_propagated(lib, recvs, at, kernel):
+    """Levels that one pass of a workgroup takes, but not the records of the chunked kernel: the kernel for wider levels."""
+    d = wl.layered_dag(3, levels=24, width=at, fan_in=(2, 3), back=1, n_recv=recvs, attach=(1, 2))
+    rc, h = lib.build(d)
+    assert rc == 0, lib.error()
+    lib.host_forget_launches()
+    assert lib.tictac_dag_recompute_deps(h, None) == 0, lib.error()
+    (name, _, _, lds, _), = [l for l in lib.launches() if "propagate" in l[0]]
+    assert kernel in name and lds <= 150 * 1024, (name, lds)
+    lib.free(h)
+
+
 @pytest.mark.parametrize("name", ["chain", "wide", "device"])
 def test_a_first_tac_call_waits_for_nothing_of_the_callers(lib, name):
     """The tables that a first TAC call makes go to the device without a wait for the caller's stream or the device."""
