@@ -16,6 +16,7 @@ constexpr int32_t kFrontierMaxClasses = (1 << 18) - 1;  // a class shares a word
 constexpr int32_t kFrontierMaxRecvs = (1 << 14) - 2;
 constexpr int32_t kFrontierMaxQ = 128;                  // members of Q, of the frontier: what the kernel has room for
 constexpr int32_t kFrontierMaxFrontier = 448;
+constexpr int32_t kFrontierMaxStack = 256;              // classes to be looked at
 constexpr int32_t kFrontierMaxInputs = 64;              // of a class: they are looked at again and again
 
 // An output of a class, a class that has it among its inputs: bits 0..17 the class.  Each class keeps the number of its inputs
@@ -46,6 +47,87 @@ struct FrontierPlan {
     std::vector<int32_t> free_cols;         // columns of the ops that depend on no recv
     std::vector<int32_t> own_ptr, own;      // [R + 1]: the classes with recv i among their inputs
 };
+
+// Whether a sample outgrows the kernel's lists by a quarter of one: it is followed as by the kernel, with one unit of time for
+// every op and 1/4 to 7/4 of the ops per recv for a recv.  (An estimate, hence the quarter: with 260 classes a level it comes to 131
+// members of Q, and samples with exponential times mostly stay within the 128 there is room for.)
+inline bool frontier_outgrown(int32_t R, int32_t N, const FrontierPlan &p)
+{
+    const int32_t C = (int32_t)p.row.size();
+    struct Member { int32_t c, low, high; };
+    std::vector<int32_t> at(C, 0), open(C), stack(p.roots.rbegin(), p.roots.rend()), Q;     // (at: the recv a class points at)
+    std::vector<Member> frontier;
+    std::vector<char> gone(R + 1, 0);
+    std::vector<float> P(R, 0.0f), t(R);
+    gone[R] = 1;
+    for (int32_t c = 0; c < C; ++c) open[c] = p.counters[c >> 3] >> (c & 7) * 4 & 15u;
+    for (size_t i = 0; i < p.wide.size(); ++i) open[p.wide[i]] = (int32_t)p.counters[(C + 7) / 8 + i];
+    uint32_t draw = 1;
+    for (float &x : t) {
+        draw = draw * 1664525u + 1013904223u;
+        x = (float)N / (float)R * (0.25f + 1.5f * (float)(draw >> 8) / (1 << 24));
+    }
+    const auto over = [](size_t n, int32_t most) { return n * 4 > (size_t)most * 5; };
+    for (int32_t step = 0; step < R; ++step) {
+        while (!stack.empty()) {
+            if (step && over(stack.size(), kFrontierMaxStack)) return true;     // (the first ones come 64 at a time)
+            const int32_t c = stack.back();
+            const FrontierRow &row = p.row[c];
+            stack.pop_back();
+            int32_t low = INT32_MAX, high = -1;
+            const auto look = [&](const int32_t *in) {
+                for (int j = 0; j < 4; ++j) {
+                    const int32_t r = in[j] < 0 ? ~in[j] : at[in[j]];
+                    if (gone[r]) continue;
+                    low = std::min(low, r);
+                    high = std::max(high, r);
+                }
+            };
+            look(row.in);
+            for (int32_t k = 0; k < (row.more & 15); ++k) look(&p.inputs[(row.more >> 4) * 4 + 4 * k]);
+            if (high < 0) continue;
+            if (low != high) {
+                frontier.push_back({c, low, high});
+                if (over(frontier.size(), kFrontierMaxFrontier)) return true;
+                continue;
+            }
+            at[c] = low;
+            if (row.n && P[low] == 0.0f) Q.push_back(low);
+            P[low] += (float)row.n;
+            const uint32_t *out = row.out, *rest = p.outputs.data() + row.rest;
+            for (;; out = rest, rest += 4) {
+                for (int j = 0; j < 4; ++j) {
+                    const int32_t x = (int32_t)(out[j] & 0x3ffffu), o = out[j] & kFrontierWide ? p.wide[x] : x;
+                    if (!(out[j] & kFrontierFill) && --open[o] == 0) stack.push_back(o);
+                }
+                if (out[0] & kFrontierLast) break;
+            }
+        }
+        if (over(Q.size(), kFrontierMaxQ)) return true;
+        int32_t best = 0;
+        if (!Q.empty()) {
+            size_t k = 0;
+            for (size_t i = 1; i < Q.size(); ++i)
+                if (std::min(P[Q[k]], t[Q[i]]) < std::min(P[Q[i]], t[Q[k]])) k = i;
+            best = Q[k];
+            Q[k] = Q.back();
+            Q.pop_back();
+        } else if (!frontier.empty()) {
+            const auto M = [&](const Member &m) { return t[m.low] + t[m.high]; };
+            best = std::min_element(frontier.begin(), frontier.end(), [&](const Member &a, const Member &b) { return M(a) < M(b); })->low;
+        } else {
+            while (gone[best]) ++best;
+        }
+        gone[best] = 1;
+        size_t kept = 0;
+        for (const Member m : frontier) {
+            if (m.low == best || m.high == best) stack.push_back(m.c);
+            else frontier[kept++] = m;
+        }
+        frontier.resize(kept);
+    }
+    return false;
+}
 
 // By op: level, class (-1: a recv), recv (-1: a compute op).  cnt0: |dep| by class.  col_cls: class by column.
 inline void make_frontier_plan(int32_t n, int32_t R, int32_t C, const int32_t *row_ptr, const int32_t *col_idx, const int32_t *level,
@@ -162,7 +244,21 @@ inline void make_frontier_plan(int32_t n, int32_t R, int32_t C, const int32_t *r
             uint32_t &o = j < 4 ? p.row[v].out[j] : p.outputs[p.row[v].rest + j - 4];
             o = (o & kFrontierLast) | (uint32_t)place[c] | (n_open[c] == 1 ? kFrontierOnly : n_open[c] > 15 ? kFrontierWide : 0u);
         }
-    p.ok = true;
+    // What comes later is followed where it may be too long: where a recv or a class holds more classes back than Q has members,
+    // or a level has more than twice as many classes (on layered graphs Q grows to about half a level).  Where it outgrows the
+    // lists the bit-sliced form takes all of a batch; samples by the frontier form up to there and the bit-sliced one then, against
+    // that alone, 4 096 samples: 1 619 classes, one recv in 200 of them, 14.4 and 12.6 ms; 2 270 classes, 900 behind one,
+    // 6.6 and 6.6.  (On layered graphs near the line samples still fit: 260 and 280 classes a level, eleven and twelve
+    // thousand in all, 9 to 25 ms against 37 to 118.)
+    bool follow = false;
+    std::vector<int32_t> on_level;
+    for (int32_t c = 0; c < C; ++c) {
+        const size_t l = (size_t)level[rep[c]];
+        if (l >= on_level.size()) on_level.resize(l + 1, 0);
+        follow |= n_out[c] > kFrontierMaxQ || ++on_level[l] > 2 * kFrontierMaxQ;
+    }
+    for (int32_t i = 0; i < R; ++i) follow |= p.own_ptr[i + 1] - p.own_ptr[i] > kFrontierMaxQ;
+    p.ok = !follow || !frontier_outgrown(R, (int32_t)col_cls.size(), p);
 }
 
 }  // namespace tictac

@@ -462,7 +462,8 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
         // 1 200 and 4 096 samples: 62 837 classes, 4 096 recvs 19 / 25, 44 / 32, 97 / 34, 265 / 48; 17 249 classes, 2 000 recvs
         // 7.2 / 9.2, 7.8 / 9.8, 22 / 12, 66 / 16; 10 182 classes, 4 096 recvs 21 / 17, 30 / 22, 69 / 23, 250 / 40; 4 411 classes,
         // 1 000 recvs 3.6 / 3.8, 3.8 / 4.0, 5.8 / 4.7, 16 / 5.9; 1 556 classes with up to 21 outstanding recvs each, 4 096
-        // recvs 30 / 49, 32 / 51, 93 / 59, 255 / 134.
+        // recvs 30 / 49, 32 / 51, 93 / 59, 255 / 134.  (Graphs whose samples outgrow its lists have none of its tables:
+        // frontier_plan.h.)
         int32_t *flags = nullptr;
         bool frontier = false, sliced = e == hipSuccess && tac_sliced_fits(d);
         if (many && d.frontier.ok) {

@@ -36,7 +36,7 @@
 namespace tictac {
 
 constexpr int kNoRecv = 0x3fff;             // (recvs take 14 bits in the lists)
-constexpr int kStack = 256, kFrontier = kFrontierMaxFrontier, kLog = 128;      // entries of the lists of a wave
+constexpr int kStack = kFrontierMaxStack, kFrontier = kFrontierMaxFrontier, kLog = 128;      // entries of the lists of a wave
 constexpr int kPoints = 0x8000;             // state of a class that points: kPoints | recv; of another: 0
 
 struct FrontierParams {

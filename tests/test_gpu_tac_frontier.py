@@ -66,6 +66,15 @@ def long_frontier(k):
     return with_layers(first, 300)
 
 
+def frontier_in_two(k):
+    """A frontier of 290 classes from the start and k more once recv 0 has been transferred, fewer at a time than the stack holds."""
+    def first(b, rs):
+        a = b.op([rs[0]], 1e-3, "op")
+        return [b.op([rs[1 + i], rs[1 + (i + 1) % 290]], 1e-3, "op") for i in range(290)] + \
+            [b.op([a, rs[1 + i], rs[1 + (i + 2) % 290]], 1e-3, "op") for i in range(k)]
+    return with_layers(first, 300)
+
+
 def long_classes():
     """Classes of up to 700 ops: split into pieces, more than two columns each."""
     def first(b, rs):
@@ -88,9 +97,12 @@ GRAPHS = {
     "own_recvs": lambda: layered(30, 60, 500, attach=(8, 16)),             # more than eight outstanding recvs
     "in4": lambda: fans(4), "in5": lambda: fans(5), "in15": lambda: fans(15), "in16": lambda: fans(16),
     "in61": lambda: fans(61),
-    "in62": lambda: fans(62),               # more inputs than the form takes: the bit-sliced kernel
+    "in62": lambda: fans(62), "in64": lambda: fans(64),
+    "in65": lambda: fans(65),               # more inputs than the form takes: the bit-sliced kernel
     "q127": lambda: many_pointed(127), "q200": lambda: many_pointed(200),
     "frontier400": lambda: long_frontier(400), "frontier900": lambda: long_frontier(900),
+    # a little longer than the lists: the plan takes the form, the kernel leaves samples
+    "q140": lambda: many_pointed(140), "frontier300": lambda: long_frontier(300), "frontier500": lambda: frontier_in_two(210),
     "long_classes": long_classes,
 }
 

@@ -3,6 +3,7 @@ while its tables are made, and streams under capture."""
 
 import pytest
 
+from test_gpu_tac_frontier import GRAPHS as LISTS
 from test_host import GRAPHS, layered, lib          # noqa: F401  (lib: the fixture)
 
 LARGE = 600                                         # samples: more than two per compute unit
@@ -23,6 +24,18 @@ def test_batches_that_take_the_frontier_form(lib, B, frontier):
     d = GRAPHS["wide"]()
     h = lib.build(d)[1]
     assert tac(lib, h, d, B) == ["tac_frontier_kernel"] * frontier + ["tac_sliced_kernel", "tac_kernel"]
+    lib.free(h)
+
+
+@pytest.mark.parametrize("name,frontier", [("q127", True), ("q140", True), ("q200", False), ("frontier300", True), ("frontier500", True),
+                                           ("frontier400", False), ("frontier900", False), ("in64", True), ("in65", False),
+                                           ("wide260", True), ("wide400", False)])
+def test_graphs_whose_samples_outgrow_the_lists(lib, name, frontier):
+    """(And classes with more inputs than the form takes.)  Where every sample would be left to the bit-sliced kernel, that takes the batch at once; a little beyond the lists'
+    lengths samples may fit or not."""
+    d = layered(40, int(name[4:]), 800) if name.startswith("wide") else LISTS[name]()
+    h = lib.build(d)[1]
+    assert tac(lib, h, d, LARGE) == ["tac_frontier_kernel"] * frontier + ["tac_sliced_kernel", "tac_kernel"]
     lib.free(h)
 
 
