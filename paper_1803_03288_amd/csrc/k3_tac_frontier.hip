@@ -773,7 +773,9 @@ hipError_t launch_tac_frontier(Dag &d, const TacArgs &a, size_t flag_bytes, size
     const int per_cu = std::min((int)(160 * 1024 / lds), 32);
     const int grid = std::min(a.B, per_cu * device_cu_count(d.device));
     p.scratch_stride = ls ? 0 : (state + 255) & ~(size_t)255;
-    const hipError_t e = ensure_workspace(&d, std::max(at_least, flag_bytes + p.scratch_stride * grid));
+    const size_t room = std::max(at_least, flag_bytes + p.scratch_stride * grid);
+    if (room > d.work_bytes && being_captured(s)) return hipErrorNotSupported;      // (the caller has forms that may do with less)
+    const hipError_t e = ensure_workspace(&d, room);
     if (e != hipSuccess) return e;
     p.flags = static_cast<int32_t *>(d.d_work);
     p.scratch = static_cast<char *>(d.d_work) + flag_bytes;

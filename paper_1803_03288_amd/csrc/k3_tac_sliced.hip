@@ -803,7 +803,9 @@ static hipError_t launch_sliced_k(SlicedParams &p, Dag &d, const TacArgs &a, siz
     int grid = per_cu * device_cu_count(d.device);
     if (grid > a.B) grid = a.B;
     p.scratch_stride = tac_sliced_scratch_stride(d, KW);
-    e = ensure_workspace(&d, std::max(at_least, flag_bytes + p.scratch_stride * (size_t)grid));
+    const size_t room = std::max(at_least, flag_bytes + p.scratch_stride * (size_t)grid);
+    if (!flags_out && room > d.work_bytes && being_captured(s)) return hipErrorNotSupported;
+    e = ensure_workspace(&d, room);
     if (e != hipSuccess || !flags_out) return e;
     p.flags = static_cast<int32_t *>(d.d_work);
     p.scratch = static_cast<char *>(d.d_work) + flag_bytes;

@@ -1,7 +1,10 @@
 """Host side of the frontier form of TAC, against the stand-in for the HIP runtime: which calls take it, memory that runs out
 while its tables are made, and streams under capture."""
 
+import numpy as np
 import pytest
+
+from paper_1803_03288_amd import workloads as wl
 
 from test_gpu_tac_frontier import GRAPHS as LISTS
 from test_host import GRAPHS, layered, lib          # noqa: F401  (lib: the fixture)
@@ -110,3 +113,53 @@ def test_without_room_for_the_bit_sliced_form(lib):
         assert tac(lib, h, d, LARGE) == want
         lib.free(h)
     assert taken[0] == want and all(t == ["tac_frontier_kernel", "tac_kernel"] for t in taken[1:]), taken
+
+
+def intervals(starts, R):
+    """Chains of ops with recvs a, a + 1, .. behind each other, from each of the first recvs on: the sets a .. j, one of each chain in
+    the frontier at a time."""
+    a, j = np.triu_indices(starts, 1, R)                # by the op before and recv j, or by recvs a and j = a + 1
+    n = a.size
+    col = np.stack([np.where(j == a + 1, a, R + np.arange(n) - 1), j], axis=1)
+    row = np.concatenate([np.zeros(R, int), 2 * np.arange(n + 1)])
+    return wl.Dag("intervals", R + n, row.astype(np.int32), col.ravel().astype(np.int32), np.arange(R, dtype=np.int32), np.ones(n), np.ones(R))
+
+
+def test_capture_after_calls_that_found_no_room(lib):
+    """A call under capture allocates nothing when an earlier one was at least as large, also where that one found room for one of
+    the two forms only: the same kernels take it."""
+    def captured(h, d, B, room):
+        lib.host_forget_launches()
+        lib.host_capturing(1)
+        rc = lib.tac(h, d, B, room)
+        lib.host_capturing(0)
+        assert rc == 0 and lib.hipGetLastError() == 0, lib.error()
+        return names(lib)
+
+    def first(d, B, room, extra):
+        h = lib.build(d)[1]
+        lib.tictac_trim_memory()
+        lib.host_device_limit(lib.count("device_bytes") + extra if extra >= 0 else -1)
+        lib.host_forget_launches()
+        assert lib.tac(h, d, B, room) == 0, lib.error()
+        lib.host_device_limit(-1)
+        return h, names(lib)
+
+    # room for the frontier form (0.1 GB less than the other)
+    d, room = GRAPHS["wide"](), {}
+    h, taken = first(d, LARGE, room, 50 << 20)
+    assert taken == ["tac_frontier_kernel", "tac_kernel"]
+    assert captured(h, d, LARGE, room) == taken
+    lib.free(h)
+
+    # room for the bit-sliced form only: from about 86 000 classes on the other wants more, for it has more samples under way
+    d, B = intervals(214, 512), 4096
+    room = dict(B=B, op=np.zeros((B, d.n_compute)), rv=np.zeros((B, d.n_recv)), order=np.zeros((B, d.n_recv), np.int32),
+                out=np.zeros((5, B)))                   # (never touched)
+    h, taken = first(d, B, room, -1)
+    assert taken == ["tac_frontier_kernel", "tac_sliced_kernel", "tac_kernel"]
+    lib.free(h)
+    h, taken = first(d, B, room, 700 << 20)
+    assert taken == ["tac_sliced_kernel", "tac_kernel"]
+    assert captured(h, d, B, room) == taken
+    lib.free(h)
