@@ -964,7 +964,13 @@ hipError_t launch_simulate(Dag &d, const SimArgs &a, hipStream_t s)
                            a.order, d.d_cls_ptr, d.d_cls_cols, d.d_col_cls, kappa, kappa_col, d.d_bad_order);
         p.kappa = kappa;
     }
-    if (!shared || kappa_col) {
+    // An order each, more than 2 048 classes, no more samples than compute units: sixteen waves per sample rather than one, which
+    // walks over the classes by itself.  64 / 256 / 384 samples, us, by sixteen waves and by recv: 3 465 classes, 300 recvs 74 /
+    // 79 / 143 and 116 / 126 / 137; 3 815, 128 recvs 89 / 172 / 318 and 183 / 210 / 209; 8 016, 400 recvs 263 / 306 / 572 and 377 /
+    // 341 / 379; 13 666, 500 recvs 407 / 417 / 812 and 471 / 478 / 775.  With rows of one word it is by recv at any size: 2 033, 64
+    // recvs 105 / 154 / 293 and 92 / 101 / 109.
+    const bool wide = !shared && d.C > 2048 && d.W > 1 && a.B <= device_cu_count(d.device);
+    if ((!shared && !wide) || kappa_col) {
         const hipError_t e = try_simulate_wave(d, a, kappa_col, s);
         if (e != hipErrorNotSupported) return e;
     }

@@ -286,6 +286,24 @@ def test_many_recvs_without_room_for_flags(lib):
     lib.free(h)
 
 
+@pytest.mark.parametrize("width,recvs,B,kernel", [(130, 100, 1, "simulate_kernelILi1024E"), (130, 100, 256, "simulate_kernelILi1024E"),
+                                                  (130, 100, 257, "simulate_wave"), (50, 100, 1, "simulate_wave"),
+                                                  (220, 64, 1, "simulate_wave")])
+def test_small_batches_with_an_order_each(lib, width, recvs, B, kernel):
+    """Graphs of more than 2 048 classes and rows of two words or more, no more samples than compute units: a workgroup per sample."""
+    d = layered(40, width, recvs)
+    h = lib.build(d)[1]
+    classes = I32()
+    lib.tictac_dag_info(h, None, None, None, None, ctypes.byref(classes))
+    assert (classes.value > 2048) == (width > 50)
+    op, rv, order = np.ones((B, d.n_compute)), np.ones((B, recvs)), np.tile(np.arange(recvs, dtype=np.int32), (B, 1))
+    out = [np.zeros(B) for _ in range(5)]
+    lib.host_forget_launches()
+    assert lib.tictac_simulate(h, I32(B), ptr(order), I32(recvs), ptr(op), ptr(rv), *(ptr(x) for x in out), None) == 0, lib.error()
+    assert any(kernel in k for k in lib.kernels()), lib.kernels()
+    lib.free(h)
+
+
 def test_one_order_without_room_for_a_word_per_column(lib):
     """One order for all samples on a stream that is being captured: a workspace that holds a word per class but not per
     column serves the call, by class."""
