@@ -1,4 +1,7 @@
 // Calls into the library's launchers that no entry point reaches in a test (host_lib.py).
+#include <string.h>
+
+#include "frontier_plan.h"
 #include "internal.h"
 
 using namespace tictac;
@@ -27,3 +30,31 @@ extern "C" int host_tac_sliced(int32_t C, int32_t R, int32_t B)
     (void)hipFree(d.d_work);
     return e;
 }
+
+// the plan of the frontier form (frontier_plan.h); NULL: it does not take the graph
+extern "C" void *host_frontier_plan(int32_t n, int32_t R, int32_t C, int32_t N, const int32_t *row_ptr, const int32_t *col_idx, const int32_t *level,
+                                    const int32_t *cls_of_op, const int32_t *recv_of_op, const int32_t *cnt0, const int32_t *col_cls)
+{
+    FrontierPlan *p = new FrontierPlan;
+    make_frontier_plan(n, R, C, row_ptr, col_idx, level, cls_of_op, recv_of_op, std::vector<int32_t>(cnt0, cnt0 + C),
+                       std::vector<int32_t>(col_cls, col_cls + N), *p);
+    if (p->ok) return p;
+    delete p;
+    return nullptr;
+}
+// the words of one of its arrays
+extern "C" int64_t host_frontier_array(const void *plan, const char *name, const void **at)
+{
+    const FrontierPlan &p = *static_cast<const FrontierPlan *>(plan);
+    const struct { const char *name; const void *at; size_t n; } all[] = {
+        {"row", p.row.data(), p.row.size() * 16}, {"inputs", p.inputs.data(), p.inputs.size()}, {"outputs", p.outputs.data(), p.outputs.size()},
+        {"counters", p.counters.data(), p.counters.size()}, {"wide", p.wide.data(), p.wide.size()}, {"roots", p.roots.data(), p.roots.size()},
+        {"free_cols", p.free_cols.data(), p.free_cols.size()}, {"own_ptr", p.own_ptr.data(), p.own_ptr.size()}, {"own", p.own.data(), p.own.size()}};
+    for (const auto &a : all)
+        if (!strcmp(a.name, name)) {
+            *at = a.at;
+            return (int64_t)a.n;
+        }
+    return -1;
+}
+extern "C" void host_frontier_free(void *plan) { delete static_cast<FrontierPlan *>(plan); }

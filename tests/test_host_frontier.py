@@ -1,11 +1,14 @@
 """Host side of the frontier form of TAC, against the stand-in for the HIP runtime: which calls take it, memory that runs out
 while its tables are made, and streams under capture."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
 from paper_1803_03288_amd import workloads as wl
 
+from host_lib import I32, ptr
 from test_gpu_tac_frontier import GRAPHS as LISTS
 from test_host import GRAPHS, layered, lib          # noqa: F401  (lib: the fixture)
 
@@ -40,6 +43,118 @@ def test_graphs_whose_samples_outgrow_the_lists(lib, name, frontier):
     h = lib.build(d)[1]
     assert tac(lib, h, d, LARGE) == ["tac_frontier_kernel"] * frontier + ["tac_sliced_kernel", "tac_kernel"]
     lib.free(h)
+
+
+def plan_of(lib, d, pieces):
+    """The plan of graph ``d`` with the sets of its compute ops as classes, each in ``pieces`` of consecutive ops, and what it was made
+    from: ``(plan or None, dep of the classes, class of every op, columns by class)``."""
+    n, R = d.n_ops, d.n_recv
+    recv_of, cls_of, level, deps = np.full(n, -1, np.int32), np.full(n, -1, np.int32), np.zeros(n, np.int32), [0] * n
+    recv_of[d.recv_ids] = np.arange(R)
+    members = {}
+    for v in range(n):                      # (the graphs' ops are in topological order)
+        before = d.col_idx[d.row_ptr[v]:d.row_ptr[v + 1]]
+        assert (before < v).all()
+        level[v] = 1 + max((level[u] for u in before), default=-1)
+        for u in before:
+            deps[v] |= deps[u]
+        if recv_of[v] >= 0:
+            deps[v] |= 1 << int(recv_of[v])
+        else:
+            members.setdefault(deps[v], []).append(v)
+    dep, columns = [], []
+    column = np.cumsum(recv_of < 0) - 1
+    for bits, ops in members.items():
+        for part in np.array_split(ops, min(pieces, len(ops))):
+            cls_of[part] = len(dep)
+            dep.append(bits)
+            columns.append(column[part].tolist())
+    col_cls, cnt0 = cls_of[recv_of < 0], [b.bit_count() for b in dep]
+    arrays = [np.ascontiguousarray(x, np.int32) for x in (d.row_ptr, d.col_idx, level, cls_of, recv_of, cnt0, col_cls)]
+    lib.L.host_frontier_plan.restype = ctypes.c_void_p
+    lib.L.host_frontier_array.restype = ctypes.c_int64
+    plan = lib.L.host_frontier_plan(I32(n), I32(R), I32(len(dep)), I32(col_cls.size), *(ptr(a) for a in arrays))
+    if not plan:
+        return None, dep, cls_of, columns
+    got = {}
+    for name in ("row", "inputs", "outputs", "counters", "wide", "roots", "free_cols", "own_ptr", "own"):
+        at = ctypes.c_void_p()
+        k = lib.L.host_frontier_array(ctypes.c_void_p(plan), name.encode(), ctypes.byref(at))
+        got[name] = np.ctypeslib.as_array(ctypes.cast(at, ctypes.POINTER(ctypes.c_int32)), (k,)).copy() if k else np.zeros(0, np.int32)
+    lib.L.host_frontier_free(ctypes.c_void_p(plan))
+    return got, dep, cls_of, columns
+
+
+FILL, WIDE, ONLY, LAST = 1 << 18, 1 << 19, 1 << 30, 1 << 31
+
+
+@pytest.mark.parametrize("name,pieces", [("layered", 1), ("layered", 3), ("in4", 1), ("in5", 1), ("in15", 1), ("in16", 1), ("in61", 1),
+                                         ("in64", 2), ("q127", 1), ("frontier300", 1), ("long_classes", 2)])
+def test_the_plan_of_the_class_graph(lib, name, pieces):
+    """dep of a class is the union of its inputs', none of which another one holds; outputs, counters, the classes of every recv, roots
+    and columns say the same."""
+    d = layered(12, 160, 300) if name == "layered" else LISTS[name]()
+    p, dep, _, columns = plan_of(lib, d, pieces)
+    assert p is not None
+    R, C, row = d.n_recv, len(dep), p["row"].reshape(-1, 16)
+    assert row.shape[0] == C
+    inputs, outputs, own = [], [set() for _ in range(C)], [[] for _ in range(R)]
+    for c in range(C):
+        more = int(row[c, 8])
+        x = np.array(inputs_of(row, p, R, c), dtype=np.int64)
+        assert x.size <= 64 and (np.diff(x) > 0).all() and (more & 15) == max(0, -(-x.size // 4) - 1)
+        sets = [dep[v] if v >= 0 else 1 << int(~v) for v in x]
+        union = 0
+        for b in sets:
+            union |= b
+        assert union == dep[c], c
+        inputs.append(x.tolist())
+        for v in x:
+            if v >= 0:
+                outputs[v].add(c)
+            else:
+                own[~v].append(c)
+        for v in x[x >= 0]:                 # (no input of an input)
+            assert not set(inputs_of(row, p, R, v)) & set(x.tolist()), (c, v)
+    assert p["own_ptr"].tolist() == np.cumsum([0] + [len(o) for o in own]).tolist()
+    assert p["own"].tolist() == [c for o in own for c in o]
+    open_ = [sum(v >= 0 for v in x) for x in inputs]
+    words, wide = p["counters"].astype(np.int64) & 0xffffffff, p["wide"].tolist()
+    assert wide == [c for c in range(C) if open_[c] > 15] and words.size % 4 == 0
+    for c in range(C):
+        assert (words[c >> 3] >> (c & 7) * 4) & 15 == (open_[c] if open_[c] < 16 else 0)
+    assert words[(C + 7) // 8:(C + 7) // 8 + len(wide)].tolist() == [open_[c] for c in wide]
+    assert p["roots"].tolist() == [c for c in range(C) if dep[c] and not open_[c]]
+    assert p["free_cols"].tolist() == [j for c in range(C) if not dep[c] for j in columns[c]]
+    order = [j for c in range(C) for j in columns[c]]
+    for c in range(C):
+        fours, at = [row[c, 4:8].view(np.uint32).tolist()], int(row[c, 9])
+        while not fours[-1][0] & LAST:
+            fours.append(p["outputs"][at:at + 4].view(np.uint32).tolist())
+            at += 4
+        assert len({bool(z & LAST) for z in fours[-1]}) == 1 and not any(z & LAST for f in fours[:-1] for z in f)
+        got = []
+        for z in (z for f in fours for z in f):
+            if z & FILL:
+                continue
+            o = wide[z & 0x3ffff] if z & WIDE else z & 0x3ffff
+            assert bool(z & ONLY) == (open_[o] == 1) and bool(z & WIDE) == (open_[o] > 15)
+            got.append(o)
+        assert len(got) == len(set(got)) and set(got) == outputs[c], c
+        n, first = int(row[c, 12]), int(row[c, 13])
+        assert order[first:first + n] == columns[c] and row[c, 14:16].tolist() == (columns[c] + [0, 0])[:2]
+
+
+def inputs_of(row, p, R, c):
+    more = int(row[c, 8])
+    at = (more >> 4) * 4
+    x = np.concatenate([row[c, :4], p["inputs"][at:at + 4 * (more & 15)]])
+    return x[x != ~R].tolist()
+
+
+@pytest.mark.parametrize("name", ["in65", "q200", "frontier900"])
+def test_graphs_without_a_plan(lib, name):
+    assert plan_of(lib, LISTS[name](), 1)[0] is None
 
 
 def test_under_capture(lib):
