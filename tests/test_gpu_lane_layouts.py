@@ -178,3 +178,78 @@ def test_tac_in_registers(tt, name):
         exp = oracle.simulate(*args, eo, op[rows], rv[rows])
         for g, e in zip(got[4:9], exp):     # (integers times a power of two: every sum is exact)
             assert np.array_equal(g.cpu().numpy()[rows], e), what
+
+
+# ---- several samples per wave, several waves per workgroup: more samples than the chip holds at a time ----
+MANY = 9001                                 # sixteen waves on each of 256 compute units, twice over, and a few more
+
+
+def copies(a, n=MANY):
+    """n rows: those of ``a`` over and over (an odd number of rows, so that the copies of one fall to different waves)."""
+    return cuda(a)[torch.arange(n, device="cuda") % len(a)].contiguous()
+
+
+def same_in_every_copy(got, first):
+    for g, f in zip(got, first):
+        f = f if torch.is_tensor(f) else cuda(f)
+        assert torch.equal(g, f[torch.arange(len(g), device="cuda") % len(f)])
+
+
+@pytest.mark.parametrize("name", ["k4", "k8", "k10", "k13", "k13_wide", "k16", "chain1000"])
+def test_tac_in_registers_many_samples(tt, name):
+    d = SLOTS[name]()
+    R, B = d.n_recv, 37
+    args = (d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    h = tt.build_deps(*args)
+    dep = oracle.find_dependencies(*args)
+    rng = np.random.default_rng(10)
+    op = rng.integers(0, 1 << 20, size=(B, d.n_compute)).astype(np.float64) * wl.QUANTUM
+    rv = rng.integers(1, 1 << 20, size=(B, R)).astype(np.float64) * wl.QUANTUM
+    op[::3], rv[::3] = np.floor(op[::3] / wl.QUANTUM % 3) * wl.QUANTUM, np.floor(rv[::3] / wl.QUANTUM % 3 + 1) * wl.QUANTUM      # (ties)
+    rv[4::9, 0] = 0.0                       # (the general kernel's, between the others)
+    first = tt.tac_simulate(h, cuda(op), cuda(rv), want_rank=True)
+    rows = [0, 4, 5, 36]
+    eo = oracle_tac_rows(dep, d.recv_ids, op[rows], rv[rows])[0]
+    assert np.array_equal(first[0].cpu().numpy()[rows], eo)
+    many = tt.tac_simulate(h, copies(op), copies(rv), want_rank=True)
+    print(f"[registers] {name}: classes={h.n_classes} R={R} B={MANY}", flush=True)
+    same_in_every_copy([many[k] for k in (0, 1, 4, 5, 6, 7, 8)], [first[k] for k in (0, 1, 4, 5, 6, 7, 8)])
+
+
+@pytest.mark.parametrize("name", ["layered300", "layered63", "wide", "two_words"])
+def test_release_positions_many_samples(tt, name):
+    # (the last: small batches are a workgroup's per sample, these a wave's)
+    d = layered(40, 130, 100) if name == "two_words" else RELEASES[name]()
+    R, B = d.n_recv, 29
+    args = (d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    h = tt.build_deps(*args)
+    assert name != "two_words" or h.n_classes > 2048
+    rng = np.random.default_rng(11)
+    orders = np.stack([rng.permutation(R) for _ in range(B)]).astype(np.int32)
+    op = rng.integers(0, 50, size=(B, d.n_compute)).astype(np.float64) * wl.QUANTUM
+    rv = rng.integers(0, 50, size=(B, R)).astype(np.float64) * wl.QUANTUM
+    print(f"[releases] {name}: classes={h.n_classes} R={R} B={MANY}", flush=True)
+    for n in (B, 256, 257, MANY):
+        same_in_every_copy(tt.simulate(h, copies(orders, n), copies(op, n), copies(rv, n)), oracle.simulate(*args, orders, op, rv))
+    same_in_every_copy(tt.simulate(h, cuda(orders[0]), copies(op), copies(rv)), oracle.simulate(*args, orders[0], op, rv))
+    h.check_orders()
+
+
+@pytest.mark.parametrize("name", ["many_classes28", "many_classes300", "chain193"])
+def test_consecutive_positions_many_samples(tt, name):
+    d = POSITIONS[name]()
+    R, B = d.n_recv, 23
+    args = (d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    h = tt.build_deps(*args)
+    rng = np.random.default_rng(12)
+    orders = np.stack([rng.permutation(R) for _ in range(B)]).astype(np.int32)
+    op = rng.integers(0, 50, size=(B, d.n_compute)).astype(np.float64) * wl.QUANTUM
+    rv = rng.integers(0, 50, size=(B, R)).astype(np.float64) * wl.QUANTUM
+    chan = rng.integers(0, 3, size=R).astype(np.int32)
+    print(f"[positions] {name}: classes={h.n_classes} R={R} B={MANY}", flush=True)
+    same_in_every_copy(tt.simulate_channels(h, 3, chan, copies(orders), copies(op), copies(rv)),
+                       oracle.simulate_channels(*args, 3, chan, orders, op, rv))
+    moves = rng.integers(0, R, size=(64, 2)).astype(np.int32)
+    same_in_every_copy(tt.order_search(h, copies(orders), cuda(moves), copies(op), copies(rv)),
+                       oracle.order_search(*args, orders, moves, op, rv))
+    h.check_orders()

@@ -154,3 +154,29 @@ def test_tac_by_the_frontier_form(tt, name):
         assert torch.equal(full[k][:97], part[k]), k
         assert torch.equal(full[k], f32[k]), k
     h.close()
+
+
+# states in LDS and in memory; the last two: samples are left to the bit-sliced kernel, their lists full
+@pytest.mark.parametrize("name,many", [("layered", 8200), ("many_inputs", 12001), ("q140", 8200), ("frontier500", 12001)])
+def test_several_samples_per_wave(tt, name, many):
+    """More samples than there are waves at a time: what a wave has of the one before it is not seen in the next."""
+    d = GRAPHS[name]()
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    dep = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    rng = np.random.default_rng(8)
+    op = rng.integers(1, 1 << 20, size=(B, d.n_compute)).astype(np.float64) * wl.QUANTUM
+    rv = rng.integers(1, 1 << 20, size=(B, d.n_recv)).astype(np.float64) * wl.QUANTUM
+    op[1::4], rv[1::4] = np.floor(op[1::4] / wl.QUANTUM % 3) * wl.QUANTUM, np.floor(rv[1::4] / wl.QUANTUM % 3 + 1) * wl.QUANTUM      # (ties)
+    op[2::4], rv[2::4] = rng.exponential(1e-3, size=op[2::4].shape), rng.lognormal(-6.5, 1.5, size=rv[2::4].shape)
+    rv[3::8, 2] = 0.0
+    print(f"[frontier] {name}: classes={h.n_classes} R={d.n_recv} B={many}", flush=True)
+    op, rv = torch.from_numpy(op).cuda(), torch.from_numpy(rv).cuda()
+    first = tt.tac_simulate(h, op, rv, want_rank=True)
+    rows = [0, 1, 3, 4, B - 1]
+    eo = oracle_tac_rows(dep, d.recv_ids, op.cpu().numpy()[rows], rv.cpu().numpy()[rows])[0]
+    assert np.array_equal(first[0].cpu().numpy()[rows], eo)
+    of = torch.arange(many, device="cuda") % B
+    got = tt.tac_simulate(h, op[of], rv[of], want_rank=True)
+    for k in (0, 1, 4, 5, 6, 7, 8):
+        assert torch.equal(got[k], first[k][of]), k
+    h.close()
