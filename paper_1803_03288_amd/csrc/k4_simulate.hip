@@ -136,9 +136,11 @@ simulate_kernel(const SimKernelParams p)
         __syncthreads();
         if (tid == 0) {
             double F = 0.0, busy = A[0];
+            // (fmax: of sums it is one instruction too, and the loop is unrolled, its loads ahead of the chain.  8 192 samples of 4 096
+            // recvs, one order: 3.30 ms, with max_f64 7.16)
             for (int k = 1; k <= R; ++k) {
                 F += Fs[k];
-                busy = max_f64(busy, F) + A[k];
+                busy = fmax(busy, F) + A[k];
             }
             const double m = max_f64(busy, F);
             const double U = sum_c + F;

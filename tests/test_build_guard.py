@@ -72,3 +72,11 @@ def test_a_store_after_the_request_is_found(asm):
 def test_a_kernel_that_is_gone_is_found(asm):
     bad = b.check_counted_waits(asm.replace("propagate_levels_q_batch", "propagate_levels_x_batch"))
     assert any("24propagate_levels_q_batchILi" in x for x in bad)
+
+
+def test_the_chain_over_the_recvs_is_unrolled():
+    """The recurrence of simulate_kernel, one thread's work: a loop that is not unrolled waits for LDS at every recv."""
+    asm = b.device_assembly(os.path.join(b.CSRC, "k4_simulate.hip"))
+    for key in ("15simulate_kernelILi64E", "15simulate_kernelILi1024E"):
+        lo, hi = function_span(asm, key)
+        assert asm[lo:hi].count("v_max_f64") >= 3 + 8, key
