@@ -64,13 +64,16 @@ struct TacRegParams {
 
 // Waves per workgroup.  The class rows in LDS are shared by the workgroup, so where they are large (many classes per lane, many
 // recvs) one large workgroup per compute unit leaves the most LDS to the per-wave arrays; sixteen waves cap the registers at
-// 128 per lane, four waves per SIMD.  From nine classes per lane on some are spilled at that, outside the common rounds: 61 x 23
-// layered ops, 203 recvs, 775 classes, one set of eight waves with 196 registers against sixteen, 65 536 samples 11.4 and 7.1 ms
-// (vector instructions issue in 22 % of a wave's time, so that four waves per SIMD keep it busy), 5 003 samples, in two sets, 1.13
-// and 0.94 ms, a single sample 316 and 307 us.  More than 384 recvs, any number that LDS holds, against the general kernel, 5 003
-// samples, ms: 20 x 10 ops and 500 recvs 5.8 and 2.1; 30 x 20 and 400, 9.2 and 1.5; 61 x 23 and 400, 17.6 and 2.7; 25 x 15 and
-// 1 000, 28.8 and 11.4.
-constexpr int kRegWavesMax = 16;
+// 128 per lane, four waves per SIMD.  From nine classes per lane on some are spilled at that: 61 x 23 layered ops, 203 recvs, 775
+// classes, eight waves with 196 registers against sixteen, 65 536 samples 11.4 and 7.1 ms (vector instructions issue in 22 % of
+// a wave's time, so that four waves per SIMD keep it busy), 5 003 samples, in two sets, 1.13 and 0.94 ms.  Where eight waves take
+// no more sets than as many as LDS holds, the kernel of eight, which spills nothing, has the batch: 22 x 35 ops and 336 recvs, one
+// sample 442 us (with 128 registers 467), 1 024 samples 498 (531); 58 x 23 and 380, where LDS holds ten, 532 (587) and 597
+// (665), 3 000 samples 1 280 (1 552).
+//   More than 384 recvs, up to 1 024 (a bit per lane and position of a 32-bit word) where LDS holds the rows, against the general
+// kernel, 5 003 samples, ms: 20 x 10 ops and 500 recvs 5.8 and 2.1; 30 x 20 and 400, 9.2 and 1.5; 61 x 23 and 400, 17.6 and 2.7;
+// 25 x 15 and 1 000, 28.8 and 11.4.
+constexpr int kRegWavesMax = 16, kRegWavesFew = 8;
 constexpr int reg_waves(int KT, int W) { return KT <= 4 && W <= 6 ? 4 : kRegWavesMax; }
 // More than this many classes per lane: the class totals are summed in the whole region of the wave, M comes out of tables of
 // subset sums (with both, 61 x 23 ops: 54 900 -> 44 700 vector instructions per sample).  Below, where M is rarely looked at and
@@ -101,8 +104,8 @@ __device__ __forceinline__ int first_alive(const uint32_t *rows, const uint32_t 
 #define TT_EACH_K(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7) F(8) F(9) F(10) F(11) F(12) F(13) F(14) F(15)
 
 // LIST: for graphs whose Q often has several members (see launch_tac_reg)
-template <int KT, bool LIST>
-__global__ void __launch_bounds__(64 * kRegWavesMax, (KT <= 3 ? 6 : (KT <= 4 ? 5 : 1)))
+template <int KT, bool LIST, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, (KT <= 3 ? 6 : (KT <= 4 ? 5 : 1)))
 tac_reg_kernel(const TacRegParams p)
 {
     extern __shared__ double smem[];
@@ -713,6 +716,14 @@ static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
     // as many waves as LDS allows
     int waves = reg_waves(KT, d.W);
     while (waves > 4 && (rows_doubles + per_wave * waves) * 8 > 150 * 1024) --waves;
+    auto kern = tac_reg_kernel<KT, LIST, kRegWavesMax>;
+    if constexpr (KT > kTableSlots) {
+        const int few = std::min(waves, kRegWavesFew), each = (p.B + device_cu_count(d.device) - 1) / device_cu_count(d.device);
+        if ((each + few - 1) / few <= (each + waves - 1) / waves) {
+            kern = tac_reg_kernel<KT, LIST, kRegWavesFew>;
+            waves = few;
+        }
+    }
     const size_t lds = (rows_doubles + per_wave * waves) * 8;
     if (lds > 150 * 1024) return hipErrorNotSupported;
     // (a small batch is spread over the compute units, the waves of a SIMD slow each other down; those without a sample
@@ -725,10 +736,10 @@ static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
     int per_cu = 0;
     hipError_t e;
     if (lds > 48 * 1024) {
-        e = ensure_dynamic_lds(reinterpret_cast<const void *>(tac_reg_kernel<KT, LIST>), lds);
+        e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds);
         if (e != hipSuccess) return e;
     }
-    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(tac_reg_kernel<KT, LIST>), 64 * waves, lds);
+    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(kern), 64 * waves, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
     const int n_cu = device_cu_count(d.device);
@@ -736,7 +747,7 @@ static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
     const int need = (p.B + p.active - 1) / p.active;
     if (grid > need) grid = need;
     p.n_waves = grid * p.active;
-    hipLaunchKernelGGL((tac_reg_kernel<KT, LIST>), dim3(grid), dim3(64 * waves), lds, s, p);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), lds, s, p);
     return hipGetLastError();
 }
 

@@ -211,9 +211,10 @@ def test_tac_in_registers_many_samples(tt, name):
     rows = [0, 4, 5, 36]
     eo = oracle_tac_rows(dep, d.recv_ids, op[rows], rv[rows])[0]
     assert np.array_equal(first[0].cpu().numpy()[rows], eo)
-    many = tt.tac_simulate(h, copies(op), copies(rv), want_rank=True)
-    print(f"[registers] {name}: classes={h.n_classes} R={R} B={MANY}", flush=True)
-    same_in_every_copy([many[k] for k in (0, 1, 4, 5, 6, 7, 8)], [first[k] for k in (0, 1, 4, 5, 6, 7, 8)])
+    for n in (2048, 2049, MANY):            # (eight samples per compute unit, the most that the kernel with more registers takes)
+        print(f"[registers] {name}: classes={h.n_classes} R={R} B={n}", flush=True)
+        many = tt.tac_simulate(h, copies(op, n), copies(rv, n), want_rank=True)
+        same_in_every_copy([many[k] for k in (0, 1, 4, 5, 6, 7, 8)], [first[k] for k in (0, 1, 4, 5, 6, 7, 8)])
 
 
 @pytest.mark.parametrize("name", ["layered300", "layered63", "wide", "two_words"])

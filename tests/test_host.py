@@ -10,6 +10,7 @@ import pytest
 from paper_1803_03288_amd import workloads as wl
 
 from host_lib import HostLib, I32, build_host_lib, ptr
+from test_gpu_lane_layouts import SLOTS
 
 
 @pytest.fixture(scope="module")
@@ -257,6 +258,23 @@ def test_a_first_tac_call_under_capture(lib):
     lib.host_forget_launches()
     assert lib.tac(h, d, 8256) == 0 and any("tac_reg" in k or "tac_chain" in k for k in lib.kernels())
     lib.host_capturing(0)
+    lib.free(h)
+
+
+@pytest.mark.parametrize("name,B,waves", [("k13", 1, 8), ("k13", 2048, 8), ("k13", 2049, 16), ("k15", 3000, 8), ("k15", 4000, 8),
+                                          ("k15", 4097, 16), ("wide", 9000, 8), ("k6", 1, 16)])
+def test_waves_of_tac_in_registers(lib, name, B, waves):
+    """More than eight classes per lane: the kernel of eight waves with all registers where it takes no more sets than as many waves
+    as LDS holds: at least twelve with k13, ten with k15, fewer than eight with wide."""
+    d = wl.layered_dag(17, levels=44, width=20, fan_in=(1, 4), back=3, n_recv=640, attach=(1, 8)) if name == "wide" else SLOTS[name]()
+    h = lib.build(d)[1]
+    classes = I32()
+    lib.tictac_dag_info(h, None, None, None, None, ctypes.byref(classes))
+    assert (classes.value > 512) == (name != "k6") and classes.value <= 1024, classes.value
+    lib.host_forget_launches()
+    assert lib.tac(h, d, B) == 0, lib.error()
+    (name, _, threads, lds, _), = [l for l in lib.launches() if "tac_reg" in l[0]]
+    assert f"ELi{waves}E" in name and threads <= 64 * waves and lds <= 150 * 1024, (name, threads, lds)
     lib.free(h)
 
 
