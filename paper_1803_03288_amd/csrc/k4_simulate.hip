@@ -670,17 +670,23 @@ simulate_channels_kernel(const SimChanParams p)
         for (int k = 0; k < KT; ++k) rho[k] = 0.0;
         if (p.depT) {
             // Rows of many runs: most hold one of the recvs that arrive late.  The maximum over those of them that the row holds
-            // is the maximum over the row, whatever the line between late and not.
+            // is the maximum over the row, whatever the line between late and not.  32 recvs at a time, whose part of the rows is in
+            // registers meanwhile.
             const double line = last_arrival * max(0.0, 1.0 - 32.0 / R);
+            for (int h = 0; 32 * h < R; ++h) {
+                const double x = lane < 32 && 32 * h + lane < R ? arr[32 * h + lane] : -1.0;
+                uint32_t late = (uint32_t)__ballot(x >= line);
+                if (!late) continue;
+                uint32_t row[KT];
 #pragma unroll
-            for (int q = 0; q < D; ++q) {
-                for (uint64_t late = __ballot(of[q] >= 0 && a[q] >= line); late != 0ull; late &= late - 1ull) {
-                    const int l = __builtin_ctzll(late), r = __builtin_amdgcn_readlane(of[q], l) & 1023;
-                    const double at_r = readlane_f64(a[q], l);
-                    const uint32_t *word = p.depT + ((size_t)(r >> 6) * p.Cpad + lane) * 2 + (r >> 5 & 1);
+                for (int k = 0; k < KT; ++k)
+                    row[k] = p.depT[((size_t)(h >> 1) * p.Cpad + min(k * 64, p.Cpad - 64) + lane) * 2 + (h & 1)];
+                for (; late != 0u; late &= late - 1u) {
+                    const int i = __builtin_ctz(late);
+                    const double at_r = readlane_f64(x, i);
 #pragma unroll
                     for (int k = 0; k < KT; ++k)
-                        if (k * 64 < C && (word[(size_t)min(k * 64, p.Cpad - 64) * 2] >> (r & 31) & 1u) && at_r > rho[k]) rho[k] = at_r;
+                        if ((row[k] >> i & 1u) && at_r > rho[k]) rho[k] = at_r;
                 }
             }
         }
@@ -796,12 +802,16 @@ static hipError_t launch_sim_chan(SimChanParams &p, const Dag &d, hipStream_t s)
     const size_t arr_doubles = ((size_t)4 * nb + 2) & ~(size_t)1;             // (sums by rank: one more than there are recvs)
     p.arr_doubles = (int32_t)arr_doubles;
     const size_t wave_bytes = (arr_doubles + x_doubles) * 8;                    // a multiple of 16
-    // (trying the late recvs costs what several runs cost: 65 536 samples, four channels, three runs per row (tiny) 106 us without,
-    // 132 with; six (21 x 18 layered ops, 28 recvs) 303 either way; 42 (24 x 20 and 300) 5 498 and 1 878)
-    p.depT = d.n_runs <= 8 * d.C ? nullptr : reinterpret_cast<const uint32_t *>(d.d_cls_depT);
+    // (more than two runs per row: the late recvs first.  65 536 samples, four channels, an order each, us without and with: three
+    // runs (tiny) 100 either way; 4.5 (9 x 17 layered ops, 18 recvs) 190 and 155; seven (18 x 17 and 45) 353 and 234; 57 (24 x 20
+    // and 300) 5 622 and 1 699.  The parts of the rows in registers: with a word from memory for every late recv and slot the last
+    // took 1 868, and one order that leaves many recvs late, one channel, 11 x 4 ops, 48 recvs, 60 000 samples 172 instead of 119,
+    // against 147 run by run)
+    const bool many = d.n_runs > 2 * d.C;
+    p.depT = many ? reinterpret_cast<const uint32_t *>(d.d_cls_depT) : nullptr;
     p.Cpad = d.Cpad;
-    p.cls_lane = d.n_runs <= 2 * d.C ? KT : 1;
-    p.cls_slot = d.n_runs <= 2 * d.C ? 1 : 64;
+    p.cls_lane = many ? 1 : KT;
+    p.cls_slot = many ? 64 : 1;
     int waves = 4;
     while (waves > 1 && wave_bytes * waves > 40 * 1024) waves >>= 1;
     const size_t chan_bytes = (((size_t)d.R + 128) * 4 + 15) & ~(size_t)15;
