@@ -72,8 +72,10 @@ __device__ __forceinline__ double dpp_f64(double identity, double v)
 }
 
 // fmin and fmax of numbers in one instruction: the compiler quiets an operand first that is loaded, selected or moved as two
-// integers (half of the minima and maxima of the kernels were that).  With the moves above: order search 1 753 -> 1 684 us, sends
-// 109.5 -> 106.7 us, TAC in registers with 14 class slots 1 087 -> 1 068 us, the other cases 0 to 1 % faster.
+// integers (half of the minima and maxima of the kernels were that).  Not in a loop that is to be unrolled by a number of turns not
+// known before: the compiler takes an asm for convergent and leaves such a loop as it is (simulate_kernel).  With the moves above: order
+// search 1 753 -> 1 684 us, sends 109.5 -> 106.7 us, TAC in registers with 14 class slots 1 087 -> 1 068 us, the other cases 0 to
+// 1 % faster.
 __device__ __forceinline__ double min_f64(double a, double b)
 {
     double r;
@@ -206,7 +208,7 @@ __device__ __forceinline__ void load4(const float *__restrict__ q, double (&x)[4
     x[0] = (double)a.x; x[1] = (double)a.y; x[2] = (double)a.z; x[3] = (double)a.w;
 }
 
-// a + b; what is rounded off is added to `lost`
+// a + b; what is rounded off, exactly (Knuth's two-sum), is added to `lost`
 __device__ __forceinline__ double add_exact(double a, double b, double &lost)
 {
     const double s = a + b, bb = s - a;

@@ -13,9 +13,11 @@
 // So a sample costs one visit per edge of the class graph instead of R rounds over all classes: with 62 837 classes and
 // 4 096 recvs 171 000 edges against 1.7 * 10^8 set bits.  The frontier has 40 members on average and 150 at most there, Q (the
 // recvs with P > 0) 23 and 79, so one wave keeps both in LDS, and the states of the classes (16 bits each) and the numbers of
-// their open inputs (4 bits) are in memory, where the window that is in use mostly stays in the L2 cache: sixteen samples and
-// more share a compute unit.  4 096 samples of that graph take 49 ms (bit-sliced: 267 ms, two samples per compute unit), 11.7 us
-// per round and wave, 6.4 us while a wave has the chip to itself: what bounds it is the latency of dependent trips to memory,
+// their open inputs (4 bits) are in memory, so that sixteen samples and more share a compute unit.  That is more than the L2
+// caches hold (157 KB per sample): 4 096 samples of one of 60 567 classes fetch 48.5 GB and write 25.8, 21 times their times and outputs
+// (states, counters, rows, single times of ops: how much of it is whose has not been counted), 1.6 TB/s.  Those of that graph take 49
+// ms (bit-sliced: 267 ms, two samples per compute unit), 11.7 us per round and wave, 6.4 us while a wave has the chip to itself: what bounds it is the latency
+// of dependent trips to memory,
 // for the rows of the classes looked at (0.9 ms in 10 of a sample's time), the states of their inputs (0.7), the counters of
 // their outputs (2.5) and the times of the ops released (2.2), and the rest is instructions, 640 vector and 410 scalar ones a
 // round.  That is why a class's row is one 64-byte line with its first inputs, outputs and columns, why four lanes look at a

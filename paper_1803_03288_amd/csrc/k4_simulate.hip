@@ -137,7 +137,7 @@ simulate_kernel(const SimKernelParams p)
         if (tid == 0) {
             double F = 0.0, busy = A[0];
             // (fmax: of sums it is one instruction too, and the loop is unrolled, its loads ahead of the chain.  8 192 samples of 4 096
-            // recvs, one order: 3.30 ms, with max_f64 7.16)
+            // recvs, one order: 3.01 ms, with max_f64 7.16)
             for (int k = 1; k <= R; ++k) {
                 F += Fs[k];
                 busy = fmax(busy, F) + A[k];
@@ -165,7 +165,8 @@ simulate_kernel(const SimKernelParams p)
 //     number of classes (inception3, 65 536 samples: 650 -> 606 us; 61 x 23 layered ops, 203 recvs, 775 classes, 20 000
 //     samples, which went to the kernel above: 917 -> 72 us).
 //   * A row of many runs mostly holds one of the recvs that come last: there, and where there are too many classes for the
-//     registers, those are tried first, from the last one on (61 x 23 ops, an order each: 1 470 -> 222 us).
+//     registers (up to the 18 000 or so whose totals LDS holds), those are tried first, from the last one on (61 x 23 ops, an
+//     order each: 1 470 -> 222 us).
 // Then A by kappa, and
 //     makespan = max over k of F_k + (A_k + ... + A_R),   F_0 = 0,
 // which is the recurrence above unrolled.
