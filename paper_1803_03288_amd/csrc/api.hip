@@ -1481,7 +1481,7 @@ static hipError_t make_sliced_tables(Dag *d)
 }
 
 // What the frontier form's tables hold, from the graph as given (host work only).
-static void plan_frontier(const Dag *d, FrontierPlan &p)
+static void plan_frontier(const Dag *d, FrontierPlan &p, FrontierTable &table)
 {
     const std::vector<int32_t> cls_of_op = classes_of_ops(d);
     std::vector<int32_t> recv_of_op(d->n, -1), level(d->n, 0), order;
@@ -1496,21 +1496,19 @@ static void plan_frontier(const Dag *d, FrontierPlan &p)
     int32_t n_levels = 0;
     if (topological || find_levels(d->n, row_ptr, col_idx, level, order, n_levels))
         make_frontier_plan(d->n, d->R, d->C, row_ptr, col_idx, level.data(), cls_of_op.data(), recv_of_op.data(), d->h_cls_cnt0, d->h_col_cls, p);
+    if (p.ok) make_frontier_table(p, table);
 }
 
-static hipError_t commit_frontier(Dag *d, const FrontierPlan &p)
+static hipError_t commit_frontier(Dag *d, const FrontierPlan &p, const FrontierTable &table)
 {
     FrontierTables &f = d->frontier;
     if (!p.ok) {
         f.made = true;
         return hipSuccess;
     }
-    static_assert(sizeof(FrontierRow) == 64, "as it is read");
     Packer t;
-    FrontierRow *row = nullptr;
-    t.add(&row, p.row);
-    t.add(&f.d_inputs, p.inputs);
-    t.add(&f.d_outputs, p.outputs);
+    t.add(&f.d_table, table.words);
+    t.add(&f.d_inputs, table.inputs);
     t.add(&f.d_counters, p.counters);
     t.add(&f.d_wide, p.wide);
     t.add(&f.d_roots, p.roots);
@@ -1522,7 +1520,6 @@ static hipError_t commit_frontier(Dag *d, const FrontierPlan &p)
     if (e == hipSuccess) e = t.commit(f.block, d->device, s);
     if (e == hipSuccess) e = t.finish();
     if (e != hipSuccess) return e;
-    f.d_row = reinterpret_cast<int4 *>(row);
     f.n_counters = (int32_t)p.counters.size();
     f.n_roots = (int32_t)p.roots.size();
     f.n_free = (int32_t)p.free_cols.size();
@@ -1536,8 +1533,9 @@ hipError_t ensure_large_tables(Dag *d, bool frontier)
     frontier = frontier && !d->frontier.made;
     if (!frontier) return d->sliced_made ? hipSuccess : make_sliced_tables(d);
     FrontierPlan plan;
+    FrontierTable table;
     std::future<void> planned;              // (after what its thread works on: it ends first)
-    auto make = [&] { plan_frontier(d, plan); };
+    auto make = [&] { plan_frontier(d, plan, table); };
     hipError_t e = hipSuccess, ef = hipSuccess;
     if (!d->sliced_made) {
         if ((int64_t)d->n + d->E > kPropThread) {
@@ -1551,7 +1549,7 @@ hipError_t ensure_large_tables(Dag *d, bool frontier)
     try {
         if (planned.valid()) planned.get();
         else make();
-        ef = commit_frontier(d, plan);
+        ef = commit_frontier(d, plan, table);
     } catch (const std::bad_alloc &) {
         ef = hipErrorOutOfMemory;
     }

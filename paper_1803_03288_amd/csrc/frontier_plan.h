@@ -261,4 +261,59 @@ inline void make_frontier_plan(int32_t n, int32_t R, int32_t C, const int32_t *r
     p.ok = !follow || !frontier_outgrown(R, (int32_t)col_cls.size(), p);
 }
 
+// The plan's rows and outputs as the kernel reads them, one after the other in a table of words.  Lane j of the four that look at a
+// class takes words 4 j .. 4 j + 3 of its sixteen at a time: inputs j and 4 + j in sixteen bits each, output j, and
+//   j = 0: further inputs: where they start in `inputs` (a multiple of four) times eight, and their number of fours; the first column
+//   j = 1: where its further outputs start (bytes from the table's start); the second column (one column: the same again)
+//   j = 2: the number of columns, where they are      j = 3: nothing
+// An input in sixteen bits is a class, as how far it is before this one, or kInRecv + recv (R: none); where one does not fit all are
+// among the further ones, as in FrontierRow.  An output is laid out so that its low five bits are where its counter is in its word.
+constexpr uint32_t kOutFill = 1u << 20, kOutWide = 1u << 21, kOutOnly = 1u << 30, kOutLast = 1u << 31;      // bits 2..19: the class, or its number
+constexpr uint32_t kOutClass = 0xffffcu;
+constexpr uint32_t kInRecv = 0xc000u;
+
+struct FrontierTable {
+    std::vector<uint32_t> words;
+    std::vector<int32_t> inputs;
+};
+
+inline void make_frontier_table(const FrontierPlan &p, FrontierTable &t)
+{
+    const size_t C = p.row.size();
+    const int32_t R = (int32_t)p.own_ptr.size() - 1;
+    const auto out = [](uint32_t z) {
+        return (z & 0x3ffffu) << 2 | (z & kFrontierFill ? kOutFill : 0u) | (z & kFrontierWide ? kOutWide : 0u) | (z & (kFrontierOnly | kFrontierLast));
+    };
+    t.words.assign(C * 16 + p.outputs.size(), 0);
+    std::vector<int32_t> in;
+    for (size_t c = 0; c < C; ++c) {
+        const FrontierRow &r = p.row[c];
+        const int32_t *more = p.inputs.data() + (r.more >> 4) * 4;
+        in.assign(r.in, r.in + 4);
+        in.insert(in.end(), more, more + (r.more & 15) * 4);
+        while (!in.empty() && in.back() == ~R) in.pop_back();
+        bool fits = true;
+        for (size_t k = 0; k < std::min<size_t>(8, in.size()); ++k) fits &= in[k] < 0 || (in[k] < (int32_t)c && (int32_t)c - in[k] < (int32_t)kInRecv);
+        uint32_t *q = &t.words[c * 16];
+        for (int j = 0; j < 4; ++j) {
+            for (int h = 0; h < 2; ++h) {
+                const size_t k = (size_t)(4 * h + j);
+                const uint32_t x = !fits || k >= in.size() ? kInRecv + (uint32_t)R : in[k] < 0 ? kInRecv + (uint32_t)~in[k] : (uint32_t)((int32_t)c - in[k]);
+                q[4 * j] |= x << 16 * h;
+            }
+            q[4 * j + 1] = out(r.out[j]);
+        }
+        const size_t first = t.inputs.size();
+        for (size_t k = fits ? 8 : 0; k < in.size(); ++k) t.inputs.push_back(in[k]);
+        t.inputs.resize((t.inputs.size() + 3) / 4 * 4, ~R);
+        q[2] = (uint32_t)(first * 8 + (t.inputs.size() - first) / 4);
+        q[3] = (uint32_t)r.c0;
+        q[6] = (uint32_t)((C * 16 + (size_t)r.rest) * 4);
+        q[7] = (uint32_t)(r.n > 1 ? r.c1 : r.c0);
+        q[10] = (uint32_t)r.n;
+        q[11] = (uint32_t)r.list;
+    }
+    for (size_t i = 0; i < p.outputs.size(); ++i) t.words[C * 16 + i] = out(p.outputs[i]);
+}
+
 }  // namespace tictac

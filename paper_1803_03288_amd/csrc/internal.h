@@ -45,9 +45,9 @@ struct FrontierTables {
     bool made = false, ok = false;
     int32_t n_roots = 0, n_free = 0, n_counters = 0;
     Block block;
-    int4 *d_row = nullptr;
+    uint32_t *d_table = nullptr;    // FrontierTable
     int32_t *d_inputs = nullptr, *d_roots = nullptr, *d_free_cols = nullptr, *d_own_ptr = nullptr, *d_own = nullptr, *d_wide = nullptr;
-    uint32_t *d_outputs = nullptr, *d_counters = nullptr;
+    uint32_t *d_counters = nullptr;
 };
 
 // Everything a handle owns.  Device arrays are sized exactly; empty ones are NULL.

@@ -57,4 +57,18 @@ extern "C" int64_t host_frontier_array(const void *plan, const char *name, const
         }
     return -1;
 }
+// what the kernel reads of it: the words of its table and of the inputs that rows have no room for
+extern "C" void *host_frontier_table(const void *plan)
+{
+    FrontierTable *t = new FrontierTable;
+    make_frontier_table(*static_cast<const FrontierPlan *>(plan), *t);
+    return t;
+}
+extern "C" int64_t host_frontier_table_array(const void *table, int32_t inputs, const void **at)
+{
+    const FrontierTable &t = *static_cast<const FrontierTable *>(table);
+    *at = inputs ? static_cast<const void *>(t.inputs.data()) : t.words.data();
+    return (int64_t)(inputs ? t.inputs.size() : t.words.size());
+}
+extern "C" void host_frontier_table_free(void *table) { delete static_cast<FrontierTable *>(table); }
 extern "C" void host_frontier_free(void *plan) { delete static_cast<FrontierPlan *>(plan); }

@@ -180,3 +180,44 @@ def test_several_samples_per_wave(tt, name, many):
     for k in (0, 1, 4, 5, 6, 7, 8):
         assert torch.equal(got[k], first[k][of]), k
     h.close()
+
+
+def side_by_side(parts):
+    """Graphs that have nothing to do with each other, one after the other: samples are busy in all of them, thousands of classes apart."""
+    n = np.cumsum([0] + [d.n_ops for d in parts])
+    edges = np.cumsum([0] + [d.row_ptr[-1] for d in parts])
+    return wl.Dag(name="side_by_side", n_ops=int(n[-1]),
+                  row_ptr=np.concatenate([d.row_ptr[:-1] + e for d, e in zip(parts, edges)] + [edges[-1:]]).astype(np.int32),
+                  col_idx=np.concatenate([d.col_idx + k for d, k in zip(parts, n)]).astype(np.int32),
+                  recv_ids=np.concatenate([d.recv_ids + k for d, k in zip(parts, n)]).astype(np.int32),
+                  op_median=np.concatenate([d.op_median for d in parts]), recv_bytes=np.concatenate([d.recv_bytes for d in parts]))
+
+
+def backwards(d):
+    """The same graph with its ops numbered the other way round: no input of a class is an earlier class."""
+    rows = [(d.n_ops - 1 - d.col_idx[d.row_ptr[v]:d.row_ptr[v + 1]])[::-1] for v in range(d.n_ops)][::-1]
+    return wl.Dag(name="backwards", n_ops=d.n_ops, row_ptr=np.cumsum([0] + [len(r) for r in rows]).astype(np.int32),
+                  col_idx=np.concatenate(rows).astype(np.int32), recv_ids=(d.n_ops - 1 - d.recv_ids)[::-1].astype(np.int32).copy(),
+                  op_median=d.op_median[::-1].copy(), recv_bytes=d.recv_bytes[::-1].copy())
+
+
+# The counters in LDS are those of 4 096 classes: some more, classes busy in several places, all of them moving the other way.
+@pytest.mark.parametrize("name", ["layers", "three", "fans", "backwards"])
+def test_counters_in_and_out_of_the_window(tt, name):
+    d = {"layers": lambda: layered(70, 110, 500), "three": lambda: side_by_side([layered(30, 90, 120), layered(32, 100, 150), layered(31, 95, 90)]),
+         "fans": lambda: side_by_side([fans(16), layered(36, 110, 200), fans(9)]), "backwards": lambda: backwards(layered(70, 110, 500))}[name]()
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    assert h.n_classes > 4096, h.n_classes
+    dep = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    rng = np.random.default_rng(9)
+    op = rng.integers(1, 1 << 20, size=(B, d.n_compute)).astype(np.float64) * wl.QUANTUM
+    rv = rng.integers(1, 1 << 20, size=(B, d.n_recv)).astype(np.float64) * wl.QUANTUM
+    rv[1::2, :d.n_recv // 2] *= 64.0        # (the classes that come first are done last)
+    print(f"[frontier] {name}: classes={h.n_classes} R={d.n_recv}", flush=True)
+    got = tt.tac_simulate(h, torch.from_numpy(op).cuda(), torch.from_numpy(rv).cuda(), want_rank=True)
+    rows = [0, 1, B - 1]
+    assert np.array_equal(got[0].cpu().numpy()[rows], oracle_tac_rows(dep, d.recv_ids, op[rows], rv[rows])[0])
+    part = tt.tac_simulate(h, torch.from_numpy(op[:97]).cuda(), torch.from_numpy(rv[:97]).cuda(), want_rank=True)       # bit-sliced
+    for k in (0, 1, 4, 5, 6, 7, 8):
+        assert torch.equal(got[k][:97], part[k]), k
+    h.close()

@@ -81,6 +81,14 @@ def plan_of(lib, d, pieces):
         at = ctypes.c_void_p()
         k = lib.L.host_frontier_array(ctypes.c_void_p(plan), name.encode(), ctypes.byref(at))
         got[name] = np.ctypeslib.as_array(ctypes.cast(at, ctypes.POINTER(ctypes.c_int32)), (k,)).copy() if k else np.zeros(0, np.int32)
+    lib.L.host_frontier_table.restype = ctypes.c_void_p
+    lib.L.host_frontier_table_array.restype = ctypes.c_int64
+    table = ctypes.c_void_p(lib.L.host_frontier_table(ctypes.c_void_p(plan)))
+    for i, name in enumerate(("table", "table_inputs")):
+        at = ctypes.c_void_p()
+        k = lib.L.host_frontier_table_array(table, I32(i), ctypes.byref(at))
+        got[name] = np.ctypeslib.as_array(ctypes.cast(at, ctypes.POINTER(ctypes.c_int32)), (k,)).copy() if k else np.zeros(0, np.int32)
+    lib.L.host_frontier_table_free(table)
     lib.L.host_frontier_free(ctypes.c_void_p(plan))
     return got, dep, cls_of, columns
 
@@ -143,6 +151,51 @@ def test_the_plan_of_the_class_graph(lib, name, pieces):
         assert len(got) == len(set(got)) and set(got) == outputs[c], c
         n, first = int(row[c, 12]), int(row[c, 13])
         assert order[first:first + n] == columns[c] and row[c, 14:16].tolist() == (columns[c] + [0, 0])[:2]
+
+
+def far_apart():
+    """Fifty thousand classes between a class and two that have it among their inputs: more than the kernel's row can say."""
+    d = wl.layered_dag(5, levels=500, width=160, fan_in=(1, 4), back=3, n_recv=2500, attach=(1, 8))
+    recv = np.zeros(d.n_ops, bool)
+    recv[d.recv_ids] = True
+    head = next(v for v in range(d.n_ops) if not recv[v] and d.row_ptr[v + 1] > d.row_ptr[v])
+    last = d.n_ops - 1
+    more = [[head, last], [head, last, int(d.recv_ids[-1])]]
+    return wl.Dag("far_apart", d.n_ops + 2, np.concatenate([d.row_ptr, d.row_ptr[-1] + np.cumsum([len(m) for m in more])]).astype(np.int32),
+                  np.concatenate([d.col_idx, *more]).astype(np.int32), d.recv_ids, np.ones(d.n_compute + 2), d.recv_bytes)
+
+
+@pytest.mark.parametrize("name,pieces", [("layered", 1), ("in4", 1), ("in5", 1), ("in15", 1), ("in16", 1), ("in62", 1), ("in64", 2),
+                                         ("many_inputs", 1), ("long_classes", 2), ("far_apart", 1)])
+def test_the_table_that_the_kernel_reads(lib, name, pieces):
+    """It says of every class what the plan says; and inputs that are no earlier class, or one too far away, are listed."""
+    d = layered(12, 160, 300) if name == "layered" else far_apart() if name == "far_apart" else LISTS[name]()
+    p, dep, _, _ = plan_of(lib, d, pieces)
+    R, C, row = d.n_recv, len(dep), p["row"].reshape(-1, 16)
+    table, listed = p["table"], 0
+    assert table.size == 16 * C + p["outputs"].size
+
+    def outputs_are(got, plan):
+        got, plan = got.view(np.uint32).astype(np.int64), plan.view(np.uint32).astype(np.int64)
+        want = (plan & 0x3ffff) << 2 | (plan & FILL != 0) << 20 | (plan & WIDE != 0) << 21 | plan & (ONLY | LAST)
+        return np.array_equal(got, want)
+
+    assert outputs_are(table[16 * C:], p["outputs"])
+    words = table[:16 * C].reshape(C, 4, 4)
+    assert outputs_are(words[:, :, 1].ravel(), row[:, 4:8].ravel())
+    for c in range(C):
+        q = words[c]
+        short = [(int(q[k & 3, 0]) >> 16 * (k >> 2)) & 0xffff for k in range(8)]
+        more = int(q[0, 2])
+        x = [c - s if s < 0xc000 else ~(s - 0xc000) for s in short] + p["table_inputs"][(more >> 5) * 4:(more >> 5) * 4 + 4 * (more & 31)].tolist()
+        want = inputs_of(row, p, R, c)
+        assert [v for v in x if v != ~R] == want, c
+        listed += more & 31 != 0 and len(want) <= 8
+        assert (more & 31 != 0) == (len(want) > 8 or any(v > c or c - v >= 0xc000 for v in want[:8] if v >= 0)), c
+        n = int(row[c, 12])
+        assert q[1, 2] == 4 * (16 * C + row[c, 9]) and q[2, 2] == n and q[2, 3] == row[c, 13]
+        assert q[0, 3] == row[c, 14] and (n < 1 or q[1, 3] == row[c, 15 if n > 1 else 14])
+    assert pieces > 1 or (listed > 0) == (name == "far_apart")      # (a piece may come before what feeds its set)
 
 
 def inputs_of(row, p, R, c):
