@@ -1620,9 +1620,9 @@ try {
     if (e != hipSuccess) return e;
     c.d_rec = reinterpret_cast<int4 *>(rec);
     c.d_gate = reinterpret_cast<int4 *>(gate);
-    c.n_chains = p.n_slots; c.n_totals = p.n_totals; c.n_gates = (int32_t)p.gate.size(); c.n_list = (int32_t)p.list.size();
+    c.n_chains = p.n_slots; c.n_totals = p.n_totals; c.n_gates = (int32_t)p.gate.size();
     c.start = p.start; c.n_start = p.n_start; c.n_several = (int32_t)p.several.size(); c.empty = p.empty;
-    c.n_extra = p.n_extra; c.n_pairs = p.n_pairs; c.n_head = (int32_t)p.head.size();
+    c.second_gates = p.second_gates; c.n_extra = p.n_extra; c.n_pairs = p.n_pairs; c.n_head = (int32_t)p.head.size();
     c.ok = c.made = true;
     return hipSuccess;
 } catch (const std::bad_alloc &) {

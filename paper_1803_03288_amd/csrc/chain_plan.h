@@ -54,8 +54,9 @@ struct ChainPlan {
     int32_t start = 0, n_start = 0;
     std::vector<int16_t> place;         // [R] place of a recv on its chain
     std::vector<int32_t> head;          // the first kChainAhead recvs of every chain: recv | total << 16
-    std::vector<int16_t> extra;         // [R] 1-based number among the recvs with a second gate or a list, 0 for the others
+    std::vector<int16_t> extra;         // [R] 1-based number among the recvs with a list, 0 for the others
     int n_extra = 0;
+    bool second_gates = false;          // some recv is a sink of two gates
     // totals in more than one row, as first row | number of rows << 16: first those in two rows (n_pairs of them)
     std::vector<int32_t> several;
     int n_pairs = 0;
@@ -230,8 +231,9 @@ inline void make_chain_plan(int R, int W, int N, int D, const uint64_t *const *r
     }
     p.extra.assign(R, 0);
     p.n_extra = 0;
+    p.second_gates = std::any_of(p.rec.begin(), p.rec.end(), [](const ChainRec &q) { return q.gate1 >= 0; });
     for (int r = 0; r < R; ++r)
-        if (p.rec[r].gate1 >= 0 || p.rec[r].n_more > 0) p.extra[r] = (int16_t)++p.n_extra;
+        if (p.rec[r].n_more > 0) p.extra[r] = (int16_t)++p.n_extra;
     p.start = (int32_t)p.list.size();
     p.n_start = (int32_t)start.size();
     p.list.insert(p.list.end(), start.begin(), start.end());

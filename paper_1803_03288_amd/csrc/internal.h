@@ -32,7 +32,8 @@ struct Block {
 // Tables of the chain form of TAC (chain_plan.h, k3_tac_chain.hip), made at the first call that takes that form.
 struct ChainTables {
     bool made = false, ok = false;  // made: whether the graph has the form is known, and if so (ok) the tables are there
-    int32_t n_chains = 0, n_totals = 0, n_gates = 0, n_list = 0, start = 0, n_start = 0, n_several = 0, empty = -1, n_extra = 0, n_pairs = 0, n_head = 0;
+    int32_t n_chains = 0, n_totals = 0, n_gates = 0, start = 0, n_start = 0, n_several = 0, empty = -1, n_extra = 0, n_pairs = 0, n_head = 0;
+    bool second_gates = false;      // some recv is a sink of two gates
     Block block;
     int4 *d_rec = nullptr, *d_gate = nullptr;
     int16_t *d_list = nullptr, *d_place = nullptr, *d_extra = nullptr;

@@ -64,7 +64,6 @@ __device__ __forceinline__ void store_device_8(void *q, uint64_t v) { *(__attrib
 __device__ __forceinline__ uint64_t load_device_8(const void *q) { return *(const __attribute__((address_space(1))) uint64_t *)q; }
 __device__ __forceinline__ int32_t load_device_4(const void *q) { return *(const __attribute__((address_space(1))) int32_t *)q; }
 
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void drain_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int WC>

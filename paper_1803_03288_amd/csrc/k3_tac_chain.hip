@@ -119,7 +119,7 @@ class_totals_kernel(const TotalsParams p)
 }
 
 struct ChainParams {
-    int32_t B, R, W, n_gates, n_list, start, n_start, n_several, empty;
+    int32_t B, R, W, n_gates, start, n_start, n_several, empty;
     size_t Bp;
     const int4 *rec;                    // ChainRec [R]
     const int4 *gate;                   // ChainGate [n_gates]
@@ -141,8 +141,8 @@ constexpr int kStagePad = 66;
 
 static size_t chain_lds_bytes(int NC, const ChainParams &p)
 {
-    return ((size_t)p.R + NC + p.n_extra + p.n_gates) * 16 + (size_t)NC * kChainAhead * 64 * 16 + ((size_t)p.n_gates + 1) * 64 * 12 +
-           ((size_t)2 * p.W + 1) * 64 * 4 + (size_t)kStage * kStagePad * 2 + (size_t)p.n_list * 2;
+    return ((size_t)p.R + NC) * 16 + (size_t)NC * kChainAhead * 64 * 16 + ((size_t)p.n_gates + 1) * 64 * 12 +
+           ((size_t)2 * p.W + 1) * 64 * 4 + (size_t)kStage * kStagePad * 2 + ((size_t)p.n_gates + p.n_extra + 1) * NC * 4;
 }
 
 // A wave has a SIMD to itself at 65 536 samples, so a round costs its instructions (four cycles each) and every wait that
@@ -150,26 +150,38 @@ static size_t chain_lds_bytes(int NC, const ChainParams &p)
 // Cache or from HBM.  Therefore: when a recv is taken, the values of the recv four places further on its chain are
 // requested; they land three rounds later in a ring in LDS (per slot and lane), from which a recv that becomes ready is
 // entered.  A slot without a ready recv has P < 0 (the P of some recv with its sign set), which precedes nothing and is
-// preceded by every ready recv; a recv that is the sink of no gate counts down gate n_gates, which never opens; second
-// gates and lists of successors, which few recvs have, hide behind one field of the record.
-template <int NC>
+// preceded by every ready recv; a recv that is the sink of no gate counts down gate n_gates, which never opens.
+//
+// The 64 samples of a wave are at different places, so what happens to one recv in thirty happens to some lane in almost
+// every round: gates that open and recvs with several successors are on the path of every round.  Therefore what becomes
+// ready then is a row of NC packed words, one per slot (successors of one recv do not depend on each other, so they are on
+// different chains): one trip to LDS for the row and one for all its recvs.  A round has four dependent trips: the record
+// of the recv taken; its ring entry, gates and joins; the row; the recvs of the row.  With the successors one after the
+// other, each behind its list, its record and its gate, there were up to nine trips more per successor: 65 536 samples,
+// inception3 (four branches) 377 -> 366 us, resnet50 (two) 99 -> 94 us.  What is left, from copies that leave something
+// out: 80 and 21 us are the stores of the selections, 40 us and nothing the loads, the rest is a round's 110 vector
+// instructions and its trips to LDS.  (A second wave that writes the selections takes the stores off the chain's wave and
+// is no faster: 387 and 93 us.)  SECOND: some recv is a sink of two gates.
+template <int NC, bool SECOND>
 __global__ void __launch_bounds__(64)
 tac_chain_kernel(const ChainParams p)
 {
     extern __shared__ int4 chain_smem[];
     const int R = p.R, lane = threadIdx.x;
-    // record of recv r: x = next | number of its extra record << 10 | that of next << 20 | sign: no next (next = R + slot);
-    // y and z = byte offsets of the class total and the times of the recv kChainAhead places further; w = its ring entry |
-    // ring entry of next << 5 | its gate << 10 | gate of next << 16
+    // record of recv r: x = next | 1-based row of its other successors << 10 | second gate of next << 20 | sign: no next (next =
+    // R + slot); y and z = byte offsets of the class total and the times of the recv kChainAhead places further; w = its ring
+    // entry | ring entry of next << 5 | its gate << 10 | gate of next << 16 | its second gate << 22
     int4 *rec_l = chain_smem;                                           // [R + NC]
-    int4 *more_l = rec_l + (R + NC);                                    // [n_extra] ChainRec of the recvs with a second gate or a list
-    int4 *gate_l = more_l + p.n_extra;                                  // [n_gates] ChainGate
-    double2 *ring = reinterpret_cast<double2 *>(gate_l + p.n_gates);    // [NC * kChainAhead][64] P, Time
+    double2 *ring = reinterpret_cast<double2 *>(rec_l + (R + NC));      // [NC * kChainAhead][64] P, Time
     double *join_l = reinterpret_cast<double *>(ring + NC * kChainAhead * 64);  // [n_gates + 1][64] time of the join
     uint32_t *gcnt = reinterpret_cast<uint32_t *>(join_l + (p.n_gates + 1) * 64);     // [n_gates + 1][64] sinks outstanding << 16 | their xor
     uint32_t *alive = gcnt + (p.n_gates + 1) * 64;                      // [2 W + 1][64] outstanding recvs
     uint16_t *stage = reinterpret_cast<uint16_t *>(alive + (2 * p.W + 1) * 64); // [kStage][kStagePad]
-    int16_t *list_l = reinterpret_cast<int16_t *>(stage + kStage * kStagePad);  // [n_list]
+    // [n_gates + n_extra + 1] what is ready once a gate is open or a recv taken, by slot: recv | ring entry << 10 | its gate
+    // << 15 | its second gate << 21, ~0 for nothing; the last row is empty
+    struct alignas(NC >= 4 ? 16 : 4 * NC) Row { uint32_t e[NC]; };
+    Row *rows = reinterpret_cast<Row *>(stage + kStage * kStagePad);
+    const int no_row = p.n_gates + p.n_extra;
 
     const uint32_t row_bytes = (uint32_t)(p.Bp * 8);                    // (all rows together stay below 4 GB)
     const int b0 = blockIdx.x * 64, b = b0 + lane;                      // (rows hold a multiple of 64 samples)
@@ -209,21 +221,47 @@ tac_chain_kernel(const ChainParams p)
         const int4 q = p.rec[r];
         const int next = (int)(int16_t)q.x, slot = q.z >> 16, at = p.place[r], extra = p.extra[r];
         const int ahead = (q.w >> 16) >= 0 ? q.w >> 16 : r;             // (at the end of a chain: a value that is never used)
-        if (extra) more_l[extra - 1] = q;
-        const int e = slot * kChainAhead, own = e + (at & (kChainAhead - 1)), gate = q.x >> 16;
-        const int gate_next = next >= 0 ? p.rec[next].x >> 16 : -1;
-        rec_l[r] = make_int4((next >= 0 ? next : (R + slot) | (int)0x80000000u) | extra << 10 | (next >= 0 ? p.extra[next] << 20 : 0),
+        const int e = slot * kChainAhead, own = e + (at & (kChainAhead - 1)), gate = q.x >> 16, gate1 = (int)(int16_t)q.y;
+        const int gate_next = next >= 0 ? p.rec[next].x >> 16 : -1, gate1_next = next >= 0 ? (int)(int16_t)p.rec[next].y : -1;
+        rec_l[r] = make_int4((next >= 0 ? next : (R + slot) | (int)0x80000000u) | extra << 10 | (gate1_next >= 0 ? gate1_next : p.n_gates) << 20,
                              (int)((int)(int16_t)p.rec[ahead].w * row_bytes), (int)(ahead * row_bytes),
                              own | (next >= 0 ? e + ((at + 1) & (kChainAhead - 1)) : own) << 5 |
-                             (gate >= 0 ? gate : p.n_gates) << 10 | (gate_next >= 0 ? gate_next : p.n_gates) << 16);
+                             (gate >= 0 ? gate : p.n_gates) << 10 | (gate_next >= 0 ? gate_next : p.n_gates) << 16 | (gate1 >= 0 ? gate1 : p.n_gates) << 22);
     }
-    for (int i = lane; i < p.n_gates; i += 64) gate_l[i] = p.gate[i];
-    for (int i = lane; i < p.n_list; i += 64) list_l[i] = p.list[i];
-    if (lane < NC) rec_l[R + lane] = make_int4((R + lane) | (int)0x80000000u, 0, 0, lane * kChainAhead * 0x21 | p.n_gates * 0x10400);
+    if (lane < NC)
+        rec_l[R + lane] = make_int4((R + lane) | (int)0x80000000u | p.n_gates << 20, 0, 0, lane * kChainAhead * 0x21 | p.n_gates * 0x410400);
+    // (a word of LDS is written by one lane only: a row is its gate's or its recv's)
+    auto packed = [&](int r) __attribute__((always_inline)) {
+        const int4 q = p.rec[r];
+        const int gate = q.x >> 16, gate1 = (int)(int16_t)q.y;
+        return (uint32_t)(r | ((q.z >> 16) * kChainAhead + (p.place[r] & (kChainAhead - 1))) << 10 | (gate >= 0 ? gate : p.n_gates) << 15 |
+                          (gate1 >= 0 ? gate1 : p.n_gates) << 21);
+    };
+    auto make_row = [&](int row, int first, int n) __attribute__((always_inline)) {
+        Row e;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) e.e[k] = ~0u;
+        for (int i = 0; i < n; ++i) {
+            const uint32_t v = packed(p.list[first + i]);
+#pragma unroll
+            for (int k = 0; k < NC; ++k) e.e[k] = (int)(v >> 10 & 0x1fu) / kChainAhead == k ? v : e.e[k];
+        }
+        rows[row] = e;
+    };
+    for (int i = lane; i < p.n_gates; i += 64) {
+        const int4 c = p.gate[i];
+        make_row(i, c.y >> 16, (int)(int16_t)c.z);
+    }
+    for (int r = lane; r < R; r += 64)
+        if (const int extra = p.extra[r]) {
+            const int4 q = p.rec[r];
+            make_row(p.n_gates + extra - 1, q.y >> 16, (int)(int16_t)q.z);
+        }
+    if (lane == 0) make_row(no_row, 0, 0);
     wave_sync();
 #pragma unroll 4
     for (int g = 0; g < p.n_gates; ++g) {
-        const int4 c = gate_l[g];
+        const int4 c = p.gate[g];
         gcnt[g * 64 + lane] = (uint32_t)c.x;
         const int j = (int)(int16_t)c.y;
         const double x = total_at((uint32_t)max(j, 0) * row_bytes);
@@ -249,27 +287,37 @@ tac_chain_kernel(const ChainParams p)
 #define TC_DECL(k) int id_##k = R + k; double P_##k = -1.0 - k, T_##k = TT_INF;
     TC_EACH(TC_DECL)
 
-    // time of the join of the second gate of a recv that is ready now, if it is the last outstanding sink of that gate
-    auto second_join = [&](int extra) __attribute__((always_inline)) {
-        const int g = (int)(int16_t)more_l[extra - 1].y;
-        return g >= 0 && (gcnt[g * 64 + lane] >> 16) == 1u ? join_l[g * 64 + lane] : 0.0;
+    // time of the join of gate g, if a recv that is ready now is the last outstanding sink of it
+    auto join_of = [&](int g) __attribute__((always_inline)) {
+        const uint32_t left = gcnt[g * 64 + lane];
+        const double x = join_l[g * 64 + lane];
+        return (left >> 16) == 1u ? x : 0.0;
     };
-    // a recv that becomes ready other than as the next one of the one taken
-    auto enter = [&](int r) __attribute__((always_inline)) {
-        const int4 q = rec_l[r];
-        const double2 v = ring[(q.w & 0x1f) * 64 + lane];
-        const int s = (q.w & 0x1f) / kChainAhead, extra = (q.x >> 10) & 0x3ff, g = (q.w >> 10) & 0x3f;
-        double pr = v.x + ((gcnt[g * 64 + lane] >> 16) == 1u ? join_l[g * 64 + lane] : 0.0);
-        if (extra) pr += second_join(extra);
+    // the recvs of a row become ready
+    auto enter = [&](const Row &e) __attribute__((always_inline)) {
 #define TC_ENTER(k)                                                                       \
         if constexpr (k < NC) {                                                           \
-            id_##k = s == k ? r : id_##k;                                                 \
-            P_##k = s == k ? pr : P_##k;                                                  \
-            T_##k = s == k ? v.y : T_##k;                                                 \
+            const double2 v = ring[(k * kChainAhead + ((e.e[k] >> 10) & (kChainAhead - 1))) * 64 + lane]; \
+            double pr = v.x + join_of(min((int)((e.e[k] >> 15) & 0x3fu), p.n_gates));     \
+            if constexpr (SECOND) pr += join_of(min((int)((e.e[k] >> 21) & 0x3fu), p.n_gates)); \
+            const bool here = (int)e.e[k] >= 0;                                           \
+            id_##k = here ? (int)(e.e[k] & 0x3ffu) : id_##k;                              \
+            P_##k = here ? pr : P_##k;                                                    \
+            T_##k = here ? v.y : T_##k;                                                   \
         }
         TC_EACH(TC_ENTER)
     };
-    for (int i = 0; i < p.n_start; ++i) enter(list_l[p.start + i]);
+    {
+        Row e;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) e.e[k] = ~0u;
+        for (int i = 0; i < p.n_start; ++i) {
+            const uint32_t v = packed(p.list[p.start + i]);
+#pragma unroll
+            for (int k = 0; k < NC; ++k) e.e[k] = (int)(v >> 10 & 0x1fu) / kChainAhead == k ? v : e.e[k];
+        }
+        enter(e);
+    }
 
     // M+ of a ready recv, and the literal ascending scan: only where the comparator ties
     auto m_plus = [&](int r) __attribute__((always_inline)) {
@@ -359,21 +407,29 @@ tac_chain_kernel(const ChainParams p)
         in.x = total_at((uint32_t)q.y);
         in.y = time_at((uint32_t)q.z);
         in_at = q.w & 0x1f;
-        const int g = (q.w >> 10) & 0x3f, gf = (q.w >> 16) & 0x3f;
+        const int g = (q.w >> 10) & 0x3f, g1 = (q.w >> 22) & 0x3f;
         const double2 v = ring[((q.w >> 5) & 0x1f) * 64 + lane];
-        const uint32_t c_f = gcnt[gf * 64 + lane], c = (gcnt[g * 64 + lane] - 0x10000u) ^ (uint32_t)best;
-        const double j_f = join_l[gf * 64 + lane];
-        gcnt[g * 64 + lane] = c;
+        const double f_join = join_of((q.w >> 16) & 0x3f), f_join1 = SECOND ? join_of((q.x >> 20) & 0x3f) : 0.0;
+        const uint32_t c = (gcnt[g * 64 + lane] - 0x10000u) ^ (uint32_t)best;
+        const double x = join_l[g * 64 + lane];
+        uint32_t c1 = 0x20000u;
+        double x1 = 0.0;
+        if constexpr (SECOND) {
+            c1 = (gcnt[g1 * 64 + lane] - 0x10000u) ^ (uint32_t)best;
+            x1 = join_l[g1 * 64 + lane];
+        }
         F += bT;
         busy = max_f64(busy, F) + bP;
         sum_c += bP;
 
         // ---- what is ready now: the next recv on the chain, with the join that points at it already.  (It is no sink of
-        // the gate that was counted down: sinks of one gate do not depend on each other.) ----
-        const int f = q.x & 0x3ff, extra = (q.x >> 10) & 0x3ff, f_extra = (q.x >> 20) & 0x3ff;
+        // a gate that was counted down: sinks of one gate do not depend on each other.) ----
+        const int f = q.x & 0x3ff, extra = (q.x >> 10) & 0x3ff;
+        gcnt[g * 64 + lane] = c;
+        if constexpr (SECOND) gcnt[g1 * 64 + lane] = c1;
         double fP = __hiloint2double(__double2hiint(v.x) | (q.x & (int)0x80000000u), __double2loint(v.x));
-        fP += (c_f >> 16) == 1u ? j_f : 0.0;
-        if (f_extra) fP += second_join(f_extra);
+        fP += f_join;
+        if constexpr (SECOND) fP += f_join1;
 #define TC_NEXT(k)                                                                        \
         if constexpr (k < NC) {                                                           \
             id_##k = slot == k ? f : id_##k;                                              \
@@ -381,28 +437,29 @@ tac_chain_kernel(const ChainParams p)
             T_##k = slot == k ? v.y : T_##k;                                              \
         }
         TC_EACH(TC_NEXT)
-        // a gate with one sink outstanding: its join points at that sink, if it is ready (else it does once it is); with
-        // none: it opens
-        auto gate_counted = [&](int i, uint32_t left) __attribute__((always_inline)) {
-            const double x = (left >> 16) == 1u ? join_l[i * 64 + lane] : 0.0;
+        // a gate with one sink outstanding: its join points at that sink, if it is ready (else it does once it is)
+        auto join_points = [&](uint32_t left, double time) __attribute__((always_inline)) {
+            const double y = (left >> 16) == 1u ? time : 0.0;
             const int sink = (int)(left & 0xffffu);
-#define TC_JOIN(k) if constexpr (k < NC) { P_##k += id_##k == sink ? x : 0.0; }
+#define TC_JOIN(k) if constexpr (k < NC) { P_##k += id_##k == sink ? y : 0.0; }
             TC_EACH(TC_JOIN)
-            if ((left >> 16) == 0u) {
-                const int4 gr = gate_l[i];
-                for (int n = 0; n < (int)(int16_t)gr.z; ++n) enter(list_l[(gr.y >> 16) + n]);
-            }
         };
-        if (c < 0x20000u) gate_counted(g, c);
-        if (extra) {
-            const int4 m = more_l[extra - 1];
-            const int first = m.y >> 16, n_more = (int)(int16_t)m.z, g1 = (int)(int16_t)m.y;
-            for (int i = 0; i < n_more; ++i) enter(list_l[first + i]);
-            if (g1 >= 0) {
-                const uint32_t c1 = (gcnt[g1 * 64 + lane] - 0x10000u) ^ (uint32_t)best;
-                gcnt[g1 * 64 + lane] = c1;
-                if (c1 < 0x20000u) gate_counted(g1, c1);
+        if (NC > 1 && c < 0x20000u) join_points(c, x);
+        if (SECOND && c1 < 0x20000u) join_points(c1, x1);
+        // with none outstanding it opens.  (What it opens, what a second gate opens and the other successors of the recv do
+        // not depend on each other either: one word per slot holds them all)
+        const bool opens = c < 0x10000u, opens1 = SECOND && c1 < 0x10000u;
+        if (NC > 1 && (opens || opens1 || extra != 0)) {
+            Row e = rows[opens ? g : no_row];
+            const Row e1 = rows[extra != 0 ? p.n_gates + extra - 1 : no_row];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) e.e[k] = min(e.e[k], e1.e[k]);
+            if constexpr (SECOND) {
+                const Row e2 = rows[opens1 ? g1 : no_row];
+#pragma unroll
+                for (int k = 0; k < NC; ++k) e.e[k] = min(e.e[k], e2.e[k]);
             }
+            enter(e);
         }
 
         // ---- selections to memory, kStage rounds at a time: two samples per store, whole lines of the order ----
@@ -410,10 +467,16 @@ tac_chain_kernel(const ChainParams p)
             wave_sync();
             const int s = (step & ~(kStage - 1)) + (lane & 31), n_b = min(64, p.B - b0);
             if (s <= step)
-                for (int j = lane >> 5; j < n_b; j += 2) {
-                    const int r = min((int)stage[(lane & 31) * kStagePad + j], R - 1);
-                    order_w[j * R + s] = r;
-                    if (rank_w) rank_w[j * R + r] = s;
+                for (int j0 = lane >> 5; j0 < 64; j0 += 16) {
+                    int r[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) r[i] = min((int)stage[(lane & 31) * kStagePad + j0 + 2 * i], R - 1);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (j0 + 2 * i < n_b) {
+                            order_w[(j0 + 2 * i) * R + s] = r[i];
+                            if (rank_w) rank_w[(j0 + 2 * i) * R + r[i]] = s;
+                        }
                 }
             wave_sync();
         }
@@ -442,15 +505,15 @@ tac_chain_kernel(const ChainParams p)
     }
 }
 
-template <int NC>
+template <int NC, bool SECOND>
 static hipError_t launch_chain_nc(const ChainParams &p, hipStream_t s)
 {
     const size_t lds = chain_lds_bytes(NC, p);
     if (lds > 48 * 1024) {
-        const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(tac_chain_kernel<NC>), lds);
+        const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(tac_chain_kernel<NC, SECOND>), lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((tac_chain_kernel<NC>), dim3((unsigned)((p.B + 63) / 64)), dim3(64), lds, s, p);
+    hipLaunchKernelGGL((tac_chain_kernel<NC, SECOND>), dim3((unsigned)((p.B + 63) / 64)), dim3(64), lds, s, p);
     return hipGetLastError();
 }
 
@@ -502,7 +565,7 @@ hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t 
         if (e != hipSuccess) return e;
         ChainParams p{};
         p.B = nb; p.R = d.R; p.W = d.W; p.Bp = chunk;
-        p.n_gates = c.n_gates; p.n_list = c.n_list; p.start = c.start; p.n_start = c.n_start;
+        p.n_gates = c.n_gates; p.start = c.start; p.n_start = c.n_start;
         p.n_several = c.n_several; p.empty = c.empty;
         p.rec = c.d_rec; p.gate = c.d_gate; p.list = c.d_list; p.place = c.d_place; p.extra = c.d_extra; p.n_extra = c.n_extra;
         p.n_pairs = c.n_pairs; p.n_head = c.n_head; p.head = c.d_head; p.several = c.d_several;
@@ -517,10 +580,10 @@ hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t 
         p.L = a.L ? a.L + b0 : nullptr;
         p.S = a.S ? a.S + b0 : nullptr;
         p.flags = flags + b0;
-        if (c.n_chains <= 1) e = launch_chain_nc<1>(p, s);
-        else if (c.n_chains <= 2) e = launch_chain_nc<2>(p, s);
-        else if (c.n_chains <= 4) e = launch_chain_nc<4>(p, s);
-        else e = launch_chain_nc<8>(p, s);
+        if (c.n_chains <= 1) e = launch_chain_nc<1, false>(p, s);
+        else if (c.n_chains <= 2) e = c.second_gates ? launch_chain_nc<2, true>(p, s) : launch_chain_nc<2, false>(p, s);
+        else if (c.n_chains <= 4) e = c.second_gates ? launch_chain_nc<4, true>(p, s) : launch_chain_nc<4, false>(p, s);
+        else e = c.second_gates ? launch_chain_nc<8, true>(p, s) : launch_chain_nc<8, false>(p, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -78,7 +78,6 @@ struct EvEntry {                    // 16 bytes: a class that fell to one outsta
     double ct;
 };
 
-__device__ __forceinline__ void lds_only_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l)     // l wave-uniform
@@ -244,14 +243,14 @@ tac_sliced_kernel(const SlicedParams p)
 #define TS_REQUEST(code)                                                                  \
             {                                                                             \
                 if (lane == 0) ctrl[CT_REQ] = (code);                                     \
-                lds_only_barrier();                                                       \
+                lds_barrier();                                                       \
                 if ((code) == REQ_FLUSH) wait_memory();                                   \
-                if ((code) == REQ_QEMPTY) { wait_memory(); lds_only_barrier(); lds_only_barrier(); } \
-                if ((code) == REQ_MPLUS) { wait_memory(); lds_only_barrier(); }           \
-                lds_only_barrier();                                                       \
+                if ((code) == REQ_QEMPTY) { wait_memory(); lds_barrier(); lds_barrier(); } \
+                if ((code) == REQ_MPLUS) { wait_memory(); lds_barrier(); }           \
+                lds_barrier();                                                       \
             }
             for (int step = 0; step < R; ++step) {
-                lds_only_barrier();         // the events of the previous round are in the list
+                lds_barrier();         // the events of the previous round are in the list
 
                 // ---- the events of the previous round: class times into P, new members of Q ----
                 // Every worker wave has left its events in a region of its own, in an order that depends on
@@ -443,7 +442,7 @@ tac_sliced_kernel(const SlicedParams p)
                     alive[best >> 6] &= ~(1ull << (best & 63));
                     Qb[best >> 6] &= ~(1ull << (best & 63));
                 }
-                lds_only_barrier();
+                lds_barrier();
             }
 #undef TS_REQUEST
         } else {
@@ -455,9 +454,9 @@ tac_sliced_kernel(const SlicedParams p)
                 for (int j = 0; j < kPlanes; ++j) pl[j][k] = in ? p.planes0[(size_t)j * CWpad + cwk[k]] : 0ull;
             }
             for (int step = 0; step < R; ++step) {
-                lds_only_barrier();
+                lds_barrier();
                 for (;;) {
-                    lds_only_barrier();
+                    lds_barrier();
                     const int req = __builtin_amdgcn_readfirstlane(ctrl[CT_REQ]);
                     if (req == REQ_DONE) break;
                     if (req == REQ_FLUSH) {
@@ -465,7 +464,7 @@ tac_sliced_kernel(const SlicedParams p)
                     } else if (req == REQ_QEMPTY) {
                         // parent counts are decremented by atomics that are not waited for: wait now
                         wait_memory();
-                        lds_only_barrier();
+                        lds_barrier();
                         double lm = TT_INF;
                         int li = INT32_MAX;
                         if (wave >= 1) {
@@ -497,7 +496,7 @@ tac_sliced_kernel(const SlicedParams p)
                             }
                             if (lane == 0 && li != INT32_MAX) atomicMin(&cmin[0], (unsigned long long)__double_as_longlong(lm));
                         }
-                        lds_only_barrier();
+                        lds_barrier();
                         if (wave >= 1 && lane == 0 && li != INT32_MAX && (unsigned long long)__double_as_longlong(lm) == cmin[0])
                             atomicMin(&ctrl[CT_CIDX], li);
                     } else {
@@ -509,7 +508,7 @@ tac_sliced_kernel(const SlicedParams p)
                         for (int k = 0; k < KW; ++k)
                             if (cwk[k] < CW) live_pub[cwk[k]] = live[k];
                         wait_memory();
-                        lds_only_barrier();
+                        lds_barrier();
 #pragma unroll
                         for (int which = 0; which < 2; ++which) {
                             const int r = __builtin_amdgcn_readfirstlane(ctrl[which == 0 ? CT_R1 : CT_R2]);
@@ -556,7 +555,7 @@ tac_sliced_kernel(const SlicedParams p)
                             if (lane == 0 && any) atomicMin(&cmin[which], (unsigned long long)__double_as_longlong(lm));
                         }
                     }
-                    lds_only_barrier();
+                    lds_barrier();
                 }
                 const int best = __builtin_amdgcn_readfirstlane(ctrl[CT_BEST]);
 
