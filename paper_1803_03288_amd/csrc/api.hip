@@ -883,18 +883,17 @@ struct PropTables {
     Condensed g;
     std::vector<int32_t> copied;
     std::vector<Dag::NodeRec> nodes;
-    std::vector<Dag::FastRec> lrecs, frecs;
-    std::vector<int32_t> ovf_idx, chunk_end, lfovf, fovf;
+    std::vector<Dag::FastRec> frecs;
+    std::vector<int32_t> ovf_idx, chunk_end, fovf;
+    std::vector<int32_t> slot;              // level-major records: the slot of every node (the device makes them)
+    const std::vector<int32_t> no_lists = std::vector<int32_t>(1, 0);
     QuadTables quads;
     std::future<void> quads_made;           // (waited for before the rest goes: a thread of their own makes them)
 
     void add_to(Packer &p, Dag *d)
     {
-        p.add(&d->d_lrecs, lrecs);
-        p.add(&d->d_lfovf, lfovf);
         p.add(&d->d_frecs, frecs);
         p.add(&d->d_fovf, fovf);
-        d->lfovf_len = (int32_t)lfovf.size();
         d->fovf_len = (int32_t)fovf.size();
         if (d->k1_lring == 0) {
             // the kernels that go by positions; the one for wide levels reads NodeRecs
@@ -903,6 +902,15 @@ struct PropTables {
             p.add(&d->d_nlvl_ptr, g.lvl_ptr);
             p.add(&d->d_chunk_end, chunk_end);
         } else {
+            // what launch_level_records makes them from
+            p.add(&d->d_nlvl_ptr, g.lvl_ptr);
+            p.add(&d->d_node_ptr, g.ptr.data(), (size_t)g.M + 1);
+            p.add(&d->d_node_in, g.in.data(), (size_t)g.ptr[g.M]);
+            p.add(&d->d_node_op, g.op.data(), (size_t)g.M);
+            p.add(&d->d_node_slot, slot);
+            p.add(&d->d_lfovf_used, no_lists);
+            p.reserve(&d->d_lrecs, (size_t)d->n_node_levels * (d->k1_threads / d->k1_wc) * sizeof(Dag::FastRec));
+            p.reserve(&d->d_lfovf, (size_t)d->lfovf_len * 4);
             p.reserve(&d->d_k1_sink, (size_t)((d->W + d->k1_wc - 1) / d->k1_wc) * d->k1_threads * 8);
         }
         p.add(&d->d_copied, copied);
@@ -969,7 +977,8 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
     // one-word slices (many narrow workgroups: four of them then share a compute unit when several
     // graphs are propagated by one launch)
     int32_t lring = 0;
-    if (max_width <= per_pass && threads > 64 && (int64_t)n_node_levels * per_pass <= (int64_t)4 * M + 8192) {
+    if (max_width <= per_pass && threads > 64 && (int64_t)n_node_levels * per_pass <= (int64_t)4 * M + 8192 &&
+        (int64_t)M + g.ptr[M] <= INT32_MAX) {
         const size_t ring_cap = d->k1_wc == 1 ? 32 * 1024 : 64 * 1024;
         lring = 64;
         while ((size_t)lring * 2 * d->k1_wc * 8 <= ring_cap && lring < n_node_levels * per_pass) lring *= 2;
@@ -1018,23 +1027,11 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
         for (const int32_t *x = g.begin(k); x != g.end(k); ++x) lists.push_back(*x < 0 ? *x : name(*x));
     };
     if (lring > 0) {
-        // While level l is computed the ring holds the slots from (l + 1) * P - ring on.
-        const int32_t P = per_pass, row_bytes = d->k1_wc * 8, zero_row = lring * row_bytes;
-        Dag::FastRec none;
-        for (int j = 0; j < 4; ++j) none.in[j] = zero_row;
-        none.rcv[0] = none.rcv[1] = -1;
-        none.op = -1;
-        none.ovf = -1;
-        t.lrecs.assign((size_t)n_node_levels * P, none);
-        std::vector<int32_t> slot(M);
-        for (int32_t k = 0; k < M; ++k) {
-            const int32_t l = g.lvl[k];
-            slot[k] = l * P + (g.pos[k] - nlvl_ptr[l]);
-            const int32_t oldest = (l + 1) * P - lring;
-            fast(t.lrecs[slot[k]], k, zero_row, t.lfovf,
-                 [&](int32_t x) { return slot[x] >= oldest ? (slot[x] & (lring - 1)) * row_bytes : -1; },
-                 [&](int32_t x) { return slot[x]; });
-        }
+        // (a kernel makes the records and the lists: launch_level_records)
+        t.slot.resize(M);
+        for (int32_t k = 0; k < M; ++k) t.slot[k] = g.lvl[k] * per_pass + (g.pos[k] - nlvl_ptr[g.lvl[k]]);
+        d->lfovf_len = M + g.ptr[M];
+        d->lfovf_count = (int32_t)std::min<size_t>(list_entries, 4096);
     } else if (!d->k1_wide) {
         const int32_t row_bytes = d->k1_wc * 8, zero_row = ring * row_bytes;
         t.frecs.resize(M);
@@ -1154,6 +1151,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         graph.add(&d->d_bad_order, zeros);
         graph.reserve(&d->d_dep, (size_t)n * d->W * 8);
         HIP_TRY(graph.commit(d->graph_block, d->device, s));
+        HIP_TRY(launch_level_records(*d, s));
         HIP_TRY(graph.finish());
         if ((size_t)n * d->W) HIP_TRY(launch_propagate(*d, s));
     }
@@ -1328,7 +1326,10 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         cls.reserve(&d->d_cls_depT, (size_t)d->W * d->Cpad * 8);
     }
     HIP_TRY(cls.commit(d->class_block, d->device, s));
-    if (from_sets && dep_words) HIP_TRY(launch_expand_sets(*d, s));
+    if (from_sets && dep_words) {
+        HIP_TRY(launch_expand_sets(*d, s));
+        HIP_TRY(launch_level_records(*d, s));
+    }
     int32_t *mismatch = d->d_bad_order + 1;         // (a second word of the zeroed flag block)
     if (on_device) HIP_TRY(launch_class_rows(*d, d->d_op_of_col, d->d_cls_first_op, mismatch, s));
     int32_t differs = 0;

@@ -102,7 +102,10 @@ struct Dag {
     // graph takes another kernel.
     FastRec *d_lrecs = nullptr;     // [n_node_levels * P]
     int32_t *d_lfovf = nullptr;
-    int32_t lfovf_len = 0;
+    int32_t lfovf_len = 0;          // room for them (the kernel that makes the records makes the lists: *d_lfovf_used entries)
+    int32_t lfovf_count = 0;        // those of the nodes with more than four nodes or two recvs among their inputs, up to 4 096
+    // what the records are made from: the condensed graph by node, the slot of every node
+    int32_t *d_node_ptr = nullptr, *d_node_in = nullptr, *d_node_op = nullptr, *d_node_slot = nullptr, *d_lfovf_used = nullptr;
     int32_t k1_lring = 0;           // slots held in LDS (a power of two, at least 16 levels)
     // The level-major records of the kernel with 64-byte slices (four lanes per slot, P = k1_threads / 4):
     // ring slots of up to four input rows in 16-bit halves (unused: the zero row, slot k1_lring), two recv indices
@@ -240,6 +243,7 @@ hipError_t launch_propagate(const Dag &d, hipStream_t s);
 // copies from pinned host memory (16-byte aligned, rounded up to 16 bytes) by a kernel
 hipError_t launch_copy_in(void *dst, const void *pinned, size_t bytes, hipStream_t s);
 // op.dep from cls_dep and d_op_src
+hipError_t launch_level_records(const Dag &d, hipStream_t s);
 hipError_t launch_expand_sets(const Dag &d, hipStream_t s);
 // the same for G graphs of one launch shape in one launch; staging: device memory of propagate_batch_staging_bytes(G)
 size_t propagate_batch_staging_bytes(int G);
