@@ -470,24 +470,33 @@ static void group_classes(const std::vector<uint64_t> &rows, int32_t N, int32_t 
 // The same grouping from the device's: rep[j] the lowest op with the row of op j.  first_col: the first member of every
 // class (piece), whose row is the row of the class.
 static void group_reps(const int32_t *rep, int32_t N, int32_t max_members, std::vector<int32_t> &cls_ptr,
-                       std::vector<int32_t> &cls_cols, std::vector<int32_t> &first_col, int32_t &n_distinct)
+                       std::vector<int32_t> &cls_cols, std::vector<int32_t> &first_col, std::vector<int32_t> &col_cls, int32_t &n_distinct)
 {
-    std::vector<int32_t> set_of(N), start(1, 0);
-    for (int32_t j = 0; j < N; ++j) {
-        if (rep[j] == j) {
-            set_of[j] = (int32_t)start.size() - 1;
-            start.push_back(0);
-        } else {
-            set_of[j] = set_of[rep[j]];
-        }
-        ++start[set_of[j] + 1];
+    std::vector<int32_t> set_of(N), start((size_t)N + 1, 0);
+    int32_t sets = 0;
+    for (int32_t j = 0; j < N; ++j) {               // (whether an op starts a set could go either way: no branch)
+        const bool fresh = rep[j] == j;
+        const int32_t seen = set_of[rep[j]], set = fresh ? sets : seen;
+        set_of[j] = set;
+        sets += fresh;
+        ++start[set + 1];
     }
-    n_distinct = (int32_t)start.size() - 1;
+    n_distinct = sets;
+    start.resize((size_t)sets + 1);
     for (int32_t c = 0; c < n_distinct; ++c) start[c + 1] += start[c];
     cls_cols.resize(N);
     {
         std::vector<int32_t> fill(start.begin(), start.end() - 1);
         for (int32_t j = 0; j < N; ++j) cls_cols[fill[set_of[j]]++] = j;
+    }
+    int32_t largest = 0;
+    for (int32_t c = 0; c < n_distinct; ++c) largest = std::max(largest, start[c + 1] - start[c]);
+    if (largest <= max_members) {                   // (nothing to split)
+        first_col.resize(n_distinct);
+        for (int32_t c = 0; c < n_distinct; ++c) first_col[c] = cls_cols[start[c]];
+        cls_ptr = std::move(start);
+        col_cls = std::move(set_of);
+        return;
     }
     cls_ptr.reserve(n_distinct + 64);
     first_col.reserve(n_distinct + 64);
@@ -681,10 +690,17 @@ struct Condensed {
     const int32_t *end(int32_t k) const { return &in[0] + ptr[k + 1]; }
 };
 
+// Whether a branch on the number of predecessors of an op would go either way: two and more on average (layered graphs).  Then
+// the passes over all ops do as if all had four (100 000 ops, 2.6 on average: levels 635 -> 345 us, condensation 810 -> 500);
+// on chains of ops, where the branch is foreseen, they do what there is to do (inception3, 1.5: a build 136 us, 157 with four).
+// On small graphs the branches of one build are remembered until the next (1 700 ops, 2.5: 93 us, 97 with four).
+static bool mixed_degrees(int32_t n, int32_t E) { return n >= 4096 && E / 2 >= n; }
+
 static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
                      const std::vector<int32_t> &level, const std::vector<int32_t> &order, Condensed &g)
 {
     const int32_t n = d.n;
+    const bool mixed = mixed_degrees(n, d.E);
     g.val.resize(n);
     g.op.resize(n); g.ptr.resize(n + 1);
     g.in.resize((size_t)d.E + 1);           // (one more: begin() of an empty list)
@@ -694,9 +710,28 @@ static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_id
         const int32_t v = order.empty() ? i : order[i];
         if (recv_of_op[v] >= 0) { val[v] = ~recv_of_op[v]; continue; }
         const int32_t first = at, e0 = row_ptr[v], deg = row_ptr[v + 1] - e0;
-        // (few predecessors, as most ops have: each value is written and kept if it differs from those before, without a
-        // branch that could go either way)
         const int32_t *pred = col_idx + e0;
+        // (few predecessors, as most ops have: each value is written and kept if it differs from those before, without a
+        // branch that could go either way; where numbers of predecessors vary the last one stands in for those missing)
+        if (mixed && (uint32_t)(deg - 1) < 4u) {
+            const int32_t x0 = val[pred[0]], x1 = val[pred[std::min(1, deg - 1)]], x2 = val[pred[std::min(2, deg - 1)]], x3 = val[pred[deg - 1]];
+            const int32_t k1 = x1 != x0, k2 = (x2 != x0) & (x2 != x1), k3 = (x3 != x0) & (x3 != x1) & (x3 != x2);
+            in[at] = x0;
+            in[at += 1] = x1;
+            in[at += k1] = x2;
+            in[at += k2] = x3;
+            at += k3;
+            const int32_t nr = (x0 < 0) + ((x1 < 0) & k1) + ((x2 < 0) & k2) + ((x3 < 0) & k3);
+            g.list_entries += nr > 2 ? 1 + (size_t)(at - first) : 0;
+            const bool same = (at == first + 1) & (x0 >= 0);        // (the row of that node)
+            val[v] = same ? x0 : M;
+            at = same ? first : at;
+            g.op[M] = v;
+            g.ptr[M + 1] = at;
+            used[level[v]] |= !same;
+            M += !same;
+            continue;
+        }
         if (deg <= 4) {
             if (deg > 0) in[at++] = val[pred[0]];
             if (deg > 1) {
@@ -762,12 +797,15 @@ static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_id
 static std::vector<int32_t> copied_rows(const Condensed &g)
 {
     const int32_t n = (int32_t)g.val.size();
-    std::vector<int32_t> copied(2 * (size_t)(n - g.M));
+    std::vector<int32_t> copied(2 * (size_t)(n - g.M) + 2);         // (two more: every op is written, a node's is written over)
     size_t at = 0;
-    for (int32_t v = 0; v < n && at < copied.size(); ++v) {
+    for (int32_t v = 0; v < n; ++v) {
         const int32_t x = g.val[v], from = x < 0 ? x : g.op[x];
-        if (from != v) { copied[at++] = v; copied[at++] = from; }
+        copied[at] = v;
+        copied[at + 1] = from;
+        at += from != v ? 2 : 0;
     }
+    copied.resize(at);
     return copied;
 }
 
@@ -821,6 +859,19 @@ static QuadTables make_quad_tables(const Condensed &g, const std::vector<int32_t
         const int32_t k = node_at[p], l = g.lvl[k];
         Dag::QuadRec &f = qrecs[slot_of[k]];
         f.op = g.op[k];
+        // (most nodes: one to four inputs, no recv, all in the ring; the last input again in place of those that are missing)
+        if (const int32_t n_in = g.ptr[k + 1] - g.ptr[k]; (uint32_t)(n_in - 1) < 4u) {
+            const int32_t *x = g.begin(k), x0 = x[0], x1 = x[std::min(1, n_in - 1)], x2 = x[std::min(2, n_in - 1)], x3 = x[n_in - 1];
+            if ((x0 | x1 | x2 | x3) >= 0) {
+                const int32_t s0 = slot_of[x0], s1 = slot_of[x1], s2 = slot_of[x2], s3 = slot_of[x3];
+                if (std::min(std::min(s0, s1), std::min(s2, s3)) >= (l + 1) * P - ring) {
+                    const int32_t m = ring - 1;
+                    f.in01 = (uint32_t)(s0 & m) | (n_in > 1 ? (uint32_t)(s1 & m) : none) << 16;
+                    f.in23 = (n_in > 2 ? (uint32_t)(s2 & m) : none) | (n_in > 3 ? (uint32_t)(s3 & m) : none) << 16;
+                    continue;
+                }
+            }
+        }
         int nn = 0, nr = 0;
         for (const int32_t *x = g.begin(k); x != g.end(k); ++x) (*x < 0 ? nr : nn) += 1;
         // (copies are made only for a node that then fits a record)
@@ -883,10 +934,9 @@ struct PropTables {
     Condensed g;
     std::vector<int32_t> copied;
     std::vector<Dag::NodeRec> nodes;
-    std::vector<Dag::FastRec> frecs;
-    std::vector<int32_t> ovf_idx, chunk_end, fovf;
-    std::vector<int32_t> slot;              // level-major records: the slot of every node (the device makes them)
-    const std::vector<int32_t> no_lists = std::vector<int32_t>(1, 0);
+    std::vector<Dag::FastRec> lrecs, frecs;
+    std::vector<int32_t> ovf_idx, chunk_end, lfovf, fovf;
+    std::vector<int32_t> slot, lfovf_used;  // level-major records: the slot of every node; entries of the lists so far
     QuadTables quads;
     std::future<void> quads_made;           // (waited for before the rest goes: a thread of their own makes them)
 
@@ -902,15 +952,19 @@ struct PropTables {
             p.add(&d->d_nlvl_ptr, g.lvl_ptr);
             p.add(&d->d_chunk_end, chunk_end);
         } else {
-            // what launch_level_records makes them from
-            p.add(&d->d_nlvl_ptr, g.lvl_ptr);
-            p.add(&d->d_node_ptr, g.ptr.data(), (size_t)g.M + 1);
-            p.add(&d->d_node_in, g.in.data(), (size_t)g.ptr[g.M]);
-            p.add(&d->d_node_op, g.op.data(), (size_t)g.M);
-            p.add(&d->d_node_slot, slot);
-            p.add(&d->d_lfovf_used, no_lists);
-            p.reserve(&d->d_lrecs, (size_t)d->n_node_levels * (d->k1_threads / d->k1_wc) * sizeof(Dag::FastRec));
-            p.reserve(&d->d_lfovf, (size_t)d->lfovf_len * 4);
+            p.add(&d->d_lfovf_used, lfovf_used);
+            if (lrecs.empty()) {            // (launch_level_records makes them)
+                p.add(&d->d_nlvl_ptr, g.lvl_ptr);
+                p.add(&d->d_node_ptr, g.ptr.data(), (size_t)g.M + 1);
+                p.add(&d->d_node_in, g.in.data(), (size_t)g.ptr[g.M]);
+                p.add(&d->d_node_op, g.op.data(), (size_t)g.M);
+                p.add(&d->d_node_slot, slot);
+                p.reserve(&d->d_lrecs, (size_t)d->n_node_levels * (d->k1_threads / d->k1_wc) * sizeof(Dag::FastRec));
+                p.reserve(&d->d_lfovf, (size_t)d->lfovf_len * 4);
+            } else {
+                p.add(&d->d_lrecs, lrecs);
+                p.add(&d->d_lfovf, lfovf);
+            }
             p.reserve(&d->d_k1_sink, (size_t)((d->W + d->k1_wc - 1) / d->k1_wc) * d->k1_threads * 8);
         }
         p.add(&d->d_copied, copied);
@@ -929,9 +983,11 @@ struct PropTables {
 };
 
 // Makes them.  order: the ops in topological order (empty: by id); level: longest path from a root.  The tables for several
-// graphs are made by a thread of their own meanwhile.
+// graphs are made by a thread of their own meanwhile.  by_kernel: the level-major records are left to
+// launch_level_records, which pays for graphs whose rows the device forms (on smaller ones the launch and the wait for it cost 3
+// to 50 us more than the records).
 static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
-                                  const std::vector<int32_t> &level, const std::vector<int32_t> &order, PropTables &t)
+                                  const std::vector<int32_t> &level, const std::vector<int32_t> &order, const bool by_kernel, PropTables &t)
 {
     Condensed &g = t.g;
     condense(*d, row_ptr, col_idx, recv_of_op, level, order, g);
@@ -1027,11 +1083,27 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
         for (const int32_t *x = g.begin(k); x != g.end(k); ++x) lists.push_back(*x < 0 ? *x : name(*x));
     };
     if (lring > 0) {
-        // (a kernel makes the records and the lists: launch_level_records)
+        const int32_t P = per_pass;
         t.slot.resize(M);
-        for (int32_t k = 0; k < M; ++k) t.slot[k] = g.lvl[k] * per_pass + (g.pos[k] - nlvl_ptr[g.lvl[k]]);
-        d->lfovf_len = M + g.ptr[M];
-        d->lfovf_count = (int32_t)std::min<size_t>(list_entries, 4096);
+        for (int32_t k = 0; k < M; ++k) t.slot[k] = g.lvl[k] * P + (g.pos[k] - nlvl_ptr[g.lvl[k]]);
+        if (by_kernel) {
+            d->lfovf_len = M + g.ptr[M];
+            d->lfovf_count = (int32_t)std::min<size_t>(list_entries, 4096);
+            t.lfovf_used.assign(1, 0);
+        } else {
+            // While level l is computed the ring holds the slots from (l + 1) * P - ring on.
+            const int32_t row_bytes = d->k1_wc * 8, zero_row = lring * row_bytes;
+            t.lrecs.assign((size_t)n_node_levels * P, Dag::FastRec{{zero_row, zero_row, zero_row, zero_row}, {-1, -1}, -1, -1});
+            for (int32_t k = 0; k < M; ++k) {
+                const int32_t oldest = (g.lvl[k] + 1) * P - lring;
+                fast(t.lrecs[t.slot[k]], k, zero_row, t.lfovf,
+                     [&](int32_t x) { return t.slot[x] >= oldest ? (t.slot[x] & (lring - 1)) * row_bytes : -1; },
+                     [&](int32_t x) { return t.slot[x]; });
+            }
+            d->lfovf_len = (int32_t)t.lfovf.size();
+            d->lfovf_count = d->lfovf_len <= 4096 ? d->lfovf_len : 0;
+            t.lfovf_used.assign(1, d->lfovf_len);
+        }
     } else if (!d->k1_wide) {
         const int32_t row_bytes = d->k1_wc * 8, zero_row = ring * row_bytes;
         t.frecs.resize(M);
@@ -1089,9 +1161,22 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     bool topological = true;
     std::vector<int32_t> level(n, 0);
     int32_t n_levels = 0;
+    const bool mixed = mixed_degrees(n, E);
     for (int32_t v = 0; v < n; ++v) {
-        int32_t l = 0;
-        for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) {
+        int32_t l = 0, e0 = row_ptr[v];
+        const int32_t e1 = row_ptr[v + 1];
+        // (one to four predecessors, as most ops have: the last one again in place of those that are missing, so that no
+        // branch depends on how many there are)
+        if (mixed && (uint32_t)(e1 - e0 - 1) < 4u) {
+            const int32_t a = col_idx[e0], b = col_idx[std::min(e0 + 1, e1 - 1)], c = col_idx[std::min(e0 + 2, e1 - 1)], f = col_idx[e1 - 1];
+            const uint32_t most = std::max(std::max((uint32_t)a, (uint32_t)b), std::max((uint32_t)c, (uint32_t)f));
+            if (most < (uint32_t)n) {
+                topological &= most < (uint32_t)v;
+                l = std::max(std::max(level[a], level[b]), std::max(level[c], level[f])) + 1;
+                e0 = e1;
+            }
+        }
+        for (int32_t e = e0; e < e1; ++e) {
             const int32_t u = col_idx[e];
             if (u < 0 || u >= n) { set_error("pred_col_idx[%d]=%d out of range", e, u); return TICTAC_ERR_BAD_CSR; }
             topological &= u < v;
@@ -1132,21 +1217,24 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     PropTables prop;
     std::future<void> prop_made;            // (after what its thread works on: it ends first)
     if ((size_t)n * d->W) {
-        auto make = [&] { make_propagate_tables(d, row_ptr, col_idx, recv_of_op, level, order, prop); };
+        auto make = [&] { make_propagate_tables(d, row_ptr, col_idx, recv_of_op, level, order, !on_host, prop); };
         if (on_host && (int64_t)n + E > kPropThread) prop_made = std::async(make);
         else make();
     }
+    std::vector<int32_t> op_of_col;
     if (on_host) {
         host_sets(n, d->W, row_ptr, col_idx, recv_of_op, order, sets);
     } else {
-        std::vector<int32_t> op_of_col;
         const std::vector<int32_t> zeros(64, 0);
         Packer graph;
         prop.add_to(graph, d);
         graph.add(&d->d_recv_of_op, recv_of_op);
-        op_of_col.reserve(d->N);
-        for (int32_t v = 0; v < n; ++v)
-            if (recv_of_op[v] < 0) op_of_col.push_back(v);
+        op_of_col.resize((size_t)d->N + 1);
+        for (int32_t v = 0, j = 0; v < n; ++v) {
+            op_of_col[j] = v;
+            j += recv_of_op[v] < 0;
+        }
+        op_of_col.pop_back();
         graph.add(&d->d_op_of_col, op_of_col);
         graph.add(&d->d_bad_order, zeros);
         graph.reserve(&d->d_dep, (size_t)n * d->W * 8);
@@ -1166,7 +1254,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     // table, the host numbers the sets, and the device forms the class rows and checks every op's row against its class (on a mismatch, which two
     // different rows with one hash would cause, everything below is done again from the rows themselves).
     std::vector<uint64_t> rows, cls_dep, depT;
-    std::vector<int32_t> cls_ptr, cls_cols, cnt0, first_op, lowest, cls_of_set, op_src, op_of_col;
+    std::vector<int32_t> cls_ptr, cls_cols, cnt0, first_op, lowest, cls_of_set, op_src, col_cls;
     const std::vector<int32_t> zeros(64, 0);
     // only classes far larger than a lane's fair share of the ops are split
     const int32_t max_members = std::min(256, std::max(16, (d->N + 63) / 64));
@@ -1183,14 +1271,11 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         HIP_TRY(hipMemcpyAsync(rep, d->d_work, (size_t)d->N * 12, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         std::vector<int32_t> first_col;
-        group_reps(rep, d->N, max_members, cls_ptr, cls_cols, first_col, d->C_distinct);
+        group_reps(rep, d->N, max_members, cls_ptr, cls_cols, first_col, col_cls, d->C_distinct);
         d->C = (int32_t)cls_ptr.size() - 1;
         d->Cpad = (d->C + 63) / 64 * 64;
         if (d->R <= 1024 && d->C <= 1024) return 1;      // the small-graph kernels want tables made from the rows
         cnt0.resize(d->C); first_op.resize(d->C); lowest.resize(d->C);
-        op_of_col.reserve(d->N);
-        for (int32_t v = 0; v < n; ++v)
-            if (recv_of_op[v] < 0) op_of_col.push_back(v);
         for (int32_t c = 0; c < d->C; ++c) {
             cnt0[c] = rep[(size_t)d->N + first_col[c]];
             lowest[c] = rep[(size_t)2 * d->N + first_col[c]];
@@ -1292,9 +1377,11 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
     cls.add(&d->d_cls_cnt0, cnt0);
     cls.add(&d->d_cls_ptr, cls_ptr);
     cls.add(&d->d_cls_cols, cls_cols);
-    std::vector<int32_t> col_cls(d->N, 0);
-    for (int32_t c = 0; c < d->C; ++c)
-        for (int32_t m = cls_ptr[c]; m < cls_ptr[c + 1]; ++m) col_cls[cls_cols[m]] = c;
+    if (col_cls.empty()) {
+        col_cls.assign(d->N, 0);
+        for (int32_t c = 0; c < d->C; ++c)
+            for (int32_t m = cls_ptr[c]; m < cls_ptr[c + 1]; ++m) col_cls[cls_cols[m]] = c;
+    }
     cls.add(&d->d_col_cls, col_cls);
     if (!on_device && d->C <= 512 + kChainMaxGates) d->h_cls_dep = cls_dep;
 
@@ -1326,10 +1413,7 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         cls.reserve(&d->d_cls_depT, (size_t)d->W * d->Cpad * 8);
     }
     HIP_TRY(cls.commit(d->class_block, d->device, s));
-    if (from_sets && dep_words) {
-        HIP_TRY(launch_expand_sets(*d, s));
-        HIP_TRY(launch_level_records(*d, s));
-    }
+    if (from_sets && dep_words) HIP_TRY(launch_expand_sets(*d, s));
     int32_t *mismatch = d->d_bad_order + 1;         // (a second word of the zeroed flag block)
     if (on_device) HIP_TRY(launch_class_rows(*d, d->d_op_of_col, d->d_cls_first_op, mismatch, s));
     int32_t differs = 0;

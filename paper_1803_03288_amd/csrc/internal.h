@@ -102,9 +102,10 @@ struct Dag {
     // graph takes another kernel.
     FastRec *d_lrecs = nullptr;     // [n_node_levels * P]
     int32_t *d_lfovf = nullptr;
-    int32_t lfovf_len = 0;          // room for them (the kernel that makes the records makes the lists: *d_lfovf_used entries)
-    int32_t lfovf_count = 0;        // those of the nodes with more than four nodes or two recvs among their inputs, up to 4 096
-    // what the records are made from: the condensed graph by node, the slot of every node
+    int32_t lfovf_len = 0;          // room for its entries, of which *d_lfovf_used are in use
+    int32_t lfovf_count = 0;        // entries, up to 4 096, that LDS is to have room for where several graphs share a compute unit:
+                                    // all (0 if more), or where a kernel makes the lists those of nodes with more than four nodes or two recvs
+    // what that kernel makes the records from (launch_level_records): the condensed graph by node, the slot of every node
     int32_t *d_node_ptr = nullptr, *d_node_in = nullptr, *d_node_op = nullptr, *d_node_slot = nullptr, *d_lfovf_used = nullptr;
     int32_t k1_lring = 0;           // slots held in LDS (a power of two, at least 16 levels)
     // The level-major records of the kernel with 64-byte slices (four lanes per slot, P = k1_threads / 4):

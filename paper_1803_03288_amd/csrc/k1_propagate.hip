@@ -823,7 +823,7 @@ level_records_kernel(const LevelRecordParams p)
 
 hipError_t launch_level_records(const Dag &d, hipStream_t s)
 {
-    if (!d.d_lrecs || d.M <= 0) return hipSuccess;
+    if (!d.d_lrecs || !d.d_node_ptr || d.M <= 0) return hipSuccess;          // (there are none, or the host has made them)
     LevelRecordParams p;
     p.M = d.M; p.n_levels = d.n_node_levels; p.P = d.k1_threads / d.k1_wc; p.ring = d.k1_lring; p.row_bytes = d.k1_wc * 8; p.room = d.lfovf_len;
     p.lvl_ptr = d.d_nlvl_ptr; p.ptr = d.d_node_ptr; p.in = d.d_node_in; p.op = d.d_node_op; p.slot = d.d_node_slot;
