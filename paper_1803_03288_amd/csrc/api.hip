@@ -2176,6 +2176,17 @@ static int ensure_send_tables(Dag *d, int32_t n_send, const int32_t *send_ids, h
                 if (recv_of_op[d->h_col_idx[e]] >= 0) st_chk.push_back(recv_of_op[d->h_col_idx[e]]);
         }
         if (!ok) { st_tiles.clear(); st_code.clear(); st_chk.clear(); }
+        // (sends alone at the end: nothing runs there)
+        while (st_tiles.size() > 2 && !(st_tiles.back().x | st_tiles.back().y | st_tiles.back().z | st_tiles.back().w)) {
+            st_tiles.resize(st_tiles.size() - 2);
+            st_code.resize(st_tiles.size() * 32);
+        }
+        d->straight_req_lo = d->straight_req_span = 0;
+        if (!st_req.empty()) {
+            const auto ends = std::minmax_element(st_req.begin(), st_req.end());
+            d->straight_req_lo = *ends.first;
+            d->straight_req_span = *ends.second - *ends.first + 1;
+        }
     }
     st_chk.resize(st_chk.size() + 32, 0);
     d->n_straight_tiles = (int32_t)st_tiles.size() / 2;

@@ -202,7 +202,7 @@ struct Dag {
     uint32_t *d_straight_code = nullptr;
     int32_t *d_straight_chk = nullptr, *d_straight_req = nullptr;
     int4 *d_straight_tiles = nullptr;
-    int32_t n_straight_tiles = 0;
+    int32_t n_straight_tiles = 0, straight_req_lo = 0, straight_req_span = 0;   // (the columns that the sends lie in)
     int32_t n_send_free = 0;
     size_t work_bytes = 0;
     // of the tables below, which a handle's first TAC call makes

@@ -18,10 +18,13 @@
 // (busy -> max(busy + A, B)).
 //
 // 16 384 samples of the ResNet-50 inference graph with 161 sends (187 MB of times, 38 us at the copy rate): 4.0 ms in the
-// event-driven form with a wave per sample, 97 us here.  Bound by the latencies of a tile, since there is one workgroup
-// of 64 samples per compute unit: 15 us for the arrivals, 60 us for the 20 tiles, 20 us for the uplink.  With the columns
-// followed one by one the fifth wave took 4 us per tile (137 us in all), at the columns that matter 2 us.  On times that are
-// not quantised makespan, U and L are within 4e-16 of sums in long double (event-driven form: 3e-15).
+// event-driven form with a wave per sample, 75 us here (the call 86 us).  Bound by the latencies of a tile, since there is
+// one workgroup of 64 samples per compute unit: 13 us for the arrivals, 43 us for the 18 tiles (18 of them for the fifth wave,
+// which is behind the loaders then), 7 us for the uplink.  It was 93 us (18, 55, 20) as long as the loads of a batch hid
+// behind branches, each with a wait of its own, the times of transfers and sends were read by a lane per row, and a wait for an
+// index in a table was one for the tiles on their way.  With the columns followed one by one the fifth wave took 4 us per
+// tile, at the columns that matter 2 us.  On times that are not quantised makespan, U and L are within 4e-16 of sums in long
+// double (event-driven form: 3e-15).
 #include <algorithm>
 
 #include "device_utils.h"
@@ -30,10 +33,20 @@
 namespace tictac {
 
 constexpr int kTileCols = 64, kTileChecks = 32, kTilePitch = 65;
+constexpr int kRowCols = (2 * kTileCols * kTilePitch + 2 * kTileChecks * 64) / kTilePitch;      // columns of 64 rows that fit the tiles' space
 typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
+
+// The tables are the same for all lanes: read through the scalar cache, they have a counter of waits of their own.  (By vector
+// loads, a wait for the number of a recv was one for the tiles on their way as well.)
+typedef int Int2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef int Int4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int uniform_int(const int32_t *p) { return *(const __attribute__((address_space(4))) int *)p; }
+__device__ __forceinline__ Int2 uniform_int2(const int32_t *p) { return *(const __attribute__((address_space(4))) Int2 *)p; }
+__device__ __forceinline__ Int4 uniform_int4(const int4 *p) { return *(const __attribute__((address_space(4))) Int4 *)p; }
 
 struct StraightParams {
     int32_t B, N, R, n_req, n_req0, n_tiles;
+    int32_t req_lo, req_span;       // the columns of the sends lie in req_lo .. req_lo + req_span - 1; 0: in more than kRowCols
     const uint32_t *code;           // [n_tiles * 64] see internal.h
     const int32_t *chk;             // recvs, in the order in which the columns need them; 32 zeros after the last
     const int32_t *req_col;         // [n_req] columns of the sends in the order of their requests, the first n_req0 at 0
@@ -62,12 +75,42 @@ sends_straight_kernel(const StraightParams p)
     double *arrive = p.arrive + (size_t)blockIdx.x * (R + 1) * 64;
     double *req_at = p.req_at + (size_t)blockIdx.x * p.n_req * 64;
     const int groups = (p.B + 63) / 64;
+    const int at_row = tid >> 5, at_col = (tid & 31) * 2;       // (of the loaders)
+    const bool rows_fit = R >= 2 && R <= kRowCols;
 
     for (int g = blockIdx.x; g < groups; g += gridDim.x) {
         const int b0 = g * 64, here = min(64, p.B - b0);
         const int64_t b = min(b0 + lane, p.B - 1);
 
-        // ---- arrivals: each loader takes a quarter of the transfers, twice (sums, then ends) ----
+        // columns lo .. lo + span - 1 (at most kRowCols) of the 64 rows into the tiles' space, by the four loaders, all loads
+        // before the first store
+        auto rows_to_lds = [&](const double *src, int width, int lo, int span) __attribute__((always_inline)) {
+            Pair v[3][8];
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                if (t * 64 < span) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        v[t][i] = *reinterpret_cast<const Pair *>(src + (int64_t)min(b0 + i * 8 + at_row, p.B - 1) * width +
+                                                                  min(lo + t * 64 + at_col, width - 2));
+                }
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                if (t * 64 < span) {
+                    const int c = t * 64 + at_col;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        if (c < span) xs[c * kTilePitch + i * 8 + at_row] = lo + c > width - 2 ? v[t][i].y : v[t][i].x;
+                        if (c + 1 < span) xs[(c + 1) * kTilePitch + i * 8 + at_row] = v[t][i].y;
+                    }
+                }
+        };
+        // ---- arrivals: each loader takes a quarter of the transfers, twice (sums, then ends); their times from LDS if they
+        // fit it (a lane that reads its own row of memory asks for 64 lines per load) ----
+        if (rows_fit) {
+            if (loader) rows_to_lds(p.recv_time, R, 0, R);
+            __syncthreads();
+        }
         const int quarter = (R + 3) / 4, k0 = min(R, wave * quarter), k1 = loader ? min(R, k0 + quarter) : k0;
         double sum = 0.0;
         for (int pass = 0; pass < 2; ++pass) {
@@ -78,19 +121,23 @@ sends_straight_kernel(const StraightParams p)
                 for (int w = 0; w < wave; ++w) sum += red[w * 64 + lane];
             }
             for (int k = k0; k < k1; k += 16) {
+                // (all loads are executed, with places past the end clamped, so that nothing waits between them)
                 int r[16];
                 double x[16];
 #pragma unroll
-                for (int q = 0; q < 16; ++q) r[q] = k + q < k1 ? p.order[b * p.order_stride + k + q] : -1;
+                for (int q = 0; q < 16; ++q) r[q] = p.order[b * p.order_stride + min(k + q, k1 - 1)];
+                if (rows_fit) {
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    x[q] = 0.0;
-                    if ((unsigned)r[q] < (unsigned)R) x[q] = p.recv_time[b * R + r[q]];     // (invalid: skipped)
+                    for (int q = 0; q < 16; ++q) x[q] = xs[min((unsigned)r[q], (unsigned)R - 1u) * kTilePitch + lane];
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) x[q] = p.recv_time[b * R + min((unsigned)r[q], (unsigned)R - 1u)];
                 }
 #pragma unroll
                 for (int q = 0; q < 16; ++q) {
-                    sum += x[q];
-                    if (pass == 1 && (unsigned)r[q] < (unsigned)R) arrive[(size_t)r[q] * 64 + lane] = sum;
+                    const bool valid = k + q < k1 && (unsigned)r[q] < (unsigned)R;          // (invalid: skipped)
+                    sum += valid ? x[q] : 0.0;
+                    if (pass == 1) arrive[(size_t)(valid ? r[q] : R) * 64 + lane] = sum;    // (row R is spare)
                 }
             }
         }
@@ -104,24 +151,22 @@ sends_straight_kernel(const StraightParams p)
         if (loader) {
             // Two tiles are on their way while a third is worked on, their registers by turns.  Every load is executed
             // (places outside the tile read something else, which the masks drop), so that the waits can be counted.
-            const int at_row = tid >> 5, at_col = (tid & 31) * 2;
             auto load = [&](int t, Pair (&x)[8], Pair (&a)[4], uint32_t &code) {
-                const int4 tile = p.tiles[2 * t];
+                const Int4 tile = uniform_int4(p.tiles + 2 * t);
                 const int c = tile.x + at_col, from = min(c, N - 2);
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
                     x[i] = *reinterpret_cast<const Pair *>(p.op_time + (int64_t)min(b0 + i * 8 + at_row, p.B - 1) * N + from);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int32_t *q = p.chk + tile.z + i * 8 + wave * 2;
-                    const int r0 = q[0], r1 = q[1];
-                    a[i] = *reinterpret_cast<const Pair *>(arrive + (size_t)((at_row & 1) ? r1 : r0) * 64 + at_col);
+                    const Int2 r = uniform_int2(p.chk + tile.z + i * 8 + wave * 2);
+                    a[i] = *reinterpret_cast<const Pair *>(arrive + (size_t)((at_row & 1) ? r.y : r.x) * 64 + at_col);
                 }
                 code = p.code[t * kTileCols + lane];
             };
             // into LDS: the sums of the row's times up to every column (sends count as zeros)
             auto keep = [&](int t, const Pair (&x)[8], const Pair (&a)[4], uint32_t code) {
-                const int4 tile = p.tiles[2 * t], mask = p.tiles[2 * t + 1];
+                const Int4 tile = uniform_int4(p.tiles + 2 * t), mask = uniform_int4(p.tiles + 2 * t + 1);
                 const uint64_t run = (uint64_t)(uint32_t)mask.y << 32 | (uint32_t)mask.x;
                 const bool run0 = run >> at_col & 1ull, run1 = run >> at_col & 2ull, shifted = tile.x + at_col > N - 2;
                 double *xt = xs + (t & 1) * kTileCols * kTilePitch, *at = as + (t & 1) * kTileChecks * 64;
@@ -154,45 +199,62 @@ sends_straight_kernel(const StraightParams p)
             load(min(1, last), x1, a1, c1);
             keep(0, x0, a0, c0);
             __syncthreads();
+            // (six tiles per trip: at the head of a loop the compiler waits for all loads on their way)
+#define SS_TILE(xa, aa, ca, xb, ab, cb)                                                   \
+                load(min(t + 2, last), xa, aa, ca);                                       \
+                keep(t + 1, xb, ab, cb);            /* (past the last tile: into the buffer that nobody reads) */ \
+                lds_barrier();                                                            \
+                if (stop[t & 1]) { given_up = true; break; }                              \
+                if (++t > last) break;
             for (int t = 0;;) {
-                load(min(t + 2, last), x0, a0, c0);
-                keep(t + 1, x1, a1, c1);                        // (past the last tile: into the buffer that nobody reads)
-                __syncthreads();
-                if (stop[t & 1]) { given_up = true; break; }
-                if (++t > last) break;
-                load(min(t + 2, last), x1, a1, c1);
-                keep(t + 1, x0, a0, c0);
-                __syncthreads();
-                if (stop[t & 1]) { given_up = true; break; }
-                if (++t > last) break;
+                SS_TILE(x0, a0, c0, x1, a1, c1)
+                SS_TILE(x1, a1, c1, x0, a0, c0)
+                SS_TILE(x0, a0, c0, x1, a1, c1)
+                SS_TILE(x1, a1, c1, x0, a0, c0)
+                SS_TILE(x0, a0, c0, x1, a1, c1)
+                SS_TILE(x1, a1, c1, x0, a0, c0)
             }
         } else {
             double *req = req_at + (size_t)p.n_req0 * 64 + lane;
             __syncthreads();
             for (int t = 0; t < p.n_tiles; ++t) {
-                const int4 mask = p.tiles[2 * t + 1];
+                const Int4 mask = uniform_int4(p.tiles + 2 * t + 1);
                 const uint64_t special = (uint64_t)(uint32_t)mask.w << 32 | (uint32_t)mask.z;   // recvs to look at, sends to request
                 const uint32_t code = codes[(t & 1) * kTileCols + lane];
                 const double *xt = xs + (t & 1) * kTileCols * kTilePitch + lane;
                 const double *at = as + (t & 1) * kTileChecks * 64 + lane;
                 const double all = xt[(kTileCols - 1) * kTilePitch];
-                // only the columns with recvs or sends are looked at; the device is at base + the sum up to there
+                // only the columns with recvs or sends are looked at, four at a time with their reads from LDS together; the
+                // device is at base + the sum up to there
                 uint64_t rest = special;
+                int at_chk = 0;
                 while (rest != 0ull) {
-                    const int c = __builtin_ctzll(rest);
-                    rest &= rest - 1ull;
-                    const uint32_t todo = (uint32_t)__builtin_amdgcn_readlane((int)code, c);
-                    const double done = xt[c * kTilePitch];
-                    if (const int n_chk = (int)(todo >> 1 & 0x7fu)) {
-                        double before = xt[max(c - 1, 0) * kTilePitch], last = *at;
-                        if (c == 0) before = 0.0;
-                        at += 64;
-                        for (int j = 1; j < n_chk; ++j, at += 64) last = max_f64(last, *at);
-                        const bool late = last > base + before;
-                        off |= !(todo & 0x100u) && late;
-                        base = late ? last - before : base;     // (`off`: whatever, the sample is given up)
+                    uint32_t todo[4];
+                    int first_chk[4];
+                    double done[4], before[4], arrived[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int c = rest ? __builtin_ctzll(rest) : 0;
+                        todo[i] = rest ? (uint32_t)__builtin_amdgcn_readlane((int)code, c) : 0u;
+                        rest &= rest - 1ull;                    // (0 stays 0)
+                        first_chk[i] = at_chk;
+                        at_chk += (int)(todo[i] >> 1 & 0x7fu);
+                        done[i] = xt[c * kTilePitch];
+                        before[i] = xt[max(c - 1, 0) * kTilePitch];
+                        before[i] = c == 0 ? 0.0 : before[i];
+                        arrived[i] = at[min(first_chk[i], kTileChecks - 1) * 64];
                     }
-                    for (uint32_t j = todo >> 16; j > 0u; --j) { *req = base + done; req += 64; }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (const int n_chk = (int)(todo[i] >> 1 & 0x7fu)) {
+                            double last = arrived[i];
+                            for (int j = 1; j < n_chk; ++j) last = max_f64(last, at[(first_chk[i] + j) * 64]);
+                            const bool late = last > base + before[i];
+                            off |= !(todo[i] & 0x100u) && late;
+                            base = late ? last - before[i] : base;      // (`off`: whatever, the sample is given up)
+                        }
+                        for (uint32_t j = todo[i] >> 16; j > 0u; --j) { *req = base + done[i]; req += 64; }
+                    }
                 }
                 base += all;
                 sum_c += all;
@@ -202,20 +264,28 @@ sends_straight_kernel(const StraightParams p)
             }
         }
 
-        // ---- the uplink ----
+        // ---- the uplink; its times from LDS too if their columns fit it ----
+        if (p.req_span > 0 && !given_up) {                      // (the same for all waves)
+            if (loader) rows_to_lds(p.op_time, N, p.req_lo, p.req_span);
+            __syncthreads();
+        }
         double add = 0.0, least = -TT_INF;
         if (loader && !given_up) {
             const int part = (p.n_req + 3) / 4, q0 = min(p.n_req, wave * part), q1 = min(p.n_req, q0 + part);
             for (int q = q0; q < q1; q += 16) {
                 double at[16], y[16];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    at[i] = y[i] = 0.0;
-                    if (q + i < q1) {
-                        y[i] = p.op_time[b * N + p.req_col[q + i]];
-                        if (q + i >= p.n_req0) at[i] = req_at[(size_t)(q + i) * 64 + lane];
-                    }
+                for (int i = 0; i < 16; ++i) at[i] = req_at[(size_t)min(q + i, q1 - 1) * 64 + lane];
+                if (p.req_span > 0) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) y[i] = xs[(uniform_int(p.req_col + min(q + i, q1 - 1)) - p.req_lo) * kTilePitch + lane];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) y[i] = p.op_time[b * N + uniform_int(p.req_col + min(q + i, q1 - 1))];
                 }
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (q + i < p.n_req0) at[i] = 0.0;          // (requested at the start: not stored)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     if (q + i < q1) { add += y[i]; least = max_f64(least, at[i]) + y[i]; }
@@ -270,6 +340,7 @@ hipError_t launch_sends_straight(Dag &d, const SimArgs &a, size_t rest, int32_t 
     const int grid = std::min(groups, device_cu_count(d.device));
     StraightParams p{};
     p.B = a.B; p.N = d.N; p.R = d.R; p.n_req = (int32_t)d.h_send_ids.size(); p.n_req0 = d.n_send_free; p.n_tiles = d.n_straight_tiles;
+    p.req_lo = d.straight_req_lo; p.req_span = d.straight_req_span <= kRowCols ? d.straight_req_span : 0;
     p.code = d.d_straight_code; p.chk = d.d_straight_chk; p.req_col = d.d_straight_req; p.tiles = d.d_straight_tiles;
     p.order = a.order; p.order_stride = a.order_stride;
     p.op_time = static_cast<const double *>(a.op_time); p.recv_time = static_cast<const double *>(a.recv_time);
