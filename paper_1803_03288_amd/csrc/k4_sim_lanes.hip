@@ -73,12 +73,35 @@ __device__ __forceinline__ void write_metrics(const SimLanesParams &p, int b, do
     if (p.S) p.S[b] = (U == L || L == 0.0) ? 0.0 : (U - L) / L;
 }
 
-template <typename T>
+// TILES > 0: the rows of the next 64 samples are requested into registers before those in LDS are computed, as TILES pieces
+// of 256 bytes of the op_time rows and one of the recv_time rows; 0: longer rows are brought when they are needed.  All waves
+// of a compute unit start together, so without that they load together and compute together: vgg16 as above spent 23 us
+// loading, 16 computing and 9 before the first sample, 49 in all; now the first rows come while the events are formed and
+// the others while samples are computed: 35 us.  All loads are executed without a branch, a lane past the end of a row reads
+// its last columns once more.
+template <typename T, int TILES>
 __global__ void __launch_bounds__(64)
 simulate_lanes_shared_kernel(const SimLanesParams p)
 {
     extern __shared__ char lanes_smem[];
     const int N = p.N, R = p.R, W = p.W, C = p.C, lane = threadIdx.x;
+    constexpr int VEC = 16 / (int)sizeof(T), LPR = 16, TC = LPR * VEC, RPI = 64 / LPR, NI = 64 / RPI;
+    typedef T Vec __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
+    const int sub = (lane % LPR) * VEC, lr = lane / LPR;
+    Vec ahead[TILES + 1][NI];
+    auto request = [&](int g) __attribute__((always_inline)) {
+        const int last = min(63, p.B - 1 - g * 64);
+        const T *op = static_cast<const T *>(p.op_time) + (size_t)g * 64 * N, *rv = static_cast<const T *>(p.recv_time) + (size_t)g * 64 * R;
+#pragma unroll
+        for (int t = 0; t <= TILES; ++t)
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int row = min(i * RPI + lr, last);
+                ahead[t][i] = t < TILES ? *reinterpret_cast<const Vec *>(op + (row * N + min(t * TC + sub, N - VEC)))
+                                        : *reinterpret_cast<const Vec *>(rv + (row * R + min(sub, R - VEC)));
+            }
+    };
+    if (TILES > 0) request(blockIdx.x);
     T *tile = reinterpret_cast<T *>(lanes_smem);        // [N + R + 1][65]: columns, recvs, zeros
     // ---- the events, formed in the space of the tile: tile row | 0x8000 for a transfer ----
     int32_t *pos = reinterpret_cast<int32_t *>(lanes_smem);     // [R] 1-based position, 0: left out
@@ -134,13 +157,28 @@ simulate_lanes_shared_kernel(const SimLanesParams p)
     wave_sync();
     tile[n_ev * 65 + lane] = T(0);
 
-    // (requesting the rows of the next group while one is computed takes twice the registers: 41 -> 60 us on vgg16)
     for (int g = blockIdx.x; g < p.n_groups; g += gridDim.x) {
         const int b0 = g * 64;
         wave_sync();                                    // the rows of the group before are not read any more
-        rows_to_lds(tile, 0, static_cast<const T *>(p.op_time), N, b0, p.B, lane);
-        rows_to_lds(tile, N, static_cast<const T *>(p.recv_time), R, b0, p.B, lane);
-        wave_sync();
+        if constexpr (TILES > 0) {
+#pragma unroll
+            for (int t = 0; t <= TILES; ++t) {
+                const int first = t < TILES ? 0 : N, width = t < TILES ? N : R, c = t < TILES ? t * TC + sub : sub;
+                if (c < width) {                        // (the last lane of a row may repeat columns of the one before)
+                    T *to = tile + (first + min(c, width - VEC)) * 65 + lr;
+#pragma unroll
+                    for (int i = 0; i < NI; ++i)
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) to[e * 65 + i * RPI] = ahead[t][i][e];
+                }
+            }
+            wave_sync();
+            if (g + (int)gridDim.x < p.n_groups) request(g + gridDim.x);
+        } else {
+            rows_to_lds(tile, 0, static_cast<const T *>(p.op_time), N, b0, p.B, lane);
+            rows_to_lds(tile, N, static_cast<const T *>(p.recv_time), R, b0, p.B, lane);
+            wave_sync();
+        }
         double F = 0.0, busy = 0.0, sum_c = 0.0;
 #pragma unroll
         for (int q = 0; q < kLaneCols / 64; ++q) {
@@ -317,7 +355,12 @@ static hipError_t launch_lanes_t(SimLanesParams &p, const Dag &d, hipStream_t s)
     lds = (lds + 15) & ~(size_t)15;
     // (two waves per compute unit at the least)
     if (lds > 80 * 1024) return hipErrorNotSupported;
-    const void *kern = shared ? reinterpret_cast<const void *>(simulate_lanes_shared_kernel<T>) : reinterpret_cast<const void *>(simulate_lanes_kernel<T>);
+    // (the registers of three pieces of 64 rows, 192, are what a wave has beside its own at two waves per SIMD)
+    constexpr int VEC = 16 / (int)sizeof(T), TC = 16 * VEC;
+    const bool fits = p.N >= VEC && p.R >= VEC && p.N <= 2 * TC && p.R <= TC;
+    void (*const kernel)(SimLanesParams) = !shared ? simulate_lanes_kernel<T> : !fits ? simulate_lanes_shared_kernel<T, 0>
+                                           : p.N <= TC ? simulate_lanes_shared_kernel<T, 1> : simulate_lanes_shared_kernel<T, 2>;
+    const void *kern = reinterpret_cast<const void *>(kernel);
     hipError_t e;
     if (lds > 48 * 1024) {
         e = ensure_dynamic_lds(kern, lds);
@@ -327,13 +370,12 @@ static hipError_t launch_lanes_t(SimLanesParams &p, const Dag &d, hipStream_t s)
     e = cached_blocks_per_cu(&per_cu, kern, 64, lds);
     if (e != hipSuccess) return e;
     const int grid = std::min(p.n_groups, per_cu * device_cu_count(d.device));
-    if (shared) hipLaunchKernelGGL(simulate_lanes_shared_kernel<T>, dim3(grid), dim3(64), lds, s, p);
-    else hipLaunchKernelGGL(simulate_lanes_kernel<T>, dim3(grid), dim3(64), lds, s, p);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), lds, s, p);
     return hipGetLastError();
 }
 
 // One order for all samples: always, where the rows fit (vgg16, 262 144 samples as float32, with the straggler effect:
-// 168 -> 54 us, 105 MB; float64 146 -> 80 us; tiny 570 -> 72 us; with few samples 31 -> 23 us, the checks and kappa are no
+// 168 -> 40 us, 105 MB; float64 146 -> 63 us; tiny 570 -> 54 us; with few samples 31 -> 23 us, the checks and kappa are no
 // launches of their own).  An order per sample: from 24 576 samples on (vgg16 float32 225 -> 157 us, float64 212 -> 196 us
 // for 262 144; tiny 655 -> 221 us, float32 133 us); a smaller batch leaves compute units without a wave of 64 samples, and a
 // wave per sample is done sooner (16 384 samples: vgg16 25 against 28 us).
