@@ -34,6 +34,9 @@ struct TotalsParams {
 // Per tile 256 bytes of each of the 64 rows: a request of a wave covers four rows.  (128 and 512 bytes: 4 % and 5 % slower
 // on inception3's rows, 4 % and 12 % on resnet50's; 0.70 ms and 0.15 ms for 65 536 samples, 4.7 and 4.4 TB/s.)  The next
 // tile is requested once the present one is in LDS.
+// Totals and times are written past the caches, which hold neither all of them (434 MB for inception3) nor then what is read
+// meanwhile: inception3 773 -> 761 us and 366 -> 355 for tac_chain_kernel, resnet50 204 -> 198.  (The rows read past the
+// caches, whose 128-byte lines two requests share, take 894 us, the orders written so 7 us more.)
 template <typename T>
 __global__ void __launch_bounds__(64, 2)
 class_totals_kernel(const TotalsParams p)
@@ -89,7 +92,7 @@ class_totals_kernel(const TotalsParams p)
             for (int c = 0; c < n; ++c) {
                 const double y = (double)tile[c * 65 + lane];
                 zero_seen |= !(y > 0.0);
-                out[(size_t)(c0 + c) * p.Bp] = y;
+                __builtin_nontemporal_store(y, &out[(size_t)(c0 + c) * p.Bp]);
             }
         }
         if (b0 + lane < p.B) p.flags[b0 + lane] = zero_seen ? 1 : 0;
@@ -110,7 +113,7 @@ class_totals_kernel(const TotalsParams p)
             for (int c = 0; c < 16; ++c) {
                 acc += (double)tile[(16 * h + c) * 65 + lane];
                 if ((mask >> c) & 1u) {
-                    out[(size_t)p.flush_row[run++] * p.Bp] = acc;
+                    __builtin_nontemporal_store(acc, &out[(size_t)p.flush_row[run++] * p.Bp]);
                     acc = 0.0;
                 }
             }
@@ -158,7 +161,7 @@ static size_t chain_lds_bytes(int NC, const ChainParams &p)
 // different chains): one trip to LDS for the row and one for all its recvs.  A round has four dependent trips: the record
 // of the recv taken; its ring entry, gates and joins; the row; the recvs of the row.  With the successors one after the
 // other, each behind its list, its record and its gate, there were up to nine trips more per successor: 65 536 samples,
-// inception3 (four branches) 377 -> 366 us, resnet50 (two) 99 -> 94 us.  What is left, from copies that leave something
+// inception3 (four branches) 377 -> 366 us (355 since totals are written past the caches), resnet50 (two) 99 -> 94 us.  What is left, from copies that leave something
 // out: 80 and 21 us are the stores of the selections, 40 us and nothing the loads, the rest is a round's 110 vector
 // instructions and its trips to LDS.  (A second wave that writes the selections takes the stores off the chain's wave and
 // is no faster: 387 and 93 us.)  SECOND: some recv is a sink of two gates.
