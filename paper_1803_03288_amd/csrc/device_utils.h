@@ -238,16 +238,39 @@ __device__ __forceinline__ void add_by_rows(double *sums, int at, double x, int 
     if (at >= 0 && (!whole || (lane & 15) == 0)) atomicAdd(&sums[at], whole ? all : x);
 }
 
+// x to sums[at] (at < 0: nowhere), four lanes next to each other with one place by one addition; by all lanes of a wave.
+__device__ __forceinline__ void add_by_quads(double *sums, int at, double x)
+{
+    uint64_t quad = __ballot(at == dpp0_i32<0x111>(at)) | 0x1111111111111111ull;    // (the first of four is not compared)
+    quad &= quad >> 1;
+    quad &= (quad >> 2) & 0x1111111111111111ull;                    // bit 4 q: lanes 4 q to 4 q + 3 have one place
+    if (quad != 0ull) {
+        double all = x;
+        all += dpp0_f64<0xb1>(all);                                 // lanes 1, 0, 3, 2
+        all += dpp0_f64<0x4e>(all);                                 // lanes 2, 3, 0, 1
+        x = __builtin_amdgcn_inverse_ballot_w64(quad * 15ull) ? all : x;
+        at = __builtin_amdgcn_inverse_ballot_w64(quad * 14ull) ? -1 : at;
+    }
+    if (at >= 0) atomicAdd(&sums[at], x);
+}
+
+enum class Sums { plain, quads, rows };     // how class_totals adds what lanes next to each other have for one place
+
 // totals[cls_of[j]] += row[j] for j in [0, N), totals in LDS, by one wave.  A lane takes four
 // consecutive columns at a time and first adds up runs of equal class in registers: columns of
 // one class tend to sit next to each other, and every LDS add of several lanes to one address
 // is served one lane after the other.
-// ROWS: neighbours in the row mostly go to one place (add_by_rows)
-template <bool ROWS = false, typename T>
+// Sums::rows: neighbours in the row mostly go to one place (add_by_rows).
+// Sums::quads: four lanes with one class make one addition (add_by_quads).  Columns of one class are in runs of 14 on average on
+// inception3: 832 additions one after the other per sample become 280.  TAC in registers of 300 samples 236 -> 212 us, of 3 000
+// 265 -> 241; several channels, 65 536 samples, 987 -> 932.  With short runs (resnet50, 6) the test costs up to 8 % where
+// registers are few, on layered graphs nothing with more than four classes per lane: that is where those two kernels use it.
+// Simulation with an order each gains 1 to 2 % on some such graphs and loses that on others.
+template <Sums HOW = Sums::plain, typename T>
 __device__ __forceinline__ void class_totals(double *totals, const T *__restrict__ row,
                                              const int32_t *__restrict__ cls_of, int N, int lane)
 {
-    for (int j0 = lane * 4; (ROWS ? j0 - lane * 4 : j0) < N; j0 += 64 * 4 * 2) {     // (ROWS: no lane leaves before the others)
+    for (int j0 = lane * 4; (HOW == Sums::plain ? j0 : j0 - lane * 4) < N; j0 += 64 * 4 * 2) {   // (rows, quads: lanes leave together)
         // two groups of four in flight per lane
         double x[2][4];
         int c[2][4];
@@ -282,7 +305,7 @@ __device__ __forceinline__ void class_totals(double *totals, const T *__restrict
                     acc = x[g][i];
                 }
             }
-            if constexpr (ROWS) {
+            if constexpr (HOW == Sums::rows) {
                 if (g == 0) {
                     acc0 = acc;
                     cur0 = cur;
@@ -292,6 +315,8 @@ __device__ __forceinline__ void class_totals(double *totals, const T *__restrict
                     add_by_rows(totals, cur0, acc0, lane);
                     add_by_rows(totals, cur, acc, lane);
                 }
+            } else if constexpr (HOW == Sums::quads) {
+                add_by_quads(totals, cur, acc);
             } else if (cur >= 0) {
                 atomicAdd(&totals[cur], acc);
             }
@@ -299,12 +324,12 @@ __device__ __forceinline__ void class_totals(double *totals, const T *__restrict
     }
 }
 
-template <bool ROWS = false>
+template <Sums HOW = Sums::plain>
 __device__ __forceinline__ void class_totals(double *totals, const TimeRow &row, const int32_t *__restrict__ cls_of,
                                              int N, int lane)
 {
-    if (row.f32) class_totals<ROWS>(totals, row.as_f32(), cls_of, N, lane);
-    else class_totals<ROWS>(totals, row.as_f64(), cls_of, N, lane);
+    if (row.f32) class_totals<HOW>(totals, row.as_f32(), cls_of, N, lane);
+    else class_totals<HOW>(totals, row.as_f64(), cls_of, N, lane);
 }
 
 __device__ __forceinline__ int wave_min_i32(int v)

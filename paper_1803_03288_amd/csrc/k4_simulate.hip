@@ -259,7 +259,7 @@ simulate_wave_kernel(const SimWaveParams p)
         const int n_totals = KAPPA == kKappaTable ? R + 1 : KAPPA == kKappaLoop ? C : 64 * KT;
         for (int c = lane; c < n_totals; c += 64) csum[c] = 0.0;
         wave_sync();
-        class_totals<KAPPA == kKappaTable>(csum, ot, KAPPA == kKappaTable ? p.kappa_col : p.col_cls, N, lane);
+        class_totals<KAPPA == kKappaTable ? Sums::rows : Sums::plain>(csum, ot, KAPPA == kKappaTable ? p.kappa_col : p.col_cls, N, lane);
         wave_sync();
 #define SW_DECL(k) [[maybe_unused]] double ct_##k = 0.0; [[maybe_unused]] int kap_##k = 0;
         SW_EACH_K(SW_DECL)
@@ -570,7 +570,7 @@ simulate_channels_kernel(const SimChanParams p)
         for (int k = 0; k < D; ++k) at[k] = lane * D + k < R ? ord[lane * D + k] : -1;
         for (int c = lane; c < 64 * KT; c += 64) csum[c] = 0.0;
         wave_sync();
-        class_totals(csum, ot, p.col_cls, N, lane);
+        class_totals<(KT > 4) ? Sums::quads : Sums::plain>(csum, ot, p.col_cls, N, lane);
         wave_sync();
         double ct[KT];
 #pragma unroll
