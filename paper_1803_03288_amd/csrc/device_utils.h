@@ -264,8 +264,8 @@ enum class Sums { plain, quads, rows };     // how class_totals adds what lanes 
 // Sums::quads: four lanes with one class make one addition (add_by_quads).  Columns of one class are in runs of 14 on average on
 // inception3: 832 additions one after the other per sample become 280.  TAC in registers of 300 samples 236 -> 212 us, of 3 000
 // 265 -> 241; several channels, 65 536 samples, 987 -> 932.  With short runs (resnet50, 6) the test costs up to 8 % where
-// registers are few, on layered graphs nothing with more than four classes per lane: that is where those two kernels use it.
-// Simulation with an order each gains 1 to 2 % on some such graphs and loses that on others.
+// registers are few, on layered graphs nothing with more than four classes per lane: that is where those two kernels use it, and
+// the simulation with an order each (inception3 727 -> 678 us).
 template <Sums HOW = Sums::plain, typename T>
 __device__ __forceinline__ void class_totals(double *totals, const T *__restrict__ row,
                                              const int32_t *__restrict__ cls_of, int N, int lane)

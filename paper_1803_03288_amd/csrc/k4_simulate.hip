@@ -196,32 +196,39 @@ constexpr int kWalkRecvs = 6, kWalkSteps = 32;
 // rows that are read again for every sample, recv by recv, the recvs that come last first.
 enum { kKappaTable, kKappaRuns, kKappaLoop };
 
-// Bytes of a wave.  Times and sums; then the class totals (in the space of F and A while classes are in registers) and the
-// range maxima of the positions.
+// With classes in registers: F, the positions, and from here on (in doubles) the transfer times and A.
+__host__ __device__ constexpr int sim_times_at(int R) { return R + (R + 3) / 4; }
+
+// Bytes of a wave.  Times and sums; then the class totals and the positions.  With classes in registers the totals are summed where
+// all the others come later, and the range maxima of the positions are in the place of the transfer times, which are known by
+// position by then, and of A, which comes after them: 16 KB per wave of inception3 were 10, so that three workgroups instead of
+// two share a compute unit.  An order each, 65 536 samples: inception3 842 -> 727 us, as float32, where the waits for what is
+// loaded weigh more, 978 -> 834; resnet50, where registers are the bound, 181 -> 171; 3 000 samples of inception3 55 -> 49.  (And
+// with Sums::quads: 678, 784 and 47.)
 static size_t sim_wave_bytes(int KAPPA, int KT, int R, int C, int levels)
 {
     size_t n = ((size_t)3 * R + 1) * 8;
     if (KAPPA == kKappaTable) return n;
     if (KAPPA == kKappaLoop) return n + (size_t)C * 8 + (size_t)R * 2;
-    n = ((size_t)R + std::max((size_t)2 * R + 1, (size_t)64 * KT)) * 8;
-    return n + (size_t)levels * R * 2;
+    n = (size_t)sim_times_at(R) * 8 + ((size_t)2 * R + 1) * 8;
+    return std::max(n, std::max((size_t)R * 8 + (size_t)levels * R * 2, (size_t)64 * KT * 8));
 }
 
 template <int KT, int KAPPA>
-__global__ void __launch_bounds__(64 * kSimWaves, KT <= 3 ? 5 : (KT <= 4 ? 4 : 2))
+__global__ void __launch_bounds__(64 * kSimWaves, KT <= 3 ? 5 : (KT <= 4 ? 4 : 3))
 simulate_wave_kernel(const SimWaveParams p)
 {
     extern __shared__ double smem[];
     const int R = p.R, C = p.C, N = p.N;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     char *mine = reinterpret_cast<char *>(smem) + (size_t)wave * p.wave_bytes;
-    double *t = reinterpret_cast<double *>(mine);           // [R]   Time(recv)
-    double *F = t + R;                                      // [R]   F[k-1] = end of the k-th transfer
-    double *A = F + R;                                      // [R+1] class time by kappa
-    // the class totals while they are summed: by kappa at once; [64 KT] in the space of F and A; [C]
-    double *csum = KAPPA == kKappaTable ? A : KAPPA == kKappaLoop ? A + (R + 1) : F;
-    uint16_t *pos = reinterpret_cast<uint16_t *>(KAPPA == kKappaLoop ? csum + C : F + max(2 * R + 1, 64 * KT)); // [levels][R] range maxima of the 1-based positions
     constexpr bool kInRegs = KAPPA == kKappaRuns;
+    double *F = reinterpret_cast<double *>(mine) + (kInRegs ? 0 : R);       // [R]   F[k-1] = end of the k-th transfer
+    double *t = reinterpret_cast<double *>(mine) + (kInRegs ? sim_times_at(R) : 0);     // [R]   Time(recv)
+    double *A = (kInRegs ? t : F) + R;                      // [R+1] class time by kappa
+    // the class totals while they are summed: by kappa at once; [64 KT] before anything else is there; [C]
+    double *csum = KAPPA == kKappaTable ? A : KAPPA == kKappaLoop ? A + (R + 1) : F;
+    uint16_t *pos = reinterpret_cast<uint16_t *>(KAPPA == kKappaLoop ? csum + C : F + R);   // [levels][R] range maxima of the 1-based positions
 
     // Per class slot, fixed for the launch: the first two runs of the class row (lo | hi << 16; longer rows read the rest from
     // memory).
@@ -259,12 +266,14 @@ simulate_wave_kernel(const SimWaveParams p)
         const int n_totals = KAPPA == kKappaTable ? R + 1 : KAPPA == kKappaLoop ? C : 64 * KT;
         for (int c = lane; c < n_totals; c += 64) csum[c] = 0.0;
         wave_sync();
-        class_totals<KAPPA == kKappaTable ? Sums::rows : Sums::plain>(csum, ot, KAPPA == kKappaTable ? p.kappa_col : p.col_cls, N, lane);
+        constexpr Sums how = KAPPA == kKappaTable ? Sums::rows : kInRegs && KT > 4 ? Sums::quads : Sums::plain;
+        class_totals<how>(csum, ot, KAPPA == kKappaTable ? p.kappa_col : p.col_cls, N, lane);
         wave_sync();
 #define SW_DECL(k) [[maybe_unused]] double ct_##k = 0.0; [[maybe_unused]] int kap_##k = 0;
         SW_EACH_K(SW_DECL)
 #define SW_TOTAL(k) if constexpr (k < KT && kInRegs) { ct_##k = csum[k * 64 + lane]; }
         SW_EACH_K(SW_TOTAL)
+        if constexpr (kInRegs) wave_sync();
 #define SW_TIMES(q)                                                                       \
         if constexpr (q < KT) {                                                           \
             if (q * 64 + lane < R) {                                                      \
@@ -292,7 +301,7 @@ simulate_wave_kernel(const SimWaveParams p)
         }
         SW_EACH_K(SW_PLACE)
         const double Ftot = fc;
-        if constexpr (KAPPA != kKappaTable)
+        if constexpr (KAPPA == kKappaLoop)
             for (int j = lane; j <= R; j += 64) A[j] = 0.0;
         wave_sync();
 
@@ -366,6 +375,11 @@ simulate_wave_kernel(const SimWaveParams p)
         }
 
         // ---- A by kappa, suffix sums, makespan ----
+        if constexpr (kInRegs) {
+            wave_sync();
+            for (int j = lane; j <= R; j += 64) A[j] = 0.0;
+            wave_sync();
+        }
 #define SW_RELEASE(k) if constexpr (k < KT && kInRegs) { if (k * 64 + lane < C) atomicAdd(&A[kap_##k], ct_##k); ct_sum += ct_##k; }
         SW_EACH_K(SW_RELEASE)
         wave_sync();
@@ -439,7 +453,7 @@ static hipError_t try_simulate_wave(const Dag &d, const SimArgs &a, const int32_
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
     // Rows of more than two runs on average, or more classes than the registers of a lane hold: by recv.  65 536 samples, an order
     // each, by run and by recv: 24 x 20 layered ops, 300 recvs 3.59 and 0.58 ms; 21 x 18 and 28, 227 and 107 us; resnet50, less
-    // than one run, 187 and 222 us; inception3 844 and 839.
+    // than one run, 171 and 222 us; inception3 678 and 839.
     const int kr = (d.R + 63) / 64, K = std::max((d.C + 63) / 64, kr);      // slots per lane: positions; classes as well
 #define SW_LAUNCH_EACH(k, kappa)                                                          \
     SW_LAUNCH(k, 1, kappa) SW_LAUNCH(k, 2, kappa) SW_LAUNCH(k, 3, kappa) SW_LAUNCH(k, 4, kappa)     \

@@ -1,5 +1,5 @@
 """GPU parity of the class totals that four lanes with one class add together (TAC in registers of five to eight class slots per
-lane, several channels with more than four): runs of columns of one class at every offset from the sixteen columns that four
+lane, several channels and simulation with an order each with more than four): runs of columns of one class at every offset from the sixteen columns that four
 lanes take, classes that come back within them, rows that end anywhere in them; against the CPU oracle."""
 
 import numpy as np
@@ -79,7 +79,37 @@ def test_class_totals_of_runs(tt, name):
         assert np.array_equal(got[1].cpu().numpy(), er)
         for a, b, what in zip(got[4:9], exp, "mEULS"):
             assert np.array_equal(a.cpu().numpy(), b), what
+        alone = tt.simulate(h, torch.from_numpy(orders).cuda(), gop, grv)
+        for a, b, what in zip(alone, oracle.simulate(*args, orders, op, rv), "mEULS"):
+            assert np.array_equal(a.cpu().numpy(), b), what
         if dtype == np.float64:
             many = tt.simulate_channels(h, 3, chan, torch.from_numpy(orders).cuda(), gop, grv)
             for a, b, what in zip(many, oracle.simulate_channels(*args, 3, chan, orders, op, rv), "mEULS"):
                 assert np.array_equal(a.cpu().numpy(), b), what
+
+
+@pytest.mark.parametrize("recvs", [1, 2, 3, 4, 5, 63, 64, 65, 255, 256, 257, 511, 512])
+def test_an_order_each(tt, recvs):
+    """The simulation with an order each, whose positions share their place with times and sums: every remainder of four recvs, where
+    the levels of the maxima grow, the most recvs it takes."""
+    # rows of one run, of one to all recvs
+    b = wl._Builder()
+    rs = [b.recv(1e5 * (1 + k % 7)) for k in range(recvs)]
+    for i in range(recvs):
+        for _ in range(1 + i % 3):
+            b.op(rs[i:i + 1 + (7 * i) % recvs], 1e-4, "op")
+    d = b.finish("spans", seed=3, batch=4)
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    rng = np.random.default_rng(recvs)
+    B = 700
+    op = rng.integers(0, 1 << 20, size=(B, d.n_compute)).astype(np.float64) * wl.QUANTUM
+    rv = rng.integers(0, 1 << 20, size=(B, d.n_recv)).astype(np.float64) * wl.QUANTUM
+    orders = np.stack([rng.permutation(recvs) for _ in range(B)]).astype(np.int32)
+    rows = np.r_[0:12, B - 12:B]
+    exp = oracle.simulate(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids, orders[rows], op[rows], rv[rows])
+    for dtype in (np.float64, np.float32):
+        print(f"[an order each] {recvs} {np.dtype(dtype).name}: N={d.n_compute} classes={h.n_classes}", flush=True)
+        got = tt.simulate(h, torch.from_numpy(orders).cuda(), torch.from_numpy(op.astype(dtype)).cuda(),
+                          torch.from_numpy(rv.astype(dtype)).cuda())
+        for a, b_, what in zip(got, exp, "mEULS"):
+            assert np.array_equal(a.cpu().numpy()[rows], b_), what
