@@ -525,7 +525,7 @@ __device__ __forceinline__ void propagate_levels_body(const LevelParams &p, uint
     const uint32_t rmask = (uint32_t)p.ring - 1u;
     int32_t *fov = reinterpret_cast<int32_t *>(ring + (size_t)(p.ring + 2) * WC);
     if (threadIdx.x < 2 * WC) ring[(size_t)p.ring * WC + threadIdx.x] = 0;
-    const int n_lists = load_device_4(p.lfovf_used);
+    const int n_lists = __builtin_amdgcn_readfirstlane(load_device_4(p.lfovf_used));
     const bool in_lds = n_lists <= p.lfovf_lds;
     for (int i = threadIdx.x; in_lds && i < n_lists; i += blockDim.x) fov[i] = load_device_4(p.lfovf + i);
     __syncthreads();
