@@ -31,13 +31,20 @@ struct TotalsParams {
     int32_t *flags;                     // [B] 1 = a transfer time is not positive
 };
 
+template <bool PAST>
+__device__ __forceinline__ void store_total(double *to, double x)
+{
+    if constexpr (PAST) __builtin_nontemporal_store(x, to);
+    else *to = x;
+}
+
 // Per tile 256 bytes of each of the 64 rows: a request of a wave covers four rows.  (128 and 512 bytes: 4 % and 5 % slower
 // on inception3's rows, 4 % and 12 % on resnet50's; 0.70 ms and 0.15 ms for 65 536 samples, 4.7 and 4.4 TB/s.)  The next
 // tile is requested once the present one is in LDS.
-// Totals and times are written past the caches, which hold neither all of them (434 MB for inception3) nor then what is read
-// meanwhile: inception3 773 -> 761 us and 366 -> 355 for tac_chain_kernel, resnet50 204 -> 198.  (The rows read past the
+// PAST: totals and times are written past the caches, which hold neither all of them (434 MB for inception3) nor then what is
+// read meanwhile: inception3 773 -> 761 us and 366 -> 355 for tac_chain_kernel, resnet50 204 -> 198.  (The rows read past the
 // caches, whose 128-byte lines two requests share, take 894 us, the orders written so 7 us more.)
-template <typename T>
+template <typename T, bool PAST>
 __global__ void __launch_bounds__(64, 2)
 class_totals_kernel(const TotalsParams p)
 {
@@ -92,7 +99,7 @@ class_totals_kernel(const TotalsParams p)
             for (int c = 0; c < n; ++c) {
                 const double y = (double)tile[c * 65 + lane];
                 zero_seen |= !(y > 0.0);
-                __builtin_nontemporal_store(y, &out[(size_t)(c0 + c) * p.Bp]);
+                store_total<PAST>(&out[(size_t)(c0 + c) * p.Bp], y);
             }
         }
         if (b0 + lane < p.B) p.flags[b0 + lane] = zero_seen ? 1 : 0;
@@ -113,7 +120,7 @@ class_totals_kernel(const TotalsParams p)
             for (int c = 0; c < 16; ++c) {
                 acc += (double)tile[(16 * h + c) * 65 + lane];
                 if ((mask >> c) & 1u) {
-                    __builtin_nontemporal_store(acc, &out[(size_t)p.flush_row[run++] * p.Bp]);
+                    store_total<PAST>(&out[(size_t)p.flush_row[run++] * p.Bp], acc);
                     acc = 0.0;
                 }
             }
@@ -525,6 +532,11 @@ static hipError_t launch_chain_nc(const ChainParams &p, hipStream_t s)
 // register-resident kernel, which needs four bytes per sample, is as fast (launch_tac).
 constexpr size_t kChainChunkBytes = (size_t)512 << 20;
 constexpr size_t kChainChunkLeast = 8192;
+// Bytes read and written by class_totals_kernel up to which totals and times go through the caches: the Infinity Cache (256 MB)
+// then still holds enough of them for tac_chain_kernel.  A pass with and without: vgg16, 262 144 samples, 347 MB 121 and 125 us, as
+// float32, 242 MB 117 and 128; 65 536 samples, 87 MB 39.1 and 39.8; resnet50, 50 000 samples as float32, 386 MB 191.8 and 190.6,
+// 65 536, 837 MB 301 and 295; inception3, 20 000 samples, 1.1 GB 492 and 488.
+constexpr size_t kTotalsCached = (size_t)352 << 20;
 
 hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s)
 {
@@ -562,8 +574,10 @@ hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t 
         t.flush = c.d_flush; t.flush_row = c.d_flush_row; t.block_first = c.d_block_first;
         t.totals = totals; t.t = totals + (size_t)c.n_totals * chunk; t.flags = flags + b0;
         const dim3 grid((unsigned)groups, (unsigned)t.n_parts + 1);
-        if (a.f32) hipLaunchKernelGGL(class_totals_kernel<float>, grid, dim3(64), 0, s, t);
-        else hipLaunchKernelGGL(class_totals_kernel<double>, grid, dim3(64), 0, s, t);
+        const bool past = nb * (((size_t)d.N + d.R) * elem + per_sample) > kTotalsCached;
+        void (*const kernel)(TotalsParams) = a.f32 ? (past ? class_totals_kernel<float, true> : class_totals_kernel<float, false>)
+                                                   : (past ? class_totals_kernel<double, true> : class_totals_kernel<double, false>);
+        hipLaunchKernelGGL(kernel, grid, dim3(64), 0, s, t);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ChainParams p{};

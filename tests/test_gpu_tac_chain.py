@@ -115,3 +115,22 @@ def test_chain_form_inception(tt):
     dep = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
     eo, er = oracle_tac_rows(dep, d.recv_ids, op[rows], rv[rows])[:2]
     assert np.array_equal(got[0][rows].cpu().numpy(), eo) and np.array_equal(got[1][rows].cpu().numpy(), er)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_totals_past_the_caches(dtype):
+    """A batch whose rows and totals exceed 352 MiB writes the totals past the caches; parts of it do not.  Times are
+    multiples of 2^-20 below 2^-6, so every sum is exact and the bytes are the same."""
+    import torch
+    from paper_1803_03288_amd import binding as tt, workloads as wl
+    d = wl.resnet50_dag()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    B, part, n_comp = 65536, 16387, d.n_ops - d.n_recv
+    op = (torch.randint(1, 1 << 14, (B, n_comp), device="cuda", generator=gen) * 2.0 ** -20).to(getattr(torch, dtype))
+    rv = (torch.randint(1, 1 << 14, (B, d.n_recv), device="cuda", generator=gen) * 2.0 ** -20).to(getattr(torch, dtype))
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    whole = tt.tac_simulate(h, op, rv)
+    for b in range(0, B, part):
+        for x, y in zip(whole, tt.tac_simulate(h, op[b:b + part].contiguous(), rv[b:b + part].contiguous())):
+            assert (x is None and y is None) or torch.equal(x[b:b + part], y)
