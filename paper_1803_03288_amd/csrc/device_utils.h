@@ -254,7 +254,7 @@ __device__ __forceinline__ void add_by_quads(double *sums, int at, double x)
     if (at >= 0) atomicAdd(&sums[at], x);
 }
 
-enum class Sums { plain, quads, rows };     // how class_totals adds what lanes next to each other have for one place
+enum class Sums { plain, quads, rows, plain_together };    // how class_totals adds what lanes next to each other have for one place
 
 // totals[cls_of[j]] += row[j] for j in [0, N), totals in LDS, by one wave.  A lane takes four
 // consecutive columns at a time and first adds up runs of equal class in registers: columns of
@@ -262,10 +262,13 @@ enum class Sums { plain, quads, rows };     // how class_totals adds what lanes 
 // is served one lane after the other.
 // Sums::rows: neighbours in the row mostly go to one place (add_by_rows).
 // Sums::quads: four lanes with one class make one addition (add_by_quads).  Columns of one class are in runs of 14 on average on
-// inception3: 832 additions one after the other per sample become 280.  TAC in registers of 300 samples 236 -> 212 us, of 3 000
-// 265 -> 241; several channels, 65 536 samples, 987 -> 932.  With short runs (resnet50, 6) the test costs up to 8 % where
-// registers are few, on layered graphs nothing with more than four classes per lane: that is where those two kernels use it, and
-// the simulation with an order each (inception3 727 -> 678 us).
+// inception3, a third of them in runs of more than 32: 832 additions one after the other per sample become 280.  Simulation with an
+// order each 727 -> 678 us, several channels, 65 536 samples, 987 -> 932.  Where runs are short the test costs 1 to 5 %: those two
+// use it by how the columns lie (long_class_runs), with more than four class slots per lane.  TAC in registers uses it from six
+// slots to eight; what a round costs leaves nothing to be seen of the sums, but the code of the rounds comes out 2 % faster with
+// six to eight and 1.7 % slower with five (a literal scan every round, 290 to 500 recvs).
+// Sums::plain_together: as plain, but no lane leaves before the others, which takes up to five registers less and else up to 1 %
+// more time.
 template <Sums HOW = Sums::plain, typename T>
 __device__ __forceinline__ void class_totals(double *totals, const T *__restrict__ row,
                                              const int32_t *__restrict__ cls_of, int N, int lane)

@@ -152,6 +152,7 @@ struct Dag {
     int32_t *d_run_hi = nullptr;    // [n_runs]
     int32_t n_runs = 0;
     int32_t max_members = 0;        // largest class (ops)
+    bool long_runs = false;         // (more than 256 classes or recvs, at most 512) class totals by quads pay, see long_class_runs
 
     // Tables of the bit-sliced TAC kernel (graphs with many classes; NULL / 0 otherwise).  Classes are
     // taken 64 at a time ("class words"): bit c & 63 of word c >> 6 stands for class c.

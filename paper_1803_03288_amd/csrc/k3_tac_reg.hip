@@ -176,7 +176,7 @@ tac_reg_kernel(const TacRegParams p)
             // the row is read once; every column (run of columns) adds itself to the total of its class
             for (int c = lane; c < 64 * KT; c += 64) csum[c] = 0.0;
             wave_sync();
-            class_totals<(KT > 4 && KT <= kTableSlots) ? Sums::quads : Sums::plain>(csum, ot, p.col_cls, N, lane);
+            class_totals<(KT > 5 && KT <= kTableSlots) ? Sums::quads : Sums::plain>(csum, ot, p.col_cls, N, lane);
             wave_sync();
 #define TT_READ_TOTAL(k) if constexpr (k < KT) { ct_##k = csum[k * 64 + lane]; }
             TT_EACH_K(TT_READ_TOTAL)

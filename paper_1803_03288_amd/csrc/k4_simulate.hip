@@ -194,7 +194,7 @@ constexpr int kWalkRecvs = 6, kWalkSteps = 32;
 
 // Where kappa comes from: a table by column; two runs of most rows, of classes in registers (and memory for the other runs); or
 // rows that are read again for every sample, recv by recv, the recvs that come last first.
-enum { kKappaTable, kKappaRuns, kKappaLoop };
+enum { kKappaTable, kKappaRuns, kKappaLoop, kKappaRunsLong };
 
 // With classes in registers: F, the positions, and from here on (in doubles) the transfer times and A.
 __host__ __device__ constexpr int sim_times_at(int R) { return R + (R + 3) / 4; }
@@ -202,9 +202,9 @@ __host__ __device__ constexpr int sim_times_at(int R) { return R + (R + 3) / 4; 
 // Bytes of a wave.  Times and sums; then the class totals and the positions.  With classes in registers the totals are summed where
 // all the others come later, and the range maxima of the positions are in the place of the transfer times, which are known by
 // position by then, and of A, which comes after them: 16 KB per wave of inception3 were 10, so that three workgroups instead of
-// two share a compute unit.  An order each, 65 536 samples: inception3 842 -> 727 us, as float32, where the waits for what is
-// loaded weigh more, 978 -> 834; resnet50, where registers are the bound, 181 -> 171; 3 000 samples of inception3 55 -> 49.  (And
-// with Sums::quads: 678, 784 and 47.)
+// two share a compute unit.  An order each, 65 536 samples: inception3 842 -> 727 us;
+// resnet50, where registers are the bound, 181 -> 171; 3 000 samples of inception3 55 -> 49.  (And with Sums::quads: 678 and 47; as
+// float32 974 -> 708.)
 static size_t sim_wave_bytes(int KAPPA, int KT, int R, int C, int levels)
 {
     size_t n = ((size_t)3 * R + 1) * 8;
@@ -214,15 +214,21 @@ static size_t sim_wave_bytes(int KAPPA, int KT, int R, int C, int levels)
     return std::max(n, std::max((size_t)R * 8 + (size_t)levels * R * 2, (size_t)64 * KT * 8));
 }
 
+// Workgroups per compute unit that the registers are to leave room for.  Three share one with up to 168 registers: from five slots
+// to seven no more are used without being asked for, and where the compiler is asked it waits for loads earlier (float32, five slots,
+// 290 classes with 16 columns each, 65 536 samples: 490 and 558 us; six, 380 classes 599 and 684; seven, inception3 708 and 782; 100
+// samples 23.2 and 24.2).  Eight slots would take 186.
+constexpr int sim_workgroups(int KT) { return KT <= 3 ? 5 : KT <= 4 ? 4 : KT <= 7 ? 2 : 3; }
+
 template <int KT, int KAPPA>
-__global__ void __launch_bounds__(64 * kSimWaves, KT <= 3 ? 5 : (KT <= 4 ? 4 : 3))
+__global__ void __launch_bounds__(64 * kSimWaves, sim_workgroups(KT))
 simulate_wave_kernel(const SimWaveParams p)
 {
     extern __shared__ double smem[];
     const int R = p.R, C = p.C, N = p.N;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     char *mine = reinterpret_cast<char *>(smem) + (size_t)wave * p.wave_bytes;
-    constexpr bool kInRegs = KAPPA == kKappaRuns;
+    constexpr bool kInRegs = KAPPA == kKappaRuns || KAPPA == kKappaRunsLong;
     double *F = reinterpret_cast<double *>(mine) + (kInRegs ? 0 : R);       // [R]   F[k-1] = end of the k-th transfer
     double *t = reinterpret_cast<double *>(mine) + (kInRegs ? sim_times_at(R) : 0);     // [R]   Time(recv)
     double *A = (kInRegs ? t : F) + R;                      // [R+1] class time by kappa
@@ -233,15 +239,14 @@ simulate_wave_kernel(const SimWaveParams p)
     // Per class slot, fixed for the launch: the first two runs of the class row (lo | hi << 16; longer rows read the rest from
     // memory).
 #define SW_RUNS(k)                                                                        \
-    [[maybe_unused]] int rb_##k = 0, re_##k = 0;                                          \
-    [[maybe_unused]] unsigned ra_##k = 0, rc_##k = 0;                                     \
+    [[maybe_unused]] unsigned rn_##k = 0, ra_##k = 0, rc_##k = 0;    /* first run | last + 1 << 16; the first two of them */ \
     if constexpr (k < KT && kInRegs) {                                                    \
         const int c = k * 64 + lane;                                                      \
         if (c < C) {                                                                      \
-            rb_##k = p.run_ptr[c];                                                        \
-            re_##k = p.run_ptr[c + 1];                                                    \
-            if (re_##k > rb_##k) ra_##k = (unsigned)p.run_lo[rb_##k] | ((unsigned)p.run_hi[rb_##k] << 16);              \
-            if (re_##k > rb_##k + 1) rc_##k = (unsigned)p.run_lo[rb_##k + 1] | ((unsigned)p.run_hi[rb_##k + 1] << 16);  \
+            const int rb = p.run_ptr[c], re = p.run_ptr[c + 1];                           \
+            rn_##k = (unsigned)rb | (unsigned)re << 16;                                   \
+            if (re > rb) ra_##k = (unsigned)p.run_lo[rb] | ((unsigned)p.run_hi[rb] << 16);              \
+            if (re > rb + 1) rc_##k = (unsigned)p.run_lo[rb + 1] | ((unsigned)p.run_hi[rb + 1] << 16);  \
         }                                                                                 \
     }
     SW_EACH_K(SW_RUNS)
@@ -266,7 +271,7 @@ simulate_wave_kernel(const SimWaveParams p)
         const int n_totals = KAPPA == kKappaTable ? R + 1 : KAPPA == kKappaLoop ? C : 64 * KT;
         for (int c = lane; c < n_totals; c += 64) csum[c] = 0.0;
         wave_sync();
-        constexpr Sums how = KAPPA == kKappaTable ? Sums::rows : kInRegs && KT > 4 ? Sums::quads : Sums::plain;
+        constexpr Sums how = KAPPA == kKappaTable ? Sums::rows : KAPPA == kKappaRunsLong ? Sums::quads : kInRegs && KT == 7 ? Sums::plain_together : Sums::plain;
         class_totals<how>(csum, ot, KAPPA == kKappaTable ? p.kappa_col : p.col_cls, N, lane);
         wave_sync();
 #define SW_DECL(k) [[maybe_unused]] double ct_##k = 0.0; [[maybe_unused]] int kap_##k = 0;
@@ -335,9 +340,10 @@ simulate_wave_kernel(const SimWaveParams p)
             if constexpr (k < KT && kInRegs) {                                            \
                 if (k * 64 + lane < C) {                                                  \
                     int m = 0;                                                            \
-                    if (re_##k > rb_##k) SW_RANGE_MAX((int)(ra_##k & 0xffffu), (int)(ra_##k >> 16))          \
-                    if (re_##k > rb_##k + 1) SW_RANGE_MAX((int)(rc_##k & 0xffffu), (int)(rc_##k >> 16))      \
-                    for (int q = rb_##k + 2; q < re_##k; ++q) {                           \
+                    const int rb = (int)(rn_##k & 0xffffu), re = (int)(rn_##k >> 16);     \
+                    if (re > rb) SW_RANGE_MAX((int)(ra_##k & 0xffffu), (int)(ra_##k >> 16))          \
+                    if (re > rb + 1) SW_RANGE_MAX((int)(rc_##k & 0xffffu), (int)(rc_##k >> 16))      \
+                    for (int q = rb + 2; q < re; ++q) {                                   \
                         const int lo = p.run_lo[q], hi = p.run_hi[q];                     \
                         SW_RANGE_MAX(lo, hi)                                              \
                     }                                                                     \
@@ -463,6 +469,10 @@ static hipError_t try_simulate_wave(const Dag &d, const SimArgs &a, const int32_
         SW_LAUNCH_EACH(kr, kKappaTable)
     } else if (K > 8 || !d.d_run_ptr || d.n_runs > 2 * d.C) {
         SW_LAUNCH_EACH(kr, kKappaLoop)
+    } else if (K > 4 && d.long_runs && a.B > kSimWaves * device_cu_count(d.device)) {
+        // (by quads, a sample by itself takes longer: up to a workgroup per compute unit, inception3 21.2 and 21.7 us, 300 classes
+        // with 64 columns each 26.4 and 29.9)
+        SW_LAUNCH(K, 5, kKappaRunsLong) SW_LAUNCH(K, 6, kKappaRunsLong) SW_LAUNCH(K, 7, kKappaRunsLong) SW_LAUNCH(K, 8, kKappaRunsLong)
     } else {
         SW_LAUNCH_EACH(K, kKappaRuns)
     }
@@ -518,7 +528,7 @@ struct SimChanParams {
 // and 64 positions before, 26 % more vector instructions), resnet50 357 -> 257 us.  Waves wait for the op_time row two thirds of
 // their time; the registers (an occupancy bound per KT: where spills of a few words cost less than a wave) and LDS, which holds
 // everything but the arrivals in one place, say how many there are.
-template <int KT>
+template <int KT, Sums HOW>
 __global__ void __launch_bounds__(256, KT <= 3 ? 5 : KT <= 4 ? 4 : 3)
 simulate_channels_kernel(const SimChanParams p)
 {
@@ -584,7 +594,7 @@ simulate_channels_kernel(const SimChanParams p)
         for (int k = 0; k < D; ++k) at[k] = lane * D + k < R ? ord[lane * D + k] : -1;
         for (int c = lane; c < 64 * KT; c += 64) csum[c] = 0.0;
         wave_sync();
-        class_totals<(KT > 4) ? Sums::quads : Sums::plain>(csum, ot, p.col_cls, N, lane);
+        class_totals<HOW>(csum, ot, p.col_cls, N, lane);
         wave_sync();
         double ct[KT];
 #pragma unroll
@@ -804,7 +814,7 @@ simulate_channels_kernel(const SimChanParams p)
     if (bad) atomicOr(p.bad_order, 1);
 }
 
-template <int KT>
+template <int KT, Sums HOW>
 static hipError_t launch_sim_chan(SimChanParams &p, const Dag &d, hipStream_t s)
 {
     const int nb = (d.R + 3) / 4;
@@ -836,11 +846,11 @@ static hipError_t launch_sim_chan(SimChanParams &p, const Dag &d, hipStream_t s)
     p.chan_bytes = (int32_t)chan_bytes;
     hipError_t e;
     if (lds > 48 * 1024) {
-        e = ensure_dynamic_lds(reinterpret_cast<const void *>(simulate_channels_kernel<KT>), lds);
+        e = ensure_dynamic_lds(reinterpret_cast<const void *>(simulate_channels_kernel<KT, HOW>), lds);
         if (e != hipSuccess) return e;
     }
     int per_cu = 0;
-    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(simulate_channels_kernel<KT>), 64 * waves, lds);
+    e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(simulate_channels_kernel<KT, HOW>), 64 * waves, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
     const int n_cu = device_cu_count(d.device);
@@ -848,7 +858,7 @@ static hipError_t launch_sim_chan(SimChanParams &p, const Dag &d, hipStream_t s)
     const int need = (p.B + waves - 1) / waves;
     if (grid > need) grid = need;
     p.n_waves = grid * waves;
-    hipLaunchKernelGGL((simulate_channels_kernel<KT>), dim3(grid), dim3(64 * waves), lds, s, p);
+    hipLaunchKernelGGL((simulate_channels_kernel<KT, HOW>), dim3(grid), dim3(64 * waves), lds, s, p);
     return hipGetLastError();
 }
 
@@ -866,15 +876,16 @@ hipError_t launch_simulate_channels(Dag &d, const SimArgs &a, int32_t n_channels
     p.chan = chan; p.order = a.order; p.order_stride = a.order_stride;
     p.op_time = a.op_time; p.recv_time = a.recv_time; p.f32 = a.f32 ? 1 : 0;
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;
+    const bool quads = d.long_runs;
     switch (KT) {
-    case 1: return launch_sim_chan<1>(p, d, s);
-    case 2: return launch_sim_chan<2>(p, d, s);
-    case 3: return launch_sim_chan<3>(p, d, s);
-    case 4: return launch_sim_chan<4>(p, d, s);
-    case 5: return launch_sim_chan<5>(p, d, s);
-    case 6: return launch_sim_chan<6>(p, d, s);
-    case 7: return launch_sim_chan<7>(p, d, s);
-    default: return launch_sim_chan<8>(p, d, s);
+    case 1: return launch_sim_chan<1, Sums::plain>(p, d, s);
+    case 2: return launch_sim_chan<2, Sums::plain>(p, d, s);
+    case 3: return launch_sim_chan<3, Sums::plain>(p, d, s);
+    case 4: return launch_sim_chan<4, Sums::plain>(p, d, s);
+    case 5: return quads ? launch_sim_chan<5, Sums::quads>(p, d, s) : launch_sim_chan<5, Sums::plain>(p, d, s);
+    case 6: return quads ? launch_sim_chan<6, Sums::quads>(p, d, s) : launch_sim_chan<6, Sums::plain>(p, d, s);
+    case 7: return quads ? launch_sim_chan<7, Sums::quads>(p, d, s) : launch_sim_chan<7, Sums::plain>(p, d, s);
+    default: return quads ? launch_sim_chan<8, Sums::quads>(p, d, s) : launch_sim_chan<8, Sums::plain>(p, d, s);
     }
 }
 

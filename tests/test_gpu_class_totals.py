@@ -1,6 +1,7 @@
 """GPU parity of the class totals that four lanes with one class add together (TAC in registers of five to eight class slots per
 lane, several channels and simulation with an order each with more than four): runs of columns of one class at every offset from the sixteen columns that four
-lanes take, classes that come back within them, rows that end anywhere in them; against the CPU oracle."""
+lanes take, classes that come back within them, rows that end anywhere in them; against the CPU oracle.  The simulations add that way where
+runs are long (far_...), else lane by lane."""
 
 import numpy as np
 import pytest
@@ -50,6 +51,13 @@ GRAPHS = {
     "back": lambda: runs(300, [15, 16], back=40),
     "six_slots": lambda: runs(380, [16, 14]),
     "eight_slots": lambda: runs(480, [12, 17]),
+    # runs long enough that the simulations add by quads too
+    "far": lambda: runs(290, [48]),
+    "far_offsets": lambda: runs(300, [45, 61, 3, 52, 64]),
+    "far_six_slots": lambda: runs(370, [48, 50, 33, 1]),
+    "far_seven_slots": lambda: runs(400, [46, 19, 71]),
+    "far_eight_slots": lambda: runs(450, [65, 2, 43]),
+    **{f"far_tail{k}": (lambda k=k: runs(288, [60], tail=k)) for k in (1, 3, 253, 255)},
     **{f"tail{k}": (lambda k=k: runs(288, [16], tail=k)) for k in (1, 2, 3, 4, 253, 255, 256, 257)},
 }
 
@@ -82,6 +90,10 @@ def test_class_totals_of_runs(tt, name):
         alone = tt.simulate(h, torch.from_numpy(orders).cuda(), gop, grv)
         for a, b, what in zip(alone, oracle.simulate(*args, orders, op, rv), "mEULS"):
             assert np.array_equal(a.cpu().numpy(), b), what
+        # (above 1 024 samples the simulation adds by quads where runs are long: the same samples again and again)
+        again = tt.simulate(h, *(torch.from_numpy(x).cuda().repeat(115, 1) for x in (orders, op.astype(dtype), rv.astype(dtype))))
+        for a, b, what in zip(again, alone, "mEULS"):
+            assert torch.equal(a, b.repeat(115)), what
         if dtype == np.float64:
             many = tt.simulate_channels(h, 3, chan, torch.from_numpy(orders).cuda(), gop, grv)
             for a, b, what in zip(many, oracle.simulate_channels(*args, 3, chan, orders, op, rv), "mEULS"):

@@ -304,6 +304,32 @@ def test_many_recvs_without_room_for_flags(lib):
     lib.free(h)
 
 
+@pytest.mark.parametrize("recvs,run,slots,quads", [(250, 80, 4, False), (290, 16, 5, False), (290, 40, 5, False), (290, 64, 5, True),
+                                                   (380, 16, 6, False), (380, 64, 6, True), (440, 2, 7, False), (440, 64, 7, True),
+                                                   (500, 1, 8, False), (500, 90, 8, True)])
+def test_class_totals_by_quads_where_columns_have_long_runs(lib, recvs, run, slots, quads):
+    """Four lanes are compared only where many columns next to each other have one class and, in the simulation by waves, where several
+    workgroups share a compute unit: elsewhere that costs more than it gives."""
+    b = wl._Builder()
+    for r in [b.recv(1e5) for _ in range(recvs)]:
+        for _ in range(run):
+            r = b.op([r], 1e-4, "op")
+    d = b.finish("runs", seed=3, batch=4)
+    rc, h = lib.build(d)
+    assert rc == 0, lib.error()
+    chan = np.zeros(recvs, np.int32)
+    room = np.zeros(1)                      # (no kernel runs: what the samples are is no matter)
+    for B in (8, 1024, 1025):
+        lib.host_forget_launches()
+        out = [ptr(room)] * 5
+        assert lib.tictac_simulate(h, I32(B), ptr(room), I32(recvs), ptr(room), ptr(room), *out, None) == 0, lib.error()
+        assert lib.tictac_simulate_channels(h, I32(B), I32(2), ptr(chan), ptr(room), I32(recvs), ptr(room), ptr(room), *out, None) == 0
+        one, several = [k for k in lib.kernels() if "simulate_" in k]
+        assert f"simulate_wave_kernelILi{slots}ELi{3 if quads and B > 1024 else 1}E" in one
+        assert f"simulate_channels_kernelILi{slots}ELNS_4SumsE{1 if quads else 0}E" in several
+    lib.free(h)
+
+
 @pytest.mark.parametrize("width,recvs,B,kernel", [(130, 100, 1, "simulate_kernelILi1024E"), (130, 100, 256, "simulate_kernelILi1024E"),
                                                   (130, 100, 257, "simulate_wave"), (50, 100, 1, "simulate_wave"),
                                                   (220, 64, 1, "simulate_wave")])
