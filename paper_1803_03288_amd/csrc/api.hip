@@ -231,6 +231,7 @@ struct Packer {
     struct Part { void **dst; const void *src; size_t bytes, off; };    // (src NULL: only kernels write it)
     std::vector<Part> parts;
     size_t host_bytes = 0, device_only = 0;     // the copied arrays come first
+    size_t alignment = 256;                     // of what comes behind them
     Stage staging;
     hipStream_t stream = nullptr;
     bool under_way = false;
@@ -244,7 +245,7 @@ struct Packer {
         return e;
     }
 
-    static size_t align(size_t x) { return (x + 255) & ~(size_t)255; }
+    static size_t align(size_t x, size_t to = 256) { return (x + to - 1) & ~(to - 1); }
 
     template <typename T>
     void add(T **dst, const T *src, size_t n)
@@ -258,10 +259,12 @@ struct Packer {
     template <typename T>
     void add(T **dst, const std::vector<T> &src) { add(dst, src.data(), src.size()); }
     template <typename T>
-    void reserve(T **dst, size_t n_bytes)
+    void reserve(T **dst, size_t n_bytes, size_t at = 256)
     {
         *dst = nullptr;
         if (!n_bytes) return;
+        alignment = std::max(alignment, at);
+        device_only = align(device_only, at);
         parts.push_back({reinterpret_cast<void **>(dst), nullptr, n_bytes, device_only});
         device_only += align(n_bytes);
     }
@@ -271,7 +274,7 @@ struct Packer {
     {
         for (const Part &p : parts) *p.dst = nullptr;
         hipError_t e = release(block, device);
-        const size_t total = align(host_bytes) + device_only;
+        const size_t behind = device_only ? align(host_bytes, alignment) : align(host_bytes), total = behind + device_only;
         if (e != hipSuccess || !total) return e;
         std::vector<char> pageable;
         char *st = static_cast<char *>(staging.take(host_bytes));
@@ -296,7 +299,7 @@ struct Packer {
             }
         }
         for (const Part &p : parts)
-            if (e == hipSuccess) *p.dst = static_cast<char *>(block.p) + (p.src ? 0 : align(host_bytes)) + p.off;
+            if (e == hipSuccess) *p.dst = static_cast<char *>(block.p) + (p.src ? 0 : behind) + p.off;
         return e;
     }
 };
@@ -948,7 +951,7 @@ struct PropTables {
     std::vector<Dag::NodeRec> nodes;
     std::vector<Dag::FastRec> lrecs, frecs;
     std::vector<int32_t> ovf_idx, chunk_end, lfovf, fovf;
-    std::vector<int32_t> slot, lfovf_used;  // level-major records: the slot of every node; entries of the lists so far
+    std::vector<int32_t> slot;              // level-major records: the slot of every node
     QuadTables quads;
     std::future<void> quads_made;           // (waited for before the rest goes: a thread of their own makes them)
 
@@ -964,15 +967,17 @@ struct PropTables {
             p.add(&d->d_nlvl_ptr, g.lvl_ptr);
             p.add(&d->d_chunk_end, chunk_end);
         } else {
-            p.add(&d->d_lfovf_used, lfovf_used);
             if (lrecs.empty()) {            // (launch_level_records makes them)
                 p.add(&d->d_nlvl_ptr, g.lvl_ptr);
                 p.add(&d->d_node_ptr, g.ptr.data(), (size_t)g.M + 1);
                 p.add(&d->d_node_in, g.in.data(), (size_t)g.ptr[g.M]);
                 p.add(&d->d_node_op, g.op.data(), (size_t)g.M);
                 p.add(&d->d_node_slot, slot);
-                p.reserve(&d->d_lrecs, (size_t)d->n_node_levels * (d->k1_threads / d->k1_wc) * sizeof(Dag::FastRec));
-                p.reserve(&d->d_lfovf, (size_t)d->lfovf_len * 4);
+                // (a level's records, 8 KB for 256 slots, on as few pages as there are: 500 x 200 layered ops, 1 300 recvs 146 us;
+                // 154 at a multiple of 4 KB or less)
+                p.reserve(&d->d_lrecs, (size_t)d->n_node_levels * (d->k1_threads / d->k1_wc) * sizeof(Dag::FastRec), 65536);
+                p.reserve(&d->d_lfovf, (size_t)d->lfovf_room * 4);
+                p.reserve(&d->d_lfovf_used, ((size_t)g.M + 127) / 64 * 4);
             } else {
                 p.add(&d->d_lrecs, lrecs);
                 p.add(&d->d_lfovf, lfovf);
@@ -1099,9 +1104,7 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
         t.slot.resize(M);
         for (int32_t k = 0; k < M; ++k) t.slot[k] = g.lvl[k] * P + (g.pos[k] - nlvl_ptr[g.lvl[k]]);
         if (by_kernel) {
-            d->lfovf_len = M + g.ptr[M];
-            d->lfovf_count = (int32_t)std::min<size_t>(list_entries, 4096);
-            t.lfovf_used.assign(1, 0);
+            d->lfovf_room = M + g.ptr[M];
         } else {
             // While level l is computed the ring holds the slots from (l + 1) * P - ring on.
             const int32_t row_bytes = d->k1_wc * 8, zero_row = lring * row_bytes;
@@ -1113,8 +1116,6 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
                      [&](int32_t x) { return t.slot[x]; });
             }
             d->lfovf_len = (int32_t)t.lfovf.size();
-            d->lfovf_count = d->lfovf_len <= 4096 ? d->lfovf_len : 0;
-            t.lfovf_used.assign(1, d->lfovf_len);
         }
     } else if (!d->k1_wide) {
         const int32_t row_bytes = d->k1_wc * 8, zero_row = ring * row_bytes;
@@ -1252,6 +1253,9 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         graph.reserve(&d->d_dep, (size_t)n * d->W * 8);
         HIP_TRY(graph.commit(d->graph_block, d->device, s));
         HIP_TRY(launch_level_records(*d, s));
+        // (how many entries the lists have: the wait is for this as well)
+        if (d->d_lfovf_used)
+            HIP_TRY(hipMemcpyAsync(&d->lfovf_len, d->d_lfovf_used, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         HIP_TRY(graph.finish());
         if ((size_t)n * d->W) HIP_TRY(launch_propagate(*d, s));
     }

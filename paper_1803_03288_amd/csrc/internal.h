@@ -102,11 +102,11 @@ struct Dag {
     // graph takes another kernel.
     FastRec *d_lrecs = nullptr;     // [n_node_levels * P]
     int32_t *d_lfovf = nullptr;
-    int32_t lfovf_len = 0;          // room for its entries, of which *d_lfovf_used are in use
-    int32_t lfovf_count = 0;        // entries, up to 4 096, that LDS is to have room for where several graphs share a compute unit:
-                                    // all (0 if more), or where a kernel makes the lists those of nodes with more than four nodes or two recvs
-    // what that kernel makes the records from (launch_level_records): the condensed graph by node, the slot of every node
-    int32_t *d_node_ptr = nullptr, *d_node_in = nullptr, *d_node_op = nullptr, *d_node_slot = nullptr, *d_lfovf_used = nullptr;
+    int32_t lfovf_len = 0;
+    // what level_records_kernel makes the records from: the condensed graph by node, the slot of every node
+    int32_t *d_node_ptr = nullptr, *d_node_in = nullptr, *d_node_op = nullptr, *d_node_slot = nullptr;
+    int32_t lfovf_room = 0;         // entries of lists of all nodes
+    int32_t *d_lfovf_used = nullptr;    // entries of the lists, then those of every 64 nodes
     int32_t k1_lring = 0;           // slots held in LDS (a power of two, at least 16 levels)
     // The level-major records of the kernel with 64-byte slices (four lanes per slot, P = k1_threads / 4):
     // ring slots of up to four input rows in 16-bit halves (unused: the zero row, slot k1_lring), two recv indices
@@ -244,8 +244,16 @@ hipError_t cached_blocks_per_cu(int *per_cu, const void *kernel, int threads, si
 hipError_t launch_propagate(const Dag &d, hipStream_t s);
 // copies from pinned host memory (16-byte aligned, rounded up to 16 bytes) by a kernel
 hipError_t launch_copy_in(void *dst, const void *pinned, size_t bytes, hipStream_t s);
-// op.dep from cls_dep and d_op_src
+// what the level-major records are made from, and where they and their lists go (k1_propagate.hip)
+struct LevelRecordParams {
+    int32_t M, n_levels, P, ring, row_bytes, room;
+    const int32_t *lvl_ptr, *ptr, *in, *op, *slot;
+    int32_t *used, *lists;
+    Dag::FastRec *recs;
+};
+// the level-major records, where the host has not made them
 hipError_t launch_level_records(const Dag &d, hipStream_t s);
+// op.dep from cls_dep and d_op_src
 hipError_t launch_expand_sets(const Dag &d, hipStream_t s);
 // the same for G graphs of one launch shape in one launch; staging: device memory of propagate_batch_staging_bytes(G)
 size_t propagate_batch_staging_bytes(int G);

@@ -506,8 +506,8 @@ __device__ __noinline__ uint64_t other_inputs(const int32_t *lfovf, const int32_
 struct LevelParams {
     int32_t n_levels, W, P, ring;       // P slots per level; ring: slots held in LDS (power of two)
     const Dag::FastRec *lrecs;          // [n_levels * P]
-    const int32_t *lfovf, *lfovf_used;  // the lists, how many entries they have
-    int32_t lfovf_lds;                  // entries that LDS has room for: if all of them fit they are copied there
+    const int32_t *lfovf;
+    int32_t lfovf_lds;                  // > 0: that many entries of lfovf (all of them) are copied to LDS
     uint64_t *dep;
     uint64_t *sink;                     // [gridDim.x * blockDim.x]
 };
@@ -525,9 +525,7 @@ __device__ __forceinline__ void propagate_levels_body(const LevelParams &p, uint
     const uint32_t rmask = (uint32_t)p.ring - 1u;
     int32_t *fov = reinterpret_cast<int32_t *>(ring + (size_t)(p.ring + 2) * WC);
     if (threadIdx.x < 2 * WC) ring[(size_t)p.ring * WC + threadIdx.x] = 0;
-    const int n_lists = __builtin_amdgcn_readfirstlane(load_device_4(p.lfovf_used));
-    const bool in_lds = n_lists <= p.lfovf_lds;
-    for (int i = threadIdx.x; in_lds && i < n_lists; i += blockDim.x) fov[i] = load_device_4(p.lfovf + i);
+    for (int i = threadIdx.x; i < p.lfovf_lds; i += blockDim.x) fov[i] = load_device_4(p.lfovf + i);
     __syncthreads();
     if (L == 0) return;
 
@@ -558,7 +556,7 @@ __device__ __forceinline__ void propagate_levels_body(const LevelParams &p, uint
             bits |= (b##i.y >> 6) == gw ? 1ull << (b##i.y & 63) : 0ull;                   \
             val = bits | v0 | v1 | v2 | v3;                                               \
             if (b##i.w >= 0 && gw < W)                                                    \
-                val |= other_inputs(p.lfovf, in_lds ? fov : nullptr, ring, p.lrecs, p.dep, W, b##i.w, \
+                val |= other_inputs(p.lfovf, p.lfovf_lds > 0 ? fov : nullptr, ring, p.lrecs, p.dep, W, b##i.w, \
                                     (l + 1) * P - p.ring, rmask, WC, w, gw);              \
             if (gw >= W) val = 0;                                                         \
             ring[(slot & rmask) * WC + w] = val;                                          \
@@ -772,19 +770,15 @@ expand_rows_batch(const ExpandParams *__restrict__ ps)
 }
 
 // The level-major records, a thread per slot and per node: a slot without a node gets a record without one.  A node whose
-// inputs are at most four rows that the ring still holds and two recvs fits its record; any other has a list, whose place
-// comes from a counter (in which order the lists lie is no matter).  stress (60 000 nodes in 119 000 slots): 8 us; the host
-// took 0.75 ms of a build's 4.25 for filling them and twice the bytes to the device.
-struct LevelRecordParams {
-    int32_t M, n_levels, P, ring, row_bytes, room;
-    const int32_t *lvl_ptr, *ptr, *in, *op, *slot;
-    int32_t *used, *lists;
-    Dag::FastRec *recs;
-};
+// inputs are at most four rows that the ring still holds and two recvs fits its record; any other has a list, whose place among
+// those of its wave goes into the record, and level_lists_kernel adds the lists of the waves before and writes it.  So the lists lie
+// in the order of the nodes: where lanes take them from a counter as they come, 300 x 100 layered ops, 1 300 recvs, with more lists
+// than LDS has room for, take 3 % more.  stress (60 000 nodes in 119 000 slots): 9 + 7 us; the host took 0.75 ms of a build's 4.25 for
+// filling the records and twice the bytes to the device.
 __global__ void __launch_bounds__(256)
 level_records_kernel(const LevelRecordParams p)
 {
-    const int32_t i = blockIdx.x * 256 + threadIdx.x, zero_row = p.ring * p.row_bytes;
+    const int32_t i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63, zero_row = p.ring * p.row_bytes;
     Dag::FastRec f;
     for (int j = 0; j < 4; ++j) f.in[j] = zero_row;
     f.rcv[0] = f.rcv[1] = f.op = f.ovf = -1;
@@ -792,9 +786,8 @@ level_records_kernel(const LevelRecordParams p)
         const int32_t l = i / p.P;
         if (i - l * p.P >= p.lvl_ptr[l + 1] - p.lvl_ptr[l]) p.recs[i] = f;
     }
-    if (i >= p.M) return;
-    const int32_t e0 = p.ptr[i], e1 = p.ptr[i + 1], at = p.slot[i], oldest = (at / p.P + 1) * p.P - p.ring;
-    f.op = p.op[i];
+    const bool node = i < p.M;
+    const int32_t e0 = node ? p.ptr[i] : 0, e1 = node ? p.ptr[i + 1] : 0, at = node ? p.slot[i] : 0, oldest = (at / p.P + 1) * p.P - p.ring;
     int n_in = 0, n_rcv = 0;
     bool fits = true;
     for (int32_t e = e0; e < e1; ++e) {
@@ -809,37 +802,67 @@ level_records_kernel(const LevelRecordParams p)
             fits &= q >= oldest && ++n_in <= 4;
         }
     }
+    int32_t end = fits ? 0 : 1 + e1 - e0;               // of this lane's list among those of the wave
+    const int32_t size = end;
+    if (__ballot(!fits)) {
+        for (int d = 1; d < 64; d *= 2) {
+            const int32_t before = __shfl_up(end, d);
+            end += lane >= d ? before : 0;
+        }
+    }
+    if (lane == 63 && i - 63 < p.M) p.used[1 + i / 64] = end;
     if (!fits) {
         for (int j = 0; j < 4; ++j) f.in[j] = zero_row;
         f.rcv[0] = f.rcv[1] = -1;
-        f.ovf = atomicAdd(p.used, 1 + e1 - e0);
-        if (f.ovf + 1 + e1 - e0 <= p.room) {            // (always: the room is a bound)
-            p.lists[f.ovf] = e1 - e0;
-            for (int32_t e = e0; e < e1; ++e) p.lists[f.ovf + 1 + e - e0] = p.in[e] < 0 ? p.in[e] : p.slot[p.in[e]];
-        }
+        f.ovf = end - size;
     }
-    p.recs[at] = f;
+    if (node) {
+        f.op = p.op[i];
+        p.recs[at] = f;
+    }
+}
+
+// a wave per 64 nodes
+__global__ void __launch_bounds__(64)
+level_lists_kernel(const LevelRecordParams p)
+{
+    const int32_t w = blockIdx.x, lane = threadIdx.x, i = w * 64 + lane;
+    const bool last = w == (int32_t)gridDim.x - 1;
+    const int32_t mine = p.used[1 + w];
+    if (mine == 0 && !last) return;
+    int32_t before = 0;
+    for (int32_t k = lane; k < w; k += 64) before += p.used[1 + k];
+    for (int d = 32; d > 0; d /= 2) before += __shfl_xor(before, d);
+    if (last && lane == 0) p.used[0] = before + mine;
+    if (mine == 0 || i >= p.M) return;
+    Dag::FastRec &f = p.recs[p.slot[i]];
+    if (f.ovf < 0) return;
+    const int32_t e0 = p.ptr[i], n = p.ptr[i + 1] - e0, at = before + f.ovf;
+    if (at + 1 + n > p.room) return;                    // (never: the room is for the lists of all nodes)
+    f.ovf = at;
+    p.lists[at] = n;
+    for (int32_t e = 0; e < n; ++e) p.lists[at + 1 + e] = p.in[e0 + e] < 0 ? p.in[e0 + e] : p.slot[p.in[e0 + e]];
 }
 
 hipError_t launch_level_records(const Dag &d, hipStream_t s)
 {
     if (!d.d_lrecs || !d.d_node_ptr || d.M <= 0) return hipSuccess;          // (there are none, or the host has made them)
     LevelRecordParams p;
-    p.M = d.M; p.n_levels = d.n_node_levels; p.P = d.k1_threads / d.k1_wc; p.ring = d.k1_lring; p.row_bytes = d.k1_wc * 8; p.room = d.lfovf_len;
+    p.M = d.M; p.n_levels = d.n_node_levels; p.P = d.k1_threads / d.k1_wc; p.ring = d.k1_lring; p.row_bytes = d.k1_wc * 8; p.room = d.lfovf_room;
     p.lvl_ptr = d.d_nlvl_ptr; p.ptr = d.d_node_ptr; p.in = d.d_node_in; p.op = d.d_node_op; p.slot = d.d_node_slot;
     p.used = d.d_lfovf_used; p.lists = d.d_lfovf; p.recs = d.d_lrecs;
     const int64_t threads = std::max<int64_t>(d.M, (int64_t)p.n_levels * p.P);
     hipLaunchKernelGGL(level_records_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(level_lists_kernel, dim3((unsigned)((d.M + 63) / 64)), dim3(64), 0, s, p);
     return hipGetLastError();
 }
 
-// lists: entries of the lists that LDS is to have room for
-static bool level_params(const Dag &d, int WC, int lists, LevelParams *q, size_t *lds)
+static bool level_params(const Dag &d, int WC, LevelParams *q, size_t *lds)
 {
     if (!d.d_lrecs || !d.d_k1_sink || d.k1_wc != WC) return false;
     q->n_levels = d.n_node_levels; q->W = d.W; q->P = d.k1_threads / WC; q->ring = d.k1_lring;
-    q->lrecs = d.d_lrecs; q->lfovf = d.d_lfovf; q->lfovf_used = d.d_lfovf_used; q->dep = d.d_dep; q->sink = d.d_k1_sink;
-    q->lfovf_lds = lists;
+    q->lrecs = d.d_lrecs; q->lfovf = d.d_lfovf; q->dep = d.d_dep; q->sink = d.d_k1_sink;
+    q->lfovf_lds = d.lfovf_len <= 4096 ? d.lfovf_len : 0;
     *lds = (size_t)(d.k1_lring + 2) * WC * 8 + (size_t)q->lfovf_lds * 4;
     return *lds <= 150 * 1024;
 }
@@ -869,7 +892,7 @@ static hipError_t launch_levels_batch(Dag *const *ds, int G, void *staging, hipS
     int32_t most_copied = 0;
     for (int g = 0; g < G; ++g) {
         size_t lds = 0;
-        if (!level_params(*ds[g], WC, ds[g]->lfovf_count, &lp[g], &lds)) return hipErrorNotSupported;
+        if (!level_params(*ds[g], WC, &lp[g], &lds)) return hipErrorNotSupported;
         if (g == 0) lds0 = lds;
         if (lds != lds0 || ds[g]->k1_threads != ds[0]->k1_threads || ds[g]->W != ds[0]->W || ds[g]->n != ds[0]->n)
             return hipErrorNotSupported;
@@ -963,8 +986,7 @@ static hipError_t launch_nodes(const Dag &d, hipStream_t s)
         // level-major records: no staging, no chunks
         LevelParams q;
         size_t lds_l = 0;
-        // (one graph has a compute unit per workgroup, and LDS to spare; of several graphs four workgroups share one)
-        if (!level_params(d, WC, std::min(d.lfovf_len, 4096), &q, &lds_l)) return hipErrorInvalidValue;
+        if (!level_params(d, WC, &q, &lds_l)) return hipErrorInvalidValue;
         if (lds_l > 48 * 1024) {
             hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(propagate_levels<WC>), lds_l);
             if (e != hipSuccess) return e;

@@ -1,4 +1,5 @@
 // Calls into the library's launchers that no entry point reaches in a test (host_lib.py).
+#include <stdlib.h>
 #include <string.h>
 
 #include "frontier_plan.h"
@@ -15,6 +16,35 @@ extern "C" int host_group_rows(int32_t N, int32_t W)
     return (int)launch_group_rows(d, nullptr, nullptr, nullptr);
 }
 extern "C" int64_t host_group_bytes(int32_t N) { return (int64_t)group_workspace_bytes(N); }
+
+// level_records_kernel and level_lists_kernel on the host, node by node
+extern "C" void host_run_level_records(const void *params)
+{
+    const LevelRecordParams &p = *static_cast<const LevelRecordParams *>(params);
+    const int32_t zero = p.ring * p.row_bytes;
+    *p.used = 0;
+    for (int32_t i = 0; i < p.n_levels * p.P; ++i) p.recs[i] = Dag::FastRec{{zero, zero, zero, zero}, {-1, -1}, -1, -1};
+    for (int32_t k = 0; k < p.M; ++k) {
+        Dag::FastRec &f = p.recs[p.slot[k]];
+        const int32_t oldest = (p.slot[k] / p.P + 1) * p.P - p.ring, n = p.ptr[k + 1] - p.ptr[k], *in = p.in + p.ptr[k];
+        f.op = p.op[k];
+        int32_t nodes = 0, recvs = 0;
+        bool fits = true;
+        for (int32_t e = 0; e < n && fits; ++e) {
+            if (in[e] < 0) fits = recvs < 2;
+            else fits = nodes < 4 && p.slot[in[e]] >= oldest;
+            if (!fits) break;
+            if (in[e] < 0) f.rcv[recvs++] = ~in[e];
+            else f.in[nodes++] = (p.slot[in[e]] & (p.ring - 1)) * p.row_bytes;
+        }
+        if (fits) continue;
+        f = Dag::FastRec{{zero, zero, zero, zero}, {-1, -1}, p.op[k], *p.used};
+        *p.used += 1 + n;
+        if (*p.used > p.room) abort();
+        p.lists[f.ovf] = n;
+        for (int32_t e = 0; e < n; ++e) p.lists[f.ovf + 1 + e] = in[e] < 0 ? in[e] : p.slot[in[e]];
+    }
+}
 
 // words per lane and workgroups of the bit-sliced TAC kernel for a graph of C classes and R recvs, B samples: as launched
 extern "C" int host_tac_sliced(int32_t C, int32_t R, int32_t B)

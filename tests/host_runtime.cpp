@@ -1,6 +1,6 @@
 // A stand-in for the HIP runtime with which the host code of the library is tested without a GPU (host_lib.py links the
-// host halves of csrc/*.hip against it): device memory is host memory, a launch is recorded and, but for the two kernels
-// that only fill or copy, does nothing.  What can go wrong on the way can be ordered: the n-th allocation on the device or
+// host halves of csrc/*.hip against it): device memory is host memory, a launch is recorded and, but for the one that copies
+// and the one that makes records for the host to go by (host_probe.hip), does nothing.  What can go wrong on the way can be ordered: the n-th allocation on the device or
 // on the host fails, or the stream is being captured (then whatever is not allowed meanwhile fails, as in the runtime's
 // default capture mode).
 #include <hip/hip_runtime_api.h>
@@ -177,6 +177,7 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *c)
     *c = g_capturing && !s ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
+void host_run_level_records(const void *params);            // (host_probe.hip)
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t)
 {
     Inside in;
@@ -184,6 +185,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
     Launch l{kernels()[f], (int64_t)grid.x * grid.y * grid.z, (int64_t)block.x, (int64_t)lds, 0};
     if (l.name.find("copy_in_kernel") != std::string::npos)
         memcpy(*static_cast<void **>(args[2]), *static_cast<void **>(args[1]), (size_t)*static_cast<uint32_t *>(args[0]) * 16);
+    if (l.name.find("level_records_kernel") != std::string::npos) host_run_level_records(args[0]);
     if (l.name.find("fill_i32") != std::string::npos) memcpy(&l.filled, args[1], 8);
     if (g_launches.size() < 100000) g_launches.push_back(l);
     return hipSuccess;

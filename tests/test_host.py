@@ -304,6 +304,44 @@ def test_many_recvs_without_room_for_flags(lib):
     lib.free(h)
 
 
+def three_inputs(levels, width, far, wide, recvs, idle):
+    """Three inputs per op from the two levels before; every ``far``-th op one from the first level as well, every ``wide``-th six;
+    ``idle`` further recvs without a use."""
+    row, col = [0] * (recvs + idle + 1), []
+    for v in range(levels * width):
+        l, w = divmod(v, width)
+        ins = {v % recvs} if l == 0 else {recvs + idle + max(0, l - 1 - k % 2) * width + (w + 7 * k) % width for k in range(6 if v % wide == 0 else 3)}
+        if l and v % far == 0:
+            ins.add(recvs + idle + w)
+        col += sorted(ins)
+        row.append(len(col))
+    n = recvs + idle + levels * width
+    return wl.Dag("three_inputs", n, np.array(row, np.int32), np.array(col, np.int32), np.arange(recvs + idle, dtype=np.int32),
+                  np.ones(levels * width), np.ones(recvs + idle))
+
+
+@pytest.mark.parametrize("far,wide,fits", [(1 << 30, 1 << 30, True), (1000, 1 << 30, True), (1 << 30, 500, True), (100, 300, True), (10, 20, False)])
+def test_room_for_the_lists_of_the_level_kernel(lib, far, wide, fits):
+    """Nodes that fit no record (more inputs than it has room for, or one that has left the ring) have lists; LDS has room for all of
+    them, or for none where they are too many, whether the host makes the records or a kernel does."""
+    most = {}
+    for idle in (0, 192):
+        d = three_inputs(280, 100, far, wide, 1080, idle)
+        on_host = (d.n_ops + d.n_edges) * ((d.n_recv + 63) // 64) <= 1 << 21
+        handles = [lib.build(d) for _ in range(3)]
+        assert [rc for rc, _ in handles] == [0, 0, 0], lib.error()
+        arr = (ctypes.c_void_p * 3)(*[h for _, h in handles])
+        lib.host_forget_launches()
+        assert lib.tictac_dag_recompute_deps_batch(arr, I32(3), None) == 0, lib.error()
+        most[on_host], = [lds for name, _, _, lds, _ in lib.launches() if "propagate_levels_batch" in name]
+        for _, h in handles:
+            lib.free(h)
+    ring = most[True] // 8192 * 8192 + 16       # (of one-word slices: 1 024 slots and more, two words of zeros)
+    lists = (most[True] - ring) // 4
+    assert most[True] == most[False] and lists == (0 if far == wide or not fits else lists) <= 4096
+    assert (lists > 0) == (fits and far != wide)
+
+
 @pytest.mark.parametrize("recvs,run,slots,quads", [(250, 80, 4, False), (290, 16, 5, False), (290, 40, 5, False), (290, 64, 5, True),
                                                    (380, 16, 6, False), (380, 64, 6, True), (440, 2, 7, False), (440, 64, 7, True),
                                                    (500, 1, 8, False), (500, 90, 8, True)])
