@@ -1617,9 +1617,14 @@ static hipError_t commit_frontier(Dag *d, const FrontierPlan &p, const FrontierT
     t.add(&f.d_free_cols, p.free_cols);
     t.add(&f.d_own_ptr, p.own_ptr);
     t.add(&f.d_own, p.own);
+    if (p.numbered) {
+        t.add(&f.d_cls_of, p.cls_of);
+        t.reserve(&f.d_cls_dep, (size_t)d->C * d->W * 8);
+    }
     hipStream_t s;
     hipError_t e = table_stream(d->device, &s);
     if (e == hipSuccess) e = t.commit(f.block, d->device, s);
+    if (e == hipSuccess && p.numbered) e = launch_frontier_rows(*d, s);
     if (e == hipSuccess) e = t.finish();
     if (e != hipSuccess) return e;
     f.n_counters = (int32_t)p.counters.size();

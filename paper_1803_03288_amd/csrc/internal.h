@@ -49,6 +49,9 @@ struct FrontierTables {
     uint32_t *d_table = nullptr;    // FrontierTable
     int32_t *d_inputs = nullptr, *d_roots = nullptr, *d_free_cols = nullptr, *d_own_ptr = nullptr, *d_own = nullptr, *d_wide = nullptr;
     uint32_t *d_counters = nullptr;
+    // where the classes have numbers of their own: the class by number, the rows of cls_dep by number
+    int32_t *d_cls_of = nullptr;
+    uint64_t *d_cls_dep = nullptr;
 };
 
 // Everything a handle owns.  Device arrays are sized exactly; empty ones are NULL.
@@ -299,6 +302,8 @@ hipError_t launch_sliced_tables(const Dag &d, hipStream_t s);
 // chain form, one lane per sample (needs d.chain; the same contract as launch_tac_sliced).  hipErrorOutOfMemory: nothing has
 // been launched
 hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s);
+// d.frontier.d_cls_dep from d_cls_dep
+hipError_t launch_frontier_rows(const Dag &d, hipStream_t s);
 // frontier form, one wave per sample (needs d.frontier; the same contract as launch_tac_sliced; the samples that outgrow its lists
 // are flagged 2, for launch_tac_sliced or, like those flagged 1, for the general kernel)
 hipError_t launch_tac_frontier(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s);

@@ -42,7 +42,7 @@ namespace tictac {
 
 constexpr int kNoRecv = 0x3fff;             // (recvs take 14 bits in the lists)
 constexpr int kStack = kFrontierMaxStack, kFrontier = kFrontierMaxFrontier, kLog = 127;      // entries of the lists of a wave (and one for lanes that have none)
-constexpr int kWindow = 4096, kSlide = 256; // classes whose counters are in LDS, and by how many they move on
+constexpr int kWindow = kFrontierWindow, kSlide = 256;     // classes whose counters are in LDS, and by how many they move on
 constexpr int kPoints = 0x8000;             // state of a class that points: kPoints | recv; of another: 0
 
 struct FrontierParams {
@@ -879,6 +879,22 @@ static hipError_t launch_frontier_t(const FrontierParams &p, int grid, size_t ld
     return hipGetLastError();
 }
 
+// rows of W words, row k of `to` from row from_row[k]
+__global__ void __launch_bounds__(256)
+frontier_rows_kernel(size_t words, int32_t W, const int32_t *__restrict__ from_row, const uint64_t *__restrict__ from, uint64_t *__restrict__ to)
+{
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < words) to[i] = from[(size_t)from_row[i / W] * W + i % W];
+}
+
+hipError_t launch_frontier_rows(const Dag &d, hipStream_t s)
+{
+    const size_t words = (size_t)d.C * d.W;
+    hipLaunchKernelGGL(frontier_rows_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, words, d.W, d.frontier.d_cls_of,
+                       d.d_cls_dep, d.frontier.d_cls_dep);
+    return hipGetLastError();
+}
+
 hipError_t launch_tac_frontier(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s)
 {
     const FrontierTables &f = d.frontier;
@@ -889,7 +905,7 @@ hipError_t launch_tac_frontier(Dag &d, const TacArgs &a, size_t flag_bytes, size
     p.counters = f.d_counters; p.n_counters = f.n_counters;
     p.roots = f.d_roots; p.free_cols = f.d_free_cols; p.own_ptr = f.d_own_ptr; p.own = f.d_own;
     p.n_roots = f.n_roots; p.n_free = f.n_free;
-    p.cls_cols = d.d_cls_cols; p.cls_dep = d.d_cls_dep;
+    p.cls_cols = d.d_cls_cols; p.cls_dep = f.d_cls_dep ? f.d_cls_dep : d.d_cls_dep;
     p.op_time = a.op_time; p.recv_time = a.recv_time;
     p.order = a.order; p.rank = a.rank; p.simulate = a.simulate ? 1 : 0;
     p.makespan = a.makespan; p.eff = a.eff; p.U = a.U; p.L = a.L; p.S = a.S;

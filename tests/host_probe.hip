@@ -79,7 +79,7 @@ extern "C" int64_t host_frontier_array(const void *plan, const char *name, const
     const struct { const char *name; const void *at; size_t n; } all[] = {
         {"row", p.row.data(), p.row.size() * 16}, {"inputs", p.inputs.data(), p.inputs.size()}, {"outputs", p.outputs.data(), p.outputs.size()},
         {"counters", p.counters.data(), p.counters.size()}, {"wide", p.wide.data(), p.wide.size()}, {"roots", p.roots.data(), p.roots.size()},
-        {"free_cols", p.free_cols.data(), p.free_cols.size()}, {"own_ptr", p.own_ptr.data(), p.own_ptr.size()}, {"own", p.own.data(), p.own.size()}};
+        {"free_cols", p.free_cols.data(), p.free_cols.size()}, {"own_ptr", p.own_ptr.data(), p.own_ptr.size()}, {"own", p.own.data(), p.own.size()}, {"cls_of", p.cls_of.data(), p.cls_of.size()}};
     for (const auto &a : all)
         if (!strcmp(a.name, name)) {
             *at = a.at;

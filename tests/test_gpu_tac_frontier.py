@@ -89,6 +89,14 @@ def long_classes():
     return with_layers(first, 320)
 
 
+def backwards(d):
+    """The same graph with its ops numbered the other way round: no input of a class is an earlier class, as they come."""
+    rows = [(d.n_ops - 1 - d.col_idx[d.row_ptr[v]:d.row_ptr[v + 1]])[::-1] for v in range(d.n_ops)][::-1]
+    return wl.Dag(name="backwards", n_ops=d.n_ops, row_ptr=np.cumsum([0] + [len(r) for r in rows]).astype(np.int32),
+                  col_idx=np.concatenate(rows).astype(np.int32), recv_ids=(d.n_ops - 1 - d.recv_ids)[::-1].astype(np.int32).copy(),
+                  op_median=d.op_median[::-1].copy(), recv_bytes=d.recv_bytes[::-1].copy())
+
+
 GRAPHS = {
     "layered": lambda: layered(40, 40, 400),
     "one_word": lambda: layered(40, 150, 63, attach=(1, 4)),
@@ -104,6 +112,10 @@ GRAPHS = {
     # a little longer than the lists: the plan takes the form, the kernel leaves samples
     "q140": lambda: many_pointed(140), "frontier300": lambda: long_frontier(300), "frontier500": lambda: frontier_in_two(210),
     "long_classes": long_classes,
+    # ids that do not rise along the graph: classes numbered by level
+    "fallen": lambda: backwards(layered(40, 40, 400)), "fallen_own": lambda: backwards(layered(30, 60, 500, attach=(8, 16))),
+    "fallen_long": lambda: backwards(long_classes()), "fallen_in64": lambda: backwards(fans(64)),
+    "relabelled": lambda: wl.relabel(layered(40, 100, 300), 3)[0],
 }
 
 
@@ -191,14 +203,6 @@ def side_by_side(parts):
                   col_idx=np.concatenate([d.col_idx + k for d, k in zip(parts, n)]).astype(np.int32),
                   recv_ids=np.concatenate([d.recv_ids + k for d, k in zip(parts, n)]).astype(np.int32),
                   op_median=np.concatenate([d.op_median for d in parts]), recv_bytes=np.concatenate([d.recv_bytes for d in parts]))
-
-
-def backwards(d):
-    """The same graph with its ops numbered the other way round: no input of a class is an earlier class."""
-    rows = [(d.n_ops - 1 - d.col_idx[d.row_ptr[v]:d.row_ptr[v + 1]])[::-1] for v in range(d.n_ops)][::-1]
-    return wl.Dag(name="backwards", n_ops=d.n_ops, row_ptr=np.cumsum([0] + [len(r) for r in rows]).astype(np.int32),
-                  col_idx=np.concatenate(rows).astype(np.int32), recv_ids=(d.n_ops - 1 - d.recv_ids)[::-1].astype(np.int32).copy(),
-                  op_median=d.op_median[::-1].copy(), recv_bytes=d.recv_bytes[::-1].copy())
 
 
 # The counters in LDS are those of 4 096 classes: some more, classes busy in several places, all of them moving the other way.

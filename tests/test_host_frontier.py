@@ -9,7 +9,7 @@ import pytest
 from paper_1803_03288_amd import workloads as wl
 
 from host_lib import I32, ptr
-from test_gpu_tac_frontier import GRAPHS as LISTS
+from test_gpu_tac_frontier import GRAPHS as LISTS, backwards
 from test_host import GRAPHS, layered, lib          # noqa: F401  (lib: the fixture)
 
 LARGE = 600                                         # samples: more than two per compute unit
@@ -45,6 +45,24 @@ def test_graphs_whose_samples_outgrow_the_lists(lib, name, frontier):
     lib.free(h)
 
 
+def in_order(d):
+    """The ops, each after those before it."""
+    if all((d.col_idx[d.row_ptr[v]:d.row_ptr[v + 1]] < v).all() for v in range(d.n_ops)):
+        return range(d.n_ops)
+    done, out = np.zeros(d.n_ops, bool), []
+    for v in range(d.n_ops):
+        todo = [v]
+        while todo:
+            u = todo[-1]
+            before = [] if done[u] else [w for w in d.col_idx[d.row_ptr[u]:d.row_ptr[u + 1]] if not done[w]]
+            todo += before
+            if not before:
+                todo.pop()
+                out += [] if done[u] else [u]
+                done[u] = True
+    return out
+
+
 def plan_of(lib, d, pieces):
     """The plan of graph ``d`` with the sets of its compute ops as classes, each in ``pieces`` of consecutive ops, and what it was made
     from: ``(plan or None, dep of the classes, class of every op, columns by class)``."""
@@ -52,9 +70,8 @@ def plan_of(lib, d, pieces):
     recv_of, cls_of, level, deps = np.full(n, -1, np.int32), np.full(n, -1, np.int32), np.zeros(n, np.int32), [0] * n
     recv_of[d.recv_ids] = np.arange(R)
     members = {}
-    for v in range(n):                      # (the graphs' ops are in topological order)
+    for v in in_order(d):
         before = d.col_idx[d.row_ptr[v]:d.row_ptr[v + 1]]
-        assert (before < v).all()
         level[v] = 1 + max((level[u] for u in before), default=-1)
         for u in before:
             deps[v] |= deps[u]
@@ -64,8 +81,8 @@ def plan_of(lib, d, pieces):
             members.setdefault(deps[v], []).append(v)
     dep, columns = [], []
     column = np.cumsum(recv_of < 0) - 1
-    for bits, ops in members.items():
-        for part in np.array_split(ops, min(pieces, len(ops))):
+    for bits, ops in sorted(members.items(), key=lambda m: min(m[1])):
+        for part in np.array_split(np.sort(ops), min(pieces, len(ops))):
             cls_of[part] = len(dep)
             dep.append(bits)
             columns.append(column[part].tolist())
@@ -77,7 +94,7 @@ def plan_of(lib, d, pieces):
     if not plan:
         return None, dep, cls_of, columns
     got = {}
-    for name in ("row", "inputs", "outputs", "counters", "wide", "roots", "free_cols", "own_ptr", "own"):
+    for name in ("row", "inputs", "outputs", "counters", "wide", "roots", "free_cols", "own_ptr", "own", "cls_of"):
         at = ctypes.c_void_p()
         k = lib.L.host_frontier_array(ctypes.c_void_p(plan), name.encode(), ctypes.byref(at))
         got[name] = np.ctypeslib.as_array(ctypes.cast(at, ctypes.POINTER(ctypes.c_int32)), (k,)).copy() if k else np.zeros(0, np.int32)
@@ -196,6 +213,47 @@ def test_the_table_that_the_kernel_reads(lib, name, pieces):
         assert q[1, 2] == 4 * (16 * C + row[c, 9]) and q[2, 2] == n and q[2, 3] == row[c, 13]
         assert q[0, 3] == row[c, 14] and (n < 1 or q[1, 3] == row[c, 15 if n > 1 else 14])
     assert pieces > 1 or (listed > 0) == (name == "far_apart")      # (a piece may come before what feeds its set)
+
+
+def two_far_apart():
+    """Two graphs of which the ops of one come between those of the other: inputs that are more than the window before what they feed."""
+    d = layered(24, 260, 300)
+    first, n = d.n_recv, d.n_ops
+    new = np.concatenate([np.arange(first), first + (np.arange(n - first) % 2) * ((n - first + 1) // 2) + np.arange(n - first) // 2])
+    old = np.argsort(new)
+    rows = [np.sort(new[d.col_idx[d.row_ptr[v]:d.row_ptr[v + 1]]]) for v in old]
+    return wl.Dag("two_far_apart", n, np.cumsum([0] + [len(r) for r in rows]).astype(np.int32), np.concatenate(rows).astype(np.int32),
+                  d.recv_ids, d.op_median, d.recv_bytes)
+
+
+@pytest.mark.parametrize("name,pieces,by_level", [("layered", 1, False), ("in16", 1, False), ("backwards", 1, True), ("backwards", 2, True),
+                                                  ("relabelled", 1, True), ("long_classes", 2, True), ("two_far_apart", 1, True)])
+def test_classes_are_numbered_along_the_graph(lib, name, pieces, by_level):
+    """As they come where inputs come before what they feed and not far before it, else by level; either way the plan says the same of
+    the classes, and the table where their rows and columns are."""
+    d = {"layered": lambda: layered(12, 160, 300), "in16": LISTS["in16"], "backwards": lambda: backwards(layered(12, 160, 300)),
+         "relabelled": lambda: wl.relabel(layered(12, 160, 300), 5)[0], "long_classes": lambda: backwards(LISTS["long_classes"]()),
+         "two_far_apart": two_far_apart}[name]()
+    p, dep, cls_of_op, columns = plan_of(lib, d, pieces)
+    R, C, row, of = d.n_recv, len(dep), p["row"].reshape(-1, 16), p["cls_of"]
+    assert sorted(of) == list(range(C)) and (of.tolist() != list(range(C))) == by_level
+    table, order, holds, feeds = p["table"][:16 * C].reshape(C, 4, 4), [j for c in columns for j in c], {}, {}
+    assert not table[:, 3, 2:].any()
+    for c in range(C):
+        x, union = inputs_of(row, p, R, c), 0
+        for v in x:
+            assert v < c or (not by_level and name == "layered"), (c, v)
+            union |= dep[of[v]] if v >= 0 else 1 << ~v
+            holds.setdefault(v, []).append(c)
+        assert union == dep[of[c]], c
+        feeds[c] = sum(v >= 0 for v in x)
+        n, first = int(row[c, 12]), int(row[c, 13])
+        assert order[first:first + n] == columns[of[c]] and row[c, 14:16].tolist() == (columns[of[c]] + [0, 0])[:2]
+        assert table[c, 2, 2] == n and table[c, 2, 3] == first
+    assert p["roots"].tolist() == [c for c in range(C) if dep[of[c]] and not feeds[c]]
+    assert p["free_cols"].tolist() == [j for c in range(C) if not dep[of[c]] for j in columns[of[c]]]
+    for r in range(R):
+        assert p["own"][p["own_ptr"][r]:p["own_ptr"][r + 1]].tolist() == holds.get(~r, []), r
 
 
 def inputs_of(row, p, R, c):
