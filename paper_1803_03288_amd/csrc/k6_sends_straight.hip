@@ -26,6 +26,7 @@
 // tile, at the columns that matter 2 us.  On times that are not quantised makespan, U and L are within 4e-16 of sums in long
 // double (event-driven form: 3e-15).
 #include <algorithm>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "internal.h"
@@ -34,6 +35,7 @@ namespace tictac {
 
 constexpr int kTileCols = 64, kTileChecks = 32, kTilePitch = 65;
 constexpr int kRowCols = (2 * kTileCols * kTilePitch + 2 * kTileChecks * 64) / kTilePitch;      // columns of 64 rows that fit the tiles' space
+constexpr int kRowsLeast = 16;  // so many and fewer columns are read by lanes, a row each (SMALL)
 typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
 
 // The tables are the same for all lanes: read through the scalar cache, they have a counter of waits of their own.  (By vector
@@ -60,6 +62,13 @@ struct StraightParams {
     int32_t *list, *count;          // the samples given up
 };
 
+// SMALL: at most 64 recvs and sends, a quarter of which is a batch of loads or two.  All loads of a batch are executed, of the last
+// place again where there are no more, so that nothing waits between them; 64 lines each where every sample has an order.
+// Hence batches of eight, of the recvs four at the end, and the times of at most sixteen recvs or columns of sends by lanes that read their
+// rows instead of through LDS.  40 000 samples, an order each, a send behind every op: chains of 8 recvs 33.9 us (51.5 with sixteen at a
+// time, through LDS), of 12 36.8 (50.9), of 40 71.4 (74.5), vgg16 59.1 (64.4).  Larger graphs: sixteen at a time, of the recvs eight at the end;
+// a chain of 250 recvs 452 us, 528 by eight; resnet50 with one order 221 and 226.
+template <bool SMALL>
 __global__ void __launch_bounds__(320)
 sends_straight_kernel(const StraightParams p)
 {
@@ -76,7 +85,7 @@ sends_straight_kernel(const StraightParams p)
     double *req_at = p.req_at + (size_t)blockIdx.x * p.n_req * 64;
     const int groups = (p.B + 63) / 64;
     const int at_row = tid >> 5, at_col = (tid & 31) * 2;       // (of the loaders)
-    const bool rows_fit = R >= 2 && R <= kRowCols;
+    const bool rows_fit = R > (SMALL ? kRowsLeast : 1) && R <= kRowCols;
 
     for (int g = blockIdx.x; g < groups; g += gridDim.x) {
         const int b0 = g * 64, here = min(64, p.B - b0);
@@ -120,26 +129,32 @@ sends_straight_kernel(const StraightParams p)
                 sum = 0.0;
                 for (int w = 0; w < wave; ++w) sum += red[w * 64 + lane];
             }
-            for (int k = k0; k < k1; k += 16) {
-                // (all loads are executed, with places past the end clamped, so that nothing waits between them)
-                int r[16];
-                double x[16];
+            auto ends = [&](int k, auto loads) __attribute__((always_inline)) {
+                constexpr int n = decltype(loads)::value;
+                int r[n];
+                double x[n];
 #pragma unroll
-                for (int q = 0; q < 16; ++q) r[q] = p.order[b * p.order_stride + min(k + q, k1 - 1)];
+                for (int q = 0; q < n; ++q) r[q] = p.order[b * p.order_stride + min(k + q, k1 - 1)];
                 if (rows_fit) {
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) x[q] = xs[min((unsigned)r[q], (unsigned)R - 1u) * kTilePitch + lane];
+                    for (int q = 0; q < n; ++q) x[q] = xs[min((unsigned)r[q], (unsigned)R - 1u) * kTilePitch + lane];
                 } else {
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) x[q] = p.recv_time[b * R + min((unsigned)r[q], (unsigned)R - 1u)];
+                    for (int q = 0; q < n; ++q) x[q] = p.recv_time[b * R + min((unsigned)r[q], (unsigned)R - 1u)];
                 }
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {
+                for (int q = 0; q < n; ++q) {
                     const bool valid = k + q < k1 && (unsigned)r[q] < (unsigned)R;          // (invalid: skipped)
                     sum += valid ? x[q] : 0.0;
                     if (pass == 1) arrive[(size_t)(valid ? r[q] : R) * 64 + lane] = sum;    // (row R is spare)
                 }
-            }
+            };
+            int k = k0;
+            if constexpr (!SMALL)
+                for (; k1 - k > 8; k += 16) ends(k, std::integral_constant<int, 16>());
+            if constexpr (SMALL)
+                for (; k1 - k > 4; k += 8) ends(k, std::integral_constant<int, 8>());
+            if (k < k1) ends(k, std::integral_constant<int, SMALL ? 4 : 8>());
         }
         const double sum_r = wave == 4 ? sum : 0.0;             // (the fifth wave has added up all four quarters)
         if (tid < 2) stop[tid] = 0;
@@ -272,22 +287,23 @@ sends_straight_kernel(const StraightParams p)
         double add = 0.0, least = -TT_INF;
         if (loader && !given_up) {
             const int part = (p.n_req + 3) / 4, q0 = min(p.n_req, wave * part), q1 = min(p.n_req, q0 + part);
-            for (int q = q0; q < q1; q += 16) {
-                double at[16], y[16];
+            constexpr int n = SMALL ? 8 : 16;
+            for (int q = q0; q < q1; q += n) {
+                double at[n], y[n];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) at[i] = req_at[(size_t)min(q + i, q1 - 1) * 64 + lane];
+                for (int i = 0; i < n; ++i) at[i] = req_at[(size_t)min(q + i, q1 - 1) * 64 + lane];
                 if (p.req_span > 0) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) y[i] = xs[(uniform_int(p.req_col + min(q + i, q1 - 1)) - p.req_lo) * kTilePitch + lane];
+                    for (int i = 0; i < n; ++i) y[i] = xs[(uniform_int(p.req_col + min(q + i, q1 - 1)) - p.req_lo) * kTilePitch + lane];
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) y[i] = p.op_time[b * N + uniform_int(p.req_col + min(q + i, q1 - 1))];
+                    for (int i = 0; i < n; ++i) y[i] = p.op_time[b * N + uniform_int(p.req_col + min(q + i, q1 - 1))];
                 }
 #pragma unroll
-                for (int i = 0; i < 16; ++i)
+                for (int i = 0; i < n; ++i)
                     if (q + i < p.n_req0) at[i] = 0.0;          // (requested at the start: not stored)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
+                for (int i = 0; i < n; ++i) {
                     if (q + i < q1) { add += y[i]; least = max_f64(least, at[i]) + y[i]; }
                 }
             }
@@ -340,7 +356,9 @@ hipError_t launch_sends_straight(Dag &d, const SimArgs &a, size_t rest, int32_t 
     const int grid = std::min(groups, device_cu_count(d.device));
     StraightParams p{};
     p.B = a.B; p.N = d.N; p.R = d.R; p.n_req = (int32_t)d.h_send_ids.size(); p.n_req0 = d.n_send_free; p.n_tiles = d.n_straight_tiles;
-    p.req_lo = d.straight_req_lo; p.req_span = d.straight_req_span <= kRowCols ? d.straight_req_span : 0;
+    const bool small = d.R <= 64 && p.n_req <= 64;
+    p.req_lo = d.straight_req_lo;
+    p.req_span = d.straight_req_span > (small ? kRowsLeast : 0) && d.straight_req_span <= kRowCols ? d.straight_req_span : 0;
     p.code = d.d_straight_code; p.chk = d.d_straight_chk; p.req_col = d.d_straight_req; p.tiles = d.d_straight_tiles;
     p.order = a.order; p.order_stride = a.order_stride;
     p.op_time = static_cast<const double *>(a.op_time); p.recv_time = static_cast<const double *>(a.recv_time);
@@ -355,10 +373,11 @@ hipError_t launch_sends_straight(Dag &d, const SimArgs &a, size_t rest, int32_t 
     *list = p.list;
     *count = p.count;
     const size_t lds = (size_t)(2 * kTileCols * kTilePitch + 2 * kTileChecks * 64 + 2 * 4 * 64) * 8 + 2 * kTileCols * 4 + 16;
-    e = ensure_dynamic_lds(reinterpret_cast<const void *>(sends_straight_kernel), lds);
+    void (*const kernel)(StraightParams) = small ? sends_straight_kernel<true> : sends_straight_kernel<false>;
+    e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernel), lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(1), 0, s, p.count);
-    hipLaunchKernelGGL(sends_straight_kernel, dim3(grid), dim3(320), lds, s, p);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(320), lds, s, p);
     return hipGetLastError();
 }
 

@@ -41,7 +41,11 @@ def chain_with_sends(recvs, extra, sends, first):
 
 
 @pytest.mark.parametrize("recvs,extra,sends,first", [(1, 1, 1, True), (2, 61, 1, False), (64, 0, 63, True), (65, 3, 66, False),
-                                                     (190, 1, 191, False), (191, 2, 192, True), (192, 70, 190, False), (300, 0, 300, True)])
+                                                     (190, 1, 191, False), (191, 2, 192, True), (192, 70, 190, False), (300, 0, 300, True),
+                                                     # batches of sixteen, eight and four loads; sixteen recvs or sends and one more
+                                                     (3, 1, 4, True), (4, 13, 16, False), (16, 0, 16, True), (17, 0, 17, False), (16, 3, 17, True),
+                                                     (17, 9, 16, False), (33, 0, 33, True), (36, 4, 37, False), (63, 1, 64, True), (64, 0, 64, False),
+                                                     (64, 2, 65, True), (65, 0, 64, False), (96, 8, 100, True), (100, 8, 97, False)])
 def test_straight_form(tt, recvs, extra, sends, first):
     d, ids = chain_with_sends(recvs, extra, sends, first)
     h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
