@@ -773,7 +773,7 @@ expand_rows_batch(const ExpandParams *__restrict__ ps)
 // inputs are at most four rows that the ring still holds and two recvs fits its record; any other has a list, whose place among
 // those of its wave goes into the record, and level_lists_kernel adds the lists of the waves before and writes it.  So the lists lie
 // in the order of the nodes: where lanes take them from a counter as they come, 300 x 100 layered ops, 1 300 recvs, with more lists
-// than LDS has room for, take 3 % more.  stress (60 000 nodes in 119 000 slots): 9 + 7 us; the host took 0.75 ms of a build's 4.25 for
+// than LDS has room for, take 3 % more.  stress (60 000 nodes in 119 000 slots): 9 + 5 us; the host took 0.75 ms of a build's 4.25 for
 // filling the records and twice the bytes to the device.
 __global__ void __launch_bounds__(256)
 level_records_kernel(const LevelRecordParams p)
@@ -831,7 +831,13 @@ level_lists_kernel(const LevelRecordParams p)
     const int32_t mine = p.used[1 + w];
     if (mine == 0 && !last) return;
     int32_t before = 0;
-    for (int32_t k = lane; k < w; k += 64) before += p.used[1 + k];
+    for (int32_t k0 = 0; k0 < w; k0 += 8 * 64) {        // (eight requests under way)
+#pragma unroll
+        for (int32_t j = 0; j < 8; ++j) {
+            const int32_t k = k0 + 64 * j + lane, x = p.used[1 + min(k, w - 1)];
+            before += k < w ? x : 0;
+        }
+    }
     for (int d = 32; d > 0; d /= 2) before += __shfl_xor(before, d);
     if (last && lane == 0) p.used[0] = before + mine;
     if (mine == 0 || i >= p.M) return;
