@@ -705,17 +705,27 @@ struct Condensed {
     const int32_t *end(int32_t k) const { return &in[0] + ptr[k + 1]; }
 };
 
-// Whether a branch on the number of predecessors of an op would go either way: two and more on average (layered graphs).  Then
-// the passes over all ops do as if all had four (100 000 ops, 2.6 on average: levels 635 -> 345 us, condensation 810 -> 500);
-// on chains of ops, where the branch is foreseen, they do what there is to do (inception3, 1.5: a build 136 us, 157 with four).
-// On small graphs the branches of one build are remembered until the next (1 700 ops, 2.5: 93 us, 97 with four).
-static bool mixed_degrees(int32_t n, int32_t E) { return n >= 4096 && E / 2 >= n; }
+// Whether a branch on the number of predecessors of an op would go either way: in a sample of 256 ops more than a quarter have
+// another number than the op before, and there are two and more on average.  Then the passes over all ops do as if all had four
+// (layered graphs with one to four each, every graph seen once: 100 000 ops, levels and condensation 1.44 -> 0.85 ms; a build of 1 800 ops
+// 255 -> 232 us, of 600 154 -> 152).  Where the branch is foreseen they do what there is to do: 30 000 ops with three each 1.4 ms, 1.65 with
+// four; inception3, chains of ops with 1.5 on average, 136 us, 157 with four.
+static bool mixed_degrees(int32_t n, const int32_t *row_ptr)
+{
+    if (n < 3 || row_ptr[n] / 2 < n) return false;
+    int32_t changes = 0;
+    for (int32_t i = 1; i <= 256; ++i) {
+        const int32_t v = 1 + (int32_t)((int64_t)i * (n - 2) / 256);
+        changes += row_ptr[v + 1] - row_ptr[v] != row_ptr[v] - row_ptr[v - 1];
+    }
+    return changes > 64;
+}
 
+template <bool MIXED>
 static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_idx, const std::vector<int32_t> &recv_of_op,
                      const std::vector<int32_t> &level, const std::vector<int32_t> &order, Condensed &g)
 {
     const int32_t n = d.n;
-    const bool mixed = mixed_degrees(n, d.E);
     g.val.resize(n);
     g.op.resize(n); g.ptr.resize(n + 1);
     g.in.resize((size_t)d.E + 1);           // (one more: begin() of an empty list)
@@ -728,7 +738,7 @@ static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_id
         const int32_t *pred = col_idx + e0;
         // (few predecessors, as most ops have: each value is written and kept if it differs from those before, without a
         // branch that could go either way; where numbers of predecessors vary the last one stands in for those missing)
-        if (mixed && (uint32_t)(deg - 1) < 4u) {
+        if (MIXED && (uint32_t)(deg - 1) < 4u) {
             const int32_t x0 = val[pred[0]], x1 = val[pred[std::min(1, deg - 1)]], x2 = val[pred[std::min(2, deg - 1)]], x3 = val[pred[deg - 1]];
             const int32_t k1 = x1 != x0, k2 = (x2 != x0) & (x2 != x1), k3 = (x3 != x0) & (x3 != x1) & (x3 != x2);
             in[at] = x0;
@@ -809,16 +819,19 @@ static void condense(const Dag &d, const int32_t *row_ptr, const int32_t *col_id
 }
 
 // The ops whose rows are copies (of a recv's single bit, or of the row of the node the op collapses onto).
+template <bool MIXED>
 static std::vector<int32_t> copied_rows(const Condensed &g)
 {
     const int32_t n = (int32_t)g.val.size();
-    std::vector<int32_t> copied(2 * (size_t)(n - g.M) + 2);         // (two more: every op is written, a node's is written over)
+    std::vector<int32_t> copied(2 * (size_t)(n - g.M) + 2);         // (two more: MIXED writes every op, a node's is written over)
     size_t at = 0;
     for (int32_t v = 0; v < n; ++v) {
         const int32_t x = g.val[v], from = x < 0 ? x : g.op[x];
-        copied[at] = v;
-        copied[at + 1] = from;
-        at += from != v ? 2 : 0;
+        if (MIXED || from != v) {
+            copied[at] = v;
+            copied[at + 1] = from;
+            at += from != v ? 2 : 0;
+        }
     }
     copied.resize(at);
     return copied;
@@ -1007,11 +1020,12 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
                                   const std::vector<int32_t> &level, const std::vector<int32_t> &order, const bool by_kernel, PropTables &t)
 {
     Condensed &g = t.g;
-    condense(*d, row_ptr, col_idx, recv_of_op, level, order, g);
+    const bool mixed = mixed_degrees(d->n, row_ptr);
+    (mixed ? condense<true> : condense<false>)(*d, row_ptr, col_idx, recv_of_op, level, order, g);
     const int32_t M = g.M, n_node_levels = g.n_levels, max_width = g.max_width;
     const std::vector<int32_t> &nlvl_ptr = g.lvl_ptr;
     d->M = M; d->n_node_levels = n_node_levels;
-    t.copied = copied_rows(g);
+    t.copied = (mixed ? copied_rows<true> : copied_rows<false>)(g);
     d->n_copied = (int32_t)(t.copied.size() / 2);
     // words per workgroup slice, threads, and the chunks of levels of the node kernel
     // a workgroup's LDS traffic per level grows with its slice, so wide bitsets get many narrow slices
@@ -1158,29 +1172,17 @@ constexpr int64_t kHostRowWords = (int64_t)1 << 21;
 // ops, a first batch of 32 such handles 31 ms instead of 2.8.
 constexpr int64_t kPropThread = 16384;
 
-static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int32_t R, const int32_t *recv_ids,
-                 hipStream_t s, Dag *d)
+// Checks the predecessors; levels, as long as every predecessor has a lower id (topological).
+template <bool MIXED>
+static int levels_by_id(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, std::vector<int32_t> &level, int32_t &n_levels,
+                        bool &topological)
 {
-    // ---- validation (host) ----
-    if (n < 0 || R < 0 || R > n) { set_error("bad sizes: n_ops=%d n_recv=%d", n, R); return TICTAC_ERR_BAD_CSR; }
-    if (!row_ptr) { set_error("pred_row_ptr is NULL"); return TICTAC_ERR_NULL; }
-    if (R > 0 && !recv_ids) { set_error("recv_ids is NULL"); return TICTAC_ERR_NULL; }
-    if (row_ptr[0] != 0) { set_error("pred_row_ptr[0] != 0"); return TICTAC_ERR_BAD_CSR; }
-    for (int32_t v = 0; v < n; ++v)
-        if (row_ptr[v + 1] < row_ptr[v]) { set_error("pred_row_ptr decreases at op %d", v); return TICTAC_ERR_BAD_CSR; }
-    const int32_t E = row_ptr[n];
-    if (E > 0 && !col_idx) { set_error("pred_col_idx is NULL"); return TICTAC_ERR_NULL; }
-    // (levels along the way, as long as every predecessor has a lower id)
-    bool topological = true;
-    std::vector<int32_t> level(n, 0);
-    int32_t n_levels = 0;
-    const bool mixed = mixed_degrees(n, E);
     for (int32_t v = 0; v < n; ++v) {
         int32_t l = 0, e0 = row_ptr[v];
         const int32_t e1 = row_ptr[v + 1];
         // (one to four predecessors, as most ops have: the last one again in place of those that are missing, so that no
         // branch depends on how many there are)
-        if (mixed && (uint32_t)(e1 - e0 - 1) < 4u) {
+        if (MIXED && (uint32_t)(e1 - e0 - 1) < 4u) {
             const int32_t a = col_idx[e0], b = col_idx[std::min(e0 + 1, e1 - 1)], c = col_idx[std::min(e0 + 2, e1 - 1)], f = col_idx[e1 - 1];
             const uint32_t most = std::max(std::max((uint32_t)a, (uint32_t)b), std::max((uint32_t)c, (uint32_t)f));
             if (most < (uint32_t)n) {
@@ -1198,6 +1200,27 @@ static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int3
         level[v] = l;
         n_levels = std::max(n_levels, l + 1);
     }
+    return TICTAC_OK;
+}
+
+static int build(int32_t n, const int32_t *row_ptr, const int32_t *col_idx, int32_t R, const int32_t *recv_ids,
+                 hipStream_t s, Dag *d)
+{
+    // ---- validation (host) ----
+    if (n < 0 || R < 0 || R > n) { set_error("bad sizes: n_ops=%d n_recv=%d", n, R); return TICTAC_ERR_BAD_CSR; }
+    if (!row_ptr) { set_error("pred_row_ptr is NULL"); return TICTAC_ERR_NULL; }
+    if (R > 0 && !recv_ids) { set_error("recv_ids is NULL"); return TICTAC_ERR_NULL; }
+    if (row_ptr[0] != 0) { set_error("pred_row_ptr[0] != 0"); return TICTAC_ERR_BAD_CSR; }
+    for (int32_t v = 0; v < n; ++v)
+        if (row_ptr[v + 1] < row_ptr[v]) { set_error("pred_row_ptr decreases at op %d", v); return TICTAC_ERR_BAD_CSR; }
+    const int32_t E = row_ptr[n];
+    if (E > 0 && !col_idx) { set_error("pred_col_idx is NULL"); return TICTAC_ERR_NULL; }
+    // (levels along the way, as long as every predecessor has a lower id)
+    bool topological = true;
+    std::vector<int32_t> level(n, 0);
+    int32_t n_levels = 0;
+    const int status = (mixed_degrees(n, row_ptr) ? levels_by_id<true> : levels_by_id<false>)(n, row_ptr, col_idx, level, n_levels, topological);
+    if (status != TICTAC_OK) return status;
     std::vector<int32_t> recv_of_op(n, -1);
     for (int32_t i = 0; i < R; ++i) {
         int32_t v = recv_ids[i];

@@ -304,6 +304,54 @@ def test_many_recvs_without_room_for_flags(lib):
     lib.free(h)
 
 
+def out_of_order(degrees, seed=2):
+    """An op per entry of ``degrees`` behind four recvs, with so many predecessors among the ops before it."""
+    g = np.random.default_rng(seed)
+    row, col = [0] * 5, []
+    for k, n in enumerate(degrees):
+        col += sorted(g.choice(4 + k, size=min(n, 4 + k), replace=False).tolist())
+        row.append(len(col))
+    n = 4 + len(degrees)
+    return wl.Dag("degrees", n, np.array(row, np.int32), np.array(col, np.int32), np.arange(4, dtype=np.int32), np.ones(len(degrees)), np.ones(4))
+
+
+# numbers of predecessors that vary from op to op, and that do not; a few ops and many
+@pytest.mark.parametrize("count", [3, 60, 5000])
+@pytest.mark.parametrize("degrees", [(1, 4, 2, 3), (2,), (3, 3, 3, 1), (1, 2, 9, 3), (0, 4, 3, 5)])
+def test_predecessors_are_checked(lib, count, degrees):
+    """A predecessor out of range is refused with its place, whichever of an op's it is; one with the op's own or a higher id is not,
+    unless that makes a cycle."""
+    d = out_of_order([degrees[k % len(degrees)] for k in range(count)])
+    rc, h = lib.build(d)
+    assert rc == 0, lib.error()
+    lib.free(h)
+    g = np.random.default_rng(count)
+    for v in g.choice(np.arange(4, d.n_ops), size=min(count, 6), replace=False):
+        for e in range(d.row_ptr[v], d.row_ptr[v + 1]):
+            for bad in (-1, d.n_ops, -2**31, 2**31 - 1):
+                col = d.col_idx.copy()
+                col[e] = bad
+                rc, _ = lib.build(wl.Dag("bad", d.n_ops, d.row_ptr, col, d.recv_ids, d.op_median, d.recv_bytes))
+                assert rc == -2 and lib.error() == f"pred_col_idx[{e}]={bad} out of range"
+            col = d.col_idx.copy()
+            col[e] = v
+            assert lib.build(wl.Dag("self", d.n_ops, d.row_ptr, col, d.recv_ids, d.op_median, d.recv_bytes))[0] == -3
+    # the other way round: every predecessor has a higher id
+    n = d.n_ops
+    rows = [(n - 1 - d.col_idx[d.row_ptr[v]:d.row_ptr[v + 1]])[::-1] for v in range(n)][::-1]
+    back = wl.Dag("back", n, np.cumsum([0] + [len(r) for r in rows]).astype(np.int32), np.concatenate(rows).astype(np.int32),
+                  (n - 1 - d.recv_ids)[::-1].astype(np.int32).copy(), d.op_median, d.recv_bytes)
+    levels = []
+    for x in (d, back):
+        rc, h = lib.build(x)
+        assert rc == 0, lib.error()
+        got = I32()
+        lib.tictac_dag_info(h, None, None, None, ctypes.byref(got), None)
+        levels.append(got.value)
+        lib.free(h)
+    assert levels[0] == levels[1]
+
+
 def three_inputs(levels, width, far, wide, recvs, idle):
     """Three inputs per op from the two levels before; every ``far``-th op one from the first level as well, every ``wide``-th six;
     ``idle`` further recvs without a use."""
