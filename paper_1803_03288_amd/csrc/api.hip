@@ -708,11 +708,12 @@ struct Condensed {
 // Whether a branch on the number of predecessors of an op would go either way: in a sample of 256 ops more than a quarter have
 // another number than the op before, and there are two and more on average.  Then the passes over all ops do as if all had four
 // (layered graphs with one to four each, every graph seen once: 100 000 ops, levels and condensation 1.44 -> 0.85 ms; a build of 1 800 ops
-// 255 -> 232 us, of 600 154 -> 152).  Where the branch is foreseen they do what there is to do: 30 000 ops with three each 1.4 ms, 1.65 with
-// four; inception3, chains of ops with 1.5 on average, 136 us, 157 with four.
+// 255 -> 232 us, of 960 155 -> 145).  Where the branch is foreseen they do what there is to do: 30 000 ops with three each 1.4 ms, 1.65 with
+// four; inception3, chains of ops with 1.5 on average, 136 us, 157 with four; and of a graph of a few hundred ops that is built again and
+// again the branches are remembered (700 ops 101 us, 103 with four, 152 and 147 once; 960 ops 92 either way).
 static bool mixed_degrees(int32_t n, const int32_t *row_ptr)
 {
-    if (n < 3 || row_ptr[n] / 2 < n) return false;
+    if (n < 800 || row_ptr[n] / 2 < n) return false;
     int32_t changes = 0;
     for (int32_t i = 1; i <= 256; ++i) {
         const int32_t v = 1 + (int32_t)((int64_t)i * (n - 2) / 256);
