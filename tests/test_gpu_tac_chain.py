@@ -40,6 +40,26 @@ def modules_dag(modules, name="modules"):
     return b.finish(name, seed=5, batch=8)
 
 
+def overlapping_dag(branches, units, fork=False, name="overlapping"):
+    """Units of branches of which neighbours are joined: the recv of a branch in the middle is a sink of two gates.  A layer follows
+    every join, and all of them are joined at the end of the unit.  Two branches: the first goes on behind the join, and what it ends
+    with is joined with the second too.  fork: two layers follow the layer of every branch in the middle as well."""
+    b = wl._Builder()
+
+    def layer(x):
+        return b.op([b.op([x, b.recv(1e5 * (1 + len(b.preds) % 3))], 1e-3, "layer")], 1e-3, "op")
+    x = b.op([], 1e-3, "input")
+    for _ in range(units):
+        ends = [layer(x) for _ in range(branches)]
+        if branches == 2:
+            joins = [b.op(ends, 1e-3, "join"), b.op([layer(ends[0]), ends[1]], 1e-3, "join")]
+        else:
+            joins = [layer(b.op([y, z], 1e-3, "join")) for y, z in zip(ends, ends[1:])]
+            joins += [layer(y) for y in ends[1:-1] for _ in range(2) if fork]
+        x = b.op(joins, 1e-3, "join")
+    return b.finish(name, seed=5, batch=8)
+
+
 GRAPHS = {
     "chain": lambda: wl.chain_dag(97),
     "one": lambda: wl.chain_dag(1),
@@ -50,7 +70,12 @@ GRAPHS = {
     "eight_branches": lambda: modules_dag([[1, 2, 3, 1, 2, 3, 1, 2], [2], [1, 1, 1, 1, 1, 1, 1, 1]]),
     "jobs": lambda: wl.independent_jobs_dag(8),
     "resnet50": wl.resnet50_dag,
+    # recvs that are sinks of two gates: the kernel's instantiations for two, four and eight slots that know of second gates
+    "second_two": lambda: overlapping_dag(2, 12), "second_three": lambda: overlapping_dag(3, 9), "second_four": lambda: overlapping_dag(4, 1),
+    "second_five": lambda: overlapping_dag(5, 7), "second_eight": lambda: overlapping_dag(8, 4), "second_fork": lambda: overlapping_dag(3, 6, fork=True),
+    "second_fork_four": lambda: overlapping_dag(4, 4, fork=True),
 }
+SECOND_GATES = {"second_two": 2, "second_three": 4, "second_four": 4, "second_five": 8, "second_eight": 8, "second_fork": 4, "second_fork_four": 8}
 
 
 def times(d, B, kind, rng):

@@ -11,6 +11,7 @@ from paper_1803_03288_amd import workloads as wl
 
 from host_lib import HostLib, I32, build_host_lib, ptr
 from test_gpu_lane_layouts import SLOTS
+from test_gpu_tac_chain import GRAPHS as CHAINS, SECOND_GATES
 
 
 @pytest.fixture(scope="module")
@@ -304,6 +305,19 @@ def test_many_recvs_without_room_for_flags(lib):
     lib.free(h)
 
 
+@pytest.mark.parametrize("name", list(CHAINS))
+def test_chain_form_and_second_gates(lib, name):
+    """Every graph of the chain form's tests takes it, those with recvs that are sinks of two gates the kernels that know of them."""
+    d = CHAINS[name]()
+    h = lib.build(d)[1]
+    lib.host_forget_launches()
+    assert lib.tac(h, d, 8192) == 0, lib.error()
+    kernel, = [k for k in lib.kernels() if "tac_chain_kernel" in k]
+    slots, second = int(kernel[kernel.index("ILi") + 3]), "ELb1E" in kernel
+    assert second == (name in SECOND_GATES) and slots == SECOND_GATES.get(name, slots), kernel
+    lib.free(h)
+
+
 def out_of_order(degrees, seed=2):
     """An op per entry of ``degrees`` behind four recvs, with so many predecessors among the ops before it."""
     g = np.random.default_rng(seed)
@@ -316,7 +330,7 @@ def out_of_order(degrees, seed=2):
 
 
 # numbers of predecessors that vary from op to op, and that do not; a few ops and many
-@pytest.mark.parametrize("count", [3, 60, 5000])
+@pytest.mark.parametrize("count", [3, 795, 796, 5000])
 @pytest.mark.parametrize("degrees", [(1, 4, 2, 3), (2,), (3, 3, 3, 1), (1, 2, 9, 3), (0, 4, 3, 5)])
 def test_predecessors_are_checked(lib, count, degrees):
     """A predecessor out of range is refused with its place, whichever of an op's it is; one with the op's own or a higher id is not,
