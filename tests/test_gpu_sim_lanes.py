@@ -67,6 +67,43 @@ def test_simulate_lanes(tt, name):
     h.check_orders()
 
 
+def chain_of(ops, recvs):
+    """A chain of ops, the first ones with a recv each."""
+    b = wl._Builder()
+    rs, x = [b.recv(1e5) for _ in range(recvs)], []
+    for k in range(ops):
+        x = [b.op(x + (rs[k:k + 1] if k < ops - 1 else rs[k:]), 1e-3, "op")]
+    return b.finish("chain_of", seed=3, batch=4)
+
+
+# One order for all, rows of the next samples requested ahead: pieces of 32 columns (float64) or 64 (float32), one or two of op_time's rows
+# and one of recv_time's; rows as long as a request, a column more, and so long that nothing is requested ahead.
+@pytest.mark.parametrize("ops,recvs", [(2, 2), (3, 2), (4, 4), (5, 3), (31, 8), (32, 32), (33, 32), (40, 33), (63, 17), (64, 31), (64, 64), (65, 32),
+                                       (90, 64), (127, 63), (128, 64), (128, 65), (129, 64)])
+def test_more_samples_than_are_under_way(tt, ops, recvs):
+    """Every wave takes several groups of 64 samples, the last one not whole."""
+    d = chain_of(ops, recvs)
+    B, part = 64 * 256 * 16 + 64 * 5 + 29, 16384                # (at most sixteen such waves share a compute unit)
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    gen = torch.Generator(device="cuda").manual_seed(ops)
+    op = torch.randint(0, 1 << 14, (B, ops), device="cuda", generator=gen) * 2.0 ** -20
+    rv = torch.randint(0, 1 << 14, (B, recvs), device="cuda", generator=gen) * 2.0 ** -20
+    order = torch.randperm(recvs, device="cuda", generator=gen).to(torch.int32)
+    rows = [0, 63, 64, part, B // 2, B - 30, B - 1]
+    for dtype in (torch.float64, torch.float32):
+        print(f"[lanes] {ops} ops, {recvs} recvs, {dtype}, {B} samples", flush=True)
+        o, r = op.to(dtype), rv.to(dtype)
+        got = tt.simulate(h, order, o, r)
+        for lo in range(0, B, part):
+            for x, y in zip(got, tt.simulate(h, order, o[lo:lo + part].contiguous(), r[lo:lo + part].contiguous())):
+                assert torch.equal(x[lo:lo + part], y), lo
+        exp = oracle.simulate(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids, order.cpu().numpy()[None].repeat(len(rows), 0),
+                              o[rows].double().cpu().numpy(), r[rows].double().cpu().numpy())
+        for x, y in zip(got, exp):
+            np.testing.assert_allclose(x[rows].cpu().numpy(), y, rtol=1e-12, atol=0)
+    h.check_orders()
+
+
 @pytest.mark.parametrize("value", [-1, 7, 1 << 20, "twice"])
 def test_bad_orders_in_the_lane_kernels(tt, value):
     """An entry out of range or a recv named twice, in one sample of a large batch and in a shared order: reported, and
