@@ -533,10 +533,16 @@ static hipError_t launch_chain_nc(const ChainParams &p, hipStream_t s)
 constexpr size_t kChainChunkBytes = (size_t)512 << 20;
 constexpr size_t kChainChunkLeast = 8192;
 // Bytes read and written by class_totals_kernel up to which totals and times go through the caches: the Infinity Cache (256 MB)
-// then still holds enough of them for tac_chain_kernel.  A pass with and without: vgg16, 262 144 samples, 347 MB 121 and 125 us, as
-// float32, 242 MB 117 and 128; 65 536 samples, 87 MB 39.1 and 39.8; resnet50, 50 000 samples as float32, 386 MB 191.8 and 190.6,
-// 65 536, 837 MB 301 and 295; inception3, 20 000 samples, 1.1 GB 492 and 488.
-constexpr size_t kTotalsCached = (size_t)352 << 20;
+// then still holds enough of them for tac_chain_kernel.  What a pass takes past the caches, against through them (150 to 800 MB in steps of
+// 20 to 100; up to 220 MB the same to 3 % more):
+//   MB                  300     350     400     420     460     500-520   600     800
+//   vgg16     float64   +8 %    +6      +3      +2      +1      +1        -1      -4
+//             float32   +7      +3      +5      +4      +1      +1        -4      -4
+//   resnet50  float64   -1      +4      +4      +2      +1      +1        +1      -0.5
+//             float32   +7      +1      +1      -0.5    -1      -2        -2      -3
+//   inception3, both    +1      +1      0       0       0       0         0       -0.5
+// So the sides meet between 415 MB (resnet50, float32) and 700 (resnet50, float64), and by then nothing hangs on it.
+constexpr size_t kTotalsCached = (size_t)432 << 20;
 
 hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s)
 {

@@ -145,7 +145,7 @@ def test_chain_form_inception(tt):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["float64", "float32"])
 def test_totals_past_the_caches(dtype):
-    """A batch whose rows and totals exceed 352 MiB writes the totals past the caches; parts of it do not.  Times are
+    """A batch whose rows and totals exceed 432 MiB writes the totals past the caches; parts of it do not.  Times are
     multiples of 2^-20 below 2^-6, so every sum is exact and the bytes are the same."""
     import torch
     from paper_1803_03288_amd import binding as tt, workloads as wl
