@@ -10,20 +10,20 @@
 //   * a class with an input that does not point yet has that input's outstanding recvs, two at least, and its M is no smaller:
 //     neither P nor the least M is concerned with it.  It only keeps the number of such inputs, which each input
 //     lowers by one when it begins to point.
-// So a sample costs one visit per edge of the class graph instead of R rounds over all classes: with 62 837 classes and
-// 4 096 recvs 171 000 edges against 1.7 * 10^8 set bits.  The frontier has 40 members on average and 150 at most there, Q (the
+// So a sample costs one visit per edge of the class graph instead of R rounds over all classes: on stress, 60 567 classes and
+// 4 096 recvs, 193 000 edges against 1.7 * 10^8 set bits.  The frontier has 40 members on average and 150 at most there, Q (the
 // recvs with P > 0) 23 and 79, so one wave keeps both in LDS.  The states of the classes (16 bits each) are in memory, and so are the
 // numbers of their open inputs (4 bits) but for those of 4 096 classes, which move on with the highest class that has been told of an
-// input: what a sample is busy with are a few thousand classes, whose numbers come from the graph when the window reaches them and go to memory
+// input: classes are numbered along the graph (frontier_plan.h), and what a sample is busy with are a few thousand of them, whose numbers come from the graph when the window reaches them and go to memory
 // when it leaves them.  So sixteen samples share a compute unit.
-//   A round is a chain of 2.3 goes at up to sixteen classes each.  4 096 samples of that graph, cycles per round and wave, sixteen waves
+//   A round is a chain of 2.3 goes at up to sixteen classes each.  4 096 samples of stress, cycles per round and wave, sixteen waves
 // to a compute unit (all but a tenth of it also while a wave is by itself): the rows of the classes 3 500, the states of their inputs 2 600,
 // putting down those that point 1 400, their outputs' counters and the next classes 3 600, and, when all is done, times and P of what points 4 300;
-// the selection before 2 800, the frontier 700.  46 GB are fetched, nearly all of it for the times: 100 000 of them per
-// sample come a line each, since a line's are asked for at rounds far apart.  46.1 -> 38.4 ms by the following, each by itself 3 to 8 %: the counters
-// in LDS (a trip to the L2 per go; 26 GB written -> 10); a class's row in one request, sixteen bytes to a lane, with eight inputs, so
+// the selection before 2 800, the frontier 700.  48 GB are fetched, nearly all of it for the times: 100 000 of them per
+// sample come a line each, since a line's are asked for at rounds far apart.  46.1 -> 38.6 ms by the following, each by itself 3 to 8 %: the counters
+// in LDS (a trip to the L2 per go; 25.8 GB written -> 8.6); a class's row in one request, sixteen bytes to a lane, with eight inputs, so
 // that more than four are no further trip; the sums of the iteration 64 steps at a time, over the lanes; loads and LDS operations by all lanes
-// instead of behind branches (680 vector and 390 scalar instructions a round, 800 and 560 before).  Not faster: times
+// instead of behind branches (640 vector and 370 scalar instructions a round, 800 and 560 before).  Not faster: times
 // requested in the go that finds the class (memory operations of a wave come back in order, so the next rows wait for them), times past
 // the L2, the selection by the high words of the times with fewer instructions, rare branches out of line.  Sixteen-bit counters beside the states had
 // taken 65 ms to 49, and all counters in LDS leave room for seven samples per compute unit.
@@ -81,11 +81,6 @@ __device__ __forceinline__ T *at(T *base, uint32_t i)
 // over the four lanes of a quad
 template <int CTRL>
 __device__ __forceinline__ int quad_perm(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true); }
-template <int CTRL>
-__device__ __forceinline__ double quad_get(double v)
-{
-    return __hiloint2double(quad_perm<CTRL>(__double2hiint(v)), quad_perm<CTRL>(__double2loint(v)));
-}
 __device__ __forceinline__ int quad_min(int v)
 {
     v = min(v, quad_perm<0xb1>(v));
@@ -113,7 +108,9 @@ __device__ __forceinline__ void scan_exact(double &v, double &lo)
 }
 
 // States of the classes of one sample, 16 bits each, in LDS or in memory: kPoints | recv, or 0.  Only the wave itself reads and
-// writes them (plain loads and stores, which the L1 of its compute unit keeps coherent; wait_vmem() between the two).
+// writes them.  A get of what another lane has put needs no wait: the vector memory operations of a wave reach the L1 of its compute unit in
+// the order in which they are issued, so what orders the two at the scope of a wavefront (wave_sync(), which lies between any put and the gets of
+// the next go, and which the compiler moves neither across) is enough.
 template <bool LDS>
 struct States {
     uint16_t *p;
