@@ -39,8 +39,11 @@ __device__ __forceinline__ void store_total(double *to, double x)
 }
 
 // Per tile 256 bytes of each of the 64 rows: a request of a wave covers four rows.  (128 and 512 bytes: 4 % and 5 % slower
-// on inception3's rows, 4 % and 12 % on resnet50's; 0.70 ms and 0.15 ms for 65 536 samples, 4.7 and 4.4 TB/s.)  The next
-// tile is requested once the present one is in LDS.
+// on inception3's rows, 4 % and 12 % on resnet50's.)  The next tile is requested once the present one is in LDS.
+// 65 536 samples take 761 us on inception3 and 198 on resnet50: 4.3 and 3.3 TB/s of rows, but 5.7 and 5.4 of what is read and written,
+// the rate of a copy.  The totals and times written are 13 % and 27 % on top of the rows, and lines are read twice: a piece of 256 bytes
+// that does not start on a line touches three, and the shared one has left the cache when the next piece comes (3 941 MB read for 3 299 MB
+// of rows on inception3, 904 for 661 on resnet50).
 // PAST: totals and times are written past the caches, which hold neither all of them (434 MB for inception3) nor then what is
 // read meanwhile: inception3 773 -> 761 us and 366 -> 355 for tac_chain_kernel, resnet50 204 -> 198.  (The rows read past the
 // caches, whose 128-byte lines two requests share, take 894 us, the orders written so 7 us more.)

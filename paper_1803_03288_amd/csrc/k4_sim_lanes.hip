@@ -355,7 +355,9 @@ static hipError_t launch_lanes_t(SimLanesParams &p, const Dag &d, hipStream_t s)
     lds = (lds + 15) & ~(size_t)15;
     // (two waves per compute unit at the least)
     if (lds > 80 * 1024) return hipErrorNotSupported;
-    // (the registers of three pieces of 64 rows, 192, are what a wave has beside its own at two waves per SIMD)
+    // The rows of the next 64 samples are requested ahead where they fit registers: three pieces of 64 rows, 192, are what a wave has
+    // beside its own at two waves per SIMD.  That is up to 64 columns and 32 recvs in float64, 128 and 64 in float32; wider samples are loaded when
+    // the wave comes to them.
     constexpr int VEC = 16 / (int)sizeof(T), TC = 16 * VEC;
     const bool fits = p.N >= VEC && p.R >= VEC && p.N <= 2 * TC && p.R <= TC;
     void (*const kernel)(SimLanesParams) = !shared ? simulate_lanes_kernel<T> : !fits ? simulate_lanes_shared_kernel<T, 0>

@@ -18,8 +18,9 @@
 // (busy -> max(busy + A, B)).
 //
 // 16 384 samples of the ResNet-50 inference graph with 161 sends (187 MB of times, 38 us at the copy rate): 4.0 ms in the
-// event-driven form with a wave per sample, 75 us here (the call 86 us).  Bound by the latencies of a tile, since there is
-// one workgroup of 64 samples per compute unit: 13 us for the arrivals, 43 us for the 18 tiles (18 of them for the fifth wave,
+// event-driven form with a wave per sample, 73 us here (the call 84 us).  Bound by the latencies of a tile, since there is
+// one workgroup of 64 samples per compute unit (two of 32 would not fit: a wave has up to 256 registers): waves wait 54 % of their time.  Of
+// 75 us, before batches of loads ended with one of eight where eight are enough: 13 us for the arrivals, 43 us for the 18 tiles (18 of them for the fifth wave,
 // which is behind the loaders then), 7 us for the uplink.  It was 93 us (18, 55, 20) as long as the loads of a batch hid
 // behind branches, each with a wait of its own, the times of transfers and sends were read by a lane per row, and a wait for an
 // index in a table was one for the tiles on their way.  With the columns followed one by one the fifth wave took 4 us per
