@@ -70,10 +70,14 @@ struct TacRegParams {
 // no more sets than as many as LDS holds, the kernel of eight, which spills nothing, has the batch: 22 x 35 ops and 336 recvs, one
 // sample 442 us (with 128 registers 467), 1 024 samples 498 (531); 58 x 23 and 380, where LDS holds ten, 532 (587) and 597
 // (665), 3 000 samples 1 280 (1 552).
+//   Where more than twelve are needed twice or more and twelve, three waves per SIMD with 168 registers, take no more sets, twelve have the batch, and
+// the samples of a compute unit are dealt to its sets evenly (two of ten and not sixteen and four): 5 003 samples of 61 x 23 and 203
+// 902 -> 770 us, 6 144 of them 900 -> 770, 30 x 20 and 203 749 -> 648, 24 x 20 and 300 1 118 -> 971, 40 x 25 and 260 1 138 -> 969; sixteen remain in one set
+// (nine to twelve samples: 408, twelve 401) and where twelve would take another set (32 samples per compute unit: 914 in two of sixteen).
 //   More than 384 recvs, up to 1 024 (a bit per lane and position of a 32-bit word) where LDS holds the rows, against the general
 // kernel, 5 003 samples, ms: 20 x 10 ops and 500 recvs 5.8 and 2.1; 30 x 20 and 400, 9.2 and 1.5; 61 x 23 and 400, 17.6 and 2.7;
 // 25 x 15 and 1 000, 28.8 and 11.4.
-constexpr int kRegWavesMax = 16, kRegWavesFew = 8;
+constexpr int kRegWavesMax = 16, kRegWavesMid = 12, kRegWavesFew = 8;
 constexpr int reg_waves(int KT, int W) { return KT <= 4 && W <= 6 ? 4 : kRegWavesMax; }
 // More than this many classes per lane: the class totals are summed in the whole region of the wave, M comes out of tables of
 // subset sums (with both, 61 x 23 ops: 54 900 -> 44 700 vector instructions per sample).  Below, where M is rarely looked at and
@@ -715,20 +719,25 @@ static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
     if (KT > kTableSlots) per_wave = std::max(per_wave + 256, (size_t)64 * KT);     // (the table; room for the class totals)
     // as many waves as LDS allows
     int waves = reg_waves(KT, d.W);
+    const int each = std::max(1, (p.B + device_cu_count(d.device) - 1) / device_cu_count(d.device));   // samples per compute unit
     while (waves > 4 && (rows_doubles + per_wave * waves) * 8 > 150 * 1024) --waves;
     auto kern = tac_reg_kernel<KT, LIST, kRegWavesMax>;
     if constexpr (KT > kTableSlots) {
-        const int few = std::min(waves, kRegWavesFew), each = (p.B + device_cu_count(d.device) - 1) / device_cu_count(d.device);
+        const int few = std::min(waves, kRegWavesFew);
         if ((each + few - 1) / few <= (each + waves - 1) / waves) {
             kern = tac_reg_kernel<KT, LIST, kRegWavesFew>;
             waves = few;
+        } else if (waves > kRegWavesMid && each > waves && (each + kRegWavesMid - 1) / kRegWavesMid <= (each + waves - 1) / waves) {
+            kern = tac_reg_kernel<KT, LIST, kRegWavesMid>;
+            waves = kRegWavesMid;
         }
     }
     const size_t lds = (rows_doubles + per_wave * waves) * 8;
     if (lds > 150 * 1024) return hipErrorNotSupported;
-    // (a small batch is spread over the compute units, the waves of a SIMD slow each other down; those without a sample
+    // (the samples of a compute unit are dealt to its sets evenly: the waves of a SIMD slow each other down; those without a sample
     // help to bring in the rows)
-    p.active = std::min(waves, std::max(1, (p.B + device_cu_count(d.device) - 1) / device_cu_count(d.device)));
+    const int sets = (each + waves - 1) / waves;
+    p.active = (each + sets - 1) / sets;
     p.wave_doubles = (int32_t)per_wave;
     // the class totals are summed in the space of P, ordl and the outstanding set when that holds
     // one double per class slot

@@ -72,6 +72,27 @@ def test_tac_with_many_classes(tt, name):
     h.close()
 
 
+@pytest.mark.parametrize("levels,width,recvs,low,high", [(50, 18, 203, 513, 640), (45, 22, 203, 641, 768), (61, 23, 203, 769, 896), (60, 28, 203, 897, 1024)])
+def test_two_sets_of_twelve_waves(tt, levels, width, recvs, low, high):
+    """Batches whose samples take two sets of sixteen waves per compute unit: twelve waves, and the samples dealt to them evenly, give
+    every sample what batches of one set give."""
+    d = wl.layered_dag(41, levels=levels, width=width, fan_in=(1, 4), back=3, n_recv=recvs, attach=(1, 8))
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    print(f"[tac] two sets: {levels} x {width}, {recvs}: classes={h.n_classes}", flush=True)
+    assert low <= h.n_classes <= high, h.n_classes
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    gen = torch.Generator(device="cuda").manual_seed(levels)
+    for B in (16 * cu + 1, 20 * cu - 117, 24 * cu):
+        op = torch.randint(1, 1 << 20, (B, d.n_compute), device="cuda", generator=gen).double() * wl.QUANTUM
+        rv = torch.randint(1, 1 << 20, (B, d.n_recv), device="cuda", generator=gen).double() * wl.QUANTUM
+        got = tt.tac_simulate(h, op, rv, want_rank=True)
+        for lo in range(0, B, 8 * cu):
+            part = tt.tac_simulate(h, op[lo:lo + 8 * cu].contiguous(), rv[lo:lo + 8 * cu].contiguous(), want_rank=True)
+            for k in (0, 1, 4, 5, 6, 7, 8):
+                assert torch.equal(got[k][lo:lo + 8 * cu], part[k]), (B, lo, k)
+    h.close()
+
+
 def test_one_and_two_words_per_lane(tt):
     """The bit-sliced kernel on a graph whose classes take two words per lane for a batch of more samples than compute
     units (two workgroups share one) and one word for a smaller batch: the same results for every sample."""
