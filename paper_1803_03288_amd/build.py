@@ -40,11 +40,14 @@ def is_stale() -> bool:
 #   "request": after the stores that follow a wait come `loads` 16-byte loads in straight-line code (the request
 #              the wait is counted for); up to the next wait only loads follow (a load whose value is used has
 #              been waited for, and everything older with it: memory instructions of a wave complete in order)
+#   "stores": in the loops of the waves that store, N = 6 k: k 16-byte stores and no other memory instruction between the wait and
+#             the branch, barrier or wait before it (a loop stores k rows per level; all of k = 1 .. n occur)
 COUNTED_WAITS = {
     "16propagate_levelsILi": {"n": 21, "kind": "level", "loads": 2, "stores": 1},
     "22propagate_levels_batchILi": {"n": 21, "kind": "level", "loads": 2, "stores": 1},
     "24propagate_levels_q_batchILi": {"n": 14, "kind": "level", "loads": 1, "stores": 1},
     "15propagate_nodesILi": {"n": 8, "kind": "request", "loads": 8},
+    "25propagate_levels_q_storedILi": {"n": 7, "kind": "stores"},
 }
 _VM_PREFIXES = ("global_", "flat_", "scratch_", "buffer_")
 
@@ -86,13 +89,27 @@ def check_counted_waits(asm: str) -> list:
                     events.append(("wait", n))
             elif t.startswith(_VM_PREFIXES):
                 events.append(("vm", t.split()[0]))
-            elif t.startswith(("s_cbranch", "s_branch", "s_swappc", "s_setpc")):
+            elif t.startswith(("s_cbranch", "s_branch", "s_swappc", "s_setpc", "s_barrier")):
                 events.append(("branch",))
-        if any(e[0] == "vm" and e[1].startswith(("scratch_", "buffer_")) for e in events):
+        spills = ("scratch_",) if rule["kind"] == "stores" else ("scratch_", "buffer_")
+        if any(e[0] == "vm" and e[1].startswith(spills) for e in events):
             bad.append(f"{name}: register spills (scratch instructions) in a kernel with counted waits")
         waits = [i for i, e in enumerate(events) if e[0] == "wait"]
         if not waits:
             bad.append(f"{name}: no hand-written wait found")
+            continue
+        if rule["kind"] == "stores":
+            found = set()
+            for i in waits:
+                first = i
+                while first > 0 and events[first - 1][0] == "vm":
+                    first -= 1
+                ops, n = [e[1] for e in events[first:i]], events[i][1]
+                if n % 6 or len(ops) != n // 6 or any(o != "buffer_store_dwordx4" for o in ops):
+                    bad.append(f"{name}: {ops} before a wait for all but {n}")
+                found.add(n // 6)
+            if found != set(range(1, rule["n"] + 1)):
+                bad.append(f"{name}: loops that store {sorted(found)} rows per level, expected 1 to {rule['n']}")
             continue
         if any(events[i][1] != rule["n"] for i in waits):
             bad.append(f"{name}: a hand-written wait is not vmcnt({rule['n']})")

@@ -611,7 +611,8 @@ propagate_levels_batch(const LevelParams *__restrict__ ps, int blocks_per)
 // the ring a copy node some levels later (see the build of the records), so a level still reads LDS only.
 // The records are 16 bytes (see internal.h): a level issues exactly one 16-byte load and one 16-byte store per thread.
 typedef unsigned long long tt_u64x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void store_device_16(void *q, tt_u64x2 v) { *(__attribute__((address_space(1))) tt_u64x2 *)q = v; }
+// (with less priority in the caches: 32 graphs of 400 x 240 layered ops, whose levels leave no room for waves that store, 573 -> 560 us)
+__device__ __forceinline__ void store_device_16(void *q, tt_u64x2 v) { __builtin_nontemporal_store(v, (__attribute__((address_space(1))) tt_u64x2 *)q); }
 
 // words gw, gw + 1 of all inputs of a node that does not fit a record (see other_inputs)
 __device__ __noinline__ tt_u64x2 other_inputs_q(const int32_t *lfovf, const int32_t *fov, const uint64_t *ring,
@@ -644,11 +645,49 @@ struct QuadParams {
     const int32_t *lfovf;
     int32_t lfovf_lds;                  // > 0: that many entries of lfovf (all of them) are copied to LDS
     uint64_t *dep;
+    int32_t dep_bytes;                  // 0: more than a buffer descriptor takes here
     uint64_t *sink;                     // [gridDim.x * blockDim.x][2]
 };
 
-// QC lanes per slot (4: 64-byte slices, 2: 32-byte slices)
-template <int QC>
+// The rows of level l go to memory while level l + 1 is computed: by kStoreThreads threads, N stores each, of which those of levels up to
+// l - 6 have been completed when level l + 2 begins (a list reads a row from memory eight levels later or more).  They are written
+// through the caches (kThrough): the rows of 32 graphs are 1.7 GB, and lines that wait in the L2 to be pushed out by later ones
+// leave it at half the rate of a copy, whoever stores them and in whatever order.  stress, 32 graphs: 278 us without the stores; the computing
+// waves storing 541, two more waves 550, the latter contiguously 520; with less priority in the caches (nt) 460 and 446; nt and through
+// them 390 (sc1 alone 588).  With the copied rows 584 -> 427 us; 16 graphs 440 -> 330, 8 350 -> 318; 32 graphs of 500 x 100 469 -> 383, of
+// 500 x 30 and 1 024 recvs 178 -> 166.
+typedef int tt_row16 __attribute__((ext_vector_type(4)));
+constexpr int kStoreThreads = 128;
+constexpr int kThrough = 18;                // sc1 (to memory at once) and nt
+template <int QC, int N>
+__device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t *ring, const int32_t *ops, int t, int gw)
+{
+    constexpr int RW = 2 * QC, SLOTS = kStoreThreads / QC;
+    static_assert(SLOTS == 32, "the slots of a level are a multiple of this");
+    const int P = p.P, L = p.n_levels, s0 = t / QC;
+    const uint32_t rmask = (uint32_t)p.ring - 1u;
+    const uint64_t *const mine = ring + (t % QC) * 2;
+    const auto dep = __builtin_amdgcn_make_buffer_rsrc(p.dep, 0, p.dep_bytes, 0x00027000);
+    for (int l = 0; l < L; ++l) {
+        lds_barrier();
+        int op[N];
+        tt_row16 row[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            op[j] = ops[(l & 1) * P + j * SLOTS + s0];
+            row[j] = *reinterpret_cast<const tt_row16 *>(mine + ((uint32_t)(l * P + j * SLOTS + s0) & rmask) * RW);
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j)             // (a slot without an op: beyond the end of the buffer, where nothing is written)
+            __builtin_amdgcn_raw_buffer_store_b128(row[j], dep, op[j] >= 0 ? (op[j] * p.W + gw) * 8 : -1, 0, kThrough);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 * N) : "memory");
+    }
+    for (int l = L; l % 32 != 0; ++l) lds_barrier();        // (those that compute go 32 levels at a time)
+}
+
+// QC lanes per slot (4: 64-byte slices, 2: 32-byte slices).  STORED: two waves beside those that compute bring the rows to memory; the
+// threads of a level find the op of its slots in one half of `ops`.
+template <int QC, bool STORED>
 __device__ __forceinline__ void propagate_levels_q_body(const QuadParams &p, uint64_t *ring, int block, int n_blocks)
 {
     constexpr int RW = 2 * QC;                  // words of a row in the ring
@@ -662,12 +701,27 @@ __device__ __forceinline__ void propagate_levels_q_body(const QuadParams &p, uin
     for (int i = threadIdx.x; i < p.lfovf_lds; i += blockDim.x) fov[i] = load_device_4(p.lfovf + i);
     __syncthreads();
     if (L == 0) return;
+    int32_t *const ops = fov + p.lfovf_lds;     // [2][P]
+    if constexpr (STORED) {
+        if ((int)threadIdx.x >= P * QC) {
+            const int t = (int)threadIdx.x - P * QC;
+            switch (P / (kStoreThreads / QC)) {
+            case 1: return store_levels<QC, 1>(p, ring, ops, t, gw);
+            case 2: return store_levels<QC, 2>(p, ring, ops, t, gw);
+            case 3: return store_levels<QC, 3>(p, ring, ops, t, gw);
+            case 4: return store_levels<QC, 4>(p, ring, ops, t, gw);
+            case 5: return store_levels<QC, 5>(p, ring, ops, t, gw);
+            case 6: return store_levels<QC, 6>(p, ring, ops, t, gw);
+            default: return store_levels<QC, 7>(p, ring, ops, t, gw);
+            }
+        }
+    }
 
 #define KQ_LOAD(a, l) a = load_device_16(p.qrecs + (size_t)min((l), L - 1) * P + sub);
 #define KQ_DECL(i) int4 a##i; KQ_LOAD(a##i, i)
     KL_EACH(KQ_DECL)
 
-    uint64_t *const sink = p.sink + ((size_t)block * blockDim.x + threadIdx.x) * 2;
+    uint64_t *const sink = p.sink + ((size_t)block * (P * QC) + threadIdx.x) * 2;
     const char *const rb = reinterpret_cast<const char *>(ring) + qd * 16;
     uint32_t slot = (uint32_t)sub;              // the slot of these four lanes at the level being computed
 #define KQ_BIT(r)                                                                         \
@@ -699,11 +753,15 @@ __device__ __forceinline__ void propagate_levels_q_body(const QuadParams &p, uin
             *reinterpret_cast<tt_u64x2 *>(ring + (slot & rmask) * RW + qd * 2) = val;     \
             if (a##i.w >= 0) dst = &p.dep[(size_t)a##i.w * W + gw];                       \
         }                                                                                 \
-        store_device_16(dst, val);                                                        \
+        if constexpr (STORED) {                                                           \
+            if (qd == 0) ops[(l & 1) * P + sub] = a##i.w;                                 \
+        } else {                                                                          \
+            store_device_16(dst, val);                                                    \
+        }                                                                                 \
         slot += (uint32_t)P;                                                              \
         asm volatile("" : "+v"(slot));   /* (else one register per unrolled level holds its slot) */ \
         KQ_LOAD(a##i, l + 8)                                                              \
-        asm volatile("s_waitcnt vmcnt(14)" ::: "memory");                                 \
+        if constexpr (!STORED) asm volatile("s_waitcnt vmcnt(14)" ::: "memory");          \
         lds_barrier();                                                                    \
     }
     for (int l0 = 0; l0 < L; l0 += 32) {
@@ -730,7 +788,19 @@ propagate_levels_q_batch(const QuadParams *__restrict__ ps, int blocks_per)
     const int v = (n & 7) == 0 ? (blockIdx.x & 7) * (n >> 3) + (blockIdx.x >> 3) : (int)blockIdx.x;
     const int g = v / blocks_per;
     const QuadParams p = ps[g];
-    propagate_levels_q_body<QC>(p, ring, v - g * blocks_per, 1);
+    propagate_levels_q_body<QC, false>(p, ring, v - g * blocks_per, 1);
+}
+
+template <int QC>
+__global__ void __launch_bounds__(256 * QC)
+propagate_levels_q_stored(const QuadParams *__restrict__ ps, int blocks_per)
+{
+    extern __shared__ uint64_t ring[];          // as above, then the ops of two levels
+    const int n = gridDim.x;
+    const int v = (n & 7) == 0 ? (blockIdx.x & 7) * (n >> 3) + (blockIdx.x >> 3) : (int)blockIdx.x;
+    const int g = v / blocks_per;
+    const QuadParams p = ps[g];
+    propagate_levels_q_body<QC, true>(p, ring, v - g * blocks_per, 1);
 }
 
 // rows that are copies: a recv's single bit, or the row of the node an op collapses onto.  `copied`: the ops
@@ -881,6 +951,8 @@ static bool quad_params(const Dag &d, int QC, QuadParams *q, size_t *lds)
         return false;
     q->n_levels = d.n_node_levels; q->W = d.W; q->P = d.k1_q_threads / 4; q->ring = d.k1_q_ring;
     q->qrecs = d.d_qrecs; q->lfovf = d.d_qfovf; q->dep = d.d_dep; q->sink = d.d_k1_q_sink;
+    const size_t bytes = (size_t)d.n * d.W * 8;
+    q->dep_bytes = bytes <= INT32_MAX ? (int32_t)bytes : 0;
     q->lfovf_lds = d.qfovf_len <= 4096 ? d.qfovf_len : 0;
     *lds = (size_t)(d.k1_q_ring + 2) * QC * 16 + (size_t)q->lfovf_lds * 4;
     return *lds <= 150 * 1024;
@@ -946,14 +1018,21 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     if (e != hipSuccess) return e;
     e = hipMemcpyAsync(d_ep, ep.data(), sizeof(ExpandParams) * G, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
-    if (lds0 > 48 * 1024) {
-        e = ensure_dynamic_lds(reinterpret_cast<const void *>(propagate_levels_q_batch<QC>), lds0);
-        if (e != hipSuccess) return e;
-    }
     const Dag &d0 = *ds[0];
     const int blocks_per = d0.W / (2 * QC);
-    hipLaunchKernelGGL(propagate_levels_q_batch<QC>, dim3(blocks_per * G), dim3(d0.k1_q_threads / 4 * QC), lds0, s, d_lp,
-                       blocks_per);
+    // two waves more, which store, where a workgroup has room for them (levels of 225 slots and more fill it with those that compute)
+    int threads = d0.k1_q_threads / 4 * QC;
+    const bool stored = lp[0].dep_bytes > 0 && threads >= kStoreThreads && threads + kStoreThreads <= 256 * QC;
+    if (stored) {
+        threads += kStoreThreads;
+        lds0 += (size_t)2 * d0.k1_q_threads / 4 * sizeof(int32_t);
+    }
+    void (*const kernel)(const QuadParams *, int) = stored ? propagate_levels_q_stored<QC> : propagate_levels_q_batch<QC>;
+    if (lds0 > 48 * 1024) {
+        e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernel), lds0);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(blocks_per * G), dim3(threads), lds0, s, d_lp, blocks_per);
     const size_t total = (size_t)most_copied * d0.W;
     if (total) hipLaunchKernelGGL(expand_rows_batch, dim3((unsigned)((total + 255) / 256), G), dim3(256), 0, s, d_ep);
     return hipGetLastError();

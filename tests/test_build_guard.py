@@ -43,6 +43,17 @@ def test_a_missing_load_between_two_waits_is_found(asm, key, n):
     assert any(key in x and "between two waits" in x for x in bad)
 
 
+@pytest.mark.parametrize("n", [6, 24, 42])
+def test_a_missing_store_of_the_waves_that_store_is_found(asm, n):
+    key = "25propagate_levels_q_storedILi4"
+    lo, hi = function_span(asm, key)
+    body = asm[lo:hi]
+    (w,) = hand_waits(body, n)
+    at = body.rindex("buffer_store_dwordx4", 0, w)
+    bad = b.check_counted_waits(asm[:lo] + body[:at] + "; " + body[at:] + asm[hi:])
+    assert any(key in x and f"before a wait for all but {n}" in x for x in bad)
+
+
 def test_a_spill_is_found(asm):
     lo, hi = function_span(asm, "22propagate_levels_batchILi4")
     body = asm[lo:hi]

@@ -77,3 +77,38 @@ def test_first_recompute_in_a_captured_graph(tt, name):  # noqa: F811
         if k == 1:
             h.recompute_deps()
     h.close()
+
+
+def lists_dag(levels, width, recvs):
+    """Layered, and every seventh op depends on ops of up to twelve levels before and on more of them than a record holds."""
+    rng = np.random.default_rng([levels, width])
+    b = wl._Builder()
+    rs = [b.recv(1e5) for _ in range(recvs)]
+    ops = []
+    for lv in range(levels):
+        for k in range(width):
+            pool = ops[max(0, (lv - (12 if k % 7 == 0 else 2)) * width):]
+            preds = [pool[i] for i in rng.choice(len(pool), size=min(len(pool), 9 if k % 7 == 0 else 2), replace=False)] if pool else []
+            if lv == 0 or k % 3 == 0:
+                preds.append(rs[int(rng.integers(recvs))])
+            ops.append(b.op(preds, 1e-3, "op"))
+    return b.finish("lists", seed=4, batch=8)
+
+
+# Slots per level of the kernel with 64-byte slices, a multiple of 32: up to 224 two more waves bring the rows to memory (one to seven per
+# thread and level), with 256 there is no room for them; levels just short of and beyond the 32 that are computed in a row.
+@pytest.mark.parametrize("levels,width", [(31, 32), (33, 64), (32, 96), (64, 100), (65, 150), (40, 190), (40, 224), (30, 225), (35, 250)])
+@pytest.mark.parametrize("kind", ["layered", "lists"])
+def test_several_graphs_by_one_launch(tt, levels, width, kind):  # noqa: F811
+    d = wide(levels, width, 1024) if kind == "layered" else lists_dag(levels, width, 1000)
+    want = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    hs = [tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids) for _ in range(9)]
+    for n in (2, 9):
+        for h in hs:
+            h.deps_view().fill_(-1)
+        print(f"[batch] {kind} {levels} x {width}: {n} handles", flush=True)
+        tt.recompute_deps_batch(hs[:n])
+        for h in hs[:n]:
+            assert np.array_equal(h.deps().cpu().numpy().view(np.uint64), want)
+    for h in hs:
+        h.close()
