@@ -611,8 +611,7 @@ propagate_levels_batch(const LevelParams *__restrict__ ps, int blocks_per)
 // the ring a copy node some levels later (see the build of the records), so a level still reads LDS only.
 // The records are 16 bytes (see internal.h): a level issues exactly one 16-byte load and one 16-byte store per thread.
 typedef unsigned long long tt_u64x2 __attribute__((ext_vector_type(2)));
-// (with less priority in the caches: 32 graphs of 400 x 240 layered ops, whose levels leave no room for waves that store, 573 -> 560 us)
-__device__ __forceinline__ void store_device_16(void *q, tt_u64x2 v) { __builtin_nontemporal_store(v, (__attribute__((address_space(1))) tt_u64x2 *)q); }
+__device__ __forceinline__ void store_device_16(void *q, tt_u64x2 v) { *(__attribute__((address_space(1))) tt_u64x2 *)q = v; }
 
 // words gw, gw + 1 of all inputs of a node that does not fit a record (see other_inputs)
 __device__ __noinline__ tt_u64x2 other_inputs_q(const int32_t *lfovf, const int32_t *fov, const uint64_t *ring,
@@ -651,14 +650,16 @@ struct QuadParams {
 
 // The rows of level l go to memory while level l + 1 is computed: by kStoreThreads threads, N stores each, of which those of levels up to
 // l - 6 have been completed when level l + 2 begins (a list reads a row from memory eight levels later or more).  They are written
-// through the caches (kThrough): the rows of 32 graphs are 1.7 GB, and lines that wait in the L2 to be pushed out by later ones
-// leave it at half the rate of a copy, whoever stores them and in whatever order.  stress, 32 graphs: 278 us without the stores; the computing
-// waves storing 541, two more waves 550, the latter contiguously 520; with less priority in the caches (nt) 460 and 446; nt and through
-// them 390 (sc1 alone 588).  With the copied rows 584 -> 427 us; 16 graphs 440 -> 330, 8 350 -> 318; 32 graphs of 500 x 100 469 -> 383, of
-// 500 x 30 and 1 024 recvs 178 -> 166.
+// through the caches (kThrough), up to kThroughMost bytes of rows of all graphs: rows that wait in the L2 to be pushed out by later ones hold up the
+// levels behind them.  Three sets of handles in turn, us, the computing waves storing and this: 2 to 8 graphs of stress (53 MB of rows each) 307 and 301,
+// 347 and 308; 9 to 11 369, 371, 393 and 309, 330, 346; 12 to 14 (640 to 746 MB) 390, 413, 412 and 393, 400, 430; 16 and 32 432, 568 and 477, 642; 32 graphs of 500 x 64
+// and 4 096 recvs (591 MB) 709 and 599, of 200 x 200 and 2 048 (360 MB) 196 and 155, of 500 x 30 and 1 024 187 and 169.  The separate waves without the
+// way through the caches give 1 to 4 %, or take 7 % (400 x 224, 32 graphs).  (One set of handles again and again 427 instead of 584 with 32 graphs: what
+// the pieces of 64 bytes find in the Infinity Cache then is not what a program finds.)
 typedef int tt_row16 __attribute__((ext_vector_type(4)));
 constexpr int kStoreThreads = 128;
 constexpr int kThrough = 18;                // sc1 (to memory at once) and nt
+constexpr size_t kThroughMost = (size_t)600 << 20;
 template <int QC, int N>
 __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t *ring, const int32_t *ops, int t, int gw)
 {
@@ -804,26 +805,36 @@ propagate_levels_q_stored(const QuadParams *__restrict__ ps, int blocks_per)
 }
 
 // rows that are copies: a recv's single bit, or the row of the node an op collapses onto.  `copied`: the ops
-// with such rows, as pairs (op, ~i for recv i or the op id of the node whose row it has).
-__device__ __forceinline__ void expand_word(int32_t n_copied, int32_t W, const int32_t *copied, uint64_t *dep, size_t idx)
+// with such rows, as pairs (op, ~i for recv i or the op id of the node whose row it has).  A thread takes two words where rows have an
+// even number of them (32 graphs of the stress configuration, 8 190 rows of 64 words each: a word 37 us, two 28), which lie in two words' alignment then.
+__host__ __device__ __forceinline__ size_t expand_threads(size_t n_copied, int32_t W) { return n_copied * (W % 2 == 0 ? W / 2 : W); }
+__device__ __forceinline__ void expand_words(int32_t n_copied, int32_t W, const int32_t *copied, uint64_t *dep, size_t idx)
 {
-    if (idx >= (size_t)n_copied * W) return;
-    const int e = (int)(idx / W), w = (int)(idx % W);
+    if (idx >= expand_threads(n_copied, W)) return;
+    const int n = W % 2 == 0 ? 2 : 1, per_row = W / n;
+    const int e = (int)(idx / per_row), w = (int)(idx % per_row) * n;
     const int v = load_device_4(copied + 2 * e), s = load_device_4(copied + 2 * e + 1);
-    uint64_t val;
-    if (s < 0) {
-        const int i = ~s;
-        val = (i >> 6) == w ? 1ull << (i & 63) : 0ull;
+    const uint64_t *const from = dep + (size_t)s * W + w;
+    uint64_t *const to = dep + (size_t)v * W + w;
+    const uint64_t bit = 1ull << (~s & 63);         // (s < 0: of recv ~s)
+    const int word = ~s >> 6;
+    if (n == 2) {
+        tt_u64x2 val = {word == w ? bit : 0ull, word == w + 1 ? bit : 0ull};
+        if (s >= 0) {
+            const int4 q = load_device_16(from);
+            val.x = (uint64_t)(uint32_t)q.y << 32 | (uint32_t)q.x;
+            val.y = (uint64_t)(uint32_t)q.w << 32 | (uint32_t)q.z;
+        }
+        *(__attribute__((address_space(1))) tt_u64x2 *)to = val;
     } else {
-        val = load_device_8(dep + (size_t)s * W + w);
+        store_device_8(to, s < 0 ? (word == w ? bit : 0ull) : load_device_8(from));
     }
-    store_device_8(dep + (size_t)v * W + w, val);
 }
 
 __global__ void __launch_bounds__(256)
 expand_rows(int32_t n_copied, int32_t W, const int32_t *__restrict__ copied, uint64_t *dep)
 {
-    expand_word(n_copied, W, copied, dep, (size_t)blockIdx.x * blockDim.x + threadIdx.x);
+    expand_words(n_copied, W, copied, dep, (size_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // the same for several graphs: blockIdx.y = graph
@@ -836,7 +847,7 @@ __global__ void __launch_bounds__(256)
 expand_rows_batch(const ExpandParams *__restrict__ ps)
 {
     const ExpandParams p = ps[blockIdx.y];
-    expand_word(p.n_copied, p.W, p.copied, p.dep, (size_t)blockIdx.x * blockDim.x + threadIdx.x);
+    expand_words(p.n_copied, p.W, p.copied, p.dep, (size_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // The level-major records, a thread per slot and per node: a slot without a node gets a record without one.  A node whose
@@ -990,7 +1001,7 @@ static hipError_t launch_levels_batch(Dag *const *ds, int G, void *staging, hipS
     const Dag &d0 = *ds[0];
     const int blocks_per = (d0.W + WC - 1) / WC;
     hipLaunchKernelGGL(propagate_levels_batch<WC>, dim3(blocks_per * G), dim3(d0.k1_threads), lds0, s, d_lp, blocks_per);
-    const size_t total = (size_t)most_copied * d0.W;
+    const size_t total = expand_threads(most_copied, d0.W);
     if (total) hipLaunchKernelGGL(expand_rows_batch, dim3((unsigned)((total + 255) / 256), G), dim3(256), 0, s, d_ep);
     return hipGetLastError();
 }
@@ -1022,7 +1033,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     const int blocks_per = d0.W / (2 * QC);
     // two waves more, which store, where a workgroup has room for them (levels of 225 slots and more fill it with those that compute)
     int threads = d0.k1_q_threads / 4 * QC;
-    const bool stored = lp[0].dep_bytes > 0 && threads >= kStoreThreads && threads + kStoreThreads <= 256 * QC;
+    const bool stored = lp[0].dep_bytes > 0 && (size_t)lp[0].dep_bytes * G <= kThroughMost && threads >= kStoreThreads && threads + kStoreThreads <= 256 * QC;
     if (stored) {
         threads += kStoreThreads;
         lds0 += (size_t)2 * d0.k1_q_threads / 4 * sizeof(int32_t);
@@ -1033,7 +1044,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kernel, dim3(blocks_per * G), dim3(threads), lds0, s, d_lp, blocks_per);
-    const size_t total = (size_t)most_copied * d0.W;
+    const size_t total = expand_threads(most_copied, d0.W);
     if (total) hipLaunchKernelGGL(expand_rows_batch, dim3((unsigned)((total + 255) / 256), G), dim3(256), 0, s, d_ep);
     return hipGetLastError();
 }
@@ -1121,7 +1132,7 @@ hipError_t launch_propagate(const Dag &d, hipStream_t s)
         else e = launch_nodes<4>(d, s);
         if (e != hipSuccess) return e;
     }
-    const size_t total = (size_t)d.n_copied * d.W;
+    const size_t total = expand_threads(d.n_copied, d.W);
     if (total)
         hipLaunchKernelGGL(expand_rows, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, d.n_copied, d.W, d.d_copied, d.d_dep);
     return hipGetLastError();
