@@ -232,6 +232,7 @@ struct Packer {
     std::vector<Part> parts;
     size_t host_bytes = 0, device_only = 0;     // the copied arrays come first
     size_t alignment = 256;                     // of what comes behind them
+    bool by_kernel = true;                      // (false: not by a kernel, for which a busy device may have no room)
     Stage staging;
     hipStream_t stream = nullptr;
     bool under_way = false;
@@ -291,7 +292,7 @@ struct Packer {
         if (host_bytes) {
             under_way = true;
             // (small blocks: a kernel reads the pinned memory itself)
-            if (pageable.empty() && host_bytes <= kCopyInMax) {
+            if (by_kernel && pageable.empty() && host_bytes <= kCopyInMax) {
                 e = launch_copy_in(block.p, st, host_bytes, s);
             } else {
                 e = hipMemcpyAsync(block.p, st, host_bytes, hipMemcpyHostToDevice, s);
@@ -404,7 +405,7 @@ static void free_dag(Dag *d)
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     const Block blocks[] = {
         d->graph_block, d->quad_block, d->class_block, {d->d_work, d->work_bytes}, {d->d_chan, (size_t)d->R * sizeof(int32_t)},
-        d->send_block, d->chain.block, d->sliced_block, d->frontier.block};
+        d->send_block, d->chain.block, d->chain.cols_block, d->sliced_block, d->frontier.block};
     for (const auto &b : blocks) {
         if (!b.p) continue;
         if (idle) pool_put(b.p, b.bytes, d->device);
@@ -1687,74 +1688,130 @@ hipError_t ensure_large_tables(Dag *d, bool frontier)
     return e != hipSuccess || ef == hipErrorOutOfMemory ? e : ef;
 }
 
+struct ChainUpload {
+    const ChainPlan &p;
+    ChainRec *rec = nullptr;
+    ChainGate *gate = nullptr;
+
+    explicit ChainUpload(const ChainPlan &plan) : p(plan) {}
+    void add(Packer &t, ChainTables &c)
+    {
+        static_assert(sizeof(ChainRec) == 16 && sizeof(ChainGate) == 16, "records are read as 16 bytes");
+        t.add(&rec, p.rec);
+        t.add(&gate, p.gate);
+        t.add(&c.d_list, p.list);
+        t.add(&c.d_place, p.place);
+        t.add(&c.d_extra, p.extra);
+        t.add(&c.d_head, p.head);
+        t.add(&c.d_cand_ptr, p.cand_ptr);
+        t.add(&c.d_cand, p.cand);
+    }
+    void done(ChainTables &c) const         // (they are on the device)
+    {
+        c.d_rec = reinterpret_cast<int4 *>(rec);
+        c.d_gate = reinterpret_cast<int4 *>(gate);
+        c.n_chains = p.n_slots; c.n_gates = (int32_t)p.gate.size();
+        c.start = p.start; c.n_start = p.n_start; c.empty = p.empty;
+        c.second_gates = p.second_gates; c.n_extra = p.n_extra; c.n_head = (int32_t)p.head.size();
+        c.ok = c.made = true;
+    }
+};
+
+// The tables of class_totals_kernel first, for which a call launches it; those of tac_chain_kernel (ensure_chain_tables) are made while it
+// runs, so that the device waits 45 us less at the first call on inception3 (5 912 ops, all of it 95 us) and 12 on resnet50 (1 260).  Of small
+// graphs (vgg16, 90 ops) all tables are made at once: a second copy and its wait take 6 us more than there is to plan.
+// (hipErrorNotSupported: the graph has not the form, as far as is known)
+constexpr int64_t kChainAtOnce = 1000;      // ops and predecessors
+hipError_t ensure_chain_columns(Dag *d)
+try {
+    std::lock_guard<std::mutex> lock(d->tables_mutex);
+    ChainTables &c = d->chain;
+    if (c.made) return c.ok ? hipSuccess : hipErrorNotSupported;
+    if (c.cols_made) return hipSuccess;
+    const size_t W = (size_t)d->W;
+    auto sets = std::make_shared<ChainSets>();
+    ChainColumns p;
+    // pieces of one set (classes with equal rows) are one set again: they follow each other
+    std::vector<int32_t> set_of_cls(d->C), set_of_col(d->N), set_of_op(d->n, 0);
+    bool may_be = !d->h_cls_dep.empty();
+    for (int32_t k = 0; k < d->C && may_be; ++k) {
+        const uint64_t *row = &d->h_cls_dep[k * W];
+        if (sets->rows.empty() || memcmp(sets->rows.back(), row, W * 8) != 0) {
+            sets->rows.push_back(row);
+            sets->row_of_set.push_back(k);
+        }
+        set_of_cls[k] = (int32_t)sets->rows.size() - 1;
+    }
+    may_be = may_be && chain_may_be(d->R, (int)sets->rows.size());
+    if (may_be) {
+        for (int32_t r : d->h_recv_ids) set_of_op[r] = -1;
+        for (int32_t v = 0, j = 0; v < d->n; ++v)
+            if (set_of_op[v] >= 0) {
+                set_of_op[v] = set_of_col[j] = set_of_cls[d->h_col_cls[j]];
+                ++j;
+            }
+        may_be = chain_owners(d->R, d->W, d->n, d->h_row_ptr.data(), d->h_col_idx.data(), set_of_op.data(), *sets) &&
+                 make_chain_columns(d->N, (int)sets->rows.size(), set_of_col.data(), p);
+    }
+    if (!may_be) {
+        c.made = true;
+        return hipErrorNotSupported;
+    }
+    const bool at_once = (int64_t)d->n + d->E <= kChainAtOnce;
+    ChainPlan plan;
+    if (at_once) {
+        make_chain_plan(d->R, d->W, *sets, p.first, plan);
+        if (!plan.ok) {
+            c.made = true;
+            return hipErrorNotSupported;
+        }
+    }
+    ChainUpload up(plan);
+    Packer t;
+    t.add(&c.d_several, p.several);
+    t.add(&c.d_flush, p.flush);
+    t.add(&c.d_flush_row, p.flush_row);
+    t.add(&c.d_block_first, p.block_first);
+    if (at_once) up.add(t, c);
+    hipStream_t s;
+    hipError_t e = table_stream(d->device, &s);
+    if (e == hipSuccess) e = t.commit(c.cols_block, d->device, s);
+    if (e == hipSuccess) e = t.finish();
+    if (e != hipSuccess) return e;
+    c.first_total = std::move(p.first);
+    c.n_totals = c.first_total.back(); c.n_several = (int32_t)p.several.size(); c.n_pairs = p.n_pairs;
+    c.cols_made = true;
+    if (at_once) up.done(c);
+    else c.sets = std::move(sets);
+    return hipSuccess;
+} catch (const std::bad_alloc &) {
+    return hipErrorOutOfMemory;
+}
+
+// (after ensure_chain_columns; hipErrorNotSupported: the graph has not the form)
 hipError_t ensure_chain_tables(Dag *d)
 try {
     std::lock_guard<std::mutex> lock(d->tables_mutex);
     ChainTables &c = d->chain;
-    if (c.made) return hipSuccess;
-    const int32_t n = d->n, N = d->N, R = d->R, W = d->W;
-    if (d->h_cls_dep.empty() || R < 1) {
-        c.made = true;
-        return hipSuccess;
-    }
-    // pieces of one set (classes with equal rows) are one set again: they follow each other
-    std::vector<const uint64_t *> rows;
-    std::vector<int32_t> row_of_set, set_of_cls(d->C), set_of_col(N);
-    for (int32_t k = 0; k < d->C; ++k) {
-        const uint64_t *row = &d->h_cls_dep[(size_t)k * W];
-        if (rows.empty() || memcmp(rows.back(), row, (size_t)W * 8) != 0) {
-            rows.push_back(row);
-            row_of_set.push_back(k);
-        }
-        set_of_cls[k] = (int32_t)rows.size() - 1;
-    }
-    for (int32_t j = 0; j < N; ++j) set_of_col[j] = set_of_cls[d->h_col_cls[j]];
-    std::vector<int32_t> recv_of_op(n, -1), col_of_op(n, -1), in_ptr(1, 0), in;
-    for (int32_t i = 0; i < R; ++i) recv_of_op[d->h_recv_ids[i]] = i;
-    for (int32_t v = 0, j = 0; v < n; ++v)
-        if (recv_of_op[v] < 0) col_of_op[v] = j++;
-    in.reserve(d->E);
-    for (int32_t v = 0; v < n; ++v) {
-        if (recv_of_op[v] >= 0) continue;
-        for (int32_t e = d->h_row_ptr[v]; e < d->h_row_ptr[v + 1]; ++e) {
-            const int32_t u = d->h_col_idx[e];
-            in.push_back(recv_of_op[u] >= 0 ? ~recv_of_op[u] : col_of_op[u]);
-        }
-        in_ptr.push_back((int32_t)in.size());
-    }
+    if (c.made) return c.ok ? hipSuccess : hipErrorNotSupported;
     ChainPlan p;
-    make_chain_plan(R, W, N, (int)rows.size(), rows.data(), row_of_set.data(), set_of_col.data(), in_ptr, in, set_of_col, p);
+    make_chain_plan(d->R, d->W, *c.sets, c.first_total, p);
     if (!p.ok) {
         c.made = true;
-        return hipSuccess;
+        c.sets.reset();
+        return hipErrorNotSupported;
     }
-    static_assert(sizeof(ChainRec) == 16 && sizeof(ChainGate) == 16, "records are read as 16 bytes");
+    ChainUpload up(p);
     Packer t;
-    ChainRec *rec = nullptr;
-    ChainGate *gate = nullptr;
-    t.add(&rec, p.rec);
-    t.add(&gate, p.gate);
-    t.add(&c.d_list, p.list);
-    t.add(&c.d_place, p.place);
-    t.add(&c.d_extra, p.extra);
-    t.add(&c.d_several, p.several);
-    t.add(&c.d_head, p.head);
-    t.add(&c.d_cand_ptr, p.cand_ptr);
-    t.add(&c.d_cand, p.cand);
-    t.add(&c.d_flush, p.flush);
-    t.add(&c.d_flush_row, p.flush_row);
-    t.add(&c.d_block_first, p.block_first);
+    t.by_kernel = false;                    // (class_totals_kernel runs meanwhile)
+    up.add(t, c);
     hipStream_t s;
     hipError_t e = table_stream(d->device, &s);
     if (e == hipSuccess) e = t.commit(c.block, d->device, s);
     if (e == hipSuccess) e = t.finish();
-    if (e != hipSuccess) return e;
-    c.d_rec = reinterpret_cast<int4 *>(rec);
-    c.d_gate = reinterpret_cast<int4 *>(gate);
-    c.n_chains = p.n_slots; c.n_totals = p.n_totals; c.n_gates = (int32_t)p.gate.size();
-    c.start = p.start; c.n_start = p.n_start; c.n_several = (int32_t)p.several.size(); c.empty = p.empty;
-    c.second_gates = p.second_gates; c.n_extra = p.n_extra; c.n_pairs = p.n_pairs; c.n_head = (int32_t)p.head.size();
-    c.ok = c.made = true;
+    if (e != hipSuccess) return e;          // (the next call plans again)
+    up.done(c);
+    c.sets.reset();
     return hipSuccess;
 } catch (const std::bad_alloc &) {
     return hipErrorOutOfMemory;

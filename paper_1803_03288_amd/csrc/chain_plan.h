@@ -43,10 +43,21 @@ struct ChainGate {                      // 16 bytes
     int16_t unused[3];
 };
 
+// The class totals: one row per run of consecutive columns of a set inside a block; the rows of a set are consecutive.
+struct ChainColumns {
+    std::vector<int32_t> first;         // [D + 1] the first row of every set
+    // totals in more than one row, as first row | number of rows << 16: first those in two rows (n_pairs of them)
+    std::vector<int32_t> several;
+    int n_pairs = 0;
+    // op_time columns, block by block of kChainBlock: a bit per column after which a row of the totals is complete
+    // (sixteen columns per word), those rows in that order, and where a block starts among them
+    std::vector<uint32_t> flush;
+    std::vector<int32_t> flush_row, block_first;
+};
+
 struct ChainPlan {
     bool ok = false;
     int n_slots = 0;                    // chains
-    int n_totals = 0;                   // rows of class totals; a set with several runs of columns has as many, consecutive
     int32_t empty = -1;                 // total of the ops that depend on no recv
     std::vector<ChainRec> rec;          // [R]
     std::vector<ChainGate> gate;
@@ -57,71 +68,120 @@ struct ChainPlan {
     std::vector<int16_t> extra;         // [R] 1-based number among the recvs with a list, 0 for the others
     int n_extra = 0;
     bool second_gates = false;          // some recv is a sink of two gates
-    // totals in more than one row, as first row | number of rows << 16: first those in two rows (n_pairs of them)
-    std::vector<int32_t> several;
-    int n_pairs = 0;
     // classes that can attain M+ of a ready recv r: cand[cand_ptr[r] .. cand_ptr[r + 1]), as rows of cls_dep
     std::vector<int32_t> cand_ptr, cand;
-    // op_time columns, block by block of kChainBlock: a bit per column after which a row of the totals is complete
-    // (sixteen columns per word), those rows in that order, and where a block starts among them
-    std::vector<uint32_t> flush;
-    std::vector<int32_t> flush_row, block_first;
 };
 
-// rows [D][W]: the distinct dep sets of the compute ops, in order of first member;  set_of_col [N];  row_of_set [D]: a
-// row of cls_dep that holds the set.
-// nodes: inputs of node k in node_in[node_in_ptr[k] .. node_in_ptr[k + 1]) (~i for recv i, else a node), node_set[k]: the
-// set its op belongs to.
-inline void make_chain_plan(int R, int W, int N, int D, const uint64_t *const *rows, const int32_t *row_of_set,
-                            const int32_t *set_of_col, const std::vector<int32_t> &node_in_ptr,
-                            const std::vector<int32_t> &node_in, const std::vector<int32_t> &node_set, ChainPlan &p)
+// Whether as many sets may have the form.
+inline bool chain_may_be(int R, int D) { return R >= 1 && R <= 512 && D >= R && D <= R + kChainMaxGates + 1; }
+
+// set_of_col [N]; false: more rows than a record can name
+inline bool make_chain_columns(int N, int D, const int32_t *set_of_col, ChainColumns &c)
 {
-    p.ok = false;
-    if (R < 1 || R > 512 || D < R || D > R + kChainMaxGates + 1) return;
+    const int n_blocks = (N + kChainBlock - 1) / kChainBlock;
+    std::vector<int32_t> &at = c.first;
+    at.assign(D + 1, 0);
+    for (int j = 0; j < N; ++j)
+        if (j + 1 == N || set_of_col[j + 1] != set_of_col[j] || (j + 1) % kChainBlock == 0) ++at[set_of_col[j] + 1];
+    c.several.clear();
+    c.n_pairs = 0;
+    for (int k = 0; k < D; ++k) {
+        const int n = at[k + 1];
+        at[k + 1] += at[k];
+        if (n > 1) c.several.push_back(at[k] | n << 16);
+        c.n_pairs += n == 2;
+        if (at[k + 1] > 32767) return false;
+    }
+    std::stable_partition(c.several.begin(), c.several.end(), [](int32_t v) { return v >> 16 == 2; });
+    c.flush.assign((size_t)n_blocks * (kChainBlock / 16), 0);
+    c.flush_row.clear();
+    c.block_first.assign(1, 0);
+    std::vector<int32_t> fill(at.begin(), at.end() - 1);
+    for (int j = 0; j < N; ++j) {
+        if (j + 1 == N || set_of_col[j + 1] != set_of_col[j] || (j + 1) % kChainBlock == 0) {
+            c.flush[j / 16] |= 1u << (j % 16);
+            c.flush_row.push_back(fill[set_of_col[j]]++);
+        }
+        if (j + 1 == N || (j + 1) % kChainBlock == 0) c.block_first.push_back((int32_t)c.flush_row.size());
+    }
+    return true;
+}
+
+// The distinct dep sets of the compute ops, in order of first member, and what they inherit.
+struct ChainSets {
+    std::vector<const uint64_t *> rows; // [D][W]
+    std::vector<int32_t> row_of_set;    // [D] a row of cls_dep that holds the set
+    std::vector<uint64_t> U;            // [D][W] the union of the sets of the predecessors
+    std::vector<int32_t> par_ptr, par;  // their sets
+    std::vector<int32_t> own, owner;    // [D] the recv that a set adds, [R] the set that adds a recv
+    std::vector<int32_t> count;         // [D] recvs of a set
+    int empty_set = -1;
+};
+
+// Whether every recv is added by one set, by itself; without that the graph has not the form.  s.rows and s.row_of_set are given;
+// set_of_op [n]: the set of an op, -1 for a recv;  predecessors of op v: col_idx[row_ptr[v] .. row_ptr[v + 1]).
+inline bool chain_owners(int R, int W, int n, const int32_t *row_ptr, const int32_t *col_idx, const int32_t *set_of_op, ChainSets &s)
+{
+    const int D = (int)s.rows.size();
+    if (!chain_may_be(R, D)) return false;
     const size_t w8 = (size_t)W;
-    std::vector<uint64_t> U((size_t)D * w8, 0);
     std::vector<int32_t> edge_from, edge_into, last(D, -1);
-    for (size_t k = 0; k < node_set.size(); ++k) {
-        const int c = node_set[k];
-        for (int32_t e = node_in_ptr[k]; e < node_in_ptr[k + 1]; ++e) {
-            const int32_t x = node_in[e];
-            if (x < 0) continue;
-            const int u = node_set[x];
-            if (u == c || last[u] == c) continue;       // (nodes of one set tend to follow each other)
+    s.U.assign((size_t)D * w8, 0);
+    for (int v = 0; v < n; ++v) {
+        const int c = set_of_op[v];
+        if (c < 0) continue;
+        for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) {
+            const int u = set_of_op[col_idx[e]];
+            if (u < 0 || u == c || last[u] == c) continue;      // (ops of one set tend to follow each other)
             last[u] = c;
-            for (int w = 0; w < W; ++w) U[c * w8 + w] |= rows[u][w];
+            for (int w = 0; w < W; ++w) s.U[c * w8 + w] |= s.rows[u][w];
             edge_from.push_back(u);
             edge_into.push_back(c);
         }
     }
-    std::vector<int32_t> par_ptr(D + 1, 0), par(edge_from.size());
-    for (int32_t c : edge_into) ++par_ptr[c + 1];
-    for (int c = 0; c < D; ++c) par_ptr[c + 1] += par_ptr[c];
+    s.par_ptr.assign(D + 1, 0);
+    s.par.resize(edge_from.size());
+    for (int32_t c : edge_into) ++s.par_ptr[c + 1];
+    for (int c = 0; c < D; ++c) s.par_ptr[c + 1] += s.par_ptr[c];
     {
-        std::vector<int32_t> fill(par_ptr.begin(), par_ptr.end() - 1);
-        for (size_t e = 0; e < edge_from.size(); ++e) par[fill[edge_into[e]]++] = edge_from[e];
+        std::vector<int32_t> fill(s.par_ptr.begin(), s.par_ptr.end() - 1);
+        for (size_t e = 0; e < edge_from.size(); ++e) s.par[fill[edge_into[e]]++] = edge_from[e];
     }
     // owners and joins
-    std::vector<int32_t> own(D, -1), owner(R, -1), count(D, 0);
-    int empty_set = -1;
+    s.own.assign(D, -1);
+    s.owner.assign(R, -1);
+    s.count.assign(D, 0);
+    s.empty_set = -1;
     for (int c = 0; c < D; ++c) {
         int fresh = 0, r = -1;
         for (int w = 0; w < W; ++w) {
-            count[c] += __builtin_popcountll(rows[c][w]);
-            const uint64_t x = rows[c][w] & ~U[c * w8 + w];
+            s.count[c] += __builtin_popcountll(s.rows[c][w]);
+            const uint64_t x = s.rows[c][w] & ~s.U[c * w8 + w];
             fresh += __builtin_popcountll(x);
             if (x) r = w * 64 + __builtin_ctzll(x);
         }
-        if (count[c] == 0) { empty_set = c; continue; }
-        if (fresh > 1) return;
+        if (s.count[c] == 0) { s.empty_set = c; continue; }
+        if (fresh > 1) return false;
         if (fresh == 1) {
-            if (owner[r] >= 0) return;
-            owner[r] = c;
-            own[c] = r;
+            if (s.owner[r] >= 0) return false;
+            s.owner[r] = c;
+            s.own[c] = r;
         }
     }
     for (int r = 0; r < R; ++r)
-        if (owner[r] < 0) return;
+        if (s.owner[r] < 0) return false;
+    return true;
+}
+
+// s: after chain_owners;  at [D + 1]: the first row of totals of every set
+inline void make_chain_plan(int R, int W, const ChainSets &sets, const std::vector<int32_t> &at, ChainPlan &p)
+{
+    p.ok = false;
+    const int D = (int)sets.rows.size(), empty_set = sets.empty_set;
+    const size_t w8 = (size_t)W;
+    const std::vector<uint64_t> &U = sets.U;
+    const std::vector<int32_t> &par_ptr = sets.par_ptr, &par = sets.par, &own = sets.own, &owner = sets.owner, &count = sets.count;
+    const std::vector<int32_t> &row_of_set = sets.row_of_set;
     // sinks, smaller sets first
     std::vector<int32_t> by_count(D);
     for (int c = 0; c < D; ++c) by_count[c] = c;
@@ -252,22 +312,6 @@ inline void make_chain_plan(int R, int W, int N, int D, const uint64_t *const *r
             }
         p.cand_ptr.push_back((int32_t)p.cand.size());
     }
-    // class totals: one row per run of consecutive columns of a set inside a block; the rows of a set are consecutive
-    const int n_blocks = (N + kChainBlock - 1) / kChainBlock;
-    std::vector<int32_t> at(D + 1, 0);
-    for (int j = 0; j < N; ++j)
-        if (j + 1 == N || set_of_col[j + 1] != set_of_col[j] || (j + 1) % kChainBlock == 0) ++at[set_of_col[j] + 1];
-    p.several.clear();
-    p.n_pairs = 0;
-    for (int c = 0; c < D; ++c) {
-        const int n = at[c + 1];
-        at[c + 1] += at[c];
-        if (n > 1) p.several.push_back(at[c] | n << 16);
-        p.n_pairs += n == 2;
-        if (at[c + 1] > 32767) return;
-    }
-    std::stable_partition(p.several.begin(), p.several.end(), [](int32_t v) { return v >> 16 == 2; });
-    p.n_totals = at[D];
     p.head.clear();
     for (int r = 0; r < R; ++r) {
         p.rec[r].total = (int16_t)at[owner[r]];
@@ -275,17 +319,6 @@ inline void make_chain_plan(int R, int W, int N, int D, const uint64_t *const *r
     }
     for (size_t g = 0; g < p.gate.size(); ++g) p.gate[g].join = (int16_t)(gate_join[g] >= 0 ? at[gate_join[g]] : -1);
     p.empty = empty_set >= 0 ? at[empty_set] : -1;
-    p.flush.assign((size_t)n_blocks * (kChainBlock / 16), 0);
-    p.flush_row.clear();
-    p.block_first.assign(1, 0);
-    std::vector<int32_t> fill(at.begin(), at.end() - 1);
-    for (int j = 0; j < N; ++j) {
-        if (j + 1 == N || set_of_col[j + 1] != set_of_col[j] || (j + 1) % kChainBlock == 0) {
-            p.flush[j / 16] |= 1u << (j % 16);
-            p.flush_row.push_back(fill[set_of_col[j]]++);
-        }
-        if (j + 1 == N || (j + 1) % kChainBlock == 0) p.block_first.push_back((int32_t)p.flush_row.size());
-    }
     p.ok = true;
 }
 

@@ -434,8 +434,8 @@ hipError_t launch_tac(Dag &d, const TacArgs &a, hipStream_t s)
         // (where there is no memory for its tables or for enough samples at once, the kernels below take the call; also on a
         // stream that is being captured, where tables cannot be made)
         int32_t *flags = nullptr;
-        hipError_t e = !d.chain.made && being_captured(s) ? hipErrorNotSupported : ensure_chain_tables(&d);
-        if (e == hipSuccess) e = d.chain.ok ? launch_tac_chain(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s) : hipErrorNotSupported;
+        hipError_t e = !d.chain.made && being_captured(s) ? hipErrorNotSupported : ensure_chain_columns(&d);
+        if (e == hipSuccess) e = launch_tac_chain(d, a, flag_bytes, flag_bytes + gstate_bytes, &flags, s);
         if (e == hipSuccess) p.only_flagged = flags;
         else if (e != hipErrorNotSupported && e != hipErrorOutOfMemory) return e;
     }

@@ -550,7 +550,7 @@ constexpr size_t kTotalsCached = (size_t)432 << 20;
 hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t at_least, int32_t **flags_out, hipStream_t s)
 {
     const ChainTables &c = d.chain;
-    if (!c.ok || a.sel_P || a.sel_Mplus) return hipErrorNotSupported;
+    if (a.sel_P || a.sel_Mplus) return hipErrorNotSupported;
     const size_t per_sample = ((size_t)c.n_totals + d.R) * 8;
     size_t chunk = std::min((size_t)a.B, kChainChunkBytes / per_sample);
     chunk = (chunk + 63) & ~(size_t)63;
@@ -562,7 +562,6 @@ hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t 
     }
     if (e != hipSuccess) return e;
     int32_t *flags = static_cast<int32_t *>(d.d_work);
-    *flags_out = flags;
     double *totals = reinterpret_cast<double *>(static_cast<char *>(d.d_work) + flag_bytes);
     const size_t elem = a.f32 ? 4 : 8;
     const int n_cu = device_cu_count(d.device);
@@ -589,6 +588,10 @@ hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t 
         hipLaunchKernelGGL(kernel, grid, dim3(64), 0, s, t);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
+        // (at a handle's first call the chains are planned while the first totals are formed; where it turns out that there are more than
+        // eight, or that branches join otherwise, those were in vain)
+        if (b0 == 0) e = ensure_chain_tables(&d);
+        if (e != hipSuccess) return e;
         ChainParams p{};
         p.B = nb; p.R = d.R; p.W = d.W; p.Bp = chunk;
         p.n_gates = c.n_gates; p.start = c.start; p.n_start = c.n_start;
@@ -612,6 +615,7 @@ hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t 
         else e = c.second_gates ? launch_chain_nc<8, true>(p, s) : launch_chain_nc<8, false>(p, s);
         if (e != hipSuccess) return e;
     }
+    *flags_out = flags;
     return hipSuccess;
 }
 

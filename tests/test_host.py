@@ -120,6 +120,35 @@ def test_no_exception_leaves_an_entry_point(lib, name):
             lib.free(h)
 
 
+def test_chains_planned_beside_the_class_totals(lib):
+    """The tables of the chain form of a graph of more than a thousand ops and predecessors are made in two parts, the second while the
+    class totals are formed: whichever allocation fails, of the device's memory or the host's, the call is taken all the same, or says so, and the
+    next one is what it is on a fresh handle."""
+    d = wl.chain_dag(400)
+    rc, h = lib.build(d)
+    lib.host_forget_launches()
+    assert lib.tac(h, d, 8192) == 0
+    want = [k for k in lib.kernels() if "copy_in" not in k]
+    assert ["class_totals" in want[0], "tac_chain" in want[1]] == [True, True], want
+    lib.free(h)
+    for fail, left in ((lib.host_fail_device, lib.host_fail_device_left), (lib.host_fail_new, lib.host_fail_new_left)):
+        for k in range(4000):
+            rc, h = lib.build(d)
+            assert lib.tictac_trim_memory() == 0
+            fail(k)
+            rc = lib.tac(h, d, 8192)
+            struck = left() < 0
+            fail(-1)
+            assert rc in (0, -8) and lib.hipGetLastError() == 0, (k, rc, lib.error())
+            for _ in range(2):
+                lib.host_forget_launches()
+                assert lib.tac(h, d, 8192) == 0, lib.error()
+                assert [x for x in lib.kernels() if "copy_in" not in x] == want, (k, lib.kernels())
+            lib.free(h)
+            if not struck:
+                break
+
+
 @pytest.mark.parametrize("name", list(GRAPHS) + ["sends"])
 def test_a_failed_allocation_leaves_nothing_behind(lib, name):
     """Every allocation of device memory that a call makes fails once, one after the other, and so does every one of host
