@@ -243,7 +243,8 @@ tac_reg_kernel(const TacRegParams p)
         // subtractions of the rounds since m_sync, in their order.  ordl holds those rounds.
         // With many class slots it is formed from the outstanding recvs of the row, eight at a time: one lookup in a table of the
         // 256 sums of their subsets (lane l has those of bits 0..5 of its number), and formed again when more rounds have
-        // passed than that costs (about 42 + 3 KT instructions per eight recvs, 5 KT + 6 per round).  It is looked at in 21 of
+        // passed than that costs (about 42 + 3 KT instructions per eight recvs, 5 KT + 6 per round).  Eights of which none is left are passed over
+        // where registers allow (one sample 273 -> 262 us, 1 024 samples 311 -> 293; with sixteen waves, which spill, 471 -> 473).  It is looked at in 21 of
         // the 203 rounds of 61 x 23 layered ops and in 163 of 500 with 50 x 20.
 #define TT_M_WORD(k) uint32_t w_##k = 0; if constexpr (k < KT) { w_##k = wr[k]; }
 #define TT_M_ADD(k)                                                                       \
@@ -264,6 +265,8 @@ tac_reg_kernel(const TacRegParams p)
                 TT_EACH_K(TT_M_ALIVE)                                                     \
                 _Pragma("unroll 1")                                                       \
                 for (int j = 0; j < 4; ++j) {                                             \
+                    /* (all eight transferred) */                                         \
+                    if (WAVES < kRegWavesMax && (__builtin_amdgcn_readfirstlane((int)alive_) >> (8 * j) & 255) == 0) continue; \
                     double s_ = 0.0;                                                      \
                     _Pragma("unroll")                                                     \
                     for (int i = 0; i < 6; ++i) {                                         \
