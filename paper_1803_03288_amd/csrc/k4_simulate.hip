@@ -525,11 +525,14 @@ struct SimChanParams {
 // neighbours have rows of similar length.  (More than two runs per row on average; resnet50, less than one, four channels: 257 us
 // with consecutive classes, 343 without; 24 x 20 layered ops, 300 recvs, all run by run: 6.9 and 6.2 ms.)
 // The order is checked on the way.  65 536 samples, four channels, with the check: inception3 1 188 -> 1 000 us (a scan per channel
-// and 64 positions before, 26 % more vector instructions), resnet50 357 -> 257 us.  Waves wait for the op_time row two thirds of
-// their time; the registers (an occupancy bound per KT: where spills of a few words cost less than a wave) and LDS, which holds
-// everything but the arrivals in one place, say how many there are.
+// and 64 positions before, 26 % more vector instructions), resnet50 357 -> 257 us.  Waves wait for the op_time row most of
+// their time, so what counts is how many there are: the registers (an occupancy bound per KT) and LDS, which holds
+// everything but the arrivals in one place, say so.  The first two runs of every class are in LDS, the same for all waves: kept in registers over all samples they
+// and what the compiler formed from them ahead of the loop took 45 of 168 and spilled 17 more (seven class slots), and four waves per SIMD
+// are possible without them instead of three: inception3, 65 536 samples, one, four and sixteen channels 787 -> 664, 930 -> 732, 1 467 -> 1 113 us; 1 000
+// samples 48 -> 40; resnet50 242 -> 224; 22 x 20 layered ops, 380 recvs 1 233 -> 945.  (Two waves per SIMD and nothing spilled: 1 212.)
 template <int KT, Sums HOW>
-__global__ void __launch_bounds__(256, KT <= 3 ? 5 : KT <= 4 ? 4 : 3)
+__global__ void __launch_bounds__(256, KT <= 2 ? 6 : KT <= 4 ? 5 : 3)
 simulate_channels_kernel(const SimChanParams p)
 {
     extern __shared__ double smem[];
@@ -539,6 +542,7 @@ simulate_channels_kernel(const SimChanParams p)
     int32_t *chan_l = reinterpret_cast<int32_t *>(smem);    // [R] channel of every recv, shared by the waves
     int32_t *coff = chan_l + R;             // [64] where the arrivals of a channel start in `lists`
     int32_t *clen = coff + 64;              // [64] recvs of a channel
+    uint32_t *runs_l = reinterpret_cast<uint32_t *>(clen + 64);         // [2][KT][64] the first two runs of every class
     double *mine = reinterpret_cast<double *>(reinterpret_cast<char *>(smem) + p.chan_bytes + (size_t)wave * p.wave_bytes);
     const int Rp = (R + 3) & ~3, nb = p.nb;
     double *arr = mine;                     // [Rp] arrival of recv r, zero beyond R
@@ -565,17 +569,18 @@ simulate_channels_kernel(const SimChanParams p)
     __syncthreads();
     // the first two runs of every class row (lo | hi << 10) and, above the first, their number; fixed for the launch, as are the
     // further ones, which stay in memory
-    uint32_t ra[KT], rc[KT];
-#pragma unroll
-    for (int k = 0; k < KT; ++k) {
-        const int c = lane * cls_lane + k * cls_slot;
-        ra[k] = rc[k] = 0;
+    for (int i = wave; i < KT; i += blockDim.x >> 6) {
+        const int c = lane * cls_lane + i * cls_slot;
+        uint32_t ra = 0, rc = 0;
         if (c < C) {
             const int q = p.run_ptr[c], n = p.run_ptr[c + 1] - q;
-            if (n > 0) ra[k] = (uint32_t)p.run_lo[q] | (uint32_t)p.run_hi[q] << 10 | (uint32_t)n << 20;
-            if (n > 1) rc[k] = (uint32_t)p.run_lo[q + 1] | (uint32_t)p.run_hi[q + 1] << 10;
+            if (n > 0) ra = (uint32_t)p.run_lo[q] | (uint32_t)p.run_hi[q] << 10 | (uint32_t)n << 20;
+            if (n > 1) rc = (uint32_t)p.run_lo[q + 1] | (uint32_t)p.run_hi[q + 1] << 10;
         }
+        runs_l[i * 64 + lane] = ra;
+        runs_l[(KT + i) * 64 + lane] = rc;
     }
+    __syncthreads();
 
     bool bad = false;
     const int gwave = blockIdx.x * (blockDim.x >> 6) + wave;
@@ -718,9 +723,10 @@ simulate_channels_kernel(const SimChanParams p)
 #pragma unroll
         for (int k = 0; k < KT; ++k) {
             double m = rho[k];
-            const int n = m > 0.0 ? 0 : (int)(ra[k] >> 20);
-            if (n > 0) m = range_max(m, (int)(ra[k] & 1023u), (int)((ra[k] >> 10) & 1023u));
-            if (n > 1) m = range_max(m, (int)(rc[k] & 1023u), (int)(rc[k] >> 10));
+            const uint32_t ra = runs_l[k * 64 + lane], rc = runs_l[(KT + k) * 64 + lane];
+            const int n = m > 0.0 ? 0 : (int)(ra >> 20);
+            if (n > 0) m = range_max(m, (int)(ra & 1023u), (int)((ra >> 10) & 1023u));
+            if (n > 1) m = range_max(m, (int)(rc & 1023u), (int)(rc >> 10));
             if (n > 2) {
                 const int q = p.run_ptr[lane * cls_lane + k * cls_slot];
                 int lo = p.run_lo[q + 2], hi = p.run_hi[q + 2];
@@ -839,7 +845,7 @@ static hipError_t launch_sim_chan(SimChanParams &p, const Dag &d, hipStream_t s)
     p.cls_slot = many ? 64 : 1;
     int waves = 4;
     while (waves > 1 && wave_bytes * waves > 40 * 1024) waves >>= 1;
-    const size_t chan_bytes = (((size_t)d.R + 128) * 4 + 15) & ~(size_t)15;
+    const size_t chan_bytes = (((size_t)d.R + 128 + 2 * 64 * KT) * 4 + 15) & ~(size_t)15;
     const size_t lds = chan_bytes + wave_bytes * waves;
     if (lds > 150 * 1024) return hipErrorNotSupported;     // 160 KB of LDS per compute unit
     p.wave_bytes = (int32_t)wave_bytes;
