@@ -679,8 +679,8 @@ __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t
             row[j] = *reinterpret_cast<const tt_row16 *>(mine + ((uint32_t)(l * P + j * SLOTS + s0) & rmask) * RW);
         }
 #pragma unroll
-        for (int j = 0; j < N; ++j)             // (a slot without an op: beyond the end of the buffer, where nothing is written)
-            __builtin_amdgcn_raw_buffer_store_b128(row[j], dep, op[j] >= 0 ? (op[j] * p.W + gw) * 8 : -1, 0, kThrough);
+        for (int j = 0; j < N; ++j)             // (a slot without an op: at the end of the buffer, where nothing is written)
+            __builtin_amdgcn_raw_buffer_store_b128(row[j], dep, op[j] >= 0 ? (op[j] * p.W + gw) * 8 : p.dep_bytes, 0, kThrough);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 * N) : "memory");
     }
     for (int l = L; l % 32 != 0; ++l) lds_barrier();        // (those that compute go 32 levels at a time)
