@@ -1720,7 +1720,7 @@ struct ChainUpload {
 // The tables of class_totals_kernel first, for which a call launches it; those of tac_chain_kernel (ensure_chain_tables) are made while it
 // runs, so that the device waits 45 us less at the first call on inception3 (5 912 ops, all of it 95 us) and 12 on resnet50 (1 260).  Of small
 // graphs (vgg16, 90 ops) all tables are made at once: a second copy and its wait take 6 us more than there is to plan.
-// (hipErrorNotSupported: the graph has not the form, as far as is known)
+// Whether the graph has the form is known here, before a call takes memory or launches anything for it (hipErrorNotSupported: it has not).
 constexpr int64_t kChainAtOnce = 1000;      // ops and predecessors
 hipError_t ensure_chain_columns(Dag *d)
 try {
@@ -1730,6 +1730,7 @@ try {
     if (c.cols_made) return hipSuccess;
     const size_t W = (size_t)d->W;
     auto sets = std::make_shared<ChainSets>();
+    auto form = std::make_shared<ChainForm>();
     ChainColumns p;
     // pieces of one set (classes with equal rows) are one set again: they follow each other
     std::vector<int32_t> set_of_cls(d->C), set_of_col(d->N), set_of_op(d->n, 0);
@@ -1751,7 +1752,7 @@ try {
                 ++j;
             }
         may_be = chain_owners(d->R, d->W, d->n, d->h_row_ptr.data(), d->h_col_idx.data(), set_of_op.data(), *sets) &&
-                 make_chain_columns(d->N, (int)sets->rows.size(), set_of_col.data(), p);
+                 chain_form(d->R, d->W, *sets, *form) && make_chain_columns(d->N, (int)sets->rows.size(), set_of_col.data(), p);
     }
     if (!may_be) {
         c.made = true;
@@ -1759,13 +1760,7 @@ try {
     }
     const bool at_once = (int64_t)d->n + d->E <= kChainAtOnce;
     ChainPlan plan;
-    if (at_once) {
-        make_chain_plan(d->R, d->W, *sets, p.first, plan);
-        if (!plan.ok) {
-            c.made = true;
-            return hipErrorNotSupported;
-        }
-    }
+    if (at_once) make_chain_plan(d->R, *sets, *form, p.first, plan);
     ChainUpload up(plan);
     Packer t;
     t.add(&c.d_several, p.several);
@@ -1781,26 +1776,25 @@ try {
     c.first_total = std::move(p.first);
     c.n_totals = c.first_total.back(); c.n_several = (int32_t)p.several.size(); c.n_pairs = p.n_pairs;
     c.cols_made = true;
-    if (at_once) up.done(c);
-    else c.sets = std::move(sets);
+    if (at_once) {
+        up.done(c);
+    } else {
+        c.sets = std::move(sets);
+        c.form = std::move(form);
+    }
     return hipSuccess;
 } catch (const std::bad_alloc &) {
     return hipErrorOutOfMemory;
 }
 
-// (after ensure_chain_columns; hipErrorNotSupported: the graph has not the form)
+// (after ensure_chain_columns has found that the graph has the form)
 hipError_t ensure_chain_tables(Dag *d)
 try {
     std::lock_guard<std::mutex> lock(d->tables_mutex);
     ChainTables &c = d->chain;
-    if (c.made) return c.ok ? hipSuccess : hipErrorNotSupported;
+    if (c.made) return hipSuccess;
     ChainPlan p;
-    make_chain_plan(d->R, d->W, *c.sets, c.first_total, p);
-    if (!p.ok) {
-        c.made = true;
-        c.sets.reset();
-        return hipErrorNotSupported;
-    }
+    make_chain_plan(d->R, *c.sets, *c.form, c.first_total, p);
     ChainUpload up(p);
     Packer t;
     t.by_kernel = false;                    // (class_totals_kernel runs meanwhile)
@@ -1812,6 +1806,7 @@ try {
     if (e != hipSuccess) return e;          // (the next call plans again)
     up.done(c);
     c.sets.reset();
+    c.form.reset();
     return hipSuccess;
 } catch (const std::bad_alloc &) {
     return hipErrorOutOfMemory;

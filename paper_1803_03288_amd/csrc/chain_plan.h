@@ -56,7 +56,6 @@ struct ChainColumns {
 };
 
 struct ChainPlan {
-    bool ok = false;
     int n_slots = 0;                    // chains
     int32_t empty = -1;                 // total of the ops that depend on no recv
     std::vector<ChainRec> rec;          // [R]
@@ -153,16 +152,16 @@ inline bool chain_owners(int R, int W, int n, const int32_t *row_ptr, const int3
     s.count.assign(D, 0);
     s.empty_set = -1;
     for (int c = 0; c < D; ++c) {
-        int fresh = 0, r = -1;
+        int r = -1;
         for (int w = 0; w < W; ++w) {
             s.count[c] += __builtin_popcountll(s.rows[c][w]);
             const uint64_t x = s.rows[c][w] & ~s.U[c * w8 + w];
-            fresh += __builtin_popcountll(x);
-            if (x) r = w * 64 + __builtin_ctzll(x);
+            if (!x) continue;
+            if (r >= 0 || (x & (x - 1))) return false;          // (two recvs at once)
+            r = w * 64 + __builtin_ctzll(x);
         }
         if (s.count[c] == 0) { s.empty_set = c; continue; }
-        if (fresh > 1) return false;
-        if (fresh == 1) {
+        if (r >= 0) {
             if (s.owner[r] >= 0) return false;
             s.owner[r] = c;
             s.own[c] = r;
@@ -173,103 +172,147 @@ inline bool chain_owners(int R, int W, int n, const int32_t *row_ptr, const int3
     return true;
 }
 
-// s: after chain_owners;  at [D + 1]: the first row of totals of every set
-inline void make_chain_plan(int R, int W, const ChainSets &sets, const std::vector<int32_t> &at, ChainPlan &p)
+// What decides whether a graph has the form: sinks, gates and joins, and a cover by few enough chains.
+struct ChainForm {
+    std::vector<int32_t> sink_ptr, sink_n, sinks;       // [D] where the sinks of a set start and their number; sinks in rising order
+    std::vector<int32_t> by_count;      // [D] the sets, smaller ones first
+    std::vector<int32_t> order_r;       // [R] the recvs, smaller sets of their owners first
+    std::vector<int32_t> gate_set;      // a set that has the sinks of the gate
+    std::vector<int32_t> gate_of;       // [D] the gate of a set with two sinks or more; -1 none
+    std::vector<ChainRec> rec;          // [R] gates, slot and next
+    int n_slots = 0;
+};
+
+// Whether the graph has the form.  s: after chain_owners.  A call asks this before it takes memory or launches anything for the
+// form; the lists and candidates of make_chain_plan can be made later.
+inline bool chain_form(int R, int W, const ChainSets &s, ChainForm &f)
 {
-    p.ok = false;
-    const int D = (int)sets.rows.size(), empty_set = sets.empty_set;
+    const int D = (int)s.rows.size();
     const size_t w8 = (size_t)W;
-    const std::vector<uint64_t> &U = sets.U;
-    const std::vector<int32_t> &par_ptr = sets.par_ptr, &par = sets.par, &own = sets.own, &owner = sets.owner, &count = sets.count;
-    const std::vector<int32_t> &row_of_set = sets.row_of_set;
-    // sinks, smaller sets first
-    std::vector<int32_t> by_count(D);
-    for (int c = 0; c < D; ++c) by_count[c] = c;
-    std::sort(by_count.begin(), by_count.end(), [&](int a, int b) { return count[a] != count[b] ? count[a] < count[b] : a < b; });
-    std::vector<std::vector<int32_t>> sinks(D);
+    // sets by their numbers of recvs, and recvs by those of their owners; ties in rising order
+    std::vector<int32_t> at(R + 2);
+    auto by = [&](auto n_of, int n, std::vector<int32_t> &out) {
+        out.resize(n);
+        std::fill(at.begin(), at.end(), 0);
+        for (int i = 0; i < n; ++i) ++at[n_of(i) + 1];
+        for (int i = 0; i <= R; ++i) at[i + 1] += at[i];
+        for (int i = 0; i < n; ++i) out[at[n_of(i)]++] = i;
+    };
+    by([&](int c) { return s.count[c]; }, D, f.by_count);
+    by([&](int r) { return s.count[s.owner[r]]; }, R, f.order_r);
+    // sinks
+    f.sink_ptr.assign(D, 0);
+    f.sink_n.assign(D, 0);
+    f.sinks.clear();
+    f.sinks.reserve(D);
     std::vector<uint64_t> cand(w8), covered(w8);
-    for (int c : by_count) {
-        if (count[c] == 0) continue;
+    for (int c : f.by_count) {
+        if (s.count[c] == 0) continue;
+        f.sink_ptr[c] = (int32_t)f.sinks.size();
+        // (one set before it, as along a chain: what that one adds)
+        int u0 = -1;
+        bool one = true;
+        for (int32_t e = s.par_ptr[c]; e < s.par_ptr[c + 1]; ++e) {
+            if (s.count[s.par[e]] == 0) continue;
+            one = one && (u0 < 0 || u0 == s.par[e]);
+            u0 = s.par[e];
+        }
+        if (one && u0 >= 0 && s.own[u0] >= 0) {
+            if (s.own[c] < 0) return false;
+            f.sinks.push_back(s.own[u0]);
+            f.sink_n[c] = 1;
+            continue;
+        }
         std::fill(cand.begin(), cand.end(), 0);
         std::fill(covered.begin(), covered.end(), 0);
         auto take = [&](int r) {
             cand[r >> 6] |= 1ull << (r & 63);
-            for (int w = 0; w < W; ++w) covered[w] |= U[owner[r] * w8 + w];
+            for (int w = 0; w < W; ++w) covered[w] |= s.U[s.owner[r] * w8 + w];
         };
-        for (int32_t e = par_ptr[c]; e < par_ptr[c + 1]; ++e) {
-            const int u = par[e];
-            if (count[u] == 0) continue;
-            if (own[u] >= 0) take(own[u]);
-            else for (int r : sinks[u]) take(r);
+        for (int32_t e = s.par_ptr[c]; e < s.par_ptr[c + 1]; ++e) {
+            const int u = s.par[e];
+            if (s.count[u] == 0) continue;
+            if (s.own[u] >= 0) take(s.own[u]);
+            else for (int i = 0; i < f.sink_n[u]; ++i) take(f.sinks[f.sink_ptr[u] + i]);
         }
         for (int w = 0; w < W; ++w) {
-            if ((cand[w] | covered[w]) != U[c * w8 + w]) return;
-            for (uint64_t x = cand[w] & ~covered[w]; x; x &= x - 1) sinks[c].push_back(w * 64 + __builtin_ctzll(x));
+            if ((cand[w] | covered[w]) != s.U[c * w8 + w]) return false;
+            for (uint64_t x = cand[w] & ~covered[w]; x; x &= x - 1) f.sinks.push_back(w * 64 + __builtin_ctzll(x));
         }
-        if (own[c] < 0 && sinks[c].size() < 2) return;
+        f.sink_n[c] = (int32_t)f.sinks.size() - f.sink_ptr[c];
+        if (s.own[c] < 0 && f.sink_n[c] < 2) return false;
     }
     // gates
-    p.gate.clear();
-    std::vector<int32_t> gate_set;                  // a set that has the sinks of the gate
-    std::vector<int32_t> gate_of(D, -1);
-    std::vector<std::vector<int32_t>> gate_next;
-    std::vector<int32_t> gate_join;
-    p.rec.assign(R, ChainRec{-1, -1, -1, 0, 0, 0, -1, -1});
-    for (int c : by_count) {
-        if (sinks[c].size() < 2) continue;
+    f.gate_set.clear();
+    f.gate_of.assign(D, -1);
+    f.rec.assign(R, ChainRec{-1, -1, -1, 0, 0, 0, -1, -1});
+    for (int c : f.by_count) {
+        const int32_t *const sk = f.sinks.data() + f.sink_ptr[c], n = f.sink_n[c];
+        if (n < 2) continue;
+        auto same = [&](int u) { return f.sink_n[u] == n && std::equal(sk, sk + n, f.sinks.data() + f.sink_ptr[u]); };
         int g = 0;
-        while (g < (int)gate_set.size() && sinks[gate_set[g]] != sinks[c]) ++g;
-        if (g == (int)gate_set.size()) {
-            if (g == kChainMaxGates) return;
-            gate_set.push_back(c);
-            gate_next.emplace_back();
-            gate_join.push_back(-1);
-            int32_t v = (int32_t)sinks[c].size() << 16;
-            for (int r : sinks[c]) {
-                v ^= r;
-                ChainRec &q = p.rec[r];
+        while (g < (int)f.gate_set.size() && !same(f.gate_set[g])) ++g;
+        if (g == (int)f.gate_set.size()) {
+            if (g == kChainMaxGates) return false;
+            f.gate_set.push_back(c);
+            for (int i = 0; i < n; ++i) {
+                ChainRec &q = f.rec[sk[i]];
                 if (q.gate0 < 0) q.gate0 = (int16_t)g;
                 else if (q.gate1 < 0) q.gate1 = (int16_t)g;
-                else return;
+                else return false;
             }
-            p.gate.push_back(ChainGate{v, -1, 0, 0, {0, 0, 0}});
         }
-        gate_of[c] = g;
-        if (own[c] >= 0) gate_next[g].push_back(own[c]);
-        else gate_join[g] = c;
+        f.gate_of[c] = g;
     }
     // chains
-    std::vector<int32_t> order_r(R);
-    for (int r = 0; r < R; ++r) order_r[r] = r;
-    std::sort(order_r.begin(), order_r.end(), [&](int a, int b) {
-        const int ca = count[owner[a]], cb = count[owner[b]];
-        return ca != cb ? ca < cb : a < b;
-    });
     // (a recv goes on from a direct predecessor where it can, else from any recv of pre(r) that ends a chain so far)
-    std::vector<int32_t> tail;                      // last recv of every chain
-    std::vector<std::vector<int32_t>> more(R);
-    std::vector<int32_t> start;
-    for (int r : order_r) {
-        const std::vector<int32_t> &sk = sinks[owner[r]];
+    int tail[kChainMaxChains];                      // last recv of every chain
+    f.n_slots = 0;
+    for (int r : f.order_r) {
+        const int c = s.owner[r];
+        const int32_t *const sk = f.sinks.data() + f.sink_ptr[c], n = f.sink_n[c];
         int k = -1;
-        for (int s : sk)
-            if (tail[p.rec[s].slot] == s) { k = p.rec[s].slot; break; }
-        for (int i = 0; i < (int)tail.size() && k < 0; ++i)
-            if ((U[owner[r] * w8 + (tail[i] >> 6)] >> (tail[i] & 63)) & 1ull) k = i;
-        if (sk.empty()) start.push_back(r);
-        else if (sk.size() == 1) {
-            if (k >= 0 && tail[k] == sk[0]) p.rec[sk[0]].next = (int16_t)r;
-            else more[sk[0]].push_back(r);
-        }
+        for (int i = 0; i < n && k < 0; ++i)
+            if (tail[f.rec[sk[i]].slot] == sk[i]) k = f.rec[sk[i]].slot;
+        for (int i = 0; i < f.n_slots && k < 0; ++i)
+            if ((s.U[c * w8 + (tail[i] >> 6)] >> (tail[i] & 63)) & 1ull) k = i;
+        if (n == 1 && k >= 0 && tail[k] == sk[0]) f.rec[sk[0]].next = (int16_t)r;
         if (k < 0) {
-            if (tail.size() == (size_t)kChainMaxChains) return;
-            k = (int)tail.size();
-            tail.push_back(r);
+            if (f.n_slots == kChainMaxChains) return false;
+            k = f.n_slots++;
         }
         tail[k] = r;
-        p.rec[r].slot = (int16_t)k;
+        f.rec[r].slot = (int16_t)k;
     }
-    p.n_slots = (int)tail.size();
+    return true;
+}
+
+// The tables of a graph that has the form (f: of chain_form);  at [D + 1]: the first row of totals of every set
+inline void make_chain_plan(int R, const ChainSets &s, const ChainForm &f, const std::vector<int32_t> &at, ChainPlan &p)
+{
+    const int n_gates = (int)f.gate_set.size();
+    const std::vector<int32_t> &owner = s.owner, &order_r = f.order_r;
+    p.rec = f.rec;
+    // gates
+    p.gate.clear();
+    for (int c : f.gate_set) {
+        int32_t v = f.sink_n[c] << 16;
+        for (int i = 0; i < f.sink_n[c]; ++i) v ^= f.sinks[f.sink_ptr[c] + i];
+        p.gate.push_back(ChainGate{v, -1, 0, 0, {0, 0, 0}});
+    }
+    std::vector<std::vector<int32_t>> gate_next(n_gates), more(R);
+    std::vector<int32_t> gate_join(n_gates, -1), start;
+    for (int c : f.by_count) {
+        if (f.gate_of[c] < 0) continue;
+        if (s.own[c] >= 0) gate_next[f.gate_of[c]].push_back(s.own[c]);
+        else gate_join[f.gate_of[c]] = c;
+    }
+    for (int r : order_r) {
+        const int n = f.sink_n[owner[r]], sink = n == 1 ? f.sinks[f.sink_ptr[owner[r]]] : -1;
+        if (n == 0) start.push_back(r);
+        if (sink >= 0 && p.rec[sink].next != r) more[sink].push_back(r);
+    }
+    p.n_slots = f.n_slots;
     p.place.assign(R, 0);
     std::vector<std::vector<int32_t>> chain(p.n_slots);
     for (int r : order_r) {
@@ -302,12 +345,12 @@ inline void make_chain_plan(int R, int W, const ChainSets &sets, const std::vect
     p.cand_ptr.assign(1, 0);
     p.cand.clear();
     for (int r = 0; r < R; ++r) {
-        auto add = [&](int set) { p.cand.push_back(row_of_set[set]); };
+        auto add = [&](int set) { p.cand.push_back(s.row_of_set[set]); };
         if (p.rec[r].next >= 0) add(owner[p.rec[r].next]);
-        for (int s : more[r]) add(owner[s]);
+        for (int x : more[r]) add(owner[x]);
         for (int g : {(int)p.rec[r].gate0, (int)p.rec[r].gate1})
             if (g >= 0) {
-                for (int s : gate_next[g]) add(owner[s]);
+                for (int x : gate_next[g]) add(owner[x]);
                 if (gate_join[g] >= 0) add(gate_join[g]);
             }
         p.cand_ptr.push_back((int32_t)p.cand.size());
@@ -318,8 +361,7 @@ inline void make_chain_plan(int R, int W, const ChainSets &sets, const std::vect
         if (p.place[r] < kChainAhead) p.head.push_back(r | at[owner[r]] << 16);
     }
     for (size_t g = 0; g < p.gate.size(); ++g) p.gate[g].join = (int16_t)(gate_join[g] >= 0 ? at[gate_join[g]] : -1);
-    p.empty = empty_set >= 0 ? at[empty_set] : -1;
-    p.ok = true;
+    p.empty = s.empty_set >= 0 ? at[s.empty_set] : -1;
 }
 
 }  // namespace tictac

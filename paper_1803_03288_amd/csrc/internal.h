@@ -32,6 +32,7 @@ struct Block {
 
 // Tables of the chain form of TAC (chain_plan.h, k3_tac_chain.hip), made at the first call that takes that form.
 struct ChainSets;
+struct ChainForm;
 struct ChainTables {
     bool made = false, ok = false;  // made: whether the graph has the form is known, and if so (ok) the tables are there
     int32_t n_chains = 0, n_totals = 0, n_gates = 0, start = 0, n_start = 0, n_several = 0, empty = -1, n_extra = 0, n_pairs = 0, n_head = 0;
@@ -39,7 +40,8 @@ struct ChainTables {
     // What class_totals_kernel needs is there first (cols_made), so that it runs while the rest is planned.
     bool cols_made = false;
     std::vector<int32_t> first_total;       // of every set
-    std::shared_ptr<ChainSets> sets;        // until the rest is planned
+    std::shared_ptr<ChainSets> sets;        // until the rest is planned, and
+    std::shared_ptr<ChainForm> form;
     Block block, cols_block;
     int4 *d_rec = nullptr, *d_gate = nullptr;
     int16_t *d_list = nullptr, *d_place = nullptr, *d_extra = nullptr;
@@ -229,7 +231,7 @@ struct Dag {
 };
 
 hipError_t ensure_workspace(Dag *d, size_t bytes);
-// the tables of the chain form, made at the first call; d->chain.ok says whether the graph has that form
+// the tables of the chain form, made at the first call (hipErrorNotSupported: the graph has not that form); the second after the first
 hipError_t ensure_chain_columns(Dag *d);
 hipError_t ensure_chain_tables(Dag *d);
 // likewise for the bit-sliced and, if wanted, the frontier form: side by side, the frontier's planned by a thread of its own on

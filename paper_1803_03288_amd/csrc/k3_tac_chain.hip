@@ -588,8 +588,7 @@ hipError_t launch_tac_chain(Dag &d, const TacArgs &a, size_t flag_bytes, size_t 
         hipLaunchKernelGGL(kernel, grid, dim3(64), 0, s, t);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        // (at a handle's first call the chains are planned while the first totals are formed; where it turns out that there are more than
-        // eight, or that branches join otherwise, those were in vain)
+        // (at a handle's first call the tables of the chains are made while the first totals are formed)
         if (b0 == 0) e = ensure_chain_tables(&d);
         if (e != hipSuccess) return e;
         ChainParams p{};

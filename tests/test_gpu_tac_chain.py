@@ -78,6 +78,29 @@ GRAPHS = {
 SECOND_GATES = {"second_two": 2, "second_three": 4, "second_four": 4, "second_five": 8, "second_eight": 8, "second_fork": 4, "second_fork_four": 8}
 
 
+def crossed_dag(layers, units, gates, name="crossed"):
+    """A chain of layers, and units of a layer and ``gates`` more, which the next layer of the chain joins; with more than one there is a join of
+    the first with each of them before, so that its recv is a sink of one gate more than those."""
+    b = wl._Builder()
+
+    def layer(*xs):
+        return b.chain([b.op([*xs, b.recv(1e5 * (1 + len(b.preds) % 3))], 1e-3, "layer")], [1e-3], "op")
+    x = b.op([], 1e-3, "input")
+    for _ in range(layers):
+        x = layer(x)
+    for _ in range(units):
+        ends = [layer(x) for _ in range(gates + 1)]
+        x = layer(*([b.op([ends[0], y], 1e-3, "join") for y in ends[1:]] if gates > 1 else ends))
+    return b.finish(name, seed=5, batch=8)
+
+
+# every recv is added by one class, as the chain form asks, but: more than eight chains, a recv that is a sink of three gates, 41 gates
+REFUSED = {
+    "nine": lambda: modules_dag([[30] * 9]), "nine_behind_one": lambda: modules_dag([[200], [8] * 9]), "twelve": lambda: modules_dag([[24] * 12]),
+    "sixteen": lambda: modules_dag([[20] * 16]), "three_gates": lambda: crossed_dag(300, 1, 2), "many_gates": lambda: crossed_dag(200, 41, 1),
+}
+
+
 def times(d, B, kind, rng):
     """Timing arrays: lognormal multiples of 2**-30 s; or a few values only, so that most comparisons tie; or with some
     times of zero (which the samples are left to the general kernel for)."""
@@ -140,6 +163,26 @@ def test_chain_form_inception(tt):
     dep = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
     eo, er = oracle_tac_rows(dep, d.recv_ids, op[rows], rv[rows])[:2]
     assert np.array_equal(got[0][rows].cpu().numpy(), eo) and np.array_equal(got[1][rows].cpu().numpy(), er)
+
+
+@pytest.mark.parametrize("name", list(REFUSED))
+def test_graphs_without_the_form(tt, name):
+    """First and second call of a batch large enough for the chain form, on a graph that has more chains or gates than it takes."""
+    d = REFUSED[name]()
+    rng = np.random.default_rng(len(name))
+    h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    assert h.n_classes > 256                                  # (from 64 samples on)
+    print(f"[chain] {name}: N={d.n_compute} R={d.n_recv} classes={h.n_classes}", flush=True)
+    dep = oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)
+    for B in (64, 70):
+        op, rv = times(d, B, "lognormal", rng)
+        got = tt.tac_simulate(h, torch.from_numpy(op).cuda(), torch.from_numpy(rv).cuda(), want_rank=True)
+        rows = [0, 33, B - 1]
+        eo, er = oracle_tac_rows(dep, d.recv_ids, op[rows], rv[rows])[:2]
+        assert np.array_equal(got[0][rows].cpu().numpy(), eo) and np.array_equal(got[1][rows].cpu().numpy(), er)
+        em = oracle.simulate(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids, eo, op[rows], rv[rows])
+        for k in range(5):
+            np.testing.assert_allclose(got[4 + k][rows].cpu().numpy(), em[k], rtol=1e-12, atol=0)
 
 
 @pytest.mark.gpu

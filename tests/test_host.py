@@ -11,7 +11,7 @@ from paper_1803_03288_amd import workloads as wl
 
 from host_lib import HostLib, I32, build_host_lib, ptr
 from test_gpu_lane_layouts import SLOTS
-from test_gpu_tac_chain import GRAPHS as CHAINS, SECOND_GATES
+from test_gpu_tac_chain import GRAPHS as CHAINS, REFUSED, SECOND_GATES
 
 
 @pytest.fixture(scope="module")
@@ -147,6 +147,28 @@ def test_chains_planned_beside_the_class_totals(lib):
             lib.free(h)
             if not struck:
                 break
+        else:
+            raise AssertionError("no end")
+
+
+@pytest.mark.parametrize("name", list(REFUSED))
+def test_graphs_without_the_chain_form(lib, name):
+    """A graph that has more chains or gates than the chain form takes: its first call launches nothing for that form and takes no memory
+    for it, whether its tables would be made at once or in two parts."""
+    d = REFUSED[name]()
+    B = 8192
+    assert d.n_ops + d.col_idx.size > 1000
+    h = lib.build(d)[1]
+    lib.tictac_trim_memory()
+    before = lib.count("device_bytes")
+    room = {}
+    for _ in range(2):
+        lib.host_forget_launches()
+        assert lib.tac(h, d, B, room) == 0, lib.error()
+        first, *rest = lib.kernels()
+        assert "tac_reg_kernel" in first and len(rest) == 1 and "10tac_kernel" in rest[0], lib.kernels()
+        assert 4 * B <= lib.count("device_bytes") - before <= 5 * B         # (a flag per sample, an eighth more)
+    lib.free(h)
 
 
 @pytest.mark.parametrize("name", list(GRAPHS) + ["sends"])
