@@ -278,14 +278,35 @@ struct Packer {
         const size_t behind = device_only ? align(host_bytes, alignment) : align(host_bytes), total = behind + device_only;
         if (e != hipSuccess || !total) return e;
         std::vector<char> pageable;
+        char *st = stage(pageable);
+        e = pool_alloc(&block.p, total);
+        if (e != hipSuccess) return e;
+        block.bytes = total;
+        return send(static_cast<char *>(block.p), behind, st, pageable, s);
+    }
+    // The same into memory that a block has reserved, where nothing is allocated on the device.
+    hipError_t commit_at(void *to, size_t room, hipStream_t s)
+    {
+        for (const Part &p : parts) *p.dst = nullptr;
+        if (host_bytes > room || device_only) return hipErrorInvalidValue;
+        std::vector<char> pageable;
+        char *st = stage(pageable);
+        return send(static_cast<char *>(to), 0, st, pageable, s);
+    }
+
+private:
+    char *stage(std::vector<char> &pageable)
+    {
         char *st = static_cast<char *>(staging.take(host_bytes));
         if (!st && host_bytes) {
             pageable.resize(host_bytes);
             st = pageable.data();
         }
-        e = pool_alloc(&block.p, total);
-        if (e != hipSuccess) return e;
-        block.bytes = total;
+        return st;
+    }
+    hipError_t send(char *to, size_t behind, char *st, const std::vector<char> &pageable, hipStream_t s)
+    {
+        hipError_t e = hipSuccess;
         for (const Part &p : parts)
             if (p.src) memcpy(st + p.off, p.src, p.bytes);
         stream = s;
@@ -293,14 +314,14 @@ struct Packer {
             under_way = true;
             // (small blocks: a kernel reads the pinned memory itself)
             if (by_kernel && pageable.empty() && host_bytes <= kCopyInMax) {
-                e = launch_copy_in(block.p, st, host_bytes, s);
+                e = launch_copy_in(to, st, host_bytes, s);
             } else {
-                e = hipMemcpyAsync(block.p, st, host_bytes, hipMemcpyHostToDevice, s);
+                e = hipMemcpyAsync(to, st, host_bytes, hipMemcpyHostToDevice, s);
                 if (!pageable.empty() && e == hipSuccess) e = hipStreamSynchronize(s);
             }
         }
         for (const Part &p : parts)
-            if (e == hipSuccess) *p.dst = static_cast<char *>(block.p) + (p.src ? 0 : behind) + p.off;
+            if (e == hipSuccess) *p.dst = to + (p.src ? 0 : behind) + p.off;
         return e;
     }
 };
@@ -405,7 +426,7 @@ static void free_dag(Dag *d)
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     const Block blocks[] = {
         d->graph_block, d->quad_block, d->class_block, {d->d_work, d->work_bytes}, {d->d_chan, (size_t)d->R * sizeof(int32_t)},
-        d->send_block, d->chain.block, d->chain.cols_block, d->sliced_block, d->frontier.block};
+        d->send_block, d->chain.block, d->sliced_block, d->frontier.block};
     for (const auto &b : blocks) {
         if (!b.p) continue;
         if (idle) pool_put(b.p, b.bytes, d->device);
@@ -1718,9 +1739,10 @@ struct ChainUpload {
 };
 
 // The tables of class_totals_kernel first, for which a call launches it; those of tac_chain_kernel (ensure_chain_tables) are made while it
-// runs, so that the device waits 45 us less at the first call on inception3 (5 912 ops, all of it 95 us) and 12 on resnet50 (1 260).  Of small
+// runs: the first call on inception3 (5 912 ops), 8 192 samples, takes 383 us and not 427, on resnet50 (1 260 ops) 139 and not 149.  Of small
 // graphs (vgg16, 90 ops) all tables are made at once: a second copy and its wait take 6 us more than there is to plan.
-// Whether the graph has the form is known here, before a call takes memory or launches anything for it (hipErrorNotSupported: it has not).
+// Whether the graph has the form is known here, before a call takes memory or launches anything for it (hipErrorNotSupported: it has not), and
+// so is the room that its other tables take: a workspace that left none for them would be of no use.
 constexpr int64_t kChainAtOnce = 1000;      // ops and predecessors
 hipError_t ensure_chain_columns(Dag *d)
 try {
@@ -1768,9 +1790,10 @@ try {
     t.add(&c.d_flush_row, p.flush_row);
     t.add(&c.d_block_first, p.block_first);
     if (at_once) up.add(t, c);
+    else t.reserve(&c.room, chain_plan_bytes(d->R, *form));
     hipStream_t s;
     hipError_t e = table_stream(d->device, &s);
-    if (e == hipSuccess) e = t.commit(c.cols_block, d->device, s);
+    if (e == hipSuccess) e = t.commit(c.block, d->device, s);
     if (e == hipSuccess) e = t.finish();
     if (e != hipSuccess) return e;
     c.first_total = std::move(p.first);
@@ -1801,7 +1824,7 @@ try {
     up.add(t, c);
     hipStream_t s;
     hipError_t e = table_stream(d->device, &s);
-    if (e == hipSuccess) e = t.commit(c.block, d->device, s);
+    if (e == hipSuccess) e = t.commit_at(c.room, chain_plan_bytes(d->R, *c.form), s);
     if (e == hipSuccess) e = t.finish();
     if (e != hipSuccess) return e;          // (the next call plans again)
     up.done(c);

@@ -287,6 +287,17 @@ inline bool chain_form(int R, int W, const ChainSets &s, ChainForm &f)
     return true;
 }
 
+// Bytes that the tables of make_chain_plan take on the device at most, each from a multiple of 256 on.  (A recv is in one list of another, of a
+// gate or of the start, or is the next of one; a set is a candidate of its sinks.)
+inline size_t chain_plan_bytes(int R, const ChainForm &f)
+{
+    const size_t arrays[] = {sizeof(ChainRec) * R, sizeof(ChainGate) * f.gate_set.size(), 2 * (size_t)R, 2 * (size_t)R, 2 * (size_t)R,
+                             4 * (size_t)f.n_slots * kChainAhead, 4 * ((size_t)R + 1), 4 * f.sinks.size()};
+    size_t bytes = 0;
+    for (size_t n : arrays) bytes += (n + 255) & ~(size_t)255;
+    return bytes;
+}
+
 // The tables of a graph that has the form (f: of chain_form);  at [D + 1]: the first row of totals of every set
 inline void make_chain_plan(int R, const ChainSets &s, const ChainForm &f, const std::vector<int32_t> &at, ChainPlan &p)
 {

@@ -42,7 +42,8 @@ struct ChainTables {
     std::vector<int32_t> first_total;       // of every set
     std::shared_ptr<ChainSets> sets;        // until the rest is planned, and
     std::shared_ptr<ChainForm> form;
-    Block block, cols_block;
+    void *room = nullptr;                   // for the rest, in the block
+    Block block;
     int4 *d_rec = nullptr, *d_gate = nullptr;
     int16_t *d_list = nullptr, *d_place = nullptr, *d_extra = nullptr;
     int32_t *d_head = nullptr, *d_several = nullptr, *d_cand_ptr = nullptr, *d_cand = nullptr, *d_flush_row = nullptr, *d_block_first = nullptr;

@@ -244,6 +244,29 @@ def test_tac_makes_do_with_the_memory_there_is(lib):
         lib.free(h)
 
 
+def test_a_workspace_leaves_room_for_the_tables(lib):
+    """Whatever memory there is, the class totals are formed only where the chains come after them."""
+    d, B, room = wl.chain_dag(400), 16384, {}
+
+    def run(limit):
+        h = lib.build(d)[1]
+        lib.tictac_trim_memory()
+        before = lib.count("device_bytes")
+        lib.host_device_limit(before + limit if limit >= 0 else -1)
+        lib.host_forget_launches()
+        assert lib.tac(h, d, B, room) == 0, lib.error()
+        lib.host_device_limit(-1)
+        taken, kernels = lib.count("device_bytes") - before, lib.kernels()
+        lib.free(h)
+        return taken, tuple(sum(k in x for x in kernels) for k in ("class_totals", "tac_chain", "tac_reg"))
+    most, launches = run(-1)
+    assert launches == (1, 1, 0)
+    for some in (most, most // 2):                  # (of one chunk and of two)
+        for kib in range(0, 240, 4):
+            launches = run(some - (kib << 10))[1]
+            assert launches in ((1, 1, 0), (2, 2, 0), (0, 0, 1)), (some, kib, launches)
+
+
 @pytest.mark.parametrize("name", list(GRAPHS))
 def test_the_first_propagation_finds_its_tables_made(lib, name):
     """recompute_deps on a handle that has just been built allocates nothing, waits for nothing and can be captured; the
