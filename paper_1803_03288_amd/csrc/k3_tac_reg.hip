@@ -70,9 +70,10 @@ struct TacRegParams {
 // no more sets than as many as LDS holds, the kernel of eight, which spills nothing, has the batch: 22 x 35 ops and 336 recvs, one
 // sample 442 us (with 128 registers 467), 1 024 samples 498 (531); 58 x 23 and 380, where LDS holds ten, 532 (587) and 597
 // (665), 3 000 samples 1 280 (1 552).
-//   Where more than twelve are needed twice or more and twelve, three waves per SIMD with 168 registers, take no more sets, twelve have the batch, and
-// the samples of a compute unit are dealt to its sets evenly (two of ten and not sixteen and four): 5 003 samples of 61 x 23 and 203
-// 902 -> 770 us, 6 144 of them 900 -> 770, 30 x 20 and 203 749 -> 648, 24 x 20 and 300 1 118 -> 971, 40 x 25 and 260 1 138 -> 969; sixteen remain in one set
+//   Where more than twelve are needed twice or more and twelve, three waves per SIMD with 168 registers, take no more sets, twelve have the batch
+// (spilled with 10, 12, 14 and 16 class slots: 0, 0, 11 and 33 registers, of sixteen waves 15, 35, 51 and 78): 5 003 samples of 61 x 23 and 203
+// 902 -> 770 us, 6 144 of them 900 -> 770, 30 x 20 and 203 749 -> 648, 40 x 25 and 260 1 138 -> 969, with the samples of a compute unit dealt to its sets
+// evenly (launch_reg_k); sixteen remain in one set
 // (nine to twelve samples: 408, twelve 401) and where twelve would take another set (32 samples per compute unit: 914 in two of sixteen).
 //   More than 384 recvs, up to 1 024 (a bit per lane and position of a 32-bit word) where LDS holds the rows, against the general
 // kernel, 5 003 samples, ms: 20 x 10 ops and 500 recvs 5.8 and 2.1; 30 x 20 and 400, 9.2 and 1.5; 61 x 23 and 400, 17.6 and 2.7;
@@ -737,10 +738,6 @@ static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
     }
     const size_t lds = (rows_doubles + per_wave * waves) * 8;
     if (lds > 150 * 1024) return hipErrorNotSupported;
-    // (the samples of a compute unit are dealt to its sets evenly: the waves of a SIMD slow each other down; those without a sample
-    // help to bring in the rows)
-    const int sets = (each + waves - 1) / waves;
-    p.active = (each + sets - 1) / sets;
     p.wave_doubles = (int32_t)per_wave;
     // the class totals are summed in the space of P, ordl and the outstanding set when that holds
     // one double per class slot
@@ -754,6 +751,13 @@ static hipError_t launch_reg_k(TacRegParams &p, const Dag &d, hipStream_t s)
     e = cached_blocks_per_cu(&per_cu, reinterpret_cast<const void *>(kern), 64 * waves, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
+    // A workgroup that has a compute unit to itself (five class slots and more): the samples of the compute unit are dealt to its sets evenly (two of
+    // ten and not sixteen and four), since the waves of a SIMD slow each other down; those without a sample help to bring in the rows: six to eight class
+    // slots, 17 to 24 samples per compute unit 24 x 20 ops and 300 recvs 1 090 -> 947 us, 18 x 18 and 380 1 355 -> 1 197, 33 of them 1 616 -> 1 406.  Where several workgroups share one, its
+    // samples are under way together anyhow, and fewer waves per workgroup are more workgroups that bring in the rows (five and six samples per
+    // compute unit, three waves each instead of four and two: 16 x 15 ops and 200 recvs 243 us instead of 240).
+    const int sets = per_cu > 1 ? 1 : (each + waves - 1) / waves;
+    p.active = std::min(waves, (each + sets - 1) / sets);
     const int n_cu = device_cu_count(d.device);
     int grid = per_cu * n_cu;                       // one resident set of workgroups, no tail
     const int need = (p.B + p.active - 1) / p.active;

@@ -72,9 +72,9 @@ def test_tac_with_many_classes(tt, name):
     h.close()
 
 
-@pytest.mark.parametrize("levels,width,recvs,low,high", [(50, 18, 203, 513, 640), (45, 22, 203, 641, 768), (61, 23, 203, 769, 896), (60, 28, 203, 897, 1024)])
-def test_two_sets_of_twelve_waves(tt, levels, width, recvs, low, high):
-    """Batches whose samples take two sets of sixteen waves per compute unit: twelve waves, and the samples dealt to them evenly, give
+@pytest.mark.parametrize("levels,width,recvs,low,high", [(20, 20, 200, 321, 384), (24, 20, 300, 385, 448), (50, 18, 203, 513, 640), (45, 22, 203, 641, 768), (61, 23, 203, 769, 896), (60, 28, 203, 897, 1024)])
+def test_two_sets_of_waves(tt, levels, width, recvs, low, high):
+    """Batches whose samples take two sets of sixteen waves per compute unit (of twelve, above 512 classes): dealt to the sets evenly, they give
     every sample what batches of one set give."""
     d = wl.layered_dag(41, levels=levels, width=width, fan_in=(1, 4), back=3, n_recv=recvs, attach=(1, 8))
     h = tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids)

@@ -353,6 +353,21 @@ def test_waves_of_tac_in_registers(lib, name, B, waves):
     lib.free(h)
 
 
+@pytest.mark.parametrize("each", [1, 3, 4, 5, 6, 8, 9, 13])
+@pytest.mark.parametrize("slots,dag", [(1, lambda: layered(12, 5, 20)), (3, wl.resnet50_dag), (4, lambda: layered(20, 14, 200))])
+def test_full_workgroups_of_tac_in_registers(lib, slots, dag, each):
+    """Up to four classes per lane several workgroups of four waves share a compute unit: no more of them than take the samples."""
+    d = dag()
+    h = lib.build(d)[1]
+    B = 256 * each - 3
+    lib.host_forget_launches()
+    assert lib.tac(h, d, B) == 0, lib.error()
+    (name, blocks, threads, _, _), = [l for l in lib.launches() if "tac_reg" in l[0]]
+    assert f"tac_reg_kernelILi{slots}E" in name and threads == 256
+    assert blocks == min(256 * 4, -(-B // min(4, each))), (name, blocks)
+    lib.free(h)
+
+
 def test_many_recvs_without_room_for_flags(lib):
     """A graph with more than 384 recvs, whose general kernel needs no workspace, is taken without one: on a stream that is
     being captured, and where the device has no memory left."""
