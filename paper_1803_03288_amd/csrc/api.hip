@@ -867,6 +867,7 @@ static std::vector<int32_t> copied_rows(const Condensed &g)
 struct QuadTables {
     std::vector<Dag::QuadRec> qrecs;
     std::vector<int32_t> lists, left;       // inputs of the nodes that fit no record; copied rows that found no slot
+    int32_t far = 0;                        // inputs on the lists that have left the ring
 };
 static QuadTables make_quad_tables(const Condensed &g, const std::vector<int32_t> &copied, int32_t P, int32_t ring)
 {
@@ -945,7 +946,10 @@ static QuadTables make_quad_tables(const Condensed &g, const std::vector<int32_t
         f.in01 = 0xffffffffu;
         f.in23 = (uint32_t)lists.size();
         lists.push_back(nn + nr);
-        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) lists.push_back(*x < 0 ? *x : slot_of[*x]);
+        for (const int32_t *x = g.begin(k); x != g.end(k); ++x) {
+            lists.push_back(*x < 0 ? *x : slot_of[*x]);
+            out.far += *x >= 0 && slot_of[*x] < (l + 1) * P - ring;
+        }
     }
     // The copied rows ride along in slots that are still free: a recv's row anywhere (no input, one recv
     // bit), the copy of a node's row at a level within reach of the node or of one of its copy nodes, as
@@ -1030,6 +1034,7 @@ struct PropTables {
         p.add(&d->d_qfovf, quads.lists);
         p.add(&d->d_q_copied, quads.left);
         d->qfovf_len = (int32_t)quads.lists.size();
+        d->q_far = quads.far;
         d->n_q_copied = (int32_t)(quads.left.size() / 2);
         p.reserve(&d->d_k1_q_sink, (size_t)(d->W / 8) * d->k1_q_threads * 16);
     }

@@ -132,6 +132,7 @@ struct Dag {
     QuadRec *d_qrecs = nullptr;     // [n_node_levels * P]
     int32_t *d_qfovf = nullptr;     // the lists of the other nodes, as lfovf
     int32_t qfovf_len = 0;
+    int32_t q_far = 0;              // inputs on those lists that have left the ring
     uint64_t *d_k1_q_sink = nullptr;    // [slices * k1_q_threads][2]
     int32_t *d_q_copied = nullptr;  // [n_q_copied][2] the copied rows (see d_copied) that found no free slot of these records
     int32_t n_q_copied = 0;

@@ -628,3 +628,29 @@ def test_two_workgroups_of_the_sliced_kernel_share_a_compute_unit_where_they_fit
     assert f"tac_sliced_kernelILi{words}E" in name, name
     assert (threads // 64 - 1) * 64 * 64 * words >= C
     assert blocks == min(B, 256 * min(160 * 1024 // lds, 16 // (threads // 64)))
+
+
+def lists_at(levels, width, every, back, recvs=1024):
+    """Layered, two inputs per op from the level before; every ``every``-th op has nine, from ``back`` levels before."""
+    row, col = [0] * (recvs + 1), []
+    for v in range(levels * width):
+        l, w = divmod(v, width)
+        n, at = (9, max(0, l - back)) if v % every == 0 else (2, l - 1)
+        col += [v % recvs] if l == 0 else sorted(recvs + at * width + (w + k) % width for k in range(n))
+        row.append(len(col))
+    n = recvs + levels * width
+    return wl.Dag("lists_at", n, np.array(row, np.int32), np.array(col, np.int32), np.arange(recvs, dtype=np.int32), np.ones(levels * width), np.ones(recvs))
+
+
+# nine inputs at one node in so many: of the level before (none leaves the ring), of 18 levels before (77 and 163 from beyond a ring of
+# sixteen levels, at 8 000 nodes: the nodes that follow such a node are at higher levels themselves)
+@pytest.mark.parametrize("every,back,stored", [(1 << 30, 1, True), (11, 1, True), (9, 1, False), (60, 18, True), (30, 18, False)])
+def test_batches_of_graphs_with_many_lists(lib, every, back, stored):
+    """The computing waves store the rows of graphs with more than one list entry per node, or one row from memory per hundred."""
+    d = lists_at(80, 100, every, back)
+    h = lib.build(d)[1]
+    lib.host_forget_launches()
+    assert lib.tictac_dag_recompute_deps_batch((ctypes.c_void_p * 3)(h, h, h), I32(3), None) == 0, lib.error()
+    kernel = [k for k in lib.kernels() if "propagate" in k][0]
+    assert ("propagate_levels_q_stored" if stored else "propagate_levels_q_batch") in kernel, kernel
+    lib.free(h)
