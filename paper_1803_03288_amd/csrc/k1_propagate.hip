@@ -667,8 +667,11 @@ constexpr size_t kThroughMost = (size_t)600 << 20;
 //   0.2 to 0.7          300 x 60  460 and 444;  200 x 100  644 and 623, 373 and 356;  64 x 200  140 and 138
 //   3.2                 64 x 200  199 and 209
 //   10 to 25            300 x 60  1 109 and 1 203, 1 582 and 1 749;  200 x 100  907 and 1 043, 1 303 and 1 509
-// So there may be as many entries as nodes, and a row from memory per hundred nodes.
-constexpr int kNodesPerFar = 100;
+// and with lists of recvs (three and more at a node), which LDS holds (up to 4 096 entries): 31 x 32 ops and 1 024 recvs, 227 entries, 68 and 65; 100 x 32 and
+// 2 048, 91, 164 and 158; which it does not: 64 x 100 and 4 096, 96, two graphs (16 workgroups) 167 and 169, eight (64) 161 and 161; 100 x 200 and 8 192, 35,
+// 269 and 283 (32 workgroups), 287 and 262 (128).
+// So LDS holds the lists, or there are no more entries than nodes and 64 workgroups; and of a hundred nodes' rows one is from memory.
+constexpr int kNodesPerFar = 100, kListedLeast = 64;
 template <int QC, int N>
 __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t *ring, const int32_t *ops, int t, int gw)
 {
@@ -1030,7 +1033,8 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
         if (g == 0) lds0 = lds;
         if (lds != lds0 || ds[g]->k1_q_threads != ds[0]->k1_q_threads || ds[g]->W != ds[0]->W || ds[g]->n != ds[0]->n)
             return hipErrorNotSupported;
-        few_lists = few_lists && ds[g]->qfovf_len <= ds[g]->M && ds[g]->q_far <= ds[g]->M / kNodesPerFar;
+        few_lists = few_lists && (lp[g].lfovf_lds == ds[g]->qfovf_len || (ds[g]->qfovf_len <= ds[g]->M && ds[g]->W / (2 * QC) * G >= kListedLeast)) &&
+                    ds[g]->q_far <= ds[g]->M / kNodesPerFar;
         ep[g] = ExpandParams{ds[g]->n_q_copied, ds[g]->W, ds[g]->d_q_copied, ds[g]->d_dep};
         most_copied = std::max(most_copied, ds[g]->n_q_copied);
     }
