@@ -1112,7 +1112,8 @@ static void make_propagate_tables(Dag *d, const int32_t *row_ptr, const int32_t 
         (int64_t)n_node_levels * q_slots <= (int64_t)4 * M + 8192) {
         q_ring = 2048;
         while (q_ring > 64 && q_ring / 2 >= n_node_levels * q_slots) q_ring /= 2;
-        if (q_ring < 4 * q_slots && q_ring < n_node_levels * q_slots) q_ring = 0;
+        // (eight levels: a list reads a row that has left the ring from memory, and stores are waited for seven levels on)
+        if (q_ring < 8 * q_slots && q_ring < n_node_levels * q_slots) q_ring = 0;
     }
     d->k1_q_ring = q_ring;
     d->k1_q_threads = q_ring > 0 ? 4 * q_slots : 0;

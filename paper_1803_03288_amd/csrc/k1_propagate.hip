@@ -698,13 +698,14 @@ __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t
     for (int l = L; l % 32 != 0; ++l) lds_barrier();        // (those that compute go 32 levels at a time)
 }
 
-// QC lanes per slot (4: 64-byte slices, 2: 32-byte slices).  STORED: two waves beside those that compute bring the rows to memory; the
+// QC lanes per slot, four of them (32-byte slices, two lanes, were as fast up to sixteen graphs and a third slower from 32 on).  STORED: two waves beside those that compute bring the rows to memory; the
 // threads of a level find the op of its slots in one half of `ops`.
 template <int QC, bool STORED>
 __device__ __forceinline__ void propagate_levels_q_body(const QuadParams &p, uint64_t *ring, int block, int n_blocks)
 {
     constexpr int RW = 2 * QC;                  // words of a row in the ring
-    constexpr int SH = QC == 4 ? 6 : 5;         // log2 of the bytes of a row in the ring
+    static_assert(QC == 4, "the records, SH and the waves that store are for four lanes per slot");
+    constexpr int SH = 6;                       // log2 of the bytes of a row in the ring
     const int W = p.W, L = p.n_levels, P = p.P;
     const int sub = threadIdx.x / QC, qd = threadIdx.x % QC;
     const int gw = slice_of(block, n_blocks) * RW + qd * 2;      // first of this thread's two words of the row
@@ -968,8 +969,7 @@ static bool level_params(const Dag &d, int WC, LevelParams *q, size_t *lds)
 
 static bool quad_params(const Dag &d, int QC, QuadParams *q, size_t *lds)
 {
-    // (k1_q_threads is four lanes per slot; QC lanes per slot need a multiple of 64 threads as well)
-    const int threads = d.k1_q_threads / 4 * QC;
+    const int threads = d.k1_q_threads;
     if (d.k1_q_ring <= 0 || !d.d_qrecs || !d.d_k1_q_sink || d.W % 8 != 0 || threads % 64 != 0 || threads > 256 * QC)
         return false;
     q->n_levels = d.n_node_levels; q->W = d.W; q->P = d.k1_q_threads / 4; q->ring = d.k1_q_ring;
@@ -1018,7 +1018,7 @@ static hipError_t launch_levels_batch(Dag *const *ds, int G, void *staging, hipS
     return hipGetLastError();
 }
 
-// the same for graphs that take the kernel with 64-byte (QC = 4) or 32-byte (QC = 2) slices
+// the same for graphs that take the kernel with 64-byte slices
 template <int QC>
 static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStream_t s)
 {
@@ -1047,7 +1047,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     const Dag &d0 = *ds[0];
     const int blocks_per = d0.W / (2 * QC);
     // two waves more, which store, where a workgroup has room for them (levels of 225 slots and more fill it with those that compute)
-    int threads = d0.k1_q_threads / 4 * QC;
+    int threads = d0.k1_q_threads;
     const bool stored = few_lists && lp[0].dep_bytes > 0 && (size_t)lp[0].dep_bytes * G <= kThroughMost && threads + kStoreThreads <= 256 * QC;
     if (stored) {
         threads += kStoreThreads;
@@ -1073,7 +1073,6 @@ hipError_t launch_propagate_batch(Dag *const *ds, int G, void *staging, hipStrea
 {
     if (G <= 0) return hipSuccess;
     if (ds[0]->n == 0 || ds[0]->W == 0 || ds[0]->M == 0) return hipErrorNotSupported;
-    // (32-byte slices, QC = 2, were measured too: as fast up to sixteen graphs, a third slower from 32 on)
     if (G >= 2 && ds[0]->k1_q_ring > 0) return launch_quad_batch<4>(ds, G, staging, s);
     if (ds[0]->k1_wc == 1) return launch_levels_batch<1>(ds, G, staging, s);
     if (ds[0]->k1_wc == 2) return launch_levels_batch<2>(ds, G, staging, s);
