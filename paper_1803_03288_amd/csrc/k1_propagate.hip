@@ -660,18 +660,14 @@ typedef int tt_row16 __attribute__((ext_vector_type(4)));
 constexpr int kStoreThreads = 128;
 constexpr int kThrough = 18;                // sc1 (to memory at once) and nt
 constexpr size_t kThroughMost = (size_t)600 << 20;
-// Graphs many of whose nodes fit no record gain nothing, or lose, most where their lists name rows that have left the ring: those come from
-// memory then, not from the L2.  Four graphs, us, the computing waves storing and this, list entries and rows from memory per hundred nodes:
-//   none from memory    200 x 100 ops, 1 000 recvs  26: 720 and 700, 148: 1 280 and 1 210;  64 x 200, 1 024  26: 273 and 265, 148: 473 and 487;
-//                       300 x 60, 2 048  26: 805 and 811, 148: 1 723 and 1 691;  few lists  139 and 122, 69 and 62, 174 and 161
-//   0.2 to 0.7          300 x 60  460 and 444;  200 x 100  644 and 623, 373 and 356;  64 x 200  140 and 138
-//   3.2                 64 x 200  199 and 209
-//   10 to 25            300 x 60  1 109 and 1 203, 1 582 and 1 749;  200 x 100  907 and 1 043, 1 303 and 1 509
-// and with lists of recvs (three and more at a node), which LDS holds (up to 4 096 entries): 31 x 32 ops and 1 024 recvs, 227 entries, 68 and 65; 100 x 32 and
-// 2 048, 91, 164 and 158; which it does not: 64 x 100 and 4 096, 96, two graphs (16 workgroups) 167 and 169, eight (64) 161 and 161; 100 x 200 and 8 192, 35,
-// 269 and 283 (32 workgroups), 287 and 262 (128).
-// So LDS holds the lists, or there are no more entries than nodes and 64 workgroups; and of a hundred nodes' rows one is from memory.
-constexpr int kNodesPerFar = 100, kListedLeast = 64;
+// Where the lists of nodes that fit no record name rows that have left the ring, those come from memory then, not from the L2.  Four graphs, us, the
+// computing waves storing and this, by rows from memory per hundred nodes:
+//   3.2 to 25    300 x 60 ops, 2 048 recvs  1 109 and 1 203, 1 582 and 1 749;  200 x 100, 1 000  907 and 1 043, 1 303 and 1 509;  64 x 200, 1 024  199 and 209
+//   0.2 to 0.7   460 and 444;  644 and 623, 373 and 356;  140 and 138
+//   none         26 and 148 list entries per hundred nodes  805 and 811, 1 723 and 1 691;  720 and 700, 1 280 and 1 210;  273 and 265, 473 and 487
+//                lists of recvs, 500 x 10 and 4 096, 30 graphs 1 093 and 962;  500 x 5 and 3 584, four 1 125 and 1 058;  100 x 200 and 8 192, two 269 and 283, eight 287 and 262
+// So of a hundred nodes' rows one is from memory.
+constexpr int kNodesPerFar = 100;
 template <int QC, int N>
 __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t *ring, const int32_t *ops, int t, int gw)
 {
@@ -1026,15 +1022,14 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     std::vector<ExpandParams> ep(G);
     size_t lds0 = 0;
     int32_t most_copied = 0;
-    bool few_lists = true;
+    bool few_far = true;
     for (int g = 0; g < G; ++g) {
         size_t lds = 0;
         if (!quad_params(*ds[g], QC, &lp[g], &lds)) return hipErrorNotSupported;
         if (g == 0) lds0 = lds;
         if (lds != lds0 || ds[g]->k1_q_threads != ds[0]->k1_q_threads || ds[g]->W != ds[0]->W || ds[g]->n != ds[0]->n)
             return hipErrorNotSupported;
-        few_lists = few_lists && (lp[g].lfovf_lds == ds[g]->qfovf_len || (ds[g]->qfovf_len <= ds[g]->M && ds[g]->W / (2 * QC) * G >= kListedLeast)) &&
-                    ds[g]->q_far <= ds[g]->M / kNodesPerFar;
+        few_far = few_far && ds[g]->q_far <= ds[g]->M / kNodesPerFar;
         ep[g] = ExpandParams{ds[g]->n_q_copied, ds[g]->W, ds[g]->d_q_copied, ds[g]->d_dep};
         most_copied = std::max(most_copied, ds[g]->n_q_copied);
     }
@@ -1048,7 +1043,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     const int blocks_per = d0.W / (2 * QC);
     // two waves more, which store, where a workgroup has room for them (levels of 225 slots and more fill it with those that compute)
     int threads = d0.k1_q_threads;
-    const bool stored = few_lists && lp[0].dep_bytes > 0 && (size_t)lp[0].dep_bytes * G <= kThroughMost && threads + kStoreThreads <= 256 * QC;
+    const bool stored = few_far && lp[0].dep_bytes > 0 && (size_t)lp[0].dep_bytes * G <= kThroughMost && threads + kStoreThreads <= 256 * QC;
     if (stored) {
         threads += kStoreThreads;
         lds0 += (size_t)2 * d0.k1_q_threads / 4 * sizeof(int32_t);

@@ -126,24 +126,24 @@ def lists_at(levels, width, every, back, recvs=1024):
     return wl.Dag("lists_at", n, np.array(row, np.int32), np.array(col, np.int32), np.arange(recvs, dtype=np.int32), np.ones(levels * width), np.ones(recvs))
 
 
-# graph, and from how many handles on (None: never) the waves beside those that compute store its rows.  Widths as above; "far": rows that have
-# left the ring, from memory (one for a hundred nodes); "near": more than 4 096 list entries, which LDS does not hold; "narrow": rows of eight words,
-# two slices to a line; "listed": more entries than the waves that store are for, and far ones
-BATCHES = {**{f"w{w}": (lambda l=l, w=w: (wide(l, w, 1024), 2 if w <= 224 else None))
+# graph, and whether the waves beside those that compute store its rows.  Widths as above; "far": rows that have left the ring, from memory (just
+# less than one for a hundred nodes); "near": more than 4 096 list entries, which LDS does not hold; "narrow": rows of eight words, two slices
+# to a line; "listed": more from memory
+BATCHES = {**{f"w{w}": (lambda l=l, w=w: (wide(l, w, 1024), w <= 224))
               for l, w in ((31, 32), (33, 64), (32, 96), (64, 100), (65, 150), (40, 190), (40, 224), (30, 225))},
-           "far": lambda: (lists_at(80, 100, 60, 18), 2), "near": lambda: (lists_at(120, 100, 20, 1), 32), "narrow": lambda: (lists_at(60, 50, 14, 1, 512), 2),
-           "listed": lambda: (lists_dag(40, 190, 1000), None), "listed_wide": lambda: (lists_dag(64, 224, 1000), None)}
+           "far": lambda: (lists_at(80, 100, 60, 18), True), "near": lambda: (lists_at(120, 100, 20, 1), True), "narrow": lambda: (lists_at(60, 50, 14, 1, 512), True),
+           "listed": lambda: (lists_dag(40, 190, 1000), False), "listed_wide": lambda: (lists_dag(64, 224, 1000), False)}
 
 
 @pytest.mark.parametrize("name", list(BATCHES))
 def test_several_graphs_by_both_kernels(tt, name):  # noqa: F811
     """Batches on either side of the 600 MiB up to which two more waves store the rows.  (Above it some graphs are in the list many
     times: the workgroups that form the same rows write the same words.)"""
-    d, least = BATCHES[name]()
+    d, _ = BATCHES[name]()
     want = torch.from_numpy(oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids).view(np.int64)).cuda()
     hs = [tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids) for _ in range(5)]
     over = (600 << 20) // (want.numel() * 8) + 1
-    for n in sorted({2, 5, least or 5, over}):
+    for n in (2, 5, over):
         for h in hs:
             h.deps_view().fill_(-1)
         print(f"[batch] {name}: {n} handles", flush=True)
