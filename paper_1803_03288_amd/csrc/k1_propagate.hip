@@ -668,6 +668,14 @@ constexpr size_t kThroughMost = (size_t)600 << 20;
 //                lists of recvs, 500 x 10 and 4 096, 30 graphs 1 093 and 962;  500 x 5 and 3 584, four 1 125 and 1 058;  100 x 200 and 8 192, two 269 and 283, eight 287 and 262
 // So of a hundred nodes' rows one is from memory.
 constexpr int kNodesPerFar = 100;
+// Lists that LDS does not hold (more than 4 096 entries) are read from memory, beside the rows on their way there.  What this takes where the computing
+// waves storing take 1, 29 shapes of 10 000 to 19 000 ops and 2 048 to 4 096 recvs, by the number of workgroups n:
+//   n a multiple of 8 (both halves of a line meet in one L2, propagate_levels_q_batch)  8 to 56  0.96 to 1.08, mean 1.02 (100 x 100 ops, 4 096 recvs, two
+//     graphs 246 and 262 us);  64 to 80  0.91 to 1.04, mean 0.97;  from 88 on  0.87 to 0.97
+//   other n  10 to 31  0.94 to 1.01, mean 0.97 (300 x 40 and 3 584, two graphs 587 and 554);  33 to 63  0.97 to 1.04, mean 1.00;  65 to 91  0.98 to 1.03, mean
+//     1.00;  from 105 on  0.80 to 1.01
+constexpr int kListedFew = 32, kListedMany = 64;
+static bool listed_stored(int n) { return n >= kListedMany || (n < kListedFew && n % 8 != 0); }
 template <int QC, int N>
 __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t *ring, const int32_t *ops, int t, int gw)
 {
@@ -1022,7 +1030,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     std::vector<ExpandParams> ep(G);
     size_t lds0 = 0;
     int32_t most_copied = 0;
-    bool few_far = true;
+    bool few_far = true, in_lds = true;
     for (int g = 0; g < G; ++g) {
         size_t lds = 0;
         if (!quad_params(*ds[g], QC, &lp[g], &lds)) return hipErrorNotSupported;
@@ -1030,6 +1038,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
         if (lds != lds0 || ds[g]->k1_q_threads != ds[0]->k1_q_threads || ds[g]->W != ds[0]->W || ds[g]->n != ds[0]->n)
             return hipErrorNotSupported;
         few_far = few_far && ds[g]->q_far <= ds[g]->M / kNodesPerFar;
+        in_lds = in_lds && lp[g].lfovf_lds == ds[g]->qfovf_len;
         ep[g] = ExpandParams{ds[g]->n_q_copied, ds[g]->W, ds[g]->d_q_copied, ds[g]->d_dep};
         most_copied = std::max(most_copied, ds[g]->n_q_copied);
     }
@@ -1043,7 +1052,8 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     const int blocks_per = d0.W / (2 * QC);
     // two waves more, which store, where a workgroup has room for them (levels of 225 slots and more fill it with those that compute)
     int threads = d0.k1_q_threads;
-    const bool stored = few_far && lp[0].dep_bytes > 0 && (size_t)lp[0].dep_bytes * G <= kThroughMost && threads + kStoreThreads <= 256 * QC;
+    const bool stored = few_far && (in_lds || listed_stored(blocks_per * G)) && lp[0].dep_bytes > 0 &&
+                        (size_t)lp[0].dep_bytes * G <= kThroughMost && threads + kStoreThreads <= 256 * QC;
     if (stored) {
         threads += kStoreThreads;
         lds0 += (size_t)2 * d0.k1_q_threads / 4 * sizeof(int32_t);

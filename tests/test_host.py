@@ -645,6 +645,20 @@ def test_batches_of_graphs_with_far_inputs(lib, every, back, stored):
     lib.free(h)
 
 
+# two workgroups per graph;  1 000 list entries, which LDS holds, and 6 000
+@pytest.mark.parametrize("every", [120, 20])
+def test_batches_of_graphs_with_many_list_entries(lib, every):
+    """Lists that LDS does not hold: the computing waves store the rows of 8 to 56 workgroups if their number is a multiple of eight, and of 32 to 63."""
+    h = lib.build(lists_at(120, 100, every, 1))[1]
+    for n in (4, 5, 8, 15, 16, 17, 20, 28, 31, 32):
+        lib.host_forget_launches()
+        assert lib.tictac_dag_recompute_deps_batch((ctypes.c_void_p * n)(*[h] * n), I32(n), None) == 0, lib.error()
+        (kernel, blocks, *_), = [l for l in lib.launches() if "propagate" in l[0]]
+        assert blocks == 2 * n
+        assert ("propagate_levels_q_stored" in kernel) == (every == 120 or n in (5, 15, 32)), (n, kernel)
+    lib.free(h)
+
+
 @pytest.mark.parametrize("name", list(BATCHES))
 def test_which_kernel_takes_several_graphs(lib, name):
     """Two waves more store the rows of graphs with up to 224 slots per level, up to 600 MiB of rows; beyond, and of graphs with wider
