@@ -649,17 +649,25 @@ struct QuadParams {
 };
 
 // The rows of level l go to memory while level l + 1 is computed: by kStoreThreads threads, N stores each, of which those of levels up to
-// l - 6 have been completed when level l + 2 begins (a list reads a row from memory eight levels later or more).  They are written
-// through the caches (kThrough), up to kThroughMost bytes of rows of all graphs: rows that wait in the L2 to be pushed out by later ones hold up the
-// levels behind them.  Three sets of handles in turn, us, the computing waves storing and this: 2 to 8 graphs of stress (53 MB of rows each) 307 and 301,
-// 347 and 308; 9 to 11 369, 371, 393 and 309, 330, 346; 12 to 14 (640 to 746 MB) 390, 413, 412 and 393, 400, 430; 16 and 32 432, 568 and 477, 642; 32 graphs of 500 x 64
-// and 4 096 recvs (591 MB) 709 and 599, of 200 x 200 and 2 048 (360 MB) 196 and 155, of 500 x 30 and 1 024 187 and 169.  The separate waves without the
-// way through the caches give 1 to 4 %, or take 7 % (400 x 224, 32 graphs).  (One set of handles again and again 427 instead of 584 with 32 graphs: what
-// the pieces of 64 bytes find in the Infinity Cache then is not what a program finds.)
+// l - 6 have been completed when level l + 2 begins (a list reads a row from memory eight levels later or more).
+//   THROUGH: past the caches (kThrough).  What it gives comes from the hint of no reuse (nt): rows then stay in the Infinity Cache from pass to pass
+// instead of making room for the next, so a later pass over the same handles finds part of them there; a first one does not, and where rows are formed
+// faster than memory takes these stores (some 1.5 TB/s) both wait for them.  Us, first pass on three sets of handles and later ones, the computing waves
+// storing, stores through the caches, past them:
+//   2, 4 graphs of stress (53 MB of rows each)                         first 318, 327; 306, 313; 305, 320        later 314, 324; 299, 312; 303, 308
+//   8, 11 of stress (427, 583 MB; 0.92, 1.25 MB per level)             363, 406; 350, 392; 382, 436              352, 401; 339, 388; 310, 321
+//   32 of 500 x 64 ops, 2 048 recvs (279 MB; 0.62)                     278; 262; 273                             273; 256; 235
+//   32 of 200 x 200 and 2 048 (344 MB; 1.76)                           218; 212; 238                             207; 200; 197
+//   60 of 120 x 200 and 2 048 (400 MB; 3.5)                            223; 217; 257                             200; 194; 225
+//   30 of 200 x 100 and 4 096, lists from memory (370 MB; 2.0)         474; 466; 472                             465; 462; 400
+// Past the caches against the computing waves, first and later, by MB per level: 0.6 to 1.0 0.95 to 1.03 and 0.85 to 0.93 (8 graphs of stress 1.05 and 0.88); 1.15 to 2
+// 0.92 to 1.09 and 0.72 to 1.13; 2.2 to 3.5 0.93 to 1.15 and 0.90 to 1.17; through them never more than 1.02.  So past them go rows that the cache holds, and
+// others where lists from memory or at most a MiB per level leave the stores time.
+// Above kStoredMost the computing waves store: 12 to 14 graphs of stress 390, 413, 412 and past the caches 393, 400, 430; 16 and 32 432, 568 and 477, 642.
 typedef int tt_row16 __attribute__((ext_vector_type(4)));
 constexpr int kStoreThreads = 128;
 constexpr int kThrough = 18;                // sc1 (to memory at once) and nt
-constexpr size_t kThroughMost = (size_t)600 << 20;
+constexpr size_t kThroughMost = (size_t)256 << 20, kThroughPerLevel = (size_t)1 << 20, kStoredMost = (size_t)600 << 20;
 // Where the lists of nodes that fit no record name rows that have left the ring, those come from memory then, not from the L2.  Four graphs, us, the
 // computing waves storing and this, by rows from memory per hundred nodes:
 //   3.2 to 25    300 x 60 ops, 2 048 recvs  1 109 and 1 203, 1 582 and 1 749;  200 x 100, 1 000  907 and 1 043, 1 303 and 1 509;  64 x 200, 1 024  199 and 209
@@ -676,7 +684,7 @@ constexpr int kNodesPerFar = 100;
 //     1.00;  from 105 on  0.80 to 1.01
 constexpr int kListedFew = 32, kListedMany = 64;
 static bool listed_stored(int n) { return n >= kListedMany || (n < kListedFew && n % 8 != 0); }
-template <int QC, int N>
+template <int QC, bool THROUGH, int N>
 __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t *ring, const int32_t *ops, int t, int gw)
 {
     constexpr int RW = 2 * QC, SLOTS = kStoreThreads / QC;
@@ -696,7 +704,8 @@ __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t
         }
 #pragma unroll
         for (int j = 0; j < N; ++j)             // (a slot without an op: at the end of the buffer, where nothing is written)
-            __builtin_amdgcn_raw_buffer_store_b128(row[j], dep, op[j] >= 0 ? (op[j] * p.W + gw) * 8 : p.dep_bytes, 0, kThrough);
+            __builtin_amdgcn_raw_buffer_store_b128(row[j], dep, op[j] >= 0 ? (op[j] * p.W + gw) * 8 : p.dep_bytes, 0,
+                                                   THROUGH ? kThrough : 0);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 * N) : "memory");
     }
     for (int l = L; l % 32 != 0; ++l) lds_barrier();        // (those that compute go 32 levels at a time)
@@ -704,7 +713,7 @@ __device__ __forceinline__ void store_levels(const QuadParams &p, const uint64_t
 
 // QC lanes per slot, four of them (32-byte slices, two lanes, were as fast up to sixteen graphs and a third slower from 32 on).  STORED: two waves beside those that compute bring the rows to memory; the
 // threads of a level find the op of its slots in one half of `ops`.
-template <int QC, bool STORED>
+template <int QC, bool STORED, bool THROUGH>
 __device__ __forceinline__ void propagate_levels_q_body(const QuadParams &p, uint64_t *ring, int block, int n_blocks)
 {
     constexpr int RW = 2 * QC;                  // words of a row in the ring
@@ -724,13 +733,13 @@ __device__ __forceinline__ void propagate_levels_q_body(const QuadParams &p, uin
         if ((int)threadIdx.x >= P * QC) {
             const int t = (int)threadIdx.x - P * QC;
             switch (P / (kStoreThreads / QC)) {
-            case 1: return store_levels<QC, 1>(p, ring, ops, t, gw);
-            case 2: return store_levels<QC, 2>(p, ring, ops, t, gw);
-            case 3: return store_levels<QC, 3>(p, ring, ops, t, gw);
-            case 4: return store_levels<QC, 4>(p, ring, ops, t, gw);
-            case 5: return store_levels<QC, 5>(p, ring, ops, t, gw);
-            case 6: return store_levels<QC, 6>(p, ring, ops, t, gw);
-            default: return store_levels<QC, 7>(p, ring, ops, t, gw);
+            case 1: return store_levels<QC, THROUGH, 1>(p, ring, ops, t, gw);
+            case 2: return store_levels<QC, THROUGH, 2>(p, ring, ops, t, gw);
+            case 3: return store_levels<QC, THROUGH, 3>(p, ring, ops, t, gw);
+            case 4: return store_levels<QC, THROUGH, 4>(p, ring, ops, t, gw);
+            case 5: return store_levels<QC, THROUGH, 5>(p, ring, ops, t, gw);
+            case 6: return store_levels<QC, THROUGH, 6>(p, ring, ops, t, gw);
+            default: return store_levels<QC, THROUGH, 7>(p, ring, ops, t, gw);
             }
         }
     }
@@ -806,10 +815,10 @@ propagate_levels_q_batch(const QuadParams *__restrict__ ps, int blocks_per)
     const int v = (n & 7) == 0 ? (blockIdx.x & 7) * (n >> 3) + (blockIdx.x >> 3) : (int)blockIdx.x;
     const int g = v / blocks_per;
     const QuadParams p = ps[g];
-    propagate_levels_q_body<QC, false>(p, ring, v - g * blocks_per, 1);
+    propagate_levels_q_body<QC, false, false>(p, ring, v - g * blocks_per, 1);
 }
 
-template <int QC>
+template <int QC, bool THROUGH>
 __global__ void __launch_bounds__(256 * QC)
 propagate_levels_q_stored(const QuadParams *__restrict__ ps, int blocks_per)
 {
@@ -818,7 +827,7 @@ propagate_levels_q_stored(const QuadParams *__restrict__ ps, int blocks_per)
     const int v = (n & 7) == 0 ? (blockIdx.x & 7) * (n >> 3) + (blockIdx.x >> 3) : (int)blockIdx.x;
     const int g = v / blocks_per;
     const QuadParams p = ps[g];
-    propagate_levels_q_body<QC, true>(p, ring, v - g * blocks_per, 1);
+    propagate_levels_q_body<QC, true, THROUGH>(p, ring, v - g * blocks_per, 1);
 }
 
 // rows that are copies: a recv's single bit, or the row of the node an op collapses onto.  `copied`: the ops
@@ -1029,7 +1038,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     std::vector<QuadParams> lp(G);
     std::vector<ExpandParams> ep(G);
     size_t lds0 = 0;
-    int32_t most_copied = 0;
+    int32_t most_copied = 0, n_levels = 0;
     bool few_far = true, in_lds = true;
     for (int g = 0; g < G; ++g) {
         size_t lds = 0;
@@ -1039,6 +1048,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
             return hipErrorNotSupported;
         few_far = few_far && ds[g]->q_far <= ds[g]->M / kNodesPerFar;
         in_lds = in_lds && lp[g].lfovf_lds == ds[g]->qfovf_len;
+        n_levels = std::max(n_levels, lp[g].n_levels);
         ep[g] = ExpandParams{ds[g]->n_q_copied, ds[g]->W, ds[g]->d_q_copied, ds[g]->d_dep};
         most_copied = std::max(most_copied, ds[g]->n_q_copied);
     }
@@ -1052,13 +1062,16 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     const int blocks_per = d0.W / (2 * QC);
     // two waves more, which store, where a workgroup has room for them (levels of 225 slots and more fill it with those that compute)
     int threads = d0.k1_q_threads;
+    const size_t rows = (size_t)lp[0].dep_bytes * G;
     const bool stored = few_far && (in_lds || listed_stored(blocks_per * G)) && lp[0].dep_bytes > 0 &&
-                        (size_t)lp[0].dep_bytes * G <= kThroughMost && threads + kStoreThreads <= 256 * QC;
+                        rows <= kStoredMost && threads + kStoreThreads <= 256 * QC;
     if (stored) {
         threads += kStoreThreads;
         lds0 += (size_t)2 * d0.k1_q_threads / 4 * sizeof(int32_t);
     }
-    void (*const kernel)(const QuadParams *, int) = stored ? propagate_levels_q_stored<QC> : propagate_levels_q_batch<QC>;
+    const bool through = rows <= kThroughMost || !in_lds || rows <= kThroughPerLevel * n_levels;
+    void (*const kernel)(const QuadParams *, int) =
+        !stored ? propagate_levels_q_batch<QC> : through ? propagate_levels_q_stored<QC, true> : propagate_levels_q_stored<QC, false>;
     if (lds0 > 48 * 1024) {
         e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernel), lds0);
         if (e != hipSuccess) return e;

@@ -152,3 +152,19 @@ def test_several_graphs_by_both_kernels(tt, name):  # noqa: F811
             assert torch.equal(h.deps_view().view(want.shape), want), (name, n)
     for h in hs:
         h.close()
+
+
+@pytest.mark.parametrize("name", [n for n in BATCHES if "listed" not in n])
+def test_several_graphs_beyond_the_infinity_cache(tt, name):  # noqa: F811
+    """Batches just above 256 MiB of rows, whose rows go through the caches unless lists come from memory."""
+    d, _ = BATCHES[name]()
+    want = torch.from_numpy(oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids).view(np.int64)).cuda()
+    hs = [tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids) for _ in range(5)]
+    n = (256 << 20) // (want.numel() * 8) + 1
+    for h in hs:
+        h.deps_view().fill_(-1)
+    print(f"[batch] {name}: {n} handles", flush=True)
+    tt.recompute_deps_batch([hs[i % 5] for i in range(n)])
+    for h in hs:
+        assert torch.equal(h.deps_view().view(want.shape), want), name
+        h.close()

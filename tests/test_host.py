@@ -659,6 +659,21 @@ def test_batches_of_graphs_with_many_list_entries(lib, every):
     lib.free(h)
 
 
+# 256 MiB of rows are 74 graphs of 60 x 200 ops and 29 of 600 x 50, 600 MiB 174 and 76; the latter are 1 MiB per level
+@pytest.mark.parametrize("levels,width,every,past,stored", [(60, 200, 1 << 30, 74, 174), (60, 200, 9, 174, 174), (600, 50, 1 << 30, 76, 76)])
+def test_batches_whose_rows_go_past_the_caches(lib, levels, width, every, past, stored):
+    """Rows beyond what the Infinity Cache holds are stored past the caches where lists come from memory or a level has at most a MiB of them."""
+    d = lists_at(levels, width, every, 1, 2048)
+    h = lib.build(d)[1]
+    for n in (73, 74, 75, 76, 77, 174, 175):
+        lib.host_forget_launches()
+        assert lib.tictac_dag_recompute_deps_batch((ctypes.c_void_p * n)(*[h] * n), I32(n), None) == 0, lib.error()
+        kernel = [k for k in lib.kernels() if "propagate" in k][0]
+        want = "propagate_levels_q_storedILi4ELb1E" if n <= past else "propagate_levels_q_storedILi4ELb0E" if n <= stored else "propagate_levels_q_batchILi4E"
+        assert want in kernel, (n, kernel)
+    lib.free(h)
+
+
 @pytest.mark.parametrize("name", list(BATCHES))
 def test_which_kernel_takes_several_graphs(lib, name):
     """Two waves more store the rows of graphs with up to 224 slots per level, up to 600 MiB of rows; beyond, and of graphs with wider
