@@ -651,23 +651,28 @@ struct QuadParams {
 // The rows of level l go to memory while level l + 1 is computed: by kStoreThreads threads, N stores each, of which those of levels up to
 // l - 6 have been completed when level l + 2 begins (a list reads a row from memory eight levels later or more).
 //   THROUGH: past the caches (kThrough).  What it gives comes from the hint of no reuse (nt): rows then stay in the Infinity Cache from pass to pass
-// instead of making room for the next, so a later pass over the same handles finds part of them there; a first one does not, and where rows are formed
-// faster than memory takes these stores (some 1.5 TB/s) both wait for them.  Us, first pass on three sets of handles and later ones, the computing waves
-// storing, stores through the caches, past them:
-//   2, 4 graphs of stress (53 MB of rows each)                         first 318, 327; 306, 313; 305, 320        later 314, 324; 299, 312; 303, 308
-//   8, 11 of stress (427, 583 MB; 0.92, 1.25 MB per level)             363, 406; 350, 392; 382, 436              352, 401; 339, 388; 310, 321
-//   32 of 500 x 64 ops, 2 048 recvs (279 MB; 0.62)                     278; 262; 273                             273; 256; 235
-//   32 of 200 x 200 and 2 048 (344 MB; 1.76)                           218; 212; 238                             207; 200; 197
-//   60 of 120 x 200 and 2 048 (400 MB; 3.5)                            223; 217; 257                             200; 194; 225
-//   30 of 200 x 100 and 4 096, lists from memory (370 MB; 2.0)         474; 466; 472                             465; 462; 400
-// Past the caches against the computing waves, first and later, by MB per level: 0.6 to 1.0 0.95 to 1.03 and 0.85 to 0.93 (8 graphs of stress 1.05 and 0.88); 1.15 to 2
-// 0.92 to 1.09 and 0.72 to 1.13; 2.2 to 3.5 0.93 to 1.15 and 0.90 to 1.17; through them never more than 1.02.  So past them go rows that the cache holds, and
-// others where lists from memory or at most a MiB per level leave the stores time.
+// instead of making room for the next, so a later pass over the same handles finds part of them there (a first one does not), and halves of lines from two
+// L2s need not be merged.  Where rows are formed faster than memory takes these stores, all passes wait for them.  Us, first pass on three
+// sets of handles and later ones, the computing waves storing, stores through the caches, past them:
+//   2, 4 graphs of stress (53 MB of rows each)                     first 318, 327; 306, 313; 305, 320        later 314, 324; 299, 312; 303, 308
+//   8, 11 of stress (427, 583 MB, 64 and 88 workgroups)            363, 406; 350, 392; 382, 436              352, 401; 339, 388; 310, 321
+//   32 of 500 x 64 ops, 2 048 recvs (279 MB, 128)                  278; 262; 273                             273; 256; 235
+//   30 of 200 x 100 and 4 096, lists from memory (370 MB, 240)     474; 466; 472                             465; 462; 400
+//   48 of 200 x 200 and 2 048 (517 MB, 192)                        231; 226; 252                             206; 197; 237
+//   60 of 120 x 200 and 2 048 (400 MB, 240)                        223; 217; 257                             200; 194; 225
+// Past the caches against the computing waves, 40 drawn batches of 256 to 600 MiB: first 0.91 to 1.08, later 0.66 to 0.94 (through them 0.94 to 1.03 and 0.95 to
+// 0.99).  What loses (first 1.0 to 1.15, later 0.98 to 1.17) are rows that the Infinity Cache does not hold, formed at more than 1.5 TB/s by many workgroups
+// whose halves of lines meet in one L2 (a number that is a multiple of 8): forms_fast.  Those go through the caches.
 // Above kStoredMost the computing waves store: 12 to 14 graphs of stress 390, 413, 412 and past the caches 393, 400, 430; 16 and 32 432, 568 and 477, 642.
 typedef int tt_row16 __attribute__((ext_vector_type(4)));
 constexpr int kStoreThreads = 128;
 constexpr int kThrough = 18;                // sc1 (to memory at once) and nt
-constexpr size_t kThroughMost = (size_t)256 << 20, kThroughPerLevel = (size_t)1 << 20, kStoredMost = (size_t)600 << 20;
+constexpr size_t kThroughMost = (size_t)256 << 20, kStoredMost = (size_t)600 << 20;
+// A level takes 0.62 us and 0.068 more for every entry of a list in LDS (1.0 us with 5.6 on average, 2.1 with 22).
+static bool forms_fast(size_t rows, int n_levels, int entries, int n_blocks)
+{
+    return n_blocks >= 120 && n_blocks % 8 == 0 && (double)rows > 1.5e6 * (0.62 * n_levels + 0.068 * entries);
+}
 // Where the lists of nodes that fit no record name rows that have left the ring, those come from memory then, not from the L2.  Four graphs, us, the
 // computing waves storing and this, by rows from memory per hundred nodes:
 //   3.2 to 25    300 x 60 ops, 2 048 recvs  1 109 and 1 203, 1 582 and 1 749;  200 x 100, 1 000  907 and 1 043, 1 303 and 1 509;  64 x 200, 1 024  199 and 209
@@ -1038,7 +1043,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
     std::vector<QuadParams> lp(G);
     std::vector<ExpandParams> ep(G);
     size_t lds0 = 0;
-    int32_t most_copied = 0, n_levels = 0;
+    int32_t most_copied = 0;
     bool few_far = true, in_lds = true;
     for (int g = 0; g < G; ++g) {
         size_t lds = 0;
@@ -1048,7 +1053,6 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
             return hipErrorNotSupported;
         few_far = few_far && ds[g]->q_far <= ds[g]->M / kNodesPerFar;
         in_lds = in_lds && lp[g].lfovf_lds == ds[g]->qfovf_len;
-        n_levels = std::max(n_levels, lp[g].n_levels);
         ep[g] = ExpandParams{ds[g]->n_q_copied, ds[g]->W, ds[g]->d_q_copied, ds[g]->d_dep};
         most_copied = std::max(most_copied, ds[g]->n_q_copied);
     }
@@ -1069,7 +1073,7 @@ static hipError_t launch_quad_batch(Dag *const *ds, int G, void *staging, hipStr
         threads += kStoreThreads;
         lds0 += (size_t)2 * d0.k1_q_threads / 4 * sizeof(int32_t);
     }
-    const bool through = rows <= kThroughMost || !in_lds || rows <= kThroughPerLevel * n_levels;
+    const bool through = rows <= kThroughMost || !in_lds || !forms_fast(rows, lp[0].n_levels, ds[0]->qfovf_len, blocks_per * G);
     void (*const kernel)(const QuadParams *, int) =
         !stored ? propagate_levels_q_batch<QC> : through ? propagate_levels_q_stored<QC, true> : propagate_levels_q_stored<QC, false>;
     if (lds0 > 48 * 1024) {

@@ -156,11 +156,11 @@ def test_several_graphs_by_both_kernels(tt, name):  # noqa: F811
 
 @pytest.mark.parametrize("name", [n for n in BATCHES if "listed" not in n])
 def test_several_graphs_beyond_the_infinity_cache(tt, name):  # noqa: F811
-    """Batches just above 256 MiB of rows, whose rows go through the caches unless lists come from memory."""
+    """Batches just above 256 MiB of rows, formed by a multiple of eight workgroups: through the caches unless lists take longer."""
     d, _ = BATCHES[name]()
     want = torch.from_numpy(oracle.find_dependencies(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids).view(np.int64)).cuda()
     hs = [tt.build_deps(d.n_ops, d.row_ptr, d.col_idx, d.recv_ids) for _ in range(5)]
-    n = (256 << 20) // (want.numel() * 8) + 1
+    n = ((256 << 20) // (want.numel() * 8) // 8 + 1) * 8
     for h in hs:
         h.deps_view().fill_(-1)
     print(f"[batch] {name}: {n} handles", flush=True)

@@ -659,18 +659,21 @@ def test_batches_of_graphs_with_many_list_entries(lib, every):
     lib.free(h)
 
 
-# 256 MiB of rows are 74 graphs of 60 x 200 ops and 29 of 600 x 50, 600 MiB 174 and 76; the latter are 1 MiB per level
-@pytest.mark.parametrize("levels,width,every,past,stored", [(60, 200, 1 << 30, 74, 174), (60, 200, 9, 174, 174), (600, 50, 1 << 30, 76, 76)])
-def test_batches_whose_rows_go_past_the_caches(lib, levels, width, every, past, stored):
-    """Rows beyond what the Infinity Cache holds are stored past the caches where lists come from memory or a level has at most a MiB of them."""
+# four workgroups per graph.  60 x 200 ops: 256 MiB are 74 graphs, 600 MiB 174;  600 x 50: 1.5 TB/s are 68 graphs, 600 MiB 76
+@pytest.mark.parametrize("levels,width,every,through", [(60, 200, 1 << 30, (76, 78, 174)), (60, 200, 9, ()), (600, 50, 1 << 30, (72, 74, 76))])
+def test_batches_whose_rows_go_through_the_caches(lib, levels, width, every, through):
+    """Rows beyond what the Infinity Cache holds are stored through the caches where many workgroups, a multiple of eight, form them fast; past the
+    caches where lists come from memory."""
     d = lists_at(levels, width, every, 1, 2048)
     h = lib.build(d)[1]
-    for n in (73, 74, 75, 76, 77, 174, 175):
+    most = (600 << 20) // (d.n_ops * 32 * 8)
+    for n in (30, 64, 72, 73, 74, 75, 76, 77, 78, 79, 174, 175):
         lib.host_forget_launches()
         assert lib.tictac_dag_recompute_deps_batch((ctypes.c_void_p * n)(*[h] * n), I32(n), None) == 0, lib.error()
         kernel = [k for k in lib.kernels() if "propagate" in k][0]
-        want = "propagate_levels_q_storedILi4ELb1E" if n <= past else "propagate_levels_q_storedILi4ELb0E" if n <= stored else "propagate_levels_q_batchILi4E"
-        assert want in kernel, (n, kernel)
+        want = "stored<4, false>" if n in through else "stored<4, true>" if n <= most else "batch<4>"
+        got = kernel.replace("ILi4ELb1E", "<4, true>").replace("ILi4ELb0E", "<4, false>").replace("ILi4E", "<4>")
+        assert "propagate_levels_q_" + want in got, (n, kernel)
     lib.free(h)
 
 
