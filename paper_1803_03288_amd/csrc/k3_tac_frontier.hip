@@ -19,8 +19,9 @@
 //   A round is a chain of 2.3 goes at up to sixteen classes each.  4 096 samples of stress, cycles per round and wave, sixteen waves
 // to a compute unit (all but a tenth of it also while a wave is by itself): the rows of the classes 3 500, the states of their inputs 2 600,
 // putting down those that point 1 400, their outputs' counters and the next classes 3 600, and, when all is done, times and P of what points 4 300;
-// the selection before 2 800, the frontier 700.  48 GB are fetched, nearly all of it for the times: 100 000 of them per
-// sample come a line each, since a line's are asked for at rounds far apart.  46.1 -> 38.6 ms by the following, each by itself 3 to 8 %: the counters
+// the selection before 2 800, the frontier 700.  48 GB are fetched: 16 GB of them for the times (with all times read
+// from 512 columns 32 GB are left, and the launch takes 38.8 ms instead of 39.1), the rest for what the L2 does not hold of the states and for the
+// rows and counters of the classes.  46.1 -> 38.6 ms by the following, each by itself 3 to 8 %: the counters
 // in LDS (a trip to the L2 per go; 25.8 GB written -> 8.6); a class's row in one request, sixteen bytes to a lane, with eight inputs, so
 // that more than four are no further trip; the sums of the iteration 64 steps at a time, over the lanes; loads and LDS operations by all lanes
 // instead of behind branches (640 vector and 370 scalar instructions a round, 800 and 560 before).  Not faster: times
